@@ -1,17 +1,38 @@
 // Sampling acceptance of a verified draft tree (speculative sampling with several candidates
 // per position), in exact fixed-point integers so that every decision is reproducible.
 //
-// One workgroup per sequence walks the tree from the root.  At a node, the children are tried in
+// The tree is walked from the root.  At a node, the children are tried in
 // index order: child with token x is accepted iff  u * q_x * S(p) < 2^32 * p_x * S(q)  (p, q:
 // fix(.) = floor(. * 2^30) of the target's / the draft's distribution after the node, S = sum);
 // a rejection replaces p by the residual  r_v = max(p_v S(q) - q_v S(p), 0)  rescaled to 2^30
-// (r_v / max(S(r) >> 30, 1), kept in the caller's workspace) and removes x from q.  When no child
+// (r_v / max(S(r) >> 30, 1)) and removes x from q.  When no child
 // is accepted the step's last token is the smallest v with p_0 + .. + p_v > (u_bonus S(p)) >> 32.
 // Sums are integer sums, so they do not depend on the order in which the lanes add them up.
 //
 // Rejected tokens need no mask over q in the vocabulary passes: after its rejection round a token
 // has p_x = 0 (rejection means q_x S(p) > p_x S(q)), so its residual is 0 whatever q_x is; only
 // S(q) and the single look-ups of q_x honour the removals.
+//
+// Decomposition.  A node needs one pass over its two rows and every rejection two more (the
+// residual's sum, then the rescaled residual and its sum), each depending on the sums of the one
+// before.  One workgroup per sequence would read 1.2 MB per pass through one CU's memory path on 16
+// of 256 CUs (5.3 ms for 16 sequences of 60 nodes over 152064 tokens, measured in that form).  Here
+// the vocabulary of a sequence is dealt to wavefronts, 2560 consecutive tokens each, which read their
+// range of a node's rows once and keep it in registers (40 values of p and of q per lane), so that a
+// rejection touches no vocabulary in memory; what crosses wavefronts are the sums.  Every wavefront
+// keeps p_x and q_x of the node's children in its lanes, updates them like any other value, and takes
+// every decision itself: no barrier anywhere.  16 sequences of 60 nodes over 152064 tokens: 81 us.
+// What bounds it is the chain of the sequence with the most rejections (ten at the root: 73 us): per
+// rejection two exchanges of 2 us each and 2.5 us of 64-bit integer work, per node visited 5 us for its
+// rows.  20 values per lane (twice the wavefronts, twice the partners per exchange) take 107 us;
+// recomputing the residual for the division instead of keeping its 80 registers 88 us; sums by LDS
+// permutes and workgroup barriers 95 us.
+//
+// Exchange: slot (k, w) holds wavefront w's partial sum of exchange k, bit 63 set; a slot is written
+// once per launch (they are cleared by a kernel before it) and polled by the sequence's other
+// wavefronts, the data being its own flag.  The workgroups of a sequence are consecutive in the
+// grid and none waits for another sequence's, so the waits end as soon as one sequence's workgroups
+// (15 for 152064 tokens; the chip holds 256) are resident beside whatever else runs.
 #include "hb_internal.h"
 
 namespace hb {
@@ -35,148 +56,274 @@ __device__ __forceinline__ bool mul_less(unsigned long long a, unsigned long lon
   return lh < rh || (lh == rh && ll < rl);
 }
 
-__device__ __forceinline__ unsigned long long block_sum(unsigned long long x, unsigned long long *red) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-  __syncthreads();  // red may still be read from the previous call
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
-  __syncthreads();
-  return red[0] + red[1] + red[2] + red[3];
+typedef unsigned long long u64;
+
+constexpr int kPer = 40;                       // vocabulary entries a lane keeps in registers
+constexpr int kRange = kPer * 64;              // ... a wavefront (2560)
+constexpr int kMaxWorkers = 128;               // wavefronts per sequence; beyond 327680 tokens the rest stays in memory
+constexpr int kExchanges = 192;                // at most 64 nodes visited and two exchanges for each of 63 children
+constexpr u64 kPosted = 1ull << 63;
+constexpr int kBufferFlags = 0x00027000;       // untyped 32-bit elements
+
+template <int CTRL>
+__device__ __forceinline__ u64 dpp_add(u64 x) {
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)x, CTRL, 0xf, 0xf, true);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(x >> 32), CTRL, 0xf, 0xf, true);
+  return x + (((u64)hi << 32) | lo);
+}
+// sum over the wavefront, in every lane: inside a row of 16 lanes by data-parallel moves, across
+// rows by the lane swaps (an LDS permute per step costs a memory round trip each)
+__device__ __forceinline__ u64 wave_sum(u64 x) {
+  x = dpp_add<0xB1>(x);   // lanes ^ 1
+  x = dpp_add<0x4E>(x);   // lanes ^ 2
+  x = dpp_add<0x141>(x);  // the other quad of eight
+  x = dpp_add<0x140>(x);  // the other eight of sixteen
+  typedef unsigned int swap2 __attribute__((ext_vector_type(2)));
+  swap2 lo = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)x, false, false);
+  swap2 hi = __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(x >> 32), false, false);
+  x = (((u64)hi[0] << 32) | lo[0]) + (((u64)hi[1] << 32) | lo[1]);
+  lo = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)x, false, false);
+  hi = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(x >> 32), false, false);
+  return (((u64)hi[0] << 32) | lo[0]) + (((u64)hi[1] << 32) | lo[1]);
+}
+
+// max(p S(q) - q S(p), 0); the sums of rows and of residuals are below 2^32
+__device__ __forceinline__ u64 residual(uint32_t p, uint32_t q, uint32_t sp, uint32_t sq) {
+  const u64 a = (u64)p * sq, b = (u64)q * sp;
+  return a > b ? a - b : 0ull;
+}
+
+// r / max(S(r) >> 30, 1) by a 32-bit reciprocal: with 2^k <= div < 2^(k+1) the estimate
+// ((r >> k) * floor(2^(32+k) / div)) >> 32 is at most two below the quotient (each factor loses less
+// than one unit), and the remainder says by how much.  r <= S(r) keeps r >> k below 2^32.
+struct Divisor {
+  uint32_t div, recip;
+  int k;
+};
+__device__ __forceinline__ Divisor make_divisor(u64 sr) {
+  Divisor d;
+  const u64 div = sr >> kFixBits;
+  d.div = div ? (uint32_t)div : 1u;
+  d.k = 31 - __builtin_clz(d.div);
+  const u64 r = (1ull << (32 + d.k)) / d.div;
+  d.recip = r > 0xffffffffull ? 0xffffffffu : (uint32_t)r;
+  return d;
+}
+__device__ __forceinline__ uint32_t divide(u64 r, const Divisor &d) {
+  uint32_t q = __umulhi((uint32_t)(r >> d.k), d.recip);
+  const u64 rem = r - (u64)q * d.div;
+  q += rem >= d.div ? 1u : 0u;
+  q += rem >= 2ull * d.div ? 1u : 0u;
+  return q;
+}
+
+__device__ __forceinline__ u64 *slots_of(uint32_t *work) { return (u64 *)(((uintptr_t)work + 7) & ~(uintptr_t)7); }
+
+__global__ __launch_bounds__(256) void accept_sample_clear_kernel(int V, int workers, uint32_t *__restrict__ work_all) {
+  u64 *slots = slots_of(work_all + (size_t)blockIdx.x * V);
+  for (int i = threadIdx.x; i < kExchanges * workers; i += 256) slots[i] = 0ull;
 }
 
 __global__ __launch_bounds__(kThreads) void tree_accept_sample_kernel(
-    int max_nodes, int V, const int32_t *__restrict__ node_offset, const int32_t *__restrict__ parent,
+    int max_nodes, int V, int workers, int groups, int chunk, const int32_t *__restrict__ node_offset, const int32_t *__restrict__ parent,
     const int32_t *__restrict__ draft_ids, const float *__restrict__ p_target, const float *__restrict__ q_draft,
     const uint32_t *__restrict__ u_accept, const uint32_t *__restrict__ u_bonus, int max_path,
     int32_t *__restrict__ accept_len, int32_t *__restrict__ accept_path, int32_t *__restrict__ out_tokens,
     int32_t *__restrict__ bonus_id, uint32_t *__restrict__ work_all) {
-  __shared__ int32_t spar[64], sdraft[64], spath[64], sremoved[64];
-  __shared__ unsigned long long red[4];
-  __shared__ unsigned long long chunk_sum[kThreads];
-  __shared__ int s_decision;
-  const int b = blockIdx.x;
-  const int tid = threadIdx.x;
+  const int b = (int)(blockIdx.x / (unsigned)groups);
+  const int w = __builtin_amdgcn_readfirstlane((int)(blockIdx.x % (unsigned)groups) * (kThreads / 64) + (int)(threadIdx.x >> 6));
+  if (w >= workers) return;
+  const int lane = threadIdx.x & 63;
   const int n0 = node_offset[b];
   int n = node_offset[b + 1] - n0;
   n = n < 0 ? 0 : (n > max_nodes ? max_nodes : n);
   int32_t *path_out = accept_path + (size_t)b * max_path;
   int32_t *tok_out = out_tokens + (size_t)b * max_path;
   if (n == 0) {  // nothing to verify: nothing is emitted
-    for (int j = tid; j < max_path; j += kThreads) { path_out[j] = -1; tok_out[j] = -1; }
-    if (tid == 0) { accept_len[b] = 0; bonus_id[b] = -1; }
+    if (w != 0) return;
+    for (int j = lane; j < max_path; j += 64) { path_out[j] = -1; tok_out[j] = -1; }
+    if (lane == 0) { accept_len[b] = 0; bonus_id[b] = -1; }
     return;
   }
-  if (tid < 64) {
-    int par = -1, did = 0;
-    if (tid < n) {
-      par = parent[n0 + tid];
-      if (par >= tid || par < -1 || tid == 0) par = -1;  // malformed: never anybody's child
-      did = draft_ids[n0 + tid];
-    }
-    spar[tid] = par;
-    sdraft[tid] = did;
+  // the tree, one node per lane
+  int par = -1, did = 0;
+  uint32_t u_mine = 0;
+  if (lane < n) {
+    par = parent[n0 + lane];
+    if (par >= lane || par < -1 || lane == 0) par = -1;  // malformed: never anybody's child
+    did = draft_ids[n0 + lane];
+    u_mine = u_accept[n0 + lane];
   }
-  __syncthreads();
-  uint32_t *work = work_all + (size_t)b * V;
+  u64 *slots = slots_of(work_all + (size_t)b * V);
+  const int v_begin = w * chunk, v_end = min(V, v_begin + chunk);  // this wavefront's range
+  const int r_end = min(v_end, v_begin + kRange);                  // the part in registers
+  // what lies beyond the registers keeps its residual behind the slots
+  uint32_t *work = (uint32_t *)(slots + kExchanges * kMaxWorkers) + (long long)w * (chunk - kRange) - v_begin - kRange;
+  int k = 0;
 
-  int cur = 0, len = 1, bonus = -1;
-  if (tid == 0) spath[0] = 0;
+  // Sum of x over the sequence's wavefronts; lane i keeps the shares of wavefronts i and i + 64.
+  u64 share0 = 0, share1 = 0;
+  auto exchange = [&](u64 x) -> u64 {
+    if (workers == 1) {
+      share0 = lane == 0 ? x : 0ull;
+      return x;
+    }
+    u64 *slot = slots + k * workers;
+    ++k;
+    if (lane == 0) __hip_atomic_store(slot + w, x | kPosted, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int i0 = min(lane, workers - 1), i1 = min(lane + 64, workers - 1);
+    u64 y0, y1;
+    do {
+      y0 = __hip_atomic_load(slot + i0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      y1 = workers > 64 ? __hip_atomic_load(slot + i1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : kPosted;
+    } while (!__all((y0 & y1 & kPosted) != 0));
+    share0 = lane < workers ? y0 & ~kPosted : 0ull;
+    share1 = lane + 64 < workers ? y1 & ~kPosted : 0ull;
+    return wave_sum(share0 + share1);
+  };
+
+  int cur = 0, len = 1;
+  int path = 0;  // lane i: node i of the path
+  uint32_t sp = 0;
+  uint32_t sp0 = 0, sp1 = 0;  // shares of S(p)
+  uint32_t p[kPer], q[kPer];
+  const float *prow, *qrow;
+  bool in_work = false;  // beyond the registers: p is the target's row (false) or the residual in the workspace
 #pragma unroll 1
   for (;;) {
-    const float *prow = p_target + (size_t)(n0 + cur) * V;
-    const float *qrow = q_draft + (size_t)(n0 + cur) * V;
-    bool in_work = false;  // current p: the target's row (false) or the residual in the workspace
-    int n_removed = 0;
-    unsigned long long sp = 0, sq = 0;
-    for (int v = tid; v < V; v += kThreads) { sp += fix_prob(prow[v]); sq += fix_prob(qrow[v]); }
-    sp = block_sum(sp, red);
-    sq = block_sum(sq, red);
+    prow = p_target + (size_t)(n0 + cur) * V;
+    qrow = q_draft + (size_t)(n0 + cur) * V;
+    in_work = false;
+    // lanes that hold a child of the node: p and q of its token
+    const bool child = par == cur && len < max_path;
+    const int tok = child && did >= 0 && did < V ? did : -1;
+    float pf = 0.f, qf = 0.f;
+    if (tok >= 0) {
+      pf = prow[tok];
+      qf = qrow[tok];
+    }
+    // The range's loads are all in flight before the first is used; buffer loads return zero beyond
+    // the range and cost one address register for all of them.
+    u64 both = 0;  // S(q) in the low word, S(p) in the high one: rows sum to less than 2
+    {
+      const int bytes = (r_end > v_begin ? r_end - v_begin : 0) * 4;
+      const auto pr = __builtin_amdgcn_make_buffer_rsrc((void *)(prow + v_begin), 0, bytes, kBufferFlags);
+      const auto qr = __builtin_amdgcn_make_buffer_rsrc((void *)(qrow + v_begin), 0, bytes, kBufferFlags);
+#pragma unroll
+      for (int j = 0; j < kPer; ++j) {
+        p[j] = __builtin_amdgcn_raw_buffer_load_b32(pr, lane * 4, j * 256, 0);
+        q[j] = __builtin_amdgcn_raw_buffer_load_b32(qr, lane * 4, j * 256, 0);
+      }
+      uint32_t a = 0, c = 0;
+#pragma unroll
+      for (int j = 0; j < kPer; ++j) {
+        p[j] = fix_prob(__uint_as_float(p[j]));
+        q[j] = fix_prob(__uint_as_float(q[j]));
+        a += p[j];
+        c += q[j];
+      }
+      for (int v = v_begin + kRange + lane; v < v_end; v += 64) { a += fix_prob(prow[v]); c += fix_prob(qrow[v]); }
+      both = ((u64)a << 32) | c;
+    }
+    uint32_t px = fix_prob(pf), qx = fix_prob(qf), q_left = qx;  // q_left: 0 once the token has been removed from q
+    both = exchange(wave_sum(both));
+    sp = (uint32_t)(both >> 32);
+    uint32_t sq = (uint32_t)both;
+    sp0 = (uint32_t)(share0 >> 32);
+    sp1 = (uint32_t)(share1 >> 32);
     int taken = -1;
-    if (len < max_path) {
+    u64 left = __ballot(child);
 #pragma unroll 1
-      for (int c = cur + 1; c < n; ++c) {
-        if (spar[c] != cur) continue;  // uniform
-        int x = sdraft[c];
-        const bool x_ok = x >= 0 && x < V;
-        x = x_ok ? x : 0;
-        if (tid == 0) {
-          unsigned long long px = x_ok ? (in_work ? work[x] : fix_prob(prow[x])) : 0ull;
-          unsigned long long qx = x_ok ? fix_prob(qrow[x]) : 0ull;
-          for (int i = 0; i < n_removed; ++i) qx = sremoved[i] == x ? 0ull : qx;
-          const unsigned long long u = u_accept[n0 + c];
-          // u q_x S(p) < 2^32 p_x S(q); u q_x < 2^63 and p_x S(q) < 2^62 fit 64 bits
-          s_decision = mul_less(u * qx, sp, px * sq, 1ull << 32) ? 1 : 0;
-          chunk_sum[0] = qx;
-        }
-        __syncthreads();
-        const bool accept = s_decision != 0;
-        const unsigned long long qx = chunk_sum[0];
-        __syncthreads();
-        if (accept) { taken = c; break; }
-        // residual: first its sum, then the rescaled values (and their sum) into the workspace
-        unsigned long long sr = 0;
-        for (int v = tid; v < V; v += kThreads) {
-          const unsigned long long pv = in_work ? work[v] : fix_prob(prow[v]);
-          const unsigned long long a = pv * sq, bq = (unsigned long long)fix_prob(qrow[v]) * sp;
-          sr += a > bq ? a - bq : 0ull;
-        }
-        sr = block_sum(sr, red);
-        if (sr != 0) {
-          unsigned long long div = sr >> kFixBits;
-          div = div ? div : 1ull;
-          unsigned long long snew = 0;
-          for (int v = tid; v < V; v += kThreads) {
-            const unsigned long long pv = in_work ? work[v] : fix_prob(prow[v]);
-            const unsigned long long a = pv * sq, bq = (unsigned long long)fix_prob(qrow[v]) * sp;
-            const unsigned long long r = (a > bq ? a - bq : 0ull) / div;
-            work[v] = (uint32_t)r;
-            snew += r;
-          }
-          sp = block_sum(snew, red);
-          in_work = true;
-        }
-        if (tid == 0 && x_ok) sremoved[n_removed] = x;
-        n_removed += x_ok ? 1 : 0;
-        sq -= qx;
-        __syncthreads();
+    while (left) {
+      const int c = __builtin_amdgcn_readfirstlane(__builtin_ctzll(left));
+      left &= left - 1;
+      const uint32_t cp = __builtin_amdgcn_readlane(px, c), cq = __builtin_amdgcn_readlane(q_left, c);
+      const uint32_t u = __builtin_amdgcn_readlane(u_mine, c);
+      // u q_x S(p) < 2^32 p_x S(q)
+      if (mul_less((u64)u * cq, sp, (u64)cp * sq, 1ull << 32)) { taken = c; break; }
+      // the residual's sum, then the rescaled residual and its sum
+      u64 sr = 0;
+#pragma unroll
+      for (int j = 0; j < kPer; ++j) {
+        
+        sr += residual(p[j], q[j], sp, sq);
       }
-    }
-    if (taken < 0) {
-      // last token: inverse CDF of the current p over contiguous chunks, one per thread
-      if (sp != 0) {
-        const unsigned long long t = ((unsigned long long)u_bonus[b] * sp) >> 32;  // S(p) < 2^32
-        const int chunk = (V + kThreads - 1) / kThreads;
-        const int v0 = tid * chunk, v1 = min(V, v0 + chunk);
-        unsigned long long cs = 0;
-        for (int v = v0; v < v1; ++v) cs += in_work ? work[v] : fix_prob(prow[v]);
-        __syncthreads();
-        chunk_sum[tid] = cs;
-        __syncthreads();
-        unsigned long long before = 0;
-        for (int i = 0; i < tid; ++i) before += chunk_sum[i];
-        if (before <= t && t < before + cs) {  // exactly one thread
-          unsigned long long acc = before;
-          for (int v = v0; v < v1; ++v) {
-            acc += in_work ? work[v] : fix_prob(prow[v]);
-            if (acc > t) { s_decision = v; break; }
-          }
+      for (int v = v_begin + kRange + lane; v < v_end; v += 64)
+        sr += residual(in_work ? work[v] : fix_prob(prow[v]), fix_prob(qrow[v]), sp, sq);
+      sr = exchange(wave_sum(sr));
+      if (sr != 0) {
+        const Divisor d = make_divisor(sr);
+        u64 snew = 0;
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+          p[j] = divide(residual(p[j], q[j], sp, sq), d);
+          snew += p[j];
         }
-        __syncthreads();
-        bonus = s_decision;
+        for (int v = v_begin + kRange + lane; v < v_end; v += 64) {
+          const uint32_t x = divide(residual(in_work ? work[v] : fix_prob(prow[v]), fix_prob(qrow[v]), sp, sq), d);
+          work[v] = x;
+          snew += x;
+        }
+        px = divide(residual(px, qx, sp, sq), d);
+        in_work = true;
+        sp = (uint32_t)exchange(wave_sum(snew));
+        sp0 = (uint32_t)share0;
+        sp1 = (uint32_t)share1;
       }
-      break;
+      sq -= cq;
+      const int cx = __builtin_amdgcn_readlane(tok, c);
+      if (tok == cx) q_left = 0;
     }
-    if (tid == 0) spath[len] = taken;
+    if (taken < 0) break;
+    if (lane == len) path = taken;
     ++len;
     cur = taken;
-    __syncthreads();
   }
-  __syncthreads();
-  for (int j = tid; j < max_path; j += kThreads) {
-    path_out[j] = j < len ? spath[j] : -1;
-    tok_out[j] = j + 1 < len ? sdraft[spath[j + 1]] : (j + 1 == len ? bonus : -1);
+
+  // Last token: the wavefront whose share of p holds the bonus uniform's place finds it, and writes
+  // the step's results; wavefront 0 does when p is all zero.
+  int bonus = -1;
+  if (sp == 0) {
+    if (w != 0) return;
+  } else {
+    u64 t = ((u64)u_bonus[b] * sp) >> 32;
+    const u64 before = wave_sum((lane < w ? (u64)sp0 : 0ull) + (lane + 64 < w ? (u64)sp1 : 0ull));
+    const u64 mine = wave_sum((lane == w ? (u64)sp0 : 0ull) + (lane + 64 == w ? (u64)sp1 : 0ull));
+    if (t < before || t - before >= mine) return;
+    t -= before;
+    // the row of 64 consecutive tokens that holds the place, then the token
+    u64 acc = 0;
+    auto look = [&](uint32_t x, int v) {
+      const u64 row = wave_sum(x);
+      if (bonus < 0 && t < acc + row) {
+        u64 upto = x;  // inclusive prefix over the lanes
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+          const u64 y = __shfl_up(upto, off, 64);
+          if (lane >= off) upto += y;
+        }
+        bonus = v + __builtin_ctzll(__ballot(acc + upto > t));
+      }
+      acc += row;
+    };
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) look(p[j], v_begin + j * 64);
+    for (int v = v_begin + kRange; v < v_end; v += 64) {
+      const int at = v + lane;
+      look(at < v_end ? (in_work ? work[at] : fix_prob(prow[at])) : 0u, v);
+    }
   }
-  if (tid == 0) { accept_len[b] = len; bonus_id[b] = bonus; }
+  for (int j0 = 0; j0 < max_path; j0 += 64) {
+    const int j = j0 + lane;
+    const int node = j < len ? path : -1;
+    const int next = j0 == 0 ? __shfl(path, lane < 63 ? lane + 1 : lane, 64) : 0;
+    const int next_tok = __shfl(did, next, 64);
+    if (j < max_path) {
+      path_out[j] = j0 == 0 ? node : -1;
+      tok_out[j] = j0 == 0 && j + 1 < len ? next_tok : (j + 1 == len ? bonus : -1);
+    }
+  }
+  if (lane == 0) { accept_len[b] = len; bonus_id[b] = bonus; }
 }
 
 }  // namespace
@@ -186,9 +333,15 @@ hipError_t launch_tree_accept_sample(int32_t B, int32_t max_nodes, int32_t V, co
                                      const float *q_draft, const uint32_t *u_accept, const uint32_t *u_bonus,
                                      int32_t max_path, int32_t *accept_len, int32_t *accept_path,
                                      int32_t *out_tokens, int32_t *bonus_id, uint32_t *work, hipStream_t s) {
-  tree_accept_sample_kernel<<<B, kThreads, 0, s>>>(max_nodes, V, node_offset, parent, draft_ids, p_target, q_draft,
-                                                   u_accept, u_bonus, max_path, accept_len, accept_path, out_tokens,
-                                                   bonus_id, work);
+  // as few wavefronts as hold the vocabulary in registers: fewer partners per exchange
+  int workers = (int)(((int64_t)V + kRange - 1) / kRange);
+  if (workers > kMaxWorkers) workers = kMaxWorkers;
+  const int chunk = workers < kMaxWorkers ? kRange : (int)(((int64_t)V + workers - 1) / workers);
+  const int groups = (workers + kThreads / 64 - 1) / (kThreads / 64);
+  if (workers > 1) accept_sample_clear_kernel<<<(unsigned)B, 256, 0, s>>>(V, workers, work);
+  tree_accept_sample_kernel<<<(unsigned)B * (unsigned)groups, kThreads, 0, s>>>(
+      max_nodes, V, workers, groups, chunk, node_offset, parent, draft_ids, p_target, q_draft, u_accept, u_bonus, max_path,
+      accept_len, accept_path, out_tokens, bonus_id, work);
   return hipGetLastError();
 }
 

@@ -122,3 +122,17 @@ def test_full_vocabulary_chains(step):
     draft = _draw_drafts(rng, trees, Q, V)
     ref = _both(step, trees, draft, P, Q, _u32(rng, 8 * B), _u32(rng, B), 8)
     assert 1.0 < ref[0].mean() < 8.0
+
+
+@pytest.mark.parametrize("V", [2559, 2561, 10240, 64 * 2560, 64 * 2560 + 1, 128 * 2560 + 77])
+def test_vocabularies_around_the_shares_of_the_wavefronts(step, V):
+    """One and two wavefronts, a whole workgroup, 64 and 65 partners of an exchange, and a vocabulary
+    whose end does not fit the registers; several rejections at the root, some accepted children."""
+    rng = np.random.default_rng(V)
+    trees = [np.array([-1] + [0] * 6 + [1, 2, 3, 7], dtype=np.int32), W.chain_tree(3), W.chain_tree(1)]
+    total = sum(len(t) for t in trees)
+    logits = rng.standard_normal((total, V)) * 2.0
+    P = np.exp(logits); P /= P.sum(1, keepdims=True)
+    Q = np.exp(0.7 * logits + rng.standard_normal((total, V))); Q /= Q.sum(1, keepdims=True)
+    for trial in range(3):
+        _both(step, trees, _draw_drafts(rng, trees, Q, V), P, Q, _u32(rng, total), _u32(rng, 3), 4)

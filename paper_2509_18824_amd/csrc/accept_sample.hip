@@ -30,9 +30,16 @@
 //
 // Exchange: slot (k, w) holds wavefront w's partial sum of exchange k, bit 63 set; a slot is written
 // once per launch (they are cleared by a kernel before it) and polled by the sequence's other
-// wavefronts, the data being its own flag.  The workgroups of a sequence are consecutive in the
-// grid and none waits for another sequence's, so the waits end as soon as one sequence's workgroups
-// (15 for 152064 tokens; the chip holds 256) are resident beside whatever else runs.
+// wavefronts, the data being its own flag.
+//
+// The waits have to end also when several launches on different streams compete for the chip, which
+// holds one of these workgroups per CU.  Up to 64 workgroups (8 per XCD) a few launches always fit
+// together.  Larger launches draw: a workgroup takes its place (sequence, share) from a counter when
+// it starts, so the places held are always the lowest and only the last sequence of a launch that has
+// begun can be waiting for workgroups that have not, at most 31 CUs of 256.  By the workgroup's index
+// two launches could each fill one XCD and wait there for the other's.  The counter costs 6 to 14 us
+// of 80 for 240 workgroups (one address), nothing measurable for 60; the workgroups of a sequence on
+// one XCD instead cost 18 us.
 #include "hb_internal.h"
 
 namespace hb {
@@ -61,6 +68,7 @@ typedef unsigned long long u64;
 constexpr int kPer = 40;                       // vocabulary entries a lane keeps in registers
 constexpr int kRange = kPer * 64;              // ... a wavefront (2560)
 constexpr int kMaxWorkers = 128;               // wavefronts per sequence; beyond 327680 tokens the rest stays in memory
+constexpr int kDrawAbove = 64;                 // workgroups of a launch
 constexpr int kExchanges = 192;                // at most 64 nodes visited and two exchanges for each of 63 children
 constexpr u64 kPosted = 1ull << 63;
 constexpr int kBufferFlags = 0x00027000;       // untyped 32-bit elements
@@ -121,17 +129,24 @@ __device__ __forceinline__ u64 *slots_of(uint32_t *work) { return (u64 *)(((uint
 
 __global__ __launch_bounds__(256) void accept_sample_clear_kernel(int V, int workers, uint32_t *__restrict__ work_all) {
   u64 *slots = slots_of(work_all + (size_t)blockIdx.x * V);
-  for (int i = threadIdx.x; i < kExchanges * workers; i += 256) slots[i] = 0ull;
+  for (int i = threadIdx.x; i < 1 + kExchanges * workers; i += 256) slots[i] = 0ull;
 }
 
 __global__ __launch_bounds__(kThreads) void tree_accept_sample_kernel(
-    int max_nodes, int V, int workers, int groups, int chunk, const int32_t *__restrict__ node_offset, const int32_t *__restrict__ parent,
+    int draw, int max_nodes, int V, int workers, int groups, int chunk, const int32_t *__restrict__ node_offset, const int32_t *__restrict__ parent,
     const int32_t *__restrict__ draft_ids, const float *__restrict__ p_target, const float *__restrict__ q_draft,
     const uint32_t *__restrict__ u_accept, const uint32_t *__restrict__ u_bonus, int max_path,
     int32_t *__restrict__ accept_len, int32_t *__restrict__ accept_path, int32_t *__restrict__ out_tokens,
     int32_t *__restrict__ bonus_id, uint32_t *__restrict__ work_all) {
-  const int b = (int)(blockIdx.x / (unsigned)groups);
-  const int w = __builtin_amdgcn_readfirstlane((int)(blockIdx.x % (unsigned)groups) * (kThreads / 64) + (int)(threadIdx.x >> 6));
+  __shared__ unsigned drawn;  // the counter is word 0 of the first sequence's slots
+  unsigned place = blockIdx.x;
+  if (draw) {
+    if (threadIdx.x == 0) drawn = atomicAdd((unsigned *)slots_of(work_all), 1u);
+    __syncthreads();
+    place = drawn;
+  }
+  const int b = __builtin_amdgcn_readfirstlane((int)(place / (unsigned)groups));
+  const int w = __builtin_amdgcn_readfirstlane((int)(place % (unsigned)groups) * (kThreads / 64) + (int)(threadIdx.x >> 6));
   if (w >= workers) return;
   const int lane = threadIdx.x & 63;
   const int n0 = node_offset[b];
@@ -154,7 +169,7 @@ __global__ __launch_bounds__(kThreads) void tree_accept_sample_kernel(
     did = draft_ids[n0 + lane];
     u_mine = u_accept[n0 + lane];
   }
-  u64 *slots = slots_of(work_all + (size_t)b * V);
+  u64 *slots = slots_of(work_all + (size_t)b * V) + 1;
   const int v_begin = w * chunk, v_end = min(V, v_begin + chunk);  // this wavefront's range
   const int r_end = min(v_end, v_begin + kRange);                  // the part in registers
   // what lies beyond the registers keeps its residual behind the slots
@@ -245,7 +260,6 @@ __global__ __launch_bounds__(kThreads) void tree_accept_sample_kernel(
       u64 sr = 0;
 #pragma unroll
       for (int j = 0; j < kPer; ++j) {
-        
         sr += residual(p[j], q[j], sp, sq);
       }
       for (int v = v_begin + kRange + lane; v < v_end; v += 64)
@@ -281,7 +295,8 @@ __global__ __launch_bounds__(kThreads) void tree_accept_sample_kernel(
   }
 
   // Last token: the wavefront whose share of p holds the bonus uniform's place finds it, and writes
-  // the step's results; wavefront 0 does when p is all zero.
+  // the step's results; wavefront 0 does when p is all zero, or when sums that overflow (rows far
+  // above 1) leave the place in nobody's share.
   int bonus = -1;
   if (sp == 0) {
     if (w != 0) return;
@@ -289,8 +304,9 @@ __global__ __launch_bounds__(kThreads) void tree_accept_sample_kernel(
     u64 t = ((u64)u_bonus[b] * sp) >> 32;
     const u64 before = wave_sum((lane < w ? (u64)sp0 : 0ull) + (lane + 64 < w ? (u64)sp1 : 0ull));
     const u64 mine = wave_sum((lane == w ? (u64)sp0 : 0ull) + (lane + 64 == w ? (u64)sp1 : 0ull));
-    if (t < before || t - before >= mine) return;
-    t -= before;
+    const bool nobody = t >= wave_sum((u64)sp0 + sp1);
+    if (nobody ? w != 0 : (t < before || t - before >= mine)) return;
+    t -= nobody ? 0 : before;
     // the row of 64 consecutive tokens that holds the place, then the token
     u64 acc = 0;
     auto look = [&](uint32_t x, int v) {
@@ -339,8 +355,9 @@ hipError_t launch_tree_accept_sample(int32_t B, int32_t max_nodes, int32_t V, co
   const int chunk = workers < kMaxWorkers ? kRange : (int)(((int64_t)V + workers - 1) / workers);
   const int groups = (workers + kThreads / 64 - 1) / (kThreads / 64);
   if (workers > 1) accept_sample_clear_kernel<<<(unsigned)B, 256, 0, s>>>(V, workers, work);
-  tree_accept_sample_kernel<<<(unsigned)B * (unsigned)groups, kThreads, 0, s>>>(
-      max_nodes, V, workers, groups, chunk, node_offset, parent, draft_ids, p_target, q_draft, u_accept, u_bonus, max_path,
+  const int64_t grid = (int64_t)B * groups;
+  tree_accept_sample_kernel<<<(unsigned)grid, kThreads, 0, s>>>(
+      workers > 1 && grid > kDrawAbove, max_nodes, V, workers, groups, chunk, node_offset, parent, draft_ids, p_target, q_draft, u_accept, u_bonus, max_path,
       accept_len, accept_path, out_tokens, bonus_id, work);
   return hipGetLastError();
 }

@@ -1,62 +1,131 @@
-// Scalar tree-verify attention: one wavefront per (node, query head, KV chunk), lanes spread
-// over the head dimension, fp32 arithmetic whatever the storage type.  It is the kernel for
-// fp32 inputs and for shapes the MFMA kernel does not take, and it defines the semantics the
-// fast kernel must match: keys are the prefix positions of the chunk, plus (chunk 0 only) the
-// tree nodes on the node's own root path.  Also holds the split-K merge kernel.
+// Scalar tree-verify attention: one workgroup per (node, query head, KV chunk), fp32 arithmetic
+// whatever the storage type.  It is the kernel for fp32 inputs and for shapes the MFMA kernel does
+// not take, and it defines the semantics the fast kernel must match: keys are the prefix positions
+// of the chunk, plus (chunk 0 only) the tree nodes on the node's own root path.  Also holds the
+// split-K merge kernel.
+//
+// What bounds it at the sizes it is used for is latency: memory round trips in a row and chains of
+// dependent instructions, not bytes.  The four wavefronts of a workgroup deal out blocks of 64 keys;
+// a block is a handful of round trips (page ids, K, the V rows 16 at a time) and one softmax update
+// whatever the number of keys in it.  4 nodes x 4 heads of 64 over 256 float32 positions: 12 us;
+// one wavefront that took the keys one by one, each with a sum across lanes and two exponentials,
+// 138 us.
 #include "hb_internal.h"
 
 namespace hb {
 
 namespace {
 
-constexpr int kMaxPerLane = 4;  // head_dim <= 256 = 64 lanes * 4
+constexpr int kThreads = 256;
+constexpr int kWaves = 4;
+constexpr int kRowsInFlight = 16;  // V rows requested before the first is used
 
+__device__ inline float wave_max(float x) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) x = fmaxf(x, __shfl_xor(x, off, 64));
+  return x;
+}
 __device__ inline float wave_sum(float x) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
   return x;
 }
 
-struct OnlineSoftmax {
-  float m, l;
-  float acc[kMaxPerLane];
-};
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-template <typename T>
-__device__ inline void absorb_key(OnlineSoftmax &st, const float (&qv)[kMaxPerLane], const T *krow,
-                                  const T *vrow, int D, int lane, float scale) {
-  float part = 0.f;
-  float vv[kMaxPerLane];
+// eight consecutive elements, 16-byte aligned (head_dim % 8 == 0, tensors 16-byte aligned)
+__device__ inline void load8(const float *p, float (&x)[8]) {
+  const f32x4 a = *reinterpret_cast<const f32x4 *>(p), b = *reinterpret_cast<const f32x4 *>(p + 4);
 #pragma unroll
-  for (int e = 0; e < kMaxPerLane; ++e) {
-    int d = lane + 64 * e;
-    float kd = 0.f;
-    vv[e] = 0.f;
-    if (d < D) {
-      kd = load_f32(krow + d);
-      vv[e] = load_f32(vrow + d);
-    }
-    // select, not multiply: a lane past D contributes exactly zero
-    part += (d < D) ? qv[e] * kd : 0.f;
+  for (int e = 0; e < 4; ++e) {
+    x[e] = a[e];
+    x[4 + e] = b[e];
   }
-  float s = wave_sum(part) * scale;
-  float m_new = fmaxf(st.m, s);
-  float corr = expf(st.m - m_new);  // exp(-inf) = 0 on the first key
-  float p = expf(s - m_new);
-  st.l = st.l * corr + p;
+}
+__device__ inline void load8(const bf16_t *p, float (&x)[8]) {
+  const u32x4 a = *reinterpret_cast<const u32x4 *>(p);
 #pragma unroll
-  for (int e = 0; e < kMaxPerLane; ++e) st.acc[e] = st.acc[e] * corr + p * vv[e];
-  st.m = m_new;
+  for (int e = 0; e < 4; ++e) {
+    x[2 * e] = __uint_as_float(a[e] << 16);
+    x[2 * e + 1] = __uint_as_float(a[e] & 0xffff0000u);
+  }
 }
 
-template <typename T>
-__global__ __launch_bounds__(64) void attn_scalar_kernel(
+template <int E>
+struct OnlineSoftmax {
+  float m, l;     // reference exponent; this lane's share of the sum
+  float acc[E];   // head dimensions lane, lane + 64, ...
+};
+
+// Up to 64 keys, one per lane: `live` marks the lanes that hold one, `off` is the key's offset in
+// k and v.  A lane takes the whole dot product of its key, so the block needs one maximum and no
+// sum across lanes; then the lanes spread over the head dimension and the V rows of the live keys
+// are added up, kRowsInFlight of them requested at a time.
+template <typename T, int E>
+__device__ inline void absorb_keys(OnlineSoftmax<E> &st, const float *q_lds, const T *k, const T *v, size_t off,
+                                   unsigned long long live, int D, int lane, float scale) {
+  if (live == 0) return;
+  const bool mine = (live >> lane) & 1;
+  float s = -__builtin_huge_valf();
+  if (mine) {
+    float part[4] = {0.f, 0.f, 0.f, 0.f};
+    const T *row = k + off;
+#pragma unroll 8
+    for (int d = 0; d < D; d += 8) {
+      float x[8];
+      load8(row + d, x);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) part[e & 3] = fmaf(q_lds[d + e], x[e], part[e & 3]);
+    }
+    s = ((part[0] + part[1]) + (part[2] + part[3])) * scale;
+  }
+  const float m_new = fmaxf(st.m, wave_max(s));
+  const float corr = expf(st.m - m_new);  // exp(-inf) = 0 on the first keys
+  const float p = mine ? expf(s - m_new) : 0.f;
+  st.l = st.l * corr + p;
+  st.m = m_new;
+#pragma unroll
+  for (int e = 0; e < E; ++e) st.acc[e] *= corr;
+  const uint32_t off_lo = (uint32_t)off, off_hi = (uint32_t)(off >> 32);
+  while (live) {
+    float w[kRowsInFlight], x[kRowsInFlight][E];
+#pragma unroll
+    for (int u = 0; u < kRowsInFlight; ++u) {
+      w[u] = 0.f;
+#pragma unroll
+      for (int e = 0; e < E; ++e) x[u][e] = 0.f;
+      if (live) {  // uniform
+        const int j = __builtin_amdgcn_readfirstlane(__builtin_ctzll(live));
+        live &= live - 1;
+        w[u] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(p), j));
+        const size_t o = (size_t)(uint32_t)__builtin_amdgcn_readlane(off_lo, j) |
+                         ((size_t)(uint32_t)__builtin_amdgcn_readlane(off_hi, j) << 32);
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+          if (lane + 64 * e < D) x[u][e] = load_f32(v + o + lane + 64 * e);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kRowsInFlight; ++u)
+#pragma unroll
+      for (int e = 0; e < E; ++e) st.acc[e] = fmaf(w[u], x[u][e], st.acc[e]);
+  }
+}
+
+// E: head dimensions per lane (D <= 64 E)
+template <typename T, int E>
+__global__ __launch_bounds__(kThreads) void attn_scalar_kernel(
     hb_attn_desc d, int splits, int chunk_tokens, const T *__restrict__ q, const T *__restrict__ k_tree,
     const T *__restrict__ v_tree, const T *__restrict__ k_pool, const T *__restrict__ v_pool,
     const int32_t *__restrict__ block_table, const int32_t *__restrict__ prefix_len,
     const int32_t *__restrict__ node_offset, const int32_t *__restrict__ parent, T *__restrict__ out,
     float *__restrict__ lse, float *__restrict__ part_o, float *__restrict__ part_ml) {
-  const int lane = threadIdx.x;
+  __shared__ float q_lds[64 * E];
+  __shared__ float acc_lds[kWaves][64 * E];
+  __shared__ float ml_lds[kWaves][2];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int row = blockIdx.x;  // node * Hq + head
   const int c = blockIdx.y;
   const int node = row / d.num_q_heads;
@@ -64,6 +133,7 @@ __global__ __launch_bounds__(64) void attn_scalar_kernel(
   const int g = h / (d.num_q_heads / d.num_kv_heads);
   const int D = d.head_dim;
 
+  for (int i = threadIdx.x; i < D; i += kThreads) q_lds[i] = load_f32(q + (size_t)row * D + i);
   // sequence of this node: largest b with node_offset[b] <= node
   int lo = 0, hi = d.batch;  // invariant: node_offset[lo] <= node < node_offset[hi] (if well formed)
   while (hi - lo > 1) {
@@ -77,58 +147,78 @@ __global__ __launch_bounds__(64) void attn_scalar_kernel(
   int L = prefix_len[b];
   const int cap = d.max_blocks_per_seq * d.page_size;
   L = L < 0 ? 0 : (L > cap ? cap : L);
+  __syncthreads();
 
-  float qv[kMaxPerLane];
-#pragma unroll
-  for (int e = 0; e < kMaxPerLane; ++e) {
-    int dd = lane + 64 * e;
-    qv[e] = dd < D ? load_f32(q + (size_t)row * D + dd) : 0.f;
-  }
-  OnlineSoftmax st;
+  OnlineSoftmax<E> st;
   st.m = -__builtin_huge_valf();
   st.l = 0.f;
 #pragma unroll
-  for (int e = 0; e < kMaxPerLane; ++e) st.acc[e] = 0.f;
+  for (int e = 0; e < E; ++e) st.acc[e] = 0.f;
 
-  int begin = c * chunk_tokens;
-  int end = (c == splits - 1) ? L : min(L, begin + chunk_tokens);
+  const int begin = c * chunk_tokens;
+  const int end = (c == splits - 1) ? L : min(L, begin + chunk_tokens);
   const size_t page_stride = (size_t)d.num_kv_heads * d.page_size * D;
-  for (int p = begin; p < end; ++p) {
+  for (int p0 = begin + 64 * wave; p0 < end; p0 += 64 * kWaves) {
+    const int n = min(64, end - p0);
+    const int p = p0 + min(lane, n - 1);
     int blk = block_table[(size_t)b * d.max_blocks_per_seq + p / d.page_size];
     blk = blk < 0 ? 0 : (blk >= d.num_blocks ? d.num_blocks - 1 : blk);
-    size_t off = (size_t)blk * page_stride + ((size_t)g * d.page_size + p % d.page_size) * D;
-    absorb_key(st, qv, k_pool + off, v_pool + off, D, lane, d.softmax_scale);
+    const size_t off = (size_t)blk * page_stride + ((size_t)g * d.page_size + p % d.page_size) * D;
+    absorb_keys<T, E>(st, q_lds, k_pool, v_pool, off, n < 64 ? (1ull << n) - 1 : ~0ull, D, lane, d.softmax_scale);
   }
-  if (c == 0) {
-    // walk up from the node to the root; every visited node is on the node's own path
-    int x = node - n0;
+  if (c == 0 && wave == kWaves - 1) {  // the wavefront that has the least prefix when it is short
+    // walk up from the node to the root through the parents held by the lanes; every visited node
+    // is on the node's own path
+    const int last = d.total_nodes - 1;
+    const int at = max(0, min(n0 + lane, last));
+    const int par = parent[at];
+    unsigned long long live = 0;
+    int x = __builtin_amdgcn_readfirstlane(node - n0);
     if (x >= n_nodes) x = -1;
     for (int guard = 0; x >= 0 && guard < 64; ++guard) {
-      size_t off = ((size_t)(n0 + x) * d.num_kv_heads + g) * D;
-      absorb_key(st, qv, k_tree + off, v_tree + off, D, lane, d.softmax_scale);
-      int px = parent[n0 + x];
+      live |= 1ull << x;
+      const int px = __builtin_amdgcn_readlane(par, x);
       x = (px < x) ? px : -1;  // a malformed parent ends the walk
     }
+    const size_t off = ((size_t)at * d.num_kv_heads + g) * D;
+    absorb_keys<T, E>(st, q_lds, k_tree, v_tree, off, live, D, lane, d.softmax_scale);
   }
 
-  if (splits == 1) {
-    float inv = st.l > 0.f ? 1.f / st.l : 0.f;
+  // the wavefronts' results are combined through LDS; one without keys has l = 0 and no weight
+  const float l_wave = wave_sum(st.l);
 #pragma unroll
-    for (int e = 0; e < kMaxPerLane; ++e) {
-      int dd = lane + 64 * e;
-      if (dd < D) store_f32(out + (size_t)row * D + dd, st.acc[e] * inv);
-    }
-    if (lse && lane == 0) lse[row] = st.m + logf(st.l);
-  } else {
-    size_t slot = (size_t)row * splits + c;
+  for (int e = 0; e < E; ++e) acc_lds[wave][lane + 64 * e] = st.acc[e];
+  if (lane == 0) {
+    ml_lds[wave][0] = st.m;
+    ml_lds[wave][1] = l_wave;
+  }
+  __syncthreads();
+  float m = ml_lds[0][0], l = 0.f, w[kWaves];
 #pragma unroll
-    for (int e = 0; e < kMaxPerLane; ++e) {
-      int dd = lane + 64 * e;
-      if (dd < D) part_o[slot * D + dd] = st.acc[e];
-    }
-    if (lane == 0) {
-      part_ml[slot * 2 + 0] = st.m;
-      part_ml[slot * 2 + 1] = st.l;
+  for (int i = 1; i < kWaves; ++i) m = fmaxf(m, ml_lds[i][0]);
+#pragma unroll
+  for (int i = 0; i < kWaves; ++i) {
+    const float li = ml_lds[i][1];
+    w[i] = li == 0.f ? 0.f : expf(ml_lds[i][0] - m);
+    l += w[i] * li;
+  }
+  const float inv = l > 0.f ? 1.f / l : 0.f;
+  const size_t slot = (size_t)row * splits + c;
+  for (int i = threadIdx.x; i < D; i += kThreads) {
+    float o = 0.f;
+#pragma unroll
+    for (int u = 0; u < kWaves; ++u) o += w[u] * acc_lds[u][i];
+    if (splits == 1)
+      store_f32(out + (size_t)row * D + i, o * inv);
+    else
+      part_o[slot * D + i] = o;
+  }
+  if (threadIdx.x == 0) {
+    if (splits == 1) {
+      if (lse) lse[row] = m + logf(l);
+    } else {
+      part_ml[slot * 2 + 0] = m;
+      part_ml[slot * 2 + 1] = l;
     }
   }
 }
@@ -220,14 +310,21 @@ hipError_t launch_attn_scalar(const hb_attn_desc &d, const AttnPlan &plan, const
                               const int32_t *parent, void *out, float *lse, float *part_o,
                               float *part_ml, hipStream_t s) {
   dim3 grid((unsigned)(d.total_nodes * d.num_q_heads), (unsigned)plan.splits);
-  if (d.dtype == HB_F32)
-    attn_scalar_kernel<float><<<grid, 64, 0, s>>>(d, plan.splits, plan.chunk_tokens, (const float *)q,
-        (const float *)k_tree, (const float *)v_tree, (const float *)k_pool, (const float *)v_pool,
-        block_table, prefix_len, node_offset, parent, (float *)out, lse, part_o, part_ml);
-  else
-    attn_scalar_kernel<bf16_t><<<grid, 64, 0, s>>>(d, plan.splits, plan.chunk_tokens, (const bf16_t *)q,
-        (const bf16_t *)k_tree, (const bf16_t *)v_tree, (const bf16_t *)k_pool, (const bf16_t *)v_pool,
-        block_table, prefix_len, node_offset, parent, (bf16_t *)out, lse, part_o, part_ml);
+#define HB_ATTN_SCALAR(T_, E_)                                                                                  \
+  attn_scalar_kernel<T_, E_><<<grid, kThreads, 0, s>>>(d, plan.splits, plan.chunk_tokens, (const T_ *)q,        \
+      (const T_ *)k_tree, (const T_ *)v_tree, (const T_ *)k_pool, (const T_ *)v_pool, block_table, prefix_len,  \
+      node_offset, parent, (T_ *)out, lse, part_o, part_ml)
+  const int e = d.head_dim <= 64 ? 1 : d.head_dim <= 128 ? 2 : 4;  // head dimensions per lane
+  if (d.dtype == HB_F32) {
+    if (e == 1) HB_ATTN_SCALAR(float, 1);
+    else if (e == 2) HB_ATTN_SCALAR(float, 2);
+    else HB_ATTN_SCALAR(float, 4);
+  } else {
+    if (e == 1) HB_ATTN_SCALAR(bf16_t, 1);
+    else if (e == 2) HB_ATTN_SCALAR(bf16_t, 2);
+    else HB_ATTN_SCALAR(bf16_t, 4);
+  }
+#undef HB_ATTN_SCALAR
   return hipGetLastError();
 }
 

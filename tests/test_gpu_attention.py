@@ -98,6 +98,19 @@ def test_ragged_edges_and_odd_shapes(hb, step):
                 check_attn(inp, out, lse, ref=ref, label=f"edges {dtype} Hq={Hq} Hkv={Hkv} D={D} algo={algo} s={splits}")
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("D", [8, 72, 136, 256])
+def test_scalar_kernel_blocks_and_wavefronts(hb, step, dtype, D):
+    """Head dimensions of one, two and four elements per lane with and without a remainder, and
+    prefixes around one block of 64 keys and one round of the four wavefronts (256 keys)."""
+    trees = [W.chain_tree(2), W.seeded_tree(1), W.chain_tree(1), W.seeded_tree(2, n_nodes=64), W.chain_tree(20), W.chain_tree(3)]
+    inp = W.make_verify_inputs(78, dtype, 4, 2, D, [0, 1, 192, 255, 257, 600], trees, kv_std=1.0, q_std=1.0)
+    ref = oracle_attn(inp)
+    for splits in (1, 2, 0):
+        out, lse, _ = _run(step, inp, num_splits=splits, algo=hb.HB_ATTN_SCALAR)
+        check_attn(inp, out, lse, ref=ref, label=f"scalar {dtype} D={D} splits={splits}")
+
+
 def test_schedules_of_the_matrix_core_kernel(hb, step):
     """With num_splits = 0 the kernel cuts the KV itself, on the device, from the prefix lengths:
     work-proportionally when that finishes first (one long sequence among short ones: pieces of

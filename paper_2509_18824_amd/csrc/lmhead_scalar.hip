@@ -1,7 +1,7 @@
-// LM head with fused argmax, scalar fp32 kernel (any dtype, any sizes), plus the two tiny
+// LM head with fused argmax, scalar fp32 kernels (any dtype, any sizes), plus the two tiny
 // kernels every LM-head path shares: key initialisation and the final unpack.
 //
-// Each workgroup computes a 64 x 64 tile of logits (rows of `hidden` x rows of `weight`) in
+// lmhead_rows_kernel serves few rows (see there).  Otherwise each workgroup computes a 64 x 64 tile of logits (rows of `hidden` x rows of `weight`) in
 // registers, reduces each row of the tile to one (value, index) key and folds it into the
 // row's global key with a 64-bit atomic max.  max over keys is order independent, so the
 // result does not depend on scheduling.
@@ -74,6 +74,92 @@ __global__ __launch_bounds__(256) void lmhead_scalar_kernel(int M, int K, int V,
   if (tid < TM && m0 + tid < M && srow[tid]) atomicMax(&keys[m0 + tid], srow[tid]);
 }
 
+// Few rows: the product is bound by latency and by the weight rows, and a 64 x 64 tile would leave
+// most of its rows empty and give work to V / 64 workgroups only, each a chain of K / 16 round
+// trips.  Here a wavefront takes kRowsV weight rows against kRowsM hidden rows with its lanes spread
+// over K (16-byte loads, all of a step's twelve in flight), and the 32 sums are folded over the
+// lanes by halving: each step sends half of the values and keeps the other.
+constexpr int kRowsV = 4, kRowsM = 8;
+constexpr int kRowsWaves = 4;
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+template <typename T> struct Piece;  // 16 bytes of a row
+template <> struct Piece<float> {
+  static constexpr int n = 4;
+  f32x4 v;
+  __device__ float at(int e) const { return v[e]; }
+};
+template <> struct Piece<bf16_t> {
+  static constexpr int n = 8;
+  u32x4 v;
+  __device__ float at(int e) const { return __uint_as_float((e & 1) ? (v[e >> 1] & 0xffff0000u) : (v[e >> 1] << 16)); }
+};
+
+template <int N>
+__device__ inline void fold_lanes(float (&x)[kRowsV * kRowsM], int lane) {
+  // lanes that differ in bit 2 N of their number exchange halves of x[0 .. 2 N)
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const bool up = lane & (2 * N);
+    const float keep = up ? x[i + N] : x[i], send = up ? x[i] : x[i + N];
+    x[i] = keep + __shfl_xor(send, 2 * N, 64);
+  }
+}
+
+template <typename T>
+__global__ __launch_bounds__(64 * kRowsWaves) void lmhead_rows_kernel(int M, int K, int V, const T *__restrict__ hidden,
+                                                                      const T *__restrict__ weight,
+                                                                      unsigned long long *__restrict__ keys) {
+  __shared__ unsigned long long best[kRowsWaves][kRowsM];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int v0 = (blockIdx.x * kRowsWaves + wave) * kRowsV, m0 = blockIdx.y * kRowsM;
+  const T *w[kRowsV], *h[kRowsM];  // rows past the end read the last one and are dropped below
+#pragma unroll
+  for (int i = 0; i < kRowsV; ++i) w[i] = weight + (size_t)min(v0 + i, V - 1) * K;
+#pragma unroll
+  for (int j = 0; j < kRowsM; ++j) h[j] = hidden + (size_t)min(m0 + j, M - 1) * K;
+  float acc[kRowsV * kRowsM];
+#pragma unroll
+  for (int i = 0; i < kRowsV * kRowsM; ++i) acc[i] = 0.f;
+  for (int k = lane * Piece<T>::n; k < K; k += 64 * Piece<T>::n) {
+    Piece<T> a[kRowsV], b[kRowsM];
+#pragma unroll
+    for (int i = 0; i < kRowsV; ++i) a[i] = *reinterpret_cast<const Piece<T> *>(w[i] + k);
+#pragma unroll
+    for (int j = 0; j < kRowsM; ++j) b[j] = *reinterpret_cast<const Piece<T> *>(h[j] + k);
+#pragma unroll
+    for (int i = 0; i < kRowsV; ++i)
+#pragma unroll
+      for (int j = 0; j < kRowsM; ++j)
+#pragma unroll
+        for (int e = 0; e < Piece<T>::n; ++e) acc[i * kRowsM + j] = fmaf(a[i].at(e), b[j].at(e), acc[i * kRowsM + j]);
+  }
+  fold_lanes<16>(acc, lane);
+  fold_lanes<8>(acc, lane);
+  fold_lanes<4>(acc, lane);
+  fold_lanes<2>(acc, lane);
+  fold_lanes<1>(acc, lane);
+  const float x = acc[0] + __shfl_xor(acc[0], 1, 64);  // product of weight row lane / 16 and hidden row (lane / 2) % 8
+  const int v = v0 + (lane >> 4);
+  unsigned long long key = v < V ? argmax_key(x, (uint32_t)v) : 0ull;
+#pragma unroll
+  for (int off = 16; off <= 32; off <<= 1) {
+    const unsigned long long other = __shfl_xor(key, off, 64);
+    key = other > key ? other : key;
+  }
+  if (lane < 2 * kRowsM && !(lane & 1)) best[wave][lane >> 1] = key;
+  __syncthreads();
+  if (threadIdx.x < kRowsM && m0 + (int)threadIdx.x < M) {
+    key = best[0][threadIdx.x];
+#pragma unroll
+    for (int i = 1; i < kRowsWaves; ++i) key = best[i][threadIdx.x] > key ? best[i][threadIdx.x] : key;
+    unsigned long long *dst = &keys[m0 + threadIdx.x];
+    if (key > __atomic_load_n(dst, __ATOMIC_RELAXED)) atomicMax(dst, key);
+  }
+}
+
 __global__ void lmhead_init_kernel(unsigned long long *keys, int M) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < M) keys[i] = 0ull;
@@ -92,8 +178,25 @@ __global__ void lmhead_finish_kernel(const unsigned long long *keys, int M, int 
 
 }  // namespace
 
+// Up to 32 rows the wavefronts' re-reading of the weight rows, once per eight hidden rows, costs less
+// than the tile kernel's empty rows and round trips (float32, call with both small kernels):
+// K x V = 256 x 1000, 1..256 rows 17.5 us against 32.6..36; 1024 x 32000: 8 rows 39 us against 155, 32 rows 116
+// against 157, 64 rows 224 against 177.  Rows must consist of whole 16-byte pieces.
+static bool rows_kernel_takes(int32_t dtype, int32_t M, int32_t K) {
+  return M <= 32 && K % (dtype == HB_F32 ? Piece<float>::n : Piece<bf16_t>::n) == 0;
+}
+
 hipError_t launch_lmhead_scalar(int32_t dtype, int32_t M, int32_t K, int32_t V, const void *hidden,
                                 const void *weight, unsigned long long *keys, hipStream_t s) {
+  if (rows_kernel_takes(dtype, M, K)) {
+    constexpr int kPerGroup = kRowsWaves * kRowsV;
+    dim3 grid((unsigned)((V + kPerGroup - 1) / kPerGroup), (unsigned)((M + kRowsM - 1) / kRowsM));
+    if (dtype == HB_F32)
+      lmhead_rows_kernel<float><<<grid, 64 * kRowsWaves, 0, s>>>(M, K, V, (const float *)hidden, (const float *)weight, keys);
+    else
+      lmhead_rows_kernel<bf16_t><<<grid, 64 * kRowsWaves, 0, s>>>(M, K, V, (const bf16_t *)hidden, (const bf16_t *)weight, keys);
+    return hipGetLastError();
+  }
   dim3 grid((unsigned)((V + TN - 1) / TN), (unsigned)((M + TM - 1) / TM));
   if (dtype == HB_F32)
     lmhead_scalar_kernel<float><<<grid, 256, 0, s>>>(M, K, V, (const float *)hidden, (const float *)weight, keys);

@@ -66,6 +66,18 @@ def test_small_shapes(step, dtype, M, K, V):
     _check(hidden, weight, ids, mx)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+# 1 .. 32 rows of whole 16-byte pieces take the few-rows kernel (eight rows and sixteen vocabulary
+# entries per workgroup, 256 or 512 elements of K per step); 33 rows or a broken piece the tiles
+@pytest.mark.parametrize("M,K,V", [(1, 8, 15), (8, 264, 16), (9, 504, 17), (31, 1032, 65), (32, 520, 1000),
+                                   (33, 520, 64), (7, 250, 100)])
+def test_few_rows(step, dtype, M, K, V):
+    hidden, weight = W.make_lmhead_inputs(M * 5 + V, M, K, V, dtype=dtype, w_std=0.05)
+    ids, mx = step.lmhead_argmax(hidden.cuda(), weight.cuda())
+    torch.cuda.synchronize()
+    _check(hidden, weight, ids, mx)
+
+
 def test_work_units_of_the_left_over_cus(step):
     """960 rows are five 192-row hidden tiles: six lockstep groups occupy 30 of an XCD's 32 CUs.
     With 152 vocabulary tiles (19 per XCD) the other two CUs take the XCD's first tile as five

@@ -453,6 +453,23 @@ int32_t hb_meta_query_attn(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q
                            void *pre, void *residual_out_or_null, void *workspace, size_t workspace_bytes,
                            void *stream);
 
+/*
+ * hb_meta_query_attn without v_proj: the features are mixed first and W_v (w_v [D, D], device) is
+ * applied to the mixture, which is the same sum in another order and L / Q times less work.  Steps
+ * (2) and (3) above in one call; heads of 128 only (UNSUPPORTED otherwise, and 0 bytes).  The
+ * workspace, 16-byte aligned, also takes a copy of w_v that every call makes anew.
+ * hb_meta_query_attn_project_pays: 1 where this is the faster way (from about 25 tokens on for 28
+ * layers and 3 queries), else 0.
+ */
+int32_t hb_meta_query_attn_project_pays(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q);
+
+size_t hb_meta_query_attn_project_workspace_bytes(int32_t S, int32_t D, int32_t H, int32_t Q);
+
+int32_t hb_meta_query_attn_project(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q, const void *feats,
+                                   const void *w_v, const void *a_fold, const int32_t *residual_layers_or_null,
+                                   void *pre, void *residual_out_or_null, void *workspace, size_t workspace_bytes,
+                                   void *stream);
+
 #ifdef __cplusplus
 }
 #endif

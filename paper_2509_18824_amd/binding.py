@@ -104,6 +104,12 @@ def _load():
     lib.hb_meta_query_fold.argtypes = [i32, i32, i32, p, p, p, p, p, sz, p]
     lib.hb_meta_query_attn.restype = i32
     lib.hb_meta_query_attn.argtypes = [i32] * 5 + [p, p, p, C.POINTER(i32), p, p, p, sz, p]
+    lib.hb_meta_query_attn_project.restype = i32
+    lib.hb_meta_query_attn_project.argtypes = lib.hb_meta_query_attn.argtypes
+    lib.hb_meta_query_attn_project_workspace_bytes.restype = sz
+    lib.hb_meta_query_attn_project_workspace_bytes.argtypes = [i32, i32, i32, i32]
+    lib.hb_meta_query_attn_project_pays.restype = i32
+    lib.hb_meta_query_attn_project_pays.argtypes = [i32] * 5
     lib.hb_meta_query_attn_workspace_bytes.restype = sz
     lib.hb_meta_query_attn_workspace_bytes.argtypes = [i32, i32, i32, i32]
     lib.hb_kv_compact.restype = i32
@@ -346,16 +352,37 @@ def hb_meta_query_attn_workspace_bytes(S: int, D: int, H: int, Q: int) -> int:
     return int(lib.hb_meta_query_attn_workspace_bytes(S, D, H, Q))
 
 
-def hb_meta_query_attn(H: int, Q: int, feats, v_proj, a_fold, residual_layers, pre, residual_out, workspace,
-                       stream=None) -> None:
+def hb_meta_query_attn_project_workspace_bytes(S: int, D: int, H: int, Q: int) -> int:
+    return int(lib.hb_meta_query_attn_project_workspace_bytes(S, D, H, Q))
+
+
+def hb_meta_query_attn_project_pays(S: int, L: int, D: int, H: int, Q: int) -> bool:
+    return bool(lib.hb_meta_query_attn_project_pays(S, L, D, H, Q))
+
+
+def _meta_query_attn(call, H, Q, feats, v_proj_or_w_v, a_fold, residual_layers, pre, residual_out, workspace, stream):
     S, L, D = feats.shape
-    for t in (feats, v_proj, a_fold, pre):
+    for t in (feats, v_proj_or_w_v, a_fold, pre):
         if t.dtype != torch.bfloat16 or not t.is_contiguous():
             raise ValueError("bf16 contiguous tensors expected")
     layers = (C.c_int32 * Q)(*[int(x) for x in residual_layers]) if residual_layers is not None else None
     ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    _check(lib.hb_meta_query_attn(S, L, D, H, Q, _ptr(feats), _ptr(v_proj), _ptr(a_fold), layers, _ptr(pre),
-                                  _ptr(residual_out), _ptr(workspace), ws_bytes, _stream(stream)))
+    _check(call(S, L, D, H, Q, _ptr(feats), _ptr(v_proj_or_w_v), _ptr(a_fold), layers, _ptr(pre), _ptr(residual_out),
+                _ptr(workspace), ws_bytes, _stream(stream)))
+
+
+def hb_meta_query_attn(H: int, Q: int, feats, v_proj, a_fold, residual_layers, pre, residual_out, workspace,
+                       stream=None) -> None:
+    _meta_query_attn(lib.hb_meta_query_attn, H, Q, feats, v_proj, a_fold, residual_layers, pre, residual_out, workspace, stream)
+
+
+def hb_meta_query_attn_project(H: int, Q: int, feats, w_v, a_fold, residual_layers, pre, residual_out, workspace,
+                               stream=None) -> None:
+    D = feats.shape[2]
+    if tuple(w_v.shape) != (D, D):
+        raise ValueError("w_v must be [D, D]")
+    _meta_query_attn(lib.hb_meta_query_attn_project, H, Q, feats, w_v, a_fold, residual_layers, pre, residual_out, workspace,
+                     stream)
 
 
 def hb_kv_compact(desc: AttnDesc, k_tree, v_tree, k_pool, v_pool, block_table, prefix_len, node_offset,

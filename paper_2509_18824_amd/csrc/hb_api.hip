@@ -545,13 +545,14 @@ size_t hb_meta_query_attn_workspace_bytes(int32_t S, int32_t D, int32_t H, int32
   return meta_attn_workspace_bytes(S, D, H, Q);
 }
 
-int32_t hb_meta_query_attn(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q, const void *feats,
-                           const void *v_proj, const void *a_fold, const int32_t *residual_layers_or_null,
-                           void *pre, void *residual_out_or_null, void *workspace, size_t workspace_bytes,
-                           void *stream) {
+static int32_t meta_attn(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q, const void *feats, const void *v_proj_or_w_v,
+                         bool project, const void *a_fold, const int32_t *residual_layers_or_null, void *pre,
+                         void *residual_out_or_null, void *workspace, size_t workspace_bytes, void *stream) {
   if (S < 0) return fail(HB_ERR_INVALID_ARG, "S must be >= 0");
   int32_t rc = check_meta_shape(L, D, H, Q);
   if (rc) return rc;
+  if (project && !meta_project_supports(D, H))
+    return fail(HB_ERR_UNSUPPORTED, "D %d, H %d: values are projected after the mixing for heads of 128 only", D, H);
   if (residual_layers_or_null) {
     for (int q = 0; q < Q; ++q)
       if (residual_layers_or_null[q] < 0 || residual_layers_or_null[q] >= L)
@@ -559,19 +560,50 @@ int32_t hb_meta_query_attn(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q
     if (!residual_out_or_null) return fail(HB_ERR_INVALID_ARG, "residual layers given without residual_out");
   }
   if (S == 0) return HB_OK;
-  if (!feats || !v_proj || !a_fold || !pre) return fail(HB_ERR_INVALID_ARG, "a required device pointer is NULL");
-  if (misaligned(feats) || misaligned(v_proj) || misaligned(a_fold) || misaligned(pre) ||
+  if (!feats || !v_proj_or_w_v || !a_fold || !pre) return fail(HB_ERR_INVALID_ARG, "a required device pointer is NULL");
+  if (misaligned(feats) || misaligned(v_proj_or_w_v) || misaligned(a_fold) || misaligned(pre) ||
       (residual_out_or_null && misaligned(residual_out_or_null)))
     return fail(HB_ERR_INVALID_ARG, "tensors must be 16-byte aligned");
-  const size_t need = meta_attn_workspace_bytes(S, D, H, Q);
+  const size_t need = project ? meta_project_workspace_bytes(S, D, H, Q) : meta_attn_workspace_bytes(S, D, H, Q);
   if (!workspace || workspace_bytes < need)
     return fail(HB_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need,
                 workspace ? workspace_bytes : (size_t)0);
-  if ((uintptr_t)workspace % 4) return fail(HB_ERR_WORKSPACE, "workspace must be 4-byte aligned");
-  HB_HIP_TRY(launch_meta_attn(S, L, D, H, Q, feats, v_proj, a_fold, residual_layers_or_null, pre,
-                              residual_layers_or_null ? residual_out_or_null : nullptr, (float *)workspace,
-                              (hipStream_t)stream));
+  if ((uintptr_t)workspace % (project ? 16 : 4))
+    return fail(HB_ERR_WORKSPACE, "workspace must be %d-byte aligned", project ? 16 : 4);
+  void *res = residual_layers_or_null ? residual_out_or_null : nullptr;
+  hipStream_t s = (hipStream_t)stream;
+  if (project)
+    HB_HIP_TRY(launch_meta_attn_project(S, L, D, H, Q, feats, a_fold, v_proj_or_w_v, residual_layers_or_null, pre, res,
+                                        (float *)workspace, s));
+  else
+    HB_HIP_TRY(launch_meta_attn(S, L, D, H, Q, feats, v_proj_or_w_v, a_fold, residual_layers_or_null, pre, res,
+                                (float *)workspace, s));
   return HB_OK;
+}
+
+int32_t hb_meta_query_attn(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q, const void *feats,
+                           const void *v_proj, const void *a_fold, const int32_t *residual_layers_or_null,
+                           void *pre, void *residual_out_or_null, void *workspace, size_t workspace_bytes,
+                           void *stream) {
+  return meta_attn(S, L, D, H, Q, feats, v_proj, false, a_fold, residual_layers_or_null, pre, residual_out_or_null,
+                   workspace, workspace_bytes, stream);
+}
+
+size_t hb_meta_query_attn_project_workspace_bytes(int32_t S, int32_t D, int32_t H, int32_t Q) {
+  if (S < 1 || check_meta_shape(1, D, H, Q) || !meta_project_supports(D, H)) return 0;
+  return meta_project_workspace_bytes(S, D, H, Q);
+}
+
+int32_t hb_meta_query_attn_project_pays(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q) {
+  return S > 0 && !check_meta_shape(L, D, H, Q) && meta_project_pays(S, L, D, H, Q);
+}
+
+int32_t hb_meta_query_attn_project(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q, const void *feats,
+                                   const void *w_v, const void *a_fold, const int32_t *residual_layers_or_null,
+                                   void *pre, void *residual_out_or_null, void *workspace, size_t workspace_bytes,
+                                   void *stream) {
+  return meta_attn(S, L, D, H, Q, feats, w_v, true, a_fold, residual_layers_or_null, pre, residual_out_or_null,
+                   workspace, workspace_bytes, stream);
 }
 
 int32_t hb_kv_compact(const hb_attn_desc *desc, const void *k_tree, const void *v_tree,

@@ -92,21 +92,30 @@ struct ResidualLayers {
 
 // part[p][s][row][l] (row stride 32): the scores of token s summed over the slices that
 // workgroup column p covers
+// Workgroups behind the scores' (score_wgs) rearrange W_v for meta_project_kernel, where that follows.
+__device__ void pack_values(int wave, int waves, int D, const u32x4 *__restrict__ w_v, u32x4 *__restrict__ packed);
+
 __global__ __launch_bounds__(kScoreThreads) void meta_scores_kernel(int S, int L, int D, int row_tiles,
-                                                                    int slices_per_wg,
+                                                                    int slices_per_wg, int token_groups, int score_wgs,
+                                                                    const u32x4 *__restrict__ w_v, u32x4 *__restrict__ packed,
                                                                     const u32x4 *__restrict__ feats,
                                                                     const u32x4 *__restrict__ a_hi,
                                                                     const u32x4 *__restrict__ a_lo,
                                                                     float *__restrict__ part) {
   extern __shared__ u32x4 meta_a_lds[];  // [2][rows_pad][kRowPieces]
+  if ((int)blockIdx.x >= score_wgs) {
+    pack_values((blockIdx.x - score_wgs) * kScoreWaves + (threadIdx.x >> 6), (gridDim.x - score_wgs) * kScoreWaves, D, w_v, packed);
+    return;
+  }
+  const int token_group = blockIdx.x % token_groups, column = blockIdx.x / token_groups;
   const int rows_pad = 16 * row_tiles;
   u32x4 *lds_hi = meta_a_lds, *lds_lo = meta_a_lds + rows_pad * kRowPieces;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int j16 = lane & 15, kq = lane >> 4;
   const int dp = D / 8;                       // 16-byte pieces per feature row
-  const int tok0 = blockIdx.x * kTokPerGroup + wave * kTokPerWave;
+  const int tok0 = token_group * kTokPerGroup + wave * kTokPerWave;
   const int slices = D / kSlice;
-  const int sl_begin = blockIdx.y * slices_per_wg;
+  const int sl_begin = column * slices_per_wg;
   const int sl_end = sl_begin + slices_per_wg < slices ? sl_begin + slices_per_wg : slices;
 
   // B operand: lane (j16, kq) feeds layer 16 ct + j16, features 8 kq .. 8 kq + 7 of the step.
@@ -191,7 +200,7 @@ __global__ __launch_bounds__(kScoreThreads) void meta_scores_kernel(int S, int L
 #pragma unroll
   for (int t = 0; t < kTokPerWave; ++t) {
     if (tok0 + t < S) {
-      float *dst = part + ((size_t)blockIdx.y * S + tok0 + t) * rows_pad * kMaxL;
+      float *dst = part + ((size_t)column * S + tok0 + t) * rows_pad * kMaxL;
 #pragma unroll
       for (int mt = 0; mt < kMaxRowTiles; ++mt) {
         if (mt < row_tiles) {
@@ -314,6 +323,328 @@ __global__ __launch_bounds__(kMixThreads) void meta_mix_kernel(int S, int L, int
   }
 }
 
+// ---- values projected after the mixing -------------------------------------------------------
+// pre[i, q, head h] = sum_l P[i, h, q, l] (f_i[l] W_v^T)_h = (sum_l P[i, h, q, l] f_i[l]) W_v,h^T:
+// mixing the features first leaves Q rows per token and head to project instead of L rows per
+// token, L / Q times less matrix work (28 layers, 3 queries: 9 times).  The mixed features, H Q
+// vectors of D per token, would be three times the features in memory; here a workgroup makes them
+// slice by slice in LDS and uses them up at once.
+//
+// Workgroup: TG tokens and up to eight heads (their hq rows: head-major, the queries of a head
+// together).  It walks D in slices of 64 features:
+//   mixing   feats^T P^T on the matrix cores per token (features as rows, the transposing LDS read
+//            supplies them; P^T of a wavefront's tokens stays in registers for the whole kernel).
+//            The two 16-feature tiles of 32 features are interleaved in fours, so that a lane holds
+//            eight consecutive features of one hq row and stores them as one piece.
+//   product  W_v slice (straight from memory in fragment layout) times the mixed features of the
+//            wavefront's head: accumulators for all of the workgroup's tokens.
+// The slice's weights are requested before the mixing, the next slice's features (global -> LDS)
+// before the product, so each phase covers the other's loads.
+// P and the mixed features are each a bf16 value plus the bf16 remainder (two products, about 2^-17
+// relative): what was float32 when values were projected first stays better than bf16.
+//
+// What bounds it: with 4 tokens the path L2 -> CU (every TG tokens read all of W_v once); with 16
+// tokens the two phases between barriers, matrix, vector and LDS work in turn on two wavefronts per
+// SIMD.  2048 tokens, 28 layers, D = 3584, 28 heads, 3 queries: 566 us; the value projection of all
+// layers and the mixing of its results took 1478 + 161 us.  96 tokens: 67 us against 76 + 15.
+constexpr int kMpThreads = 512;
+constexpr int kMpWaves = 8;
+constexpr int kMpHq = 24;           // hq rows of a workgroup at most: 96 KB of mixed features beside 64 KB of features
+constexpr int kMpHeadDim = 128;
+constexpr int kBufferFlags = 0x00027000;  // untyped 32-bit elements
+
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+// W_v in fragment order, made on every call by workgroups of the score kernel's launch: 16 rows x 32
+// columns are 1 KB in the order of the lanes, [head][16 rows][64 columns][32 columns][lane].  Read
+// from the matrix itself, four neighbouring lanes of a fragment load touch four rows and a load takes
+// 64 clocks instead of 16 (measured: 34 GB/s per CU, and 2.5 times the time for the whole kernel).
+__device__ void pack_values(int wave, int waves, int D, const u32x4 *__restrict__ w_v, u32x4 *__restrict__ packed) {
+  const int lane = threadIdx.x & 63;
+  const int dp = D / 8, steps = D / 64;
+  constexpr int kBatch = 4;
+  const int tiles = D / 16 * steps;  // 16 rows x 64 columns: 2 KB
+  for (int t0 = wave * kBatch; t0 < tiles; t0 += waves * kBatch) {
+    u32x4 x[kBatch][2];  // lane -> row lane / 8 (+ 8), piece lane % 8
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) {
+      const int t = min(t0 + i, tiles - 1);
+      const u32x4 *src = w_v + (size_t)(t / steps * 16 + (lane >> 3)) * dp + t % steps * 8 + (lane & 7);
+      x[i][0] = src[0];
+      x[i][1] = src[(size_t)8 * dp];
+    }
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) {
+      const int t = min(t0 + i, tiles - 1);
+      u32x4 *dst = packed + (size_t)t * 128 + ((lane & 7) >> 2) * 64 + (lane & 3) * 16 + (lane >> 3);
+      dst[0] = x[i][0];
+      dst[8] = x[i][1];
+    }
+  }
+}
+
+// value = bf16 (truncated) + bf16 remainder; two values per word
+__device__ __forceinline__ void split_pair(float a, float b, uint32_t &hi, uint32_t &lo) {
+  const uint32_t ua = __float_as_uint(a) & 0xffff0000u, ub = __float_as_uint(b) & 0xffff0000u;
+  hi = (ua >> 16) | ub;
+  const f32x2 r = {a - __uint_as_float(ua), b - __uint_as_float(ub)};
+  lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, bf16x2));
+}
+
+// Four transposing reads of 8 bytes per lane.  Inline asm with its own wait: before the builtin the
+// compiler waits for every load in flight, taking it for a reader of the features on their way.
+__device__ __forceinline__ void tr_fragments(uint32_t at0, uint32_t at1, bf16x8 (&a)[2]) {
+  bf16x4 x0, x1, y0, y1;
+  asm volatile(
+      "ds_read_b64_tr_b16 %0, %4\n\t"
+      "ds_read_b64_tr_b16 %1, %5\n\t"
+      "ds_read_b64_tr_b16 %2, %4 offset:8\n\t"
+      "ds_read_b64_tr_b16 %3, %5 offset:8\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(x0), "=&v"(x1), "=&v"(y0), "=&v"(y1)
+      : "v"(at0), "v"(at1)
+      : "memory");
+  a[0] = __builtin_shufflevector(x0, x1, 0, 1, 2, 3, 4, 5, 6, 7);
+  a[1] = __builtin_shufflevector(y0, y1, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
+// TG 16: a head's rows are Q tiles of 16 tokens (QT = Q); TG 4: one tile, row = q * 4 + token (QT = 1).
+// NT: 16-column tiles of a head per wavefront; 8 / NT wavefronts share a head.  FI: feature loads of a
+// wavefront per slice.  NS: slices of features in LDS.
+template <int TG, int QT, int NT, int FI, int NS>
+__global__ __launch_bounds__(kMpThreads) void meta_project_kernel(
+    int S, int L, int D, int H, int Q, int hg, int rows_pad, int parts, const float *__restrict__ part,
+    const u32x4 *__restrict__ feats, const u32x4 *__restrict__ packed, ResidualLayers res, bf16_t *__restrict__ pre,
+    u32x4 *__restrict__ res_out) {
+  constexpr int kWavesPerHead = 8 / NT;
+  constexpr int kTok = TG == 16 ? 2 : 1;   // tokens whose mixing a wavefront does
+  constexpr int kSub = TG == 16 ? 2 : 1;   // 32-feature halves of the slice it does for them
+  extern __shared__ u32x4 meta_a_lds[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int j16 = lane & 15, kq = lane >> 4;
+  const int dp = D / 8;
+  const int tok0 = blockIdx.x * TG, h0 = blockIdx.y * hg;
+  const int heads = min(hg, H - h0);        // >= 1
+  const int hq_rows = heads * Q;
+  const int frows = min(TG, S - tok0) * L;  // feature rows of the workgroup, consecutive in memory
+  u32x4 *lds_f = meta_a_lds;                // [NS][FI * 8 wavefronts * 8 rows][8]
+  constexpr int kStagePieces = FI * kMpWaves * 64;
+  u32x4 *lds_m = meta_a_lds + NS * kStagePieces;  // [2][mixed rows][8]: values, remainders
+  const int mixed = TG == 16 ? hg * Q * 16 : hg * 16;
+
+  // Features: 64 rows per round of the wavefronts, lane -> row lane / 8 of its wavefront's eight,
+  // piece swizzled on the source side; rows past the workgroup's are out of the buffer's range and
+  // arrive as zeros.  Always FI loads (the waits below count them): a repeated slice changes nothing.
+  typedef __attribute__((address_space(3))) void *lptr_t;
+  const int steps = D / 64;
+  const auto f_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(feats + (size_t)tok0 * L * dp), 0, frows * dp * 16, kBufferFlags);
+  const int f_src = (wave * 8 + (lane >> 3)) * dp * 16 + ((lane & 7) ^ (((wave * 8 + (lane >> 3)) >> 1) & 7)) * 16;
+  auto issue_feats = [&](int kt) {
+    const int k = min(kt, steps - 1);
+    u32x4 *stage = lds_f + (kt % NS) * kStagePieces + wave * 64;
+#pragma unroll
+    for (int i = 0; i < FI; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(f_rsrc, (lptr_t)(stage + i * kMpWaves * 64), 16, f_src,
+                                               i * kMpWaves * 8 * dp * 16 + k * 128, 0, 0);
+  };
+  issue_feats(0);
+
+  // ---- softmax over the layers, one thread per (token, hq row); P goes through LDS ------------
+  bf16x8 p_hi[kTok][2], p_lo[kTok][2];
+  {
+    u32x4 *tab = lds_m;  // [2][TG * hq_rows][4 pieces]
+    const int n = TG * hq_rows;
+    if (tid < n) {
+      const int t = tid / hq_rows, hq = tid - t * hq_rows;
+      const int s = min(tok0 + t, S - 1);
+      const f32x4 *src = reinterpret_cast<const f32x4 *>(part + ((size_t)s * rows_pad + h0 * Q + hq) * kMaxL);
+      const size_t stride = (size_t)S * rows_pad * (kMaxL / 4);
+      f32x4 sc[kMaxL / 4];
+#pragma unroll
+      for (int i = 0; i < kMaxL / 4; ++i) sc[i] = src[i];
+      for (int p = 1; p < parts; ++p)
+#pragma unroll
+        for (int i = 0; i < kMaxL / 4; ++i) sc[i] += src[p * stride + i];
+      float mx = -__builtin_huge_valf();
+#pragma unroll
+      for (int l = 0; l < kMaxL; ++l)
+        if (l < L) mx = fmaxf(mx, sc[l >> 2][l & 3]);
+      float sum = 0.f;
+#pragma unroll
+      for (int l = 0; l < kMaxL; ++l) {
+        const float e = l < L ? __expf(sc[l >> 2][l & 3] - mx) : 0.f;
+        sc[l >> 2][l & 3] = e;
+        sum += e;
+      }
+      const float inv = 1.f / sum;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        u32x4 hi, lo;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int l = 8 * i + 2 * e;
+          uint32_t a, b;
+          split_pair(sc[l >> 2][l & 3] * inv, sc[(l + 1) >> 2][(l + 1) & 3] * inv, a, b);
+          hi[e] = a;
+          lo[e] = b;
+        }
+        tab[tid * 4 + i] = hi;
+        tab[(n + tid) * 4 + i] = lo;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int tt = 0; tt < kTok; ++tt) {
+      const int t = TG == 16 ? 2 * wave + tt : wave >> 1;
+#pragma unroll
+      for (int ct = 0; ct < 2; ++ct) {
+        const int hq = 16 * ct + j16;
+        const int at = t * hq_rows + min(hq, hq_rows - 1);
+        const u32x4 zero = {0u, 0u, 0u, 0u};
+        p_hi[tt][ct] = __builtin_bit_cast(bf16x8, hq < hq_rows ? tab[at * 4 + kq] : zero);
+        p_lo[tt][ct] = __builtin_bit_cast(bf16x8, hq < hq_rows ? tab[(n + at) * 4 + kq] : zero);
+      }
+    }
+  }
+
+  // the residual rows of the workgroup's columns
+  if (res.on) {
+    const int cols = heads * (kMpHeadDim / 8), n = TG * Q * cols;
+    for (int i = tid; i < n; i += kMpThreads) {
+      const int row = i / cols, c = h0 * (kMpHeadDim / 8) + i - row * cols;
+      const int t = row / Q, q = row - t * Q;
+      if (tok0 + t < S) res_out[((size_t)(tok0 + t) * Q + q) * dp + c] = feats[((size_t)(tok0 + t) * L + res.layer[q]) * dp + c];
+    }
+  }
+
+  // transposing reads of the mixing: lane -> layer row and 8-byte half piece.  Layers past L repeat
+  // the last one (their probabilities are zero).
+  const uint32_t f_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) u32x4 *)lds_f;
+  uint32_t f_off[kTok][2];  // by half of the lane group's eight layers; ^ 64 for the slice's second 32 features
+#pragma unroll
+  for (int tt = 0; tt < kTok; ++tt) {
+    const int t = TG == 16 ? 2 * wave + tt : wave >> 1;
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf) {
+      const int r = t * L + min(8 * kq + 4 * hf + (j16 >> 2), L - 1);
+      f_off[tt][hf] = f_lds + r * 128 + ((j16 & 3) ^ ((r >> 1) & 7)) * 16;
+    }
+  }
+
+  const bool active = wave / kWavesPerHead < heads;        // a wavefront too many repeats the last head
+  const int hl = min(wave / kWavesPerHead, heads - 1);     // this wavefront's head
+  const int n0 = (wave % kWavesPerHead) * NT * 16;         // its first column in the head
+  const auto w_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(packed + (size_t)((h0 + hl) * 8 + n0 / 16) * steps * 128), 0,
+                                                        NT * steps * 2048, kBufferFlags);
+  f32x4 acc[QT][NT];
+#pragma unroll
+  for (int q = 0; q < QT; ++q)
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) acc[q][nt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+
+  bf16x8 w[2][NT];
+  auto issue_weights = [&](int kt) {
+    const int k = min(kt, steps - 1);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+        w[ks][nt] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, lane * 16, (nt * steps + k) * 2048 + ks * 1024, 0));
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the count below starts here
+  if (NS == 2) issue_feats(1);
+  __builtin_amdgcn_sched_barrier(0);
+  issue_weights(0);
+#pragma unroll 1
+  for (int kt = 0; kt < steps; ++kt) {
+    // The slice's features have landed (newer loads: with two stages the next slice's features; the
+    // slice's weights); everybody is done with the previous mixed features.
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NS - 1) * FI + 2 * NT) : "memory");
+    const uint32_t stage = (uint32_t)(kt % NS) * (uint32_t)(kStagePieces * 16);
+#pragma unroll
+    for (int tt = 0; tt < kTok; ++tt) {
+      const int t = TG == 16 ? 2 * wave + tt : wave >> 1;
+#pragma unroll
+      for (int sub = 0; sub < kSub; ++sub) {
+        const int g = TG == 16 ? sub : wave & 1;
+        bf16x8 a[2];
+        tr_fragments(stage + (f_off[tt][0] ^ (64 * g)), stage + (f_off[tt][1] ^ (64 * g)), a);
+#pragma unroll
+        for (int ct = 0; ct < 2; ++ct) {
+          if (16 * ct >= hq_rows) break;
+          f32x4 c[2];
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            c[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], p_hi[tt][ct], (f32x4){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+            c[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], p_lo[tt][ct], c[i], 0, 0, 0);
+          }
+          const int hq = 16 * ct + j16;
+          u32x4 hi, lo;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            uint32_t x, y;
+            split_pair(c[e >> 1][2 * (e & 1)], c[e >> 1][2 * (e & 1) + 1], x, y);
+            hi[e] = x;
+            lo[e] = y;
+          }
+          if (hq < hq_rows) {
+            const int row = TG == 16 ? hq * 16 + t : (hq / Q) * 16 + (hq % Q) * 4 + t;
+            const int at = row * 8 + ((4 * g + kq) ^ ((row + hq) & 7));
+            lds_m[at] = hi;
+            lds_m[mixed * 8 + at] = lo;
+          }
+        }
+      }
+    }
+    // the mixed features are complete; everybody is done with the slice's features
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    // The slice's weights are waited for before the next features are requested: the compiler's wait
+    // at their first use would include the newer loads.
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) asm volatile("" : "+v"(w[ks][nt]));
+    issue_feats(kt + NS);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int q = 0; q < QT; ++q) {
+        const int row = (TG == 16 ? (hl * Q + q) * 16 : hl * 16) + j16;
+        const int hq = TG == 16 ? hl * Q + q : hl * Q + (j16 >> 2);
+        const int at = row * 8 + ((4 * ks + kq) ^ ((row + hq) & 7));
+        const bf16x8 hi = __builtin_bit_cast(bf16x8, lds_m[at]);
+        const bf16x8 lo = __builtin_bit_cast(bf16x8, lds_m[mixed * 8 + at]);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+          acc[q][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ks][nt], hi, acc[q][nt], 0, 0, 0);
+          acc[q][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ks][nt], lo, acc[q][nt], 0, 0, 0);
+        }
+      }
+    __builtin_amdgcn_sched_barrier(0);
+    issue_weights(kt + 1);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  // lane (j16, kq) holds columns 16 nt + 4 kq .. + 3 of row j16
+  if (!active) return;
+#pragma unroll
+  for (int qt = 0; qt < QT; ++qt) {
+    const int t = TG == 16 ? j16 : j16 & 3, q = TG == 16 ? qt : j16 >> 2;
+    if (q >= Q || tok0 + t >= S) continue;
+    bf16_t *dst = pre + ((size_t)(tok0 + t) * Q + q) * D + (h0 + hl) * kMpHeadDim + n0 + 4 * kq;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+      *(u32x2 *)(dst + nt * 16) = (u32x2){(uint32_t)f32_to_bf16(acc[qt][nt][0]) | ((uint32_t)f32_to_bf16(acc[qt][nt][1]) << 16),
+                                          (uint32_t)f32_to_bf16(acc[qt][nt][2]) | ((uint32_t)f32_to_bf16(acc[qt][nt][3]) << 16)};
+    }
+  }
+}
+
 }  // namespace
 
 int32_t meta_rows_pad(int32_t H, int32_t Q) { return (H * Q + 15) / 16 * 16; }
@@ -350,29 +681,139 @@ size_t meta_attn_workspace_bytes(int32_t S, int32_t D, int32_t H, int32_t Q) {
   return (size_t)parts * S * meta_rows_pad(H, Q) * kMaxL * sizeof(float);
 }
 
-hipError_t launch_meta_attn(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q, const void *feats, const void *v_proj,
-                            const void *a_fold, const int32_t *residual_layers, void *pre, void *res_out,
-                            float *part, hipStream_t s) {
-  const int rows_pad = meta_rows_pad(H, Q);
+// scores of all tokens to part, its workgroup columns in *parts; w_v rearranged into packed if given
+static hipError_t launch_scores(int32_t S, int32_t L, int32_t D, int32_t rows_pad, const void *feats, const void *a_fold,
+                                const void *w_v, void *packed, float *part, int *parts, hipStream_t s) {
+  const bf16_t *a_hi = (const bf16_t *)a_fold, *a_lo = a_hi + (size_t)rows_pad * D;
+  int spw;
+  score_split(S, D, &spw, parts);
+  const size_t lds = (size_t)2 * rows_pad * kRowPieces * sizeof(u32x4);
+  hipError_t e = hipFuncSetAttribute((const void *)meta_scores_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     (int)((size_t)2 * kMaxRows * kRowPieces * sizeof(u32x4)));
+  if (e != hipSuccess) return e;
+  const int groups = (S + kTokPerGroup - 1) / kTokPerGroup, score_wgs = groups * *parts;
+  meta_scores_kernel<<<score_wgs + (packed ? 256 : 0), kScoreThreads, lds, s>>>(
+      S, L, D, rows_pad / 16, spw, groups, score_wgs, (const u32x4 *)w_v, (u32x4 *)packed, (const u32x4 *)feats,
+      (const u32x4 *)a_hi, (const u32x4 *)a_lo, part);
+  return hipGetLastError();
+}
+
+static ResidualLayers residuals(int32_t Q, const int32_t *residual_layers, const void *res_out) {
   ResidualLayers res = {};
   if (residual_layers && res_out) {
     res.on = 1;
     for (int q = 0; q < Q; ++q) res.layer[q] = residual_layers[q];
   }
-  const bf16_t *a_hi = (const bf16_t *)a_fold, *a_lo = a_hi + (size_t)rows_pad * D;
-  int spw, parts;
-  score_split(S, D, &spw, &parts);
-  const size_t lds = (size_t)2 * rows_pad * kRowPieces * sizeof(u32x4);
-  hipError_t e = hipFuncSetAttribute((const void *)meta_scores_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     (int)((size_t)2 * kMaxRows * kRowPieces * sizeof(u32x4)));
+  return res;
+}
+
+hipError_t launch_meta_attn(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q, const void *feats, const void *v_proj,
+                            const void *a_fold, const int32_t *residual_layers, void *pre, void *res_out,
+                            float *part, hipStream_t s) {
+  const int rows_pad = meta_rows_pad(H, Q);
+  int parts;
+  hipError_t e = launch_scores(S, L, D, rows_pad, feats, a_fold, nullptr, nullptr, part, &parts, s);
   if (e != hipSuccess) return e;
-  meta_scores_kernel<<<dim3((S + kTokPerGroup - 1) / kTokPerGroup, parts), kScoreThreads, lds, s>>>(
-      S, L, D, rows_pad / 16, spw, (const u32x4 *)feats, (const u32x4 *)a_hi, (const u32x4 *)a_lo, part);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  meta_mix_kernel<<<dim3(S, (D / 8 + kMixThreads - 1) / kMixThreads), kMixThreads, 0, s>>>(S, L, D, H, Q, rows_pad, parts, part, (const u32x4 *)feats,
-                                            (const u32x4 *)v_proj, res, (u32x4 *)pre, (u32x4 *)res_out);
+  meta_mix_kernel<<<dim3(S, (D / 8 + kMixThreads - 1) / kMixThreads), kMixThreads, 0, s>>>(
+      S, L, D, H, Q, rows_pad, parts, part, (const u32x4 *)feats, (const u32x4 *)v_proj, residuals(Q, residual_layers, res_out),
+      (u32x4 *)pre, (u32x4 *)res_out);
   return hipGetLastError();
+}
+
+bool meta_project_supports(int32_t D, int32_t H) { return D == H * kMpHeadDim; }
+
+// the partial scores, then W_v in fragment order
+static size_t meta_packed_offset(int32_t S, int32_t D, int32_t H, int32_t Q) {
+  return (meta_attn_workspace_bytes(S, D, H, Q) + 255) / 256 * 256;
+}
+size_t meta_project_workspace_bytes(int32_t S, int32_t D, int32_t H, int32_t Q) {
+  return meta_packed_offset(S, D, H, Q) + (size_t)D * D * sizeof(bf16_t);
+}
+
+namespace {
+
+template <int TG, int QT, int NT, int FI, int NS>
+hipError_t launch_project(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q, int hg, int parts, const void *feats,
+                          const void *packed, const ResidualLayers &res, void *pre, void *res_out, const float *part,
+                          hipStream_t s) {
+  const size_t lds = ((size_t)NS * FI * kMpWaves * 64 + 2 * (size_t)(TG == 16 ? hg * Q : hg) * 16 * 8) * sizeof(u32x4);
+  auto kern = meta_project_kernel<TG, QT, NT, FI, NS>;
+  hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  kern<<<dim3((S + TG - 1) / TG, (H + hg - 1) / hg), kMpThreads, lds, s>>>(
+      S, L, D, H, Q, hg, meta_rows_pad(H, Q), parts, part, (const u32x4 *)feats, (const u32x4 *)packed, res, (bf16_t *)pre,
+      (u32x4 *)res_out);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+// Which form, by the time a slice of 64 features takes (microseconds, measured at D = 3584, 28 heads, 3
+// queries): 4 tokens and 2 heads per workgroup 0.65 while all workgroups run at once; 4 tokens and 4
+// heads 1.0, from about 80 tokens on the weights through the L2s (every 4 tokens read W_v, 9.2 TB/s);
+// 16 tokens and 4 heads 3.0, 16 tokens and 6 to 8 heads 5.0, per round of 256 workgroups.  For the
+// layer up to fc1: 96 tokens 133 us (16 tokens per workgroup 203), 300 tokens 295 (4 tokens 310, 8
+// heads 385), 2048 tokens 1074 (4 heads 1260, 4 tokens 1467).
+struct ProjectPlan {
+  int tg, nt, hg;
+  double slice_us;
+};
+static int split_heads(int H, int most) {  // heads per workgroup, evenly
+  const int groups = (H + most - 1) / most;
+  return (H + groups - 1) / groups;
+}
+static ProjectPlan project_plan(int32_t S, int32_t H, int32_t Q) {
+  const int64_t g4 = (S + 3) / 4, g16 = (S + 15) / 16;
+  auto groups = [&](int hg) { return (int64_t)(H + hg - 1) / hg; };
+  if (g4 * groups(2) <= 256) return {4, 2, split_heads(H, 2), 0.65};
+  ProjectPlan best = {4, 4, split_heads(H, 4), (double)(g4 * H) * kMpHeadDim * 128 / 9.2e6};
+  if (best.slice_us < 1.0) best.slice_us = 1.0;
+  const int wide = split_heads(H, Q <= 2 ? 8 : kMpHq / Q), narrow = split_heads(H, 4);
+  const double narrow_us = 3.0 * (double)((g16 * groups(narrow) + 255) / 256);
+  const double wide_us = 5.0 * (double)((g16 * groups(wide) + 255) / 256);
+  if (narrow_us < best.slice_us) best = {16, 4, narrow, narrow_us};
+  if (Q <= 3 && wide_us < best.slice_us) best = {16, 8, wide, wide_us};  // four queries: accumulators for 4 heads only
+  return best;
+}
+
+// Against values projected first: L rows per token through the product (0.85 PFLOP/s, 20 us at least)
+// and the mixing of the projected values (2.6 TB/s, 5 us at least).  28 layers, 3 queries, D = 3584,
+// the layer up to fc1: 16 tokens 92 us that way and 95 this way, 48 tokens 117 and 103, 2048 tokens 2082 and
+// 1074; 20 layers, 1 query, D = 4096: 100 tokens 122 and 131.
+bool meta_project_pays(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q) {
+  if (!meta_project_supports(D, H)) return false;
+  const double product = 2.0 * S * L * D * (double)D / 0.85e9, mixing = 2.0 * S * L * (double)D / 2.6e6;
+  const double first = (product < 20 ? 20 : product) + (mixing < 5 ? 5 : mixing);
+  return 5 + project_plan(S, H, Q).slice_us * (D / 64) < first;
+}
+
+hipError_t launch_meta_attn_project(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q, const void *feats,
+                                    const void *a_fold, const void *w_v, const int32_t *residual_layers, void *pre,
+                                    void *res_out, float *part, hipStream_t s) {
+  int parts;
+  void *packed = (char *)part + meta_packed_offset(S, D, H, Q);
+  hipError_t e = launch_scores(S, L, D, meta_rows_pad(H, Q), feats, a_fold, w_v, packed, part, &parts, s);
+  if (e != hipSuccess) return e;
+  const ResidualLayers res = residuals(Q, residual_layers, res_out);
+  const ProjectPlan plan = project_plan(S, H, Q);
+#define HB_MP(TG_, QT_, NT_, FI_, NS_) \
+  return launch_project<TG_, QT_, NT_, FI_, NS_>(S, L, D, H, Q, plan.hg, parts, feats, packed, res, pre, res_out, part, s)
+  if (plan.tg == 4 && plan.nt == 2) HB_MP(4, 1, 2, 2, 2);
+  if (plan.tg == 4) HB_MP(4, 1, 4, 2, 2);
+  if (plan.nt == 4) {
+    switch (Q) {
+      case 1: HB_MP(16, 1, 4, 8, 1);
+      case 2: HB_MP(16, 2, 4, 8, 1);
+      case 3: HB_MP(16, 3, 4, 8, 1);
+      default: HB_MP(16, 4, 4, 8, 1);
+    }
+  }
+  switch (Q) {
+    case 1: HB_MP(16, 1, 8, 8, 1);
+    case 2: HB_MP(16, 2, 8, 8, 1);
+    default: HB_MP(16, 3, 8, 8, 1);
+  }
+#undef HB_MP
 }
 
 }  // namespace hb

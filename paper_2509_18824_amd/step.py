@@ -177,12 +177,17 @@ class MetaQueryLayer:
         S, L, D = feats.shape
         Q, dev = self.Q, feats.device
         bf = lambda *shape: torch.empty(shape, dtype=torch.bfloat16, device=dev)
-        v_proj, pre, f_c = bf(S * L, D), bf(S * Q, D), bf(S * Q, D)
+        pre, f_c = bf(S * Q, D), bf(S * Q, D)
         res = bf(S * Q, D) if self.residual_layers is not None else None
-        hb.hb_out_project(feats.view(S * L, D), self.w_v, None, v_proj)
-        ws = torch.empty(hb.hb_meta_query_attn_workspace_bytes(S, D, self.H, Q) // 4, dtype=torch.float32, device=dev)
-        hb.hb_meta_query_attn(self.H, Q, feats, v_proj.view(S, L, D), self.a_fold, self.residual_layers,
-                              pre.view(S, Q, D), None if res is None else res.view(S, Q, D), ws)
+        pre_, res_ = pre.view(S, Q, D), None if res is None else res.view(S, Q, D)
+        if hb.hb_meta_query_attn_project_pays(S, L, D, self.H, Q):  # values projected after the mixing
+            ws = alloc_workspace(hb.hb_meta_query_attn_project_workspace_bytes(S, D, self.H, Q), dev)
+            hb.hb_meta_query_attn_project(self.H, Q, feats, self.w_v, self.a_fold, self.residual_layers, pre_, res_, ws)
+        else:
+            v_proj = bf(S * L, D)
+            hb.hb_out_project(feats.view(S * L, D), self.w_v, None, v_proj)
+            ws = torch.empty(hb.hb_meta_query_attn_workspace_bytes(S, D, self.H, Q) // 4, dtype=torch.float32, device=dev)
+            hb.hb_meta_query_attn(self.H, Q, feats, v_proj.view(S, L, D), self.a_fold, self.residual_layers, pre_, res_, ws)
         linear(pre, self.w_o, res, f_c)
         f_c = f_c.view(S, Q * D)
         out = bf(S, self.w_fc1.shape[0])

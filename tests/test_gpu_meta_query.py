@@ -66,6 +66,45 @@ def test_target_model_shape(S):
     _run(S, 41, 24, 28, 3584, 28, 3, [2, 14, 27], peaked=True)
 
 
+@pytest.mark.parametrize("n_tok,L,D,H,Q,layers", [
+    (1, 1, 256, 2, 1, [0]),               # 4 tokens and 2 heads per workgroup: one token, one layer
+    (7, 28, 768, 6, 3, [1, 13, 27]),      # ... a ragged second group
+    (130, 31, 1280, 10, 4, None),         # ... all four queries; odd layers
+    (1025, 5, 512, 4, 2, [0, 4]),         # 4 tokens and 4 heads
+    (421, 17, 1280, 10, 3, [0, 8, 16]),   # 4 heads, the last group with 2
+    (3601, 3, 256, 2, 1, [2]),            # 16 tokens, 4 heads per workgroup, one token in the last group
+    (1203, 4, 768, 6, 2, [0, 3]),
+    (1203, 32, 768, 6, 3, [0, 8, 31]),
+    (3203, 4, 768, 6, 4, None),
+    (2203, 2, 1280, 10, 1, [1]),          # 16 tokens, up to 8 heads
+    (2203, 12, 1280, 10, 2, [1, 11]),
+    (2203, 9, 1280, 10, 3, None),
+])
+def test_values_projected_after_the_mixing(S, n_tok, L, D, H, Q, layers):
+    """hb_meta_query_attn_project at sizes of each of its forms, at the edges of its token groups, head
+    groups and layer tiles: the attention output before the output projection, on sampled tokens
+    (the first, the last and 30 others).  Rounded once to bf16 (2^-9 relative to the element): 4e-3
+    relative in the norm leaves room for the float32 softmax."""
+    import paper_2509_18824_amd as hb
+    x = W.make_meta_inputs(5 + n_tok, n_tok, L, D, H, Q, peaked=True)
+    g = {k: v.cuda() for k, v in x.items()}
+    layer = S.MetaQueryLayer(g["f_q"], g["w_q"], g["w_k"], g["w_v"], g["w_o"], g["w_fc1"], H, residual_layers=layers)
+    new = lambda: torch.full((n_tok, Q, D), float("nan"), dtype=torch.bfloat16, device="cuda")
+    pre, res = new(), new() if layers is not None else None
+    ws = S.alloc_workspace(hb.binding.hb_meta_query_attn_project_workspace_bytes(n_tok, D, H, Q))
+    hb.binding.hb_meta_query_attn_project(H, Q, g["feats"], g["w_v"], layer.a_fold, layers, pre, res, ws)
+    torch.cuda.synchronize()
+    if layers is not None:
+        assert torch.equal(res, g["feats"][:, layers, :])
+    assert torch.isfinite(pre).all()
+    pick = np.unique(np.concatenate([[0, n_tok - 1], np.random.default_rng(5).integers(0, n_tok, 30)]))
+    w = {k: v.float().numpy().astype(np.float64) for k, v in x.items() if k != "feats"}
+    feats = x["feats"][torch.from_numpy(pick)].float().numpy().astype(np.float64)
+    ref = meta_query_attn_ref(w["f_q"], feats, w["w_q"], w["w_k"], w["w_v"], np.eye(D), H)
+    got = pre[torch.from_numpy(pick).cuda()].float().cpu().numpy().astype(np.float64).reshape(len(pick), -1)
+    assert np.linalg.norm(got - ref) <= 4e-3 * np.linalg.norm(ref)
+
+
 def test_prefill_scale_on_sampled_tokens(S):
     """1024 tokens of the target model's shape (one workgroup column per two slices of D in the
     score kernel, 128 token groups); every token is independent of the others, so the oracle

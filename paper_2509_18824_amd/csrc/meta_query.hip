@@ -447,8 +447,8 @@ __global__ __launch_bounds__(kMpThreads) void meta_project_kernel(
     u32x4 *stage = lds_f + (kt % NS) * kStagePieces + wave * 64;
 #pragma unroll
     for (int i = 0; i < FI; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(f_rsrc, (lptr_t)(stage + i * kMpWaves * 64), 16, f_src,
-                                               i * kMpWaves * 8 * dp * 16 + k * 128, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(f_rsrc, (lptr_t)(stage + i * kMpWaves * 64), 16,
+                                               f_src + i * kMpWaves * 8 * dp * 16, k * 128, 0, 0);
   };
   issue_feats(0);
 

@@ -87,6 +87,20 @@ hipError_t launch_lmhead_init(unsigned long long *keys, int32_t M, hipStream_t s
 hipError_t launch_lmhead_finish(const unsigned long long *keys, int32_t M, int32_t V,
                                 int32_t *out_ids, float *out_max, hipStream_t s);
 
+// Few tokens (proj_stream.hip): N counts weight rows (for the gated projection gate and up rows together)
+enum class StreamKind { kPlain, kRope, kGlu };
+struct StreamArgs {
+  const bf16_t *residual;  // plain: [M, N] or null
+  bf16_t *out;             // plain [M, N], gated [M, N / 2]
+  const bf16_t *bias;      // rotary: [N] or null
+  const float *cos, *sin;  // [M, 64]
+  bf16_t *q, *k, *v;       // [M, Hq, 128], [M, Hkv, 128], [M, Hkv, 128]
+  int Hq, Hkv;
+};
+bool proj_stream_takes(int32_t M, int32_t K, int32_t N);
+hipError_t launch_proj_stream(StreamKind kind, int32_t M, int32_t K, int32_t N, const void *hidden, const void *weight,
+                              const StreamArgs &sa, hipStream_t s);
+
 bool proj_mfma_supports(int32_t M, int32_t K, int32_t N);
 // part: fp32 scratch of proj_workspace_bytes(M, K, N) bytes for the split-K path, or null (then: one workgroup per tile)
 size_t proj_workspace_bytes(int32_t M, int32_t K, int32_t N);

@@ -540,6 +540,10 @@ hipError_t launch_qkv_rope(int32_t M, int32_t K, int32_t Hq, int32_t Hkv, const 
   QkvArgs qa = {(const bf16_t *)bias, cos, sin, (bf16_t *)q, (bf16_t *)k, (bf16_t *)v, Hq, Hkv};
   StoreArgs sa = {nullptr, nullptr};
   const int V = (Hq + 2 * Hkv) * kHeadDim;
+  if (proj_stream_takes(M, K, V)) {
+    const StreamArgs st = {nullptr, nullptr, qa.bias, cos, sin, qa.q, qa.k, qa.v, Hq, Hkv};
+    return launch_proj_stream(StreamKind::kRope, M, K, V, hidden, w_qkv, st, s);
+  }
   const SplitPlan plan = part ? split_plan(M, K, V) : SplitPlan{1, 1};
   if (plan.ks > 1) return launch_splitk<true, false>(M, K, V, plan, hidden, w_qkv, qa, sa, part, s);
   return dispatch<true, false>(M, K, V, hidden, w_qkv, qa, sa, s);
@@ -549,6 +553,7 @@ hipError_t launch_linear(int32_t M, int32_t K, int32_t N, const void *x, const v
                          float *part, hipStream_t s) {
   QkvArgs qa = {};
   StoreArgs sa = {(const bf16_t *)residual, (bf16_t *)out};
+  if (proj_stream_takes(M, K, N)) return launch_proj_stream(StreamKind::kPlain, M, K, N, x, w, {sa.residual, sa.out}, s);
   const SplitPlan plan = part ? split_plan(M, K, N) : SplitPlan{1, 1};
   if (plan.ks > 1) return launch_splitk<false, false>(M, K, N, plan, x, w, qa, sa, part, s);
   return dispatch<false, false>(M, K, N, x, w, qa, sa, s);
@@ -558,6 +563,7 @@ hipError_t launch_swiglu(int32_t M, int32_t K, int32_t F, const void *x, const v
                          hipStream_t s) {
   QkvArgs qa = {};
   StoreArgs sa = {nullptr, (bf16_t *)out};
+  if (proj_stream_takes(M, K, 2 * F)) return launch_proj_stream(StreamKind::kGlu, M, K, 2 * F, x, w_gate_up, {nullptr, sa.out}, s);
   const SplitPlan plan = part ? split_plan(M, K, 2 * F) : SplitPlan{1, 1};
   if (plan.ks > 1) return launch_splitk<false, true>(M, K, 2 * F, plan, x, w_gate_up, qa, sa, part, s);
   return dispatch<false, true>(M, K, 2 * F, x, w_gate_up, qa, sa, s);

@@ -112,6 +112,28 @@ def test_output_projection_split_over_k(hb, T, K, N, res):
     _out_case(hb, T, K, N, res, True)
 
 
+# Up to 32 tokens take the streaming kernel: 8, 16 and 32 tokens are its token tiles; 8 K steps give every
+# wavefront one, 9 the first one two; 64 steps are the most whose tokens stay in registers; 16-row
+# tiles with and without a remainder (N = 4: no partner rows; 20, 12); more tiles than workgroups
+@pytest.mark.parametrize("T,K,N,res", [(1, 512, 4, True), (8, 576, 20, False), (9, 4096, 36, True), (16, 4160, 12, True),
+                                       (17, 512, 100, False), (32, 4160, 264, True), (33, 4160, 264, True),
+                                       (8, 4160, 4620, True), (20, 576, 16404, False), (3, 1024, 9000, True)])
+def test_output_projection_of_few_tokens(hb, T, K, N, res):
+    _out_case(hb, T, K, N, res, False)
+    _out_case(hb, T, K, N, res, True)
+
+
+@pytest.mark.parametrize("T,K,Hq,Hkv,bias", [(1, 512, 1, 1, True), (8, 3584, 28, 4, True), (16, 4160, 3, 1, False),
+                                             (17, 576, 6, 2, True), (32, 4160, 28, 4, False), (24, 1024, 16, 2, True)])
+def test_qkv_projection_of_few_tokens(hb, T, K, Hq, Hkv, bias):
+    _qkv_case(hb, T, K, Hq, Hkv, bias, False)
+
+
+@pytest.mark.parametrize("T,K,F", [(1, 512, 4), (7, 576, 12), (8, 3584, 18944), (16, 4160, 100), (31, 1024, 9004), (32, 4160, 264)])
+def test_gated_silu_projection_of_few_tokens(hb, T, K, F):
+    test_gated_silu_projection(hb, T, K, F, False)
+
+
 def _out_case(hb, T, K, N, res, with_workspace):
     g = torch.Generator().manual_seed(T + K + N)
     x = torch.randn((T, K), generator=g).to(torch.bfloat16)

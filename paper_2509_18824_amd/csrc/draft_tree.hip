@@ -82,22 +82,12 @@ struct Partial {  // one per (row, chunk), followed in memory by k keys
   float max, sum;
 };
 
-constexpr int kChunkMax = 16384;            // logits per chunk: 64 per thread, held in registers
-constexpr int kPerThread = kChunkMax / kThreads;
+// Logits per chunk: 64 per thread, held in registers.  Always the most a workgroup holds: it takes 5
+// to 10 us whatever its chunk, and every chunk adds k winners to the merge, whose ranking is quadratic
+// (16 rows x 152064 in chunks of 3072: 33 us, of 16384: 13 us).
+constexpr int kChunk = 16384;
+constexpr int kPerThread = kChunk / kThreads;
 constexpr int kListCap = 2048;              // candidates that pass the threshold
-
-// Position inside the chunk of a thread's j-th value, or n when the thread has no such value.
-// Vector layout (rows whose chunk starts 16-byte aligned; loads of PER values, consecutive lanes
-// consecutive loads): value e of load q sits at (q * 256 + tid) * PER + e while that load lies
-// inside the n_full full vectors of the chunk; value kPerThread is the thread's share of the up
-// to PER - 1 values behind them.  Scalar layout: value j sits at j * 256 + tid.
-template <int PER>
-__device__ __forceinline__ int pos_of(bool vec, int j, int n, int n_full) {
-  const int tid = (int)threadIdx.x;
-  if (!vec) return j < kPerThread ? min(n, j * kThreads + tid) : n;
-  if (j == kPerThread) return min(n, n_full * PER + tid);
-  return (j / PER) * kThreads + tid < n_full ? ((j / PER) * kThreads + tid) * PER + (j % PER) : n;
-}
 
 // Pass 1 of the top-k: one workgroup per (chunk, row).  The chunk goes from memory straight into
 // registers (every load is in flight before the first value is used).  The k best entries are
@@ -106,66 +96,28 @@ __device__ __forceinline__ int pos_of(bool vec, int j, int n, int n_full) {
 // >= T can be among the k best; those few are collected in LDS (as order-preserving keys) and
 // the k best picked there by counting ranks.
 // Many equal values can let more pass than the list holds; then k rounds of a workgroup-wide
-// maximum run over the registers instead (same result, slower).
-template <typename T>
-__global__ __launch_bounds__(kThreads) void topk_chunk_kernel(int V, int k, int chunk, int n_chunks,
-                                                              const T *__restrict__ logits,
-                                                              unsigned char *__restrict__ work) {
-  __shared__ unsigned long long red[kThreads / 64];
-  __shared__ float fred[kThreads / 64];
-  __shared__ unsigned long long win[kMaxTopK];
-  __shared__ unsigned long long list[kListCap];
-  __shared__ int list_n;
-  __shared__ float thr_w[kThreads / 64];
-  constexpr int PER = 16 / (int)sizeof(T);
-  const int c = blockIdx.x, m = blockIdx.y;
-  const int tid = threadIdx.x;
-  const int v0 = c * chunk;
-  const int n = min(chunk, V - v0);
-  const T *row = logits + (size_t)m * V + v0;
-  const int n_full = n / PER;
-  const bool vec = (((size_t)row) & 15) == 0 && n_full > 0;
-  const float ninf = -__builtin_huge_valf();
-  // every load is unconditional (addresses clamped into the chunk) so that all of them are in
-  // flight together; what a thread does not own is replaced by -inf afterwards
-  float x[kPerThread + 1];
-  if (vec) {
-    u32x4 w[kPerThread / PER];
-#pragma unroll
-    for (int q = 0; q < kPerThread / PER; ++q) w[q] = ((const u32x4 *)row)[min(q * kThreads + tid, n_full - 1)];
-    const float tail = load_f32<T>(row + min(n_full * PER + tid, n - 1));
-#pragma unroll
-    for (int q = 0; q < kPerThread / PER; ++q) {
-      const bool own = q * kThreads + tid < n_full;
-#pragma unroll
-      for (int e = 0; e < PER; ++e) {
-        float f;
-        if (sizeof(T) == 4) f = __uint_as_float(w[q][e]);
-        else f = __uint_as_float((e & 1) ? (w[q][e >> 1] & 0xffff0000u) : (w[q][e >> 1] << 16));
-        x[q * PER + e] = (own && f == f) ? f : ninf;
-      }
-    }
-    x[kPerThread] = (n_full * PER + tid < n && tail == tail) ? tail : ninf;
-  } else {
-#pragma unroll
-    for (int j = 0; j < kPerThread; ++j) {
-      const int p = j * kThreads + tid;
-      const float f = load_f32<T>(row + min(p, n - 1));
-      x[j] = (p < n && f == f) ? f : ninf;
-    }
-    x[kPerThread] = ninf;
-  }
-  if (tid == 0) list_n = 0;
-  float mt = ninf;
-#pragma unroll
-  for (int j = 0; j <= kPerThread; ++j) mt = fmaxf(mt, x[j]);
-  const float mx = wg_max_f(mt, fred);
-  // Threshold T with at least k values >= T in the chunk: every wavefront takes the k-th largest
-  // of its 64 lane maxima (a lane counts the maxima strictly above its own, lane by lane through
-  // readlane; the smallest maximum with fewer than k above it is the k-th largest), which k of its
-  // own values reach; T is the largest of the wavefronts' thresholds.  A wavefront with fewer
-  // than k lanes holding values sets no threshold; if none does, everything passes.
-  const bool has = pos_of<PER>(vec, 0, n, n_full) < n || pos_of<PER>(vec, kPerThread, n, n_full) < n;
+// maximum run over the chunk instead (same result, slower).
+//
+// What bounds it is vector instruction issue, and code that has to stay in the instruction cache.
+// The path from registers works by 16-byte pieces, without NaN tests and without a branch per value: a
+// NaN or an infinity shows in the sum of exponentials, and such a chunk is done again with a test per
+// value.  160 rows x 152064 float32 with the merge 33.7 -> 28.8 us (24 us = 4 TB/s in this pass), 16 rows 33 -> 13 us,
+// one row 42 -> 11 us (those two mostly by larger chunks).
+struct ChunkShared {
+  unsigned long long red[kThreads / 64];
+  float fred[kThreads / 64];
+  unsigned long long win[kMaxTopK];
+  unsigned long long list[kListCap];
+  int list_n;
+  float thr_w[kThreads / 64];
+};
+
+// Threshold T with at least k values >= T in the chunk: every wavefront takes the k-th largest
+// of its 64 lane maxima (a lane counts the maxima strictly above its own, lane by lane through
+// readlane; the smallest maximum with fewer than k above it is the k-th largest), which k of its
+// own values reach; T is the largest of the wavefronts' thresholds.  A wavefront with fewer
+// than k lanes holding values (`has`) sets no threshold; if none does, everything passes.
+__device__ __forceinline__ float chunk_threshold(float mt, bool has, int k, float *thr_w) {
   int above = 0;
 #pragma unroll
   for (int l = 0; l < 64; ++l) {
@@ -176,52 +128,158 @@ __global__ __launch_bounds__(kThreads) void topk_chunk_kernel(int V, int k, int 
   float tw = (has && above < k) ? mt : __builtin_huge_valf();
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) tw = fminf(tw, __shfl_xor(tw, off, 64));
-  if (holders < k) tw = ninf;
-  if ((tid & 63) == 0) thr_w[tid >> 6] = tw;
+  if (holders < k) tw = -__builtin_huge_valf();
+  if ((threadIdx.x & 63) == 0) thr_w[threadIdx.x >> 6] = tw;
   __syncthreads();
-  const float thr = fmaxf(fmaxf(thr_w[0], thr_w[1]), fmaxf(thr_w[2], thr_w[3]));
-  float sum = 0.f;
-  if (thr > ninf) {
-    // the common case: values the thread does not own are -inf, fail the test and add exp(-inf) = 0
-    const float c1 = 1.4426950408889634f, c0 = -mx * 1.4426950408889634f;
+  return fmaxf(fmaxf(thr_w[0], thr_w[1]), fmaxf(thr_w[2], thr_w[3]));
+}
+
+// A chunk from registers.  False: not done (a NaN, an infinity, too many candidates); every thread of
+// the workgroup returns the same.  The 16-byte pieces of memory are the unit: a piece's maximum is
+// kept, and the few pieces that reach the threshold are read again.  The values before the first and
+// behind the last whole piece go to one thread each.
+template <typename T>
+__device__ __forceinline__ bool fast_chunk(const T *row, int v0, int n, int k, ChunkShared &sh, float &mx, float &sum) {
+  constexpr int PER = 16 / (int)sizeof(T), kPieces = kPerThread / PER;
+  const int tid = threadIdx.x;
+  const int head = min(n, (int)((0u - (uint32_t)(uintptr_t)row) & 15u) / (int)sizeof(T));
+  const int n_full = (n - head) / PER, rest = n - n_full * PER;  // rest: head and tail together
+  const u32x4 *src = (const u32x4 *)(row + head);
+  const float ninf = -__builtin_huge_valf();
+  const int single = tid < head ? tid : tid + n_full * PER;      // this thread's value outside the pieces
+  const float tail = tid < rest ? load_f32<T>(row + single) : ninf;
+  u32x4 w[kPieces];
+  if (n_full > 0) {
 #pragma unroll
-    for (int j = 0; j <= kPerThread; ++j) {
-      sum += __builtin_amdgcn_exp2f(fmaf(x[j], c1, c0));
-      if (x[j] >= thr) {
-        const int at = atomicAdd(&list_n, 1);
-        if (at < kListCap) list[at] = sel_key(x[j], (uint32_t)(v0 + pos_of<PER>(vec, j, n, n_full)));
-      }
-    }
-  } else {
-    const bool any = mx > ninf;
+    for (int q = 0; q < kPieces; ++q) w[q] = src[min(q * kThreads + tid, n_full - 1)];
+  }
+  if (tid == 0) sh.list_n = 0;
+  auto value = [](const u32x4 &v, int e) {
+    if (sizeof(T) == 4) return __uint_as_float(v[e]);
+    return __uint_as_float((e & 1) ? (v[e >> 1] & 0xffff0000u) : (v[e >> 1] << 16));
+  };
+  auto max3 = [](float x, float y, float z) {  // fmaxf would quieten every operand first
+    float r;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "v"(y), "v"(z));
+    return r;
+  };
+  float pm[kPieces], mt = tail;
 #pragma unroll
-    for (int j = 0; j <= kPerThread; ++j) {
-      const int p = pos_of<PER>(vec, j, n, n_full);
-      if (any) sum += __expf(x[j] - mx);
-      if (p < n) {
-        const int at = atomicAdd(&list_n, 1);
-        if (at < kListCap) list[at] = sel_key(x[j], (uint32_t)(v0 + p));
-      }
+  for (int q = 0; q < kPieces; ++q) {
+    pm[q] = ninf;
+    if (q * kThreads < n_full) {
+      float m = max3(value(w[q], 0), value(w[q], 1), value(w[q], 2));
+      m = PER == 4 ? max3(m, m, value(w[q], 3)) : max3(m, value(w[q], 3), value(w[q], 4));
+      if (PER == 8) m = max3(max3(m, value(w[q], 5 % PER), value(w[q], 6 % PER)), m, value(w[q], 7 % PER));
+      pm[q] = q * kThreads + tid < n_full ? m : ninf;
+      mt = max3(mt, mt, pm[q]);
     }
   }
-  sum = wg_sum_f(sum, fred);  // its barriers also publish list and list_n
-  const int cnt = list_n;
-  if (cnt <= kListCap) {
-    rank_select(list, cnt, k, win);
-  } else {
-    unsigned long long last = ~0ull;
-    for (int r = 0; r < k; ++r) {
-      unsigned long long best = 0ull;
+  mx = wg_max_f(mt, sh.fred);
+  if (!(mx > ninf)) {  // nothing above -inf: the lowest ids win
+    if (tid < k) sh.win[tid] = tid < n ? sel_key(ninf, (uint32_t)(v0 + tid)) : 0ull;
+    sum = 0.f;
+    return true;
+  }
+  const float thr = chunk_threshold(mt, tid < n_full || tid < rest, k, sh.thr_w);
+  const float c1 = 1.4426950408889634f, c0 = -mx * 1.4426950408889634f;
+  float s = __builtin_amdgcn_exp2f(fmaf(tail, c1, c0));
+  uint32_t reach = 0;  // pieces with a value that reaches the threshold
 #pragma unroll
-      for (int j = 0; j <= kPerThread; ++j) {
-        const int p = pos_of<PER>(vec, j, n, n_full);
-        const unsigned long long key = p < n ? sel_key(x[j], (uint32_t)(v0 + p)) : 0ull;
-        best = (key < last && key > best) ? key : best;
-      }
-      best = wg_max_key(best, red);
-      if (tid == 0) win[r] = best;
-      last = best;
+  for (int q = 0; q < kPieces; ++q) {
+    if (q * kThreads < n_full) {
+      float p0 = 0.f, p1 = 0.f;
+#pragma unroll
+      for (int e = 0; e < PER; ++e) ((e & 1) ? p1 : p0) += __builtin_amdgcn_exp2f(fmaf(value(w[q], e), c1, c0));
+      s += q * kThreads + tid < n_full ? p0 + p1 : 0.f;
+      reach |= q * kThreads + tid < n_full && pm[q] >= thr ? 1u << q : 0u;
     }
+  }
+  auto offer = [&](float x, int pos) {
+    if (x >= thr) {
+      const int at = atomicAdd(&sh.list_n, 1);
+      if (at < kListCap) sh.list[at] = sel_key(x, (uint32_t)(v0 + pos));
+    }
+  };
+  if (tid < rest) offer(tail, single);
+  while (reach) {
+    const int at = __builtin_ctz(reach) * kThreads + tid;
+    reach &= reach - 1;
+    const u32x4 v = src[at];
+#pragma unroll 1
+    for (int e = 0; e < PER; ++e) {
+      const uint32_t u = sizeof(T) == 4 ? (e < 2 ? (e ? v[1] : v[0]) : (e == 2 ? v[2] : v[3]))
+                                        : ((e < 4 ? (e < 2 ? v[0] : v[1]) : (e < 6 ? v[2] : v[3])) << (e & 1 ? 0 : 16)) & 0xffff0000u;
+      offer(__uint_as_float(u), head + at * PER + e);
+    }
+  }
+  sum = wg_sum_f(s, sh.fred);  // its barriers also publish list and list_n
+  const int cnt = sh.list_n;
+  if (!(sum == sum) || cnt > kListCap) return false;
+  rank_select(sh.list, cnt, k, sh.win);
+  return true;
+}
+
+// The same for any values, read from memory in every pass; NaN counts as -inf.
+template <typename T>
+__device__ __forceinline__ void any_chunk(const T *row, int v0, int n, int k, ChunkShared &sh, float &mx, float &sum) {
+  const int tid = threadIdx.x;
+  const float ninf = -__builtin_huge_valf();
+  auto value = [&](int i) {
+    const float f = load_f32<T>(row + i);
+    return f == f ? f : ninf;
+  };
+  if (tid == 0) sh.list_n = 0;
+  float mt = ninf;
+#pragma unroll 4
+  for (int i = tid; i < n; i += kThreads) mt = fmaxf(mt, value(i));
+  mx = wg_max_f(mt, sh.fred);
+  const float thr = chunk_threshold(mt, tid < n, k, sh.thr_w);
+  const float c1 = 1.4426950408889634f, c0 = -mx * 1.4426950408889634f;
+  float s = 0.f;
+#pragma unroll 4
+  for (int i = tid; i < n; i += kThreads) {
+    const float x = value(i);
+    if (mx > ninf) s += __builtin_amdgcn_exp2f(fmaf(x, c1, c0));
+    if (x >= thr) {
+      const int at = atomicAdd(&sh.list_n, 1);
+      if (at < kListCap) sh.list[at] = sel_key(x, (uint32_t)(v0 + i));
+    }
+  }
+  sum = wg_sum_f(s, sh.fred);  // its barriers also publish list and list_n
+  const int cnt = sh.list_n;
+  if (cnt <= kListCap) {
+    rank_select(sh.list, cnt, k, sh.win);
+    return;
+  }
+  unsigned long long last = ~0ull;
+  for (int r = 0; r < k; ++r) {
+    unsigned long long best = 0ull;
+#pragma unroll 4
+    for (int i = tid; i < n; i += kThreads) {
+      const unsigned long long key = sel_key(value(i), (uint32_t)(v0 + i));
+      best = (key < last && key > best) ? key : best;
+    }
+    best = wg_max_key(best, sh.red);
+    if (tid == 0) sh.win[r] = best;
+    last = best;
+  }
+}
+
+template <typename T>
+__global__ __launch_bounds__(kThreads, 4) void topk_chunk_kernel(int V, int k, int chunk, int n_chunks,
+                                                                 const T *__restrict__ logits,
+                                                                 unsigned char *__restrict__ work) {
+  __shared__ ChunkShared sh;
+  const int c = blockIdx.x, m = blockIdx.y;
+  const int tid = threadIdx.x;
+  const int v0 = c * chunk;
+  const int n = min(chunk, V - v0);
+  const T *row = logits + (size_t)m * V + v0;
+  float mx, sum;
+  if (!fast_chunk(row, v0, n, k, sh, mx, sum)) {
+    __syncthreads();  // given up: its list is done with
+    any_chunk(row, v0, n, k, sh, mx, sum);
   }
   __syncthreads();
   unsigned char *slot = work + ((size_t)m * n_chunks + c) * (sizeof(Partial) + (size_t)k * 8);
@@ -231,7 +289,7 @@ __global__ __launch_bounds__(kThreads) void topk_chunk_kernel(int V, int k, int 
     p.sum = sum;
     *(Partial *)slot = p;
   }
-  if (tid < k) ((unsigned long long *)(slot + sizeof(Partial)))[tid] = win[tid];
+  if (tid < k) ((unsigned long long *)(slot + sizeof(Partial)))[tid] = sh.win[tid];
 }
 
 __global__ __launch_bounds__(kThreads) void topk_merge_kernel(int V, int k, int n_chunks,
@@ -427,26 +485,15 @@ __global__ __launch_bounds__(kFinalThreads) void tree_finalize_kernel(
 
 }  // namespace
 
-int32_t topk_chunk_elems(int32_t M, int32_t V) {
-  // at least about four workgroups per CU in pass 1, chunks of 2048 .. 16384 logits
-  int64_t want = (1024 + M - 1) / (M > 0 ? M : 1);
-  if (want < 1) want = 1;
-  int64_t chunk = ((int64_t)V + want - 1) / want;
-  chunk = (chunk + 1023) / 1024 * 1024;  // 16-byte alignment of a chunk's start follows the row's
-  if (chunk < 2048) chunk = 2048;
-  if (chunk > 16384) chunk = 16384;
-  return (int32_t)chunk;
-}
-
 size_t topk_workspace_bytes(int32_t M, int32_t V, int32_t k) {
-  const int chunk = topk_chunk_elems(M, V);
+  const int chunk = kChunk;
   const size_t n_chunks = ((size_t)V + chunk - 1) / chunk;
   return (size_t)M * n_chunks * (sizeof(Partial) + (size_t)k * 8);
 }
 
 hipError_t launch_topk_logprob(int32_t dtype, int32_t M, int32_t V, int32_t k, const void *logits, int32_t *out_ids,
                                float *out_logp, void *work, hipStream_t s) {
-  const int chunk = topk_chunk_elems(M, V);
+  const int chunk = kChunk;
   const int n_chunks = (V + chunk - 1) / chunk;
   dim3 grid((unsigned)n_chunks, (unsigned)M);
   if (dtype == HB_BF16)

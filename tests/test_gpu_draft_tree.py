@@ -63,6 +63,33 @@ def test_topk_rows_of_whole_vectors(S, M, V, k, bf16, ties):
     _topk_case(S, W.make_draft_logits(41 + M, M, V, ties=ties), k, bf16=bf16)
 
 
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("M,V,k", [(6, 16385, 10), (9, 16391, 32), (5, 33003, 7), (8, 9, 9), (4, 1027, 12), (17, 2, 1)])
+def test_topk_rows_that_start_anywhere(S, M, V, k, bf16):
+    """Rows of odd length start at every offset inside a 16-byte piece: values before the first and
+    behind the last whole piece, chunks of one value, rows without a whole piece."""
+    _topk_case(S, W.make_draft_logits(51 + M, M, V), k, bf16=bf16)
+
+
+def test_topk_masked_and_not_finite(S):
+    """Masked ranges (-inf) that fill whole chunks and all but a few values of one, a plateau of
+    more equal values than the candidate list holds, and NaN entries, which count as -inf."""
+    x = W.make_draft_logits(61, 5, 40001)
+    x[0, 16384:32768] = -np.inf
+    x[1, 100:] = -np.inf
+    x[2, 5000:9000] = 50.0
+    _topk_case(S, x, 10)
+    _topk_case(S, x, 10, bf16=True)
+    y = x.copy()
+    y[3, ::3] = np.nan
+    y[4, 16384:32768] = np.nan
+    x[3, ::3] = -np.inf
+    x[4, 16384:32768] = -np.inf
+    ids, logp = S.topk_logprob(torch.from_numpy(y).cuda(), 10)
+    rid, rlogp = topk_logprob_ref(x, 10)
+    assert np.array_equal(ids.cpu().numpy(), rid) and np.abs(logp.cpu().numpy() - rlogp).max() <= LOGP_TOL
+
+
 def test_topk_full_vocabulary_every_row_of_a_level(S):
     """The shape of one level of the batch-16 workload: 160 rows (16 sequences x 10 frontier
     nodes) over the vocabulary of 152064, float32; and the root level's 16 rows in bf16."""

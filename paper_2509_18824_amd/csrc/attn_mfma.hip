@@ -332,7 +332,7 @@ __device__ __forceinline__ void attend_block(bool partial, const u32x4 *__restri
 // wavefronts 0-3 and V by wavefronts 4-7 (NW = 8).
 template <int TPW, int NW, int NS>
 __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mfma_kernel(
-    hb_attn_desc d, int splits, int chunk_tokens, int workers, int row_groups, const u32x4 *__restrict__ q, const u32x4 *__restrict__ k_tree,
+    hb_attn_desc d, int splits, int chunk_tokens, int workers, int min_per, int row_groups, const u32x4 *__restrict__ q, const u32x4 *__restrict__ k_tree,
     const u32x4 *__restrict__ v_tree, const u32x4 *__restrict__ k_pool, const u32x4 *__restrict__ v_pool,
     const int32_t *__restrict__ block_table, const int32_t *__restrict__ prefix_len,
     const int32_t *__restrict__ node_offset, const int32_t *__restrict__ parent, bf16_t *__restrict__ out,
@@ -363,13 +363,12 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mfma_kernel(
   //    sequence (unit = (b, g, c)).
   //  * workers > 0 (batch <= 64): work-proportional.  The 64-key tiles of all sequences (tree
   //    tile first, then the prefix tiles) form one line; worker w of kv head g (unit = (w, g))
-  //    takes tiles [w * per, (w + 1) * per) of it, per = max(kMinPer, ceil(total / workers)),
+  //    takes tiles [w * per, (w + 1) * per) of it, per = max(min_per, ceil(total / workers)),
   //    whatever sequences they belong to.  Every workgroup finds the line by itself: lane b reads
   //    prefix_len[b], a prefix sum over the lanes gives each sequence's place.  A sequence cut
   //    by worker boundaries gets one partial slot per piece (consecutive workers, consecutive
   //    slots); the piece that ends it announces the unused slots as empty; a sequence that lies
   //    inside one worker's range is written out directly and slot 0 tells the merge so.
-  constexpr int kMinPer = NW == 8 ? 16 : 8;
   constexpr int kRestart = 4;
   int g, seg_b = 0, lo = 0, hi = 0, per = 1, w_id = 0, al_k = 0, al_n = 0;
   bool aligned = false;
@@ -394,21 +393,25 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mfma_kernel(
     }
     const int total = __builtin_amdgcn_readfirstlane(__shfl(cum, 63, 64));
     per = (total + workers - 1) / workers;
-    per = per < kMinPer ? kMinPer : per;
+    per = per < min_per ? min_per : per;
     // The alternative: the same number of workers for every sequence, each sequence cut into
     // pieces of equal length.  No worker then has to start over on a second sequence (which
     // costs about kRestart tiles' time), but the longest sequence sets the pace.  Both plans
     // are known here; take the one that finishes first.
     al_k = workers / d.batch;
     if (al_k >= 1) {
-      int nb = (tb + kMinPer - 1) / kMinPer;
+      int nb = (tb + min_per - 1) / min_per;
       nb = nb < 1 ? 1 : (nb > al_k ? al_k : nb);
       nb = nb > splits ? splits : nb;
-      al_n = nb;                                   // pieces of sequence `lane`
       int len = lane < d.batch ? (tb + nb - 1) / nb : 0;
 #pragma unroll
       for (int off = 32; off > 0; off >>= 1) len = max(len, __shfl_xor(len, off, 64));
-      aligned = __builtin_amdgcn_readfirstlane(len) <= per + kRestart;
+      len = __builtin_amdgcn_readfirstlane(len);
+      aligned = len <= per + kRestart;
+      // pieces of sequence `lane`: the longest piece sets the pace, so the others are no shorter than
+      // they must be (fewer prologues, fewer partials)
+      al_n = len > 0 ? (tb + len - 1) / len : 1;
+      al_n = al_n < 1 ? 1 : al_n;
     }
     if (aligned) {
       seg_b = w_id / al_k;
@@ -784,7 +787,7 @@ hipError_t launch(int row_groups, const hb_attn_desc &d, const AttnPlan &plan, c
   auto kern = attn_mfma_kernel<TPW, NW, NS>;
   hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
   if (e != hipSuccess) return e;
-  kern<<<grid, 64 * NW, kLdsBytes, s>>>(d, plan.splits, plan.chunk_tokens, plan.workers, row_groups, (const u32x4 *)q, (const u32x4 *)k_tree,
+  kern<<<grid, 64 * NW, kLdsBytes, s>>>(d, plan.splits, plan.chunk_tokens, plan.workers, plan.min_per, row_groups, (const u32x4 *)q, (const u32x4 *)k_tree,
                                     (const u32x4 *)v_tree, (const u32x4 *)k_pool, (const u32x4 *)v_pool,
                                     block_table, prefix_len, node_offset, parent, (bf16_t *)out, lse, part_o,
                                     part_ml);

@@ -436,7 +436,7 @@ int32_t hb_tree_finalize(int32_t B, int32_t K, int32_t T, int32_t n_nodes, const
  *   workspace   device, hb_meta_query_attn_workspace_bytes(S, D, H, Q) bytes (0 for an unsupported
  *               shape), 4-byte aligned, overwritten: partial scores of the tokens, about 12 KB per
  *               token and per share of D that a workgroup column takes (14 shares of D = 3584
- *               for up to about 300 tokens, one from 4096 tokens on)
+ *               for up to 144 tokens, one beyond 1024 tokens)
  * Errors: INVALID_ARG (sizes < 1, H not dividing D, residual layer outside [0, L), NULL or
  * misaligned pointers), UNSUPPORTED (D % 256 != 0, (D / H) % 8 != 0, H * Q > 96, Q > 4, L > 32),
  * WORKSPACE, DEVICE.  S == 0 is a no-op.

@@ -11,11 +11,12 @@
 // accuracy against projecting keys in fp32.
 //
 // meta_scores_kernel: the scores of all tokens are one dense product A [H Q, D] x feats^T
-// [D, S L].  A workgroup takes eight tokens and a range of 256-feature slices of D; it stages the
-// slice of A (both halves) in LDS once and its four wavefronts, two tokens each, run MFMA
-// 16x16x32 with the A fragments from LDS and the tokens' features straight from memory in
-// fragment layout, so A crosses the vector memory path once per eight tokens.  With few tokens
-// the slices are spread over several workgroups, which write partial scores (fp32) to a workspace.
+// [D, S L].  A workgroup takes eight tokens and a range of D, 64 features at a time: the tokens'
+// features and both halves of A go from memory to LDS directly, one step ahead of the matrix
+// instructions (16x16x32); four pairs of wavefronts take two tokens each and half of the rows of
+// A.  With few tokens D is spread over several workgroups, which write partial scores (fp32) to a
+// workspace.  2048 tokens, 28 layers, D = 3584: 130 us with W_v's
+// rearrangement (411 MB of features and nearly as much of A through the L2s); with the features loaded in fragment order, four rows per four lanes, 183 us.
 // meta_mix_kernel, one workgroup per token (and per 4096 features): sums the partial scores, one thread per (head, query)
 // row does the softmax over the L layers, and every thread then mixes the token's projected values
 // (v_proj = f_i W_v^T, a plain linear layer run beforehand) for eight feature columns of all Q
@@ -34,15 +35,13 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 256;       // the two set-up kernels
 constexpr int kWaves = 4;
-constexpr int kScoreWaves = 4;      // wavefronts of meta_scores_kernel
+constexpr int kScoreWaves = 8;      // wavefronts of meta_scores_kernel
 constexpr int kScoreThreads = 64 * kScoreWaves;
 constexpr int kTokPerWave = 2;      // tokens whose scores one wavefront accumulates
-constexpr int kTokPerGroup = kScoreWaves * kTokPerWave;
-constexpr int kSlice = 256;         // features of A staged in LDS at a time
-constexpr int kSlicePieces = kSlice / 8;       // 16-byte pieces per row of a slice
-constexpr int kSliceSteps = kSlice / 32;       // MFMA steps per slice
-constexpr int kRowPieces = kSlicePieces + 1;   // LDS row stride in pieces: fragment reads of 16 rows hit distinct banks
+constexpr int kTokPerGroup = 8;
+constexpr int kSlice = 256;         // features: the unit in which D is dealt to workgroups
 constexpr int kMixThreads = 512;      // meta_mix_kernel: one thread per eight feature columns
+constexpr int kBufferFlags = 0x00027000;  // untyped 32-bit elements
 constexpr int kMaxParts = 16;         // workgroup columns of the score kernel
 constexpr int kMaxRowTiles = 6;   // H * Q <= 96
 constexpr int kMaxRows = 16 * kMaxRowTiles;
@@ -90,101 +89,91 @@ struct ResidualLayers {
   int32_t on;
 };
 
-// part[p][s][row][l] (row stride 32): the scores of token s summed over the slices that
-// workgroup column p covers
-// Workgroups behind the scores' (score_wgs) rearrange W_v for meta_project_kernel, where that follows.
+// The first pack_wgs workgroups rearrange W_v for meta_project_kernel, where that follows.
 __device__ void pack_values(int wave, int waves, int D, const u32x4 *__restrict__ w_v, u32x4 *__restrict__ packed);
 
+constexpr int kScoreFeatRows = kTokPerGroup * kMaxL;                    // LDS rows of 64 features per stage
+constexpr int kScoreStage = (kScoreFeatRows + 2 * kMaxRows) * 8;        // pieces
+constexpr int kScoreLoads = (kScoreFeatRows + 2 * kMaxRows) / 8 / kScoreWaves;  // of a wavefront per step
+constexpr size_t kScoreLds = 2 * (size_t)kScoreStage * sizeof(u32x4);
+
+// part[p][s][row][l] (row stride 32): the scores of token s summed over the slices that
+// workgroup column p covers
 __global__ __launch_bounds__(kScoreThreads) void meta_scores_kernel(int S, int L, int D, int row_tiles,
-                                                                    int slices_per_wg, int token_groups, int score_wgs,
+                                                                    int slices_per_wg, int token_groups, int pack_wgs,
                                                                     const u32x4 *__restrict__ w_v, u32x4 *__restrict__ packed,
                                                                     const u32x4 *__restrict__ feats,
-                                                                    const u32x4 *__restrict__ a_hi,
-                                                                    const u32x4 *__restrict__ a_lo,
+                                                                    const u32x4 *__restrict__ a_fold,
                                                                     float *__restrict__ part) {
-  extern __shared__ u32x4 meta_a_lds[];  // [2][rows_pad][kRowPieces]
-  if ((int)blockIdx.x >= score_wgs) {
-    pack_values((blockIdx.x - score_wgs) * kScoreWaves + (threadIdx.x >> 6), (gridDim.x - score_wgs) * kScoreWaves, D, w_v, packed);
+  extern __shared__ u32x4 meta_a_lds[];  // [2][features of 8 x 32 rows, A (values, then remainders)][8 pieces]
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if ((int)blockIdx.x < pack_wgs) {
+    pack_values(blockIdx.x * kScoreWaves + wave, pack_wgs * kScoreWaves, D, w_v, packed);
     return;
   }
-  const int token_group = blockIdx.x % token_groups, column = blockIdx.x / token_groups;
+  const int id = blockIdx.x - pack_wgs;
+  const int token_group = id % token_groups, column = id / token_groups;
   const int rows_pad = 16 * row_tiles;
-  u32x4 *lds_hi = meta_a_lds, *lds_lo = meta_a_lds + rows_pad * kRowPieces;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int j16 = lane & 15, kq = lane >> 4;
-  const int dp = D / 8;                       // 16-byte pieces per feature row
-  const int tok0 = token_group * kTokPerGroup + wave * kTokPerWave;
+  const int row_bytes = D * 2;
+  const int tok0 = token_group * kTokPerGroup;
   const int slices = D / kSlice;
   const int sl_begin = column * slices_per_wg;
   const int sl_end = sl_begin + slices_per_wg < slices ? sl_begin + slices_per_wg : slices;
+  const int k_begin = sl_begin * (kSlice / 64), steps = (sl_end - sl_begin) * (kSlice / 64);
 
-  // B operand: lane (j16, kq) feeds layer 16 ct + j16, features 8 kq .. 8 kq + 7 of the step.
-  // Tokens past the end and layers past L read a valid row and are zeroed or dropped later.
-  const u32x4 *bp[kTokPerWave][2];
-  bool live[2];
+  // Loads of eight rows of 128 bytes, pieces swizzled on the source side; rows past the tokens' or past
+  // A's are out of range and arrive as zeros.  Layers past L are the next token's (their scores are
+  // written and not read).
+  typedef __attribute__((address_space(3))) void *lptr_t;
+  const auto f_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(feats + (size_t)tok0 * L * (row_bytes / 16)), 0,
+                                                        min(kTokPerGroup, S - tok0) * L * row_bytes, kBufferFlags);
+  const auto a_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)a_fold, 0, 2 * rows_pad * row_bytes, kBufferFlags);
+  const int r8 = lane >> 3;
+  auto swz = [](int r, int c) { return r * 8 + (c ^ ((r & 7) ^ ((r >> 3) & 1))); };
+  auto issue = [&](int t) {
+    u32x4 *stage = meta_a_lds + (t & 1) * kScoreStage;
+    const int k = (k_begin + min(t, steps - 1)) * 128;
 #pragma unroll
-  for (int ct = 0; ct < 2; ++ct) live[ct] = 16 * ct + j16 < L;
+    for (int i = 0; i < kScoreLoads; ++i) {
+      constexpr int kFeatLoads = kScoreFeatRows / 8 / kScoreWaves;  // the first of them: features, then A
+      const int row = (wave + (i < kFeatLoads ? i : i - kFeatLoads) * kScoreWaves) * 8 + r8;
+      const int src = row * row_bytes + ((lane & 7) ^ r8 ^ ((row >> 3) & 1)) * 16;
+      u32x4 *dst = stage + (wave + i * kScoreWaves) * 64;
+      if (i < kFeatLoads) __builtin_amdgcn_raw_ptr_buffer_load_lds(f_rsrc, (lptr_t)dst, 16, src, k, 0, 0);
+      else __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lptr_t)dst, 16, src, k, 0, 0);
+    }
+  };
+  const int tw = (wave & 3) * kTokPerWave;   // first token
+  const int mt0 = (wave >> 2) * (kMaxRowTiles / 2);
+  f32x4 acc[kMaxRowTiles / 2][kTokPerWave][2];
 #pragma unroll
-  for (int t = 0; t < kTokPerWave; ++t) {
-    const int tk = tok0 + t < S ? tok0 + t : S - 1;
-#pragma unroll
-    for (int ct = 0; ct < 2; ++ct) bp[t][ct] = feats + ((size_t)tk * L + (live[ct] ? 16 * ct + j16 : 0)) * dp + kq;
-  }
-  f32x4 acc[kMaxRowTiles][kTokPerWave][2];
-#pragma unroll
-  for (int mt = 0; mt < kMaxRowTiles; ++mt)
+  for (int mt = 0; mt < kMaxRowTiles / 2; ++mt)
 #pragma unroll
     for (int t = 0; t < kTokPerWave; ++t)
 #pragma unroll
       for (int ct = 0; ct < 2; ++ct) acc[mt][t][ct] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  const u32x4 zero = {0u, 0u, 0u, 0u};
-
-  for (int sl = sl_begin; sl < sl_end; ++sl) {
-    const int piece0 = sl * kSlicePieces;
-    // the tokens' fragments of the whole slice are requested before A is staged
-    u32x4 fb[kSliceSteps][kTokPerWave][2];
+  issue(0);
+  issue(1);
+#pragma unroll 1
+  for (int st = 0; st < steps; ++st) {
+    // this step's loads have landed, the next step's stay in flight
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kScoreLoads) : "memory");
+    const u32x4 *f = meta_a_lds + (st & 1) * kScoreStage, *ah = f + kScoreFeatRows * 8, *al = ah + rows_pad * 8;
 #pragma unroll
-    for (int st = 0; st < kSliceSteps; ++st)
-#pragma unroll
-      for (int t = 0; t < kTokPerWave; ++t)
-#pragma unroll
-        for (int ct = 0; ct < 2; ++ct) fb[st][t][ct] = bp[t][ct][piece0 + 4 * st];
-    __syncthreads();  // the previous slice's fragment reads are done
-    // all of the slice's loads are issued before the first LDS write
-    constexpr int kStage = kMaxRows * kSlicePieces / kScoreThreads;
-    u32x4 sh[kStage], sl_[kStage];
-#pragma unroll
-    for (int i = 0; i < kStage; ++i) {
-      const int idx = tid + i * kScoreThreads;
-      if (idx < rows_pad * kSlicePieces) {
-        const int row = idx / kSlicePieces, pc = idx % kSlicePieces;
-        sh[i] = a_hi[(size_t)row * dp + piece0 + pc];
-        sl_[i] = a_lo[(size_t)row * dp + piece0 + pc];
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < kStage; ++i) {
-      const int idx = tid + i * kScoreThreads;
-      if (idx < rows_pad * kSlicePieces) {
-        const int row = idx / kSlicePieces, pc = idx % kSlicePieces;
-        lds_hi[row * kRowPieces + pc] = sh[i];
-        lds_lo[row * kRowPieces + pc] = sl_[i];
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int st = 0; st < kSliceSteps; ++st) {
+    for (int ks = 0; ks < 2; ++ks) {
       bf16x8 x[kTokPerWave][2];
 #pragma unroll
       for (int t = 0; t < kTokPerWave; ++t)
 #pragma unroll
-        for (int ct = 0; ct < 2; ++ct) x[t][ct] = __builtin_bit_cast(bf16x8, live[ct] ? fb[st][t][ct] : zero);
+        for (int ct = 0; ct < 2; ++ct) x[t][ct] = __builtin_bit_cast(bf16x8, f[swz((tw + t) * L + 16 * ct + j16, 4 * ks + kq)]);
 #pragma unroll
-      for (int mt = 0; mt < kMaxRowTiles; ++mt) {
-        if (mt < row_tiles) {
-          const int at = (16 * mt + j16) * kRowPieces + 4 * st + kq;
-          const bf16x8 h8 = __builtin_bit_cast(bf16x8, lds_hi[at]);
-          const bf16x8 l8 = __builtin_bit_cast(bf16x8, lds_lo[at]);
+      for (int mt = 0; mt < kMaxRowTiles / 2; ++mt) {
+        if (mt0 + mt < row_tiles) {
+          const int at = swz(16 * (mt0 + mt) + j16, 4 * ks + kq);
+          const bf16x8 h8 = __builtin_bit_cast(bf16x8, ah[at]);
+          const bf16x8 l8 = __builtin_bit_cast(bf16x8, al[at]);
 #pragma unroll
           for (int t = 0; t < kTokPerWave; ++t)
 #pragma unroll
@@ -195,19 +184,22 @@ __global__ __launch_bounds__(kScoreThreads) void meta_scores_kernel(int S, int L
         }
       }
     }
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // everybody has read the stage
+    issue(st + 2);
   }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no load may land in LDS that belongs to somebody else
   // lane (j16, kq) holds rows 16 mt + 4 kq + r of layer 16 ct + j16
 #pragma unroll
   for (int t = 0; t < kTokPerWave; ++t) {
-    if (tok0 + t < S) {
-      float *dst = part + ((size_t)column * S + tok0 + t) * rows_pad * kMaxL;
+    if (tok0 + tw + t < S) {
+      float *dst = part + ((size_t)column * S + tok0 + tw + t) * rows_pad * kMaxL;
 #pragma unroll
-      for (int mt = 0; mt < kMaxRowTiles; ++mt) {
-        if (mt < row_tiles) {
+      for (int mt = 0; mt < kMaxRowTiles / 2; ++mt) {
+        if (mt0 + mt < row_tiles) {
 #pragma unroll
           for (int ct = 0; ct < 2; ++ct)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) dst[(16 * mt + 4 * kq + r) * kMaxL + 16 * ct + j16] = acc[mt][t][ct][r];
+            for (int r = 0; r < 4; ++r) dst[(16 * (mt0 + mt) + 4 * kq + r) * kMaxL + 16 * ct + j16] = acc[mt][t][ct][r];
         }
       }
     }
@@ -351,7 +343,6 @@ constexpr int kMpThreads = 512;
 constexpr int kMpWaves = 8;
 constexpr int kMpHq = 24;           // hq rows of a workgroup at most: 96 KB of mixed features beside 64 KB of features
 constexpr int kMpHeadDim = 128;
-constexpr int kBufferFlags = 0x00027000;  // untyped 32-bit elements
 
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -663,11 +654,12 @@ hipError_t launch_meta_fold(int32_t Q, int32_t D, int32_t H, const void *f_q, co
   return hipGetLastError();
 }
 
-// Workgroup columns of the score kernel: enough of them that a few tokens still fill the chip
+// Workgroup columns of the score kernel: one workgroup per CU, as many as that leaves room for (with
+// 512 wanted, 2048 tokens took 8 us more, 300 tokens 19 us more for the layer)
 static void score_split(int32_t S, int32_t D, int *slices_per_wg, int *parts) {
   const int slices = D / kSlice;
   const int groups = (S + kTokPerGroup - 1) / kTokPerGroup;
-  int p = (512 + groups - 1) / groups;
+  int p = 256 / groups;
   if (p > slices) p = slices;
   if (p > kMaxParts) p = kMaxParts;
   if (p < 1) p = 1;
@@ -684,17 +676,14 @@ size_t meta_attn_workspace_bytes(int32_t S, int32_t D, int32_t H, int32_t Q) {
 // scores of all tokens to part, its workgroup columns in *parts; w_v rearranged into packed if given
 static hipError_t launch_scores(int32_t S, int32_t L, int32_t D, int32_t rows_pad, const void *feats, const void *a_fold,
                                 const void *w_v, void *packed, float *part, int *parts, hipStream_t s) {
-  const bf16_t *a_hi = (const bf16_t *)a_fold, *a_lo = a_hi + (size_t)rows_pad * D;
   int spw;
   score_split(S, D, &spw, parts);
-  const size_t lds = (size_t)2 * rows_pad * kRowPieces * sizeof(u32x4);
-  hipError_t e = hipFuncSetAttribute((const void *)meta_scores_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     (int)((size_t)2 * kMaxRows * kRowPieces * sizeof(u32x4)));
+  hipError_t e = hipFuncSetAttribute((const void *)meta_scores_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kScoreLds);
   if (e != hipSuccess) return e;
-  const int groups = (S + kTokPerGroup - 1) / kTokPerGroup, score_wgs = groups * *parts;
-  meta_scores_kernel<<<score_wgs + (packed ? 256 : 0), kScoreThreads, lds, s>>>(
-      S, L, D, rows_pad / 16, spw, groups, score_wgs, (const u32x4 *)w_v, (u32x4 *)packed, (const u32x4 *)feats,
-      (const u32x4 *)a_hi, (const u32x4 *)a_lo, part);
+  const int groups = (S + kTokPerGroup - 1) / kTokPerGroup, pack_wgs = packed ? 128 : 0;
+  meta_scores_kernel<<<pack_wgs + groups * *parts, kScoreThreads, kScoreLds, s>>>(
+      S, L, D, rows_pad / 16, spw, groups, pack_wgs, (const u32x4 *)w_v, (u32x4 *)packed, (const u32x4 *)feats,
+      (const u32x4 *)a_fold, part);
   return hipGetLastError();
 }
 

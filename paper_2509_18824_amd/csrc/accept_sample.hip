@@ -37,9 +37,9 @@
 // together.  Larger launches draw: a workgroup takes its place (sequence, share) from a counter when
 // it starts, so the places held are always the lowest and only the last sequence of a launch that has
 // begun can be waiting for workgroups that have not, at most 31 CUs of 256.  By the workgroup's index
-// two launches could each fill one XCD and wait there for the other's.  The counter costs 6 to 14 us
-// of 80 for 240 workgroups (one address), nothing measurable for 60; the workgroups of a sequence on
-// one XCD instead cost 18 us.
+// two launches could each fill one XCD and wait there for the other's.  Drawing costs 6 to 14 us of 80 for
+// 240 workgroups, nothing measurable for 60; four counters instead of one cost the same, the
+// workgroups of a sequence on one XCD 18 us: it is where a sequence's workgroups sit, not the counter.
 #include "hb_internal.h"
 
 namespace hb {

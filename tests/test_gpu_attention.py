@@ -114,9 +114,9 @@ def test_scalar_kernel_blocks_and_wavefronts(hb, step, dtype, D):
 @pytest.mark.parametrize("nodes", [8, 60])
 @pytest.mark.parametrize("lens", [[1], [191], [193], [2048], [640, 64, 1500], [300] * 8, [100, 900, 0, 500, 70, 1400, 33, 256, 812]])
 def test_short_pieces_of_a_few_sequences(hb, step, nodes, lens):
-    """Up to 8 (trees) or 16 sequences (chains) are cut into pieces from 3 or 4 tiles on: one sequence
-    around one and two pieces, many pieces of one, unequal lengths (pieces as long as the longest
-    sequence's), and 9 sequences, where trees take longer pieces."""
+    """Sequences that do not occupy the workers with long pieces are cut from 3 (chains) or 4 tiles (trees)
+    on: one sequence around one and two pieces, many pieces of one, unequal lengths (pieces as long
+    as the longest sequence's); without a length hint the page table's span decides."""
     trees = [W.chain_tree(8) if nodes == 8 else W.seeded_tree(10 + i) for i in range(len(lens))]
     inp = W.make_verify_inputs(79, "bf16", 28, 4, 128, lens, trees, kv_std=1.0, q_std=1.0)
     ref = oracle_attn(inp)

@@ -41,6 +41,9 @@ from .binding import (
     hb_meta_query_fold,
     hb_meta_query_attn_workspace_bytes,
     hb_meta_query_attn,
+    hb_meta_query_attn_project,
+    hb_meta_query_attn_project_pays,
+    hb_meta_query_attn_project_workspace_bytes,
     HB_F32,
     HB_BF16,
     HB_ATTN_AUTO,

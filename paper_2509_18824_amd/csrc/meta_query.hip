@@ -337,7 +337,7 @@ __global__ __launch_bounds__(kMixThreads) void meta_mix_kernel(int S, int L, int
 //
 // What bounds it: with 4 tokens the path L2 -> CU (every TG tokens read all of W_v once); with 16
 // tokens the two phases between barriers, matrix, vector and LDS work in turn on two wavefronts per
-// SIMD.  2048 tokens, 28 layers, D = 3584, 28 heads, 3 queries: 566 us; the value projection of all
+// SIMD.  2048 tokens, 28 layers, D = 3584, 28 heads, 3 queries: 566 to 605 us; the value projection of all
 // layers and the mixing of its results took 1478 + 161 us.  96 tokens: 67 us against 76 + 15.
 constexpr int kMpThreads = 512;
 constexpr int kMpWaves = 8;

@@ -100,8 +100,8 @@ constexpr int kListCap = 2048;              // candidates that pass the threshol
 //
 // What bounds it is vector instruction issue, and code that has to stay in the instruction cache.
 // The path from registers works by 16-byte pieces, without NaN tests and without a branch per value: a
-// NaN or an infinity shows in the sum of exponentials, and such a chunk is done again with a test per
-// value.  160 rows x 152064 float32 with the merge 33.7 -> 28.8 us (24 us = 4 TB/s in this pass), 16 rows 33 -> 13 us,
+// NaN or an infinity shows in the sum of exponentials, or nothing is above -inf, and such a chunk is done
+// again with a test per value.  160 rows x 152064 float32 with the merge 33.7 -> 28.8 us (24 us = 4 TB/s in this pass), 16 rows 33 -> 13 us,
 // one row 42 -> 11 us (those two mostly by larger chunks).
 struct ChunkShared {
   unsigned long long red[kThreads / 64];
@@ -176,11 +176,9 @@ __device__ __forceinline__ bool fast_chunk(const T *row, int v0, int n, int k, C
     }
   }
   mx = wg_max_f(mt, sh.fred);
-  if (!(mx > ninf)) {  // nothing above -inf: the lowest ids win
-    if (tid < k) sh.win[tid] = tid < n ? sel_key(ninf, (uint32_t)(v0 + tid)) : 0ull;
-    sum = 0.f;
-    return true;
-  }
+  // Nothing above -inf, or a signalling NaN: v_max3 makes it a quiet one, and the next maximum then
+  // forgets the values beside it.
+  if (!(mx > ninf)) return false;
   const float thr = chunk_threshold(mt, tid < n_full || tid < rest, k, sh.thr_w);
   const float c1 = 1.4426950408889634f, c0 = -mx * 1.4426950408889634f;
   float s = __builtin_amdgcn_exp2f(fmaf(tail, c1, c0));
@@ -234,13 +232,18 @@ __device__ __forceinline__ void any_chunk(const T *row, int v0, int n, int k, Ch
 #pragma unroll 4
   for (int i = tid; i < n; i += kThreads) mt = fmaxf(mt, value(i));
   mx = wg_max_f(mt, sh.fred);
+  if (!(mx > ninf)) {  // the lowest ids win
+    if (tid < k) sh.win[tid] = tid < n ? sel_key(ninf, (uint32_t)(v0 + tid)) : 0ull;
+    sum = 0.f;
+    return;
+  }
   const float thr = chunk_threshold(mt, tid < n, k, sh.thr_w);
   const float c1 = 1.4426950408889634f, c0 = -mx * 1.4426950408889634f;
   float s = 0.f;
 #pragma unroll 4
   for (int i = tid; i < n; i += kThreads) {
     const float x = value(i);
-    if (mx > ninf) s += __builtin_amdgcn_exp2f(fmaf(x, c1, c0));
+    s += __builtin_amdgcn_exp2f(fmaf(x, c1, c0));
     if (x >= thr) {
       const int at = atomicAdd(&sh.list_n, 1);
       if (at < kListCap) sh.list[at] = sel_key(x, (uint32_t)(v0 + i));

@@ -90,6 +90,36 @@ def test_topk_masked_and_not_finite(S):
     assert np.array_equal(ids.cpu().numpy(), rid) and np.abs(logp.cpu().numpy() - rlogp).max() <= LOGP_TOL
 
 
+@pytest.mark.parametrize("bf16", [False, True])
+def test_topk_signalling_nan_counts_as_minus_infinity(S, bf16):
+    """Signalling NaNs beside the only values of a masked row, in every place of a 16-byte piece, in the
+    values outside the pieces, and among ordinary values."""
+    dtype, snan = (np.int16, 0x7F81) if bf16 else (np.int32, 0x7F800001)
+    V = 20003
+    x = np.full((18, V), -np.inf, dtype=np.float32)
+    at = []
+    for m in range(17):
+        x[m, 800 + m] = 5.0
+        at += [(m, 800 + (m & ~7) + i) for i in range(8) if (m & ~7) + i != m]
+    x[9:17, :] = -np.inf  # these rows hold their value where a row of odd length starts or ends
+    for m in range(9, 17):
+        x[m, m - 9 if m < 13 else V - 1 - (m - 13)] = 5.0
+        at += [(m, i) for i in range(8) if x[m, i] != 5.0] + [(m, V - 1 - i) for i in range(8) if x[m, V - 1 - i] != 5.0]
+    x[17] = W.make_draft_logits(71, 1, V)[0]
+    at += [(17, int(i)) for i in np.argsort(-x[17])[:40:2]]
+    bits = (torch.from_numpy(x).to(torch.bfloat16).view(torch.int16) if bf16 else torch.from_numpy(x).view(torch.int32)).numpy().copy()
+    ref = torch.from_numpy(bits.copy()).view(torch.bfloat16 if bf16 else torch.float32).float().numpy()
+    for m, i in at:
+        bits[m, i] = dtype(snan)
+        ref[m, i] = -np.inf
+    t = torch.from_numpy(bits).cuda().view(torch.bfloat16 if bf16 else torch.float32)
+    ids, logp = S.topk_logprob(t, 3)
+    rid, rlogp = topk_logprob_ref(ref, 3)
+    assert np.array_equal(ids.cpu().numpy(), rid)
+    got, fin = logp.cpu().numpy(), np.isfinite(rlogp)
+    assert np.abs(got[fin] - rlogp[fin]).max() <= LOGP_TOL and np.isneginf(got[~fin]).all()
+
+
 def test_topk_full_vocabulary_every_row_of_a_level(S):
     """The shape of one level of the batch-16 workload: 160 rows (16 sequences x 10 frontier
     nodes) over the vocabulary of 152064, float32; and the root level's 16 rows in bf16."""

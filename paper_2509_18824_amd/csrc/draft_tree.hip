@@ -101,7 +101,7 @@ constexpr int kListCap = 2048;              // candidates that pass the threshol
 // What bounds it is vector instruction issue, and code that has to stay in the instruction cache.
 // The path from registers works by 16-byte pieces, without NaN tests and without a branch per value: a
 // NaN or an infinity shows in the sum of exponentials, or nothing is above -inf, and such a chunk is done
-// again with a test per value.  160 rows x 152064 float32 with the merge 33.7 -> 28.8 us (24 us = 4 TB/s in this pass), 16 rows 33 -> 13 us,
+// again with a test per value; so is one of too few values for a threshold.  160 rows x 152064 float32 with the merge 33.7 -> 28.8 us (24 us = 4 TB/s in this pass), 16 rows 33 -> 13 us,
 // one row 42 -> 11 us (those two mostly by larger chunks).
 struct ChunkShared {
   unsigned long long red[kThreads / 64];
@@ -213,7 +213,10 @@ __device__ __forceinline__ bool fast_chunk(const T *row, int v0, int n, int k, C
   }
   sum = wg_sum_f(s, sh.fred);  // its barriers also publish list and list_n
   const int cnt = sh.list_n;
-  if (!(sum == sum) || cnt > kListCap) return false;
+  // The maximum's own exponential is 1.  A maximum near the type's limits (a mask of the lowest value)
+  // leaves the range when scaled, in c0, and too few values for a threshold may share an offset that c0
+  // rounds off: any_chunk takes the differences first.  Tested here, where registers are free again.
+  if (!(sum >= 0.5f && sum < __builtin_huge_valf()) || cnt > kListCap || !(thr > ninf)) return false;
   rank_select(sh.list, cnt, k, sh.win);
   return true;
 }
@@ -238,12 +241,11 @@ __device__ __forceinline__ void any_chunk(const T *row, int v0, int n, int k, Ch
     return;
   }
   const float thr = chunk_threshold(mt, tid < n, k, sh.thr_w);
-  const float c1 = 1.4426950408889634f, c0 = -mx * 1.4426950408889634f;
   float s = 0.f;
 #pragma unroll 4
   for (int i = tid; i < n; i += kThreads) {
     const float x = value(i);
-    s += __builtin_amdgcn_exp2f(fmaf(x, c1, c0));
+    s += __expf(x - mx);
     if (x >= thr) {
       const int at = atomicAdd(&sh.list_n, 1);
       if (at < kListCap) sh.list[at] = sel_key(x, (uint32_t)(v0 + i));

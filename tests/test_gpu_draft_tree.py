@@ -120,6 +120,44 @@ def test_topk_signalling_nan_counts_as_minus_infinity(S, bf16):
     assert np.abs(got[fin] - rlogp[fin]).max() <= LOGP_TOL and np.isneginf(got[~fin]).all()
 
 
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("V", [7, 33, 100, 16384 + 40, 40001])
+def test_topk_masks_of_the_types_lowest_value(S, V, bf16):
+    """Rows and chunks whose every value is the type's lowest finite one, with and without -inf, and one
+    chunk of ordinary values beside them: the difference to the maximum is finite, its scaled parts are not."""
+    low = float(torch.finfo(torch.bfloat16 if bf16 else torch.float32).min)
+    k = min(V, 10)
+    x = np.full((5, V), low, dtype=np.float32)
+    x[1, 1::2] = -np.inf
+    x[2, :5] = [3.0, 2.0, 1.0, 0.0, -1.0]
+    x[3, -5:] = [3.0, 2.0, 1.0, 0.0, -1.0]
+    x[4] = -low
+    t = torch.from_numpy(x).cuda().to(torch.bfloat16 if bf16 else torch.float32)
+    x = t.float().cpu().numpy()
+    ids, logp = S.topk_logprob(t, k)
+    rid, rlogp = topk_logprob_ref(x, k)
+    assert np.array_equal(ids.cpu().numpy(), rid)
+    got, want = logp.cpu().numpy(), rlogp.astype(np.float32)
+    # the log-probability is a float32 sum of the maximum and the logarithm of the exponentials' sum:
+    # at the type's ends that logarithm is lost in the maximum's rounding, in the result as in its bound
+    tol = np.where(np.abs(x.max(1, keepdims=True)) > 1e30, np.float32(np.log(V)), LOGP_TOL)
+    near = np.isfinite(want) & (np.abs(want) < 1e30)
+    assert (np.abs(got - want)[near] <= np.broadcast_to(tol, got.shape)[near]).all(), (got, want)
+    assert np.array_equal(got[~near] < -1e30, want[~near] < -1e30) and not np.isnan(got).any()
+
+
+@pytest.mark.parametrize("V", [9, 60, 250])
+def test_topk_few_values_of_large_magnitude(S, V):
+    """Too few values for a threshold, with a common offset of some thousands: the exponentials are those
+    of the differences to the maximum (the offset's product with log2 e alone is off by 1e-4)."""
+    x = (W.make_draft_logits(91, 4, V) + np.float32(-3000.0)).astype(np.float32)
+    ids, logp = S.topk_logprob(torch.from_numpy(x).cuda(), min(V, 9))
+    rid, rlogp = topk_logprob_ref(x, min(V, 9))
+    assert np.array_equal(ids.cpu().numpy(), rid)
+    # lse = maximum + log(sum) and logit - lse round once each at 3000 (half a unit of 2^-12 each)
+    assert np.abs(logp.cpu().numpy() - rlogp).max() <= 2.0 ** -12 + LOGP_TOL
+
+
 def test_topk_full_vocabulary_every_row_of_a_level(S):
     """The shape of one level of the batch-16 workload: 160 rows (16 sequences x 10 frontier
     nodes) over the vocabulary of 152064, float32; and the root level's 16 rows in bf16."""

@@ -291,15 +291,29 @@ int32_t hb_tree_accept(int32_t B, int32_t max_nodes_per_tree, const int32_t *nod
  *                      integer products and give unspecified, though memory-safe, results)
  *   u_accept   device uint32 [total_nodes]: the uniform used when that node is tried as a child
  *   u_bonus    device uint32 [B]: the uniform of the step's last token
- *   workspace  device, hb_tree_accept_sample_workspace_bytes(B, V) bytes, 4-byte aligned
+ *   workspace  device, hb_tree_accept_sample_workspace_bytes(B, V) bytes, 4-byte aligned; one call at a
+ *              time may use it (each call overwrites it, whatever it held)
+ * Beyond 10240 tokens the vocabulary of a sequence is dealt to ceil(V / 10240) workgroups, 32 at most, that
+ * wait for each other's sums.  The call is fast where as many CUs are free at a time for each sequence under
+ * way.  Where they are not (a stream with a CU mask, a GPU full of other work), no wait is for ever: after
+ * max_polls looks (HB_SAMPLE_POLLS: some 20 ms) the sequence is done by a single workgroup, with the same
+ * results, in tens of milliseconds (31 ms for 16 sequences of 60 nodes over 152064 tokens).  hb_tree_accept_sample_polls takes the number of looks; 0: nobody waits.
  * Errors: INVALID_ARG, UNSUPPORTED (max_nodes_per_tree > 64), WORKSPACE, DEVICE.  B == 0: no-op.
  */
+#define HB_SAMPLE_POLLS 16384
 int32_t hb_tree_accept_sample(int32_t B, int32_t max_nodes_per_tree, int32_t V, const int32_t *node_offset,
                               const int32_t *parent, const int32_t *draft_ids, const float *p_target,
                               const float *q_draft, const uint32_t *u_accept, const uint32_t *u_bonus,
                               int32_t max_path, int32_t *accept_len, int32_t *accept_path,
                               int32_t *out_tokens, int32_t *bonus_id, void *workspace,
                               size_t workspace_bytes, void *stream);
+
+int32_t hb_tree_accept_sample_polls(int32_t B, int32_t max_nodes_per_tree, int32_t V, const int32_t *node_offset,
+                                    const int32_t *parent, const int32_t *draft_ids, const float *p_target,
+                                    const float *q_draft, const uint32_t *u_accept, const uint32_t *u_bonus,
+                                    int32_t max_path, int32_t *accept_len, int32_t *accept_path,
+                                    int32_t *out_tokens, int32_t *bonus_id, void *workspace,
+                                    size_t workspace_bytes, int32_t max_polls, void *stream);
 
 size_t hb_tree_accept_sample_workspace_bytes(int32_t B, int32_t V);
 

@@ -82,6 +82,8 @@ def _load():
     lib.hb_tree_accept.argtypes = [i32, i32, p, p, p, p, p, i32, p, p, p, p, p]
     lib.hb_tree_accept_sample.restype = i32
     lib.hb_tree_accept_sample.argtypes = [i32, i32, i32] + [p] * 7 + [i32] + [p] * 4 + [p, sz, p]
+    lib.hb_tree_accept_sample_polls.restype = i32
+    lib.hb_tree_accept_sample_polls.argtypes = [i32, i32, i32] + [p] * 7 + [i32] + [p] * 4 + [p, sz, i32, p]
     lib.hb_tree_accept_sample_workspace_bytes.restype = sz
     lib.hb_tree_accept_sample_workspace_bytes.argtypes = [i32, i32]
     lib.hb_topk_logprob.restype = i32
@@ -291,17 +293,27 @@ def hb_tree_accept_sample_workspace_bytes(B: int, V: int) -> int:
     return int(lib.hb_tree_accept_sample_workspace_bytes(B, V))
 
 
-def hb_tree_accept_sample(B: int, max_nodes_per_tree: int, node_offset, parent, draft_ids, p_target, q_draft,
-                          u_accept, u_bonus, max_path: int, accept_len, accept_path, out_tokens, bonus_id,
-                          workspace, stream=None) -> None:
+HB_SAMPLE_POLLS = 16384
+
+
+def hb_tree_accept_sample_polls(B: int, max_nodes_per_tree: int, node_offset, parent, draft_ids, p_target, q_draft,
+                                u_accept, u_bonus, max_path: int, accept_len, accept_path, out_tokens, bonus_id,
+                                workspace, max_polls: int, stream=None) -> None:
     V = p_target.shape[1]
     if p_target.dtype != torch.float32 or q_draft.dtype != torch.float32 or q_draft.shape != p_target.shape:
         raise ValueError("p_target and q_draft must be float32 [total_nodes, V]")
     ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    _check(lib.hb_tree_accept_sample(B, max_nodes_per_tree, V, _ptr(node_offset), _ptr(parent), _ptr(draft_ids),
-                                     _ptr(p_target), _ptr(q_draft), _ptr(u_accept), _ptr(u_bonus), max_path,
-                                     _ptr(accept_len), _ptr(accept_path), _ptr(out_tokens), _ptr(bonus_id),
-                                     _ptr(workspace), ws_bytes, _stream(stream)))
+    _check(lib.hb_tree_accept_sample_polls(B, max_nodes_per_tree, V, _ptr(node_offset), _ptr(parent), _ptr(draft_ids),
+                                           _ptr(p_target), _ptr(q_draft), _ptr(u_accept), _ptr(u_bonus), max_path,
+                                           _ptr(accept_len), _ptr(accept_path), _ptr(out_tokens), _ptr(bonus_id),
+                                           _ptr(workspace), ws_bytes, max_polls, _stream(stream)))
+
+
+def hb_tree_accept_sample(B: int, max_nodes_per_tree: int, node_offset, parent, draft_ids, p_target, q_draft,
+                          u_accept, u_bonus, max_path: int, accept_len, accept_path, out_tokens, bonus_id,
+                          workspace, stream=None) -> None:
+    hb_tree_accept_sample_polls(B, max_nodes_per_tree, node_offset, parent, draft_ids, p_target, q_draft, u_accept, u_bonus,
+                                max_path, accept_len, accept_path, out_tokens, bonus_id, workspace, HB_SAMPLE_POLLS, stream)
 
 
 def hb_topk_logprob_workspace_bytes(M: int, V: int, k: int) -> int:

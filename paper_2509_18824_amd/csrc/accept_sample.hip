@@ -21,24 +21,27 @@
 // range of a node's rows once and keep it in registers (40 values of p and of q per lane), so that a
 // rejection touches no vocabulary in memory; what crosses wavefronts are the sums.  Every wavefront
 // keeps p_x and q_x of the node's children in its lanes, updates them like any other value, and takes
-// every decision itself: no barrier anywhere.  16 sequences of 60 nodes over 152064 tokens: 81 us.
+// every decision itself: no barrier on the way.  16 sequences of 60 nodes over 152064 tokens: 85 us, the
+// kernel that clears the slots included.
 // What bounds it is the chain of the sequence with the most rejections (ten at the root: 73 us): per
 // rejection two exchanges of 2 us each and 2.5 us of 64-bit integer work, per node visited 5 us for its
-// rows.  20 values per lane (twice the wavefronts, twice the partners per exchange) take 107 us;
-// recomputing the residual for the division instead of keeping its 80 registers 88 us; sums by LDS
-// permutes and workgroup barriers 95 us.
+// rows.  Measured against 81 us in a form whose workgroups took their places by index: 20 values per lane
+// (twice the wavefronts, twice the partners per exchange) 107 us; recomputing the residual for the division
+// instead of keeping its 80 registers 88 us; sums by LDS permutes and workgroup barriers 95 us.
 //
 // Exchange: slot (k, w) holds wavefront w's partial sum of exchange k, bit 63 set; a slot is written
 // once per launch (they are cleared by a kernel before it) and polled by the sequence's other
 // wavefronts, the data being its own flag.
 //
-// The waits have to end also when several launches on different streams compete for the chip, which
-// holds one of these workgroups per CU.  Up to 64 workgroups (8 per XCD) a few launches always fit
-// together.  Larger launches draw: a workgroup takes its place (sequence, share) from a counter when
-// it starts, so the places held are always the lowest and only the last sequence of a launch that has
-// begun can be waiting for workgroups that have not, at most 31 CUs of 256.  By the workgroup's index
-// two launches could each fill one XCD and wait there for the other's.  Drawing costs 6 to 14 us of 80 for
-// 240 workgroups, nothing measurable for 60; four counters instead of one cost the same, the
+// The waits have to end whatever else runs on the chip, which holds one of these workgroups per CU.  A
+// workgroup draws its place (sequence, share) from a counter when it starts, so the places held are
+// always the lowest and of a launch that has begun only the last sequence can be waiting for workgroups
+// that have not, at most 31 CUs of 256.  (By the workgroup's index two launches could each fill one XCD
+// and wait there for the other's.)  Where even those few find no CU, under a CU mask or beside many such
+// launches, a wavefront gives up after so many looks and says so in the sequence's leave word, which the
+// others look at while they wait; every workgroup counts itself out there, and the last one, which has no
+// partner left, does the whole sequence by itself (accept_alone).  Drawing cost that form 6 to
+// 14 us for 240 workgroups, nothing measurable for 60; four counters instead of one the same, the
 // workgroups of a sequence on one XCD 18 us: it is where a sequence's workgroups sit, not the counter.
 #include "hb_internal.h"
 
@@ -67,10 +70,11 @@ typedef unsigned long long u64;
 
 constexpr int kPer = 40;                       // vocabulary entries a lane keeps in registers
 constexpr int kRange = kPer * 64;              // ... a wavefront (2560)
-constexpr int kMaxWorkers = 128;               // wavefronts per sequence; beyond 327680 tokens the rest stays in memory
-constexpr int kDrawAbove = 64;                 // workgroups of a launch
+constexpr int kMaxWorkers = 127;               // wavefronts per sequence; beyond 325120 tokens the rest stays in memory
 constexpr int kExchanges = 192;                // at most 64 nodes visited and two exchanges for each of 63 children
 constexpr u64 kPosted = 1ull << 63;
+constexpr uint32_t kGaveUp = 1u << 16;         // in a sequence's leave word: one for every wavefront that gave up ...
+constexpr uint32_t kLeft = kGaveUp - 1;        // ... above the count of its workgroups that have left
 constexpr int kBufferFlags = 0x00027000;       // untyped 32-bit elements
 
 template <int CTRL>
@@ -127,27 +131,186 @@ __device__ __forceinline__ uint32_t divide(u64 r, const Divisor &d) {
 
 __device__ __forceinline__ u64 *slots_of(uint32_t *work) { return (u64 *)(((uintptr_t)work + 7) & ~(uintptr_t)7); }
 
+// A sequence's workspace: a word of control (low half: in the first sequence's the counter that places are
+// drawn from; high half: the leave word), the slots of its exchanges, and what lies beyond the registers.
 __global__ __launch_bounds__(256) void accept_sample_clear_kernel(int V, int workers, uint32_t *__restrict__ work_all) {
-  u64 *slots = slots_of(work_all + (size_t)blockIdx.x * V);
-  for (int i = threadIdx.x; i < 1 + kExchanges * workers; i += 256) slots[i] = 0ull;
+  u64 *control = slots_of(work_all + (size_t)blockIdx.x * V);
+  for (int i = threadIdx.x; i < 1 + kExchanges * workers; i += 256) control[i] = 0ull;
+}
+
+struct Sequence {
+  int n0, n;  // its nodes
+  const int32_t *parent, *draft_ids;
+  const float *p_target, *q_draft;
+  const uint32_t *u_accept;
+  uint32_t u_bonus;
+  int V, max_path;
+  int32_t *accept_len, *accept_path, *out_tokens, *bonus_id;
+};
+
+// One sequence by one workgroup, alone and waiting for nobody: every pass over the vocabulary reads the
+// rows from memory, and a value's residual is worked out again from the node's rejections before it (their
+// sums stay in LDS; the workspace still belongs to the launch).  Sums and products have 64 bits.
+struct Rejection {
+  u64 sp, sq, div;  // p <- max(p S(q) - q S(p), 0) / div
+};
+struct AloneShared {
+  int32_t par[64], did[64], path[64], removed[64];
+  Rejection rejections[64];
+  u64 red[kThreads / 64], share[kThreads], q_token;
+  int decision;
+};
+
+__device__ __forceinline__ u64 wide_residual(uint32_t p, uint32_t q, u64 sp, u64 sq) {
+  const u64 a = p * sq, b = q * sp;
+  return a > b ? a - b : 0ull;
+}
+
+__device__ __forceinline__ void accept_alone(const Sequence &s, AloneShared &sh) {
+  const int tid = threadIdx.x;
+  auto sum = [&](u64 x) {
+    x = wave_sum(x);
+    __syncthreads();  // red may still be read from the previous sum
+    if ((tid & 63) == 0) sh.red[tid >> 6] = x;
+    __syncthreads();
+    return sh.red[0] + sh.red[1] + sh.red[2] + sh.red[3];
+  };
+  if (tid < 64) {
+    int par = -1, did = 0;
+    if (tid < s.n) {
+      par = s.parent[s.n0 + tid];
+      if (par >= tid || par < -1 || tid == 0) par = -1;  // malformed: never anybody's child
+      did = s.draft_ids[s.n0 + tid];
+    }
+    sh.par[tid] = par;
+    sh.did[tid] = did;
+  }
+  if (tid == 0) sh.path[0] = 0;
+  __syncthreads();
+  int cur = 0, len = 1, bonus = -1;
+#pragma unroll 1
+  for (;;) {
+    const float *prow = s.p_target + (size_t)(s.n0 + cur) * s.V;
+    const float *qrow = s.q_draft + (size_t)(s.n0 + cur) * s.V;
+    int n_rejections = 0, n_removed = 0;
+    auto p_at = [&](int v) {
+      uint32_t p = fix_prob(prow[v]);
+      const uint32_t q = n_rejections ? fix_prob(qrow[v]) : 0u;
+#pragma unroll 1
+      for (int i = 0; i < n_rejections; ++i)
+        p = (uint32_t)(wide_residual(p, q, sh.rejections[i].sp, sh.rejections[i].sq) / sh.rejections[i].div);
+      return p;
+    };
+    u64 sp = 0, sq = 0;
+    for (int v = tid; v < s.V; v += kThreads) {
+      sp += fix_prob(prow[v]);
+      sq += fix_prob(qrow[v]);
+    }
+    sp = sum(sp);
+    sq = sum(sq);
+    int taken = -1;
+#pragma unroll 1
+    for (int c = cur + 1; c < s.n && len < s.max_path; ++c) {
+      if (sh.par[c] != cur) continue;  // uniform
+      const int x = sh.did[c];
+      const bool x_ok = x >= 0 && x < s.V;
+      if (tid == 0) {
+        const u64 px = x_ok ? p_at(x) : 0u;
+        u64 qx = x_ok ? fix_prob(qrow[x]) : 0u;
+        for (int i = 0; i < n_removed; ++i) qx = sh.removed[i] == x ? 0ull : qx;
+        const u64 u = s.u_accept[s.n0 + c];
+        sh.decision = mul_less(u * qx, sp, px * sq, 1ull << 32) ? 1 : 0;
+        sh.q_token = qx;
+      }
+      __syncthreads();
+      const bool accept = sh.decision != 0;
+      const u64 qx = sh.q_token;
+      __syncthreads();
+      if (accept) {
+        taken = c;
+        break;
+      }
+      u64 sr = 0;
+      for (int v = tid; v < s.V; v += kThreads) sr += wide_residual(p_at(v), fix_prob(qrow[v]), sp, sq);
+      sr = sum(sr);
+      if (sr != 0) {
+        const u64 div = sr >> kFixBits;
+        if (tid == 0) sh.rejections[n_rejections] = {sp, sq, div ? div : 1ull};
+        __syncthreads();
+        ++n_rejections;
+        u64 snew = 0;
+        for (int v = tid; v < s.V; v += kThreads) snew += p_at(v);
+        sp = sum(snew);
+      }
+      if (tid == 0 && x_ok) sh.removed[n_removed] = x;
+      n_removed += x_ok ? 1 : 0;
+      sq -= qx;
+      __syncthreads();
+    }
+    if (taken < 0) {
+      // the last token: inverse CDF of the current p over consecutive shares of the vocabulary
+      if (sp != 0) {
+        const u64 t = (s.u_bonus * sp) >> 32;
+        const int per = (s.V + kThreads - 1) / kThreads;
+        const int v0 = min(s.V, tid * per), v1 = min(s.V, v0 + per);
+        u64 mine = 0;
+        for (int v = v0; v < v1; ++v) mine += p_at(v);
+        __syncthreads();
+        sh.share[tid] = mine;
+        if (tid == 0) sh.decision = -1;  // sums that overflow 64 bits: nobody's share
+        __syncthreads();
+        u64 before = 0;
+        for (int i = 0; i < tid; ++i) before += sh.share[i];
+        if (before <= t && t < before + mine) {
+          u64 upto = before;
+          for (int v = v0; v < v1; ++v) {
+            upto += p_at(v);
+            if (upto > t) {
+              sh.decision = v;
+              break;
+            }
+          }
+        }
+        __syncthreads();
+        bonus = sh.decision;
+      }
+      break;
+    }
+    if (tid == 0) sh.path[len] = taken;
+    ++len;
+    cur = taken;
+    __syncthreads();
+  }
+  __syncthreads();
+  for (int j = tid; j < s.max_path; j += kThreads) {
+    s.accept_path[j] = j < len ? sh.path[j] : -1;
+    s.out_tokens[j] = j + 1 < len ? sh.did[sh.path[j + 1]] : (j + 1 == len ? bonus : -1);
+  }
+  if (tid == 0) {
+    *s.accept_len = len;
+    *s.bonus_id = bonus;
+  }
 }
 
 __global__ __launch_bounds__(kThreads) void tree_accept_sample_kernel(
-    int draw, int max_nodes, int V, int workers, int groups, int chunk, const int32_t *__restrict__ node_offset, const int32_t *__restrict__ parent,
+    int polls, int max_nodes, int V, int workers, int groups, int chunk, const int32_t *__restrict__ node_offset, const int32_t *__restrict__ parent,
     const int32_t *__restrict__ draft_ids, const float *__restrict__ p_target, const float *__restrict__ q_draft,
     const uint32_t *__restrict__ u_accept, const uint32_t *__restrict__ u_bonus, int max_path,
     int32_t *__restrict__ accept_len, int32_t *__restrict__ accept_path, int32_t *__restrict__ out_tokens,
     int32_t *__restrict__ bonus_id, uint32_t *__restrict__ work_all) {
-  __shared__ unsigned drawn;  // the counter is word 0 of the first sequence's slots
-  unsigned place = blockIdx.x;
-  if (draw) {
-    if (threadIdx.x == 0) drawn = atomicAdd((unsigned *)slots_of(work_all), 1u);
-    __syncthreads();
-    place = drawn;
+  __shared__ unsigned drawn;
+  __shared__ uint32_t leave_mark;  // what this workgroup adds to the leave word
+  __shared__ bool alone;
+  __shared__ AloneShared alone_shared;
+  if (threadIdx.x == 0) {
+    drawn = groups > 1 ? atomicAdd((unsigned *)slots_of(work_all), 1u) : blockIdx.x;
+    leave_mark = 1;
   }
+  __syncthreads();
+  const unsigned place = drawn;
+  if (place >= gridDim.x) return;  // somebody else draws from this workspace: wrong, but inside the tensors
   const int b = __builtin_amdgcn_readfirstlane((int)(place / (unsigned)groups));
   const int w = __builtin_amdgcn_readfirstlane((int)(place % (unsigned)groups) * (kThreads / 64) + (int)(threadIdx.x >> 6));
-  if (w >= workers) return;
   const int lane = threadIdx.x & 63;
   const int n0 = node_offset[b];
   int n = node_offset[b + 1] - n0;
@@ -169,177 +332,210 @@ __global__ __launch_bounds__(kThreads) void tree_accept_sample_kernel(
     did = draft_ids[n0 + lane];
     u_mine = u_accept[n0 + lane];
   }
-  u64 *slots = slots_of(work_all + (size_t)b * V) + 1;
+  u64 *control = slots_of(work_all + (size_t)b * V), *slots = control + 1;
+  uint32_t *leave = (uint32_t *)control + 1;
   const int v_begin = w * chunk, v_end = min(V, v_begin + chunk);  // this wavefront's range
   const int r_end = min(v_end, v_begin + kRange);                  // the part in registers
   // what lies beyond the registers keeps its residual behind the slots
   uint32_t *work = (uint32_t *)(slots + kExchanges * kMaxWorkers) + (long long)w * (chunk - kRange) - v_begin - kRange;
   int k = 0;
 
-  // Sum of x over the sequence's wavefronts; lane i keeps the shares of wavefronts i and i + 64.
+  // Sum of x over the sequence's wavefronts; lane i keeps the shares of wavefronts i and i + 64.  False:
+  // a share did not come in time, or somebody has given up (lane 63, which has no share to look for,
+  // looks at the leave word instead).
   u64 share0 = 0, share1 = 0;
-  auto exchange = [&](u64 x) -> u64 {
+  const bool wide = workers > 63;
+  auto exchange = [&](u64 &x) -> bool {
     if (workers == 1) {
       share0 = lane == 0 ? x : 0ull;
-      return x;
+      return true;
     }
     u64 *slot = slots + k * workers;
     ++k;
     if (lane == 0) __hip_atomic_store(slot + w, x | kPosted, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const int i0 = min(lane, workers - 1), i1 = min(lane + 64, workers - 1);
-    u64 y0, y1;
-    do {
-      y0 = __hip_atomic_load(slot + i0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      y1 = workers > 64 ? __hip_atomic_load(slot + i1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : kPosted;
-    } while (!__all((y0 & y1 & kPosted) != 0));
+    const u64 *at0 = lane == 63 && !wide ? control : slot + min(lane, workers - 1);
+    const u64 *at1 = lane == 63 ? control : slot + min(lane + 64, workers - 1);
+    u64 y0 = 0, y1 = 0;
+#pragma unroll 1
+    for (int i = 0;; ++i) {
+      if (i == polls) return false;
+      y0 = __hip_atomic_load(at0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      y1 = wide ? __hip_atomic_load(at1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : y0;
+      const u64 posted = lane < 63 ? y0 & y1 & kPosted : (wide ? y0 & kPosted : kPosted);
+      if (__all(posted != 0)) break;
+      if (__any(lane == 63 && (uint32_t)(y1 >> 32) >= kGaveUp)) return false;
+    }
     share0 = lane < workers ? y0 & ~kPosted : 0ull;
     share1 = lane + 64 < workers ? y1 & ~kPosted : 0ull;
-    return wave_sum(share0 + share1);
+    x = wave_sum(share0 + share1);
+    return true;
   };
 
-  int cur = 0, len = 1;
-  int path = 0;  // lane i: node i of the path
-  uint32_t sp = 0;
-  uint32_t sp0 = 0, sp1 = 0;  // shares of S(p)
-  uint32_t p[kPer], q[kPer];
-  const float *prow, *qrow;
-  bool in_work = false;  // beyond the registers: p is the target's row (false) or the residual in the workspace
+  auto walk = [&]() -> bool {
+    int cur = 0, len = 1;
+    int path = 0;  // lane i: node i of the path
+    uint32_t sp = 0;
+    uint32_t sp0 = 0, sp1 = 0;  // shares of S(p)
+    uint32_t p[kPer], q[kPer];
+    const float *prow, *qrow;
+    bool in_work = false;  // beyond the registers: p is the target's row (false) or the residual in the workspace
 #pragma unroll 1
-  for (;;) {
-    prow = p_target + (size_t)(n0 + cur) * V;
-    qrow = q_draft + (size_t)(n0 + cur) * V;
-    in_work = false;
-    // lanes that hold a child of the node: p and q of its token
-    const bool child = par == cur && len < max_path;
-    const int tok = child && did >= 0 && did < V ? did : -1;
-    float pf = 0.f, qf = 0.f;
-    if (tok >= 0) {
-      pf = prow[tok];
-      qf = qrow[tok];
-    }
-    // The range's loads are all in flight before the first is used; buffer loads return zero beyond
-    // the range and cost one address register for all of them.
-    u64 both = 0;  // S(q) in the low word, S(p) in the high one: rows sum to less than 2
-    {
-      const int bytes = (r_end > v_begin ? r_end - v_begin : 0) * 4;
-      const auto pr = __builtin_amdgcn_make_buffer_rsrc((void *)(prow + v_begin), 0, bytes, kBufferFlags);
-      const auto qr = __builtin_amdgcn_make_buffer_rsrc((void *)(qrow + v_begin), 0, bytes, kBufferFlags);
-#pragma unroll
-      for (int j = 0; j < kPer; ++j) {
-        p[j] = __builtin_amdgcn_raw_buffer_load_b32(pr, lane * 4, j * 256, 0);
-        q[j] = __builtin_amdgcn_raw_buffer_load_b32(qr, lane * 4, j * 256, 0);
+    for (;;) {
+      prow = p_target + (size_t)(n0 + cur) * V;
+      qrow = q_draft + (size_t)(n0 + cur) * V;
+      in_work = false;
+      // lanes that hold a child of the node: p and q of its token
+      const bool child = par == cur && len < max_path;
+      const int tok = child && did >= 0 && did < V ? did : -1;
+      float pf = 0.f, qf = 0.f;
+      if (tok >= 0) {
+        pf = prow[tok];
+        qf = qrow[tok];
       }
-      uint32_t a = 0, c = 0;
-#pragma unroll
-      for (int j = 0; j < kPer; ++j) {
-        p[j] = fix_prob(__uint_as_float(p[j]));
-        q[j] = fix_prob(__uint_as_float(q[j]));
-        a += p[j];
-        c += q[j];
-      }
-      for (int v = v_begin + kRange + lane; v < v_end; v += 64) { a += fix_prob(prow[v]); c += fix_prob(qrow[v]); }
-      both = ((u64)a << 32) | c;
-    }
-    uint32_t px = fix_prob(pf), qx = fix_prob(qf), q_left = qx;  // q_left: 0 once the token has been removed from q
-    both = exchange(wave_sum(both));
-    sp = (uint32_t)(both >> 32);
-    uint32_t sq = (uint32_t)both;
-    sp0 = (uint32_t)(share0 >> 32);
-    sp1 = (uint32_t)(share1 >> 32);
-    int taken = -1;
-    u64 left = __ballot(child);
-#pragma unroll 1
-    while (left) {
-      const int c = __builtin_amdgcn_readfirstlane(__builtin_ctzll(left));
-      left &= left - 1;
-      const uint32_t cp = __builtin_amdgcn_readlane(px, c), cq = __builtin_amdgcn_readlane(q_left, c);
-      const uint32_t u = __builtin_amdgcn_readlane(u_mine, c);
-      // u q_x S(p) < 2^32 p_x S(q)
-      if (mul_less((u64)u * cq, sp, (u64)cp * sq, 1ull << 32)) { taken = c; break; }
-      // the residual's sum, then the rescaled residual and its sum
-      u64 sr = 0;
-#pragma unroll
-      for (int j = 0; j < kPer; ++j) {
-        sr += residual(p[j], q[j], sp, sq);
-      }
-      for (int v = v_begin + kRange + lane; v < v_end; v += 64)
-        sr += residual(in_work ? work[v] : fix_prob(prow[v]), fix_prob(qrow[v]), sp, sq);
-      sr = exchange(wave_sum(sr));
-      if (sr != 0) {
-        const Divisor d = make_divisor(sr);
-        u64 snew = 0;
+      // The range's loads are all in flight before the first is used; buffer loads return zero beyond
+      // the range and cost one address register for all of them.
+      u64 both = 0;  // S(q) in the low word, S(p) in the high one: rows sum to less than 2
+      {
+        const int bytes = (r_end > v_begin ? r_end - v_begin : 0) * 4;
+        const auto pr = __builtin_amdgcn_make_buffer_rsrc((void *)(prow + v_begin), 0, bytes, kBufferFlags);
+        const auto qr = __builtin_amdgcn_make_buffer_rsrc((void *)(qrow + v_begin), 0, bytes, kBufferFlags);
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
-          p[j] = divide(residual(p[j], q[j], sp, sq), d);
-          snew += p[j];
+          p[j] = __builtin_amdgcn_raw_buffer_load_b32(pr, lane * 4, j * 256, 0);
+          q[j] = __builtin_amdgcn_raw_buffer_load_b32(qr, lane * 4, j * 256, 0);
         }
-        for (int v = v_begin + kRange + lane; v < v_end; v += 64) {
-          const uint32_t x = divide(residual(in_work ? work[v] : fix_prob(prow[v]), fix_prob(qrow[v]), sp, sq), d);
-          work[v] = x;
-          snew += x;
+        uint32_t a = 0, c = 0;
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+          p[j] = fix_prob(__uint_as_float(p[j]));
+          q[j] = fix_prob(__uint_as_float(q[j]));
+          a += p[j];
+          c += q[j];
         }
-        px = divide(residual(px, qx, sp, sq), d);
-        in_work = true;
-        sp = (uint32_t)exchange(wave_sum(snew));
-        sp0 = (uint32_t)share0;
-        sp1 = (uint32_t)share1;
+        for (int v = v_begin + kRange + lane; v < v_end; v += 64) { a += fix_prob(prow[v]); c += fix_prob(qrow[v]); }
+        both = ((u64)a << 32) | c;
       }
-      sq -= cq;
-      const int cx = __builtin_amdgcn_readlane(tok, c);
-      if (tok == cx) q_left = 0;
+      uint32_t px = fix_prob(pf), qx = fix_prob(qf), q_left = qx;  // q_left: 0 once the token has been removed from q
+      both = wave_sum(both);
+      if (!exchange(both)) return false;
+      sp = (uint32_t)(both >> 32);
+      uint32_t sq = (uint32_t)both;
+      sp0 = (uint32_t)(share0 >> 32);
+      sp1 = (uint32_t)(share1 >> 32);
+      int taken = -1;
+      u64 left = __ballot(child);
+#pragma unroll 1
+      while (left) {
+        const int c = __builtin_amdgcn_readfirstlane(__builtin_ctzll(left));
+        left &= left - 1;
+        const uint32_t cp = __builtin_amdgcn_readlane(px, c), cq = __builtin_amdgcn_readlane(q_left, c);
+        const uint32_t u = __builtin_amdgcn_readlane(u_mine, c);
+        // u q_x S(p) < 2^32 p_x S(q)
+        if (mul_less((u64)u * cq, sp, (u64)cp * sq, 1ull << 32)) { taken = c; break; }
+        // the residual's sum, then the rescaled residual and its sum
+        u64 sr = 0;
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+          sr += residual(p[j], q[j], sp, sq);
+        }
+        for (int v = v_begin + kRange + lane; v < v_end; v += 64)
+          sr += residual(in_work ? work[v] : fix_prob(prow[v]), fix_prob(qrow[v]), sp, sq);
+        sr = wave_sum(sr);
+        if (!exchange(sr)) return false;
+        if (sr != 0) {
+          const Divisor d = make_divisor(sr);
+          u64 snew = 0;
+#pragma unroll
+          for (int j = 0; j < kPer; ++j) {
+            p[j] = divide(residual(p[j], q[j], sp, sq), d);
+            snew += p[j];
+          }
+          for (int v = v_begin + kRange + lane; v < v_end; v += 64) {
+            const uint32_t x = divide(residual(in_work ? work[v] : fix_prob(prow[v]), fix_prob(qrow[v]), sp, sq), d);
+            work[v] = x;
+            snew += x;
+          }
+          px = divide(residual(px, qx, sp, sq), d);
+          in_work = true;
+          snew = wave_sum(snew);
+          if (!exchange(snew)) return false;
+          sp = (uint32_t)snew;
+          sp0 = (uint32_t)share0;
+          sp1 = (uint32_t)share1;
+        }
+        sq -= cq;
+        const int cx = __builtin_amdgcn_readlane(tok, c);
+        if (tok == cx) q_left = 0;
+      }
+      if (taken < 0) break;
+      if (lane == len) path = taken;
+      ++len;
+      cur = taken;
     }
-    if (taken < 0) break;
-    if (lane == len) path = taken;
-    ++len;
-    cur = taken;
-  }
 
-  // Last token: the wavefront whose share of p holds the bonus uniform's place finds it, and writes
-  // the step's results; wavefront 0 does when p is all zero, or when sums that overflow (rows far
-  // above 1) leave the place in nobody's share.
-  int bonus = -1;
-  if (sp == 0) {
-    if (w != 0) return;
-  } else {
-    u64 t = ((u64)u_bonus[b] * sp) >> 32;
-    const u64 before = wave_sum((lane < w ? (u64)sp0 : 0ull) + (lane + 64 < w ? (u64)sp1 : 0ull));
-    const u64 mine = wave_sum((lane == w ? (u64)sp0 : 0ull) + (lane + 64 == w ? (u64)sp1 : 0ull));
-    const bool nobody = t >= wave_sum((u64)sp0 + sp1);
-    if (nobody ? w != 0 : (t < before || t - before >= mine)) return;
-    t -= nobody ? 0 : before;
-    // the row of 64 consecutive tokens that holds the place, then the token
-    u64 acc = 0;
-    auto look = [&](uint32_t x, int v) {
-      const u64 row = wave_sum(x);
-      if (bonus < 0 && t < acc + row) {
-        u64 upto = x;  // inclusive prefix over the lanes
+    // Last token: the wavefront whose share of p holds the bonus uniform's place finds it, and writes
+    // the step's results; wavefront 0 does when p is all zero, or when sums that overflow (rows far
+    // above 1) leave the place in nobody's share.
+    int bonus = -1;
+    if (sp == 0) {
+      if (w != 0) return true;
+    } else {
+      u64 t = ((u64)u_bonus[b] * sp) >> 32;
+      const u64 before = wave_sum((lane < w ? (u64)sp0 : 0ull) + (lane + 64 < w ? (u64)sp1 : 0ull));
+      const u64 mine = wave_sum((lane == w ? (u64)sp0 : 0ull) + (lane + 64 == w ? (u64)sp1 : 0ull));
+      const bool nobody = t >= wave_sum((u64)sp0 + sp1);
+      if (nobody ? w != 0 : (t < before || t - before >= mine)) return true;
+      t -= nobody ? 0 : before;
+      // the row of 64 consecutive tokens that holds the place, then the token
+      u64 acc = 0;
+      auto look = [&](uint32_t x, int v) {
+        const u64 row = wave_sum(x);
+        if (bonus < 0 && t < acc + row) {
+          u64 upto = x;  // inclusive prefix over the lanes
 #pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-          const u64 y = __shfl_up(upto, off, 64);
-          if (lane >= off) upto += y;
+          for (int off = 1; off < 64; off <<= 1) {
+            const u64 y = __shfl_up(upto, off, 64);
+            if (lane >= off) upto += y;
+          }
+          bonus = v + __builtin_ctzll(__ballot(acc + upto > t));
         }
-        bonus = v + __builtin_ctzll(__ballot(acc + upto > t));
-      }
-      acc += row;
-    };
+        acc += row;
+      };
 #pragma unroll
-    for (int j = 0; j < kPer; ++j) look(p[j], v_begin + j * 64);
-    for (int v = v_begin + kRange; v < v_end; v += 64) {
-      const int at = v + lane;
-      look(at < v_end ? (in_work ? work[at] : fix_prob(prow[at])) : 0u, v);
+      for (int j = 0; j < kPer; ++j) look(p[j], v_begin + j * 64);
+      for (int v = v_begin + kRange; v < v_end; v += 64) {
+        const int at = v + lane;
+        look(at < v_end ? (in_work ? work[at] : fix_prob(prow[at])) : 0u, v);
+      }
     }
-  }
-  for (int j0 = 0; j0 < max_path; j0 += 64) {
-    const int j = j0 + lane;
-    const int node = j < len ? path : -1;
-    const int next = j0 == 0 ? __shfl(path, lane < 63 ? lane + 1 : lane, 64) : 0;
-    const int next_tok = __shfl(did, next, 64);
-    if (j < max_path) {
-      path_out[j] = j0 == 0 ? node : -1;
-      tok_out[j] = j0 == 0 && j + 1 < len ? next_tok : (j + 1 == len ? bonus : -1);
+    for (int j0 = 0; j0 < max_path; j0 += 64) {
+      const int j = j0 + lane;
+      const int node = j < len ? path : -1;
+      const int next = j0 == 0 ? __shfl(path, lane < 63 ? lane + 1 : lane, 64) : 0;
+      const int next_tok = __shfl(did, next, 64);
+      if (j < max_path) {
+        path_out[j] = j0 == 0 ? node : -1;
+        tok_out[j] = j0 == 0 && j + 1 < len ? next_tok : (j + 1 == len ? bonus : -1);
+      }
     }
+    if (lane == 0) { accept_len[b] = len; bonus_id[b] = bonus; }
+    return true;
+  };
+
+  if (w < workers && !walk() && lane == 0) {
+    if (workers > 1) atomicAdd(leave, kGaveUp);  // partners need not wait any longer
+    leave_mark = 1 + kGaveUp;
   }
-  if (lane == 0) { accept_len[b] = len; bonus_id[b] = bonus; }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t word = leave_mark;
+    if (groups > 1) word += atomicAdd(leave, leave_mark);
+    alone = word >= kGaveUp && (word & kLeft) == (uint32_t)groups;  // the last of the sequence, and somebody gave up
+  }
+  __syncthreads();
+  if (alone)
+    accept_alone({n0, n, parent, draft_ids, p_target, q_draft, u_accept, u_bonus[b], V, max_path, accept_len + b, path_out, tok_out,
+                  bonus_id + b}, alone_shared);
 }
 
 }  // namespace
@@ -348,7 +544,7 @@ hipError_t launch_tree_accept_sample(int32_t B, int32_t max_nodes, int32_t V, co
                                      const int32_t *parent, const int32_t *draft_ids, const float *p_target,
                                      const float *q_draft, const uint32_t *u_accept, const uint32_t *u_bonus,
                                      int32_t max_path, int32_t *accept_len, int32_t *accept_path,
-                                     int32_t *out_tokens, int32_t *bonus_id, uint32_t *work, hipStream_t s) {
+                                     int32_t *out_tokens, int32_t *bonus_id, uint32_t *work, int32_t polls, hipStream_t s) {
   // as few wavefronts as hold the vocabulary in registers: fewer partners per exchange
   int workers = (int)(((int64_t)V + kRange - 1) / kRange);
   if (workers > kMaxWorkers) workers = kMaxWorkers;
@@ -357,7 +553,7 @@ hipError_t launch_tree_accept_sample(int32_t B, int32_t max_nodes, int32_t V, co
   if (workers > 1) accept_sample_clear_kernel<<<(unsigned)B, 256, 0, s>>>(V, workers, work);
   const int64_t grid = (int64_t)B * groups;
   tree_accept_sample_kernel<<<(unsigned)grid, kThreads, 0, s>>>(
-      workers > 1 && grid > kDrawAbove, max_nodes, V, workers, groups, chunk, node_offset, parent, draft_ids, p_target, q_draft, u_accept, u_bonus, max_path,
+      polls, max_nodes, V, workers, groups, chunk, node_offset, parent, draft_ids, p_target, q_draft, u_accept, u_bonus, max_path,
       accept_len, accept_path, out_tokens, bonus_id, work);
   return hipGetLastError();
 }

@@ -431,14 +431,14 @@ size_t hb_tree_accept_sample_workspace_bytes(int32_t B, int32_t V) {
   return (B > 0 && V > 0) ? (size_t)B * (size_t)V * sizeof(uint32_t) : 0;
 }
 
-int32_t hb_tree_accept_sample(int32_t B, int32_t max_nodes_per_tree, int32_t V, const int32_t *node_offset,
-                              const int32_t *parent, const int32_t *draft_ids, const float *p_target,
-                              const float *q_draft, const uint32_t *u_accept, const uint32_t *u_bonus,
-                              int32_t max_path, int32_t *accept_len, int32_t *accept_path,
-                              int32_t *out_tokens, int32_t *bonus_id, void *workspace,
-                              size_t workspace_bytes, void *stream) {
-  if (B < 0 || max_path <= 0 || max_nodes_per_tree <= 0 || V <= 0)
-    return fail(HB_ERR_INVALID_ARG, "need B >= 0, max_path > 0, max_nodes_per_tree > 0, V > 0");
+int32_t hb_tree_accept_sample_polls(int32_t B, int32_t max_nodes_per_tree, int32_t V, const int32_t *node_offset,
+                                    const int32_t *parent, const int32_t *draft_ids, const float *p_target,
+                                    const float *q_draft, const uint32_t *u_accept, const uint32_t *u_bonus,
+                                    int32_t max_path, int32_t *accept_len, int32_t *accept_path,
+                                    int32_t *out_tokens, int32_t *bonus_id, void *workspace,
+                                    size_t workspace_bytes, int32_t max_polls, void *stream) {
+  if (B < 0 || max_path <= 0 || max_nodes_per_tree <= 0 || V <= 0 || max_polls < 0)
+    return fail(HB_ERR_INVALID_ARG, "need B >= 0, max_path > 0, max_nodes_per_tree > 0, V > 0, max_polls >= 0");
   if (max_nodes_per_tree > 64)
     return fail(HB_ERR_UNSUPPORTED, "max_nodes_per_tree %d: trees of more than 64 nodes are not supported",
                 max_nodes_per_tree);
@@ -453,8 +453,19 @@ int32_t hb_tree_accept_sample(int32_t B, int32_t max_nodes_per_tree, int32_t V, 
   if ((uintptr_t)workspace % 4) return fail(HB_ERR_WORKSPACE, "workspace must be 4-byte aligned");
   HB_HIP_TRY(launch_tree_accept_sample(B, max_nodes_per_tree, V, node_offset, parent, draft_ids, p_target, q_draft,
                                        u_accept, u_bonus, max_path, accept_len, accept_path, out_tokens, bonus_id,
-                                       (uint32_t *)workspace, (hipStream_t)stream));
+                                       (uint32_t *)workspace, max_polls, (hipStream_t)stream));
   return HB_OK;
+}
+
+int32_t hb_tree_accept_sample(int32_t B, int32_t max_nodes_per_tree, int32_t V, const int32_t *node_offset,
+                              const int32_t *parent, const int32_t *draft_ids, const float *p_target,
+                              const float *q_draft, const uint32_t *u_accept, const uint32_t *u_bonus,
+                              int32_t max_path, int32_t *accept_len, int32_t *accept_path,
+                              int32_t *out_tokens, int32_t *bonus_id, void *workspace,
+                              size_t workspace_bytes, void *stream) {
+  return hb_tree_accept_sample_polls(B, max_nodes_per_tree, V, node_offset, parent, draft_ids, p_target, q_draft, u_accept,
+                                     u_bonus, max_path, accept_len, accept_path, out_tokens, bonus_id, workspace,
+                                     workspace_bytes, HB_SAMPLE_POLLS, stream);
 }
 
 size_t hb_topk_logprob_workspace_bytes(int32_t M, int32_t V, int32_t k) {

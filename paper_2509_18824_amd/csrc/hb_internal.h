@@ -127,7 +127,7 @@ hipError_t launch_tree_accept_sample(int32_t B, int32_t max_nodes, int32_t V, co
                                      const int32_t *parent, const int32_t *draft_ids, const float *p_target,
                                      const float *q_draft, const uint32_t *u_accept, const uint32_t *u_bonus,
                                      int32_t max_path, int32_t *accept_len, int32_t *accept_path,
-                                     int32_t *out_tokens, int32_t *bonus_id, uint32_t *work, hipStream_t s);
+                                     int32_t *out_tokens, int32_t *bonus_id, uint32_t *work, int32_t polls, hipStream_t s);
 size_t topk_workspace_bytes(int32_t M, int32_t V, int32_t k);
 hipError_t launch_topk_logprob(int32_t dtype, int32_t M, int32_t V, int32_t k, const void *logits, int32_t *out_ids,
                                float *out_logp, void *work, hipStream_t s);

@@ -106,6 +106,9 @@ int main(void) {
   CHECK(hb_tree_accept_sample(2, 65, 100, p, p, p, p, p, p, p, 6, p, p, p, p, p, 1 << 20, NULL) == HB_ERR_UNSUPPORTED);
   CHECK(hb_tree_accept_sample(2, 60, 100, p, p, p, p, p, p, p, 6, p, p, p, p, p, 8, NULL) == HB_ERR_WORKSPACE);
   CHECK(hb_tree_accept_sample(0, 60, 100, NULL, NULL, NULL, NULL, NULL, NULL, NULL, 6, NULL, NULL, NULL, NULL, NULL, 0, NULL) == HB_OK);
+  CHECK(hb_tree_accept_sample_polls(2, 60, 100, p, p, p, p, p, p, p, 6, p, p, p, p, p, 1 << 20, -1, NULL) == HB_ERR_INVALID_ARG);
+  CHECK(hb_tree_accept_sample_polls(2, 60, 100, p, p, p, p, p, p, p, 6, p, p, p, p, p, 8, 0, NULL) == HB_ERR_WORKSPACE);
+  CHECK(hb_tree_accept_sample_polls(2, 60, 100, p, p, p, p, p, p, p, 6, p, p, p, p, (char *)p + 2, 1 << 20, 0, NULL) == HB_ERR_WORKSPACE);
   CHECK(hb_tree_accept_sample_workspace_bytes(16, 152064) == (size_t)16 * 152064 * 4);
   CHECK(hb_tree_positions(2, 65, 120, p, p, p, p, NULL) == HB_ERR_UNSUPPORTED);
   CHECK(hb_rope_table(4, 127, 1e6, p, p, p, NULL) == HB_ERR_INVALID_ARG);

@@ -136,3 +136,87 @@ def test_vocabularies_around_the_shares_of_the_wavefronts(step, V):
     Q = np.exp(0.7 * logits + rng.standard_normal((total, V))); Q /= Q.sum(1, keepdims=True)
     for trial in range(3):
         _both(step, trees, _draw_drafts(rng, trees, Q, V), P, Q, _u32(rng, total), _u32(rng, 3), 4)
+
+
+class _Case:
+    """One batch on the GPU with the oracle's answer; calls it with a workspace and a stream of the caller's."""
+
+    def __init__(self, seed, V, trees, max_path):
+        rng = np.random.default_rng(seed)
+        self.off = np.concatenate([[0], np.cumsum([len(t) for t in trees])]).astype(np.int32)
+        par, total = np.concatenate(trees).astype(np.int32), int(self.off[-1])
+        logits = rng.standard_normal((total, V)) * 2.0
+        P = np.exp(logits); P /= P.sum(1, keepdims=True)
+        Q = np.exp(0.7 * logits + rng.standard_normal((total, V))); Q /= Q.sum(1, keepdims=True)
+        draft = _draw_drafts(rng, trees, Q, V)
+        P, Q, ua, ub = P.astype(np.float32), Q.astype(np.float32), _u32(rng, total), _u32(rng, len(trees))
+        self.ref = tree_accept_sample_ref(self.off, par, draft, P, Q, ua, ub, max_path)
+        i32 = lambda a: torch.from_numpy(np.asarray(a).astype(np.uint32).view(np.int32)).cuda()
+        self.inputs = [i32(self.off), i32(par), i32(draft), torch.from_numpy(P).cuda(), torch.from_numpy(Q).cuda(), i32(ua), i32(ub)]
+        self.B, self.V, self.max_path, self.nodes = len(trees), V, max_path, max(len(t) for t in trees)
+
+    def outputs(self):
+        shapes = (self.B,), (self.B, self.max_path), (self.B, self.max_path), (self.B,)
+        return [torch.full(s, -7, dtype=torch.int32, device="cuda") for s in shapes]
+
+    def call(self, out, workspace, max_polls=None, stream=None):
+        import paper_2509_18824_amd as hb
+        args = (self.B, self.nodes, *self.inputs, self.max_path, *out, workspace)
+        if max_polls is None:
+            hb.hb_tree_accept_sample(*args, stream=stream)
+        else:
+            hb.hb_tree_accept_sample_polls(*args, max_polls, stream=stream)
+
+    def check(self, out):
+        for g, r in zip(out, self.ref):
+            assert np.array_equal(g.cpu().numpy(), r), (g.cpu().numpy(), r)
+
+
+_WIDE_TREE = np.array([-1] + [0] * 6 + [1, 2, 3, 7], dtype=np.int32)
+
+
+@pytest.mark.parametrize("max_polls", [0, 1, 3, 40])
+@pytest.mark.parametrize("V", [2561, 10241, 152064, 128 * 2560 + 77])
+def test_waits_that_run_out_give_the_same_results(V, max_polls):
+    """Partners that give up waiting (at once, or after some looks) leave the sequence to one workgroup."""
+    case = _Case(V + 1, V, [_WIDE_TREE, W.chain_tree(3), W.chain_tree(1)], 4)
+    out = case.outputs()
+    case.call(out, torch.empty(case.B * V, dtype=torch.int32, device="cuda"), max_polls)
+    torch.cuda.synchronize()
+    case.check(out)
+
+
+def test_workspace_of_an_earlier_launch_at_every_alignment():
+    """One buffer, full of other things, for launches of a large vocabulary, smaller odd ones and other
+    batches; it may start 4 bytes off an 8-byte boundary, and nothing beside it is touched."""
+    cases = [_Case(1, 327757, [_WIDE_TREE], 4), _Case(2, 2561, [_WIDE_TREE, W.chain_tree(2), _WIDE_TREE], 4),
+             _Case(3, 10243, [W.chain_tree(3)] * 2, 3)]
+    guard = 64
+    buf = torch.full((max(c.B * c.V for c in cases) + 2 * guard + 1,), -1, dtype=torch.int32, device="cuda")
+    assert buf.data_ptr() % 8 == 0
+    for rounds in range(2):
+        for c in cases:
+            for shift in (0, 1):
+                first, last = guard + shift, guard + shift + c.B * c.V
+                beside = buf.clone()
+                out = c.outputs()
+                c.call(out, buf[first:last])
+                torch.cuda.synchronize()
+                c.check(out)
+                assert torch.equal(buf[:first], beside[:first]) and torch.equal(buf[last:], beside[last:])
+
+
+def test_launches_on_two_streams():
+    """Two batches on two streams at a time, several times over, each with its own workspace."""
+    cases = [_Case(11, 152064, [_WIDE_TREE, W.chain_tree(3)] * 8, 4), _Case(12, 152064, [_WIDE_TREE] * 4, 4)]
+    streams = [torch.cuda.Stream() for _ in cases]
+    ws = [torch.empty(c.B * c.V, dtype=torch.int32, device="cuda") for c in cases]
+    outs = [[c.outputs() for _ in range(6)] for c in cases]
+    torch.cuda.synchronize()
+    for i in range(6):
+        for c, s, w, o in zip(cases, streams, ws, outs):
+            c.call(o[i], w, stream=s)
+    torch.cuda.synchronize()
+    for c, o in zip(cases, outs):
+        for out in o:
+            c.check(out)

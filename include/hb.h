@@ -287,8 +287,9 @@ int32_t hb_tree_accept(int32_t B, int32_t max_nodes_per_tree, const int32_t *nod
  *   last token    the smallest v with p_0 + .. + p_v > (u_bonus * S(p)) >> 32  (-1 when S(p) = 0)
  *
  *   p_target, q_draft  device float32 [total_nodes, V]: distributions AFTER each node (entries in
- *                      [0, 1], each row summing to at most about 1: larger sums overflow the
- *                      integer products and give unspecified, though memory-safe, results)
+ *                      [0, 1], each row summing to about 1.  Sums of 2 and more are done by one
+ *                      workgroup per sequence, slowly; from 4 on they overflow the integer
+ *                      products and give unspecified, though memory-safe, results)
  *   u_accept   device uint32 [total_nodes]: the uniform used when that node is tried as a child
  *   u_bonus    device uint32 [B]: the uniform of the step's last token
  *   workspace  device, hb_tree_accept_sample_workspace_bytes(B, V) bytes, 4-byte aligned; one call at a

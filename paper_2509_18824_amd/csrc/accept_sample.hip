@@ -21,7 +21,7 @@
 // range of a node's rows once and keep it in registers (40 values of p and of q per lane), so that a
 // rejection touches no vocabulary in memory; what crosses wavefronts are the sums.  Every wavefront
 // keeps p_x and q_x of the node's children in its lanes, updates them like any other value, and takes
-// every decision itself: no barrier on the way.  16 sequences of 60 nodes over 152064 tokens: 85 us, the
+// every decision itself: no barrier on the way.  16 sequences of 60 nodes over 152064 tokens: 79 us, the
 // kernel that clears the slots included.
 // What bounds it is the chain of the sequence with the most rejections (ten at the root: 73 us): per
 // rejection two exchanges of 2 us each and 2.5 us of 64-bit integer work, per node visited 5 us for its
@@ -40,7 +40,8 @@
 // and wait there for the other's.)  Where even those few find no CU, under a CU mask or beside many such
 // launches, a wavefront gives up after so many looks and says so in the sequence's leave word, which the
 // others look at while they wait; every workgroup counts itself out there, and the last one, which has no
-// partner left, does the whole sequence by itself (accept_alone).  Drawing cost that form 6 to
+// partner left, does the whole sequence by itself (accept_alone).  The same way go sequences whose rows sum
+// to 2 or more, which 32 bits do not hold.  Drawing cost that form 6 to
 // 14 us for 240 workgroups, nothing measurable for 60; four counters instead of one the same, the
 // workgroups of a sequence on one XCD 18 us: it is where a sequence's workgroups sit, not the counter.
 #include "hb_internal.h"
@@ -73,6 +74,7 @@ constexpr int kRange = kPer * 64;              // ... a wavefront (2560)
 constexpr int kMaxWorkers = 127;               // wavefronts per sequence; beyond 325120 tokens the rest stays in memory
 constexpr int kExchanges = 192;                // at most 64 nodes visited and two exchanges for each of 63 children
 constexpr u64 kPosted = 1ull << 63;
+constexpr uint32_t kMost = 0x7fffffff;          // sums of rows and residuals stay below: nearly 2 in fixed point
 constexpr uint32_t kGaveUp = 1u << 16;         // in a sequence's leave word: one for every wavefront that gave up ...
 constexpr uint32_t kLeft = kGaveUp - 1;        // ... above the count of its workgroups that have left
 constexpr int kBufferFlags = 0x00027000;       // untyped 32-bit elements
@@ -99,7 +101,25 @@ __device__ __forceinline__ u64 wave_sum(u64 x) {
   return (((u64)hi[0] << 32) | lo[0]) + (((u64)hi[1] << 32) | lo[1]);
 }
 
-// max(p S(q) - q S(p), 0); the sums of rows and of residuals are below 2^32
+// the same of 32-bit values, 0xffffffff where it does not fit
+__device__ __forceinline__ uint32_t add_sat(uint32_t x, uint32_t y) { return __builtin_elementwise_add_sat(x, y); }
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_add_sat(uint32_t x) {
+  return add_sat(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ uint32_t wave_sum_sat(uint32_t x) {
+  x = dpp_add_sat<0xB1>(x);
+  x = dpp_add_sat<0x4E>(x);
+  x = dpp_add_sat<0x141>(x);
+  x = dpp_add_sat<0x140>(x);
+  typedef unsigned int swap2 __attribute__((ext_vector_type(2)));
+  swap2 y = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  x = add_sat(y[0], y[1]);
+  y = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  return add_sat(y[0], y[1]);
+}
+
+// max(p S(q) - q S(p), 0); the sums of rows and of residuals are below 2^31
 __device__ __forceinline__ u64 residual(uint32_t p, uint32_t q, uint32_t sp, uint32_t sq) {
   const u64 a = (u64)p * sq, b = (u64)q * sp;
   return a > b ? a - b : 0ull;
@@ -340,15 +360,17 @@ __global__ __launch_bounds__(kThreads) void tree_accept_sample_kernel(
   uint32_t *work = (uint32_t *)(slots + kExchanges * kMaxWorkers) + (long long)w * (chunk - kRange) - v_begin - kRange;
   int k = 0;
 
-  // Sum of x over the sequence's wavefronts; lane i keeps the shares of wavefronts i and i + 64.  False:
+  // x of every wavefront of the sequence: lane i gets the shares of wavefronts i and i + 64.  False:
   // a share did not come in time, or somebody has given up (lane 63, which has no share to look for,
   // looks at the leave word instead).
-  u64 share0 = 0, share1 = 0;
   const bool wide = workers > 63;
-  auto exchange = [&](u64 &x) -> bool {
+  struct Shares {
+    u64 s0, s1;
+    bool ok;
+  };
+  auto exchange = [&](u64 x) -> Shares {
     if (workers == 1) {
-      share0 = lane == 0 ? x : 0ull;
-      return true;
+      return {lane == 0 ? x : 0ull, 0ull, true};
     }
     u64 *slot = slots + k * workers;
     ++k;
@@ -358,17 +380,14 @@ __global__ __launch_bounds__(kThreads) void tree_accept_sample_kernel(
     u64 y0 = 0, y1 = 0;
 #pragma unroll 1
     for (int i = 0;; ++i) {
-      if (i == polls) return false;
+      if (i == polls) return {0ull, 0ull, false};
       y0 = __hip_atomic_load(at0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       y1 = wide ? __hip_atomic_load(at1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : y0;
       const u64 posted = lane < 63 ? y0 & y1 & kPosted : (wide ? y0 & kPosted : kPosted);
       if (__all(posted != 0)) break;
-      if (__any(lane == 63 && (uint32_t)(y1 >> 32) >= kGaveUp)) return false;
+      if (__any(lane == 63 && (uint32_t)(y1 >> 32) >= kGaveUp)) return {0ull, 0ull, false};
     }
-    share0 = lane < workers ? y0 & ~kPosted : 0ull;
-    share1 = lane + 64 < workers ? y1 & ~kPosted : 0ull;
-    x = wave_sum(share0 + share1);
-    return true;
+    return {lane < workers ? y0 & ~kPosted : 0ull, lane + 64 < workers ? y1 & ~kPosted : 0ull, true};
   };
 
   auto walk = [&]() -> bool {
@@ -394,7 +413,7 @@ __global__ __launch_bounds__(kThreads) void tree_accept_sample_kernel(
       }
       // The range's loads are all in flight before the first is used; buffer loads return zero beyond
       // the range and cost one address register for all of them.
-      u64 both = 0;  // S(q) in the low word, S(p) in the high one: rows sum to less than 2
+      uint32_t a = 0, c = 0;  // this wavefront's shares of S(p) and S(q)
       {
         const int bytes = (r_end > v_begin ? r_end - v_begin : 0) * 4;
         const auto pr = __builtin_amdgcn_make_buffer_rsrc((void *)(prow + v_begin), 0, bytes, kBufferFlags);
@@ -404,24 +423,26 @@ __global__ __launch_bounds__(kThreads) void tree_accept_sample_kernel(
           p[j] = __builtin_amdgcn_raw_buffer_load_b32(pr, lane * 4, j * 256, 0);
           q[j] = __builtin_amdgcn_raw_buffer_load_b32(qr, lane * 4, j * 256, 0);
         }
-        uint32_t a = 0, c = 0;
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
           p[j] = fix_prob(__uint_as_float(p[j]));
           q[j] = fix_prob(__uint_as_float(q[j]));
-          a += p[j];
-          c += q[j];
+          a = add_sat(a, p[j]);
+          c = add_sat(c, q[j]);
         }
-        for (int v = v_begin + kRange + lane; v < v_end; v += 64) { a += fix_prob(prow[v]); c += fix_prob(qrow[v]); }
-        both = ((u64)a << 32) | c;
+        for (int v = v_begin + kRange + lane; v < v_end; v += 64) { a = add_sat(a, fix_prob(prow[v])); c = add_sat(c, fix_prob(qrow[v])); }
       }
       uint32_t px = fix_prob(pf), qx = fix_prob(qf), q_left = qx;  // q_left: 0 once the token has been removed from q
-      both = wave_sum(both);
-      if (!exchange(both)) return false;
-      sp = (uint32_t)(both >> 32);
-      uint32_t sq = (uint32_t)both;
-      sp0 = (uint32_t)(share0 >> 32);
-      sp1 = (uint32_t)(share1 >> 32);
+      // both in one exchange; a share that does not fit shows as kMost, and so the sum does not either
+      a = wave_sum_sat(a);
+      c = wave_sum_sat(c);
+      const Shares both = exchange(((u64)min(a, kMost) << 32) | min(c, kMost));
+      if (!both.ok) return false;
+      sp0 = (uint32_t)(both.s0 >> 32);
+      sp1 = (uint32_t)(both.s1 >> 32);
+      sp = wave_sum_sat(sp0 + sp1);
+      uint32_t sq = wave_sum_sat((uint32_t)both.s0 + (uint32_t)both.s1);
+      if (sp >= kMost || sq >= kMost) return false;
       int taken = -1;
       u64 left = __ballot(child);
 #pragma unroll 1
@@ -440,8 +461,9 @@ __global__ __launch_bounds__(kThreads) void tree_accept_sample_kernel(
         }
         for (int v = v_begin + kRange + lane; v < v_end; v += 64)
           sr += residual(in_work ? work[v] : fix_prob(prow[v]), fix_prob(qrow[v]), sp, sq);
-        sr = wave_sum(sr);
-        if (!exchange(sr)) return false;
+        const Shares rs = exchange(wave_sum(sr));
+        if (!rs.ok) return false;
+        sr = wave_sum(rs.s0 + rs.s1);
         if (sr != 0) {
           const Divisor d = make_divisor(sr);
           u64 snew = 0;
@@ -457,11 +479,11 @@ __global__ __launch_bounds__(kThreads) void tree_accept_sample_kernel(
           }
           px = divide(residual(px, qx, sp, sq), d);
           in_work = true;
-          snew = wave_sum(snew);
-          if (!exchange(snew)) return false;
-          sp = (uint32_t)snew;
-          sp0 = (uint32_t)share0;
-          sp1 = (uint32_t)share1;
+          const Shares ps = exchange(wave_sum(snew));
+          if (!ps.ok) return false;
+          sp0 = (uint32_t)ps.s0;
+          sp1 = (uint32_t)ps.s1;
+          sp = wave_sum_sat(sp0 + sp1);
         }
         sq -= cq;
         const int cx = __builtin_amdgcn_readlane(tok, c);
@@ -474,8 +496,7 @@ __global__ __launch_bounds__(kThreads) void tree_accept_sample_kernel(
     }
 
     // Last token: the wavefront whose share of p holds the bonus uniform's place finds it, and writes
-    // the step's results; wavefront 0 does when p is all zero, or when sums that overflow (rows far
-    // above 1) leave the place in nobody's share.
+    // the step's results; wavefront 0 does when p is all zero.
     int bonus = -1;
     if (sp == 0) {
       if (w != 0) return true;
@@ -483,9 +504,8 @@ __global__ __launch_bounds__(kThreads) void tree_accept_sample_kernel(
       u64 t = ((u64)u_bonus[b] * sp) >> 32;
       const u64 before = wave_sum((lane < w ? (u64)sp0 : 0ull) + (lane + 64 < w ? (u64)sp1 : 0ull));
       const u64 mine = wave_sum((lane == w ? (u64)sp0 : 0ull) + (lane + 64 == w ? (u64)sp1 : 0ull));
-      const bool nobody = t >= wave_sum((u64)sp0 + sp1);
-      if (nobody ? w != 0 : (t < before || t - before >= mine)) return true;
-      t -= nobody ? 0 : before;
+      if (t < before || t - before >= mine) return true;
+      t -= before;
       // the row of 64 consecutive tokens that holds the place, then the token
       u64 acc = 0;
       auto look = [&](uint32_t x, int v) {

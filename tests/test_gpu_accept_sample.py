@@ -220,3 +220,31 @@ def test_launches_on_two_streams():
     for c, o in zip(cases, outs):
         for out in o:
             c.check(out)
+
+
+@pytest.mark.parametrize("V", [60, 2000, 6001, 30011])
+def test_rows_that_sum_to_more_than_one(V, monkeypatch):
+    """Rows scaled to sums of 0.6 up to nearly 4, in one wavefront's share too: every sum and product is
+    held (the oracle's residual, made of Python integers here, has no limit)."""
+    import oracle.stochastic_acceptance as A
+
+    def residual(p, q, s_p, s_q):
+        r = [max(a * s_q - b * s_p, 0) for a, b in zip(p.tolist(), q.tolist())]
+        div = max(sum(r) >> A.FIX_BITS, 1)
+        return np.array([x // div for x in r], dtype=np.int64) if sum(r) else p
+
+    monkeypatch.setattr(A, "residual", residual)
+    rng = np.random.default_rng(V)
+    trees = [_WIDE_TREE, W.chain_tree(3)] * 4
+    total = sum(len(t) for t in trees)
+    logits = rng.standard_normal((total, V)) * 2.0
+    P = np.exp(logits); P /= P.sum(1, keepdims=True)
+    Q = np.exp(0.7 * logits + rng.standard_normal((total, V))); Q /= Q.sum(1, keepdims=True)
+    draft = _draw_drafts(rng, trees, Q, V)
+    scale = lambda: rng.choice([0.6, 1.0, 1.9, 2.0, 2.6, 3.9], size=(total, 1))
+    P *= scale()
+    Q *= scale()
+    P[::3, 5] = 1.5  # one token with nearly all of it
+    P[::3] *= 3.9 / P[::3].sum(1, keepdims=True)
+    import paper_2509_18824_amd.step as step
+    _both(step, trees, draft, P, Q, _u32(rng, total), _u32(rng, len(trees)), 4)

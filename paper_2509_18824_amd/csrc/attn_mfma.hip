@@ -333,13 +333,39 @@ __device__ __forceinline__ int ceil_div(int a, int b) {
   return (int)(((float)(a + b) - 0.5f) * __builtin_amdgcn_rcpf((float)b));
 }
 
+// Over the wavefront by data-parallel moves (a permute through LDS per step costs ten times as much):
+// inclusive sum over the lanes up to each, and the maximum of values >= 0.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp0(int x) {
+  return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xf, false);
+}
+__device__ __forceinline__ int scan_lanes(int x) {
+  x += dpp0<0x111, 0xf>(x);  // the lane 1, 2, 4, 8 below in the row of sixteen
+  x += dpp0<0x112, 0xf>(x);
+  x += dpp0<0x114, 0xf>(x);
+  x += dpp0<0x118, 0xf>(x);
+  x += dpp0<0x142, 0xa>(x);  // the last lane of the row below, then of the first two rows
+  x += dpp0<0x143, 0xc>(x);
+  return x;
+}
+__device__ __forceinline__ int sum_lanes(int x) { return __builtin_amdgcn_readlane(scan_lanes(x), 63); }
+__device__ __forceinline__ int max_lanes(int x) {
+  x = max(x, dpp0<0x111, 0xf>(x));
+  x = max(x, dpp0<0x112, 0xf>(x));
+  x = max(x, dpp0<0x114, 0xf>(x));
+  x = max(x, dpp0<0x118, 0xf>(x));
+  x = max(x, dpp0<0x142, 0xa>(x));
+  x = max(x, dpp0<0x143, 0xc>(x));
+  return __builtin_amdgcn_readlane(x, 63);
+}
+
 // TPW: 16-row tiles per wavefront (1 or 2).  NW: wavefronts per workgroup: 4 (two workgroups per
 // CU) or 8 (one per CU, twice the rows sharing each staged tile).  NS: LDS stages of the KV ring.
 // The tree tile, which goes through registers, is staged by all threads (NW = 4) or K by
 // wavefronts 0-3 and V by wavefronts 4-7 (NW = 8).
 template <int TPW, int NW, int NS>
 __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mfma_kernel(
-    hb_attn_desc d, int splits, int chunk_tokens, int workers, int min_per, int row_groups, const u32x4 *__restrict__ q, const u32x4 *__restrict__ k_tree,
+    hb_attn_desc d, int splits, int chunk_tokens, int workers, int each, int min_per, int row_groups, const u32x4 *__restrict__ q, const u32x4 *__restrict__ k_tree,
     const u32x4 *__restrict__ v_tree, const u32x4 *__restrict__ k_pool, const u32x4 *__restrict__ v_pool,
     const int32_t *__restrict__ block_table, const int32_t *__restrict__ prefix_len,
     const int32_t *__restrict__ node_offset, const int32_t *__restrict__ parent, bf16_t *__restrict__ out,
@@ -376,8 +402,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mfma_kernel(
   //    by worker boundaries gets one partial slot per piece (consecutive workers, consecutive
   //    slots); the piece that ends it announces the unused slots as empty; a sequence that lies
   //    inside one worker's range is written out directly and slot 0 tells the merge so.
-  constexpr int kRestart = 4;
-  int g, seg_b = 0, lo = 0, hi = 0, per = 1, w_id = 0, al_k = 0, al_n = 0;
+  constexpr int kRestart = 3;
+  int g, seg_b = 0, lo = 0, hi = 0, per = 1, w_id = 0, al_n = 0;
   bool aligned = false;
   int Lb = 0, tb = 0, cum = 0;  // lane b: prefix length, tiles and end of sequence b on the line
   if (workers == 0) {
@@ -392,36 +418,50 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mfma_kernel(
       Lb = Lb < 0 ? 0 : (Lb > cap ? cap : Lb);
       tb = (Lb + KT - 1) / KT + 1;
     }
-    cum = tb;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int y = __shfl_up(cum, off, 64);
-      if (lane >= off) cum += y;
-    }
-    const int total = __builtin_amdgcn_readfirstlane(__shfl(cum, 63, 64));
+    cum = scan_lanes(tb);
+    const int total = __builtin_amdgcn_readlane(cum, 63);
     per = (total + workers - 1) / workers;
     per = per < min_per ? min_per : per;
     // The alternative: the same number of workers for every sequence, each sequence cut into
-    // pieces of equal length.  No worker then has to start over on a second sequence (which
+    // pieces of one length.  No worker then has to start over on a second sequence (which
     // costs about kRestart tiles' time), but the longest sequence sets the pace.  Both plans
-    // are known here; take the one that finishes first.
-    al_k = workers / d.batch;
-    if (al_k >= 1) {
-      int nb = ceil_div(tb, min_per);
-      nb = nb < 1 ? 1 : (nb > al_k ? al_k : nb);
-      nb = nb > splits ? splits : nb;
-      int len = lane < d.batch ? (tb + nb - 1) / nb : 0;
+    // are known here, the second for a few lengths of piece; take the one that finishes first,
+    // counting what the pieces of cut sequences cost, in tiles' time: kPiece for each workgroup that
+    // works on one (its start, its rows written and read again by the merge), half a tile for the merge
+    // and 0.8 for every eight more slots of a row that it looks at.  (Constants and lengths from 496 shapes: 28/4, 32/8
+    // and 16/2 heads, trees of 30 and 60 nodes, chains of 8 and 16, 1 to 64 sequences of 200 to 8000, each
+    // in pieces of 2 to 32.  Whole call, us: one 60-node tree over 2048 positions 40.9 in pieces of 16, 32.7 of
+    // 8, 28 of 4; 16 over 200: 30.7 whole, 36.1 in pieces of 4; 24 over 250 to 1000: 58 whole, 63 cut; one 8-node
+    // chain over 2048: 20.1 in pieces of 8, 16.2 of 3; 24 over 200: 16.5 whole, 19.5 in pieces of 3.)
+    if (each >= 1) {
+      constexpr int kLengths[] = {NW == 8 ? 16 : 8, NW == 8 ? 8 : 6, NW == 8 ? 6 : 4, NW == 8 ? 4 : 3};
+      constexpr float kPiece = NW == 8 ? 0.018f : 0.0115f;
+      const int most = each < splits ? each : splits, longest = max_lanes(tb);
+      const float piece = kPiece * (float)(d.num_kv_heads * row_groups);
+      auto price = [&](int pieces, int of_longest) {
+        return pieces > 1 ? piece * (float)pieces + 0.5f + 0.8f * (float)((of_longest - 1) >> 3) : 0.f;
+      };
+      const int cuts = ceil_div(total, per) - 1;  // each makes two pieces of one, or one more
+      const float line = (float)(per + kRestart) + price(cuts + (cuts < d.batch ? cuts : d.batch), ceil_div(longest, per) + 1);
+      float best = __builtin_huge_valf();
 #pragma unroll
-      for (int off = 32; off > 0; off >>= 1) len = max(len, __shfl_xor(len, off, 64));
-      len = __builtin_amdgcn_readfirstlane(len);
-      aligned = len <= per + kRestart;
-      // pieces of sequence `lane`: the longest piece sets the pace, so the others are no shorter than
-      // they must be (fewer prologues, fewer partials)
-      al_n = len > 0 ? ceil_div(tb, len) : 1;
-      al_n = al_n < 1 ? 1 : (al_n > nb ? nb : al_n);
+      for (int i = 0; i < 4; ++i) {
+        if (kLengths[i] < min_per) break;  // uniform
+        int n = ceil_div(longest, kLengths[i]);
+        n = n < 1 ? 1 : (n > most ? most : n);
+        const int len = ceil_div(longest, n);
+        int mine = ceil_div(tb, len);  // pieces of sequence `lane`: the others are no shorter than they must be
+        mine = mine < 1 ? 1 : (mine > n ? n : mine);
+        const float cost = (float)len + price(sum_lanes(mine > 1 ? mine : 0), n);
+        if (cost < best) {
+          best = cost;
+          al_n = mine;
+        }
+      }
+      aligned = best <= line;
     }
     if (aligned) {
-      seg_b = w_id / al_k;
+      seg_b = w_id / each;
       if (seg_b >= d.batch) return;
     } else {
       lo = w_id * per;
@@ -455,7 +495,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mfma_kernel(
   } else if (aligned) {
     if (seg > 0) break;
     b = seg_b;
-    const int piece = w_id - b * al_k;
+    const int piece = w_id - b * each;
     const int t_b = __builtin_amdgcn_readfirstlane(__shfl(tb, b, 64));
     const int n_b = __builtin_amdgcn_readfirstlane(__shfl(al_n, b, 64));
     L = __builtin_amdgcn_readfirstlane(__shfl(Lb, b, 64));
@@ -794,7 +834,7 @@ hipError_t launch(int row_groups, const hb_attn_desc &d, const AttnPlan &plan, c
   auto kern = attn_mfma_kernel<TPW, NW, NS>;
   hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
   if (e != hipSuccess) return e;
-  kern<<<grid, 64 * NW, kLdsBytes, s>>>(d, plan.splits, plan.chunk_tokens, plan.workers, plan.min_per, row_groups, (const u32x4 *)q, (const u32x4 *)k_tree,
+  kern<<<grid, 64 * NW, kLdsBytes, s>>>(d, plan.splits, plan.chunk_tokens, plan.workers, plan.workers / (d.batch > 0 ? d.batch : 1), plan.min_per, row_groups, (const u32x4 *)q, (const u32x4 *)k_tree,
                                     (const u32x4 *)v_tree, (const u32x4 *)k_pool, (const u32x4 *)v_pool,
                                     block_table, prefix_len, node_offset, parent, (bf16_t *)out, lse, part_o,
                                     part_ml);

@@ -108,14 +108,9 @@ int32_t make_attn_plan(const hb_attn_desc *d, AttnPlan *plan) {
         int64_t workers = want / ((int64_t)d->num_kv_heads * plan->row_groups);
         if (workers < 1) workers = 1;
         if (workers > 4096) workers = 4096;
-        // The shortest piece (64-key tiles).  A piece costs a prologue (about three tiles' time) and a slot
-        // to merge; where sequences of the longest length give every worker a long one, that is the
-        // shortest, otherwise workers would be left without and pieces are cut from 4 (3) tiles on.  Whole
-        // call, 60-node trees, one sequence of 2048: 40.9 us in pieces of 16, 32.7 of 8, 28 of 4, 26.6 of 3; four of
-        // up to 4096: 54.8 / 44.2 / 44.2 / 44.3; 16 of up to 1024: 58.2 / 48.5 / 48.5 / 49.4; two of 32768: no difference.
-        // 8-node chains, one of 2048: 20.1 us in pieces of 8, 17.5 of 4, 16.3 of 3, 16.8 of 2; one of 8192:
-        // 24.6 / 23.0 / 23.8 / 29.1; 16 of up to 1024: 26.8 / 22.0 / 21.3 / 21.5; 16 of up to 4096: 0.5 us more with 3.
         const int64_t prefix_tiles = (span + 63) / 64;
+        // Pieces are no shorter than this many 64-key tiles: where sequences of the longest length give every
+        // worker a long piece, that is the shortest; otherwise the kernel, which knows the lengths, chooses.
         const int64_t long_piece = waves == 8 ? 16 : 8;
         const int64_t min_per = d->batch * prefix_tiles >= workers * long_piece ? long_piece : waves == 8 ? 4 : 3;
         plan->min_per = (int32_t)min_per;

@@ -374,6 +374,14 @@ SplitPlan split_plan(int M, int K, int V) {
   return best;
 }
 
+// whether the streaming kernel takes the product; otherwise *plan says how K is split
+bool stream_or_plan(int M, int K, int V, const float *part, SplitPlan *plan) {
+  *plan = {1, 1};
+  if (M <= kStreamAlways && proj_stream_takes(M, K, V, false)) return true;
+  if (part) *plan = split_plan(M, K, V);
+  return proj_stream_takes(M, K, V, plan->ks > 1);
+}
+
 template <bool ROPE, bool GLU>
 hipError_t launch_splitk(int M, int K, int V, SplitPlan plan, const void *hidden, const void *weight, const QkvArgs &qa,
                          const StoreArgs &sa, float *part, hipStream_t s) {
@@ -541,11 +549,11 @@ hipError_t launch_qkv_rope(int32_t M, int32_t K, int32_t Hq, int32_t Hkv, const 
   QkvArgs qa = {(const bf16_t *)bias, cos, sin, (bf16_t *)q, (bf16_t *)k, (bf16_t *)v, Hq, Hkv};
   StoreArgs sa = {nullptr, nullptr};
   const int V = (Hq + 2 * Hkv) * kHeadDim;
-  if (proj_stream_takes(M, K, V)) {
+  SplitPlan plan;
+  if (stream_or_plan(M, K, V, part, &plan)) {
     const StreamArgs st = {nullptr, nullptr, qa.bias, cos, sin, qa.q, qa.k, qa.v, Hq, Hkv};
     return launch_proj_stream(StreamKind::kRope, M, K, V, hidden, w_qkv, st, s);
   }
-  const SplitPlan plan = part ? split_plan(M, K, V) : SplitPlan{1, 1};
   if (plan.ks > 1) return launch_splitk<true, false>(M, K, V, plan, hidden, w_qkv, qa, sa, part, s);
   return dispatch<true, false>(M, K, V, hidden, w_qkv, qa, sa, s);
 }
@@ -554,8 +562,8 @@ hipError_t launch_linear(int32_t M, int32_t K, int32_t N, const void *x, const v
                          float *part, hipStream_t s) {
   QkvArgs qa = {};
   StoreArgs sa = {(const bf16_t *)residual, (bf16_t *)out};
-  if (proj_stream_takes(M, K, N)) return launch_proj_stream(StreamKind::kPlain, M, K, N, x, w, {sa.residual, sa.out}, s);
-  const SplitPlan plan = part ? split_plan(M, K, N) : SplitPlan{1, 1};
+  SplitPlan plan;
+  if (stream_or_plan(M, K, N, part, &plan)) return launch_proj_stream(StreamKind::kPlain, M, K, N, x, w, {sa.residual, sa.out}, s);
   if (plan.ks > 1) return launch_splitk<false, false>(M, K, N, plan, x, w, qa, sa, part, s);
   return dispatch<false, false>(M, K, N, x, w, qa, sa, s);
 }
@@ -564,8 +572,8 @@ hipError_t launch_swiglu(int32_t M, int32_t K, int32_t F, const void *x, const v
                          hipStream_t s) {
   QkvArgs qa = {};
   StoreArgs sa = {nullptr, (bf16_t *)out};
-  if (proj_stream_takes(M, K, 2 * F)) return launch_proj_stream(StreamKind::kGlu, M, K, 2 * F, x, w_gate_up, {nullptr, sa.out}, s);
-  const SplitPlan plan = part ? split_plan(M, K, 2 * F) : SplitPlan{1, 1};
+  SplitPlan plan;
+  if (stream_or_plan(M, K, 2 * F, part, &plan)) return launch_proj_stream(StreamKind::kGlu, M, K, 2 * F, x, w_gate_up, {nullptr, sa.out}, s);
   if (plan.ks > 1) return launch_splitk<false, true>(M, K, 2 * F, plan, x, w_gate_up, qa, sa, part, s);
   return dispatch<false, true>(M, K, 2 * F, x, w_gate_up, qa, sa, s);
 }

@@ -134,6 +134,21 @@ def test_gated_silu_projection_of_few_tokens(hb, T, K, F):
     test_gated_silu_projection(hb, T, K, F, False)
 
 
+# Past 16 tokens the split over K keeps long rows over few weight rows and many short ones; 33 tokens and
+# more always split where K allows it
+@pytest.mark.parametrize("T,K,N,res", [(25, 12288, 260, True), (24, 18944, 1024, False), (32, 18944, 2048, True), (17, 18944, 20, False),
+                                       (32, 512, 16404, True), (33, 2048, 1000, False), (33, 1024, 4, True), (40, 8192, 2052, True)])
+def test_output_projection_between_the_stream_and_the_split(hb, T, K, N, res):
+    assert hb.hb_proj_workspace_bytes(T, K, N) > 0 or N > 16384
+    _out_case(hb, T, K, N, res, True)
+    _out_case(hb, T, K, N, res, False)
+
+
+@pytest.mark.parametrize("T,K,Hq,Hkv,bias", [(33, 512, 1, 1, True), (24, 12288, 6, 1, False), (20, 3584, 28, 4, True)])
+def test_qkv_projection_between_the_stream_and_the_split(hb, T, K, Hq, Hkv, bias):
+    _qkv_case(hb, T, K, Hq, Hkv, bias, True)
+
+
 def _out_case(hb, T, K, N, res, with_workspace):
     g = torch.Generator().manual_seed(T + K + N)
     x = torch.randn((T, K), generator=g).to(torch.bfloat16)

@@ -33,6 +33,7 @@ constexpr int TV = 256;
 constexpr int CH = BK / 8;
 constexpr int kXcds = 8;
 constexpr int kHeadDim = 128;
+constexpr int64_t kUncached = 100 * 1000 * 1000;  // weights, 200 MB: read from memory whatever their loads say
 
 __device__ inline int swz(int r, int c) { return r * CH + (c ^ ((r & 7) ^ ((r >> 3) & 1))); }
 
@@ -52,8 +53,10 @@ struct StoreArgs {
 // ROPE: query/key/value projection with rotary embedding (V = (Hq + 2 Hkv) * 128 weight rows),
 // else plain projection.  One workgroup per (weight tile, hidden tile); the workgroups that share
 // a weight tile get neighbouring slots of one XCD (ids 8 apart) and find it in that XCD's L2.
-// WNT: the weight loads carry the non-temporal hint, where one hidden tile means that nobody shares
-// them (gated projection, 3584 x 37888: 64 tokens 65.3 -> 62.6 us, 128 tokens 73.4 -> 70.6 us).
+// WNT: the weight loads carry the non-temporal hint.  It pays where one hidden tile means that nobody shares
+// them and they are more than the last-level cache would keep: gated 3584 x 37888 (272 MB) 61.2 -> 57.9 us at
+// 33 tokens, 66.9 -> 63.0 at 128, 4096 x 28672 (235 MB) 71.8 -> 66.6 and 79.8 -> 74.0.  Smaller ones gain nothing
+// (3584 x 17920, 128 MB: 37.9 and 38.5), or lose what the cache would have had (512 x 2048, unsplit: 9.7 -> 11.8).
 template <int MT, bool ROPE, bool GLU, bool WNT>
 __global__ __launch_bounds__(512) void proj_mfma_kernel(int M, int K, int V, int m_tiles, int v_tiles,
                                                         const u32x4 *__restrict__ hidden,
@@ -175,7 +178,9 @@ hipError_t launch(int M, int K, int V, const void *hidden, const void *weight, c
   const int m_tiles = (M + TM - 1) / TM;
   const int v_tiles = (V + TV - 1) / TV;
   const size_t lds_bytes = (size_t)(3 * TV + 2 * TM) * CH * sizeof(u32x4);
-  auto kern = m_tiles == 1 ? proj_mfma_kernel<MT, ROPE, GLU, true> : proj_mfma_kernel<MT, ROPE, GLU, false>;
+  auto kern = proj_mfma_kernel<MT, ROPE, GLU, false>;
+  if constexpr (GLU)
+    if (m_tiles == 1 && (int64_t)K * V >= kUncached) kern = proj_mfma_kernel<MT, ROPE, GLU, true>;
   hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
   if (e != hipSuccess) return e;
   dim3 grid((unsigned)((v_tiles + kXcds - 1) / kXcds * kXcds * m_tiles));

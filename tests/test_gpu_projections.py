@@ -149,6 +149,12 @@ def test_qkv_projection_between_the_stream_and_the_split(hb, T, K, Hq, Hkv, bias
     _qkv_case(hb, T, K, Hq, Hkv, bias, True)
 
 
+# one tile of tokens and weights below and above the size from which their loads are non-temporal
+@pytest.mark.parametrize("T,K,F,ws", [(33, 4160, 11988, False), (40, 4160, 12100, False), (128, 4160, 12100, True), (24, 2048, 4100, True)])
+def test_gated_silu_projection_of_one_tile_of_tokens(hb, T, K, F, ws):
+    test_gated_silu_projection(hb, T, K, F, ws)
+
+
 def _out_case(hb, T, K, N, res, with_workspace):
     g = torch.Generator().manual_seed(T + K + N)
     x = torch.randn((T, K), generator=g).to(torch.bfloat16)

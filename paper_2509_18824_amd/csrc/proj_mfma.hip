@@ -33,7 +33,7 @@ constexpr int TV = 256;
 constexpr int CH = BK / 8;
 constexpr int kXcds = 8;
 constexpr int kHeadDim = 128;
-constexpr int64_t kUncached = 100 * 1000 * 1000;  // weights, 200 MB: read from memory whatever their loads say
+constexpr int64_t kUncached = (int64_t)1 << 27;  // weights: 256 MB, the size of the last-level cache
 
 __device__ inline int swz(int r, int c) { return r * CH + (c ^ ((r & 7) ^ ((r >> 3) & 1))); }
 
@@ -54,9 +54,9 @@ struct StoreArgs {
 // else plain projection.  One workgroup per (weight tile, hidden tile); the workgroups that share
 // a weight tile get neighbouring slots of one XCD (ids 8 apart) and find it in that XCD's L2.
 // WNT: the weight loads carry the non-temporal hint.  It pays where one hidden tile means that nobody shares
-// them and they are more than the last-level cache would keep: gated 3584 x 37888 (272 MB) 61.2 -> 57.9 us at
-// 33 tokens, 66.9 -> 63.0 at 128, 4096 x 28672 (235 MB) 71.8 -> 66.6 and 79.8 -> 74.0.  Smaller ones gain nothing
-// (3584 x 17920, 128 MB: 37.9 and 38.5), or lose what the cache would have had (512 x 2048, unsplit: 9.7 -> 11.8).
+// them and they exceed the last-level cache: gated 3584 x 37888 (272 MB) 61.2 -> 57.9 us at 33 tokens, 66.9 ->
+// 63.0 at 128, eight whole layers of 16 chains 1790 -> 1755.  4096 x 28672 (235 MB): eight layers 2018 and 2016,
+// and where the cache has the weights 40 -> 62; smaller ones lose the same way (512 x 2048, unsplit: 9.7 -> 11.8).
 template <int MT, bool ROPE, bool GLU, bool WNT>
 __global__ __launch_bounds__(512) void proj_mfma_kernel(int M, int K, int V, int m_tiles, int v_tiles,
                                                         const u32x4 *__restrict__ hidden,

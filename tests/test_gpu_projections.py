@@ -150,7 +150,7 @@ def test_qkv_projection_between_the_stream_and_the_split(hb, T, K, Hq, Hkv, bias
 
 
 # one tile of tokens and weights below and above the size from which their loads are non-temporal
-@pytest.mark.parametrize("T,K,F,ws", [(33, 4160, 11988, False), (40, 4160, 12100, False), (128, 4160, 12100, True), (24, 2048, 4100, True)])
+@pytest.mark.parametrize("T,K,F,ws", [(33, 4160, 16128, False), (40, 4160, 16136, False), (128, 4160, 16136, True), (24, 2048, 4100, True)])
 def test_gated_silu_projection_of_one_tile_of_tokens(hb, T, K, F, ws):
     test_gated_silu_projection(hb, T, K, F, ws)
 

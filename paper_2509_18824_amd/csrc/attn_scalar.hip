@@ -81,6 +81,10 @@ __device__ inline void absorb_keys(OnlineSoftmax<E> &st, const float *q_lds, con
     s = ((part[0] + part[1]) + (part[2] + part[3])) * scale;
   }
   const float m_new = fmaxf(st.m, wave_max(s));
+  if (m_new == -__builtin_huge_valf() && !__any(mine && s != s)) {
+    st.l = 1.f;  // nothing but scores of -inf so far: keys all the same, though any other outweighs them
+    return;
+  }
   const float corr = expf(st.m - m_new);  // exp(-inf) = 0 on the first keys
   const float p = mine ? expf(s - m_new) : 0.f;
   st.l = st.l * corr + p;
@@ -199,10 +203,11 @@ __global__ __launch_bounds__(kThreads) void attn_scalar_kernel(
 #pragma unroll
   for (int i = 0; i < kWaves; ++i) {
     const float li = ml_lds[i][1];
-    w[i] = li == 0.f ? 0.f : expf(ml_lds[i][0] - m);
+    w[i] = li == 0.f ? 0.f : ml_lds[i][0] == m ? 1.f : expf(ml_lds[i][0] - m);
     l += w[i] * li;
   }
-  const float inv = l > 0.f ? 1.f / l : 0.f;
+  if (splits == 1 && m == -__builtin_huge_valf() && l > 0.f) l = __builtin_nanf("");  // every score is -inf
+  const float inv = l == 0.f ? 0.f : 1.f / l;
   const size_t slot = (size_t)row * splits + c;
   for (int i = threadIdx.x; i < D; i += kThreads) {
     float o = 0.f;

@@ -111,6 +111,32 @@ def test_scalar_kernel_blocks_and_wavefronts(hb, step, dtype, D):
         check_attn(inp, out, lse, ref=ref, label=f"scalar {dtype} D={D} splits={splits}")
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("D", [64, 72])
+def test_scalar_kernel_keys_with_scores_of_minus_infinity(hb, step, dtype, D):
+    """Keys whose score is -inf have no weight beside any other, also where they fill the first block, a
+    wavefront's only one, a whole chunk, or everything but a node's own path; where a row has no other
+    keys, its result is NaN, as the definition's."""
+    trees = [W.chain_tree(2), W.seeded_tree(1), W.chain_tree(3), W.chain_tree(4), W.chain_tree(2)]
+    inp = W.make_verify_inputs(81, dtype, 4, 2, D, [600, 300, 64, 900, 100], trees, kv_std=1.0, q_std=1.0)
+    inp.q[..., 0] = inp.q[..., 0].abs() + 0.25
+    masked = [list(range(0, 128)) + list(range(256, 520)), range(64, 128), range(0, 64), list(range(0, 200)) + list(range(250, 900)), range(0, 100)]
+    for b, positions in enumerate(masked):
+        for p in positions:
+            inp.k_pool[int(inp.block_table[b, p // inp.page]), :, p % inp.page, 0] = float("-inf")
+    last = int(inp.node_offset[4])
+    inp.k_tree[last:, :, 0] = float("-inf")
+    with np.errstate(invalid="ignore"):
+        ref, ref_lse = oracle_attn(inp)
+    assert np.isfinite(ref[:last]).all() and np.isnan(ref[last:]).all()
+    for splits in (1, 2, 3, 0):
+        out, lse, _ = _run(step, inp, num_splits=splits, algo=hb.HB_ATTN_SCALAR)
+        got, got_lse = W.widen(out), W.widen(lse)
+        assert np.isnan(got[last:]).all(), splits
+        tol = 1e-5 if dtype == "f32" else 2e-2
+        assert np.abs(got[:last] - ref[:last]).max() <= tol and np.abs(got_lse[:last] - ref_lse[:last]).max() <= 1e-4, splits
+
+
 @pytest.mark.parametrize("nodes", [8, 60])
 @pytest.mark.parametrize("lens", [[1], [191], [193], [2048], [640, 64, 1500], [300] * 8, [100, 900, 0, 500, 70, 1400, 33, 256, 812]])
 def test_short_pieces_of_a_few_sequences(hb, step, nodes, lens):

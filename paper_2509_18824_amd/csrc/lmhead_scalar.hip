@@ -109,12 +109,16 @@ __device__ inline void fold_lanes(float (&x)[kRowsV * kRowsM], int lane) {
 }
 
 template <typename T>
-__global__ __launch_bounds__(64 * kRowsWaves) void lmhead_rows_kernel(int M, int K, int V, const T *__restrict__ hidden,
+__global__ __launch_bounds__(64 * kRowsWaves) void lmhead_rows_kernel(int M, int K, int V, int m_groups, const T *__restrict__ hidden,
                                                                       const T *__restrict__ weight,
                                                                       unsigned long long *__restrict__ keys) {
   __shared__ unsigned long long best[kRowsWaves][kRowsM];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int v0 = (blockIdx.x * kRowsWaves + wave) * kRowsV, m0 = blockIdx.y * kRowsM;
+  // the groups of hidden rows are neighbours, so that memory gives a weight row once and the last-level cache
+  // the others (one group after the other, 32 rows x 3592 x 152064 float32: 1900 us, beside each
+  // other 1435)
+  const int group = blockIdx.x / m_groups;
+  const int v0 = (group * kRowsWaves + wave) * kRowsV, m0 = ((int)blockIdx.x - group * m_groups) * kRowsM;
   const T *w[kRowsV], *h[kRowsM];  // rows past the end read the last one and are dropped below
 #pragma unroll
   for (int i = 0; i < kRowsV; ++i) w[i] = weight + (size_t)min(v0 + i, V - 1) * K;
@@ -180,8 +184,9 @@ __global__ void lmhead_finish_kernel(const unsigned long long *keys, int M, int 
 
 // Up to 32 rows the wavefronts' re-reading of the weight rows, once per eight hidden rows, costs less
 // than the tile kernel's empty rows and round trips (float32, call with both small kernels):
-// K x V = 256 x 1000, 1..256 rows 17.5 us against 32.6..36; 1024 x 32000: 8 rows 39 us against 155, 32 rows 116
-// against 157, 64 rows 224 against 177.  Rows must consist of whole 16-byte pieces.
+// K x V = 256 x 1000, 1..256 rows 17.5 us against 32.6..36; 1024 x 32000: 8 rows 44 us against 157, 32 rows 93
+// against 159, 64 rows 224 against 177 (one group of rows after the other); 1032 x 128000, 32 rows 406 against 396.
+// Rows must consist of whole 16-byte pieces.
 static bool rows_kernel_takes(int32_t dtype, int32_t M, int32_t K) {
   return M <= 32 && K % (dtype == HB_F32 ? Piece<float>::n : Piece<bf16_t>::n) == 0;
 }
@@ -190,11 +195,12 @@ hipError_t launch_lmhead_scalar(int32_t dtype, int32_t M, int32_t K, int32_t V, 
                                 const void *weight, unsigned long long *keys, hipStream_t s) {
   if (rows_kernel_takes(dtype, M, K)) {
     constexpr int kPerGroup = kRowsWaves * kRowsV;
-    dim3 grid((unsigned)((V + kPerGroup - 1) / kPerGroup), (unsigned)((M + kRowsM - 1) / kRowsM));
+    const int m_groups = (M + kRowsM - 1) / kRowsM;
+    const unsigned grid = (unsigned)((V + kPerGroup - 1) / kPerGroup) * (unsigned)m_groups;
     if (dtype == HB_F32)
-      lmhead_rows_kernel<float><<<grid, 64 * kRowsWaves, 0, s>>>(M, K, V, (const float *)hidden, (const float *)weight, keys);
+      lmhead_rows_kernel<float><<<grid, 64 * kRowsWaves, 0, s>>>(M, K, V, m_groups, (const float *)hidden, (const float *)weight, keys);
     else
-      lmhead_rows_kernel<bf16_t><<<grid, 64 * kRowsWaves, 0, s>>>(M, K, V, (const bf16_t *)hidden, (const bf16_t *)weight, keys);
+      lmhead_rows_kernel<bf16_t><<<grid, 64 * kRowsWaves, 0, s>>>(M, K, V, m_groups, (const bf16_t *)hidden, (const bf16_t *)weight, keys);
     return hipGetLastError();
   }
   dim3 grid((unsigned)((V + TN - 1) / TN), (unsigned)((M + TM - 1) / TM));

@@ -52,10 +52,27 @@ __device__ inline void load8(const bf16_t *p, float (&x)[8]) {
   }
 }
 
+// A lane's E elements of a row of V.  float32: every 64th, a load of 256 bytes each (two or four neighbours
+// in one load: 28/4 heads of 128, 60-node trees over 4 x 500 positions 261 -> 300 us).  bf16: E neighbours in one
+// load (every 64th, 128 bytes each: 8/8 heads of 256, 16 x 200 positions 461 us, in one load 212).
+template <typename T, int E>
+__device__ inline int dim_of(int lane, int e) { return sizeof(T) == 2 ? E * lane + e : lane + 64 * e; }
+template <int E>
+__device__ inline void load_row(const bf16_t *row, int lane, int D, float (&x)[E]) {
+  if (E * lane >= D) return;  // head_dim % 8 == 0: all of them or none
+  uint32_t a[E / 2];
+  __builtin_memcpy(a, __builtin_assume_aligned(row + E * lane, 2 * E), 2 * E);
+#pragma unroll
+  for (int e = 0; e < E / 2; ++e) {
+    x[2 * e] = __uint_as_float(a[e] << 16);
+    x[2 * e + 1] = __uint_as_float(a[e] & 0xffff0000u);
+  }
+}
+
 template <int E>
 struct OnlineSoftmax {
   float m, l;     // reference exponent; this lane's share of the sum
-  float acc[E];   // head dimensions lane, lane + 64, ...
+  float acc[E];   // head dimensions dim_of(lane, 0), ...
 };
 
 // Up to 64 keys, one per lane: `live` marks the lanes that hold one, `off` is the key's offset in
@@ -105,9 +122,13 @@ __device__ inline void absorb_keys(OnlineSoftmax<E> &st, const float *q_lds, con
         w[u] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(p), j));
         const size_t o = (size_t)(uint32_t)__builtin_amdgcn_readlane(off_lo, j) |
                          ((size_t)(uint32_t)__builtin_amdgcn_readlane(off_hi, j) << 32);
+        if constexpr (sizeof(T) == 2 && E > 1) {
+          load_row<E>(v + o, lane, D, x[u]);
+        } else {
 #pragma unroll
-        for (int e = 0; e < E; ++e)
-          if (lane + 64 * e < D) x[u][e] = load_f32(v + o + lane + 64 * e);
+          for (int e = 0; e < E; ++e)
+            if (lane + 64 * e < D) x[u][e] = load_f32(v + o + lane + 64 * e);
+        }
       }
     }
 #pragma unroll
@@ -191,7 +212,7 @@ __global__ __launch_bounds__(kThreads) void attn_scalar_kernel(
   // the wavefronts' results are combined through LDS; one without keys has l = 0 and no weight
   const float l_wave = wave_sum(st.l);
 #pragma unroll
-  for (int e = 0; e < E; ++e) acc_lds[wave][lane + 64 * e] = st.acc[e];
+  for (int e = 0; e < E; ++e) acc_lds[wave][dim_of<T, E>(lane, e)] = st.acc[e];
   if (lane == 0) {
     ml_lds[wave][0] = st.m;
     ml_lds[wave][1] = l_wave;

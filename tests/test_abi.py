@@ -171,6 +171,45 @@ def test_meta_query_argument_errors():
     assert L.hb_meta_query_attn(4, 28, 3584, 28, 3, p, p, p, None, p, None, None, need, None) == 3
 
 
+def test_meta_query_project_argument_errors():
+    L, p = hb.lib, C.c_void_p(0x1000)
+    call = L.hb_meta_query_attn_project
+    need = hb.hb_meta_query_attn_project_workspace_bytes(4, 3584, 28, 3)
+    assert need >= 3584 * 3584 * 2
+    layers, ok_layers = (C.c_int32 * 3)(0, 14, 28), (C.c_int32 * 3)(0, 14, 27)
+    assert call(4, 28, 3584, 56, 1, p, p, p, None, p, None, p, 1 << 30, None) == 2       # heads of 64
+    assert "heads of 128" in hb.hb_last_error()
+    assert call(4, 28, 3584, 14, 3, p, p, p, None, p, None, p, 1 << 30, None) == 2       # heads of 256
+    assert call(4, 33, 3584, 28, 3, p, p, p, None, p, None, p, 1 << 30, None) == 2       # L > 32
+    assert call(4, 28, 3584, 28, 5, p, p, p, None, p, None, p, 1 << 30, None) == 2       # Q > 4
+    assert call(-1, 28, 3584, 28, 3, p, p, p, None, p, None, p, 1 << 30, None) == 1
+    assert call(4, 28, 3584, 28, 3, p, p, p, layers, p, p, p, 1 << 30, None) == 1        # layer 28 of 28
+    assert call(4, 28, 3584, 28, 3, p, p, p, ok_layers, p, None, p, 1 << 30, None) == 1  # no residual_out
+    assert call(4, 28, 3584, 28, 3, p, None, p, None, p, None, p, 1 << 30, None) == 1    # no w_v
+    assert call(4, 28, 3584, 28, 3, p, C.c_void_p(0x1008), p, None, p, None, p, 1 << 30, None) == 1
+    assert call(4, 28, 3584, 28, 3, p, p, p, None, p, None, p, need - 1, None) == 3
+    assert call(4, 28, 3584, 28, 3, p, p, p, None, p, None, None, need, None) == 3
+    assert call(4, 28, 3584, 28, 3, p, p, p, None, p, None, C.c_void_p(0x1004), 1 << 30, None) == 3  # 16-byte alignment
+    assert call(0, 28, 3584, 28, 3, None, None, None, None, None, None, None, 0, None) == 0
+    assert hb.hb_meta_query_attn_project_workspace_bytes(0, 3584, 28, 3) == 0
+    assert hb.hb_meta_query_attn_project_workspace_bytes(4, 3584, 56, 1) == 0
+    assert hb.hb_meta_query_attn_project_pays(2048, 28, 3584, 28, 3) and not hb.hb_meta_query_attn_project_pays(4, 28, 3584, 28, 3)
+    assert not hb.hb_meta_query_attn_project_pays(2048, 28, 3584, 56, 1) and not hb.hb_meta_query_attn_project_pays(0, 28, 3584, 28, 3)
+
+
+def test_sampling_acceptance_with_a_number_of_polls():
+    L, p = hb.lib, C.c_void_p(0x1000)
+    args = (p, p, p, p, p, p, p, 6, p, p, p, p)
+    call = L.hb_tree_accept_sample_polls
+    assert call(2, 60, 152064, *args, p, 1 << 30, -1, None) == 1
+    assert call(2, 65, 152064, *args, p, 1 << 30, 0, None) == 2
+    assert call(2, 60, 152064, *args, p, 2 * 152064 * 4 - 1, 0, None) == 3
+    assert call(2, 60, 152064, *args, C.c_void_p(0x1002), 1 << 30, 0, None) == 3
+    assert call(0, 60, 152064, *args, None, 0, 0, None) == 0
+    header = open(os.path.join(ROOT, "include", "hb.h")).read()
+    assert int(re.search(r"#define HB_SAMPLE_POLLS (\d+)", header).group(1)) == hb.binding.HB_SAMPLE_POLLS
+
+
 def test_layer_rest_argument_errors():
     L, p = hb.lib, C.c_void_p(0x1000)
     assert L.hb_rmsnorm(4, 3584, p, p, 1e-6, None, None) == 1

@@ -105,6 +105,35 @@ def test_values_projected_after_the_mixing(S, n_tok, L, D, H, Q, layers):
     assert np.linalg.norm(got - ref) <= 4e-3 * np.linalg.norm(ref)
 
 
+@pytest.mark.parametrize("n_tok,L,D,H,Q", [(7, 28, 768, 6, 3), (1203, 5, 768, 6, 2), (1025, 5, 512, 4, 2)])
+@pytest.mark.parametrize("bad", [float("inf"), float("-inf"), float("nan")])
+def test_a_token_with_features_that_are_not_finite(S, n_tok, L, D, H, Q, bad):
+    """Its own rows are NaN whether values are projected before or after the mixing (an infinite score
+    leaves no finite probability times a finite value); every other token's are as without it."""
+    import paper_2509_18824_amd as hb
+    x = W.make_meta_inputs(9, n_tok, L, D, H, Q)
+    g = {k: v.cuda() for k, v in x.items()}
+    layer = S.MetaQueryLayer(g["f_q"], g["w_q"], g["w_k"], g["w_v"], g["w_o"], g["w_fc1"], H)
+
+    def both(feats):
+        v_proj = torch.empty(n_tok * L, D, dtype=torch.bfloat16, device="cuda")
+        hb.hb_out_project(feats.view(n_tok * L, D), g["w_v"], None, v_proj)
+        first, after = (torch.empty(n_tok, Q, D, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+        ws = S.alloc_workspace(hb.hb_meta_query_attn_workspace_bytes(n_tok, D, H, Q))
+        hb.hb_meta_query_attn(H, Q, feats, v_proj.view(n_tok, L, D), layer.a_fold, None, first, None, ws)
+        ws = S.alloc_workspace(hb.hb_meta_query_attn_project_workspace_bytes(n_tok, D, H, Q))
+        hb.hb_meta_query_attn_project(H, Q, feats, g["w_v"], layer.a_fold, None, after, None, ws)
+        torch.cuda.synchronize()
+        return first, after
+
+    clean = both(g["feats"])
+    feats, at = g["feats"].clone(), n_tok - 2
+    feats[at, L - 1, 129] = bad
+    for got, want in zip(both(feats), clean):
+        assert torch.isnan(got[at]).all()
+        assert torch.equal(got[:at], want[:at]) and torch.equal(got[at + 1:], want[at + 1:])
+
+
 def test_prefill_scale_on_sampled_tokens(S):
     """1024 tokens of the target model's shape (one workgroup column per two slices of D in the
     score kernel, 128 token groups); every token is independent of the others, so the oracle

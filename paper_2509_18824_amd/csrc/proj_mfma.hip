@@ -379,12 +379,13 @@ SplitPlan split_plan(int M, int K, int V) {
   return best;
 }
 
-// whether the streaming kernel takes the product; otherwise *plan says how K is split
+// Whether the streaming kernel takes the product; otherwise *plan says how K is split.  The plan costs the
+// host some microseconds and is made only where it matters.
 bool stream_or_plan(int M, int K, int V, const float *part, SplitPlan *plan) {
   *plan = {1, 1};
-  if (M <= kStreamAlways && proj_stream_takes(M, K, V, false)) return true;
+  if (proj_stream_takes(M, K, V, true)) return true;  // then also where K is not split
   if (part) *plan = split_plan(M, K, V);
-  return proj_stream_takes(M, K, V, plan->ks > 1);
+  return plan->ks <= 1 && proj_stream_takes(M, K, V, false);
 }
 
 template <bool ROPE, bool GLU>

@@ -290,10 +290,11 @@ hipError_t dispatch(int M, int K, int N, const void *hidden, const void *weight,
 bool proj_stream_takes(int32_t M, int32_t K, int32_t N, bool split) {
   const int tiles = (N + 15) / 16;
   if (M > 32 || K % 64 || K / 64 < kWaves || (int64_t)K * 64 >= ((int64_t)1 << 31)) return false;
-  if (M <= kStreamAlways) return true;
+  if (M <= 16) return true;
   const int64_t weights = (int64_t)K * N;
-  if (tiles > 256) return tiles >= 1024 && (split ? weights >= 60 * 1000 * 1000 : K >= 2048);
-  return !split || K <= 8192 || weights >= 60 * 1000 * 1000 || (M <= 24 && N >= 2048);
+  const bool large = weights >= 60 * 1000 * 1000;
+  if (tiles > 256) return tiles >= 1024 && (large || (!split && K >= 2048));
+  return !split || large || K <= 8192 || (M <= 24 && N >= 2048);
 }
 
 hipError_t launch_proj_stream(StreamKind kind, int32_t M, int32_t K, int32_t N, const void *hidden, const void *weight,

@@ -422,8 +422,9 @@ def bench_draft_tree(steps, warmup, B=16, K=10, T=5, N=60, V=152064):
 def bench_meta_query(steps, warmup, n_tok=96, L=28, D=3584, H=28, Q=3):
     """The draft model's intermediate layer (meta-query cross-attention over the target's layer
     features, output projection with skip connection, fc1) on the tokens one step commits at most
-    (16 sequences x 6), random weights.  Per call: value projection GEMM [n_tok * L, D] x [D, D],
-    the score and softmax / mixing kernels, output projection, fc1."""
+    (16 sequences x 6), random weights.  Per call, as MetaQueryLayer runs it: scores, then the mixing with
+    the values projected after it, or, where that does not pay, the value projection GEMM
+    [n_tok * L, D] x [D, D], scores and mixing; output projection, fc1."""
     import torch
     import workloads as W
     import paper_2509_18824_amd as hb
@@ -434,10 +435,12 @@ def bench_meta_query(steps, warmup, n_tok=96, L=28, D=3584, H=28, Q=3):
     feats = x["feats"]
     bf = lambda *shape: torch.empty(shape, dtype=torch.bfloat16, device="cuda")
     v_proj, pre, res, f_c, out = bf(n_tok * L, D), bf(n_tok * Q, D), bf(n_tok * Q, D), bf(n_tok * Q, D), bf(n_tok, D)
-    names = ("value_projection", "meta_query_attn", "output_projection", "fc1")
+    after = hb.hb_meta_query_attn_project_pays(n_tok, L, D, H, Q)  # values projected after the mixing
+    names = (() if after else ("value_projection",)) + ("meta_query_attn", "output_projection", "fc1")
     ws_fc1 = S.alloc_workspace(hb.hb_proj_workspace_bytes(n_tok, Q * D, D))  # split-K partials (few tokens only)
     ws_out = S.alloc_workspace(hb.hb_proj_workspace_bytes(n_tok * Q, D, D))
-    ws_attn = S.alloc_workspace(hb.hb_meta_query_attn_workspace_bytes(n_tok, D, H, Q))  # partial scores
+    ws_attn = S.alloc_workspace(hb.hb_meta_query_attn_project_workspace_bytes(n_tok, D, H, Q) if after
+                                else hb.hb_meta_query_attn_workspace_bytes(n_tok, D, H, Q))  # partial scores
 
     def call(ev=None):
         marks = []
@@ -447,10 +450,14 @@ def bench_meta_query(steps, warmup, n_tok=96, L=28, D=3584, H=28, Q=3):
                 e.record()
                 marks.append(e)
         mark()
-        hb.hb_out_project(feats.view(n_tok * L, D), layer.w_v, None, v_proj)
-        mark()
-        hb.hb_meta_query_attn(H, Q, feats, v_proj.view(n_tok, L, D), layer.a_fold, layer.residual_layers,
-                              pre.view(n_tok, Q, D), res.view(n_tok, Q, D), ws_attn)
+        if after:
+            hb.hb_meta_query_attn_project(H, Q, feats, layer.w_v, layer.a_fold, layer.residual_layers,
+                                          pre.view(n_tok, Q, D), res.view(n_tok, Q, D), ws_attn)
+        else:
+            hb.hb_out_project(feats.view(n_tok * L, D), layer.w_v, None, v_proj)
+            mark()
+            hb.hb_meta_query_attn(H, Q, feats, v_proj.view(n_tok, L, D), layer.a_fold, layer.residual_layers,
+                                  pre.view(n_tok, Q, D), res.view(n_tok, Q, D), ws_attn)
         mark()
         hb.hb_out_project_ws(pre, layer.w_o, res, f_c, ws_out)
         mark()
@@ -472,11 +479,13 @@ def bench_meta_query(steps, warmup, n_tok=96, L=28, D=3584, H=28, Q=3):
         call(ev)
     torch.cuda.synchronize()
     parts = {n: sum(m[i].elapsed_time(m[i + 1]) for m in ev) / steps for i, n in enumerate(names)}
-    attn_bytes = 2 * n_tok * L * D * 2 + 2 * n_tok * Q * D * 2
+    # features, projected values or W_v, the result, the residual rows
+    attn_bytes = n_tok * L * D * 2 + (D * D if after else n_tok * L * D) * 2 + 2 * n_tok * Q * D * 2
     return {
         "what": f"{n_tok} tokens x {L} layer features of size {D}, {H} heads, {Q} meta queries, bf16, random weights",
         "ms_per_call": ms, "tokens_per_s": n_tok / (ms * 1e-3), "ms_by_call": parts,
-        "value_projection_TFLOPs": 2.0 * n_tok * L * D * D / (parts["value_projection"] * 1e-3) / 1e12,
+        "values_projected_after_mixing": after,
+        "value_projection_TFLOPs": None if after else 2.0 * n_tok * L * D * D / (parts["value_projection"] * 1e-3) / 1e12,
         "meta_query_attn_bytes": attn_bytes,
         "meta_query_attn_GBps": attn_bytes / (parts["meta_query_attn"] * 1e-3) / 1e9,
     }

@@ -54,7 +54,7 @@ typedef enum hb_dtype { HB_F32 = 0, HB_BF16 = 1 } hb_dtype;
 /* Kernel choice for hb_tree_verify_attn. */
 typedef enum hb_attn_algo {
   HB_ATTN_AUTO = 0,   /* MFMA kernel when the shape allows it, else the scalar kernel        */
-  HB_ATTN_SCALAR = 1, /* one wavefront per (node, query head, split); any dtype, fp32 math  */
+  HB_ATTN_SCALAR = 1, /* one workgroup per (node, query head, split); any dtype, fp32 math   */
   HB_ATTN_MFMA = 2    /* bf16, head_dim 128, page 16: KV tile shared by all nodes and the   */
                       /* query heads of a kv group, bf16 MFMA with fp32 accumulation         */
 } hb_attn_algo;
@@ -203,6 +203,8 @@ int32_t hb_out_project(int32_t T, int32_t K, int32_t N, const void *x, const voi
  * partial results in the workspace and finish (sum in fixed order, bias, rotary embedding,
  * residual) in a second kernel.  Results are deterministic; they differ from the calls above in
  * fp32 summation order only.
+ * Up to 16 tokens (K >= 512), and up to 32 where that is the faster way, both kinds of call stream the
+ * weights in one kernel instead and leave the workspace alone; its size above does not change.
  *   workspace   device, hb_proj_workspace_bytes(T, K, N) bytes (N = (Hq + 2 Hkv) * 128 for the
  *               QKV projection), 16-byte aligned.  That size is 0 when the split does not apply
  *               (more than 1024 tokens, K too short to cut, or more than 512 tokens and no gain
@@ -473,6 +475,8 @@ int32_t hb_meta_query_attn(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q
  * applied to the mixture, which is the same sum in another order and L / Q times less work.  Steps
  * (2) and (3) above in one call; heads of 128 only (UNSUPPORTED otherwise, and 0 bytes).  The
  * workspace, 16-byte aligned, also takes a copy of w_v that every call makes anew.
+ * A token with a feature that is not finite has NaN in its own rows both ways; weights are taken to be
+ * finite (an infinite W_v may give NaN here where the other way gives an infinity).
  * hb_meta_query_attn_project_pays: 1 where this is the faster way (from about 25 tokens on for 28
  * layers and 3 queries), else 0.
  */

@@ -248,3 +248,25 @@ def test_rows_that_sum_to_more_than_one(V, monkeypatch):
     P[::3] *= 3.9 / P[::3].sum(1, keepdims=True)
     import paper_2509_18824_amd.step as step
     _both(step, trees, draft, P, Q, _u32(rng, total), _u32(rng, len(trees)), 4)
+
+
+def test_replays_from_a_hip_graph():
+    """Captured with its clearing kernel, replayed between other launches in the same workspace: the
+    counter, the leave words and the slots are as new every time."""
+    case, other = _Case(21, 30011, [_WIDE_TREE, W.chain_tree(3)] * 2, 4), _Case(22, 20002, [_WIDE_TREE] * 3, 4)
+    ws = torch.full((max(case.B * case.V, other.B * other.V),), -1, dtype=torch.int32, device="cuda")
+    out, out_other = case.outputs(), other.outputs()
+    case.call(out, ws)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        case.call(out, ws)
+    for i in range(4):
+        for o in out:
+            o.fill_(-7)
+        graph.replay()
+        torch.cuda.synchronize()
+        case.check(out)
+        other.call(out_other, ws, 0 if i % 2 else None)  # leaves its own counts behind
+        torch.cuda.synchronize()
+        other.check(out_other)

@@ -21,8 +21,8 @@
 // range of a node's rows once and keep it in registers (40 values of p and of q per lane), so that a
 // rejection touches no vocabulary in memory; what crosses wavefronts are the sums.  Every wavefront
 // keeps p_x and q_x of the node's children in its lanes, updates them like any other value, and takes
-// every decision itself: no barrier on the way.  16 sequences of 60 nodes over 152064 tokens: 79 us, the
-// kernel that clears the slots included.
+// every decision itself: no barrier on the way.  16 sequences of 60 nodes over 152064 tokens: 80 us, the
+// kernel that clears the slots included.  Vocabularies of up to 5120 tokens are one workgroup's per sequence (kAlone).
 // What bounds it is the chain of the sequence with the most rejections (ten at the root: 73 us): per
 // rejection two exchanges of 2 us each and 2.5 us of 64-bit integer work, per node visited 5 us for its
 // rows.  Measured against 81 us in a form whose workgroups took their places by index: 20 values per lane
@@ -73,6 +73,11 @@ constexpr int kPer = 40;                       // vocabulary entries a lane keep
 constexpr int kRange = kPer * 64;              // ... a wavefront (2560)
 constexpr int kMaxWorkers = 127;               // wavefronts per sequence; beyond 325120 tokens the rest stays in memory
 constexpr int kExchanges = 192;                // at most 64 nodes visited and two exchanges for each of 63 children
+// Vocabularies up to here: one workgroup per sequence, alone, p and q of a node in LDS.  Dealt to wavefronts
+// they pay 7 us a node for exchanges and registers that hardly hold anything (16 chains of 8 nodes, V = 100: 56 us
+// dealt, 16 alone, 1000: 58 and 23, 3000: 66 and 40, 5000: 67 and 59; trees of 60 nodes 5000: 59 and 73, 7000: 66 and
+// 103; one workgroup that read its rows from memory in every pass: 19, 29, 53, 72; 194, 271).
+constexpr int kAlone = 2 * kRange;
 constexpr u64 kPosted = 1ull << 63;
 constexpr uint32_t kMost = 0x7fffffff;          // sums of rows and residuals stay below: nearly 2 in fixed point
 constexpr uint32_t kGaveUp = 1u << 16;         // in a sequence's leave word: one for every wavefront that gave up ...
@@ -170,9 +175,12 @@ struct Sequence {
 
 // One sequence by one workgroup, alone and waiting for nobody: every pass over the vocabulary reads the
 // rows from memory, and a value's residual is worked out again from the node's rejections before it (their
-// sums stay in LDS; the workspace still belongs to the launch).  Sums and products have 64 bits.
+// sums stay in LDS; the workspace still belongs to the launch).  Small vocabularies (KEEP) stay in LDS: p (the
+// node's, or the residual) and q of a node in p_row and q_row.  Sums and products have 64 bits.
 struct Rejection {
   u64 sp, sq, div;  // p <- max(p S(q) - q S(p), 0) / div
+  Divisor d;        // where the sums fit it
+  bool fits;
 };
 struct AloneShared {
   int32_t par[64], did[64], path[64], removed[64];
@@ -186,7 +194,8 @@ __device__ __forceinline__ u64 wide_residual(uint32_t p, uint32_t q, u64 sp, u64
   return a > b ? a - b : 0ull;
 }
 
-__device__ __forceinline__ void accept_alone(const Sequence &s, AloneShared &sh) {
+template <bool KEEP>
+__device__ __forceinline__ void accept_alone(const Sequence &s, AloneShared &sh, uint32_t *p_row, uint32_t *q_row) {
   const int tid = threadIdx.x;
   auto sum = [&](u64 x) {
     x = wave_sum(x);
@@ -213,18 +222,26 @@ __device__ __forceinline__ void accept_alone(const Sequence &s, AloneShared &sh)
     const float *prow = s.p_target + (size_t)(s.n0 + cur) * s.V;
     const float *qrow = s.q_draft + (size_t)(s.n0 + cur) * s.V;
     int n_rejections = 0, n_removed = 0;
+    auto q_at = [&](int v) { return KEEP ? q_row[v] : fix_prob(qrow[v]); };
     auto p_at = [&](int v) {
+      if (KEEP) return p_row[v];
       uint32_t p = fix_prob(prow[v]);
       const uint32_t q = n_rejections ? fix_prob(qrow[v]) : 0u;
 #pragma unroll 1
       for (int i = 0; i < n_rejections; ++i)
-        p = (uint32_t)(wide_residual(p, q, sh.rejections[i].sp, sh.rejections[i].sq) / sh.rejections[i].div);
+        p = sh.rejections[i].fits ? divide(residual(p, q, (uint32_t)sh.rejections[i].sp, (uint32_t)sh.rejections[i].sq), sh.rejections[i].d)
+                                  : (uint32_t)(wide_residual(p, q, sh.rejections[i].sp, sh.rejections[i].sq) / sh.rejections[i].div);
       return p;
     };
     u64 sp = 0, sq = 0;
     for (int v = tid; v < s.V; v += kThreads) {
-      sp += fix_prob(prow[v]);
-      sq += fix_prob(qrow[v]);
+      const uint32_t p = fix_prob(prow[v]), q = fix_prob(qrow[v]);
+      if (KEEP) {
+        p_row[v] = p;
+        q_row[v] = q;
+      }
+      sp += p;
+      sq += q;
     }
     sp = sum(sp);
     sq = sum(sq);
@@ -236,7 +253,7 @@ __device__ __forceinline__ void accept_alone(const Sequence &s, AloneShared &sh)
       const bool x_ok = x >= 0 && x < s.V;
       if (tid == 0) {
         const u64 px = x_ok ? p_at(x) : 0u;
-        u64 qx = x_ok ? fix_prob(qrow[x]) : 0u;
+        u64 qx = x_ok ? q_at(x) : 0u;
         for (int i = 0; i < n_removed; ++i) qx = sh.removed[i] == x ? 0ull : qx;
         const u64 u = s.u_accept[s.n0 + c];
         sh.decision = mul_less(u * qx, sp, px * sq, 1ull << 32) ? 1 : 0;
@@ -251,15 +268,26 @@ __device__ __forceinline__ void accept_alone(const Sequence &s, AloneShared &sh)
         break;
       }
       u64 sr = 0;
-      for (int v = tid; v < s.V; v += kThreads) sr += wide_residual(p_at(v), fix_prob(qrow[v]), sp, sq);
+      for (int v = tid; v < s.V; v += kThreads) sr += wide_residual(p_at(v), q_at(v), sp, sq);
       sr = sum(sr);
       if (sr != 0) {
         const u64 div = sr >> kFixBits;
-        if (tid == 0) sh.rejections[n_rejections] = {sp, sq, div ? div : 1ull};
-        __syncthreads();
-        ++n_rejections;
+        const bool fits = sp <= kMost && sq <= kMost;
+        const Rejection r = {sp, sq, div ? div : 1ull, fits ? make_divisor(sr) : Divisor{}, fits};
         u64 snew = 0;
-        for (int v = tid; v < s.V; v += kThreads) snew += p_at(v);
+        if (KEEP) {
+          for (int v = tid; v < s.V; v += kThreads) {
+            const uint32_t p = p_row[v], q = q_row[v];
+            const uint32_t x = fits ? divide(residual(p, q, (uint32_t)sp, (uint32_t)sq), r.d) : (uint32_t)(wide_residual(p, q, sp, sq) / r.div);
+            p_row[v] = x;
+            snew += x;
+          }
+        } else {
+          if (tid == 0) sh.rejections[n_rejections] = r;
+          __syncthreads();
+          ++n_rejections;
+          for (int v = tid; v < s.V; v += kThreads) snew += p_at(v);
+        }
         sp = sum(snew);
       }
       if (tid == 0 && x_ok) sh.removed[n_removed] = x;
@@ -312,6 +340,28 @@ __device__ __forceinline__ void accept_alone(const Sequence &s, AloneShared &sh)
   }
 }
 
+__global__ __launch_bounds__(kThreads) void tree_accept_sample_alone_kernel(
+    int max_nodes, int V, const int32_t *__restrict__ node_offset, const int32_t *__restrict__ parent,
+    const int32_t *__restrict__ draft_ids, const float *__restrict__ p_target, const float *__restrict__ q_draft,
+    const uint32_t *__restrict__ u_accept, const uint32_t *__restrict__ u_bonus, int max_path,
+    int32_t *__restrict__ accept_len, int32_t *__restrict__ accept_path, int32_t *__restrict__ out_tokens,
+    int32_t *__restrict__ bonus_id) {
+  __shared__ AloneShared sh;
+  __shared__ uint32_t p_row[kAlone], q_row[kAlone];
+  const int b = blockIdx.x;
+  const int n0 = node_offset[b];
+  int n = node_offset[b + 1] - n0;
+  n = n < 0 ? 0 : (n > max_nodes ? max_nodes : n);
+  int32_t *path_out = accept_path + (size_t)b * max_path, *tok_out = out_tokens + (size_t)b * max_path;
+  if (n == 0) {  // nothing to verify: nothing is emitted
+    for (int j = threadIdx.x; j < max_path; j += kThreads) { path_out[j] = -1; tok_out[j] = -1; }
+    if (threadIdx.x == 0) { accept_len[b] = 0; bonus_id[b] = -1; }
+    return;
+  }
+  accept_alone<true>({n0, n, parent, draft_ids, p_target, q_draft, u_accept, u_bonus[b], V, max_path, accept_len + b, path_out,
+                      tok_out, bonus_id + b}, sh, p_row, q_row);
+}
+
 __global__ __launch_bounds__(kThreads) void tree_accept_sample_kernel(
     int polls, int max_nodes, int V, int workers, int groups, int chunk, const int32_t *__restrict__ node_offset, const int32_t *__restrict__ parent,
     const int32_t *__restrict__ draft_ids, const float *__restrict__ p_target, const float *__restrict__ q_draft,
@@ -360,34 +410,44 @@ __global__ __launch_bounds__(kThreads) void tree_accept_sample_kernel(
   uint32_t *work = (uint32_t *)(slots + kExchanges * kMaxWorkers) + (long long)w * (chunk - kRange) - v_begin - kRange;
   int k = 0;
 
-  // x of every wavefront of the sequence: lane i gets the shares of wavefronts i and i + 64.  False:
+  // x of every wavefront of the sequence: lane i gets the shares of wavefronts i and i + 64.  Not ok:
   // a share did not come in time, or somebody has given up (lane 63, which has no share to look for,
-  // looks at the leave word instead).
+  // looks at the leave word instead).  Few wavefronts have a loop of their own, and there is one way out:
+  // with one loop for both the kernel spills 24 registers (16 trees of 60 nodes over 152064 tokens: 90 us),
+  // with a return at each exit they take 85 us, this way 80.
   const bool wide = workers > 63;
   struct Shares {
     u64 s0, s1;
     bool ok;
   };
   auto exchange = [&](u64 x) -> Shares {
-    if (workers == 1) {
-      return {lane == 0 ? x : 0ull, 0ull, true};
-    }
     u64 *slot = slots + k * workers;
     ++k;
     if (lane == 0) __hip_atomic_store(slot + w, x | kPosted, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const u64 *at0 = lane == 63 && !wide ? control : slot + min(lane, workers - 1);
-    const u64 *at1 = lane == 63 ? control : slot + min(lane + 64, workers - 1);
     u64 y0 = 0, y1 = 0;
+    bool ok = false;
+    if (!wide) {
+      const u64 *at = lane == 63 ? control : slot + min(lane, workers - 1);
 #pragma unroll 1
-    for (int i = 0;; ++i) {
-      if (i == polls) return {0ull, 0ull, false};
-      y0 = __hip_atomic_load(at0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      y1 = wide ? __hip_atomic_load(at1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : y0;
-      const u64 posted = lane < 63 ? y0 & y1 & kPosted : (wide ? y0 & kPosted : kPosted);
-      if (__all(posted != 0)) break;
-      if (__any(lane == 63 && (uint32_t)(y1 >> 32) >= kGaveUp)) return {0ull, 0ull, false};
+      for (int i = 0; i < polls; ++i) {
+        y0 = __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        ok = __all(lane == 63 || (y0 & kPosted) != 0);
+        if (ok || __any(lane == 63 && (uint32_t)(y0 >> 32) >= kGaveUp)) break;
+      }
+      y0 = lane < workers ? y0 & ~kPosted : 0ull;
+    } else {
+      const u64 *at0 = slot + lane, *at1 = lane == 63 ? control : slot + min(lane + 64, workers - 1);
+#pragma unroll 1
+      for (int i = 0; i < polls; ++i) {
+        y0 = __hip_atomic_load(at0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        y1 = __hip_atomic_load(at1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        ok = __all((y0 & kPosted) != 0 && (lane == 63 || (y1 & kPosted) != 0));
+        if (ok || __any(lane == 63 && (uint32_t)(y1 >> 32) >= kGaveUp)) break;
+      }
+      y0 &= ~kPosted;
+      y1 = lane + 64 < workers ? y1 & ~kPosted : 0ull;
     }
-    return {lane < workers ? y0 & ~kPosted : 0ull, lane + 64 < workers ? y1 & ~kPosted : 0ull, true};
+    return {y0, y1, ok};
   };
 
   auto walk = [&]() -> bool {
@@ -543,7 +603,7 @@ __global__ __launch_bounds__(kThreads) void tree_accept_sample_kernel(
   };
 
   if (w < workers && !walk() && lane == 0) {
-    if (workers > 1) atomicAdd(leave, kGaveUp);  // partners need not wait any longer
+    atomicAdd(leave, kGaveUp);  // partners need not wait any longer
     leave_mark = 1 + kGaveUp;
   }
   __syncthreads();
@@ -554,8 +614,8 @@ __global__ __launch_bounds__(kThreads) void tree_accept_sample_kernel(
   }
   __syncthreads();
   if (alone)
-    accept_alone({n0, n, parent, draft_ids, p_target, q_draft, u_accept, u_bonus[b], V, max_path, accept_len + b, path_out, tok_out,
-                  bonus_id + b}, alone_shared);
+    accept_alone<false>({n0, n, parent, draft_ids, p_target, q_draft, u_accept, u_bonus[b], V, max_path, accept_len + b, path_out,
+                         tok_out, bonus_id + b}, alone_shared, nullptr, nullptr);
 }
 
 }  // namespace
@@ -565,12 +625,18 @@ hipError_t launch_tree_accept_sample(int32_t B, int32_t max_nodes, int32_t V, co
                                      const float *q_draft, const uint32_t *u_accept, const uint32_t *u_bonus,
                                      int32_t max_path, int32_t *accept_len, int32_t *accept_path,
                                      int32_t *out_tokens, int32_t *bonus_id, uint32_t *work, int32_t polls, hipStream_t s) {
+  if (V <= kAlone) {
+    tree_accept_sample_alone_kernel<<<(unsigned)B, kThreads, 0, s>>>(max_nodes, V, node_offset, parent, draft_ids, p_target, q_draft,
+                                                                    u_accept, u_bonus, max_path, accept_len, accept_path,
+                                                                    out_tokens, bonus_id);
+    return hipGetLastError();
+  }
   // as few wavefronts as hold the vocabulary in registers: fewer partners per exchange
   int workers = (int)(((int64_t)V + kRange - 1) / kRange);
   if (workers > kMaxWorkers) workers = kMaxWorkers;
   const int chunk = workers < kMaxWorkers ? kRange : (int)(((int64_t)V + workers - 1) / workers);
   const int groups = (workers + kThreads / 64 - 1) / (kThreads / 64);
-  if (workers > 1) accept_sample_clear_kernel<<<(unsigned)B, 256, 0, s>>>(V, workers, work);
+  accept_sample_clear_kernel<<<(unsigned)B, 256, 0, s>>>(V, workers, work);
   const int64_t grid = (int64_t)B * groups;
   tree_accept_sample_kernel<<<(unsigned)grid, kThreads, 0, s>>>(
       polls, max_nodes, V, workers, groups, chunk, node_offset, parent, draft_ids, p_target, q_draft, u_accept, u_bonus, max_path,

@@ -176,7 +176,7 @@ _WIDE_TREE = np.array([-1] + [0] * 6 + [1, 2, 3, 7], dtype=np.int32)
 
 
 @pytest.mark.parametrize("max_polls", [0, 1, 3, 40])
-@pytest.mark.parametrize("V", [2561, 10241, 152064, 128 * 2560 + 77])
+@pytest.mark.parametrize("V", [5121, 10241, 152064, 128 * 2560 + 77])
 def test_waits_that_run_out_give_the_same_results(V, max_polls):
     """Partners that give up waiting (at once, or after some looks) leave the sequence to one workgroup."""
     case = _Case(V + 1, V, [_WIDE_TREE, W.chain_tree(3), W.chain_tree(1)], 4)
@@ -189,7 +189,7 @@ def test_waits_that_run_out_give_the_same_results(V, max_polls):
 def test_workspace_of_an_earlier_launch_at_every_alignment():
     """One buffer, full of other things, for launches of a large vocabulary, smaller odd ones and other
     batches; it may start 4 bytes off an 8-byte boundary, and nothing beside it is touched."""
-    cases = [_Case(1, 327757, [_WIDE_TREE], 4), _Case(2, 2561, [_WIDE_TREE, W.chain_tree(2), _WIDE_TREE], 4),
+    cases = [_Case(1, 327757, [_WIDE_TREE], 4), _Case(2, 5121, [_WIDE_TREE, W.chain_tree(2), _WIDE_TREE], 4),
              _Case(3, 10243, [W.chain_tree(3)] * 2, 3)]
     guard = 64
     buf = torch.full((max(c.B * c.V for c in cases) + 2 * guard + 1,), -1, dtype=torch.int32, device="cuda")
@@ -220,6 +220,20 @@ def test_launches_on_two_streams():
     for c, o in zip(cases, outs):
         for out in o:
             c.check(out)
+
+
+@pytest.mark.parametrize("V", [1, 255, 257, 5119, 5120, 5121, 7680, 7681])
+def test_vocabularies_around_the_one_workgroup(step, V):
+    """Up to 5120 tokens a sequence is one workgroup's, 256 values a pass; from 5121 on three wavefronts share
+    it, from 7681 four."""
+    rng = np.random.default_rng(V + 5)
+    trees = [np.array([-1] + [0] * min(6, V) + [1] * min(3, V - 1), dtype=np.int32), W.chain_tree(3), np.array([], dtype=np.int32), W.chain_tree(1)]
+    total = sum(len(t) for t in trees)
+    logits = rng.standard_normal((total, V)) * 2.0
+    P = np.exp(logits); P /= P.sum(1, keepdims=True)
+    Q = np.exp(0.7 * logits + rng.standard_normal((total, V))); Q /= Q.sum(1, keepdims=True)
+    for trial in range(4):
+        _both(step, trees, _draw_drafts(rng, trees, Q, V), P, Q, _u32(rng, total), _u32(rng, 4), 4)
 
 
 @pytest.mark.parametrize("V", [60, 2000, 6001, 30011])

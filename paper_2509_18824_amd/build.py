@@ -25,9 +25,8 @@ FLAGS = [
 # with vector instructions and keeps its accumulators in place anyway: with the matrix
 # instructions selected in their vector-register form there are no accumulation registers and
 # no copies between the two register files.
-FILE_FLAGS = {
-    "attn_mfma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
-}
+# The tile kernels' accumulators are many small tiles, which the compiler otherwise copies about.
+FILE_FLAGS = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form=1"] for f in ("attn_mfma.hip", "lmhead_mfma.hip", "proj_mfma.hip")}
 
 
 def sources():

@@ -2,9 +2,9 @@
 //
 // Computes C^T[v, m] = sum_k W[v, k] * H[m, k] tile by tile and never stores it: the weight
 // rows are the MFMA "A" operand and the hidden rows the "B" operand, so that one lane's
-// accumulators of a 32x32 tile all belong to ONE hidden row m and 16 different vocabulary
-// entries v.  The row-wise argmax is then an in-register scan, one exchange between the two
-// lane halves, and one 64-bit atomic max per (row, workgroup).
+// accumulators of a 16x16 tile all belong to ONE hidden row m and four different vocabulary
+// entries v.  The row-wise argmax is then an in-register scan, two exchanges between the four
+// lane groups, and one 64-bit atomic max per (row, workgroup).
 //
 // Workgroup: 512 threads = 8 wavefronts (two per SIMD) in a 4 (v) x 2 (m) arrangement; workgroup
 // tile TV = 256 vocabulary rows x TM = 64 * MT hidden rows, K step 64.  Both operands are
@@ -12,14 +12,12 @@
 // layout wants (8 consecutive k per lane), so tiles go global -> LDS directly as 16-byte pieces
 // (global_load_lds), XOR-swizzled so that the 16-byte operand reads of 8 consecutive rows hit
 // all banks.  Weight tiles sit in a ring of three LDS stages and are fetched two K steps ahead,
-// hidden tiles in two stages one step ahead; one barrier per K step, placed before the step's
-// last MFMAs (see the pipeline comment in the kernel).
+// hidden tiles in two stages one step ahead; the two wavefronts of a SIMD alternate between
+// reading operands and matrix instructions (see mfma_gemm_tile.inc).
 //
-// What bounds the kernel is the path L2 -> LDS: a 256 x 192 tile needs one operand byte per 110
-// flop, and all CUs together draw about 10 KB per clock from the L2s at best, so operand
-// delivery and the matrix cores are busy for about the same number of cycles.  Everything here
-// serves to keep both going at once: loads in flight across barriers, no burst at a step start,
-// workgroups in lockstep so that shared tiles are fetched from HBM once.
+// What bounds the kernel at many rows is power (see there): 960 x 3584 x 152064 on normal values 876 ->
+// 826 us, 1024 rows 940 -> 839, 768 rows 752 -> 667 against 32x32x16 with one barrier per K step.
+// Workgroups go in lockstep so that shared tiles are fetched from HBM once.
 //
 // Grid: persistent workgroups, one per CU, in groups that walk the vocabulary tiles in lockstep
 // (one hidden tile per member) on one XCD.
@@ -30,7 +28,7 @@ namespace hb {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int BK = 64;           // k per step
@@ -38,28 +36,29 @@ constexpr int TV = 256;          // vocabulary rows per workgroup
 constexpr int CH = BK / 8;       // 16-byte pieces per row per step (8)
 constexpr int kXcds = 8;
 
+// Hidden tile stages in LDS.  With 64 rows three: 7 tokens x 3584 x 152064 169.9 us (176.6 with two); with 128
+// two: 128 tokens 204 us (209 with three), gated 3584 x 37888 64.7 (67.0).  More do not fit.
+constexpr int kHiddenStages(int mt) { return mt == 1 ? 3 : 2; }
+constexpr size_t tile_lds_bytes(int mt) { return (size_t)(3 * TV + kHiddenStages(mt) * 64 * mt) * CH * 16; }
+
 // Offset (in 16-byte pieces) of piece `c` of row `r` in a swizzled [rows][8] tile.  Rows are
-// 128 bytes; the XOR spreads the same logical piece of 8 consecutive rows, and of 8 consecutive
-// rows of equal parity, over distinct 16-byte bank groups, which keeps the operand reads
-// (lanes = consecutive rows, one piece each) conflict free for 128- and 256-byte wide LDS.
-__device__ inline int swz(int r, int c) { return r * CH + (c ^ ((r & 7) ^ ((r >> 3) & 1))); }
+// 128 bytes; the XOR spreads one logical piece of 8 consecutive rows over distinct 16-byte bank
+// groups.  The operand reads of 16x16x32 (lane l: row l % 16, piece l / 16) then run at 256 bytes
+// a clock; with row bit 3 in the XOR as well, as 32x32x16 wants it, at 128.
+__device__ inline int swz(int r, int c) { return r * CH + (c ^ (r & 7)); }
 
 // MT: 32-row hidden tiles per wavefront (the workgroup covers TM = 64 * MT hidden rows).
-// WV: wavefront rows along the vocabulary (2 or 4); the workgroup has 2 * WV wavefronts, each
-// with VT = 8 / WV vocabulary tiles of 32 rows.  WV = 4 (eight wavefronts, two per SIMD, at most
-// 256 registers each) lets one wavefront's matrix work cover the other's LDS, barrier and
-// memory waits.
 // WNT: weight loads carry the non-temporal hint.  With one hidden tile nobody shares a weight
 // tile, and streaming it through L2 without displacing the hidden rows is worth 5 %; with several
 // hidden tiles the hint evicts weight lines before all sharers have read them.
-template <int MT, int WV, bool WNT>
-__global__ __launch_bounds__(128 * WV) void lmhead_mfma_kernel(int M, int K, int V, int m_tiles, int v_tiles, int groups, int spare, int spare_tiles,
+template <int MT, bool WNT>
+__global__ __launch_bounds__(512) void lmhead_mfma_kernel(int M, int K, int V, int m_tiles, int v_tiles, int groups, int spare, int spare_tiles,
                                                           const u32x4 *__restrict__ hidden,
                                                           const u32x4 *__restrict__ weight,
                                                           unsigned long long *__restrict__ keys) {
   constexpr int TM = 64 * MT;
-  constexpr int NT = 128 * WV;             // threads
-  constexpr int VT = 8 / WV;               // 32-row vocabulary tiles per wavefront
+  constexpr int NT = 512;                  // threads
+  constexpr int WV = 4;                    // wavefront rows along the vocabulary
   extern __shared__ u32x4 lds[];           // [3][TV*CH] weight, then [2][TM*CH] hidden
   u32x4 *lw = lds;
   u32x4 *lh = lds + 3 * TV * CH;
@@ -70,7 +69,7 @@ __global__ __launch_bounds__(128 * WV) void lmhead_mfma_kernel(int M, int K, int
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
-  const int wv = wave >> 1;  // which 32*VT vocabulary rows of the tile
+  const int wv = wave >> 1;  // which 64 vocabulary rows of the tile
   const int wm = wave & 1;   // which 32*MT hidden rows of the tile
 
   // Persistent workgroups in lockstep groups.  Workgroup ids go round-robin to the XCDs
@@ -111,29 +110,31 @@ __global__ __launch_bounds__(128 * WV) void lmhead_mfma_kernel(int M, int K, int
 #include "mfma_gemm_tile.inc"
 #undef HB_GEMM_W_ROW
 
-  // Epilogue.  Accumulator r of lane l in tile (i, j) is C^T[v, m] with
-  //   v = v0 + wv*32*VT + i*32 + 8*(r/4) + 4*(l/32) + r%4,   m = m0 + wm*32*MT + j*32 + l%32.
-  // Scanning (i, r) in order visits v in increasing order, so a strict '>' keeps the lowest v
+  // Epilogue.  Accumulator e of lane l in tile (i, j) is C^T[v, m] with
+  //   v = v0 + wv*64 + i*16 + 4*(l/16) + e,   m = m0 + wm*32*MT + j*16 + l%16.
+  // Scanning (i, e) in order visits v in increasing order, so a strict '>' keeps the lowest v
   // among equal values; NaN compares false and never wins.
 #pragma unroll
-  for (int j = 0; j < MT; ++j) {
+  for (int j = 0; j < JT; ++j) {
     float best = -__builtin_huge_valf();
     int best_v = -1;
 #pragma unroll
-    for (int i = 0; i < VT; ++i)
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        int v = v0 + wv * 32 * VT + i * 32 + 8 * (r >> 2) + 4 * frag_half + (r & 3);
-        float x = acc[i][j][r];
+      for (int e = 0; e < 4; ++e) {
+        int v = v0 + wv * 64 + i * 16 + 4 * frag_k + e;
+        float x = acc[i][j][e];
         bool take = (v < V) && (x > best);
         best = take ? x : best;
         best_v = take ? v : best_v;
       }
     // a lane that saw nothing above -inf offers no candidate (key 0 loses to every real key)
     unsigned long long key = best_v >= 0 ? argmax_key(best, (uint32_t)best_v) : 0ull;
-    unsigned long long other = __shfl_xor(key, 32, 64);
+    unsigned long long other = __shfl_xor(key, 16, 64);
     key = other > key ? other : key;
-    if (lane < 32) row_key[wv][wm * 32 * MT + j * 32 + lane] = key;
+    other = __shfl_xor(key, 32, 64);
+    key = other > key ? other : key;
+    if (lane < 16) row_key[wv][wm * 32 * MT + j * 16 + lane] = key;
   }
   __syncthreads();
   for (int r = tid; r < TM; r += NT) {
@@ -149,7 +150,7 @@ __global__ __launch_bounds__(128 * WV) void lmhead_mfma_kernel(int M, int K, int
   }  // vocabulary tiles of this workgroup
 }
 
-template <int MT, int WV, bool WNT>
+template <int MT, bool WNT>
 hipError_t launch(int M, int K, int V, const void *hidden, const void *weight, unsigned long long *keys,
                   hipStream_t s) {
   constexpr int TM = 64 * MT;
@@ -184,12 +185,12 @@ hipError_t launch(int M, int K, int V, const void *hidden, const void *weight, u
     }
     if (spare) groups = max_groups;
   }
-  size_t lds_bytes = (size_t)(3 * TV + 2 * TM) * CH * sizeof(u32x4);
-  auto kern = lmhead_mfma_kernel<MT, WV, WNT>;
+  size_t lds_bytes = tile_lds_bytes(MT);
+  auto kern = lmhead_mfma_kernel<MT, WNT>;
   hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
   if (e != hipSuccess) return e;
   dim3 grid((unsigned)((groups * m_tiles + spare) * kXcds));
-  kern<<<grid, 128 * WV, lds_bytes, s>>>(M, K, V, m_tiles, v_tiles, groups, spare, spare_tiles, (const u32x4 *)hidden, (const u32x4 *)weight, keys);
+  kern<<<grid, 512, lds_bytes, s>>>(M, K, V, m_tiles, v_tiles, groups, spare, spare_tiles, (const u32x4 *)hidden, (const u32x4 *)weight, keys);
   return hipGetLastError();
 }
 
@@ -211,14 +212,14 @@ hipError_t launch_lmhead_mfma(int32_t M, int32_t K, int32_t V, const void *hidde
     if (best_rows < 0 || rows < best_rows) { best_rows = rows; best_mt = mt; }
   }
   switch (best_mt) {
-    case 1: return M <= 64 * 1 ? launch<1, 4, true>(M, K, V, hidden, weight, keys, s)
-                            : launch<1, 4, false>(M, K, V, hidden, weight, keys, s);
-    case 2: return M <= 64 * 2 ? launch<2, 4, true>(M, K, V, hidden, weight, keys, s)
-                            : launch<2, 4, false>(M, K, V, hidden, weight, keys, s);
-    case 3: return M <= 64 * 3 ? launch<3, 4, true>(M, K, V, hidden, weight, keys, s)
-                            : launch<3, 4, false>(M, K, V, hidden, weight, keys, s);
-    default: return M <= 64 * 4 ? launch<4, 4, true>(M, K, V, hidden, weight, keys, s)
-                            : launch<4, 4, false>(M, K, V, hidden, weight, keys, s);
+    case 1: return M <= 64 * 1 ? launch<1, true>(M, K, V, hidden, weight, keys, s)
+                            : launch<1, false>(M, K, V, hidden, weight, keys, s);
+    case 2: return M <= 64 * 2 ? launch<2, true>(M, K, V, hidden, weight, keys, s)
+                            : launch<2, false>(M, K, V, hidden, weight, keys, s);
+    case 3: return M <= 64 * 3 ? launch<3, true>(M, K, V, hidden, weight, keys, s)
+                            : launch<3, false>(M, K, V, hidden, weight, keys, s);
+    default: return M <= 64 * 4 ? launch<4, true>(M, K, V, hidden, weight, keys, s)
+                            : launch<4, false>(M, K, V, hidden, weight, keys, s);
   }
 }
 

@@ -8,10 +8,10 @@
 //   * the two small kernels that give every tree node its position (prefix length + depth) and
 //     the cosine / sine table of those positions.
 // The matrix work is the tile loop of the LM head (mfma_gemm_tile.inc: C^T = W H^T, weight rows
-// as the MFMA "A" operand, so a lane's accumulators of a 32x32 tile are 16 output features of ONE
+// as the MFMA "A" operand, so a lane's accumulators of a 16x16 tile are four output features of ONE
 // token).  For the rotary embedding the 256 weight rows of a tile are not taken in memory order:
 // a tile holds two heads, and the rows are arranged so that the two accumulators a lane holds at
-// the same position of its two 32-row sub-tiles are the pair (d, d + 64) of one head, which is
+// the same position of its two 32-row halves are the pair (d, d + 64) of one head, which is
 // what the rotate-half convention rotates together: the rotation costs no exchange at all.  The
 // gated projection uses the same device: a tile holds 128 features, the gate rows in the first
 // 32-row sub-tile of every wavefront row and the matching up rows in the second, so silu(gate) * up
@@ -24,7 +24,6 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
@@ -32,12 +31,28 @@ constexpr int BK = 64;
 constexpr int TV = 256;
 constexpr int CH = BK / 8;
 constexpr int kXcds = 8;
+
+// Hidden tile stages in LDS.  With 64 rows three: 7 tokens x 3584 x 152064 169.9 us (176.6 with two); with 128
+// two: 128 tokens 204 us (209 with three), gated 3584 x 37888 64.7 (67.0).  More do not fit.
+constexpr int kHiddenStages(int mt) { return mt == 1 ? 3 : 2; }
+constexpr size_t tile_lds_bytes(int mt) { return (size_t)(3 * TV + kHiddenStages(mt) * 64 * mt) * CH * 16; }
 constexpr int kHeadDim = 128;
 constexpr int64_t kUncached = (int64_t)1 << 27;  // weights: 256 MB, the size of the last-level cache
 
-__device__ inline int swz(int r, int c) { return r * CH + (c ^ ((r & 7) ^ ((r >> 3) & 1))); }
+__device__ inline int swz(int r, int c) { return r * CH + (c ^ (r & 7)); }
 
 __device__ inline uint32_t pack_bf16(float a, float b) { return (uint32_t)f32_to_bf16(a) | ((uint32_t)f32_to_bf16(b) << 16); }
+
+// Workgroup ids go round-robin to the XCDs.  Of the units 0 .. units - 1, numbered so that neighbours share a
+// weight tile, every XCD gets one run of equal length: neighbours find the shared tile in its L2, and no XCD
+// gets more units than its 32 CUs hold while others idle (18 weight tiles x 11 hidden tiles, whole weight tiles
+// dealt: 33 units on two of them, 2048 tokens x 3584 x 4608 113 us; so 67).
+__device__ inline int deal_unit(int units) {
+  const int per = (units + kXcds - 1) / kXcds, slot = (int)blockIdx.x / kXcds;
+  const int unit = (int)blockIdx.x % kXcds * per + slot;
+  return slot < per && unit < units ? unit : -1;
+}
+inline unsigned deal_grid(long units) { return (unsigned)((units + kXcds - 1) / kXcds * kXcds); }
 
 struct QkvArgs {
   const bf16_t *bias;      // [(Hq + 2 Hkv) * 128] or null
@@ -51,8 +66,7 @@ struct StoreArgs {
 };
 
 // ROPE: query/key/value projection with rotary embedding (V = (Hq + 2 Hkv) * 128 weight rows),
-// else plain projection.  One workgroup per (weight tile, hidden tile); the workgroups that share
-// a weight tile get neighbouring slots of one XCD (ids 8 apart) and find it in that XCD's L2.
+// else plain projection.  One workgroup per (weight tile, hidden tile), dealt by deal_unit.
 // WNT: the weight loads carry the non-temporal hint.  It pays where one hidden tile means that nobody shares
 // them and they exceed the last-level cache: gated 3584 x 37888 (272 MB) 61.2 -> 57.9 us at 33 tokens, 66.9 ->
 // 63.0 at 128, eight whole layers of 16 chains 1790 -> 1755.  4096 x 28672 (235 MB): eight layers 2018 and 2016,
@@ -61,9 +75,7 @@ template <int MT, bool ROPE, bool GLU, bool WNT>
 __global__ __launch_bounds__(512) void proj_mfma_kernel(int M, int K, int V, int m_tiles, int v_tiles,
                                                         const u32x4 *__restrict__ hidden,
                                                         const u32x4 *__restrict__ weight, QkvArgs qa, StoreArgs sa) {
-  constexpr int WV = 4;
   constexpr int TM = 64 * MT;
-  constexpr int VT = 8 / WV;
   extern __shared__ u32x4 lds[];
   u32x4 *lw = lds;
   u32x4 *lh = lds + 3 * TV * CH;
@@ -72,11 +84,9 @@ __global__ __launch_bounds__(512) void proj_mfma_kernel(int M, int K, int V, int
   const int wave = tid >> 6;
   const int wv = wave >> 1;
   const int wm = wave & 1;
-  const int id = blockIdx.x;
-  const int xcd = id % kXcds, slot = id / kXcds;
-  const int v_tile = (slot / m_tiles) * kXcds + xcd;
-  const int m_tile = slot % m_tiles;
-  if (v_tile >= v_tiles) return;
+  const int unit = deal_unit(v_tiles * m_tiles);
+  if (unit < 0) return;
+  const int v_tile = unit / m_tiles, m_tile = unit % m_tiles;
   const int m0 = m_tile * TM;
   const int v0 = v_tile * TV;
   const int kp = K / 8;
@@ -91,11 +101,11 @@ __global__ __launch_bounds__(512) void proj_mfma_kernel(int M, int K, int V, int
 #include "mfma_gemm_tile.inc"
 #undef HB_GEMM_W_ROW
 
-  // Epilogue.  Accumulator r = 4 c + e of lane l in tile (i, j): tile row wv*64 + i*32 + 8 c +
-  // 4 (l / 32) + e, token m0 + wm*32*MT + j*32 + l % 32.
+  // Epilogue.  Accumulator e of lane l in tile (i, j): tile row wv*64 + i*16 + 4 (l / 16) + e,
+  // token m0 + wm*32*MT + j*16 + l % 16.
 #pragma unroll
-  for (int j = 0; j < MT; ++j) {
-    const int m = m0 + wm * 32 * MT + j * 32 + frag_row;
+  for (int j = 0; j < JT; ++j) {
+    const int m = m0 + wm * 32 * MT + j * 16 + frag_row;
     if (m >= M) continue;
     if (ROPE) {
       const int head = (v0 >> 7) + (wv >> 1);
@@ -105,14 +115,9 @@ __global__ __launch_bounds__(512) void proj_mfma_kernel(int M, int K, int V, int
                     : head < qa.Hq + qa.Hkv ? qa.k + ((size_t)m * qa.Hkv + (head - qa.Hq)) * kHeadDim
                                             : qa.v + ((size_t)m * qa.Hkv + (head - qa.Hq - qa.Hkv)) * kHeadDim;
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const int d = (wv & 1) * 32 + 8 * c + 4 * frag_half;  // d .. d + 3 and d + 64 .. d + 67
-        float x1[4], x2[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          x1[e] = acc[0][j][4 * c + e];
-          x2[e] = acc[1][j][4 * c + e];
-        }
+      for (int i = 0; i < 2; ++i) {
+        const int d = (wv & 1) * 32 + i * 16 + 4 * frag_k;  // d .. d + 3 and d + 64 .. d + 67
+        f32x4 x1 = acc[i][j], x2 = acc[i + 2][j];
         if (qa.bias) {
           const u32x2 b1 = *(const u32x2 *)(qa.bias + head * kHeadDim + d);
           const u32x2 b2 = *(const u32x2 *)(qa.bias + head * kHeadDim + d + 64);
@@ -127,10 +132,10 @@ __global__ __launch_bounds__(512) void proj_mfma_kernel(int M, int K, int V, int
           const f32x4 sn = *(const f32x4 *)(qa.sin + (size_t)m * 64 + d);
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            const float a = x1[e] * cs[e] - x2[e] * sn[e];
-            const float b = x2[e] * cs[e] + x1[e] * sn[e];
-            x1[e] = a;
-            x2[e] = b;
+            const float a1 = x1[e] * cs[e] - x2[e] * sn[e];
+            const float a2 = x2[e] * cs[e] + x1[e] * sn[e];
+            x1[e] = a1;
+            x2[e] = a2;
           }
         }
         *(u32x2 *)(dst + d) = (u32x2){pack_bf16(x1[0], x1[1]), pack_bf16(x1[2], x1[3])};
@@ -139,34 +144,30 @@ __global__ __launch_bounds__(512) void proj_mfma_kernel(int M, int K, int V, int
     } else if (GLU) {
       const int F = V >> 1;
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const int f = (v0 >> 1) + wv * 32 + 8 * c + 4 * frag_half;  // f .. f + 3, F % 4 == 0
+      for (int i = 0; i < 2; ++i) {
+        const int f = (v0 >> 1) + wv * 32 + i * 16 + 4 * frag_k;  // f .. f + 3, F % 4 == 0
         if (f >= F) continue;
         float y[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float g = acc[0][j][4 * c + e];
-          y[e] = g / (1.f + __expf(-g)) * acc[1][j][4 * c + e];
+          const float g = acc[i][j][e];
+          y[e] = g / (1.f + __expf(-g)) * acc[i + 2][j][e];
         }
         *(u32x2 *)(sa.out + (size_t)m * F + f) = (u32x2){pack_bf16(y[0], y[1]), pack_bf16(y[2], y[3])};
       }
     } else {
 #pragma unroll
-      for (int i = 0; i < VT; ++i)
+      for (int i = 0; i < 4; ++i) {
+        const int n = v0 + wv * 64 + i * 16 + 4 * frag_k;  // n .. n + 3, V % 4 == 0
+        if (n >= V) continue;
+        f32x4 x = acc[i][j];
+        if (sa.residual) {
+          const u32x2 r = *(const u32x2 *)(sa.residual + (size_t)m * V + n);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const int n = v0 + wv * 32 * VT + i * 32 + 8 * c + 4 * frag_half;  // n .. n + 3, V % 4 == 0
-          if (n >= V) continue;
-          float x[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) x[e] = acc[i][j][4 * c + e];
-          if (sa.residual) {
-            const u32x2 r = *(const u32x2 *)(sa.residual + (size_t)m * V + n);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) x[e] += __uint_as_float((e & 1) ? (r[e >> 1] & 0xffff0000u) : (r[e >> 1] << 16));
-          }
-          *(u32x2 *)(sa.out + (size_t)m * V + n) = (u32x2){pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3])};
+          for (int e = 0; e < 4; ++e) x[e] += __uint_as_float((e & 1) ? (r[e >> 1] & 0xffff0000u) : (r[e >> 1] << 16));
         }
+        *(u32x2 *)(sa.out + (size_t)m * V + n) = (u32x2){pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3])};
+      }
     }
   }
 }
@@ -177,14 +178,13 @@ hipError_t launch(int M, int K, int V, const void *hidden, const void *weight, c
   constexpr int TM = 64 * MT;
   const int m_tiles = (M + TM - 1) / TM;
   const int v_tiles = (V + TV - 1) / TV;
-  const size_t lds_bytes = (size_t)(3 * TV + 2 * TM) * CH * sizeof(u32x4);
+  const size_t lds_bytes = tile_lds_bytes(MT);
   auto kern = proj_mfma_kernel<MT, ROPE, GLU, false>;
   if constexpr (GLU)
     if (m_tiles == 1 && (int64_t)K * V >= kUncached) kern = proj_mfma_kernel<MT, ROPE, GLU, true>;
   hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
   if (e != hipSuccess) return e;
-  dim3 grid((unsigned)((v_tiles + kXcds - 1) / kXcds * kXcds * m_tiles));
-  kern<<<grid, 512, lds_bytes, s>>>(M, K, V, m_tiles, v_tiles, (const u32x4 *)hidden, (const u32x4 *)weight, qa, sa);
+  kern<<<deal_grid((long)v_tiles * m_tiles), 512, lds_bytes, s>>>(M, K, V, m_tiles, v_tiles, (const u32x4 *)hidden, (const u32x4 *)weight, qa, sa);
   return hipGetLastError();
 }
 
@@ -194,20 +194,17 @@ hipError_t launch(int M, int K, int V, const void *hidden, const void *weight, c
 // of every tile is cut into `ks` parts, one workgroup per (weight tile, K part, hidden tile); the
 // workgroups that differ in the hidden tile only, which read the same weights, get neighbouring
 // slots of one XCD.  A workgroup runs the same tile loop over its part and stores its fp32
-// accumulators to the caller's workspace as part[kpart][weight row][token] (tokens contiguous: a
-// lane's 32 neighbours hold consecutive tokens of one weight row).  proj_reduce_kernel then sums
-// the parts in order and applies the epilogue (bias, rotary embedding, residual), one thread per
-// token and group of four features (for the rotary variant: four (d, d + 64) pairs).
+// accumulators to the caller's workspace as part[kpart][token][weight row] (a lane holds four
+// consecutive weight rows of one token).  proj_reduce_kernel then sums the parts in order and
+// applies the epilogue (bias, rotary embedding, residual).
 template <int MT>
 __global__ __launch_bounds__(512) void proj_splitk_kernel(int M, int Kfull, int V, int ks, int v_pad, int m_tiles,
                                                           int m_pad, int units,
                                                           const u32x4 *__restrict__ hidden_full,
                                                           const u32x4 *__restrict__ weight_full,
                                                           float *__restrict__ part) {
-  constexpr int WV = 4;
   constexpr bool WNT = false;  // measured: the non-temporal hint costs 10-25 % here, also with a single hidden tile
   constexpr int TM = 64 * MT;
-  constexpr int VT = 8 / WV;
   extern __shared__ u32x4 lds[];
   u32x4 *lw = lds;
   u32x4 *lh = lds + 3 * TV * CH;
@@ -216,11 +213,11 @@ __global__ __launch_bounds__(512) void proj_splitk_kernel(int M, int Kfull, int 
   const int wave = tid >> 6;
   const int wv = wave >> 1;
   const int wm = wave & 1;
-  const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
-  const int unit = (slot / m_tiles) * kXcds + xcd;  // (weight tile, K part)
-  if (unit >= units) return;
+  const int index = deal_unit(units * m_tiles);
+  if (index < 0) return;
+  const int unit = index / m_tiles;  // (weight tile, K part)
   const int v_tile = unit / ks, kpart = unit % ks;
-  const int m0 = (slot % m_tiles) * TM;
+  const int m0 = (index % m_tiles) * TM;
   const int v0 = v_tile * TV;
   const int K = Kfull / ks;          // this workgroup's share
   const int kp = Kfull / 8;          // row stride in 16-byte pieces
@@ -229,37 +226,43 @@ __global__ __launch_bounds__(512) void proj_splitk_kernel(int M, int Kfull, int 
 #define HB_GEMM_W_ROW(t_) (v0 + (t_))
 #include "mfma_gemm_tile.inc"
 #undef HB_GEMM_W_ROW
-  float *dst = part + ((size_t)kpart * v_pad + v0) * m_pad + m0;
+  float *dst = part + ((size_t)kpart * m_pad + m0) * v_pad + v0;
 #pragma unroll
-  for (int i = 0; i < VT; ++i)
+  for (int j = 0; j < JT; ++j)
 #pragma unroll
-    for (int j = 0; j < MT; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = wv * 32 * VT + i * 32 + 8 * (r >> 2) + 4 * frag_half + (r & 3);
-        dst[(size_t)row * m_pad + wm * 32 * MT + j * 32 + frag_row] = acc[i][j][r];
-      }
+    for (int i = 0; i < 4; ++i) {
+      const int row = wv * 64 + i * 16 + 4 * frag_k, token = wm * 32 * MT + j * 16 + frag_row;
+      *(f32x4 *)(dst + (size_t)token * v_pad + row) = acc[i][j];
+    }
 }
 
+// The sum over the K parts, in order, of four consecutive weight rows of one token; eight loads in flight.
+__device__ inline f32x4 sum_parts(const float *__restrict__ src, int ks, size_t stride) {
+  f32x4 x = {0.f, 0.f, 0.f, 0.f};
+  for (int k0 = 0; k0 < ks; k0 += 8) {
+    f32x4 v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = *(const f32x4 *)(src + (size_t)(k0 + i < ks ? k0 + i : ks - 1) * stride);
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (k0 + i < ks) x += v[i];
+  }
+  return x;
+}
+
+// One thread per token and group of four features (rotary variant: four (d, d + 64) pairs), groups
+// in neighbouring lanes: partials and results move in whole lines.
 template <bool ROPE, bool GLU>
-__global__ __launch_bounds__(256) void proj_reduce_kernel(int M, int V, int ks, int v_pad, int tm,
+__global__ __launch_bounds__(256) void proj_reduce_kernel(int M, int V, int ks, int v_pad, int m_pad, int groups,
                                                           const float *__restrict__ part, QkvArgs qa, StoreArgs sa) {
-  const long idx = (long)blockIdx.x * 256 + threadIdx.x;
-  const int m = (int)(idx % tm);
-  const int g = (int)(idx / tm);
-  if (m >= M) return;
+  const int g = (int)blockIdx.x * 256 + (int)threadIdx.x, m = (int)blockIdx.y;
+  if (g >= groups) return;
+  const size_t stride = (size_t)m_pad * v_pad;
+  const float *row = part + (size_t)m * v_pad;
   if (ROPE) {
     const int head = g >> 4, d = (g & 15) * 4;
-    if (head >= qa.Hq + 2 * qa.Hkv) return;
-    float x1[4] = {0.f, 0.f, 0.f, 0.f}, x2[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int kpart = 0; kpart < ks; ++kpart) {
-      const float *src = part + ((size_t)kpart * v_pad + head * kHeadDim + d) * tm + m;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        x1[e] += src[(size_t)e * tm];
-        x2[e] += src[(size_t)(64 + e) * tm];
-      }
-    }
+    f32x4 x1 = sum_parts(row + head * kHeadDim + d, ks, stride);
+    f32x4 x2 = sum_parts(row + head * kHeadDim + 64 + d, ks, stride);
     if (qa.bias) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -286,29 +289,14 @@ __global__ __launch_bounds__(256) void proj_reduce_kernel(int M, int V, int ks, 
     *(u32x2 *)(dst + d + 64) = (u32x2){pack_bf16(x2[0], x2[1]), pack_bf16(x2[2], x2[3])};
   } else if (GLU) {
     const int F = V >> 1, f = g * 4;
-    if (f >= F) return;
-    float xg[4] = {0.f, 0.f, 0.f, 0.f}, xu[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int kpart = 0; kpart < ks; ++kpart) {
-      const float *src = part + ((size_t)kpart * v_pad + f) * tm + m;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        xg[e] += src[(size_t)e * tm];
-        xu[e] += src[(size_t)(F + e) * tm];
-      }
-    }
+    const f32x4 xg = sum_parts(row + f, ks, stride), xu = sum_parts(row + F + f, ks, stride);
     float y[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) y[e] = xg[e] / (1.f + __expf(-xg[e])) * xu[e];
     *(u32x2 *)(sa.out + (size_t)m * F + f) = (u32x2){pack_bf16(y[0], y[1]), pack_bf16(y[2], y[3])};
   } else {
     const int n = g * 4;
-    if (n >= V) return;
-    float x[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int kpart = 0; kpart < ks; ++kpart) {
-      const float *src = part + ((size_t)kpart * v_pad + n) * tm + m;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) x[e] += src[(size_t)e * tm];
-    }
+    f32x4 x = sum_parts(row + n, ks, stride);
     if (sa.residual) {
       const u32x2 r = *(const u32x2 *)(sa.residual + (size_t)m * V + n);
 #pragma unroll
@@ -318,18 +306,16 @@ __global__ __launch_bounds__(256) void proj_reduce_kernel(int M, int V, int ks, 
   }
 }
 
-// Hidden tile height (64 mt rows) of the unsplit kernel by a small cost model: a workgroup's time
-// per K step is about 1 + 0.55 mt units (staging of the 256-row weight tile + mt x the matrix work
-// of 64 rows, from the LM head's measured 2100 clocks at mt = 3); one workgroup per CU at a time,
-// so the launch takes ceil(units / 256) rounds of that.  960 x 4608: mt = 2 (144 units, one round)
-// beats mt = 1 (270 units: a second round for 14 of them) and mt = 3 (90 units).
-int plain_tile_height(int M, int v_tiles) {
+// Hidden tile height (64 mt rows) of the unsplit kernel: rounds of 256 workgroups, one per CU, times
+// a workgroup's clocks, read inside the kernel: 3800 until the first tile is there, a K step, the results.
+int plain_tile_height(int M, int K, int v_tiles) {
+  static const double kStep[5] = {0, 1500, 1750, 2130, 2560}, kStore[5] = {0, 3800, 8200, 12700, 17000};
   int mt = 1;
   double best = 1e30;
   for (int t = 1; t <= 4; ++t) {
     const long units = (long)v_tiles * ((M + 64 * t - 1) / (64 * t));
-    const double cost = (double)((units + 255) / 256) * (1.0 + 0.55 * t);
-    if (cost < best - 1e-9) { best = cost; mt = t; }
+    const double cost = (double)((units + 255) / 256) * (3800 + (K / BK) * kStep[t] + kStore[t]);
+    if (cost < best) { best = cost; mt = t; }
   }
   return mt;
 }
@@ -342,7 +328,7 @@ int plain_tile_height(int M, int v_tiles) {
 //           3 + steps * (0.72 | 0.95 | 1.15 | 1.4 for the unsplit kernel's mt) per round (more tokens)
 // Up to 512 tokens the tile is 64 or 128 rows high; from there to kSplitMaxM tokens 128 to 256 rows,
 // and the split must win by 10 % (it does for long K: the feed-forward block's down projection,
-// 960 x 18944 -> 3584, takes 145 us in 4 parts of 256-row tiles against 209 us unsplit; with K =
+// 960 x 18944 -> 3584, takes 120 to 129 us in 4 parts of 256-row tiles; with K =
 // 3584 the unsplit kernel stays).  ks = 1 means: do not split.
 constexpr int kSplitMaxM = 1024;
 constexpr int kMinSteps = 4;
@@ -360,7 +346,7 @@ SplitPlan split_plan(int M, int K, int V) {
     const long plain_units = (long)v_tiles * ((M + 63) / 64);
     best_cost = 3.0 + steps * 0.75 * (double)((plain_units + 255) / 256);
   } else {
-    const int pm = plain_tile_height(M, v_tiles);
+    const int pm = plain_tile_height(M, K, v_tiles);
     const long plain_units = (long)v_tiles * ((M + 64 * pm - 1) / (64 * pm));
     best_cost = 0.9 * (3.0 + steps * kStepPlain[pm] * (double)((plain_units + 255) / 256));
   }
@@ -395,8 +381,8 @@ hipError_t launch_splitk(int M, int K, int V, SplitPlan plan, const void *hidden
   const int m_tiles = (M + tm - 1) / tm, m_pad = m_tiles * tm;
   const int v_tiles = (V + TV - 1) / TV, v_pad = v_tiles * TV;
   const int units = v_tiles * ks;
-  const unsigned grid = (unsigned)((units + kXcds - 1) / kXcds * kXcds * m_tiles);
-  const size_t lds_bytes = (size_t)(3 * TV + 2 * tm) * CH * sizeof(u32x4);
+  const unsigned grid = deal_grid((long)units * m_tiles);
+  const size_t lds_bytes = tile_lds_bytes(plan.mt);
   hipError_t e;
   switch (plan.mt) {
 #define HB_SPLITK_CASE(MT_)                                                                                       \
@@ -416,16 +402,15 @@ hipError_t launch_splitk(int M, int K, int V, SplitPlan plan, const void *hidden
   }
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const long groups = ROPE ? (long)(V / kHeadDim) * 16 : GLU ? (V / 2 + 3) / 4 : (V + 3) / 4;
-  const long threads = groups * m_pad;
-  proj_reduce_kernel<ROPE, GLU><<<(unsigned)((threads + 255) / 256), 256, 0, s>>>(M, V, ks, v_pad, m_pad, part, qa, sa);
+  const int groups = ROPE ? V / kHeadDim * 16 : GLU ? V / 8 : V / 4;
+  proj_reduce_kernel<ROPE, GLU><<<dim3((unsigned)((groups + 255) / 256), (unsigned)M), 256, 0, s>>>(M, V, ks, v_pad, m_pad, groups, part, qa, sa);
   return hipGetLastError();
 }
 
 template <bool ROPE, bool GLU>
 hipError_t dispatch(int M, int K, int V, const void *hidden, const void *weight, const QkvArgs &qa, const StoreArgs &sa,
                     hipStream_t s) {
-  const int mt = plain_tile_height(M, (V + TV - 1) / TV);
+  const int mt = plain_tile_height(M, K, (V + TV - 1) / TV);
   switch (mt) {
     case 4: return launch<4, ROPE, GLU>(M, K, V, hidden, weight, qa, sa, s);
     case 3: return launch<3, ROPE, GLU>(M, K, V, hidden, weight, qa, sa, s);

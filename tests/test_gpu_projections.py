@@ -103,6 +103,13 @@ def test_output_projection(hb, T, K, N, res):
     _out_case(hb, T, K, N, res, False)
 
 
+@pytest.mark.parametrize("T,K,N,res", [(1025, 64, 260, True), (1100, 128, 2308, False), (1537, 192, 2560, True),
+                                       (193, 256, 4612, True), (2049, 64, 4608, False), (129, 448, 1284, True)])
+def test_output_projection_with_units_dealt_across_weight_tiles(hb, T, K, N, res):
+    """Weight tiles that are no multiple of the XCDs, one to seven K steps, ragged last tiles of both kinds."""
+    _out_case(hb, T, K, N, res, False)
+
+
 @pytest.mark.parametrize("T,K,N,res", [(128, 3584, 3584, True), (96, 10752, 3584, False), (37, 256, 20, True),
                                        (5, 512, 1000, False), (1, 1024, 4, True), (64, 2048, 260, True),
                                        (129, 512, 512, True), (288, 3584, 3584, True), (300, 1024, 520, False),

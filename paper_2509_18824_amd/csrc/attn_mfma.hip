@@ -30,8 +30,9 @@
 //
 // Keys: chunk 0 starts with one 64-key tile holding the tree nodes (masked per row by the
 // node's ancestor bitmask), then every chunk streams its share of the prefix through the page
-// table in 64-key tiles.  Prefix tiles go global -> LDS directly (no staging registers, no
-// transposition in the vector unit) into a ring of LDS stages, several tiles ahead of the one
+// table in 64-key tiles.  Tiles go global -> LDS directly (no staging registers, no
+// transposition in the vector unit; a tree tile through registers cost spills, chains of 16 nodes on
+// 16 sequences 44 us, 39 so) into a ring of LDS stages, several tiles ahead of the one
 // being computed; V stays in memory order in LDS and is transposed by the LDS read itself.
 #include "hb_internal.h"
 
@@ -66,72 +67,6 @@ __device__ __forceinline__ uint32_t finite_or_zero_bf16x2(uint32_t w) {
   return lo | hi;
 }
 
-// Where one thread's pieces of a 64-key tile come from.  A tile holds either tree nodes (keys =
-// node ids < n_nodes, read from k_tree/v_tree) or prefix positions tile_start + key < end (read
-// through the page table).  Slots that are not valid keys are masked in the scores; their V is
-// staged as zeros, which keeps 0 * V finite.
-struct TileSrc {
-  const u32x4 *k_tree, *v_tree, *k_pool, *v_pool;
-  const int32_t *bt;  // page table row of the sequence
-  int g, n0, n_nodes, hkv, num_blocks;
-};
-
-// K: piece (tid % 16) of key tid/16 + 16*i
-__device__ __forceinline__ u32x4 load_k_piece(const TileSrc &s, bool tree_tile, int tile_start, int end,
-                                              int tid, int i) {
-  const int piece = tid & 15;
-  const int key = (tid >> 4) + 16 * i;
-  u32x4 x = {0u, 0u, 0u, 0u};
-  if (tree_tile) {
-    if (key < s.n_nodes) x = s.k_tree[((size_t)(s.n0 + key) * s.hkv + s.g) * 16 + piece];
-  } else {
-    int pos = tile_start + key;
-    if (pos < end) {
-      int blk = s.bt[pos / PAGE];
-      blk = blk < 0 ? 0 : (blk >= s.num_blocks ? s.num_blocks - 1 : blk);
-      x = s.k_pool[(((size_t)blk * s.hkv + s.g) * PAGE + (pos % PAGE)) * 16 + piece];
-    }
-  }
-  return x;
-}
-
-// V: d-piece (tid % 16) of key 4*(tid/16) + i
-__device__ __forceinline__ u32x4 load_v_piece(const TileSrc &s, bool tree_tile, int tile_start, int end,
-                                              int tid, int i) {
-  const int piece = tid & 15;
-  const int key = 4 * (tid >> 4) + i;
-  u32x4 x = {0u, 0u, 0u, 0u};
-  if (tree_tile) {
-    if (key < s.n_nodes) {
-      x = s.v_tree[((size_t)(s.n0 + key) * s.hkv + s.g) * 16 + piece];
-      // tree nodes off a row's path get probability 0; their V must not turn 0 * V into NaN
-      x[0] = finite_or_zero_bf16x2(x[0]);
-      x[1] = finite_or_zero_bf16x2(x[1]);
-      x[2] = finite_or_zero_bf16x2(x[2]);
-      x[3] = finite_or_zero_bf16x2(x[3]);
-    }
-  } else {
-    int pos = tile_start + key;
-    if (pos < end) {
-      int blk = s.bt[pos / PAGE];
-      blk = blk < 0 ? 0 : (blk >= s.num_blocks ? s.num_blocks - 1 : blk);
-      x = s.v_pool[(((size_t)blk * s.hkv + s.g) * PAGE + (pos % PAGE)) * 16 + piece];
-    }
-  }
-  return x;
-}
-
-// Registers -> LDS, K.  Rows keep their layout ([key][16 pieces]); the piece index is XORed with
-// the key so that the operand reads of 16 consecutive keys are conflict free.
-__device__ __forceinline__ void store_k(u32x4 *__restrict__ lk, int tid, u32x4 k0, u32x4 k1, u32x4 k2, u32x4 k3) {
-  const int piece = tid & 15;
-  const int krow = tid >> 4;
-  lk[(krow + 0) * 16 + (piece ^ krow)] = k0;   // (krow + 16 i) & 15 == krow
-  lk[(krow + 16) * 16 + (piece ^ krow)] = k1;
-  lk[(krow + 32) * 16 + (piece ^ krow)] = k2;
-  lk[(krow + 48) * 16 + (piece ^ krow)] = k3;
-}
-
 // V tile in LDS: rows = keys, 256 bytes each, in memory order ([key][d]); the 16-byte piece index is
 // XORed with v_swz(key).  The MFMA wants V^T (8 consecutive keys per lane at one d); the
 // transposing LDS read (ds_read_b64_tr_b16) delivers exactly that from this layout: within 16
@@ -139,16 +74,6 @@ __device__ __forceinline__ void store_k(u32x4 *__restrict__ lk, int tid, u32x4 k
 // The swizzle was chosen by timing all XOR patterns of this family on gfx950: with it the
 // transposed reads run conflict free (4x faster than unswizzled).
 __device__ __forceinline__ int v_swz(int key) { return (key & 7) << 1; }
-
-// Registers -> LDS, V rows of the tree tile: d-piece (tid % 16) of keys 4*(tid/16) .. +3.
-__device__ __forceinline__ void store_v(u32x4 *__restrict__ lv, int tid, u32x4 v0, u32x4 v1, u32x4 v2, u32x4 v3) {
-  const int piece = tid & 15;
-  const int key = 4 * (tid >> 4);
-  lv[(key + 0) * 16 + (piece ^ v_swz(key + 0))] = v0;
-  lv[(key + 1) * 16 + (piece ^ v_swz(key + 1))] = v1;
-  lv[(key + 2) * 16 + (piece ^ v_swz(key + 2))] = v2;
-  lv[(key + 3) * 16 + (piece ^ v_swz(key + 3))] = v3;
-}
 
 // 2^x by the hardware instruction: arguments here are <= 0 and results below the normal range
 // may flush to zero, which is what a vanishing softmax weight should do.
@@ -167,22 +92,18 @@ __device__ __forceinline__ float group_max(float x) {
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
-// One 32-key block of the current tile against all row tiles of the wavefront.
-//   partial (uniform): some keys of the block do not exist or are masked (chunk tail, tree tile).
-// Row tiles are taken in groups of at most four: scores and softmax for the group (VALU work,
-// QK^T on the matrix cores), then the group's O^T += V^T P^T.  This file is compiled with the
+// a / b for 0 <= a < 2^16, 0 < b < 2^16: (a + 1/2) / b keeps 1/(2b) away from every integer.
+__device__ __forceinline__ int small_div(int a, int b) { return (int)(((float)a + 0.5f) * __builtin_amdgcn_rcpf((float)b)); }
+
+// One 32-key block of a tile against the TPW row tiles of a wavefront, in five pieces: K fragments,
+// scores S^T = K Q^T, V^T fragments, probabilities, O^T += V^T P^T.  This file is compiled with the
 // matrix instructions in their vector-register form (scores are read by vector instructions
 // right away, so accumulation registers would only add copies); after every instruction that
 // defines an O^T accumulator an empty asm statement with a "v" constraint keeps the value where
 // it is instead of letting it be shuffled around every iteration.
-template <int TPW, int NW>
-__device__ __forceinline__ void attend_block(bool partial, const u32x4 *__restrict__ lk, const unsigned char *__restrict__ lv,
-                                             int blk32, int j, int kg, const bf16x8 (&qf)[TPW][4],
-                                             f32x4 (&o)[TPW][8], float (&m_run)[TPW], f32x4 (&l_run)[TPW],
-                                             float c1, int n_valid, bool is_tree, const unsigned long long *anc_lds,
-                                             int wave, int R, int G) {
-  // K fragments of the block's two 16-key halves, shared by all row tiles of the wavefront
-  bf16x8 ak[2][4];
+
+// K fragments of the block's two 16-key halves, shared by all row tiles of the wavefront
+__device__ __forceinline__ void read_k(const u32x4 *__restrict__ lk, int blk32, int j, int kg, bf16x8 (&ak)[2][4]) {
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
@@ -190,140 +111,161 @@ __device__ __forceinline__ void attend_block(bool partial, const u32x4 *__restri
       int key = 32 * blk32 + 16 * a + j;
       ak[a][ks] = __builtin_bit_cast(bf16x8, lk[key * 16 + ((4 * ks + kg) ^ j)]);
     }
+}
+
+template <int TPW>
+__device__ __forceinline__ void score_block(const bf16x8 (&ak)[2][4], const bf16x8 (&qf)[TPW][4], f32x4 (&sc)[TPW][2]) {
 #pragma unroll
-  for (int t0 = 0; t0 < TPW; t0 += 4) {
-    constexpr int kGroup = 4;
-    // -- scores of the group's tiles, masks, new running maxima (no branches: the matrix and
-    //    vector work of different tiles can be interleaved by the scheduler)
-    float sc[kGroup][8];
-    float lmax[kGroup];
-    bool need = false;
+  for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-    for (int u = 0; u < kGroup; ++u) {
-      const int t = t0 + u;
-      if (t >= TPW) break;
-      f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < TPW; ++t)
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
-        s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ak[0][ks], qf[t][ks], s0, 0, 0, 0);
-        s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ak[1][ks], qf[t][ks], s1, 0, 0, 0);
+      for (int a = 0; a < 2; ++a)
+        sc[t][a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ak[a][ks], qf[t][ks], ks ? sc[t][a] : (f32x4){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+}
+
+// All V^T fragments of the block.  Lane (s, kg) of a 16-lane group addresses 8 bytes of key
+// 16h + 4kg + s/4 at d = 16dt + 4(s%4); the transposing read hands lane j the four keys 16h + 4kg + 0..3
+// at d = 16dt + j, i.e. the k-slots 4h .. 4h+3 of the lane group in the order the score accumulators have.
+__device__ __forceinline__ void read_v(const unsigned char *__restrict__ lv, int blk32, int j, int kg, bf16x8 (&av)[8]) {
+  const int vkey = 4 * kg + (j >> 2);                       // + 16h + 32 blk32
+  const int vrow = (32 * blk32 + vkey) * 256 + 16 * ((j >> 1) & 1) + 8 * (j & 1);
+  const int vx = v_swz(vkey) * 16;                          // XOR on the piece index, in bytes
+#pragma unroll
+  for (int dt = 0; dt < 8; ++dt) {
+    const unsigned char *p0 = lv + vrow + ((32 * dt) ^ vx);
+    bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p0));
+    bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p0 + 16 * 256));
+    av[dt] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+  }
+}
+
+// Masks and the largest of a lane's eight scores per row tile; true if a row must move its reference.
+//   limit: the unscaled score up to which a row's reference stays, (m_run + kSlack) / c1.
+//   partial (uniform): some keys of the block do not exist or are masked (chunk tail, tree tile).
+template <int TPW, int NW>
+__device__ __forceinline__ bool mask_block(bool partial, int blk32, int j, int kg, f32x4 (&sc)[TPW][2], float (&lmax)[TPW],
+                                           const float (&limit)[TPW], int n_valid, bool is_tree,
+                                           const unsigned long long *anc_lds, int wave, int R, int G) {
+  if (partial) {
+#pragma unroll
+    for (int t = 0; t < TPW; ++t) {
+      // bit k of `allow`: key 32*blk32 + k exists and may be seen by this lane's row.  A select
+      // (not arithmetic) removes forbidden scores, so NaN/Inf there cannot leak.
+      uint32_t allow = ~0u;
+      if (is_tree) {
+        int row = (wave + NW * t) * 16 + j;  // `wave` here: the wavefront's first tile
+        int node = row < R ? small_div(row, G) : 0;
+        allow = (uint32_t)(anc_lds[node] >> (32 * blk32));
       }
+      int left = n_valid - 32 * blk32;
+      allow &= left >= 32 ? ~0u : ((1u << (left < 0 ? 0 : left)) - 1u);
+      allow >>= 4 * kg;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        sc[u][r] = s0[r];
-        sc[u][4 + r] = s1[r];
-      }
-      if (partial) {
-        // bit k of `allow`: key 32*blk32 + k exists and may be seen by this lane's row.  A select
-        // (not arithmetic) removes forbidden scores, so NaN/Inf there cannot leak.
-        uint32_t allow = ~0u;
-        if (is_tree) {
-          int row = (wave + NW * t) * 16 + j;  // `wave` here: the wavefront's first tile
-          int node = row < R ? row / G : 0;
-          allow = (uint32_t)(anc_lds[node] >> (32 * blk32));
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          sc[t][a][r] = ((allow >> (16 * a + r)) & 1u) ? sc[t][a][r] : HB_NEG_INF;
+    }
+  }
+  // Largest of the lane's own eight scores.  The row's reference exponent stays as it is
+  // unless one of the row's scores exceeds it by more than kSlack (then exp2(score -
+  // reference) <= 2^kSlack stays far from overflow and nothing needs rescaling); the four
+  // lanes that share a row see all of its scores between them, so a per-lane test decides
+  // and the common case needs no maximum across lanes.  A row without reference yet (-inf:
+  // first block) fails the test in every lane that holds an allowed key.  (No inline assembly here: the
+  // compiler does not see it read the matrix instructions' results and leaves out the wait states.)
+  bool need = false;
+#pragma unroll
+  for (int t = 0; t < TPW; ++t) {
+    float lm = fmaxf(fmaxf(fmaxf(fmaxf(fmaxf(fmaxf(fmaxf(sc[t][0][0], sc[t][0][1]), sc[t][0][2]), sc[t][0][3]), sc[t][1][0]), sc[t][1][1]), sc[t][1][2]), sc[t][1][3]);
+    lmax[t] = lm;
+    need |= !(lm <= limit[t]);
+  }
+  return need;
+}
+
+// Probabilities of the block (bf16), after moving the reference of rows that need it.
+template <int TPW>
+__device__ __forceinline__ void probabilities(bool need, const f32x4 (&sc)[TPW][2], const float (&lmax)[TPW], f32x4 (&o)[TPW][8],
+                                              float (&m_run)[TPW], float (&limit)[TPW], f32x4 (&l_run)[TPW], float c1,
+                                              bf16x8 (&pb)[TPW]) {
+  // -- rare: a row needs its first reference or has outgrown it.  The reference becomes the
+  //    row's maximum over the block and what has been accumulated is rescaled (rows that stay
+  //    get alpha = 1).  Uniform branches; the asm statement keeps the outer one a real branch,
+  //    otherwise the multiply of the whole accumulator is speculated into every pass.
+  if (__any(need)) {
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int t = 0; t < TPW; ++t) {
+      const float mx = group_max(lmax[t]) * c1;  // c1 > 0: scaling commutes with the maximum
+      const float m_old = m_run[t];
+      const float m_ref = (m_old == HB_NEG_INF) ? mx : m_old;  // nothing accumulated yet: adopt, no rescale
+      const bool grow = mx > m_ref + kSlack;
+      m_run[t] = grow ? mx : m_ref;
+      limit[t] = (m_run[t] + kSlack) / c1;
+      if (__any(grow)) {
+        const float alpha = grow ? fast_exp2(m_ref - mx) : 1.f;
+        l_run[t] *= alpha;
+#pragma unroll
+        for (int dt = 0; dt < 8; ++dt) {
+          asm volatile("" : "+v"(o[t][dt]));
+          o[t][dt] *= alpha;
+          asm volatile("" : "+v"(o[t][dt]));
         }
-        int left = n_valid - 32 * blk32;
-        allow &= left >= 32 ? ~0u : ((1u << (left < 0 ? 0 : left)) - 1u);
-        allow >>= 4 * kg;
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-          for (int r = 0; r < 4; ++r)
-            sc[u][4 * a + r] = ((allow >> (16 * a + r)) & 1u) ? sc[u][4 * a + r] : HB_NEG_INF;
-      }
-      // Largest of the lane's own eight scores.  The row's reference exponent stays as it is
-      // unless one of the row's scores exceeds it by more than kSlack (then exp2(score -
-      // reference) <= 2^kSlack stays far from overflow and nothing needs rescaling); the four
-      // lanes that share a row see all of its scores between them, so a per-lane test decides
-      // and the common case needs no maximum across lanes.  A row without reference yet (-inf:
-      // first block) fails the test in every lane that holds an allowed key.
-      float lm = fmaxf(fmaxf(fmaxf(fmaxf(fmaxf(fmaxf(fmaxf(sc[u][0], sc[u][1]), sc[u][2]), sc[u][3]), sc[u][4]), sc[u][5]), sc[u][6]), sc[u][7]);
-      lmax[u] = lm;
-      need |= !(lm * c1 <= m_run[t] + kSlack);
-    }
-    // -- all V^T fragments of the block, issued now so that they arrive during the vector work
-    //    below (they take over the registers of the K fragments, which are done).  Lane (s, kg)
-    //    of a 16-lane group addresses 8 bytes of key 16h + 4kg + s/4 at d = 16dt + 4(s%4); the
-    //    transposing read hands lane j the four keys 16h + 4kg + 0..3 at d = 16dt + j, i.e. the
-    //    k-slots 4h .. 4h+3 of the lane group in the order the score accumulators have.
-    bf16x8 av[8];
-    {
-      const int vkey = 4 * kg + (j >> 2);                       // + 16h + 32 blk32
-      const int vrow = (32 * blk32 + vkey) * 256 + 16 * ((j >> 1) & 1) + 8 * (j & 1);
-      const int vx = v_swz(vkey) * 16;                          // XOR on the piece index, in bytes
-#pragma unroll
-      for (int dt = 0; dt < 8; ++dt) {
-        const unsigned char *p0 = lv + vrow + ((32 * dt) ^ vx);
-        bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p0));
-        bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4_ptr)(p0 + 16 * 256));
-        av[dt] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    // -- rare: a row needs its first reference or has outgrown it.  The reference becomes the
-    //    row's maximum over the block and what has been accumulated is rescaled (rows that stay
-    //    get alpha = 1).  Uniform branches; the asm statement keeps the outer one a real branch,
-    //    otherwise the multiply of the whole accumulator is speculated into every pass.
-    if (__any(need)) {
-      asm volatile("" ::: "memory");
-#pragma unroll
-      for (int u = 0; u < kGroup; ++u) {
-        const int t = t0 + u;
-        if (t >= TPW) break;
-        const float mx = group_max(lmax[u]) * c1;  // c1 > 0: scaling commutes with the maximum
-        const float m_old = m_run[t];
-        const float m_ref = (m_old == HB_NEG_INF) ? mx : m_old;  // nothing accumulated yet: adopt, no rescale
-        const bool grow = mx > m_ref + kSlack;
-        m_run[t] = grow ? mx : m_ref;
-        if (__any(grow)) {
-          const float alpha = grow ? fast_exp2(m_ref - mx) : 1.f;
-          l_run[t] *= alpha;
-#pragma unroll
-          for (int dt = 0; dt < 8; ++dt) {
-            asm volatile("" : "+v"(o[t][dt]));
-            o[t][dt] *= alpha;
-            asm volatile("" : "+v"(o[t][dt]));
-          }
-        }
-      }
-    }
-    // -- probabilities.  Every row has seen at least one allowed key by now (the first key of a
-    //    prefix chunk, the root of the tree), so its reference is finite.
-    bf16x8 pb[kGroup];
-#pragma unroll
-    for (int u = 0; u < kGroup; ++u) {
-      const int t = t0 + u;
-      if (t >= TPW) break;
-      f32x8 p;
-#pragma unroll
-      for (int r = 0; r < 8; ++r) p[r] = fast_exp2(fmaf(sc[u][r], c1, -m_run[t]));
-      pb[u] = __builtin_convertvector(p, bf16x8);
-    }
-    // -- row sums on the matrix cores: an all-ones A operand makes every row of the product the
-    //    sum over the block's 32 keys of the (bf16) probabilities, summed across the lane groups
-    //    too; eight vector additions per tile and the final cross-lane sum are saved
-    {
-      const bf16x8 ones = {(__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f};
-#pragma unroll
-      for (int u = 0; u < kGroup; ++u) {
-        const int t = t0 + u;
-        if (t >= TPW) break;
-        l_run[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pb[u], l_run[t], 0, 0, 0);
-        asm volatile("" : "+v"(l_run[t]));
-      }
-    }
-    // -- O^T += V^T P^T for the group, one 16-d slab of V^T at a time
-#pragma unroll
-    for (int dt = 0; dt < 8; ++dt) {
-#pragma unroll
-      for (int u = 0; u < kGroup; ++u) {
-        const int t = t0 + u;
-        if (t >= TPW) break;
-        o[t][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[dt], pb[u], o[t][dt], 0, 0, 0);
-        asm volatile("" : "+v"(o[t][dt]));
       }
     }
   }
+  // -- Every row has seen at least one allowed key by now (the first key of a prefix chunk, the
+  //    root of the tree), so its reference is finite.
+#pragma unroll
+  for (int t = 0; t < TPW; ++t) {
+    f32x8 p;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) p[r] = fast_exp2(fmaf(sc[t][r >> 2][r & 3], c1, -m_run[t]));
+    pb[t] = __builtin_convertvector(p, bf16x8);
+  }
+}
+
+template <int TPW>
+__device__ __forceinline__ void accumulate_block(const bf16x8 (&av)[8], const bf16x8 (&pb)[TPW], f32x4 (&o)[TPW][8], f32x4 (&l_run)[TPW]) {
+  // -- row sums on the matrix cores: an all-ones A operand makes every row of the product the
+  //    sum over the block's 32 keys of the (bf16) probabilities, summed across the lane groups
+  //    too; eight vector additions per tile and the final cross-lane sum are saved
+  const bf16x8 ones = {(__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f};
+#pragma unroll
+  for (int t = 0; t < TPW; ++t) {
+    l_run[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pb[t], l_run[t], 0, 0, 0);
+    asm volatile("" : "+v"(l_run[t]));
+  }
+  // -- O^T += V^T P^T, one 16-d slab of V^T at a time
+#pragma unroll
+  for (int dt = 0; dt < 8; ++dt) {
+#pragma unroll
+    for (int t = 0; t < TPW; ++t) {
+      o[t][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[dt], pb[t], o[t][dt], 0, 0, 0);
+      asm volatile("" : "+v"(o[t][dt]));
+    }
+  }
+}
+
+// The block from start to end, for the four-wavefront shapes.
+template <int TPW, int NW>
+__device__ __forceinline__ void attend_block(bool partial, const u32x4 *__restrict__ lk, const unsigned char *__restrict__ lv,
+                                             int blk32, int j, int kg, const bf16x8 (&qf)[TPW][4],
+                                             f32x4 (&o)[TPW][8], float (&m_run)[TPW], float (&limit)[TPW], f32x4 (&l_run)[TPW],
+                                             float c1, int n_valid, bool is_tree, const unsigned long long *anc_lds,
+                                             int wave, int R, int G) {
+  bf16x8 ak[2][4], av[8], pb[TPW];
+  f32x4 sc[TPW][2];
+  float lmax[TPW];
+  read_k(lk, blk32, j, kg, ak);
+  score_block<TPW>(ak, qf, sc);
+  const bool need = mask_block<TPW, NW>(partial, blk32, j, kg, sc, lmax, limit, n_valid, is_tree, anc_lds, wave, R, G);
+  read_v(lv, blk32, j, kg, av);  // issued now: they arrive during the vector work below
+  __builtin_amdgcn_sched_barrier(0);
+  probabilities<TPW>(need, sc, lmax, o, m_run, limit, l_run, c1, pb);
+  accumulate_block<TPW>(av, pb, o, l_run);
 }
 
 // ceil(a / b) for 0 <= a < 2^21, b > 0 (an integer division by a value known at run time only costs a
@@ -361,8 +303,6 @@ __device__ __forceinline__ int max_lanes(int x) {
 
 // TPW: 16-row tiles per wavefront (1 or 2).  NW: wavefronts per workgroup: 4 (two workgroups per
 // CU) or 8 (one per CU, twice the rows sharing each staged tile).  NS: LDS stages of the KV ring.
-// The tree tile, which goes through registers, is staged by all threads (NW = 4) or K by
-// wavefronts 0-3 and V by wavefronts 4-7 (NW = 8).
 template <int TPW, int NW, int NS>
 __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mfma_kernel(
     hb_attn_desc d, int splits, int chunk_tokens, int workers, int each, int min_per, int row_groups, const u32x4 *__restrict__ q, const u32x4 *__restrict__ k_tree,
@@ -583,7 +523,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mfma_kernel(
   for (int t = 0; t < TPW; ++t) {
     int row = (wtile + NW * t) * 16 + j;
     bool ok = row < R && (wtile + NW * t) < tile_hi;
-    int node = ok ? row / G : 0;
+    int node = ok ? small_div(row, G) : 0;
     int hg = ok ? row - node * G : 0;
     const u32x4 *src = q + (row_base + (size_t)node * d.num_q_heads + hg) * 16;
 #pragma unroll
@@ -596,11 +536,11 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mfma_kernel(
 
   // fp32 O^T accumulators, kept in place in vector registers
   f32x4 o[TPW][8];
-  float m_run[TPW];
+  float m_run[TPW], limit[TPW];
   f32x4 l_run[TPW];  // row sums of the probabilities (every element holds the row's sum)
 #pragma unroll
   for (int t = 0; t < TPW; ++t) {
-    m_run[t] = HB_NEG_INF;
+    m_run[t] = limit[t] = HB_NEG_INF;
     l_run[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) {
@@ -619,7 +559,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mfma_kernel(
   // have the same position inside their page, so one offset register each serves.  The page ids
   // of a tile (wave-uniform scalar loads, clamped into the pool so every address is valid) are
   // fetched one tile before they are needed.
-  // Tiles are loaded NS - 1 ahead of the one being computed.  Every pipeline step issues one
+  // Tiles are loaded up to NS ahead of the one being computed.  Every pipeline step issues one
   // batch of PER loads per wavefront, also past the end (then it re-fetches the last tile into a
   // free stage), so that the wait "all but the newest PER * (NS - 2) loads" always means "the
   // next tile has landed".
@@ -627,9 +567,6 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mfma_kernel(
   // replaced by a select before anything is computed from them; the V rows are overwritten with
   // zeros once they have landed (0 * V must stay finite).
   constexpr int PER = 32 / NW;
-  const int stid = tid & 255;               // thread index inside a staging role (tree tile)
-  const bool do_k = NW == 4 || wave < 4;    // tree tile: who stages K, who stages V
-  const bool do_v = NW == 4 || wave >= 4;
   const int lrow = lane >> 4;               // key inside a 4-key row group
   const bool whi = wave >= 4;               // eight wavefronts: which pair of the tile's pages
   const int gcls = wave & 3;                // row groups w + NW*i sit at keys 4*gcls .. +3 of their page
@@ -666,7 +603,6 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mfma_kernel(
     pg3 = HB_PAGE(p0__ + 3);                                                \
   }
   // batch k_: the tile of pipeline step max(k_, tree_off) into stage max(k_, tree_off) % NS
-  // (in a tree chunk batch 0 loads the same as batch 1: stage 0 belongs to the tree tile)
 #define HB_ISSUE_BATCH(k_)                                                                     \
   {                                                                                            \
     const int t__ = (k_) < tree_off ? tree_off : (k_);                                         \
@@ -687,37 +623,24 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mfma_kernel(
   constexpr int kWaitImm = (kKeep & 15) | ((kKeep >> 4) << 14) | (7 << 4) | (15 << 8);  // vmcnt only
 #define HB_NEXT_LANDED() __builtin_amdgcn_s_waitcnt(kWaitImm)
 
-  TileSrc src;
-  src.k_tree = k_tree; src.v_tree = v_tree; src.k_pool = k_pool; src.v_pool = v_pool;
-  src.bt = bt_row;
-  src.g = g; src.n0 = n0; src.n_nodes = n_nodes; src.hkv = d.num_kv_heads; src.num_blocks = d.num_blocks;
-
-  // prologue: the tree tile (keys = node ids, read straight from k_tree / v_tree, non-finite V
-  // zeroed) goes through registers into stage 0; batches 0 .. NS-2 are issued behind its loads
-  u32x4 tk0, tk1, tk2, tk3, tv0, tv1, tv2, tv3;
+  // prologue: batches 0 .. NS-2; batch 0 of a tree chunk is the tree tile (keys = node ids; a row past the
+  // last node repeats it)
   if (tree_chunk) {
-    if (do_k) {
-      tk0 = load_k_piece(src, true, 0, 0, stid, 0);
-      tk1 = load_k_piece(src, true, 0, 0, stid, 1);
-      tk2 = load_k_piece(src, true, 0, 0, stid, 2);
-      tk3 = load_k_piece(src, true, 0, 0, stid, 3);
-    }
-    if (do_v) {
-      tv0 = load_v_piece(src, true, 0, 0, stid, 0);
-      tv1 = load_v_piece(src, true, 0, 0, stid, 1);
-      tv2 = load_v_piece(src, true, 0, 0, stid, 2);
-      tv3 = load_v_piece(src, true, 0, 0, stid, 3);
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int n = wave + NW * i;  // 0..15: K row group, 16..31: V row group
+      int key = 4 * (n & 15) + lrow;
+      key = key < n_nodes ? key : n_nodes - 1;
+      const u32x4 *src = (n < 16 ? k_tree : v_tree) + ((size_t)(n0 + key) * d.num_kv_heads + g) * 16 +
+                         ((lane & 15) ^ (n < 16 ? pkey : v_swz(pkey)));
+      __builtin_amdgcn_global_load_lds((gptr_t)src, (lptr_t)(smem + n * 1024), 16, 0, 0);
     }
   }
   HB_FETCH_PAGES(0);
 #pragma unroll
   for (int k = 0; k < NS - 1; ++k) {
-    HB_ISSUE_BATCH(k);
+    if (k > 0 || !tree_chunk) HB_ISSUE_BATCH(k);
     HB_FETCH_PAGES(k + 1);
-  }
-  if (tree_chunk) {
-    if (do_k) store_k((u32x4 *)smem, stid, tk0, tk1, tk2, tk3);
-    if (do_v) store_v((u32x4 *)(smem + K_PIECES * 16), stid, tv0, tv1, tv2, tv3);
   }
   // V rows past the end of the tile pipeline step t_ holds, zeroed by the wavefront that loaded
   // them (uniform condition; only a chunk's last prefix tile can be short)
@@ -742,32 +665,103 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mfma_kernel(
   // tile 0 is ready: everything but the newest NS - 2 batches has landed
   HB_NEXT_LANDED();
   HB_ZERO_V_TAIL(0);
-  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the tree tile's LDS writes
+  if (tree_chunk) {
+    // V of the tree tile, by the wavefront that loaded it: nodes off a row's path get probability 0, and their
+    // V must not turn 0 * V into NaN; rows past the last node are zeros
+#pragma unroll
+    for (int i = PER / 2; i < PER; ++i) {
+      const int n = wave + NW * i;
+      u32x4 *at = (u32x4 *)(smem + n * 1024 + lane * 16);
+      u32x4 x = *at;
+      const uint32_t node = 4 * (n - 16) + lrow < n_nodes ? ~0u : 0u;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] = finite_or_zero_bf16x2(x[e]) & node;
+      *at = x;
+    }
+  }
+  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): these writes and the ancestor masks
   HB_BARRIER();
 
+  if constexpr (NW == 4) {
+    // Two workgroups per CU, whose waits cover each other's: a block at a time.  (The loop below: 8-node chains, 16
+    // sequences 31.1 us against 30.8, two over 200 positions 16.1 against 15.1, 30-node trees of 120 rows 69 against 61.)
 #pragma unroll 1  // also keeps the compiler from peeling the tree tile's iteration into a second copy
-  for (int i = 0; i < n_tiles; ++i) {
-    const bool is_tree = tree_chunk && i == 0;
-    const int tile_start = begin + (i - tree_off) * KT;                 // prefix position of key 0
-    const int n_valid = is_tree ? n_nodes : min(KT, end - tile_start);  // keys of this tile that exist
-    const unsigned char *stage = smem + (i % NS) * kStageBytes;
-    const u32x4 *lk = (const u32x4 *)stage;
-    const unsigned char *lv = stage + K_PIECES * 16;
-    const bool partial = is_tree || n_valid < KT;  // uniform
+    for (int i = 0; i < n_tiles; ++i) {
+      const bool is_tree = tree_chunk && i == 0;
+      const int tile_start = begin + (i - tree_off) * KT;                 // prefix position of key 0
+      const int n_valid = is_tree ? n_nodes : min(KT, end - tile_start);  // keys of this tile that exist
+      const unsigned char *stage = smem + (i % NS) * kStageBytes;
+      const bool partial = is_tree || n_valid < KT;  // uniform
 
-    // the stage of tile i - 1 is free (barrier below): fill it with tile i + NS - 1
-    HB_ISSUE_BATCH(i + NS - 1);
-    HB_FETCH_PAGES(i + NS);  // for the batch of the next iteration
+      // the stage of tile i - 1 is free (barrier below): fill it with tile i + NS - 1
+      HB_ISSUE_BATCH(i + NS - 1);
+      HB_FETCH_PAGES(i + NS);  // for the batch of the next iteration
 
 #pragma unroll 1
-    for (int blk32 = 0; blk32 < 2; ++blk32) {
-      if (32 * blk32 < n_valid)
-        attend_block<TPW, NW>(partial, lk, lv, blk32, j, kg, qf, o, m_run, l_run, c1, n_valid, is_tree, anc_lds, wtile,
-                              R, G);
+      for (int blk32 = 0; blk32 < 2; ++blk32) {
+        if (32 * blk32 < n_valid)
+          attend_block<TPW, NW>(partial, (const u32x4 *)stage, stage + K_PIECES * 16, blk32, j, kg, qf, o, m_run, limit, l_run,
+                                c1, n_valid, is_tree, anc_lds, wtile, R, G);
+      }
+      HB_NEXT_LANDED();
+      HB_ZERO_V_TAIL(i + 1);
+      HB_BARRIER();
     }
-    HB_NEXT_LANDED();
-    HB_ZERO_V_TAIL(i + 1);
-    HB_BARRIER();
+  } else {
+    // One workgroup per CU.  The loop over 32-key blocks is skewed by one: with the probabilities of a block
+    // and its V^T fragments in registers, the matrix core gets O^T of this block and the scores of the next
+    // in one go (34 instructions without a wait), and the vector work that follows has its scores already:
+    // 4200 clocks a tile against 4800 block by block; two trees of 60 nodes over 32768 positions 94.8 -> 86.4 us,
+    // 16 over 1024 to 4096 79.9 -> 74.2.  What bounds it is the issue of vector instructions and MFMAs (8 clocks
+    // of the port each) by two wavefronts: taking turns phase by phase, a barrier after each, was slower (4520).
+    // A tile's stage is last read in front of the barrier that stands between its second block's vector
+    // and matrix work and is filled with tile i + NS right behind it; that barrier also lets everybody into
+    // tile i + 1, whose loads each wavefront has waited for in front of it.
+    bf16x8 ak[2][4], av[8], pb[TPW];
+    f32x4 sc[TPW][2];
+#define HB_HERE(ARR_, N_) _Pragma("unroll") for (int x__ = 0; x__ < (N_); ++x__) asm volatile("" : "+v"(ARR_[x__]))
+#define HB_VECTOR_WORK(blk_)                                                                                                \
+  {                                                                                                                         \
+    float lmax__[TPW];                                                                                                      \
+    _Pragma("unroll") for (int t__ = 0; t__ < TPW; ++t__) HB_HERE(sc[t__], 2);                                               \
+    read_v(lv, blk_, j, kg, av);                                                                                            \
+    __builtin_amdgcn_sched_barrier(0);                                                                                      \
+    const bool need__ = mask_block<TPW, NW>(partial, blk_, j, kg, sc, lmax__, limit, n_valid, is_tree, anc_lds, wtile, R, G); \
+    probabilities<TPW>(need__, sc, lmax__, o, m_run, limit, l_run, c1, pb);                                                 \
+    HB_HERE(pb, TPW);                                                                                                       \
+    HB_HERE(av, 8);                                                                                                         \
+  }
+    HB_ISSUE_BATCH(NS - 1);
+    HB_FETCH_PAGES(NS);
+    read_k((const u32x4 *)smem, 0, j, kg, ak);
+    score_block<TPW>(ak, qf, sc);
+#pragma unroll 1
+    for (int i = 0; i < n_tiles; ++i) {
+      const bool is_tree = tree_chunk && i == 0;
+      const int tile_start = begin + (i - tree_off) * KT;
+      const int n_valid = is_tree ? n_nodes : min(KT, end - tile_start);
+      const unsigned char *stage = smem + (i % NS) * kStageBytes;
+      const unsigned char *lv = stage + K_PIECES * 16;
+      const bool partial = is_tree || n_valid < KT;
+
+      HB_VECTOR_WORK(0);
+      read_k((const u32x4 *)stage, 1, j, kg, ak);
+      accumulate_block<TPW>(av, pb, o, l_run);
+      score_block<TPW>(ak, qf, sc);
+      HB_VECTOR_WORK(1);
+      HB_NEXT_LANDED();
+      HB_ZERO_V_TAIL(i + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      HB_BARRIER();
+      __builtin_amdgcn_sched_barrier(0);
+      read_k((const u32x4 *)(smem + ((i + 1) % NS) * kStageBytes), 0, j, kg, ak);
+      accumulate_block<TPW>(av, pb, o, l_run);
+      HB_ISSUE_BATCH(i + NS);  // into the stage of tile i
+      score_block<TPW>(ak, qf, sc);
+      HB_FETCH_PAGES(i + NS + 1);  // for the batch of the next iteration
+    }
+#undef HB_HERE
+#undef HB_VECTOR_WORK
   }
   // loads past the end are still in flight: let them land before the workgroup gives up its LDS
   __builtin_amdgcn_s_waitcnt((0 & 15) | (7 << 4) | (15 << 8));
@@ -786,7 +780,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mfma_kernel(
     if ((wtile + NW * t) >= tile_hi) continue;
     float l_tot = l_run[t][0];
     if (row >= R) continue;
-    int node = row / G, hg = row - node * G;
+    int node = small_div(row, G), hg = row - node * G;
     size_t rg = row_base + (size_t)node * d.num_q_heads + hg;
     if (direct_out) {
       float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;

@@ -151,6 +151,19 @@ def test_short_pieces_of_a_few_sequences(hb, step, nodes, lens):
         check_attn(inp, out, lse, ref=ref, label=f"pieces {nodes} {lens} hint={hint}")
 
 
+@pytest.mark.parametrize("n_nodes", [20, 33, 64])
+@pytest.mark.parametrize("lens", [[0, 1, 31, 32, 33, 63], [64, 65, 95, 96, 97, 127, 128, 129], [255, 256, 257, 320]])
+def test_tile_counts_and_tails_of_the_eight_wavefront_shape(hb, step, n_nodes, lens):
+    """More than 128 rows: one to six tiles a workgroup and half-empty last blocks, whole and in pieces;
+    trees that end in the first and in the second block of their tile, and one that fills it."""
+    trees = [W.seeded_tree(40 + i, n_nodes=n_nodes, levels=4, root_fanout=5) for i in range(len(lens))]
+    inp = W.make_verify_inputs(81, "bf16", 28, 4, 128, lens, trees, kv_std=1.0, q_std=1.0)
+    ref = oracle_attn(inp)
+    for splits in (1, 3, 0):
+        out, lse, _ = _run(step, inp, num_splits=splits, algo=hb.HB_ATTN_MFMA)
+        check_attn(inp, out, lse, ref=ref, label=f"tails {n_nodes} {lens} s={splits}")
+
+
 def test_schedules_of_the_matrix_core_kernel(hb, step):
     """With num_splits = 0 the kernel cuts the KV itself, on the device, from the prefix lengths:
     work-proportionally when that finishes first (one long sequence among short ones: pieces of

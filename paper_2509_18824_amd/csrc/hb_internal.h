@@ -103,6 +103,14 @@ bool proj_stream_takes(int32_t M, int32_t K, int32_t N, bool split);
 hipError_t launch_proj_stream(StreamKind kind, int32_t M, int32_t K, int32_t N, const void *hidden, const void *weight,
                               const StreamArgs &sa, hipStream_t s);
 
+// 17 to 128 tokens (proj_few.hip): 16 `rows` weight rows a tile, K in `ks` parts (more than one: partial sums
+// [part][token of m_pad][weight row of v_pad] to `part` instead of results); rows = 0: not taken
+struct FewPlan {
+  int32_t rows, ks;
+};
+hipError_t launch_proj_few(StreamKind kind, const FewPlan &p, int32_t M, int32_t K, int32_t N, const void *hidden,
+                           const void *weight, const StreamArgs &sa, float *part, int32_t v_pad, int32_t m_pad, hipStream_t s);
+
 bool proj_mfma_supports(int32_t M, int32_t K, int32_t N);
 // part: fp32 scratch of proj_workspace_bytes(M, K, N) bytes for the split-K path, or null (then: one workgroup per tile)
 size_t proj_workspace_bytes(int32_t M, int32_t K, int32_t N);

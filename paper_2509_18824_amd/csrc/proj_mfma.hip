@@ -365,13 +365,84 @@ SplitPlan split_plan(int M, int K, int V) {
   return best;
 }
 
-// Whether the streaming kernel takes the product; otherwise *plan says how K is split.  The plan costs the
-// host some microseconds and is made only where it matters.
-bool stream_or_plan(int M, int K, int V, const float *part, SplitPlan *plan) {
+size_t split_bytes(SplitPlan plan, int M, int V) {
+  if (plan.ks <= 1) return 0;
+  const size_t v_pad = (size_t)((V + TV - 1) / TV) * TV;
+  const size_t tm = 64 * plan.mt, m_pad = (M + tm - 1) / tm * tm;
+  return (size_t)plan.ks * v_pad * m_pad * sizeof(float);
+}
+
+constexpr int kFewLeast = 17, kFewMost = 128;  // tokens
+inline int few_m_pad(int M) { return M <= 64 ? 64 : 128; }
+
+// 17 to 128 tokens: rows of a tile and parts of K of proj_few.hip, one round of workgroups (rows = 0: there is
+// no such division).  Microseconds fitted to 250 measurements (18 shapes of 2048 to 18944 x 2048 to 37888, 40 to
+// 128 tokens, weights too many to stay in the last-level cache; 7 % rms), a K step's part by the rows and by the
+// share of the CUs at work.  What it takes is within 1 % of the fastest of them in the mean, and 19 % faster
+// than the split into 256-row tiles (128 tokens, split and reduction against this: 3584 x 3584 18.4 -> 16.2,
+// 18944 x 3584 49 -> 40, 2048 x 2048 13.7 -> 8.8; gated 3584 x 37888 73.5 -> 58.9, 4096 x 24576 62 -> 51).
+// Against the stream, which takes fewer tokens, the line lies at 17: at 16 / 17 / 32 tokens 3584 x 3584 9.1 / 10.9 /
+// 12.0 there, 10.7 / 10.7 / 11.0 here; 18944 x 3584 33.5 / 35.4 / 42.4 and 30 / 30 / 31; gated 2048 x 16384 16.7 /
+// 23 / 23.4 and 19; 3584 x 37888 49.3 / 53.7 / 56.7 and 48.8 / 48.8 / 49.6.
+// Gated weights are not split (tiles of pairs, and never few); 16-row tiles only where K is whole.
+// workspace: the bytes that a caller was told to bring, for split_plan.
+FewPlan few_plan(int M, int K, int V, StreamKind kind, size_t workspace) {
+  FewPlan best = {0, 1};
+  if (M < kFewLeast || M > kFewMost || K % BK) return best;
+  const int steps = K / BK, v_pad = (V + TV - 1) / TV * TV;
+  const bool gated = kind == StreamKind::kGlu;
+  static const int kRows[] = {1, 2, 4, 6, 8, 10};
+  double best_cost = 1e30;
+  for (int rows : kRows) {
+    if (rows == 1 && kind != StreamKind::kPlain) continue;
+    // many short gated rows: the tile kernel keeps up (2048 x 32768, 40 tokens: 35.5 us against 37.3)
+    if (gated && rows >= 8 && K <= 2048) continue;
+    const long tiles = gated ? (V / 2 + 8 * rows - 1) / (8 * rows) : (V + 16 * rows - 1) / (16 * rows);
+    for (int ks = 1; ks <= (gated || rows == 1 ? 1 : 8); ++ks) {
+      if (steps % ks || (ks > 1 && steps / ks < 6) || tiles * ks > 256) continue;
+      if (ks > 1 && (size_t)ks * v_pad * few_m_pad(M) * sizeof(float) > workspace) continue;
+      const double step = 0.08 + 0.039 * rows + 0.047 * rows * (double)(tiles * ks) / 256 + (M > 64 ? 0.12 : 0.0);
+      const double sums = ks > 1 ? 4.0 + 0.86 * 8.0 * ks * v_pad * few_m_pad(M) / 4e6 : 0.0;
+      const double cost = 3.0 + steps / ks * step + sums;
+      if (cost < best_cost) {
+        best_cost = cost;
+        best = {rows, ks};
+      }
+    }
+  }
+  return best;
+}
+
+template <bool ROPE, bool GLU>
+hipError_t launch_few(StreamKind kind, const FewPlan &p, int M, int K, int V, const void *hidden, const void *weight,
+                      const QkvArgs &qa, const StoreArgs &sa, float *part, hipStream_t s) {
+  if (p.ks > 1 && !part) return hipErrorInvalidValue;
+  const int v_pad = (V + TV - 1) / TV * TV, m_pad = few_m_pad(M);
+  const StreamArgs st = {sa.residual, sa.out, qa.bias, qa.cos, qa.sin, qa.q, qa.k, qa.v, qa.Hq, qa.Hkv};
+  hipError_t e = launch_proj_few(kind, p, M, K, V, hidden, weight, st, part, v_pad, m_pad, s);
+  if (e != hipSuccess || p.ks == 1) return e;
+  return launch_reduce<ROPE, GLU>(M, V, p.ks, v_pad, m_pad, qa, sa, part, s);
+}
+
+// Which kernel takes the product: the stream, few rows against all tokens, or tiles of 256 rows (split over K as
+// *plan says).  The plan costs the host some microseconds and is made only where it matters.
+enum class Way { kStream, kFew, kTiles };
+Way way_of(int M, int K, int V, StreamKind kind, const float *part, FewPlan *few, SplitPlan *plan) {
   *plan = {1, 1};
-  if (proj_stream_takes(M, K, V, true)) return true;  // then also where K is not split
+  *few = {0, 1};
+  if (M < kFewLeast && proj_stream_takes(M, K, V, true)) return Way::kStream;  // then also where K is not split
   if (part) *plan = split_plan(M, K, V);
-  return plan->ks <= 1 && proj_stream_takes(M, K, V, false);
+  *few = few_plan(M, K, V, kind, split_bytes(*plan, M, V));
+  if (few->rows) return Way::kFew;
+  if (proj_stream_takes(M, K, V, true)) return Way::kStream;
+  return plan->ks <= 1 && proj_stream_takes(M, K, V, false) ? Way::kStream : Way::kTiles;
+}
+
+template <bool ROPE, bool GLU>
+hipError_t launch_reduce(int M, int V, int ks, int v_pad, int m_pad, const QkvArgs &qa, const StoreArgs &sa, const float *part, hipStream_t s) {
+  const int groups = ROPE ? V / kHeadDim * 16 : GLU ? V / 8 : V / 4;
+  proj_reduce_kernel<ROPE, GLU><<<dim3((unsigned)((groups + 255) / 256), (unsigned)M), 256, 0, s>>>(M, V, ks, v_pad, m_pad, groups, part, qa, sa);
+  return hipGetLastError();
 }
 
 template <bool ROPE, bool GLU>
@@ -402,9 +473,7 @@ hipError_t launch_splitk(int M, int K, int V, SplitPlan plan, const void *hidden
   }
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int groups = ROPE ? V / kHeadDim * 16 : GLU ? V / 8 : V / 4;
-  proj_reduce_kernel<ROPE, GLU><<<dim3((unsigned)((groups + 255) / 256), (unsigned)M), 256, 0, s>>>(M, V, ks, v_pad, m_pad, groups, part, qa, sa);
-  return hipGetLastError();
+  return launch_reduce<ROPE, GLU>(M, V, ks, v_pad, m_pad, qa, sa, part, s);
 }
 
 template <bool ROPE, bool GLU>
@@ -527,11 +596,7 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(int K, const bf16_t *__res
 bool proj_mfma_supports(int32_t M, int32_t K, int32_t N) { return M >= 1 && K >= BK && K % BK == 0 && N >= 4 && N % 4 == 0; }
 
 size_t proj_workspace_bytes(int32_t M, int32_t K, int32_t N) {
-  const SplitPlan plan = split_plan(M, K, N);
-  if (plan.ks <= 1) return 0;
-  const size_t v_pad = (size_t)((N + TV - 1) / TV) * TV;
-  const size_t tm = 64 * plan.mt, m_pad = (M + tm - 1) / tm * tm;
-  return (size_t)plan.ks * v_pad * m_pad * sizeof(float);
+  return split_bytes(split_plan(M, K, N), M, N);
 }
 
 hipError_t launch_qkv_rope(int32_t M, int32_t K, int32_t Hq, int32_t Hkv, const void *hidden, const void *w_qkv,
@@ -540,8 +605,11 @@ hipError_t launch_qkv_rope(int32_t M, int32_t K, int32_t Hq, int32_t Hkv, const 
   QkvArgs qa = {(const bf16_t *)bias, cos, sin, (bf16_t *)q, (bf16_t *)k, (bf16_t *)v, Hq, Hkv};
   StoreArgs sa = {nullptr, nullptr};
   const int V = (Hq + 2 * Hkv) * kHeadDim;
+  FewPlan few;
   SplitPlan plan;
-  if (stream_or_plan(M, K, V, part, &plan)) {
+  const Way way = way_of(M, K, V, StreamKind::kRope, part, &few, &plan);
+  if (way == Way::kFew) return launch_few<true, false>(StreamKind::kRope, few, M, K, V, hidden, w_qkv, qa, sa, part, s);
+  if (way == Way::kStream) {
     const StreamArgs st = {nullptr, nullptr, qa.bias, cos, sin, qa.q, qa.k, qa.v, Hq, Hkv};
     return launch_proj_stream(StreamKind::kRope, M, K, V, hidden, w_qkv, st, s);
   }
@@ -553,8 +621,11 @@ hipError_t launch_linear(int32_t M, int32_t K, int32_t N, const void *x, const v
                          float *part, hipStream_t s) {
   QkvArgs qa = {};
   StoreArgs sa = {(const bf16_t *)residual, (bf16_t *)out};
+  FewPlan few;
   SplitPlan plan;
-  if (stream_or_plan(M, K, N, part, &plan)) return launch_proj_stream(StreamKind::kPlain, M, K, N, x, w, {sa.residual, sa.out}, s);
+  const Way way = way_of(M, K, N, StreamKind::kPlain, part, &few, &plan);
+  if (way == Way::kFew) return launch_few<false, false>(StreamKind::kPlain, few, M, K, N, x, w, qa, sa, part, s);
+  if (way == Way::kStream) return launch_proj_stream(StreamKind::kPlain, M, K, N, x, w, {sa.residual, sa.out}, s);
   if (plan.ks > 1) return launch_splitk<false, false>(M, K, N, plan, x, w, qa, sa, part, s);
   return dispatch<false, false>(M, K, N, x, w, qa, sa, s);
 }
@@ -563,8 +634,11 @@ hipError_t launch_swiglu(int32_t M, int32_t K, int32_t F, const void *x, const v
                          hipStream_t s) {
   QkvArgs qa = {};
   StoreArgs sa = {nullptr, (bf16_t *)out};
+  FewPlan few;
   SplitPlan plan;
-  if (stream_or_plan(M, K, 2 * F, part, &plan)) return launch_proj_stream(StreamKind::kGlu, M, K, 2 * F, x, w_gate_up, {nullptr, sa.out}, s);
+  const Way way = way_of(M, K, 2 * F, StreamKind::kGlu, part, &few, &plan);
+  if (way == Way::kFew) return launch_few<false, true>(StreamKind::kGlu, few, M, K, 2 * F, x, w_gate_up, qa, sa, part, s);
+  if (way == Way::kStream) return launch_proj_stream(StreamKind::kGlu, M, K, 2 * F, x, w_gate_up, {nullptr, sa.out}, s);
   if (plan.ks > 1) return launch_splitk<false, true>(M, K, 2 * F, plan, x, w_gate_up, qa, sa, part, s);
   return dispatch<false, true>(M, K, 2 * F, x, w_gate_up, qa, sa, s);
 }

@@ -1,4 +1,5 @@
-// The projections around the attention for up to 32 tokens: streams of the weight matrix.
+// The projections around the attention for up to 16 tokens (32 where proj_few.hip has no division of the rows):
+// streams of the weight matrix.
 //
 // With so few tokens a projection is its weights read once from HBM and next to no arithmetic.  What
 // counts is that every CU has enough bytes in flight all the time and that nothing else is launched:
@@ -277,24 +278,13 @@ hipError_t dispatch(int M, int K, int N, const void *hidden, const void *weight,
 //   3584 x 37888  46 / 49 / 56 (gated)   60 / 60 / 62
 //   512 x 16384   9 / 10 / 15         12 / 12 / 12
 //   8192 x 2048   12.4 / 13.8 / 17.2  19.5 / 19.3 / 19.3
-// Up to 16 tokens everywhere.  Beyond, only where the tiles either fit the CUs at once or are many: a second
-// tile on some CUs costs a whole round (288 tiles, 3584 x 4608).  Many tiles pay where their weights come from
-// memory in any case, from about 120 MB on (2048 x 24576: 28 both; 3584 x 18432: 32 to 34 against 37 to 39).
-// Few tiles of long rows: a workgroup reads its tokens along with the weights, and the time is that of one
-// workgroup's K x (16 + tokens) whatever the rows, while the split over K has every CU at work.  Up to
-// K = 8192 the stream is ahead (8192 x 256: 16 against 17 at 32 tokens), then up to 24 tokens for 2048 rows and
-// more (12288 x 2048 23 both, x 1024 22 against 21), and at 32 tokens with 120 MB again.
-// Where K is not split (no workspace), a workgroup per 256 rows is far behind whatever K is (18944 x 1024, 32
-// tokens: 34 against 207; 2048 x 16384 gated: 22 against 31), except for many short rows (1024 x 32768: 25
-// against 22).
+// Up to 16 tokens everywhere.  From 17 on proj_few.hip takes all but weights of more than 40960 rows and many short
+// gated rows; of those the stream takes what comes from memory in any case, from about 120 MB on (2048 x 24576, 32
+// tokens: 28 both; 3584 x 18432: 32 to 34 against 37 to 39), and, where K is not split (no workspace), all but the
+// shortest (2048 x 16384 gated: 22 against 31; 1024 x 32768: 25 against 22).
 bool proj_stream_takes(int32_t M, int32_t K, int32_t N, bool split) {
-  const int tiles = (N + 15) / 16;
   if (M > 32 || K % 64 || K / 64 < kWaves || (int64_t)K * 64 >= ((int64_t)1 << 31)) return false;
-  if (M <= 16) return true;
-  const int64_t weights = (int64_t)K * N;
-  const bool large = weights >= 60 * 1000 * 1000;
-  if (tiles > 256) return tiles >= 1024 && (large || (!split && K >= 2048));
-  return !split || large || K <= 8192 || (M <= 24 && N >= 2048);
+  return M <= 16 || (int64_t)K * N >= 60 * 1000 * 1000 || (!split && K >= 2048);
 }
 
 hipError_t launch_proj_stream(StreamKind kind, int32_t M, int32_t K, int32_t N, const void *hidden, const void *weight,

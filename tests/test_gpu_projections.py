@@ -162,6 +162,28 @@ def test_gated_silu_projection_of_one_tile_of_tokens(hb, T, K, F, ws):
     test_gated_silu_projection(hb, T, K, F, ws)
 
 
+# All tokens in one tile: 64 and 128 tokens are its sizes; one K step and odd numbers of them (two go to a stage
+# where they can); tiles of 1, 2, 4, 6, 8 and 10 groups of 16 rows, ragged last ones, K whole and in parts
+@pytest.mark.parametrize("T,K,N", [(17, 64, 4), (33, 192, 100), (64, 576, 4100), (65, 1088, 4612), (127, 832, 9004), (128, 1536, 260),
+                                   (128, 9728, 516), (100, 128, 20484), (40, 256, 30724), (96, 320, 40960), (20, 576, 41000)])
+def test_output_projection_of_all_tokens_at_once(hb, T, K, N):
+    for ws in (False, True):
+        _out_case(hb, T, K, N, T % 2 == 1, ws)
+
+
+@pytest.mark.parametrize("T,K,Hq,Hkv,bias", [(17, 64, 1, 1, True), (64, 320, 5, 1, False), (65, 1536, 12, 4, True), (128, 192, 40, 8, True),
+                                             (100, 3584, 28, 4, False)])
+def test_qkv_projection_of_all_tokens_at_once(hb, T, K, Hq, Hkv, bias):
+    for ws in (False, True):
+        _qkv_case(hb, T, K, Hq, Hkv, bias, ws)
+
+
+@pytest.mark.parametrize("T,K,F", [(17, 64, 4), (64, 192, 4100), (65, 576, 8204), (128, 1088, 12300), (33, 2112, 16388), (128, 64, 20480)])
+def test_gated_silu_projection_of_all_tokens_at_once(hb, T, K, F):
+    for ws in (False, True):
+        test_gated_silu_projection(hb, T, K, F, ws)
+
+
 def _out_case(hb, T, K, N, res, with_workspace):
     g = torch.Generator().manual_seed(T + K + N)
     x = torch.randn((T, K), generator=g).to(torch.bfloat16)

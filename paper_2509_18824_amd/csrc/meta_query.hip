@@ -131,7 +131,7 @@ __global__ __launch_bounds__(kScoreThreads) void meta_scores_kernel(int S, int L
                                                         min(kTokPerGroup, S - tok0) * L * row_bytes, kBufferFlags);
   const auto a_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)a_fold, 0, 2 * rows_pad * row_bytes, kBufferFlags);
   const int r8 = lane >> 3;
-  auto swz = [](int r, int c) { return r * 8 + (c ^ ((r & 7) ^ ((r >> 3) & 1))); };
+  auto swz = [](int r, int c) { return r * 8 + (c ^ (r & 7)); };
   auto issue = [&](int t) {
     u32x4 *stage = meta_a_lds + (t & 1) * kScoreStage;
     const int k = (k_begin + min(t, steps - 1)) * 128;
@@ -139,7 +139,7 @@ __global__ __launch_bounds__(kScoreThreads) void meta_scores_kernel(int S, int L
     for (int i = 0; i < kScoreLoads; ++i) {
       constexpr int kFeatLoads = kScoreFeatRows / 8 / kScoreWaves;  // the first of them: features, then A
       const int row = (wave + (i < kFeatLoads ? i : i - kFeatLoads) * kScoreWaves) * 8 + r8;
-      const int src = row * row_bytes + ((lane & 7) ^ r8 ^ ((row >> 3) & 1)) * 16;
+      const int src = row * row_bytes + ((lane & 7) ^ r8) * 16;
       u32x4 *dst = stage + (wave + i * kScoreWaves) * 64;
       if (i < kFeatLoads) __builtin_amdgcn_raw_ptr_buffer_load_lds(f_rsrc, (lptr_t)dst, 16, src, k, 0, 0);
       else __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lptr_t)dst, 16, src, k, 0, 0);
@@ -433,13 +433,15 @@ __global__ __launch_bounds__(kMpThreads) void meta_project_kernel(
   const int steps = D / 64;
   const auto f_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(feats + (size_t)tok0 * L * dp), 0, frows * dp * 16, kBufferFlags);
   const int f_src = (wave * 8 + (lane >> 3)) * dp * 16 + ((lane & 7) ^ (((wave * 8 + (lane >> 3)) >> 1) & 7)) * 16;
-  auto issue_feats = [&](int kt) {
+  auto issue_feat = [&](int kt, int i) {
     const int k = min(kt, steps - 1);
     u32x4 *stage = lds_f + (kt % NS) * kStagePieces + wave * 64;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(f_rsrc, (lptr_t)(stage + i * kMpWaves * 64), 16,
+                                             f_src + i * kMpWaves * 8 * dp * 16, k * 128, 0, 0);
+  };
+  auto issue_feats = [&](int kt) {
 #pragma unroll
-    for (int i = 0; i < FI; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(f_rsrc, (lptr_t)(stage + i * kMpWaves * 64), 16,
-                                               f_src + i * kMpWaves * 8 * dp * 16, k * 128, 0, 0);
+    for (int i = 0; i < FI; ++i) issue_feat(kt, i);
   };
   issue_feats(0);
 
@@ -537,24 +539,21 @@ __global__ __launch_bounds__(kMpThreads) void meta_project_kernel(
     for (int nt = 0; nt < NT; ++nt) acc[q][nt] = (f32x4){0.f, 0.f, 0.f, 0.f};
 
   bf16x8 w[2][NT];
-  auto issue_weights = [&](int kt) {
+  auto issue_weight = [&](int kt, int ks, int nt) {
     const int k = min(kt, steps - 1);
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
-        w[ks][nt] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, lane * 16, (nt * steps + k) * 2048 + ks * 1024, 0));
-    __builtin_amdgcn_sched_barrier(0);
+    w[ks][nt] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, lane * 16, (nt * steps + k) * 2048 + ks * 1024, 0));
   };
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the count below starts here
   if (NS == 2) issue_feats(1);
   __builtin_amdgcn_sched_barrier(0);
-  issue_weights(0);
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) issue_weight(0, 0, nt);
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll 1
   for (int kt = 0; kt < steps; ++kt) {
-    // The slice's features have landed (newer loads: with two stages the next slice's features; the
-    // slice's weights); everybody is done with the previous mixed features.
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NS - 1) * FI + 2 * NT) : "memory");
+    // The slice's features have landed (newer loads: with two stages the next slice's features; the first
+    // half of the slice's weights); everybody is done with the previous mixed features.
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NS - 1) * FI + NT) : "memory");
     const uint32_t stage = (uint32_t)(kt % NS) * (uint32_t)(kStagePieces * 16);
 #pragma unroll
     for (int tt = 0; tt < kTok; ++tt) {
@@ -562,6 +561,13 @@ __global__ __launch_bounds__(kMpThreads) void meta_project_kernel(
 #pragma unroll
       for (int sub = 0; sub < kSub; ++sub) {
         const int g = TG == 16 ? sub : wave & 1;
+        // the second half of the slice's weights, in the first half of the mixing
+        constexpr int kSpread = kTok * kSub > 1 ? kTok * kSub / 2 : 1;
+        if (tt * kSub + sub < kSpread) {
+#pragma unroll
+          for (int nt = 0; nt < NT / kSpread; ++nt) issue_weight(kt, 1, (tt * kSub + sub) * (NT / kSpread) + nt);
+          __builtin_amdgcn_sched_barrier(0);
+        }
         bf16x8 a[2];
         tr_fragments(stage + (f_off[tt][0] ^ (64 * g)), stage + (f_off[tt][1] ^ (64 * g)), a);
 #pragma unroll
@@ -599,8 +605,9 @@ __global__ __launch_bounds__(kMpThreads) void meta_project_kernel(
     for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) asm volatile("" : "+v"(w[ks][nt]));
-    issue_feats(kt + NS);
-    __builtin_amdgcn_sched_barrier(0);
+    // The next slice's features and then the first half of its weights are requested among the matrix
+    // instructions: in front of them and behind them the address unit had every wavefront wait (1400 and 1300
+    // of 11000 clocks a slice at 16 tokens).
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
@@ -614,10 +621,16 @@ __global__ __launch_bounds__(kMpThreads) void meta_project_kernel(
         for (int nt = 0; nt < NT; ++nt) {
           acc[q][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ks][nt], hi, acc[q][nt], 0, 0, 0);
           acc[q][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ks][nt], lo, acc[q][nt], 0, 0, 0);
+          constexpr int kPairs = QT * NT;
+          const int n = q * NT + nt, loads = ks ? NT : FI;
+#pragma unroll
+          for (int i = n * loads / kPairs; i < (n + 1) * loads / kPairs; ++i) {
+            if (ks) issue_weight(kt + 1, 0, i);
+            else issue_feat(kt + NS, i);
+          }
+          __builtin_amdgcn_sched_barrier(0);
         }
       }
-    __builtin_amdgcn_sched_barrier(0);
-    issue_weights(kt + 1);
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   // lane (j16, kq) holds columns 16 nt + 4 kq .. + 3 of row j16

@@ -134,15 +134,18 @@ def _ptr(t: Optional[torch.Tensor]):
         return None
     if not t.is_contiguous():
         raise ValueError("tensors handed to libhb must be contiguous")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()  # the declared argument types convert it
 
 
-def _stream(stream) -> C.c_void_p:
+def _stream(stream) -> Optional[int]:
     if stream is None:
+        # the raw handle: 0.5 us, against 3.4 for is_available() and the object that current_stream() makes
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
         if not torch.cuda.is_available():
-            return C.c_void_p(0)  # only argument validation can succeed without a device
+            return None  # only argument validation can succeed without a device
         stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream)
+    return stream.cuda_stream
 
 
 def _dtype_code(t: torch.Tensor) -> int:

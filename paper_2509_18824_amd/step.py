@@ -127,11 +127,13 @@ class DraftTreeBuilder:
         if C <= 0:
             raise ValueError("unsupported K / T")
         self.C = C
-        self.cand_score = torch.zeros((B, C), dtype=torch.float32, device=device)
-        self.cand_token = torch.zeros((B, C), dtype=torch.int32, device=device)
+        # what starts at zero is cleared by one launch
+        zeros = torch.zeros(2 * B * (C + K), dtype=torch.int32, device=device).split([B * C, B * C, B * K, B * K])
+        self.cand_score = zeros[0].view(torch.float32).view(B, C)
+        self.cand_token = zeros[1].view(B, C)
         self.cand_parent = torch.full((B, C), -1, dtype=torch.int32, device=device)
-        self.frontier = torch.zeros((B, K), dtype=torch.int32, device=device)
-        self.frontier_slot = torch.zeros((B, K), dtype=torch.int32, device=device)
+        self.frontier = zeros[2].view(B, K)
+        self.frontier_slot = zeros[3].view(B, K)
 
     def grow(self, child_ids, child_logp):
         hb.hb_tree_grow(self.B, self.K, self.T, self.level, child_ids, child_logp, self.cand_score, self.cand_token,

@@ -12,10 +12,13 @@
 //                  parent's score + log-probability), the K best of them become the frontier.
 //   tree_finalize  re-ranking of all candidates, the N - 1 best are kept and numbered in
 //                  candidate order (parents first); parent, token, depth, ancestor mask per node.
-// Ranking is by counting: rank(c) = number of candidates that beat c, where a beats c iff its
-// score is higher, or equal with a lower candidate index: a strict total order, so the ranks are
-// a permutation and every output slot is written exactly once.
+// Candidate a beats c iff its score is higher, or equal with a lower candidate index: a strict total
+// order, held in one 64-bit key.  A level's ranking is by counting (the number of keys above), so the ranks
+// are a permutation and every output slot is written exactly once; the re-ranking needs no order, only who
+// is among the best.
 #include "hb_internal.h"
+
+#include <type_traits>
 
 namespace hb {
 
@@ -82,27 +85,29 @@ struct Partial {  // one per (row, chunk), followed in memory by k keys
   float max, sum;
 };
 
-// Logits per chunk: 64 per thread, held in registers.  Always the most a workgroup holds: it takes 5
+// Logits per chunk: 64 per thread.  Always the most a workgroup holds: it takes 5
 // to 10 us whatever its chunk, and every chunk adds k winners to the merge, whose ranking is quadratic
 // (16 rows x 152064 in chunks of 3072: 33 us, of 16384: 13 us).
 constexpr int kChunk = 16384;
 constexpr int kPerThread = kChunk / kThreads;
 constexpr int kListCap = 2048;              // candidates that pass the threshold
 
-// Pass 1 of the top-k: one workgroup per (chunk, row).  The chunk goes from memory straight into
-// registers (every load is in flight before the first value is used).  The k best entries are
-// found without sorting: a threshold T that at least k values of the chunk reach (from the
+// Pass 1 of the top-k: one workgroup per (chunk, row).  A thread's 16-byte pieces stream through registers,
+// eight in flight; each gives its maximum and its share of the sum of exponentials as it arrives, and only the
+// maxima are kept, so that eight wavefronts fit a SIMD and every chunk of a level is resident at once.  The k
+// best entries are found without sorting: a threshold T that at least k values of the chunk reach (from the
 // per-thread maxima, see below) is a lower bound of the chunk's k-th largest value, so only values
-// >= T can be among the k best; those few are collected in LDS (as order-preserving keys) and
-// the k best picked there by counting ranks.
+// >= T can be among the k best; the few pieces that reach it are read again, those values collected in
+// LDS (as order-preserving keys) and the k best picked there by counting ranks.
 // Many equal values can let more pass than the list holds; then k rounds of a workgroup-wide
 // maximum run over the chunk instead (same result, slower).
 //
-// What bounds it is vector instruction issue, and code that has to stay in the instruction cache.
-// The path from registers works by 16-byte pieces, without NaN tests and without a branch per value: a
-// NaN or an infinity shows in the sum of exponentials, or nothing is above -inf, and such a chunk is done
-// again with a test per value; so is one of too few values for a threshold.  160 rows x 152064 float32 with the merge 33.7 -> 28.8 us (24 us = 4 TB/s in this pass), 16 rows 33 -> 13 us,
-// one row 42 -> 11 us (those two mostly by larger chunks).
+// What bounds it: memory (from 1 to 160 rows 96 MB take 17 us more), and the chain behind the last load, with
+// the merge's launch 10 us.  No NaN tests and no branch per value: a NaN or an infinity shows in the sum of
+// exponentials, or nothing is above -inf, and such a chunk is done again with a test per value; so is one of
+// too few values for a threshold.  With the merge, against whole chunks held in registers (five
+// workgroups per CU, the exponentials behind a pass for the maximum): 160 rows x 152064 float32 28.7 -> 27.3 us,
+// bfloat16 23.8 -> 21.8, 160 x 50257 16.8 -> 15.2, 16 x 152064 13.7 -> 12.1.
 struct ChunkShared {
   unsigned long long red[kThreads / 64];
   float fred[kThreads / 64];
@@ -113,22 +118,21 @@ struct ChunkShared {
 };
 
 // Threshold T with at least k values >= T in the chunk: every wavefront takes the k-th largest
-// of its 64 lane maxima (a lane counts the maxima strictly above its own, lane by lane through
-// readlane; the smallest maximum with fewer than k above it is the k-th largest), which k of its
+// of its 64 lane maxima, rounded down to its upper 16 bits (found bit by bit, a ballot each: a
+// quarter of the vector instructions of counting every lane against every other), which k of its
 // own values reach; T is the largest of the wavefronts' thresholds.  A wavefront with fewer
 // than k lanes holding values (`has`) sets no threshold; if none does, everything passes.
 __device__ __forceinline__ float chunk_threshold(float mt, bool has, int k, float *thr_w) {
-  int above = 0;
+  const uint32_t u = __float_as_uint(mt);
+  const uint32_t key = has ? ((u & 0x80000000u) ? ~u : (u | 0x80000000u)) : 0u;
+  uint32_t t = 0;
 #pragma unroll
-  for (int l = 0; l < 64; ++l) {
-    const float other = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mt), l));
-    above += other > mt ? 1 : 0;
+  for (int bit = 31; bit >= 16; --bit) {
+    const uint32_t up = t | (1u << bit);
+    t = __popcll(__ballot(key >= up)) >= k ? up : t;
   }
-  const int holders = __popcll(__ballot(has));
-  float tw = (has && above < k) ? mt : __builtin_huge_valf();
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) tw = fminf(tw, __shfl_xor(tw, off, 64));
-  if (holders < k) tw = -__builtin_huge_valf();
+  float tw = __uint_as_float((t & 0x80000000u) ? (t & 0x7fffffffu) : ~t);
+  if (t <= 0x007fffffu) tw = -__builtin_huge_valf();  // at or below the key of -inf, or too few lanes
   if ((threadIdx.x & 63) == 0) thr_w[threadIdx.x >> 6] = tw;
   __syncthreads();
   return fmaxf(fmaxf(thr_w[0], thr_w[1]), fmaxf(thr_w[2], thr_w[3]));
@@ -141,6 +145,7 @@ __device__ __forceinline__ float chunk_threshold(float mt, bool has, int k, floa
 template <typename T>
 __device__ __forceinline__ bool fast_chunk(const T *row, int v0, int n, int k, ChunkShared &sh, float &mx, float &sum) {
   constexpr int PER = 16 / (int)sizeof(T), kPieces = kPerThread / PER;
+  constexpr int kAhead = kPieces < 8 ? kPieces : 8;  // pieces in flight
   const int tid = threadIdx.x;
   const int head = min(n, (int)((0u - (uint32_t)(uintptr_t)row) & 15u) / (int)sizeof(T));
   const int n_full = (n - head) / PER, rest = n - n_full * PER;  // rest: head and tail together
@@ -148,11 +153,7 @@ __device__ __forceinline__ bool fast_chunk(const T *row, int v0, int n, int k, C
   const float ninf = -__builtin_huge_valf();
   const int single = tid < head ? tid : tid + n_full * PER;      // this thread's value outside the pieces
   const float tail = tid < rest ? load_f32<T>(row + single) : ninf;
-  u32x4 w[kPieces];
-  if (n_full > 0) {
-#pragma unroll
-    for (int q = 0; q < kPieces; ++q) w[q] = src[min(q * kThreads + tid, n_full - 1)];
-  }
+  auto load = [&](int q) { return src[min(q * kThreads + tid, n_full - 1)]; };
   if (tid == 0) sh.list_n = 0;
   auto value = [](const u32x4 &v, int e) {
     if (sizeof(T) == 4) return __uint_as_float(v[e]);
@@ -163,36 +164,67 @@ __device__ __forceinline__ bool fast_chunk(const T *row, int v0, int n, int k, C
     asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "v"(y), "v"(z));
     return r;
   };
-  float pm[kPieces], mt = tail;
+  // s: this thread's sum of 2^(x log2 e - ref), with no pass for the maximum before it.  ref is the running
+  // maximum as a whole number: a change of it scales s by a power of two, and what counts in the sum has a
+  // small exponent that rounds once.
+  const float c1 = 1.4426950408889634f;
+  float pm[kPieces], mt = ninf, s = 0.f, ref = -3e38f;
+  auto scaled = [](float x, float by) { return ldexpf(x, (int)__builtin_amdgcn_fmed3f(by, -400.f, 0.f)); };
+  auto follow = [&](float m) {
+    const float r = fmaxf(ref, rintf(m * c1));
+    s = scaled(s, ref - r);
+    ref = r;
+  };
+  // whole: every piece is there in part at least, and no branch stands between a load and the wait for it
+  auto pass = [&](auto whole) {
+    u32x4 w[kAhead];
 #pragma unroll
-  for (int q = 0; q < kPieces; ++q) {
-    pm[q] = ninf;
-    if (q * kThreads < n_full) {
-      float m = max3(value(w[q], 0), value(w[q], 1), value(w[q], 2));
-      m = PER == 4 ? max3(m, m, value(w[q], 3)) : max3(m, value(w[q], 3), value(w[q], 4));
-      if (PER == 8) m = max3(max3(m, value(w[q], 5 % PER), value(w[q], 6 % PER)), m, value(w[q], 7 % PER));
-      pm[q] = q * kThreads + tid < n_full ? m : ninf;
-      mt = max3(mt, mt, pm[q]);
+    for (int q = 0; q < kAhead; ++q) w[q] = load(q);
+#pragma unroll
+    for (int q = 0; q < kPieces; ++q) {
+      pm[q] = ninf;
+      if (whole || q * kThreads < n_full) {
+        const u32x4 v = w[q % kAhead];
+        const bool mine = (whole && q < kPieces - 1) || q * kThreads + tid < n_full;
+        float m = max3(value(v, 0), value(v, 1), value(v, 2));
+        m = PER == 4 ? max3(m, m, value(v, 3)) : max3(m, value(v, 3), value(v, 4));
+        if (PER == 8) m = max3(max3(m, value(v, 5 % PER), value(v, 6 % PER)), m, value(v, 7 % PER));
+        pm[q] = mine ? m : ninf;
+        mt = max3(mt, mt, pm[q]);
+        follow(pm[q]);
+        float p0 = 0.f, p1 = 0.f;
+#pragma unroll
+        for (int e = 0; e < PER; ++e) ((e & 1) ? p1 : p0) += __builtin_amdgcn_exp2f(fmaf(value(v, e), c1, -ref));
+        s += mine ? p0 + p1 : 0.f;
+        if (q + kAhead < kPieces) w[q % kAhead] = load(q + kAhead);
+      }
     }
+  };
+  if (n_full > (kPieces - 1) * kThreads) {
+    pass(std::true_type{});
+  } else if (n_full > 0) {
+    pass(std::false_type{});
+  } else {
+#pragma unroll
+    for (int q = 0; q < kPieces; ++q) pm[q] = ninf;
   }
-  mx = wg_max_f(mt, sh.fred);
+  mt = max3(mt, mt, tail);
+  follow(tail);
+  s += __builtin_amdgcn_exp2f(fmaf(tail, c1, -ref));
+  float mw = mt;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) mw = fmaxf(mw, __shfl_xor(mw, off, 64));
+  if ((tid & 63) == 0) sh.fred[tid >> 6] = mw;  // published by the threshold's barrier
+  const float thr = chunk_threshold(mt, tid < n_full || tid < rest, k, sh.thr_w);
+  mx = fmaxf(fmaxf(sh.fred[0], sh.fred[1]), fmaxf(sh.fred[2], sh.fred[3]));
   // Nothing above -inf, or a signalling NaN: v_max3 makes it a quiet one, and the next maximum then
   // forgets the values beside it.
   if (!(mx > ninf)) return false;
-  const float thr = chunk_threshold(mt, tid < n_full || tid < rest, k, sh.thr_w);
-  const float c1 = 1.4426950408889634f, c0 = -mx * 1.4426950408889634f;
-  float s = __builtin_amdgcn_exp2f(fmaf(tail, c1, c0));
+  const float top = rintf(mx * c1);  // the largest ref
+  s = scaled(s, ref - top);
   uint32_t reach = 0;  // pieces with a value that reaches the threshold
 #pragma unroll
-  for (int q = 0; q < kPieces; ++q) {
-    if (q * kThreads < n_full) {
-      float p0 = 0.f, p1 = 0.f;
-#pragma unroll
-      for (int e = 0; e < PER; ++e) ((e & 1) ? p1 : p0) += __builtin_amdgcn_exp2f(fmaf(value(w[q], e), c1, c0));
-      s += q * kThreads + tid < n_full ? p0 + p1 : 0.f;
-      reach |= q * kThreads + tid < n_full && pm[q] >= thr ? 1u << q : 0u;
-    }
-  }
+  for (int q = 0; q < kPieces; ++q) reach |= q * kThreads + tid < n_full && pm[q] >= thr ? 1u << q : 0u;
   auto offer = [&](float x, int pos) {
     if (x >= thr) {
       const int at = atomicAdd(&sh.list_n, 1);
@@ -211,11 +243,10 @@ __device__ __forceinline__ bool fast_chunk(const T *row, int v0, int n, int k, C
       offer(__uint_as_float(u), head + at * PER + e);
     }
   }
-  sum = wg_sum_f(s, sh.fred);  // its barriers also publish list and list_n
+  sum = wg_sum_f(s, sh.fred) * __builtin_amdgcn_exp2f(-fmaf(mx, c1, -top));  // the barriers also publish list and list_n
   const int cnt = sh.list_n;
   // The maximum's own exponential is 1.  A maximum near the type's limits (a mask of the lowest value)
-  // leaves the range when scaled, in c0, and too few values for a threshold may share an offset that c0
-  // rounds off: any_chunk takes the differences first.  Tested here, where registers are free again.
+  // leaves the range when scaled: any_chunk takes the differences first.  Tested here, where registers are free again.
   if (!(sum >= 0.5f && sum < __builtin_huge_valf()) || cnt > kListCap || !(thr > ninf)) return false;
   rank_select(sh.list, cnt, k, sh.win);
   return true;
@@ -347,9 +378,6 @@ __global__ __launch_bounds__(kThreads) void topk_merge_kernel(int V, int k, int 
   }
 }
 
-// score order: a beats b iff higher score, or equal score and lower index (no NaN in s[])
-__device__ __forceinline__ bool beats(float sa, int a, float sb, int b) { return sa > sb || (sa == sb && a < b); }
-
 __global__ __launch_bounds__(kThreads) void tree_grow_kernel(int K, int level, int C,
                                                              const int32_t *__restrict__ child_ids,
                                                              const float *__restrict__ child_logp,
@@ -358,7 +386,7 @@ __global__ __launch_bounds__(kThreads) void tree_grow_kernel(int K, int level, i
                                                              int32_t *__restrict__ cand_parent,
                                                              int32_t *__restrict__ frontier,
                                                              int32_t *__restrict__ frontier_slot) {
-  __shared__ float s_new[kMaxTopK * kMaxTopK];
+  __shared__ unsigned long long keys[kMaxTopK * kMaxTopK];
   const int b = blockIdx.x;
   const int F = level == 0 ? 1 : K;
   const int n_new = F * K;
@@ -370,7 +398,7 @@ __global__ __launch_bounds__(kThreads) void tree_grow_kernel(int K, int level, i
     const float base = par < 0 ? 0.f : cand_score[(size_t)b * C + par];
     float s = base + child_logp[((size_t)b * F) * K + t];
     if (!(s == s)) s = -__builtin_huge_valf();
-    s_new[t] = s;
+    keys[t] = sel_key(s, (uint32_t)t);
     cand_score[(size_t)b * C + first + t] = s;
     cand_token[(size_t)b * C + first + t] = child_ids[((size_t)b * F) * K + t];
     cand_parent[(size_t)b * C + first + t] = par;
@@ -379,10 +407,10 @@ __global__ __launch_bounds__(kThreads) void tree_grow_kernel(int K, int level, i
   for (int t = threadIdx.x; t < n_new; t += kThreads) {
     int rank = t;
     if (level > 0) {
-      const float s = s_new[t];
+      const unsigned long long mine = keys[t];
       rank = 0;
 #pragma unroll 8
-      for (int u = 0; u < n_new; ++u) rank += beats(s_new[u], u, s, t) ? 1 : 0;
+      for (int u = 0; u < n_new; ++u) rank += keys[u] > mine ? 1 : 0;
     }
     if (rank < K) {
       frontier[(size_t)b * K + rank] = first + t;
@@ -391,77 +419,108 @@ __global__ __launch_bounds__(kThreads) void tree_grow_kernel(int K, int level, i
   }
 }
 
-constexpr int kFinalThreads = 1024;  // one workgroup per sequence: sixteen wavefronts share the C^2 / 2 comparisons
-
-__global__ __launch_bounds__(kFinalThreads) void tree_finalize_kernel(
+// One workgroup of NW wavefronts per sequence; a thread keeps a run of up to P candidates in registers, in
+// order.  The keep best are those above the keep-th largest score, found bit by bit (a ballot per bit and
+// register), and the first of those equal to it: C comparisons per bit instead of C^2 by counting.  One
+// wavefront, and so no barrier, as long as the candidates fit it: what bounds it is the chain of 32 counts
+// behind the loads.  410 candidates 13.3 -> 8.0 us a launch, 784 32.7 -> 13,
+// 3875 688 -> 17.
+template <int NW, int P>
+__global__ __launch_bounds__(64 * NW) void tree_finalize_kernel(
     int B, int C, int n, const float *__restrict__ cand_score, const int32_t *__restrict__ cand_token,
     const int32_t *__restrict__ cand_parent, const int32_t *__restrict__ root_token, int32_t *__restrict__ node_offset,
     int32_t *__restrict__ parent, int32_t *__restrict__ draft_ids, int32_t *__restrict__ depth,
     unsigned long long *__restrict__ anc, int32_t *__restrict__ node_cand, float *__restrict__ node_score) {
-  extern __shared__ unsigned char dyn[];
-  float *s = (float *)dyn;                 // C scores
-  int16_t *node_of = (int16_t *)(s + C);   // C: node index of a kept candidate, 0 otherwise
-  unsigned char *kept = (unsigned char *)(node_of + C);  // C: the candidate is among the n - 1 best
-  __shared__ int wave_kept[kFinalThreads / 64];
+  __shared__ int16_t node_of[64 * NW * P];  // node index of a kept candidate, 0 otherwise
+  __shared__ int counts[2][NW];
   __shared__ int spar[64];
-  const int b = blockIdx.x, tid = threadIdx.x;
+  const int b = blockIdx.x, tid = threadIdx.x, wave = tid >> 6;
   const int keep = n - 1;
-  for (int c = tid; c < C; c += kFinalThreads) {
-    float x = cand_score[(size_t)b * C + c];
-    s[c] = (x == x) ? x : -__builtin_huge_valf();
+  const int per = (C + 64 * NW - 1) / (64 * NW), c0 = tid * per;
+  float score[P];
+  int32_t tok[P], par[P];
+  uint32_t key[P];  // ordered like the scores, -0 as +0, NaN as -inf; 0: none
+#pragma unroll
+  for (int i = 0; i < P; ++i) {
+    const int c = min(c0 + i, C - 1);
+    score[i] = cand_score[(size_t)b * C + c];
+    tok[i] = cand_token[(size_t)b * C + c];
+    par[i] = cand_parent[(size_t)b * C + c];
   }
-  __syncthreads();
-  // ranks: four neighbouring lanes share a candidate, each counts a quarter of the others
-  const int sub = tid & 3;
-  constexpr int kPerPass = kFinalThreads / 4;
-  const int c_end = (C + kPerPass - 1) / kPerPass * kPerPass;  // the same trip count for every lane
-  for (int c = tid >> 2; c < c_end; c += kPerPass) {
-    const bool live = c < C;
-    const float sc = live ? s[c] : 0.f;
-    int rank = 0;
-    if (live) {
-#pragma unroll 8
-      for (int u = sub; u < C; u += 4) rank += beats(s[u], u, sc, c) ? 1 : 0;
-    }
-    rank += __shfl_xor(rank, 1, 64);
-    rank += __shfl_xor(rank, 2, 64);
-    if (live && sub == 0) kept[c] = rank < keep ? 1 : 0;
+#pragma unroll
+  for (int i = 0; i < P; ++i) {
+    if (!(score[i] == score[i])) score[i] = -__builtin_huge_valf();
+    key[i] = i < per && c0 + i < C ? (uint32_t)(sel_key(score[i], 0u) >> 32) : 0u;
   }
-  __syncthreads();
-  // each thread owns a contiguous run of candidates, so that kept candidates are counted in order
-  const int per = (C + kFinalThreads - 1) / kFinalThreads;
-  const int c0 = min(C, tid * per), c1 = min(C, c0 + per);
-  int cnt = 0;
-  for (int c = c0; c < c1; ++c) cnt += kept[c];
-  // exclusive prefix count over the threads: inside the wavefront by shifts, then the wavefronts before
-  int incl = cnt;
+  // the sum over the workgroup of a wavefront's count; slots alternate, so one barrier each is enough
+  auto total = [&](int mine, int slot) {
+    if (NW == 1) return mine;
+    if ((tid & 63) == 0) counts[slot][wave] = mine;
+    __syncthreads();
+    int sum = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) sum += counts[slot][w];
+    return sum;
+  };
+  auto at_least = [&](uint32_t t) {
+    int cnt = 0;
+#pragma unroll
+    for (int i = 0; i < P; ++i) cnt += __popcll(__ballot(key[i] >= t));
+    return cnt;
+  };
+  uint32_t last = 0;  // the keep-th largest key
+#pragma unroll 1
+  for (int bit = 31; bit >= 0; --bit) {
+    const uint32_t up = last | (1u << bit);
+    if (total(at_least(up), bit & 1) >= keep) last = up;
+  }
+  // before this thread, candidates above the last one kept and (upper half) equal to it: C <= 4096
+  int mine = 0;
+#pragma unroll
+  for (int i = 0; i < P; ++i) mine += (key[i] > last ? 1 : 0) + (key[i] == last ? 1 << 16 : 0);
+  int before = mine;
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
-    const int y = __shfl_up(incl, off, 64);
-    if ((tid & 63) >= off) incl += y;
+    const int y = __shfl_up(before, off, 64);
+    if ((tid & 63) >= off) before += y;
   }
-  if ((tid & 63) == 63) wave_kept[tid >> 6] = incl;
-  __syncthreads();
-  int before = incl - cnt;
-  for (int w = 0; w < (tid >> 6); ++w) before += wave_kept[w];
-  for (int c = c0; c < c1; ++c) {
-    const bool k = kept[c] != 0;
-    node_of[c] = k ? (int16_t)(1 + before) : (int16_t)0;
-    before += k ? 1 : 0;
+  int all = __shfl(before, 63, 64);
+  before -= mine;
+  if (NW > 1) {
+    __syncthreads();
+    if ((tid & 63) == 0) counts[0][wave] = all;
+    __syncthreads();
+    all = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      if (w < wave) before += counts[0][w];
+      all += counts[0][w];
+    }
+  }
+  const int ties = keep - (all & 0xffff);
+  int node[P];
+  int above = before & 0xffff, equal = before >> 16;
+#pragma unroll
+  for (int i = 0; i < P; ++i) {
+    const bool gt = key[i] > last, eq = key[i] == last;
+    node[i] = gt || (eq && equal < ties) ? 1 + above + min(equal, ties) : 0;
+    above += gt ? 1 : 0;
+    equal += eq ? 1 : 0;
+    if (i < per && c0 + i < C) node_of[c0 + i] = (int16_t)node[i];
   }
   __syncthreads();
   const size_t o = (size_t)b * n;
-  for (int c = c0; c < c1; ++c) {
-    const int i = node_of[c];
-    if (i == 0) continue;
-    int pc = cand_parent[(size_t)b * C + c];
-    pc = pc < 0 ? -1 : (pc >= c ? -1 : pc);  // a parent comes before its children, else: the root
+#pragma unroll
+  for (int i = 0; i < P; ++i) {
+    const int c = c0 + i, at = node[i];
+    if (at == 0) continue;
+    const int pc = par[i] < 0 || par[i] >= c ? -1 : par[i];  // a parent comes before its children, else: the root
     const int p = pc < 0 ? 0 : node_of[pc];  // a dropped parent (malformed scores) also maps to the root
-    spar[i] = p;
-    parent[o + i] = p;
-    draft_ids[o + i] = cand_token[(size_t)b * C + c];
-    node_cand[o + i] = c;
-    node_score[o + i] = s[c];
+    spar[at] = p;
+    parent[o + at] = p;
+    draft_ids[o + at] = tok[i];
+    node_cand[o + at] = c;
+    node_score[o + at] = score[i];
   }
   if (tid == 0) {
     spar[0] = -1;
@@ -525,9 +584,9 @@ hipError_t launch_tree_finalize(int32_t B, int32_t C, int32_t n, const float *ca
                                 const int32_t *cand_parent, const int32_t *root_token, int32_t *node_offset,
                                 int32_t *parent, int32_t *draft_ids, int32_t *depth, unsigned long long *anc,
                                 int32_t *node_cand, float *node_score, hipStream_t s) {
-  const size_t lds = (size_t)C * (sizeof(float) + sizeof(int16_t) + 1) + 16;
-  tree_finalize_kernel<<<B, kFinalThreads, lds, s>>>(B, C, n, cand_score, cand_token, cand_parent, root_token, node_offset,
-                                                parent, draft_ids, depth, anc, node_cand, node_score);
+  auto kern = C <= 512 ? tree_finalize_kernel<1, 8> : tree_finalize_kernel<4, 16>;
+  kern<<<B, C <= 512 ? 64 : 256, 0, s>>>(B, C, n, cand_score, cand_token, cand_parent, root_token, node_offset, parent, draft_ids,
+                                         depth, anc, node_cand, node_score);
   return hipGetLastError();
 }
 

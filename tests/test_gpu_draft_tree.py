@@ -158,6 +158,28 @@ def test_topk_few_values_of_large_magnitude(S, V):
     assert np.abs(logp.cpu().numpy() - rlogp).max() <= 2.0 ** -12 + LOGP_TOL
 
 
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("V", [3000, 16384, 40001])
+def test_topk_values_that_leave_the_first_ones_behind(S, V, bf16):
+    """The exponentials' reference starts with a thread's first values: masks there (-inf and the type's lowest),
+    ramps that rise or fall by hundreds from piece to piece, a common offset; whole and partial chunks."""
+    x = W.make_draft_logits(95, 6, V)
+    x[0, :V // 3] = -np.inf
+    x[1, :V // 3] = float(torch.finfo(torch.bfloat16 if bf16 else torch.float32).min)
+    x[2] = np.linspace(-5000, 5000, V)
+    x[3] = np.linspace(5000, -5000, V)
+    x[4] -= np.float32(30000.0)
+    x[5, V // 2:] += np.float32(100.0)
+    t = torch.from_numpy(x).cuda().to(torch.bfloat16 if bf16 else torch.float32)
+    x = t.float().cpu().numpy()
+    ids, logp = S.topk_logprob(t, 10)
+    rid, rlogp = topk_logprob_ref(x, 10)
+    assert np.array_equal(ids.cpu().numpy(), rid)
+    # lse rounds at the maximum's size: half a unit of 2^-11 below 8192, of 2^-9 at 30000
+    tol = LOGP_TOL + np.array([0, 0, 2.0 ** -12, 2.0 ** -12, 2.0 ** -10, 0])[:, None]
+    assert (np.abs(logp.cpu().numpy() - rlogp) <= tol).all(), np.abs(logp.cpu().numpy() - rlogp).max(1)
+
+
 def test_topk_full_vocabulary_every_row_of_a_level(S):
     """The shape of one level of the batch-16 workload: 160 rows (16 sequences x 10 frontier
     nodes) over the vocabulary of 152064, float32; and the root level's 16 rows in bf16."""
@@ -225,6 +247,15 @@ def test_tree_shapes_and_edges(S, B, K, T, N):
 def test_tree_with_equal_scores(S):
     _grow_both(S, 2, 3, 3, 9, 0, seed=0, uniform=True)
     _grow_both(S, 4, 6, 4, 48, 3000, seed=9, ties=True)
+
+
+@pytest.mark.parametrize("B,K,T,N", [(2, 22, 2, 64), (2, 16, 3, 64), (3, 8, 9, 33), (1, 31, 5, 64), (1, 8, 64, 2), (2, 2, 64, 64)])
+def test_trees_from_many_candidates(S, B, K, T, N):
+    """506 candidates (one wavefront), 528 and 520 (four), 3875 and 4040 (most of what they hold), chains of 64
+    levels; distinct scores, ties, and all equal."""
+    _grow_both(S, B, K, T, N, 3000, seed=K + T)
+    _grow_both(S, B, K, T, N, 3000, seed=K + T, ties=True)
+    _grow_both(S, B, K, T, N, 0, seed=0, uniform=True)
 
 
 def test_tree_build_replays_from_a_hip_graph(S):

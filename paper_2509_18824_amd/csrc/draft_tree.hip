@@ -423,8 +423,7 @@ __global__ __launch_bounds__(kThreads) void tree_grow_kernel(int K, int level, i
 // order.  The keep best are those above the keep-th largest score, found bit by bit (a ballot per bit and
 // register), and the first of those equal to it: C comparisons per bit instead of C^2 by counting.  One
 // wavefront, and so no barrier, as long as the candidates fit it: what bounds it is the chain of 32 counts
-// behind the loads.  410 candidates 13.3 -> 8.0 us a launch, 784 32.7 -> 13,
-// 3875 688 -> 17.
+// behind the loads.  410 candidates 13.3 -> 8.0 us a launch, 784 32.7 -> 13, 3875 688 -> 17.
 template <int NW, int P>
 __global__ __launch_bounds__(64 * NW) void tree_finalize_kernel(
     int B, int C, int n, const float *__restrict__ cand_score, const int32_t *__restrict__ cand_token,

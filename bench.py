@@ -31,10 +31,10 @@ PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA, published
 # csrc/mfma_gemm_tile.inc (the tile loop the kernel includes); anything else reports null.
 # "tree": the 960-row launch of the headline step; "chain8": the 128-row launch of the chain run.
 LMHEAD_TRAFFIC = {
-    "5590a872aae69250": {
-        "tree": {"fetch_bytes": 1.8424e9, "write_bytes": 1.9e5, "bytes": 1.8426e9,
+    "de142ddb09a2ab21": {
+        "tree": {"fetch_bytes": 1.8467e9, "write_bytes": 2.1e5, "bytes": 1.8469e9,
                  "algorithmic_bytes": 152064 * 3584 * 2 + 960 * 3584 * 2},
-        "chain8": {"fetch_bytes": 1.1139e9, "write_bytes": 3.5e4, "bytes": 1.1140e9,
+        "chain8": {"fetch_bytes": 1.1142e9, "write_bytes": 4.2e4, "bytes": 1.1142e9,
                    "algorithmic_bytes": 152064 * 3584 * 2 + 128 * 3584 * 2},
     },
 }

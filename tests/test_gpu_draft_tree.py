@@ -180,6 +180,37 @@ def test_topk_values_that_leave_the_first_ones_behind(S, V, bf16):
     assert (np.abs(logp.cpu().numpy() - rlogp) <= tol).all(), np.abs(logp.cpu().numpy() - rlogp).max(1)
 
 
+def _topk_us(S, x, k=10):
+    """Shortest of five means of twenty calls."""
+    ids, logp = S.topk_logprob(x, k)
+    best = float("inf")
+    for _ in range(5):
+        start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        start.record()
+        for _ in range(20):
+            S.topk_logprob(x, k)
+        end.record()
+        torch.cuda.synchronize()
+        best = min(best, start.elapsed_time(end) / 20 * 1e3)
+    return best, ids, logp
+
+
+@pytest.mark.parametrize("offset", [1000.0, 10000.0, -30000.0])
+def test_topk_takes_no_longer_for_a_common_offset(S, offset):
+    """Distinct float32 logits that share an offset keep to the path of the plain ones: a threshold of 16 bits,
+    which everything reaches, took 2 to 8 times as long.  Twice leaves room for the clock."""
+    g = torch.Generator(device="cuda").manual_seed(7)
+    x = torch.randn((160, 152064), generator=g, device="cuda")
+    plain, _, _ = _topk_us(S, x)
+    x += offset
+    shifted, ids, logp = _topk_us(S, x)
+    assert torch.equal(x.gather(1, ids.long()), torch.topk(x, 10, dim=1).values)
+    # lse and logit - lse round once each at the offset's size
+    lse = torch.logsumexp(x.double(), 1, keepdim=True)
+    assert (logp.double() - (x.double().gather(1, ids.long()) - lse)).abs().max() <= abs(offset) * 2.0 ** -23 + LOGP_TOL
+    assert shifted <= 2.0 * plain, (plain, shifted)
+
+
 def test_topk_full_vocabulary_every_row_of_a_level(S):
     """The shape of one level of the batch-16 workload: 160 rows (16 sequences x 10 frontier
     nodes) over the vocabulary of 152064, float32; and the root level's 16 rows in bf16."""

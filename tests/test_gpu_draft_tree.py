@@ -211,6 +211,47 @@ def test_topk_takes_no_longer_for_a_common_offset(S, offset):
     assert shifted <= 2.0 * plain, (plain, shifted)
 
 
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("mask", [-65504.0, -1e9, -1e10, -1e20, -1e30, -2e38])
+def test_topk_takes_no_longer_for_scattered_masks(S, mask, bf16):
+    """Nine tenths of the tokens at a large negative value, so that many threads begin with nothing else: the
+    exponentials' reference must not become an infinity there (2.3 times as long).  1.6 leaves room for the clock."""
+    g = torch.Generator(device="cuda").manual_seed(8)
+    x = torch.randn((160, 152064), generator=g, device="cuda").to(torch.bfloat16 if bf16 else torch.float32)
+    drop = torch.rand(x.shape, generator=g, device="cuda") < 0.9
+    plain, _, _ = _topk_us(S, x.masked_fill(drop, float("-inf")))
+    x = x.masked_fill(drop, mask)
+    masked, ids, logp = _topk_us(S, x)
+    assert torch.equal(x.gather(1, ids.long()), torch.topk(x, 10, dim=1).values)
+    lse = torch.logsumexp(x.double(), 1, keepdim=True)
+    assert (logp.double() - (x.double().gather(1, ids.long()) - lse)).abs().max() <= LOGP_TOL
+    assert masked <= 1.6 * plain, (plain, masked)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("V", [700, 16384, 40001])
+def test_topk_of_values_around_the_least_reference(S, V, bf16):
+    """Chunks whose every value lies above, at and below -2^30 / log2 e, where the exponentials' reference stops,
+    spread by less and by more than float32 resolves there, and ordinary values behind such ones."""
+    rng = np.random.default_rng(96)
+    edge = -(2.0 ** 30) / np.log2(np.e)
+    x = np.empty((6, V), dtype=np.float32)
+    x[0] = edge + 1e3 * rng.standard_normal(V)
+    x[1] = edge - 2e4 * rng.random(V)
+    x[2] = edge + 2e4 * rng.random(V)
+    x[3] = -1e10 + 1e5 * rng.standard_normal(V)
+    x[4] = -3e20 * (1 + rng.random(V))
+    x[5] = np.where(np.arange(V) < V // 2, -1e10, rng.standard_normal(V))
+    t = torch.from_numpy(x).cuda().to(torch.bfloat16 if bf16 else torch.float32)
+    x = t.float().cpu().numpy()
+    ids, logp = S.topk_logprob(t, 10)
+    rid, rlogp = topk_logprob_ref(x, 10)
+    assert np.array_equal(ids.cpu().numpy(), rid)
+    # lse and logit - lse round once each at the maximum's size (half a unit of 2^-23 of it at most)
+    tol = LOGP_TOL + np.abs(x.max(1, keepdims=True)) * 2.0 ** -23
+    assert (np.abs(logp.cpu().numpy() - rlogp) <= tol).all(), np.abs(logp.cpu().numpy() - rlogp).max(1)
+
+
 def test_topk_full_vocabulary_every_row_of_a_level(S):
     """The shape of one level of the batch-16 workload: 160 rows (16 sequences x 10 frontier
     nodes) over the vocabulary of 152064, float32; and the root level's 16 rows in bf16."""

@@ -436,7 +436,9 @@ __global__ __launch_bounds__(kThreads) void tree_grow_kernel(int K, int level, i
 // order.  The keep best are those above the keep-th largest score, found bit by bit (a ballot per bit and
 // register), and the first of those equal to it: C comparisons per bit instead of C^2 by counting.  One
 // wavefront, and so no barrier, as long as the candidates fit it: what bounds it is the chain of 32 counts
-// behind the loads.  410 candidates 13.3 -> 8.0 us a launch, 784 32.7 -> 13, 3875 688 -> 17.
+// behind the loads, each of P ballots, so P is no larger than the candidates ask for.  In a graph, against ranks by
+// counting: 6 candidates 3.7 -> 3.5 us (6.6 with P = 8), 55 4.2 -> 3.6 (6.7), 200 6.2 -> 5.0 (6.9), 410 12.2 -> 7.1,
+// 784 32.6 -> 13.0, 3875 685 -> 17.1.
 template <int NW, int P>
 __global__ __launch_bounds__(64 * NW) void tree_finalize_kernel(
     int B, int C, int n, const float *__restrict__ cand_score, const int32_t *__restrict__ cand_token,
@@ -596,7 +598,11 @@ hipError_t launch_tree_finalize(int32_t B, int32_t C, int32_t n, const float *ca
                                 const int32_t *cand_parent, const int32_t *root_token, int32_t *node_offset,
                                 int32_t *parent, int32_t *draft_ids, int32_t *depth, unsigned long long *anc,
                                 int32_t *node_cand, float *node_score, hipStream_t s) {
-  auto kern = C <= 512 ? tree_finalize_kernel<1, 8> : tree_finalize_kernel<4, 16>;
+  auto kern = C <= 64    ? tree_finalize_kernel<1, 1>
+              : C <= 128 ? tree_finalize_kernel<1, 2>
+              : C <= 256 ? tree_finalize_kernel<1, 4>
+              : C <= 512 ? tree_finalize_kernel<1, 8>
+                         : tree_finalize_kernel<4, 16>;
   kern<<<B, C <= 512 ? 64 : 256, 0, s>>>(B, C, n, cand_score, cand_token, cand_parent, root_token, node_offset, parent, draft_ids,
                                          depth, anc, node_cand, node_score);
   return hipGetLastError();

@@ -98,8 +98,8 @@ struct StreamArgs {
   bf16_t *q, *k, *v;       // [M, Hq, 128], [M, Hkv, 128], [M, Hkv, 128]
   int Hq, Hkv;
 };
-// split: K would be split otherwise; what is taken then is taken also where it would not
-bool proj_stream_takes(int32_t M, int32_t K, int32_t N, bool split);
+bool proj_stream_supports(int32_t M, int32_t K);
+bool proj_stream_pays(int32_t K, int32_t N, bool split);  // against tiles of 256 rows (split: over K)
 hipError_t launch_proj_stream(StreamKind kind, int32_t M, int32_t K, int32_t N, const void *hidden, const void *weight,
                               const StreamArgs &sa, hipStream_t s);
 

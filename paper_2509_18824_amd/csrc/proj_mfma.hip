@@ -18,6 +18,8 @@
 // is one lane's own two accumulators.
 #include "hb_internal.h"
 
+#include <cmath>
+
 namespace hb {
 
 namespace {
@@ -381,9 +383,6 @@ inline int few_m_pad(int M) { return M <= 64 ? 64 : 128; }
 // share of the CUs at work.  What it takes is within 1 % of the fastest of them in the mean, and 19 % faster
 // than the split into 256-row tiles (128 tokens, split and reduction against this: 3584 x 3584 18.4 -> 16.2,
 // 18944 x 3584 49 -> 40, 2048 x 2048 13.7 -> 8.8; gated 3584 x 37888 73.5 -> 58.9, 4096 x 24576 62 -> 51).
-// Against the stream, which takes fewer tokens, the line lies at 17: at 16 / 17 / 32 tokens 3584 x 3584 9.1 / 10.9 /
-// 12.0 there, 10.7 / 10.7 / 11.0 here; 18944 x 3584 33.5 / 35.4 / 42.4 and 30 / 30 / 31; gated 2048 x 16384 16.7 /
-// 23 / 23.4 and 19; 3584 x 37888 49.3 / 53.7 / 56.7 and 48.8 / 48.8 / 49.6.
 // Gated weights are not split (tiles of pairs, and never few); 16-row tiles only where K is whole.
 // workspace: the bytes that a caller was told to bring, for split_plan.
 FewPlan few_plan(int M, int K, int V, StreamKind kind, size_t workspace) {
@@ -413,6 +412,30 @@ FewPlan few_plan(int M, int K, int V, StreamKind kind, size_t workspace) {
   return best;
 }
 
+// 17 to 32 tokens: microseconds of a plan and of the stream, fitted to 2400 measurements of calls in a graph on weights
+// too many to stay in the last-level cache (512 to 18944 x 128 to 40960; 5 and 4 % rms).
+// Weight rows, or parts of them, that begin a multiple of 4 KB apart meet on few memory channels once all CUs read them
+// (24 tokens: 3072 x 28672 35 us, 4096 x 28672 56).
+double few_us(const FewPlan &p, int M, int K, int V, StreamKind kind) {
+  const bool gated = kind == StreamKind::kGlu;
+  const int tiles = gated ? (V / 2 + 8 * p.rows - 1) / (8 * p.rows) : (V + 16 * p.rows - 1) / (16 * p.rows);
+  const double fill = (double)(tiles * p.ks) / 256, v_pad = (V + TV - 1) / TV * TV;
+  double row = 0.030 + (gated && (int64_t)K * V >= kUncached ? 0.026 : 0.038) * fill + 0.0017 * p.rows;
+  if (p.rows >= 4 && K / p.ks % 2048 == 0) row += (K % 8192 == 0 && p.ks == 1 ? 0.025 : 0.0147) * fill * fill;
+  const double us = 3.3 + K / BK / p.ks * (0.054 + p.rows * row + 0.0087 * fill * fill + 0.00053 * (M - 17));
+  return p.ks > 1 ? us + 2.1 + 1.33e-6 * p.ks * v_pad * 64 : us;
+}
+// Up to K = 4096 the tokens stay in registers and two workgroups fit a CU; beyond they travel with the weights, and the
+// workgroups take 256 tiles of 16 rows a round.
+double stream_us(int M, int K, int V) {
+  const double steps = K / BK;
+  const int tiles = (V + 15) / 16;
+  const double fill = (double)tiles / 256;
+  if (K > 4096) return 4.4 + (tiles + 255) / 256 * (0.56 + steps * (0.042 + 0.0016 * M)) + 0.0227 * steps * fill;
+  if (tiles > 256) return 12.0 + steps * (0.0025 * M - 0.025 + 0.07 * fill);
+  return 4.95 + steps * (0.083 + 0.001 * M + 0.0108 * fill - 0.0006 * steps) + 0.19 * std::log2((double)(tiles > 8 ? tiles : 8));
+}
+
 template <bool ROPE, bool GLU>
 hipError_t launch_few(StreamKind kind, const FewPlan &p, int M, int K, int V, const void *hidden, const void *weight,
                       const QkvArgs &qa, const StoreArgs &sa, float *part, hipStream_t s) {
@@ -426,16 +449,25 @@ hipError_t launch_few(StreamKind kind, const FewPlan &p, int M, int K, int V, co
 
 // Which kernel takes the product: the stream, few rows against all tokens, or tiles of 256 rows (split over K as
 // *plan says).  The plan costs the host some microseconds and is made only where it matters.
+// From 17 to 32 tokens stream and few rows each have their shapes (us at 17 / 32 tokens by the stream and by few rows:
+// 3584 x 3584 10.8 / 11.8 and 10.6 / 11.0; 14336 x 4096 26 / 32 and 34 / 35, in parts 28; 8192 x 8192 29 / 33 and 37; 3584 x
+// 16384 28 / 30 and 24; gated 3584 x 37888 50 / 54 and 45, 4096 x 28672 44 / 47 and 53 / 54): the one expected to be faster,
+// within 0.3 % of the faster one in the mean of the 2400 calls, and more than 3 % slower in 60 of them.
+// Parts of K of 4 KB in tiles of 96 or 128 rows lose to the split into 256-row tiles (32 / 128 tokens, 8192 x 8192 41 / 45 and
+// 33 / 41, 8192 x 7168 35 / 40 and 30 / 37, 14336 x 4608 38 / 43 and 33 / 41); other parts do not.
 enum class Way { kStream, kFew, kTiles };
 Way way_of(int M, int K, int V, StreamKind kind, const float *part, FewPlan *few, SplitPlan *plan) {
   *plan = {1, 1};
   *few = {0, 1};
-  if (M < kFewLeast && proj_stream_takes(M, K, V, true)) return Way::kStream;  // then also where K is not split
+  const bool stream = proj_stream_supports(M, K);
+  if (M < kFewLeast && stream) return Way::kStream;
   if (part) *plan = split_plan(M, K, V);
   *few = few_plan(M, K, V, kind, split_bytes(*plan, M, V));
-  if (few->rows) return Way::kFew;
-  if (proj_stream_takes(M, K, V, true)) return Way::kStream;
-  return plan->ks <= 1 && proj_stream_takes(M, K, V, false) ? Way::kStream : Way::kTiles;
+  if (few->rows) {
+    if (stream && stream_us(M, K, V) < few_us(*few, M, K, V, kind)) return Way::kStream;
+    return few->ks > 1 && K / few->ks == 2048 && (few->rows == 6 || few->rows == 8) ? Way::kTiles : Way::kFew;
+  }
+  return stream && proj_stream_pays(K, V, plan->ks > 1) ? Way::kStream : Way::kTiles;
 }
 
 template <bool ROPE, bool GLU>

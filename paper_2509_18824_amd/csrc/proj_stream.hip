@@ -1,5 +1,5 @@
-// The projections around the attention for up to 16 tokens (32 where proj_few.hip has no division of the rows):
-// streams of the weight matrix.
+// The projections around the attention for up to 16 tokens, and up to 32 where this is the faster way: streams of
+// the weight matrix.
 //
 // With so few tokens a projection is its weights read once from HBM and next to no arithmetic.  What
 // counts is that every CU has enough bytes in flight all the time and that nothing else is launched:
@@ -278,14 +278,15 @@ hipError_t dispatch(int M, int K, int N, const void *hidden, const void *weight,
 //   3584 x 37888  46 / 49 / 56 (gated)   60 / 60 / 62
 //   512 x 16384   9 / 10 / 15         12 / 12 / 12
 //   8192 x 2048   12.4 / 13.8 / 17.2  19.5 / 19.3 / 19.3
-// Up to 16 tokens everywhere.  From 17 on proj_few.hip takes all but weights of more than 40960 rows and many short
-// gated rows; of those the stream takes what comes from memory in any case, from about 120 MB on (2048 x 24576, 32
-// tokens: 28 both; 3584 x 18432: 32 to 34 against 37 to 39), and, where K is not split (no workspace), all but the
-// shortest (2048 x 16384 gated: 22 against 31; 1024 x 32768: 25 against 22).
-bool proj_stream_takes(int32_t M, int32_t K, int32_t N, bool split) {
-  if (M > 32 || K % 64 || K / 64 < kWaves || (int64_t)K * 64 >= ((int64_t)1 << 31)) return false;
-  return M <= 16 || (int64_t)K * N >= 60 * 1000 * 1000 || (!split && K >= 2048);
+// Up to 16 tokens everywhere; from 17 to 32 proj_mfma.hip compares it with proj_few.hip.
+bool proj_stream_supports(int32_t M, int32_t K) {
+  return M <= 32 && K % 64 == 0 && K / 64 >= kWaves && (int64_t)K * 64 < ((int64_t)1 << 31);
 }
+// 17 to 32 tokens where proj_few.hip has no division of the rows (more than 40960 of them, many short gated ones): what
+// comes from memory in any case, from about 120 MB on (2048 x 24576, 32 tokens: 28 both; 3584 x 18432: 32 to 34 against
+// 37 to 39), and, where K is not split, all but the shortest (2048 x 16384 gated: 22 against 31; 1024 x 32768: 25
+// against 22).
+bool proj_stream_pays(int32_t K, int32_t N, bool split) { return (int64_t)K * N >= 60 * 1000 * 1000 || (!split && K >= 2048); }
 
 hipError_t launch_proj_stream(StreamKind kind, int32_t M, int32_t K, int32_t N, const void *hidden, const void *weight,
                               const StreamArgs &sa, hipStream_t s) {

@@ -184,6 +184,36 @@ def test_gated_silu_projection_of_all_tokens_at_once(hb, T, K, F):
         test_gated_silu_projection(hb, T, K, F, ws)
 
 
+@pytest.mark.parametrize("K,N,gated", [(14336, 4096, False), (18944, 3584, False), (4096, 28672, True)])
+def test_seventeen_tokens_take_hardly_longer_than_sixteen(hb, K, N, gated):
+    """Shapes where the stream stays ahead beyond 16 tokens: 25 and 26 us, 31 and 32, 43 and 44 by it; 33, 39 and 54 by tiles
+    of few rows.  Four weight matrices in turn, in a graph."""
+    weights = [torch.randn((N, K), device="cuda", dtype=torch.bfloat16) for _ in range(4)]
+
+    def us(T):
+        x = torch.randn((T, K), device="cuda", dtype=torch.bfloat16)
+        out = torch.empty((T, N // 2 if gated else N), device="cuda", dtype=torch.bfloat16)
+        run = (lambda w: hb.hb_swiglu_project(x, w, out, None)) if gated else (lambda w: hb.hb_out_project(x, w, None, out))
+        run(weights[0])
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for i in range(12):
+                run(weights[i % 4])
+        best = float("inf")
+        for _ in range(6):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            graph.replay()
+            end.record()
+            torch.cuda.synchronize()
+            best = min(best, start.elapsed_time(end) / 12 * 1e3)
+        return best
+
+    sixteen, seventeen = us(16), us(17)
+    assert seventeen <= 1.15 * sixteen, (sixteen, seventeen)
+
+
 def _out_case(hb, T, K, N, res, with_workspace):
     g = torch.Generator().manual_seed(T + K + N)
     x = torch.randn((T, K), generator=g).to(torch.bfloat16)

@@ -437,6 +437,13 @@ double stream_us(int M, int K, int V) {
 }
 
 template <bool ROPE, bool GLU>
+hipError_t launch_reduce(int M, int V, int ks, int v_pad, int m_pad, const QkvArgs &qa, const StoreArgs &sa, const float *part, hipStream_t s) {
+  const int groups = ROPE ? V / kHeadDim * 16 : GLU ? V / 8 : V / 4;
+  proj_reduce_kernel<ROPE, GLU><<<dim3((unsigned)((groups + 255) / 256), (unsigned)M), 256, 0, s>>>(M, V, ks, v_pad, m_pad, groups, part, qa, sa);
+  return hipGetLastError();
+}
+
+template <bool ROPE, bool GLU>
 hipError_t launch_few(StreamKind kind, const FewPlan &p, int M, int K, int V, const void *hidden, const void *weight,
                       const QkvArgs &qa, const StoreArgs &sa, float *part, hipStream_t s) {
   if (p.ks > 1 && !part) return hipErrorInvalidValue;
@@ -468,13 +475,6 @@ Way way_of(int M, int K, int V, StreamKind kind, const float *part, FewPlan *few
     return few->ks > 1 && K / few->ks == 2048 && (few->rows == 6 || few->rows == 8) ? Way::kTiles : Way::kFew;
   }
   return stream && proj_stream_pays(K, V, plan->ks > 1) ? Way::kStream : Way::kTiles;
-}
-
-template <bool ROPE, bool GLU>
-hipError_t launch_reduce(int M, int V, int ks, int v_pad, int m_pad, const QkvArgs &qa, const StoreArgs &sa, const float *part, hipStream_t s) {
-  const int groups = ROPE ? V / kHeadDim * 16 : GLU ? V / 8 : V / 4;
-  proj_reduce_kernel<ROPE, GLU><<<dim3((unsigned)((groups + 255) / 256), (unsigned)M), 256, 0, s>>>(M, V, ks, v_pad, m_pad, groups, part, qa, sa);
-  return hipGetLastError();
 }
 
 template <bool ROPE, bool GLU>

@@ -38,6 +38,22 @@ def test_version_and_tree_validation():
     assert e.value.code == 2
 
 
+def test_the_current_stream_with_and_without_torchs_raw_handle(monkeypatch):
+    """torch's private function for the handle is used where it is there, else the public stream object."""
+    import types
+    import torch
+    import paper_2509_18824_amd.binding as binding
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "is_available", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x50))
+    monkeypatch.setattr(binding, "_raw_stream", lambda device: 0x40 + device)
+    assert binding._stream(None) == 0x43
+    monkeypatch.setattr(binding, "_raw_stream", None)
+    assert binding._stream(None) == 0x50
+    assert binding._stream(types.SimpleNamespace(cuda_stream=0x60)) == 0x60
+
+
 def _desc(**kw):
     base = dict(dtype="bf16", B=2, Hq=28, Hkv=4, D=128, page=16, max_blocks=64, num_blocks=200,
                 total_nodes=120, max_nodes=60, softmax_scale=0.1)

@@ -119,9 +119,10 @@ def test_output_projection_split_over_k(hb, T, K, N, res):
     _out_case(hb, T, K, N, res, True)
 
 
-# Up to 32 tokens take the streaming kernel: 8, 16 and 32 tokens are its token tiles; 8 K steps give every
+# Up to 16 tokens stream: 8 and 16 are token tiles of the streaming kernel; 8 K steps give every
 # wavefront one, 9 the first one two; 64 steps are the most whose tokens stay in registers; 16-row
-# tiles with and without a remainder (N = 4: no partner rows; 20, 12); more tiles than workgroups
+# tiles with and without a remainder (N = 4: no partner rows; 20, 12); more tiles than workgroups.
+# 17 to 33 tokens by whichever way is expected to be faster there
 @pytest.mark.parametrize("T,K,N,res", [(1, 512, 4, True), (8, 576, 20, False), (9, 4096, 36, True), (16, 4160, 12, True),
                                        (17, 512, 100, False), (32, 4160, 264, True), (33, 4160, 264, True),
                                        (8, 4160, 4620, True), (20, 576, 16404, False), (3, 1024, 9000, True)])
@@ -141,29 +142,29 @@ def test_gated_silu_projection_of_few_tokens(hb, T, K, F):
     test_gated_silu_projection(hb, T, K, F, False)
 
 
-# Past 16 tokens the split over K keeps long rows over few weight rows and many short ones; 33 tokens and
-# more always split where K allows it
+# Long rows over few weight rows, and many short ones, around the 17 and 32 tokens between which the stream, tiles of few
+# rows and the split over K each have their shapes
 @pytest.mark.parametrize("T,K,N,res", [(25, 12288, 260, True), (24, 18944, 1024, False), (32, 18944, 2048, True), (17, 18944, 20, False),
                                        (32, 512, 16404, True), (33, 2048, 1000, False), (33, 1024, 4, True), (40, 8192, 2052, True)])
-def test_output_projection_between_the_stream_and_the_split(hb, T, K, N, res):
+def test_output_projection_around_the_end_of_the_stream(hb, T, K, N, res):
     assert hb.hb_proj_workspace_bytes(T, K, N) > 0 or N > 16384
     _out_case(hb, T, K, N, res, True)
     _out_case(hb, T, K, N, res, False)
 
 
 @pytest.mark.parametrize("T,K,Hq,Hkv,bias", [(33, 512, 1, 1, True), (24, 12288, 6, 1, False), (20, 3584, 28, 4, True)])
-def test_qkv_projection_between_the_stream_and_the_split(hb, T, K, Hq, Hkv, bias):
+def test_qkv_projection_around_the_end_of_the_stream(hb, T, K, Hq, Hkv, bias):
     _qkv_case(hb, T, K, Hq, Hkv, bias, True)
 
 
-# one tile of tokens and weights below and above the size from which their loads are non-temporal
+# tiles of few rows, weights below and above the size from which their loads are non-temporal
 @pytest.mark.parametrize("T,K,F,ws", [(33, 4160, 16128, False), (40, 4160, 16136, False), (128, 4160, 16136, True), (24, 2048, 4100, True)])
 def test_gated_silu_projection_of_one_tile_of_tokens(hb, T, K, F, ws):
     test_gated_silu_projection(hb, T, K, F, ws)
 
 
 # All tokens in one tile: 64 and 128 tokens are its sizes; one K step and odd numbers of them (two go to a stage
-# where they can); tiles of 1, 2, 4, 6, 8 and 10 groups of 16 rows, ragged last ones, K whole and in parts
+# where they can), ragged last tiles, K whole and in parts
 @pytest.mark.parametrize("T,K,N", [(17, 64, 4), (33, 192, 100), (64, 576, 4100), (65, 1088, 4612), (127, 832, 9004), (128, 1536, 260),
                                    (128, 9728, 516), (100, 128, 20484), (40, 256, 30724), (96, 320, 40960), (20, 576, 41000)])
 def test_output_projection_of_all_tokens_at_once(hb, T, K, N):
@@ -182,6 +183,62 @@ def test_qkv_projection_of_all_tokens_at_once(hb, T, K, Hq, Hkv, bias):
 def test_gated_silu_projection_of_all_tokens_at_once(hb, T, K, F):
     for ws in (False, True):
         test_gated_silu_projection(hb, T, K, F, ws)
+
+
+def _kernels(call):
+    """Names of the projection kernels that a call runs, each as it is in the source with its template arguments."""
+    import re
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CUDA]) as trace:
+        call()
+        torch.cuda.synchronize()
+    names = [re.search(r"proj_(\w+)_kernel(<[^>]*>)", e.name) for e in trace.events()]
+    short = lambda t: re.sub(r"\(hb::[^)]*\)+", "", t)  # the enumerations' names
+    return [m[1] + short(m[2].replace("(anonymous namespace)::", "")) for m in names if m]
+
+
+# Every way a product can go, asserted by the kernel's name.  few<kind, 16-row groups of a tile, tokens, K steps of a stage>
+# (kind 0 plain, 1 rotary, 2 gated, 3 partial sums), stream<kind, groups of eight tokens, tokens in registers>,
+# mfma<64-token tiles, rotary, gated, non-temporal>
+@pytest.mark.parametrize("T,K,N,ws,kernel", [
+    (24, 14336, 260, False, "stream<0, 4, false>"), (20, 1472, 41000, False, "stream<0, 4, true>"),
+    (32, 4160, 41000, True, "stream<0, 4, false>"),
+    (40, 512, 260, False, "few<0, 1, 64, 2>"), (96, 576, 260, False, "few<0, 1, 128, 1>"), (64, 576, 4100, False, "few<0, 2, 64, 1>"),
+    (40, 64, 8196, False, "few<0, 4, 64, 1>"), (100, 128, 8196, False, "few<0, 4, 128, 2>"), (40, 64, 16388, False, "few<0, 6, 64, 1>"),
+    (100, 64, 16388, False, "few<0, 6, 128, 1>"), (40, 64, 24580, False, "few<0, 8, 64, 1>"), (100, 64, 24580, False, "few<0, 8, 128, 1>"),
+    (40, 64, 32772, False, "few<0, 10, 64, 1>"), (100, 64, 32772, False, "few<0, 10, 128, 1>"),
+    (32, 8192, 516, True, "few<3, 2, 64, 2>"), (40, 7168, 3072, True, "few<3, 6, 64, 1>"), (128, 7168, 8192, True, "few<3, 8, 128, 1>"),
+    (40, 7168, 4612, True, "few<3, 10, 64, 1>"), (100, 7168, 10240, True, "few<3, 10, 128, 1>"),
+    (40, 8192, 8192, True, "splitk<1>"), (100, 8192, 8192, True, "splitk<2>")])
+def test_every_way_of_the_output_projection(hb, T, K, N, ws, kernel):
+    names = _kernels(lambda: _out_case(hb, T, K, N, T % 2 == 0, ws))
+    assert names == ([kernel, "reduce<false, false>"] if kernel.startswith(("few<3", "splitk")) else [kernel])
+
+
+@pytest.mark.parametrize("T,K,Hq,Hkv,bias,ws,kernel", [
+    (24, 5120, 12, 4, True, False, "stream<1, 4, false>"), (32, 4096, 28, 2, False, False, "stream<1, 4, true>"),
+    (64, 64, 65, 1, True, False, "few<1, 4, 64, 1>"), (128, 128, 64, 8, True, False, "few<1, 4, 128, 2>"),
+    (40, 64, 130, 3, True, False, "few<1, 6, 64, 1>"), (128, 64, 130, 3, False, False, "few<1, 6, 128, 1>"),
+    (64, 64, 200, 5, False, False, "few<1, 8, 64, 1>"), (128, 64, 200, 5, True, False, "few<1, 8, 128, 1>"),
+    (40, 64, 270, 11, True, False, "few<1, 10, 64, 1>"), (128, 128, 270, 11, False, False, "few<1, 10, 128, 1>"),
+    (100, 7168, 40, 8, True, True, "few<3, 8, 128, 1>"), (40, 8192, 64, 8, True, True, "few<3, 10, 64, 1>"),
+    (100, 8192, 64, 8, False, True, "few<3, 10, 128, 1>")])
+def test_every_way_of_the_qkv_projection(hb, T, K, Hq, Hkv, bias, ws, kernel):
+    names = _kernels(lambda: _qkv_case(hb, T, K, Hq, Hkv, bias, ws))
+    assert names == ([kernel, "reduce<true, false>"] if kernel.startswith("few<3") else [kernel])
+
+
+@pytest.mark.parametrize("T,K,F,ws,kernel", [
+    (17, 2048, 16384, False, "stream<2, 4, true>"), (32, 2048, 16384, True, "stream<2, 4, true>"), (24, 8192, 4100, False, "stream<2, 4, false>"),
+    (32, 4160, 2052, False, "few<2, 2, 64, 1>"), (40, 64, 4100, False, "few<2, 4, 64, 1>"), (100, 128, 4100, False, "few<2, 4, 128, 2>"),
+    (40, 64, 8196, False, "few<2, 6, 64, 1>"), (100, 64, 8196, False, "few<2, 6, 128, 1>"), (40, 2112, 12292, False, "few<2, 8, 64, 1>"),
+    (100, 2112, 12292, False, "few<2, 8, 128, 1>"), (40, 2112, 16388, False, "few<2, 10, 64, 1>"), (100, 2112, 16388, False, "few<2, 10, 128, 1>"),
+    (64, 2048, 16384, False, "mfma<1, false, true, false>"), (64, 2048, 16384, True, "splitk<1>"),
+    (160, 3584, 18944, False, "mfma<3, false, true, true>"), (240, 3584, 18944, False, "mfma<4, false, true, true>"),
+    (500, 2048, 16384, False, "mfma<4, false, true, false>")])
+def test_every_way_of_the_gated_projection(hb, T, K, F, ws, kernel):
+    names = _kernels(lambda: test_gated_silu_projection(hb, T, K, F, ws))
+    assert names == ([kernel, "reduce<false, true>"] if kernel.startswith("splitk") else [kernel])
 
 
 @pytest.mark.parametrize("K,N,gated", [(14336, 4096, False), (18944, 3584, False), (4096, 28672, True)])

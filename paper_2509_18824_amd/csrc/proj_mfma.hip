@@ -394,9 +394,12 @@ FewPlan few_plan(int M, int K, int V, StreamKind kind, size_t workspace) {
   double best_cost = 1e30;
   for (int rows : kRows) {
     if (rows == 1 && kind != StreamKind::kPlain) continue;
-    // many short gated rows: the tile kernel keeps up (2048 x 32768, 40 tokens: 35.5 us against 37.3)
-    if (gated && rows >= 8 && K <= 2048) continue;
     const long tiles = gated ? (V / 2 + 8 * rows - 1) / (8 * rows) : (V + 16 * rows - 1) / (16 * rows);
+    // Many short gated rows.  Beyond 64 tokens it depends on the shape (96 tokens, against the tile kernel: 1280 x 36864
+    // 25 and 30 us, 1024 x 32768 22 and 18); rows 4 KB apart lose to the stream up to 32 tokens (2048 x 25600, 17 tokens:
+    // 28 and 25.5) and to the tile kernel where all CUs are at work (2048 x 32768, 40 tokens: 36 and 34, x 25600 28.5 and 33).
+    // Elsewhere the few rows are 1 to 29 % ahead (64 tokens, 1536 x 28672 22.6 and 28.6).
+    if (gated && rows >= 8 && K <= 2048 && (M > 64 || (K == 2048 && (M <= 32 || tiles > 240)))) continue;
     for (int ks = 1; ks <= (gated || rows == 1 ? 1 : 8); ++ks) {
       if (steps % ks || (ks > 1 && steps / ks < 6) || tiles * ks > 256) continue;
       if (ks > 1 && (size_t)ks * v_pad * few_m_pad(M) * sizeof(float) > workspace) continue;

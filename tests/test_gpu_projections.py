@@ -233,7 +233,7 @@ def test_every_way_of_the_qkv_projection(hb, T, K, Hq, Hkv, bias, ws, kernel):
     (32, 4160, 2052, False, "few<2, 2, 64, 1>"), (40, 64, 4100, False, "few<2, 4, 64, 1>"), (100, 128, 4100, False, "few<2, 4, 128, 2>"),
     (40, 64, 8196, False, "few<2, 6, 64, 1>"), (100, 64, 8196, False, "few<2, 6, 128, 1>"), (40, 2112, 12292, False, "few<2, 8, 64, 1>"),
     (100, 2112, 12292, False, "few<2, 8, 128, 1>"), (40, 2112, 16388, False, "few<2, 10, 64, 1>"), (100, 2112, 16388, False, "few<2, 10, 128, 1>"),
-    (64, 2048, 16384, False, "mfma<1, false, true, false>"), (64, 2048, 16384, True, "splitk<1>"),
+    (64, 2048, 16384, True, "few<2, 10, 64, 1>"), (100, 2048, 16384, False, "mfma<1, false, true, false>"), (288, 2048, 1000, True, "splitk<1>"),
     (160, 3584, 18944, False, "mfma<3, false, true, true>"), (240, 3584, 18944, False, "mfma<4, false, true, true>"),
     (500, 2048, 16384, False, "mfma<4, false, true, false>")])
 def test_every_way_of_the_gated_projection(hb, T, K, F, ws, kernel):

@@ -711,8 +711,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mfma_kernel(
     // One workgroup per CU.  The loop over 32-key blocks is skewed by one: with the probabilities of a block
     // and its V^T fragments in registers, the matrix core gets O^T of this block and the scores of the next
     // in one go (34 instructions without a wait), and the vector work that follows has its scores already:
-    // 4200 clocks a tile against 4800 block by block; two trees of 60 nodes over 32768 positions 94.8 -> 86.4 us,
-    // 16 over 1024 to 4096 79.9 -> 74.2.  What bounds it is the issue of vector instructions and MFMAs (8 clocks
+    // 4200 clocks a tile against 4800 block by block; whole calls, the merge included, in a graph: two trees of 60 nodes
+    // over 32768 positions 103.9 -> 96.6 us, 16 over 1024 to 4096 89.5 -> 84.4.  What bounds it is the issue of vector instructions and MFMAs (8 clocks
     // of the port each) by two wavefronts: taking turns phase by phase, a barrier after each, was slower (4520).
     // A tile's stage is last read in front of the barrier that stands between its second block's vector
     // and matrix work and is filled with tile i + NS right behind it; that barrier also lets everybody into

@@ -36,6 +36,9 @@ __host__ __device__ inline bf16_t f32_to_bf16(float f) {
   return (bf16_t)(u >> 16);
 }
 
+// two in one register, the first in the lower half
+__device__ inline uint32_t pack_bf16(float a, float b) { return (uint32_t)f32_to_bf16(a) | ((uint32_t)f32_to_bf16(b) << 16); }
+
 template <typename T> __device__ inline float load_f32(const T *p);
 template <> __device__ inline float load_f32<float>(const float *p) { return *p; }
 template <> __device__ inline float load_f32<bf16_t>(const bf16_t *p) { return bf16_to_f32(*p); }
@@ -112,7 +115,7 @@ hipError_t launch_proj_few(StreamKind kind, const FewPlan &p, int32_t M, int32_t
                            const void *weight, const StreamArgs &sa, float *part, int32_t v_pad, int32_t m_pad, hipStream_t s);
 
 bool proj_mfma_supports(int32_t M, int32_t K, int32_t N);
-// part: fp32 scratch of proj_workspace_bytes(M, K, N) bytes for the split-K path, or null (then: one workgroup per tile)
+// part: fp32 scratch of proj_workspace_bytes(M, K, N) bytes, for the ways that split K, or null (then K stays whole)
 size_t proj_workspace_bytes(int32_t M, int32_t K, int32_t N);
 hipError_t launch_qkv_rope(int32_t M, int32_t K, int32_t Hq, int32_t Hkv, const void *hidden, const void *w_qkv,
                            const void *bias, const float *cos, const float *sin, void *q, void *k, void *v,

@@ -12,8 +12,8 @@
 // layout wants (8 consecutive k per lane), so tiles go global -> LDS directly as 16-byte pieces
 // (global_load_lds), XOR-swizzled so that the 16-byte operand reads of 8 consecutive rows hit
 // all banks.  Weight tiles sit in a ring of three LDS stages and are fetched two K steps ahead,
-// hidden tiles in two stages one step ahead; the two wavefronts of a SIMD alternate between
-// reading operands and matrix instructions (see mfma_gemm_tile.inc).
+// hidden tiles in two stages one step ahead (64 rows: in three, two steps ahead); the two wavefronts of a
+// SIMD alternate between reading operands and matrix instructions (see mfma_gemm_tile.inc).
 //
 // What bounds the kernel at many rows is power (see there): 960 x 3584 x 152064 on normal values 876 ->
 // 826 us, 1024 rows 940 -> 839, 768 rows 752 -> 667 against 32x32x16 with one barrier per K step.
@@ -21,31 +21,11 @@
 //
 // Grid: persistent workgroups, one per CU, in groups that walk the vocabulary tiles in lockstep
 // (one hidden tile per member) on one XCD.
-#include "hb_internal.h"
+#include "mfma_gemm_tile.h"
 
 namespace hb {
 
 namespace {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-constexpr int BK = 64;           // k per step
-constexpr int TV = 256;          // vocabulary rows per workgroup
-constexpr int CH = BK / 8;       // 16-byte pieces per row per step (8)
-constexpr int kXcds = 8;
-
-// Hidden tile stages in LDS.  With 64 rows three: 7 tokens x 3584 x 152064 169.9 us (176.6 with two); with 128
-// two: 128 tokens 204 us (209 with three), gated 3584 x 37888 64.7 (67.0).  More do not fit.
-constexpr int kHiddenStages(int mt) { return mt == 1 ? 3 : 2; }
-constexpr size_t tile_lds_bytes(int mt) { return (size_t)(3 * TV + kHiddenStages(mt) * 64 * mt) * CH * 16; }
-
-// Offset (in 16-byte pieces) of piece `c` of row `r` in a swizzled [rows][8] tile.  Rows are
-// 128 bytes; the XOR spreads one logical piece of 8 consecutive rows over distinct 16-byte bank
-// groups.  The operand reads of 16x16x32 (lane l: row l % 16, piece l / 16) then run at 256 bytes
-// a clock; with row bit 3 in the XOR as well, as 32x32x16 wants it, at 128.
-__device__ inline int swz(int r, int c) { return r * CH + (c ^ (r & 7)); }
 
 // MT: 32-row hidden tiles per wavefront (the workgroup covers TM = 64 * MT hidden rows).
 // WNT: weight loads carry the non-temporal hint.  With one hidden tile nobody shares a weight
@@ -59,7 +39,7 @@ __global__ __launch_bounds__(512) void lmhead_mfma_kernel(int M, int K, int V, i
   constexpr int TM = 64 * MT;
   constexpr int NT = 512;                  // threads
   constexpr int WV = 4;                    // wavefront rows along the vocabulary
-  extern __shared__ u32x4 lds[];           // [3][TV*CH] weight, then [2][TM*CH] hidden
+  extern __shared__ u32x4 lds[];           // [3][TV*CH] weight, then [kHiddenStages][TM*CH] hidden
   u32x4 *lw = lds;
   u32x4 *lh = lds + 3 * TV * CH;
   // per-row candidates of the epilogue; reuses the weight stages once the K loop is over

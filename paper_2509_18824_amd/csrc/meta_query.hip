@@ -330,8 +330,9 @@ __global__ __launch_bounds__(kMixThreads) void meta_mix_kernel(int S, int L, int
 //            eight consecutive features of one hq row and stores them as one piece.
 //   product  W_v slice (straight from memory in fragment layout) times the mixed features of the
 //            wavefront's head: accumulators for all of the workgroup's tokens.
-// The slice's weights are requested before the mixing, the next slice's features (global -> LDS)
-// before the product, so each phase covers the other's loads.
+// The first half of a slice's weights is requested among the matrix instructions of the product before it, the
+// second half during its own mixing, the next slice's features (global -> LDS) among those of its product, so each
+// phase covers the other's loads.
 // P and the mixed features are each a bf16 value plus the bf16 remainder (two products, about 2^-17
 // relative): what was float32 when values were projected first stays better than bf16.
 //

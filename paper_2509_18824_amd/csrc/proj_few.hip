@@ -34,8 +34,6 @@ constexpr int kHeadDim = 128;
 constexpr int64_t kUncached = (int64_t)1 << 27;
 enum Kind { kPlain, kRope, kGlu, kPart };
 
-__device__ inline uint32_t pack_bf16(float a, float b) { return (uint32_t)f32_to_bf16(a) | ((uint32_t)f32_to_bf16(b) << 16); }
-
 template <int R, int TOK, int KSP>
 struct Shape {
   static constexpr int kGroups = 2 * R + TOK / 8;          // 8-row groups of a K step: weights, then tokens

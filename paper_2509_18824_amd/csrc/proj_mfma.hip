@@ -16,7 +16,7 @@
 // gated projection uses the same device: a tile holds 128 features, the gate rows in the first
 // 32-row sub-tile of every wavefront row and the matching up rows in the second, so silu(gate) * up
 // is one lane's own two accumulators.
-#include "hb_internal.h"
+#include "mfma_gemm_tile.h"
 
 #include <cmath>
 
@@ -24,26 +24,10 @@ namespace hb {
 
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int BK = 64;
-constexpr int TV = 256;
-constexpr int CH = BK / 8;
-constexpr int kXcds = 8;
-
-// Hidden tile stages in LDS.  With 64 rows three: 7 tokens x 3584 x 152064 169.9 us (176.6 with two); with 128
-// two: 128 tokens 204 us (209 with three), gated 3584 x 37888 64.7 (67.0).  More do not fit.
-constexpr int kHiddenStages(int mt) { return mt == 1 ? 3 : 2; }
-constexpr size_t tile_lds_bytes(int mt) { return (size_t)(3 * TV + kHiddenStages(mt) * 64 * mt) * CH * 16; }
 constexpr int kHeadDim = 128;
 constexpr int64_t kUncached = (int64_t)1 << 27;  // weights: 256 MB, the size of the last-level cache
-
-__device__ inline int swz(int r, int c) { return r * CH + (c ^ (r & 7)); }
-
-__device__ inline uint32_t pack_bf16(float a, float b) { return (uint32_t)f32_to_bf16(a) | ((uint32_t)f32_to_bf16(b) << 16); }
 
 // Workgroup ids go round-robin to the XCDs.  Of the units 0 .. units - 1, numbered so that neighbours share a
 // weight tile, every XCD gets one run of equal length: neighbours find the shared tile in its L2, and no XCD
@@ -70,9 +54,9 @@ struct StoreArgs {
 // ROPE: query/key/value projection with rotary embedding (V = (Hq + 2 Hkv) * 128 weight rows),
 // else plain projection.  One workgroup per (weight tile, hidden tile), dealt by deal_unit.
 // WNT: the weight loads carry the non-temporal hint.  It pays where one hidden tile means that nobody shares
-// them and they exceed the last-level cache: gated 3584 x 37888 (272 MB) 61.2 -> 57.9 us at 33 tokens, 66.9 ->
-// 63.0 at 128, eight whole layers of 16 chains 1790 -> 1755.  4096 x 28672 (235 MB): eight layers 2018 and 2016,
-// and where the cache has the weights 40 -> 62; smaller ones lose the same way (512 x 2048, unsplit: 9.7 -> 11.8).
+// them and they exceed the last-level cache (gated 3584 x 37888, 272 MB: 192 tokens 77.5 -> 73.6 us, 256 85.9 -> 82.6;
+// 4096 x 34816 at 160 84.3 -> 80.0; 5120 x 27648 and 8192 x 20480 82 and 104 both).  Weights that the cache holds lose
+// (4096 x 28672, 235 MB, read again and again: 40 -> 62; 512 x 2048 9.7 -> 11.8).
 template <int MT, bool ROPE, bool GLU, bool WNT>
 __global__ __launch_bounds__(512) void proj_mfma_kernel(int M, int K, int V, int m_tiles, int v_tiles,
                                                         const u32x4 *__restrict__ hidden,
@@ -323,15 +307,18 @@ int plain_tile_height(int M, int K, int v_tiles) {
 }
 
 // The split over K: hidden tile height (64 mt rows) and K parts (a divisor of the K steps, at
-// least kMinSteps steps per part, all workgroups resident at once), by a cost model fitted to
-// measurements on weights too many to stay in the last-level cache (microseconds):
+// least kMinSteps steps per part, all workgroups resident at once), by a cost model (microseconds, weights too
+// many to stay in the last-level cache):
 //   split:  6 + steps / ks * (0.70 | 0.86 | 1.15 | 1.45 for mt = 1 .. 4) + partial bytes written and read / 4 TB/s
-//   plain:  3 + steps * 0.75 per round of 256 workgroups (at most 512 tokens)
+//   plain:  3 + steps * 0.75 per round of 256 workgroups of 64 tokens, whatever height the unsplit kernel takes (at most
+//           512 tokens)
 //           3 + steps * (0.72 | 0.95 | 1.15 | 1.4 for the unsplit kernel's mt) per round (more tokens)
 // Up to 512 tokens the tile is 64 or 128 rows high; from there to kSplitMaxM tokens 128 to 256 rows,
-// and the split must win by 10 % (it does for long K: the feed-forward block's down projection,
-// 960 x 18944 -> 3584, takes 120 to 129 us in 4 parts of 256-row tiles; with K =
-// 3584 the unsplit kernel stays).  ks = 1 means: do not split.
+// and the split must win by 10 % (it does for long K: 960 x 18944 -> 3584 takes 124 us in 4 parts of 256-row tiles, 196
+// unsplit; with K = 3584 the unsplit kernel stays).  ks = 1 means: do not split.
+// The constants were fitted to a slower tile loop: the split now takes 7 % less than they say in the mean (960 x 18944 ->
+// 3584 143 expected), and gated 240 x 3584 -> 37888 unsplit 83 where they say 129.  What they choose holds: of 89 calls of
+// 129 to 1024 tokens that are split the unsplit kernel takes more than 2 % less in one (640 x 2048 -> 2048, 19.4 against 20.5).
 constexpr int kSplitMaxM = 1024;
 constexpr int kMinSteps = 4;
 struct SplitPlan {

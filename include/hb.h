@@ -195,21 +195,25 @@ int32_t hb_out_project(int32_t T, int32_t K, int32_t N, const void *x, const voi
                        const void *residual_or_null, void *out, void *stream);
 
 /*
- * The same two projections for small token counts (chain drafts, the draft model's batches), the
- * setting of the paper's own measurements (Section 4.2: chain decoding).  With a few hundred tokens
- * or fewer (and with up to a thousand when K is long) a projection is a stream of its weight
- * matrix from HBM, and one workgroup per 256-row weight tile and tile of tokens leaves most of
- * the chip idle; given a workspace these calls cut K into parts, one workgroup per (weight tile, K part, tile of tokens), keep the parts' fp32
- * partial results in the workspace and finish (sum in fixed order, bias, rotary embedding,
- * residual) in a second kernel.  Results are deterministic; they differ from the calls above in
- * fp32 summation order only.
- * Up to 16 tokens (K >= 512), and up to 32 where that is the faster way, both kinds of call stream the
- * weights in one kernel instead and leave the workspace alone; its size above does not change.
+ * The same two projections with a workspace, for small token counts (chain drafts, the draft model's
+ * batches), the setting of the paper's own measurements (Section 4.2: chain decoding).  With a few
+ * hundred tokens or fewer (and with up to a thousand when K is long) a projection is a stream of its
+ * weight matrix from HBM, and one workgroup per 256-row weight tile and tile of tokens leaves most of
+ * the chip idle.  By the number of tokens, with and without a workspace:
+ *   up to 16 (K >= 512)   the weights are streamed in one kernel, K whole;
+ *   17 to 128             tiles of few weight rows against all tokens at once, or (up to 32 tokens) the
+ *                         stream, whichever is expected to be faster;
+ *   more, and what has no such tiles: tiles of 256 weight rows.
+ * Given a workspace, the last two may cut K into parts where that is expected to be faster (tiles of few
+ * rows of the gated projection never): the parts' fp32 partial results go to the workspace, and a second
+ * kernel finishes (sum in fixed order, bias, rotary embedding, residual).  Results are deterministic; they
+ * differ from the calls above in fp32 summation order only.
  *   workspace   device, hb_proj_workspace_bytes(T, K, N) bytes (N = (Hq + 2 Hkv) * 128 for the
- *               QKV projection), 16-byte aligned.  That size is 0 when the split does not apply
- *               (more than 1024 tokens, K too short to cut, or more than 512 tokens and no gain
- *               expected: the split pays there for long K only); with a NULL, short or misaligned
- *               workspace the calls behave exactly as the ones above.
+ *               QKV projection), 16-byte aligned.  That size is what 256-row tiles split over K ask
+ *               for: an upper bound, of which the other ways use a part or nothing.  It is 0 when that
+ *               split does not apply (more than 1024 tokens, K too short to cut, or more than 512
+ *               tokens and no gain expected: the split pays there for long K only); with a NULL, short
+ *               or misaligned workspace the calls behave exactly as the ones above.
  * Errors as above.
  */
 size_t hb_proj_workspace_bytes(int32_t T, int32_t K, int32_t N);
@@ -234,8 +238,8 @@ int32_t hb_out_project_ws(int32_t T, int32_t K, int32_t N, const void *x, const 
  *   x [T, K];  w_gate_up [2 F, K]: the gate projection's F rows, then the up projection's F rows
  *   (y = x W^T layout);  out [T, F].
  *   workspace_or_null   device, hb_proj_workspace_bytes(T, K, 2 * F) bytes, 16-byte aligned: with
- *               it, few tokens take the split over K of hb_out_project_ws; NULL, short or
- *               misaligned: the unsplit kernel.
+ *               it, tiles of 256 weight rows may split K as in hb_out_project_ws; NULL, short or
+ *               misaligned: K stays whole.
  * The block's down projection with its residual is hb_out_project(T, F, K, act, w_down, residual, out).
  * Errors: INVALID_ARG (T < 0, sizes < 1, eps < 0, NULL or misaligned pointers), UNSUPPORTED
  * (hb_rmsnorm: K % 8 != 0; hb_swiglu_project: K % 64 != 0, F % 4 != 0), DEVICE.  T == 0 is a no-op.

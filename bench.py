@@ -31,7 +31,7 @@ PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA, published
 # and csrc/mfma_gemm_tile.inc (the tile loop the kernel includes); anything else reports null.
 # "tree": the 960-row launch of the headline step; "chain8": the 128-row launch of the chain run.
 LMHEAD_TRAFFIC = {
-    "05d128442b8d387c": {
+    "da4572dcbf7a811e": {
         "tree": {"fetch_bytes": 1.8467e9, "write_bytes": 2.1e5, "bytes": 1.8469e9,
                  "algorithmic_bytes": 152064 * 3584 * 2 + 960 * 3584 * 2},
         "chain8": {"fetch_bytes": 1.1142e9, "write_bytes": 4.2e4, "bytes": 1.1142e9,

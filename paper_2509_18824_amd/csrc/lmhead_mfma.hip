@@ -191,6 +191,12 @@ hipError_t launch_lmhead_mfma(int32_t M, int32_t K, int32_t V, const void *hidde
     long rows = (long)((M + tm - 1) / tm) * tm;
     if (best_rows < 0 || rows < best_rows) { best_rows = rows; best_mt = mt; }
   }
+  // One taller tile on a few CUs waits for its own K steps (950 ns each with 128 rows, 550 with 64), not for memory:
+  // 64-row tiles as long as one round of CUs holds them all (32 per XCD).  Taller -> 64-row tiles, us: 128 rows x 4096 x
+  // 4096 62 -> 50, x 24576 71 -> 63, x 32768 79 -> 73; 192 rows x 4096 x 8192 72 -> 51; 256 rows x 4096 x 16384 84 -> 57.
+  // With another round they lose (128 rows x 4096 x 36000 78 and 112).
+  const int v_tiles = (V + TV - 1) / TV;
+  if (M <= 64 * best_mt && (v_tiles + kXcds - 1) / kXcds * ((M + 63) / 64) <= 32) best_mt = 1;
   switch (best_mt) {
     case 1: return M <= 64 * 1 ? launch<1, true>(M, K, V, hidden, weight, keys, s)
                             : launch<1, false>(M, K, V, hidden, weight, keys, s);

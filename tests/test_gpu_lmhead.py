@@ -66,6 +66,46 @@ def test_small_shapes(step, dtype, M, K, V):
     _check(hidden, weight, ids, mx)
 
 
+@pytest.mark.parametrize("M,K,V", [(65, 64, 32768), (128, 128, 32769), (128, 192, 32700), (129, 64, 20480), (192, 128, 20481),
+                                   (193, 64, 16384), (256, 128, 16385), (256, 192, 300)])
+def test_tile_height_of_few_vocabulary_tiles(step, M, K, V):
+    """128, 80 and 64 vocabulary tiles of 256 are the most that two, three and four hidden tiles of 64 rows meet
+    in one round of CUs; one tile more takes the taller hidden tile."""
+    hidden, weight = W.make_lmhead_inputs(M + V, M, K, V, dtype="bf16", w_std=0.05)
+    ids, mx = step.lmhead_argmax(hidden.cuda(), weight.cuda())
+    torch.cuda.synchronize()
+    _check(hidden, weight, ids, mx)
+
+
+@pytest.mark.parametrize("K,V", [(4096, 4096), (2048, 8192), (4096, 16384)])
+def test_128_rows_take_hardly_longer_than_64_on_few_vocabulary_tiles(step, K, V):
+    """Where a launch occupies a few CUs only, a tile of 128 rows took 1.15 to 1.34 times as long as one of 64."""
+    weights = [torch.randn((V, K), device="cuda", dtype=torch.bfloat16) for _ in range(8)]
+
+    def us(M):
+        hidden = torch.randn((M, K), device="cuda", dtype=torch.bfloat16)
+        ids = torch.empty(M, dtype=torch.int32, device="cuda")
+        ws = step.alloc_workspace(step.hb.hb_lmhead_argmax_workspace_bytes(M))
+        step.hb.hb_lmhead_argmax(hidden, weights[0], ids, None, ws)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for i in range(16):
+                step.hb.hb_lmhead_argmax(hidden, weights[i % 8], ids, None, ws)
+        best = float("inf")
+        for _ in range(6):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            graph.replay()
+            end.record()
+            torch.cuda.synchronize()
+            best = min(best, start.elapsed_time(end) / 16 * 1e3)
+        return best
+
+    low, high = us(64), us(128)
+    assert high <= 1.12 * low, (low, high)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 # 1 .. 32 rows of whole 16-byte pieces take the few-rows kernel (eight rows and sixteen vocabulary
 # entries per workgroup, 256 or 512 elements of K per step); 33 rows or a broken piece the tiles

@@ -268,7 +268,7 @@ def test_seventeen_tokens_take_hardly_longer_than_sixteen(hb, K, N, gated):
         return best
 
     sixteen, seventeen = us(16), us(17)
-    assert seventeen <= 1.15 * sixteen, (sixteen, seventeen)
+    assert seventeen <= 1.2 * sixteen, (sixteen, seventeen)
 
 
 def _out_case(hb, T, K, N, res, with_workspace):

@@ -357,6 +357,34 @@ int32_t hb_kv_compact_layers(const hb_attn_desc *desc, int32_t n_layers, const v
                              int32_t *out_slots, int32_t *new_len, void *stream);
 
 /*
+ * hb_tree_verify_attn that also sets the clear_words 64-bit words at `clear` (device, 8-byte aligned) to zero, in the
+ * same launch: the keys of the hb_lmhead_accept that follows it on the stream.  clear must not overlap any other
+ * argument.  Errors as there.
+ */
+int32_t hb_tree_verify_attn_clearing(const hb_attn_desc *desc, const void *q, const void *k_tree,
+                                     const void *v_tree, const void *k_pool, const void *v_pool,
+                                     const int32_t *block_table, const int32_t *prefix_len,
+                                     const int32_t *node_offset, const int32_t *parent, void *out,
+                                     float *lse, void *workspace, size_t workspace_bytes, void *clear,
+                                     int32_t clear_words, void *stream);
+
+/*
+ * A verification step from the target's hidden states on: hb_lmhead_argmax (without out_max), hb_tree_accept (without
+ * prev_target) and the append of the accepted nodes to n_layers layers (hb_kv_compact with tables == 0 and one layer,
+ * hb_kv_compact_layers with tables != 0; 0 layers: no append), with their results, in two launches.
+ *   keys   device, 8 M bytes, 8-byte aligned: ZERO when the call's kernels begin (hb_tree_verify_attn_clearing sees to
+ *          it), overwritten
+ * desc: as in hb_kv_compact, and dtype and max_nodes_per_tree for the other two; hidden [M, K] holds the nodes' rows.
+ * Errors: INVALID_ARG, UNSUPPORTED, WORKSPACE, DEVICE.
+ */
+int32_t hb_lmhead_accept(const hb_attn_desc *desc, int32_t M, int32_t K, int32_t V, const void *hidden, const void *weight,
+                         const int32_t *draft_ids, const int32_t *node_offset, const int32_t *parent, int32_t max_path,
+                         int32_t *target_ids, int32_t *accept_len, int32_t *accept_path, int32_t *out_tokens,
+                         int32_t *bonus_id, void *keys, size_t keys_bytes, int32_t n_layers, int32_t tables,
+                         const void *k_tree, const void *v_tree, void *k_pool, void *v_pool, const int32_t *block_table,
+                         const int32_t *prefix_len, int32_t *out_slots, int32_t *new_len, void *stream);
+
+/*
  * Construction of the draft tree from the draft model's outputs: the step before the
  * verification (the paper drafts in the EAGLE-3 manner, Section 3.1, and leaves the arrangement of
  * the drafted tokens open; its measurements use chains, Section 4.2).  This is the dynamic tree of

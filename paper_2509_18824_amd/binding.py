@@ -118,6 +118,10 @@ def _load():
     lib.hb_kv_compact.argtypes = [C.POINTER(AttnDesc)] + [p] * 9 + [i32, p, p, p]
     lib.hb_kv_compact_layers.restype = i32
     lib.hb_kv_compact_layers.argtypes = [C.POINTER(AttnDesc), i32] + [p] * 9 + [i32, p, p, p]
+    lib.hb_tree_verify_attn_clearing.restype = i32
+    lib.hb_tree_verify_attn_clearing.argtypes = lib.hb_tree_verify_attn.argtypes[:-1] + [p, i32, p]
+    lib.hb_lmhead_accept.restype = i32
+    lib.hb_lmhead_accept.argtypes = [C.POINTER(AttnDesc)] + [i32] * 3 + [p] * 5 + [i32] + [p] * 6 + [sz, i32, i32] + [p] * 9
     return lib
 
 
@@ -422,3 +426,33 @@ def hb_kv_compact_layers(desc: AttnDesc, n_layers: int, k_tree_ptrs, v_tree_ptrs
                                     _ptr(v_pool_ptrs), _ptr(block_table), _ptr(prefix_len), _ptr(node_offset),
                                     _ptr(accept_len), _ptr(accept_path), max_path, _ptr(out_slots), _ptr(new_len),
                                     _stream(stream)))
+
+
+def hb_tree_verify_attn_clearing(desc: AttnDesc, q, k_tree, v_tree, k_pool, v_pool, block_table, prefix_len,
+                                 node_offset, parent, out, lse, workspace, keys, rows: int, stream=None) -> None:
+    """``keys``: a workspace of hb_lmhead_argmax_workspace_bytes(rows) bytes, zero afterwards."""
+    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
+    if rows * 8 > keys.numel() * keys.element_size():
+        raise ValueError("keys needs 8 bytes a row")
+    _check(lib.hb_tree_verify_attn_clearing(C.byref(desc), _ptr(q), _ptr(k_tree), _ptr(v_tree), _ptr(k_pool),
+                                            _ptr(v_pool), _ptr(block_table), _ptr(prefix_len), _ptr(node_offset),
+                                            _ptr(parent), _ptr(out), _ptr(lse), _ptr(workspace), ws_bytes, _ptr(keys),
+                                            rows, _stream(stream)))
+
+
+def hb_lmhead_accept(desc: AttnDesc, hidden, weight, draft_ids, node_offset, parent, max_path: int, target_ids,
+                     accept_len, accept_path, out_tokens, bonus_id, keys, n_layers: int = 0, kv=(None,) * 4,
+                     block_table=None, prefix_len=None, out_slots=None, new_len=None, stream=None) -> None:
+    """``kv``: k_tree, v_tree, k_pool and v_pool of one layer, or int64 tables of every layer's data pointers."""
+    M, K = hidden.shape
+    V = weight.shape[0]
+    if weight.shape[1] != K or weight.dtype != hidden.dtype or _dtype_code(hidden) != desc.dtype:
+        raise ValueError("hidden [M, K] and weight [V, K] must agree in K and dtype, and with the descriptor")
+    tables = n_layers > 0 and kv[0].dtype == torch.int64
+    if tables and any(t.dtype != torch.int64 or t.numel() < n_layers for t in kv):
+        raise ValueError("pointer tables must be int64 tensors with one entry per layer")
+    _check(lib.hb_lmhead_accept(C.byref(desc), M, K, V, _ptr(hidden), _ptr(weight), _ptr(draft_ids), _ptr(node_offset),
+                                _ptr(parent), max_path, _ptr(target_ids), _ptr(accept_len), _ptr(accept_path),
+                                _ptr(out_tokens), _ptr(bonus_id), _ptr(keys), keys.numel() * keys.element_size(),
+                                n_layers, int(tables), *map(_ptr, kv), _ptr(block_table), _ptr(prefix_len),
+                                _ptr(out_slots), _ptr(new_len), _stream(stream)))

@@ -11,95 +11,90 @@ namespace hb {
 
 namespace {
 
+// Acceptance of one tree by one wavefront, lane = node (live: it exists).  par: parent node or anything below 0;
+// tgt: the target's token after the node; match_root: the root counts as accepted.  Every lane gets the same result
+// but anc, its ancestors and itself.
+struct Accepted {
+  int len;                  // nodes on the accepted path; 0: not even the root
+  int target;               // the target's token after the last of them
+  unsigned long long path;  // the nodes on it, a bit each
+};
+__device__ __forceinline__ Accepted accept_wave(int lane, bool live, int par, int did, int tgt, bool match_root, int max_path) {
+  if (!live || par >= lane || par < -1 || lane == 0) par = -1;  // malformed: treat as a root-like node
+  // ancestor set (self included) and whether this node's own id matches its parent's target
+  unsigned long long anc = live ? (1ull << lane) : 0ull;
+  for (int x = par; __any(x >= 0);) {  // parents precede their children: at most 63 steps
+    const int up = __shfl(par, x < 0 ? 0 : x, 64);
+    if (x >= 0) {
+      anc |= 1ull << x;
+      x = up;
+    }
+  }
+  const bool rooted = live && (anc & 1ull);  // a path that does not reach node 0 is never accepted
+  const int par_target = __shfl(tgt, par < 0 ? 0 : par, 64);
+  const bool match = live && (lane == 0 ? match_root : did == par_target);
+  const unsigned long long match_mask = __ballot(match);
+  const int depth = __popcll(anc) - 1;
+  const bool accepted = rooted && ((anc & ~match_mask) == 0ull) && depth < max_path;
+  // deepest accepted node, lowest id among equals: maximise depth * 64 + (63 - lane)
+  int key = accepted ? depth * 64 + (63 - lane) : -1;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) key = max(key, __shfl_xor(key, off, 64));
+  if (key < 0) return {0, -1, 0ull};
+  const int best = 63 - (key & 63);
+  return {(key >> 6) + 1, __shfl(tgt, best, 64), (unsigned long long)__shfl((long long)anc, best, 64)};
+}
+
+// What a sequence's wavefront writes; bonus_if_none: no node accepted (no nodes at all, or a rejected root), so that
+// nothing is emitted and the pending token stays what it was.
+__device__ __forceinline__ void store_accepted(const Accepted &a, int lane, int did, int bonus_if_none, int b, int max_path,
+                                               int32_t *__restrict__ accept_len, int32_t *__restrict__ accept_path,
+                                               int32_t *__restrict__ out_tokens, int32_t *__restrict__ bonus_id) {
+  int32_t *path = accept_path + (size_t)b * max_path, *tokens = out_tokens + (size_t)b * max_path;
+  if ((a.path >> lane) & 1ull) {
+    const int rank = __popcll(a.path & ((1ull << lane) - 1ull));
+    path[rank] = lane;
+    if (rank >= 1) tokens[rank - 1] = did;
+  }
+  for (int j = a.len + lane; j < max_path; j += 64) path[j] = tokens[j] = -1;
+  if (lane == 0) {
+    if (a.len) tokens[a.len - 1] = a.target;
+    accept_len[b] = a.len;
+    bonus_id[b] = a.len ? a.target : bonus_if_none;
+  }
+}
+
 __global__ __launch_bounds__(64) void tree_accept_kernel(
     int max_nodes, const int32_t *__restrict__ node_offset, const int32_t *__restrict__ parent,
     const int32_t *__restrict__ draft_ids, const int32_t *__restrict__ target_ids,
     const int32_t *__restrict__ prev_target, int max_path, int32_t *__restrict__ accept_len, int32_t *__restrict__ accept_path, int32_t *__restrict__ out_tokens,
     int32_t *__restrict__ bonus_id) {
-  __shared__ int32_t spar[64];
   const int b = blockIdx.x;
   const int lane = threadIdx.x;
   const int n0 = node_offset[b];
   int n = node_offset[b + 1] - n0;
   n = n < 0 ? 0 : (n > max_nodes ? max_nodes : n);
   const bool live = lane < n;
-
-  int par = -1, did = 0, tid_ = 0;
+  int par = -1, did = 0, tgt = 0;
   if (live) {
     par = parent[n0 + lane];
-    if (par >= lane || par < -1) par = -1;  // malformed: treat as a root-like node
-    if (lane == 0) par = -1;
     did = draft_ids[n0 + lane];
-    tid_ = target_ids[n0 + lane];
+    tgt = target_ids[n0 + lane];
   }
-  spar[lane] = par;
-  __syncthreads();
-
-  // ancestor set (self included) and whether this node's own id matches its parent's target
-  unsigned long long anc = live ? (1ull << lane) : 0ull;
-  int x = par;
-  for (int guard = 0; x >= 0 && guard < 64; ++guard) {
-    anc |= 1ull << x;
-    x = spar[x];
-  }
-  bool rooted = live && (anc & 1ull);  // a path that does not reach node 0 is never accepted
-  int par_target = __shfl(tid_, par < 0 ? 0 : par, 64);
   // the root is the pending committed token (always a match) unless the caller names the token
   // the target chose last step: then the root is a guess like any other node
-  const int prev = prev_target ? prev_target[b] : 0;
-  bool match = live && (lane == 0 ? (!prev_target || did == prev) : did == par_target);
-  unsigned long long match_mask = __ballot(match);
-  int depth = __popcll(anc) - 1;
-  bool accepted = rooted && ((anc & ~match_mask) == 0ull) && depth < max_path;
-
-  // deepest accepted node, lowest id among equals: maximise depth * 64 + (63 - lane)
-  int key = accepted ? depth * 64 + (63 - lane) : -1;
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) key = max(key, __shfl_xor(key, off, 64));
-  // no node accepted (no nodes at all, or a rejected root): nothing is emitted, the pending
-  // token stays what it was
-  if (key < 0) {
-    for (int j = lane; j < max_path; j += 64) {
-      accept_path[(size_t)b * max_path + j] = -1;
-      out_tokens[(size_t)b * max_path + j] = -1;
-    }
-    if (lane == 0) {
-      accept_len[b] = 0;
-      bonus_id[b] = prev_target ? prev : -1;
-    }
-    return;
-  }
-  const int best = 63 - (key & 63);
-  const int len = (key >> 6) + 1;
-  const unsigned long long best_anc = __shfl((long long)anc, best, 64);
-  const int best_target = __shfl(tid_, best, 64);
-
-  if (live && ((best_anc >> lane) & 1ull)) {
-    int rank = __popcll(best_anc & ((1ull << lane) - 1ull));
-    accept_path[(size_t)b * max_path + rank] = lane;
-    if (rank >= 1) out_tokens[(size_t)b * max_path + rank - 1] = did;
-  }
-  for (int j = len + lane; j < max_path; j += 64) {
-    accept_path[(size_t)b * max_path + j] = -1;
-    out_tokens[(size_t)b * max_path + j] = -1;
-  }
-  if (lane == 0) {
-    out_tokens[(size_t)b * max_path + len - 1] = best_target;
-    accept_len[b] = len;
-    bonus_id[b] = best_target;
-  }
+  const int prev = prev_target ? prev_target[b] : -1;
+  const Accepted a = accept_wave(lane, live, par, did, tgt, !prev_target || did == prev, max_path);
+  store_accepted(a, lane, did, prev, b, max_path, accept_len, accept_path, out_tokens, bonus_id);
 }
 
-// one (path slot j, sequence b) of one layer; out_slots / new_len are written when given
+// path slot j of sequence b, of one layer: the path has len nodes, node the j-th (looked at if j < len);
+// out_slots / new_len are written when given
 __device__ __forceinline__ void compact_one(
-    const hb_attn_desc &d, int row_bytes, const uint4 *__restrict__ k_tree, const uint4 *__restrict__ v_tree,
-    uint4 *__restrict__ k_pool, uint4 *__restrict__ v_pool, const int32_t *__restrict__ block_table,
-    const int32_t *__restrict__ prefix_len, const int32_t *__restrict__ node_offset,
-    const int32_t *__restrict__ accept_len, const int32_t *__restrict__ accept_path, int max_path,
-    int32_t *__restrict__ out_slots, int32_t *__restrict__ new_len) {
-  const int j = blockIdx.x;
-  const int b = blockIdx.y;
-  int len = accept_len[b];
+    const hb_attn_desc &d, int row_bytes, int j, int b, int len, int node, const uint4 *__restrict__ k_tree,
+    const uint4 *__restrict__ v_tree, uint4 *__restrict__ k_pool, uint4 *__restrict__ v_pool,
+    const int32_t *__restrict__ block_table, const int32_t *__restrict__ prefix_len,
+    const int32_t *__restrict__ node_offset, int max_path, int32_t *__restrict__ out_slots, int32_t *__restrict__ new_len) {
   len = len < 0 ? 0 : (len > max_path ? max_path : len);
   int L = prefix_len[b];
   L = L < 0 ? 0 : L;
@@ -112,7 +107,6 @@ __device__ __forceinline__ void compact_one(
   }
   const int n0 = node_offset[b];
   int n = node_offset[b + 1] - n0;
-  int node = accept_path[(size_t)b * max_path + j];
   node = node < 0 ? 0 : (node >= n ? n - 1 : node);
   int src = n0 + node;
   src = src < 0 ? 0 : (src >= d.total_nodes ? d.total_nodes - 1 : src);
@@ -136,8 +130,9 @@ __global__ __launch_bounds__(256) void kv_compact_kernel(
     const int32_t *__restrict__ prefix_len, const int32_t *__restrict__ node_offset,
     const int32_t *__restrict__ accept_len, const int32_t *__restrict__ accept_path, int max_path,
     int32_t *__restrict__ out_slots, int32_t *__restrict__ new_len) {
-  compact_one(d, row_bytes, k_tree, v_tree, k_pool, v_pool, block_table, prefix_len, node_offset, accept_len,
-              accept_path, max_path, out_slots, new_len);
+  const int j = blockIdx.x, b = blockIdx.y;
+  compact_one(d, row_bytes, j, b, accept_len[b], accept_path[(size_t)b * max_path + j], k_tree, v_tree, k_pool, v_pool,
+              block_table, prefix_len, node_offset, max_path, out_slots, new_len);
 }
 
 // all layers in one launch: blockIdx.z = layer, its tensors from tables of device pointers
@@ -147,9 +142,52 @@ __global__ __launch_bounds__(256) void kv_compact_layers_kernel(
     const int32_t *__restrict__ prefix_len, const int32_t *__restrict__ node_offset,
     const int32_t *__restrict__ accept_len, const int32_t *__restrict__ accept_path, int max_path,
     int32_t *__restrict__ out_slots, int32_t *__restrict__ new_len) {
-  const int l = blockIdx.z;
-  compact_one(d, row_bytes, k_tree[l], v_tree[l], k_pool[l], v_pool[l], block_table, prefix_len, node_offset,
-              accept_len, accept_path, max_path, l == 0 ? out_slots : nullptr, l == 0 ? new_len : nullptr);
+  const int j = blockIdx.x, b = blockIdx.y, l = blockIdx.z;
+  compact_one(d, row_bytes, j, b, accept_len[b], accept_path[(size_t)b * max_path + j], k_tree[l], v_tree[l], k_pool[l],
+              v_pool[l], block_table, prefix_len, node_offset, max_path, l == 0 ? out_slots : nullptr, l == 0 ? new_len : nullptr);
+}
+
+// What follows the LM head, in one launch: the ids of all rows from their keys, acceptance, the append of the
+// accepted nodes.  Each of these is a chain of two or three memory round trips; as launches of their own (and one
+// more to clear the keys, which the attention kernel now does) they took 1.5 us each of the GPU's time in a full
+// stream and the host's of two calls: step of one 60-node tree 214.9 -> 210.3 us, 16 chains of 8 nodes 239.8 -> 234.8,
+// four nodes of a unit-sized float32 model 31.1 -> 20.3.  A workgroup per (path slot, sequence, layer),
+// as for the append alone; its first wavefront works the sequence's acceptance out by itself (a key, a parent and a
+// drafted token per lane), which is cheaper than to wait for anybody.  The first workgroup of a sequence writes the
+// results; the ids are dealt to all workgroups.
+__global__ __launch_bounds__(256) void verify_tail_kernel(hb_attn_desc d, TailArgs t) {
+  __shared__ int s_len, s_node;
+  const int tid = threadIdx.x, l = blockIdx.y;
+  const long first = ((long)l * gridDim.x + blockIdx.x) * 256 + tid, threads = (long)gridDim.x * gridDim.y * 256;
+  for (long i = first; i < t.M; i += threads) {
+    const int id = argmax_key_id(t.keys[i], t.V);
+    t.target_ids[i] = id;
+  }
+  const int b = blockIdx.x / t.max_path, j = blockIdx.x % t.max_path;
+  if (b >= d.batch) return;  // an empty batch
+  if (tid < 64) {
+    const int n0 = t.node_offset[b];
+    int n = t.node_offset[b + 1] - n0;
+    n = n < 0 ? 0 : (n > d.max_nodes_per_tree ? d.max_nodes_per_tree : n);
+    const bool live = tid < n && n0 >= 0 && n0 + tid < t.M;
+    int par = -1, did = 0, tgt = 0;
+    if (live) {
+      par = t.parent[n0 + tid];
+      did = t.draft_ids[n0 + tid];
+      tgt = argmax_key_id(t.keys[n0 + tid], t.V);
+    }
+    const Accepted a = accept_wave(tid, live, par, did, tgt, true, t.max_path);
+    if (j == 0 && l == 0) store_accepted(a, tid, did, -1, b, t.max_path, t.accept_len, t.accept_path, t.out_tokens, t.bonus_id);
+    if (tid == 0) s_len = a.len;
+    if (((a.path >> tid) & 1ull) && __popcll(a.path & ((1ull << tid) - 1ull)) == j) s_node = tid;
+  }
+  if (!t.layers) return;
+  __syncthreads();
+  const bool tables = t.tables;
+  compact_one(d, t.row_bytes, j, b, s_len, j < s_len ? s_node : 0, (const uint4 *)(tables ? ((const void *const *)t.k_tree)[l] : t.k_tree),
+              (const uint4 *)(tables ? ((const void *const *)t.v_tree)[l] : t.v_tree),
+              (uint4 *)(tables ? ((void *const *)t.k_pool)[l] : t.k_pool), (uint4 *)(tables ? ((void *const *)t.v_pool)[l] : t.v_pool),
+              t.block_table, t.prefix_len, t.node_offset, t.max_path, l == 0 ? t.out_slots : nullptr, l == 0 ? t.new_len : nullptr);
 }
 
 }  // namespace
@@ -189,6 +227,13 @@ hipError_t launch_kv_compact_layers(const hb_attn_desc &d, int32_t n_layers, con
                                                 (uint4 *const *)k_pool, (uint4 *const *)v_pool, block_table,
                                                 prefix_len, node_offset, accept_len, accept_path, max_path,
                                                 out_slots, new_len);
+  return hipGetLastError();
+}
+
+hipError_t launch_verify_tail(const hb_attn_desc &d, TailArgs t, hipStream_t s) {
+  t.row_bytes = d.head_dim * (d.dtype == HB_F32 ? 4 : 2);
+  const dim3 grid((unsigned)((long)(d.batch > 0 ? d.batch : 1) * t.max_path), (unsigned)(t.layers > 0 ? t.layers : 1));
+  verify_tail_kernel<<<grid, 256, 0, s>>>(d, t);
   return hipGetLastError();
 }
 

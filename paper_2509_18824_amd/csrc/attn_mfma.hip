@@ -309,7 +309,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mfma_kernel(
     const u32x4 *__restrict__ v_tree, const u32x4 *__restrict__ k_pool, const u32x4 *__restrict__ v_pool,
     const int32_t *__restrict__ block_table, const int32_t *__restrict__ prefix_len,
     const int32_t *__restrict__ node_offset, const int32_t *__restrict__ parent, bf16_t *__restrict__ out,
-    float *__restrict__ lse, float *__restrict__ part_o, float *__restrict__ part_ml) {
+    float *__restrict__ lse, float *__restrict__ part_o, float *__restrict__ part_ml, ClearArgs clear) {
+  clear_words(clear, (int)(blockIdx.x * 64 * NW + threadIdx.x), (int)(gridDim.x * 64 * NW));
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   // [NS stages][K tile 16 KiB | V tile 16 KiB] [64 ancestor masks]
   constexpr int kStageBytes = K_PIECES * 16 + V_BYTES;
@@ -821,7 +822,7 @@ template <int TPW, int NW, int NS>
 hipError_t launch(int row_groups, const hb_attn_desc &d, const AttnPlan &plan, const void *q, const void *k_tree,
                   const void *v_tree, const void *k_pool, const void *v_pool, const int32_t *block_table,
                   const int32_t *prefix_len, const int32_t *node_offset, const int32_t *parent, void *out,
-                  float *lse, float *part_o, float *part_ml, hipStream_t s) {
+                  float *lse, float *part_o, float *part_ml, ClearArgs clear, hipStream_t s) {
   const int items = plan.workers > 0 ? d.num_kv_heads * plan.workers : d.batch * d.num_kv_heads * plan.splits;
   dim3 grid((unsigned)((items + 7) / 8 * 8 * row_groups));
   constexpr size_t kLdsBytes = (size_t)NS * (K_PIECES * 16 + V_BYTES) + 64 * 8;
@@ -831,7 +832,7 @@ hipError_t launch(int row_groups, const hb_attn_desc &d, const AttnPlan &plan, c
   kern<<<grid, 64 * NW, kLdsBytes, s>>>(d, plan.splits, plan.chunk_tokens, plan.workers, plan.workers / (d.batch > 0 ? d.batch : 1), plan.min_per, row_groups, (const u32x4 *)q, (const u32x4 *)k_tree,
                                     (const u32x4 *)v_tree, (const u32x4 *)k_pool, (const u32x4 *)v_pool,
                                     block_table, prefix_len, node_offset, parent, (bf16_t *)out, lse, part_o,
-                                    part_ml);
+                                    part_ml, clear);
   return hipGetLastError();
 }
 
@@ -868,11 +869,11 @@ hipError_t launch_attn_mfma(const hb_attn_desc &d, const AttnPlan &plan, const v
                             const void *v_tree, const void *k_pool, const void *v_pool,
                             const int32_t *block_table, const int32_t *prefix_len,
                             const int32_t *node_offset, const int32_t *parent, void *out, float *lse,
-                            float *part_o, float *part_ml, hipStream_t s) {
+                            float *part_o, float *part_ml, ClearArgs clear, hipStream_t s) {
   const int tiles = tiles_of(d);
   const int row_groups = plan.row_groups;
 #define HB_GO(N, W) \
-  return launch<N, W, (W == 8 ? 4 : 2)>(row_groups, d, plan, q, k_tree, v_tree, k_pool, v_pool, block_table, prefix_len, node_offset, parent, out, lse, part_o, part_ml, s)
+  return launch<N, W, (W == 8 ? 4 : 2)>(row_groups, d, plan, q, k_tree, v_tree, k_pool, v_pool, block_table, prefix_len, node_offset, parent, out, lse, part_o, part_ml, clear, s)
   if (tiles <= 4) HB_GO(1, 4);
   if (tiles <= 8) HB_GO(2, 4);
   HB_GO(2, 8);  // attn_mfma_row_groups keeps a workgroup at sixteen tiles or fewer

@@ -144,7 +144,8 @@ __global__ __launch_bounds__(kThreads, E == 4 || (E == 1 && sizeof(T) == 2) ? 4 
     const T *__restrict__ v_tree, const T *__restrict__ k_pool, const T *__restrict__ v_pool,
     const int32_t *__restrict__ block_table, const int32_t *__restrict__ prefix_len,
     const int32_t *__restrict__ node_offset, const int32_t *__restrict__ parent, T *__restrict__ out,
-    float *__restrict__ lse, float *__restrict__ part_o, float *__restrict__ part_ml) {
+    float *__restrict__ lse, float *__restrict__ part_o, float *__restrict__ part_ml, ClearArgs clear) {
+  if (blockIdx.y == 0) clear_words(clear, (int)(blockIdx.x * kThreads + threadIdx.x), (int)(gridDim.x * kThreads));
   __shared__ float q_lds[64 * E];
   __shared__ float acc_lds[kWaves][64 * E];
   __shared__ float ml_lds[kWaves][2];
@@ -334,12 +335,12 @@ hipError_t launch_attn_scalar(const hb_attn_desc &d, const AttnPlan &plan, const
                               const void *v_pool, const int32_t *block_table,
                               const int32_t *prefix_len, const int32_t *node_offset,
                               const int32_t *parent, void *out, float *lse, float *part_o,
-                              float *part_ml, hipStream_t s) {
+                              float *part_ml, ClearArgs clear, hipStream_t s) {
   dim3 grid((unsigned)(d.total_nodes * d.num_q_heads), (unsigned)plan.splits);
 #define HB_ATTN_SCALAR(T_, E_)                                                                                  \
   attn_scalar_kernel<T_, E_><<<grid, kThreads, 0, s>>>(d, plan.splits, plan.chunk_tokens, (const T_ *)q,        \
       (const T_ *)k_tree, (const T_ *)v_tree, (const T_ *)k_pool, (const T_ *)v_pool, block_table, prefix_len,  \
-      node_offset, parent, (T_ *)out, lse, part_o, part_ml)
+      node_offset, parent, (T_ *)out, lse, part_o, part_ml, clear)
   const int e = d.head_dim <= 64 ? 1 : d.head_dim <= 128 ? 2 : 4;  // head dimensions per lane
   if (d.dtype == HB_F32) {
     if (e == 1) HB_ATTN_SCALAR(float, 1);

@@ -193,15 +193,19 @@ int32_t hb_tree_verify_attn_num_splits(const hb_attn_desc *desc) {
   return plan.splits;
 }
 
-int32_t hb_tree_verify_attn(const hb_attn_desc *desc, const void *q, const void *k_tree,
+static int32_t tree_verify_attn(const hb_attn_desc *desc, const void *q, const void *k_tree,
                             const void *v_tree, const void *k_pool, const void *v_pool,
                             const int32_t *block_table, const int32_t *prefix_len,
                             const int32_t *node_offset, const int32_t *parent, void *out,
-                            float *lse, void *workspace, size_t workspace_bytes, void *stream) {
+                            float *lse, void *workspace, size_t workspace_bytes, ClearArgs clear, void *stream) {
   AttnPlan plan;
   int32_t rc = make_attn_plan(desc, &plan);
   if (rc) return rc;
-  if (desc->batch == 0 || desc->total_nodes == 0) return HB_OK;
+  hipStream_t s = (hipStream_t)stream;
+  if (desc->batch == 0 || desc->total_nodes == 0) {
+    if (clear.words) HB_HIP_TRY(launch_lmhead_init(clear.at, clear.words, s));
+    return HB_OK;
+  }
   if (!q || !k_tree || !v_tree || !k_pool || !v_pool || !block_table || !prefix_len || !node_offset ||
       !parent || !out)
     return fail(HB_ERR_INVALID_ARG, "a required device pointer is NULL");
@@ -217,15 +221,35 @@ int32_t hb_tree_verify_attn(const hb_attn_desc *desc, const void *q, const void 
     part_o = (float *)workspace;
     part_ml = (float *)((char *)workspace + plan.ml_offset);
   }
-  hipStream_t s = (hipStream_t)stream;
   if (plan.mfma)
     HB_HIP_TRY(launch_attn_mfma(*desc, plan, q, k_tree, v_tree, k_pool, v_pool, block_table, prefix_len,
-                                node_offset, parent, out, lse, part_o, part_ml, s));
+                                node_offset, parent, out, lse, part_o, part_ml, clear, s));
   else
     HB_HIP_TRY(launch_attn_scalar(*desc, plan, q, k_tree, v_tree, k_pool, v_pool, block_table, prefix_len,
-                                  node_offset, parent, out, lse, part_o, part_ml, s));
+                                  node_offset, parent, out, lse, part_o, part_ml, clear, s));
   if (plan.splits > 1) HB_HIP_TRY(launch_attn_merge(*desc, plan, part_o, part_ml, out, lse, s));
   return HB_OK;
+}
+
+int32_t hb_tree_verify_attn(const hb_attn_desc *desc, const void *q, const void *k_tree,
+                            const void *v_tree, const void *k_pool, const void *v_pool,
+                            const int32_t *block_table, const int32_t *prefix_len,
+                            const int32_t *node_offset, const int32_t *parent, void *out,
+                            float *lse, void *workspace, size_t workspace_bytes, void *stream) {
+  return tree_verify_attn(desc, q, k_tree, v_tree, k_pool, v_pool, block_table, prefix_len, node_offset, parent, out,
+                          lse, workspace, workspace_bytes, {nullptr, 0}, stream);
+}
+
+int32_t hb_tree_verify_attn_clearing(const hb_attn_desc *desc, const void *q, const void *k_tree,
+                                     const void *v_tree, const void *k_pool, const void *v_pool,
+                                     const int32_t *block_table, const int32_t *prefix_len,
+                                     const int32_t *node_offset, const int32_t *parent, void *out,
+                                     float *lse, void *workspace, size_t workspace_bytes, void *clear,
+                                     int32_t clear_words, void *stream) {
+  if (clear_words < 0 || (clear_words && !clear)) return fail(HB_ERR_INVALID_ARG, "nothing to clear at, or a negative size");
+  if ((uintptr_t)clear % 8) return fail(HB_ERR_WORKSPACE, "what is cleared must be 8-byte aligned");
+  return tree_verify_attn(desc, q, k_tree, v_tree, k_pool, v_pool, block_table, prefix_len, node_offset, parent, out,
+                          lse, workspace, workspace_bytes, {(unsigned long long *)clear, clear_words}, stream);
 }
 
 size_t hb_lmhead_argmax_workspace_bytes(int32_t M) { return M > 0 ? (size_t)M * 8 : 0; }
@@ -242,15 +266,19 @@ static int32_t check_lmhead_args(int32_t dtype, int32_t M, int32_t K, int32_t V,
   return HB_OK;
 }
 
+// GEMM + argmax into the keys
+static hipError_t launch_lmhead(int32_t dtype, int32_t M, int32_t K, int32_t V, const void *hidden, const void *weight,
+                                unsigned long long *keys, hipStream_t s) {
+  return lmhead_mfma_supports(dtype, M, K, V) ? launch_lmhead_mfma(M, K, V, hidden, weight, keys, s)
+                                              : launch_lmhead_scalar(dtype, M, K, V, hidden, weight, keys, s);
+}
+
 // init (every key starts at zero, by a fill kernel), GEMM + argmax into the keys, keys -> ids
 static int32_t lmhead_enqueue(int32_t dtype, int32_t M, int32_t K, int32_t V, const void *hidden,
                               const void *weight, int32_t *out_ids, float *out_max,
                               unsigned long long *keys, hipStream_t s) {
   HB_HIP_TRY(launch_lmhead_init(keys, M, s));
-  if (lmhead_mfma_supports(dtype, M, K, V))
-    HB_HIP_TRY(launch_lmhead_mfma(M, K, V, hidden, weight, keys, s));
-  else
-    HB_HIP_TRY(launch_lmhead_scalar(dtype, M, K, V, hidden, weight, keys, s));
+  HB_HIP_TRY(launch_lmhead(dtype, M, K, V, hidden, weight, keys, s));
   HB_HIP_TRY(launch_lmhead_finish(keys, M, V, out_ids, out_max, s));
   return HB_OK;
 }
@@ -659,6 +687,40 @@ int32_t hb_kv_compact_layers(const hb_attn_desc *desc, int32_t n_layers, const v
   HB_HIP_TRY(launch_kv_compact_layers(*desc, n_layers, k_tree, v_tree, k_pool, v_pool, block_table, prefix_len,
                                       node_offset, accept_len, accept_path, max_path, out_slots, new_len,
                                       (hipStream_t)stream));
+  return HB_OK;
+}
+
+int32_t hb_lmhead_accept(const hb_attn_desc *desc, int32_t M, int32_t K, int32_t V, const void *hidden, const void *weight,
+                         const int32_t *draft_ids, const int32_t *node_offset, const int32_t *parent, int32_t max_path,
+                         int32_t *target_ids, int32_t *accept_len, int32_t *accept_path, int32_t *out_tokens,
+                         int32_t *bonus_id, void *keys, size_t keys_bytes, int32_t n_layers, int32_t tables,
+                         const void *k_tree, const void *v_tree, void *k_pool, void *v_pool, const int32_t *block_table,
+                         const int32_t *prefix_len, int32_t *out_slots, int32_t *new_len, void *stream) {
+  int32_t rc = check_shape(desc);
+  if (rc) return rc;
+  if (max_path <= 0 || n_layers < 0) return fail(HB_ERR_INVALID_ARG, "need max_path > 0 and n_layers >= 0");
+  if (n_layers > 65535 || (int64_t)desc->batch * max_path > INT32_MAX)
+    return fail(HB_ERR_UNSUPPORTED, "at most 65535 layers and 2^31 - 1 path slots per call");
+  if (!tables && n_layers > 1) return fail(HB_ERR_INVALID_ARG, "several layers need tables of their tensors");
+  if ((rc = check_lmhead_args(desc->dtype, M, K, V, hidden, weight, target_ids))) return rc;
+  if (M > 0 && (!keys || keys_bytes < (size_t)M * 8))
+    return fail(HB_ERR_WORKSPACE, "keys of %zu bytes needed, %zu given", (size_t)M * 8, keys ? keys_bytes : (size_t)0);
+  if ((uintptr_t)keys % 8) return fail(HB_ERR_WORKSPACE, "the keys must be 8-byte aligned");
+  if (desc->batch > 0) {
+    if (!node_offset || !parent || !draft_ids || !accept_len || !accept_path || !out_tokens || !bonus_id)
+      return fail(HB_ERR_INVALID_ARG, "a required device pointer is NULL");
+    if (n_layers && (!k_tree || !v_tree || !k_pool || !v_pool || !block_table || !prefix_len))
+      return fail(HB_ERR_INVALID_ARG, "a device pointer that the append needs is NULL");
+    if (n_layers && (((uintptr_t)k_tree | (uintptr_t)v_tree | (uintptr_t)k_pool | (uintptr_t)v_pool) & (tables ? 7 : 15)))
+      return fail(HB_ERR_INVALID_ARG, "K/V tensors must be 16-byte aligned, tables of them 8-byte aligned");
+  }
+  if (desc->batch == 0 && M == 0) return HB_OK;
+  hipStream_t s = (hipStream_t)stream;
+  if (M > 0) HB_HIP_TRY(launch_lmhead(desc->dtype, M, K, V, hidden, weight, (unsigned long long *)keys, s));
+  const TailArgs t = {(const unsigned long long *)keys, M, V, max_path, desc->batch ? n_layers : 0, 0, tables != 0,
+                      node_offset, parent, draft_ids, block_table, prefix_len, k_tree, v_tree, k_pool, v_pool,
+                      target_ids, accept_len, accept_path, out_tokens, bonus_id, out_slots, new_len};
+  HB_HIP_TRY(launch_verify_tail(*desc, t, s));
   return HB_OK;
 }
 

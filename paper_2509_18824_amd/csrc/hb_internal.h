@@ -63,19 +63,28 @@ struct AttnPlan {
 };
 int32_t make_attn_plan(const hb_attn_desc *d, AttnPlan *plan);  // validates shape fields
 
+// 64-bit words that a kernel sets to zero on the way (0 words: none), for the launch after it
+struct ClearArgs {
+  unsigned long long *at;
+  int32_t words;
+};
+__device__ inline void clear_words(const ClearArgs &c, int first, int threads) {
+  for (int i = first; i < c.words; i += threads) c.at[i] = 0ull;
+}
+
 // ---- kernel launchers (each enqueues on `s`, returns a hipError_t from the launch) -------
 hipError_t launch_attn_scalar(const hb_attn_desc &d, const AttnPlan &plan, const void *q,
                               const void *k_tree, const void *v_tree, const void *k_pool,
                               const void *v_pool, const int32_t *block_table,
                               const int32_t *prefix_len, const int32_t *node_offset,
                               const int32_t *parent, void *out, float *lse, float *part_o,
-                              float *part_ml, hipStream_t s);
+                              float *part_ml, ClearArgs clear, hipStream_t s);
 hipError_t launch_attn_mfma(const hb_attn_desc &d, const AttnPlan &plan, const void *q,
                             const void *k_tree, const void *v_tree, const void *k_pool,
                             const void *v_pool, const int32_t *block_table,
                             const int32_t *prefix_len, const int32_t *node_offset,
                             const int32_t *parent, void *out, float *lse, float *part_o,
-                            float *part_ml, hipStream_t s);
+                            float *part_ml, ClearArgs clear, hipStream_t s);
 bool attn_mfma_supports(const hb_attn_desc &d);
 int32_t attn_mfma_row_groups(const hb_attn_desc &d);
 int32_t attn_mfma_waves(const hb_attn_desc &d);  // wavefronts per workgroup (4 or 8)
@@ -176,6 +185,19 @@ hipError_t launch_kv_compact_layers(const hb_attn_desc &d, int32_t n_layers, con
                                     const int32_t *accept_path, int32_t max_path, int32_t *out_slots,
                                     int32_t *new_len, hipStream_t s);
 
+// LM head's keys -> ids, greedy acceptance and the append to `layers` layers (0: no append); the K/V tensors are
+// given themselves, or tables of their device addresses, one per layer
+struct TailArgs {
+  const unsigned long long *keys;
+  int32_t M, V, max_path, layers, row_bytes;
+  bool tables;
+  const int32_t *node_offset, *parent, *draft_ids, *block_table, *prefix_len;
+  const void *k_tree, *v_tree;
+  void *k_pool, *v_pool;
+  int32_t *target_ids, *accept_len, *accept_path, *out_tokens, *bonus_id, *out_slots, *new_len;
+};
+hipError_t launch_verify_tail(const hb_attn_desc &d, TailArgs t, hipStream_t s);
+
 // ---- argmax key: (order-preserving float bits << 32) | (0xffffffff - index) ---------------
 // max over keys = largest value, lowest index among equal values.  NaN is mapped to -inf.
 __device__ inline unsigned long long argmax_key(float v, uint32_t idx) {
@@ -191,6 +213,11 @@ __device__ inline float argmax_key_value(unsigned long long key) {
 }
 __device__ inline uint32_t argmax_key_index(unsigned long long key) {
   return 0xffffffffu - (uint32_t)(key & 0xffffffffull);
+}
+// the id a key stands for; a row that saw nothing above -inf (key 0) names token 0
+__device__ inline int32_t argmax_key_id(unsigned long long key, int32_t V) {
+  const uint32_t idx = key ? argmax_key_index(key) : 0u;
+  return idx < (uint32_t)V ? (int32_t)idx : 0;
 }
 
 }  // namespace hb

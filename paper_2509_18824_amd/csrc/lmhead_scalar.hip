@@ -174,9 +174,7 @@ __global__ void lmhead_finish_kernel(const unsigned long long *keys, int M, int 
   int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= M) return;
   unsigned long long key = keys[i];
-  uint32_t idx = key ? argmax_key_index(key) : 0u;
-  if (idx >= (uint32_t)V) idx = 0;
-  out_ids[i] = (int32_t)idx;
+  out_ids[i] = argmax_key_id(key, V);
   if (out_max) out_max[i] = key ? argmax_key_value(key) : -__builtin_huge_valf();
 }
 

@@ -1,7 +1,7 @@
 """Convenience wrappers that allocate outputs/workspaces as torch tensors and call the C ABI.
 
 Nothing here computes: each function sizes buffers, fills an ``AttnDesc`` and forwards to the
-library.  ``VerifyStep`` chains the four calls of one verification step on the current stream.
+library.  ``VerifyStep`` chains the calls of one verification step on the current stream.
 """
 from __future__ import annotations
 
@@ -240,17 +240,14 @@ class VerifyStep:
 
     def run(self, compact=True):
         dev, desc = self.dev, self.desc
-        hb.hb_tree_verify_attn(desc, dev.q, dev.k_tree, dev.v_tree, dev.k_pool, dev.v_pool, dev.block_table,
-                               dev.prefix_len, dev.node_offset, dev.parent, self.out, None, self.ws_attn)
         hidden = self.out.view(self.out.shape[0], -1)  # [T, Hq*D]: attention output feeds the LM head
-        hb.hb_lmhead_argmax(hidden, self.weight, self.target_ids, None, self.ws_lm)
-        hb.hb_tree_accept(desc.batch, desc.max_nodes_per_tree, dev.node_offset, dev.parent, self.draft_ids,
-                          self.target_ids, self.max_path, self.accept_len, self.accept_path, self.out_tokens,
-                          self.bonus)
-        if compact:
-            hb.hb_kv_compact(desc, dev.k_tree, dev.v_tree, dev.k_pool, dev.v_pool, dev.block_table,
-                             dev.prefix_len, dev.node_offset, self.accept_len, self.accept_path, self.max_path,
-                             self.out_slots, self.new_len)
+        hb.hb_tree_verify_attn_clearing(desc, dev.q, dev.k_tree, dev.v_tree, dev.k_pool, dev.v_pool, dev.block_table,
+                                        dev.prefix_len, dev.node_offset, dev.parent, self.out, None, self.ws_attn,
+                                        self.ws_lm, hidden.shape[0])
+        hb.hb_lmhead_accept(desc, hidden, self.weight, self.draft_ids, dev.node_offset, dev.parent, self.max_path,
+                            self.target_ids, self.accept_len, self.accept_path, self.out_tokens, self.bonus, self.ws_lm,
+                            int(compact), (dev.k_tree, dev.v_tree, dev.k_pool, dev.v_pool), dev.block_table,
+                            dev.prefix_len, self.out_slots, self.new_len)
 
 
 class VerifyLayerStack:
@@ -329,8 +326,10 @@ class VerifyLayerStack:
             hb.hb_qkv_rope_project_ws(a, self.w_qkv[l], None, self.cos, self.sin, self.q, self.k_tree[l],
                                       self.v_tree[l], self.ws_proj)
             mark("tree_verify_attn")
-            hb.hb_tree_verify_attn(desc, self.q, self.k_tree[l], self.v_tree[l], kp, vp, dev.block_table,
-                                   dev.prefix_len, dev.node_offset, dev.parent, self.attn_out, None, self.ws_attn)
+            # the last layer's also clears the LM head's keys
+            hb.hb_tree_verify_attn_clearing(desc, self.q, self.k_tree[l], self.v_tree[l], kp, vp, dev.block_table,
+                                            dev.prefix_len, dev.node_offset, dev.parent, self.attn_out, None, self.ws_attn,
+                                            self.ws_lm, T if l == self.n_layers - 1 else 0)
             mark("out_project")
             hb.hb_out_project_ws(self.attn_out.view(T, -1), self.w_o[l], x, y, self.ws_proj)
             if mlp is not None:
@@ -346,15 +345,11 @@ class VerifyLayerStack:
             hb.hb_rmsnorm(x, mlp["norm_f"], mlp["eps"], self.normed)
             x = self.normed
         self.final_hidden = x
-        mark("lmhead_argmax")
-        hb.hb_lmhead_argmax(x, self.lm_weight, self.target_ids, None, self.ws_lm)
-        mark("tree_accept")
-        hb.hb_tree_accept(desc.batch, desc.max_nodes_per_tree, dev.node_offset, dev.parent, self.draft_ids,
-                          self.target_ids, self.max_path, self.accept_len, self.accept_path, self.out_tokens,
-                          self.bonus)
-        if compact:
-            mark("kv_compact")
-            hb.hb_kv_compact_layers(desc, self.n_layers, *self.ptr_tables, dev.block_table, dev.prefix_len,
-                                    dev.node_offset, self.accept_len, self.accept_path, self.max_path,
-                                    self.out_slots, self.new_len)
+        mark("lmhead_accept")
+        if not self.n_layers:
+            self.ws_lm.zero_()
+        hb.hb_lmhead_accept(desc, x, self.lm_weight, self.draft_ids, dev.node_offset, dev.parent, self.max_path,
+                            self.target_ids, self.accept_len, self.accept_path, self.out_tokens, self.bonus, self.ws_lm,
+                            self.n_layers if compact else 0, self.ptr_tables, dev.block_table, dev.prefix_len,
+                            self.out_slots, self.new_len)
         mark("end")

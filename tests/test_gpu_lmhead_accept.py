@@ -1,0 +1,69 @@
+"""GPU parity: hb_tree_verify_attn_clearing + hb_lmhead_accept (LM head, acceptance and the append to
+every layer's cache in two launches) give the oracle's results bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from oracle import tree_accept_ref, kv_compact_ref
+from parity import bits
+
+pytestmark = pytest.mark.gpu
+
+
+def _trees(kind):
+    if kind == "mixed":  # a tree, no nodes, a lone root, the widest tree, a chain
+        return [W.seeded_tree(1), np.array([], dtype=np.int32), W.chain_tree(1), W.seeded_tree(2, n_nodes=64), W.chain_tree(9)]
+    return [W.chain_tree(4)] if kind == "one chain" else [W.seeded_tree(b) for b in range(16)]
+
+
+@pytest.mark.parametrize("kind,dtype,layers,short", [
+    ("mixed", "bf16", 3, 0), ("mixed", "f32", 1, 0), ("mixed", "bf16", 0, 0), ("mixed", "bf16", 1, 2),
+    ("one chain", "f32", 1, 0), ("one chain", "bf16", 3, 1), ("16 trees", "bf16", 1, 0)])
+def test_lm_head_acceptance_and_append(kind, dtype, layers, short):
+    """short: max_path so many nodes below the deepest path; layers 3: through tables of pointers."""
+    import paper_2509_18824_amd as hb
+    import paper_2509_18824_amd.step as S
+    Hq, Hkv, D, V = 8, 4, 128, 1000
+    trees = _trees(kind)
+    inps = [W.make_verify_inputs(50 + l, dtype, Hq, Hkv, D, [11 + 7 * b for b in range(len(trees))], trees, poison=False)
+            for l in range(max(layers, 1))]
+    inp = inps[0]
+    T, max_path = inp.total_nodes, max(inp.max_path - short, 1)
+    rng = np.random.default_rng(6)
+    target = rng.integers(0, V, size=T)
+    draft, _ = W.plant_draft_ids(6, [t for t in trees if len(t)], target, V)
+    want = tree_accept_ref(inp.node_offset.numpy(), inp.parent.numpy(), draft, target, max_path)
+    refs = [kv_compact_ref(bits(x.k_tree), bits(x.v_tree), bits(x.k_pool), bits(x.v_pool), inp.block_table.numpy(),
+                           inp.prefix_len.numpy(), inp.node_offset.numpy(), want[0], want[1]) for x in inps]
+    devs, desc = [S.to_device(x) for x in inps], S.desc_for(inp)
+    dev, td = devs[0], devs[0].q.dtype
+    # row t of the hidden states points at entry target[t] and nowhere else
+    weight = torch.eye(V, Hq * D, dtype=td, device="cuda")
+    hidden = weight[torch.from_numpy(target).cuda()].contiguous()
+    i32 = lambda *shape: torch.full(shape, -7, dtype=torch.int32, device="cuda")
+    B = len(trees)
+    ids, alen, path, toks, bonus, slots, new_len = i32(T), i32(B), i32(B, max_path), i32(B, max_path), i32(B), i32(B, max_path), i32(B)
+    keys = torch.full((8 * T,), 255, dtype=torch.uint8, device="cuda")  # larger than any key, were it not cleared
+    table = lambda name: torch.tensor([getattr(d, name).data_ptr() for d in devs], dtype=torch.int64, device="cuda")
+    names = ("k_tree", "v_tree", "k_pool", "v_pool")
+    kv = [table(n) for n in names] if layers > 1 else [getattr(dev, n) for n in names]
+    out, ref_out = torch.empty_like(dev.q), torch.empty_like(dev.q)
+    ws = S.alloc_workspace(hb.hb_tree_verify_attn_workspace_bytes(desc))
+    args = (desc, dev.q, dev.k_tree, dev.v_tree, dev.k_pool, dev.v_pool, dev.block_table, dev.prefix_len, dev.node_offset, dev.parent)
+    hb.hb_tree_verify_attn(*args, ref_out, None, ws)
+    hb.hb_tree_verify_attn_clearing(*args, out, None, ws, keys, T)
+    assert not keys.any() and torch.equal(out.view(torch.uint8), ref_out.view(torch.uint8))
+    hb.hb_lmhead_accept(desc, hidden, weight, torch.from_numpy(np.asarray(draft, dtype=np.int32)).cuda(), dev.node_offset,
+                        dev.parent, max_path, ids, alen, path, toks, bonus, keys, layers, kv, dev.block_table,
+                        dev.prefix_len, slots, new_len)
+    torch.cuda.synchronize()
+    assert np.array_equal(ids.cpu().numpy(), target)
+    for got, ref in zip((alen, path, toks, bonus), want):
+        assert np.array_equal(got.cpu().numpy(), ref)
+    if layers:
+        assert np.array_equal(slots.cpu().numpy(), refs[0][2]) and np.array_equal(new_len.cpu().numpy(), refs[0][3])
+        for d, (ref_k, ref_v, _, _) in zip(devs, refs):
+            assert np.array_equal(bits(d.k_pool), ref_k) and np.array_equal(bits(d.v_pool), ref_v)
+    else:
+        assert (slots == -7).all() and (new_len == -7).all()

@@ -123,6 +123,14 @@ struct FewPlan {
 hipError_t launch_proj_few(StreamKind kind, const FewPlan &p, int32_t M, int32_t K, int32_t N, const void *hidden,
                            const void *weight, const StreamArgs &sa, float *part, int32_t v_pad, int32_t m_pad, hipStream_t s);
 
+// Tiles of 32 it weight rows x 32 jt tokens whose K steps two groups of wavefronts share (proj_pair.hip), K in `ks`
+// parts (more than one: partial sums as above); it = 0: not taken
+struct PairPlan {
+  int32_t it, jt, ks;
+};
+hipError_t launch_proj_pair(StreamKind kind, const PairPlan &p, int32_t M, int32_t K, int32_t N, const void *hidden,
+                            const void *weight, const StreamArgs &sa, float *part, int32_t v_pad, int32_t m_pad, hipStream_t s);
+
 bool proj_mfma_supports(int32_t M, int32_t K, int32_t N);
 // part: fp32 scratch of proj_workspace_bytes(M, K, N) bytes, for the ways that split K, or null (then K stays whole)
 size_t proj_workspace_bytes(int32_t M, int32_t K, int32_t N);

@@ -444,18 +444,79 @@ hipError_t launch_few(StreamKind kind, const FewPlan &p, int M, int K, int V, co
   return launch_reduce<ROPE, GLU>(M, V, p.ks, v_pad, m_pad, qa, sa, part, s);
 }
 
-// Which kernel takes the product: the stream, few rows against all tokens, or tiles of 256 rows (split over K as
-// *plan says).  The plan costs the host some microseconds and is made only where it matters.
+// More than 128 tokens, where the tiles of proj_pair.hip (tokens x weight rows of 128 x 128, 160 x 128, or 128 x 224 for plain
+// projections, whose rows need no partners) fill at most one round of CUs, K of products that are not gated in up to eight parts: the division expected to
+// be the fastest, if the 256-row tiles are not.  Microseconds of both, fitted to 1200 measurements of 297 calls (136 to 6144
+// tokens, 2048 to 18944 x 2048 to 37888, weights too many to stay in the last-level cache; 6.6 % rms); a K step costs
+// by the share of the CUs at work, which meet at the L2s.  What is chosen is within 0.6 % of the faster one in the mean, 135
+// of the calls are taken and 17 % faster for it, 110 drawn ones 21 % (256-row tiles -> this, us: 960 x 3584 x 3584 44.6 -> 35.9, rotary 960 x 3584 x
+// 4608 53 -> 42, 1280 x 8192 x 4096 108 -> 81, gated 640 x 3584 x 8192 53 -> 43, 2048 x 10752 x 3584 145 -> 135); six are up
+// to 5 % slower, parts of K of 1 KB or 2 KB among 136 tokens (and 224 rows below K = 1024, hence not taken there).  More than a round never pays: then the taller tiles move fewer
+// bytes from L2 to LDS.  Not kept: 96 x 192 (never the fastest by more than 1 %), 128 x 192, 128 x 256.
+double tiles_us(SplitPlan plan, int M, int K, int V) {
+  static const double kB[5] = {0, -1.92, 3.25, 6.14, 8.91}, kS[5] = {0, 0.5815, 0.7597, 0.6764, 0.7521}, kF[5] = {0, 0.148, 0.103, 0.455, 0.652};
+  const int steps = K / BK, v_tiles = (V + TV - 1) / TV;
+  if (plan.ks > 1) {
+    const double units = (double)v_tiles * ((M + 64 * plan.mt - 1) / (64 * plan.mt)) * plan.ks;
+    return 6.3 + steps / plan.ks * (kS[plan.mt] + kF[plan.mt] * units / 256) + 0.743 * 8.0 * units * TV * 64 * plan.mt / 4e6;
+  }
+  const int mt = plain_tile_height(M, K, v_tiles);
+  const long units = (long)v_tiles * ((M + 64 * mt - 1) / (64 * mt)), rounds = (units + 255) / 256;
+  return 3.84 + (double)rounds * (kB[mt] + steps * kS[mt]) + steps * kF[mt] * (double)units / 256;
+}
+PairPlan pair_plan(int M, int K, int V, StreamKind kind, SplitPlan plan) {
+  static const struct { int it, jt; double b, s, f; } kTiles[] = {
+      {4, 4, 5.17, 0.416, 0.116}, {4, 5, 5.97, 0.513, 0.088}, {7, 4, 6.63, 0.679, 0.076}};
+  PairPlan best = {0, 0, 1};
+  if (M <= kFewMost) return best;
+  const int steps = K / BK, v_pad = (V + TV - 1) / TV * TV;
+  double best_us = 0.98 * tiles_us(plan, M, K, V);
+  for (const auto &t : kTiles) {
+    if (t.it % 2 && (kind != StreamKind::kPlain || K < 1024)) continue;
+    const long tiles = (long)((V + 32 * t.it - 1) / (32 * t.it)) * ((M + 32 * t.jt - 1) / (32 * t.jt));
+    for (int ks = 1; ks <= (kind == StreamKind::kGlu ? 1 : 8) && tiles * ks <= 256; ++ks) {
+      // in the workspace that the caller was told to bring, for split_plan
+      if (steps % ks || (ks > 1 && (steps / ks < 8 || (size_t)ks * v_pad * M * sizeof(float) > split_bytes(plan, M, V)))) continue;
+      const double sums = ks > 1 ? 3.5 + 0.728 * 8.0 * ks * v_pad * M / 4e6 : 0.0;
+      const double us = t.b + steps / ks * (t.s + t.f * (double)(tiles * ks) / 256) + sums;
+      if (us < best_us) {
+        best_us = us;
+        best = {t.it, t.jt, ks};
+      }
+    }
+  }
+  return best;
+}
+
+template <bool ROPE, bool GLU>
+hipError_t launch_pair(StreamKind kind, const PairPlan &p, int M, int K, int V, const void *hidden, const void *weight,
+                       const QkvArgs &qa, const StoreArgs &sa, float *part, hipStream_t s) {
+  if (p.ks > 1 && !part) return hipErrorInvalidValue;
+  const int v_pad = (V + TV - 1) / TV * TV;
+  const StreamArgs st = {sa.residual, sa.out, qa.bias, qa.cos, qa.sin, qa.q, qa.k, qa.v, qa.Hq, qa.Hkv};
+  hipError_t e = launch_proj_pair(kind, p, M, K, V, hidden, weight, st, part, v_pad, M, s);
+  if (e != hipSuccess || p.ks == 1) return e;
+  return launch_reduce<ROPE, GLU>(M, V, p.ks, v_pad, M, qa, sa, part, s);
+}
+
+// Which kernel takes the product: the stream, few rows against all tokens, tiles whose K steps two groups share, or
+// tiles of 256 rows (split over K as ways->split says).  The plan costs the host some microseconds and is made only where it matters.
 // From 17 to 32 tokens stream and few rows each have their shapes (us at 17 / 32 tokens by the stream and by few rows:
 // 3584 x 3584 10.8 / 11.8 and 10.6 / 11.0; 14336 x 4096 26 / 32 and 34 / 35, in parts 28; 8192 x 8192 29 / 33 and 37; 3584 x
 // 16384 28 / 30 and 24; gated 3584 x 37888 50 / 54 and 45, 4096 x 28672 44 / 47 and 53 / 54): the one expected to be faster,
 // within 0.3 % of the faster one in the mean of the 2400 calls, and more than 3 % slower in 60 of them.
 // Parts of K of 4 KB in tiles of 96 or 128 rows lose to the split into 256-row tiles (32 / 128 tokens, 8192 x 8192 41 / 45 and
 // 33 / 41, 8192 x 7168 35 / 40 and 30 / 37, 14336 x 4608 38 / 43 and 33 / 41); other parts do not.
-enum class Way { kStream, kFew, kTiles };
-Way way_of(int M, int K, int V, StreamKind kind, const float *part, FewPlan *few, SplitPlan *plan) {
-  *plan = {1, 1};
-  *few = {0, 1};
+enum class Way { kStream, kFew, kPair, kTiles };
+struct Ways {
+  FewPlan few;
+  SplitPlan split;
+  PairPlan pair;
+};
+Way way_of(int M, int K, int V, StreamKind kind, const float *part, Ways *ways) {
+  *ways = {{0, 1}, {1, 1}, {0, 0, 1}};
+  FewPlan *few = &ways->few;
+  SplitPlan *plan = &ways->split;
   const bool stream = proj_stream_supports(M, K);
   if (M < kFewLeast && stream) return Way::kStream;
   if (part) *plan = split_plan(M, K, V);
@@ -464,7 +525,9 @@ Way way_of(int M, int K, int V, StreamKind kind, const float *part, FewPlan *few
     if (stream && stream_us(M, K, V) < few_us(*few, M, K, V, kind)) return Way::kStream;
     return few->ks > 1 && K / few->ks == 2048 && (few->rows == 6 || few->rows == 8) ? Way::kTiles : Way::kFew;
   }
-  return stream && proj_stream_pays(K, V, plan->ks > 1) ? Way::kStream : Way::kTiles;
+  if (stream && proj_stream_pays(K, V, plan->ks > 1)) return Way::kStream;
+  ways->pair = pair_plan(M, K, V, kind, *plan);
+  return ways->pair.it ? Way::kPair : Way::kTiles;
 }
 
 template <bool ROPE, bool GLU>
@@ -627,15 +690,15 @@ hipError_t launch_qkv_rope(int32_t M, int32_t K, int32_t Hq, int32_t Hkv, const 
   QkvArgs qa = {(const bf16_t *)bias, cos, sin, (bf16_t *)q, (bf16_t *)k, (bf16_t *)v, Hq, Hkv};
   StoreArgs sa = {nullptr, nullptr};
   const int V = (Hq + 2 * Hkv) * kHeadDim;
-  FewPlan few;
-  SplitPlan plan;
-  const Way way = way_of(M, K, V, StreamKind::kRope, part, &few, &plan);
-  if (way == Way::kFew) return launch_few<true, false>(StreamKind::kRope, few, M, K, V, hidden, w_qkv, qa, sa, part, s);
+  Ways ways;
+  const Way way = way_of(M, K, V, StreamKind::kRope, part, &ways);
+  if (way == Way::kPair) return launch_pair<true, false>(StreamKind::kRope, ways.pair, M, K, V, hidden, w_qkv, qa, sa, part, s);
+  if (way == Way::kFew) return launch_few<true, false>(StreamKind::kRope, ways.few, M, K, V, hidden, w_qkv, qa, sa, part, s);
   if (way == Way::kStream) {
     const StreamArgs st = {nullptr, nullptr, qa.bias, cos, sin, qa.q, qa.k, qa.v, Hq, Hkv};
     return launch_proj_stream(StreamKind::kRope, M, K, V, hidden, w_qkv, st, s);
   }
-  if (plan.ks > 1) return launch_splitk<true, false>(M, K, V, plan, hidden, w_qkv, qa, sa, part, s);
+  if (ways.split.ks > 1) return launch_splitk<true, false>(M, K, V, ways.split, hidden, w_qkv, qa, sa, part, s);
   return dispatch<true, false>(M, K, V, hidden, w_qkv, qa, sa, s);
 }
 
@@ -643,12 +706,12 @@ hipError_t launch_linear(int32_t M, int32_t K, int32_t N, const void *x, const v
                          float *part, hipStream_t s) {
   QkvArgs qa = {};
   StoreArgs sa = {(const bf16_t *)residual, (bf16_t *)out};
-  FewPlan few;
-  SplitPlan plan;
-  const Way way = way_of(M, K, N, StreamKind::kPlain, part, &few, &plan);
-  if (way == Way::kFew) return launch_few<false, false>(StreamKind::kPlain, few, M, K, N, x, w, qa, sa, part, s);
+  Ways ways;
+  const Way way = way_of(M, K, N, StreamKind::kPlain, part, &ways);
+  if (way == Way::kPair) return launch_pair<false, false>(StreamKind::kPlain, ways.pair, M, K, N, x, w, qa, sa, part, s);
+  if (way == Way::kFew) return launch_few<false, false>(StreamKind::kPlain, ways.few, M, K, N, x, w, qa, sa, part, s);
   if (way == Way::kStream) return launch_proj_stream(StreamKind::kPlain, M, K, N, x, w, {sa.residual, sa.out}, s);
-  if (plan.ks > 1) return launch_splitk<false, false>(M, K, N, plan, x, w, qa, sa, part, s);
+  if (ways.split.ks > 1) return launch_splitk<false, false>(M, K, N, ways.split, x, w, qa, sa, part, s);
   return dispatch<false, false>(M, K, N, x, w, qa, sa, s);
 }
 
@@ -656,12 +719,12 @@ hipError_t launch_swiglu(int32_t M, int32_t K, int32_t F, const void *x, const v
                          hipStream_t s) {
   QkvArgs qa = {};
   StoreArgs sa = {nullptr, (bf16_t *)out};
-  FewPlan few;
-  SplitPlan plan;
-  const Way way = way_of(M, K, 2 * F, StreamKind::kGlu, part, &few, &plan);
-  if (way == Way::kFew) return launch_few<false, true>(StreamKind::kGlu, few, M, K, 2 * F, x, w_gate_up, qa, sa, part, s);
+  Ways ways;
+  const Way way = way_of(M, K, 2 * F, StreamKind::kGlu, part, &ways);
+  if (way == Way::kPair) return launch_pair<false, true>(StreamKind::kGlu, ways.pair, M, K, 2 * F, x, w_gate_up, qa, sa, part, s);
+  if (way == Way::kFew) return launch_few<false, true>(StreamKind::kGlu, ways.few, M, K, 2 * F, x, w_gate_up, qa, sa, part, s);
   if (way == Way::kStream) return launch_proj_stream(StreamKind::kGlu, M, K, 2 * F, x, w_gate_up, {nullptr, sa.out}, s);
-  if (plan.ks > 1) return launch_splitk<false, true>(M, K, 2 * F, plan, x, w_gate_up, qa, sa, part, s);
+  if (ways.split.ks > 1) return launch_splitk<false, true>(M, K, 2 * F, ways.split, x, w_gate_up, qa, sa, part, s);
   return dispatch<false, true>(M, K, 2 * F, x, w_gate_up, qa, sa, s);
 }
 

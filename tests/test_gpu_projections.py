@@ -241,6 +241,27 @@ def test_every_way_of_the_gated_projection(hb, T, K, F, ws, kernel):
     assert names == ([kernel, "reduce<false, true>"] if kernel.startswith("splitk") else [kernel])
 
 
+# Tiles whose K steps two groups of wavefronts share: pair<kind (0 plain, 1 rotary, 2 gated, 3 partial sums), 32-row
+# tiles of weights, of tokens>.  Odd and even K steps in all and per part, ragged last tiles of both kinds, one token over.
+@pytest.mark.parametrize("kind,T,K,N,ws,kernel", [
+    ("plain", 2000, 1088, 3580, False, "pair<0, 7, 4>"), ("plain", 2047, 1024, 3500, False, "pair<0, 7, 4>"),
+    ("plain", 513, 10752, 3588, False, "pair<0, 4, 4>"), ("plain", 400, 3584, 3584, False, "pair<0, 4, 4>"),
+    ("plain", 961, 3584, 3460, True, "pair<0, 4, 4>"), ("plain", 1121, 2112, 3588, True, "pair<0, 4, 5>"),
+    ("plain", 400, 3584, 3584, True, "pair<3, 4, 4>"), ("plain", 513, 10752, 3588, True, "pair<3, 7, 4>"),
+    ("plain", 288, 3584, 3584, True, "pair<3, 4, 5>"),
+    ("rope", 960, 192, 35, False, "pair<1, 4, 5>"), ("rope", 961, 256, 36, True, "pair<1, 4, 5>"),
+    ("rope", 300, 2048, 20, False, "pair<1, 4, 4>"), ("rope", 288, 3584, 36, True, "pair<3, 4, 4>"),
+    ("gated", 520, 320, 4092, False, "pair<2, 4, 5>"), ("gated", 400, 2048, 4092, True, "pair<2, 4, 4>")])
+def test_projections_whose_k_steps_two_groups_share(hb, kind, T, K, N, ws, kernel):
+    if kind == "plain":
+        names = _kernels(lambda: _out_case(hb, T, K, N, T % 2 == 0, ws))
+    elif kind == "rope":
+        names = _kernels(lambda: _qkv_case(hb, T, K, N - 2 * (N // 9), N // 9, T % 2 == 0, ws))
+    else:
+        names = _kernels(lambda: test_gated_silu_projection(hb, T, K, N, ws))
+    assert names[0] == kernel and len(names) == (2 if kernel.startswith("pair<3") else 1)
+
+
 @pytest.mark.parametrize("K,N,gated", [(14336, 4096, False), (18944, 3584, False), (4096, 28672, True)])
 def test_seventeen_tokens_take_hardly_longer_than_sixteen(hb, K, N, gated):
     """Shapes where the stream stays ahead beyond 16 tokens: 25 and 26 us, 31 and 32, 43 and 44 by it; 33, 39 and 54 by tiles

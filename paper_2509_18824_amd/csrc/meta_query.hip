@@ -25,6 +25,9 @@
 // run afterwards on pre; the mixing kernel also copies the residual rows f_i[residual_layers[q]].
 #include "hb_internal.h"
 
+#include <algorithm>
+#include <type_traits>
+
 namespace hb {
 
 namespace {
@@ -322,24 +325,24 @@ __global__ __launch_bounds__(kMixThreads) void meta_mix_kernel(int S, int L, int
 // vectors of D per token, would be three times the features in memory; here a workgroup makes them
 // slice by slice in LDS and uses them up at once.
 //
-// Workgroup: TG tokens and up to eight heads (their hq rows: head-major, the queries of a head
-// together).  It walks D in slices of 64 features:
+// Workgroup: 4 or 16 tokens and up to eight heads (their hq rows: head-major, the queries of a head
+// together).  It walks D:
 //   mixing   feats^T P^T on the matrix cores per token (features as rows, the transposing LDS read
 //            supplies them; P^T of a wavefront's tokens stays in registers for the whole kernel).
 //            The two 16-feature tiles of 32 features are interleaved in fours, so that a lane holds
 //            eight consecutive features of one hq row and stores them as one piece.
 //   product  W_v slice (straight from memory in fragment layout) times the mixed features of the
 //            wavefront's head: accumulators for all of the workgroup's tokens.
-// The first half of a slice's weights is requested among the matrix instructions of the product before it, the
-// second half during its own mixing, the next slice's features (global -> LDS) among those of its product, so each
-// phase covers the other's loads.
 // P and the mixed features are each a bf16 value plus the bf16 remainder (two products, about 2^-17
 // relative): what was float32 when values were projected first stays better than bf16.
+// With 4 tokens (meta_project_kernel) mixing and product of 64 features follow each other, each covering the other's loads:
+// the first half of a slice's weights is requested among the matrix instructions of the product before it, the second half
+// during its own mixing, the next slice's features (global -> LDS) among those of its product.
 //
-// What bounds it: with 4 tokens the path L2 -> CU (every TG tokens read all of W_v once); with 16
-// tokens the two phases between barriers, matrix, vector and LDS work in turn on two wavefronts per
-// SIMD.  2048 tokens, 28 layers, D = 3584, 28 heads, 3 queries: 566 to 605 us; the value projection of all
-// layers and the mixing of its results took 1478 + 161 us.  96 tokens: 67 us against 76 + 15.
+// What bounds it: with 4 tokens the path L2 -> CU (every 4 tokens read all of W_v once); with 16 (see
+// meta_project_wide_kernel) matrix work 43 % of the clocks, LDS reads behind the barriers, features from memory at 1.7 TB/s.
+// 2048 tokens, 28 layers, D = 3584, 28 heads, 3 queries: 460 us (530 with 64 features between barriers); the
+// value projection of all layers and the mixing of its results took 1478 + 161 us.  96 tokens: 62 us against 76 + 15.
 constexpr int kMpThreads = 512;
 constexpr int kMpWaves = 8;
 constexpr int kMpHq = 24;           // hq rows of a workgroup at most: 96 KB of mixed features beside 64 KB of features
@@ -350,7 +353,9 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 // W_v in fragment order, made on every call by workgroups of the score kernel's launch: 16 rows x 32
-// columns are 1 KB in the order of the lanes, [head][16 rows][64 columns][32 columns][lane].  Read
+// columns are 1 KB in the order of the lanes, [32 columns][16 rows][lane]: all that the workgroups want of a slice of
+// features is in one piece, spread over all channels of the L2s (with the columns inside the rows every head's part of a
+// slice began a multiple of 2 KB from the others').  Read
 // from the matrix itself, four neighbouring lanes of a fragment load touch four rows and a load takes
 // 64 clocks instead of 16 (measured: 34 GB/s per CU, and 2.5 times the time for the whole kernel).
 __device__ void pack_values(int wave, int waves, int D, const u32x4 *__restrict__ w_v, u32x4 *__restrict__ packed) {
@@ -370,7 +375,7 @@ __device__ void pack_values(int wave, int waves, int D, const u32x4 *__restrict_
 #pragma unroll
     for (int i = 0; i < kBatch; ++i) {
       const int t = min(t0 + i, tiles - 1);
-      u32x4 *dst = packed + (size_t)t * 128 + ((lane & 7) >> 2) * 64 + (lane & 3) * 16 + (lane >> 3);
+      u32x4 *dst = packed + ((size_t)(2 * (t % steps) + ((lane & 7) >> 2)) * (D / 16) + t / steps) * 64 + (lane & 3) * 16 + (lane >> 3);
       dst[0] = x[i][0];
       dst[8] = x[i][1];
     }
@@ -402,17 +407,78 @@ __device__ __forceinline__ void tr_fragments(uint32_t at0, uint32_t at1, bf16x8 
   a[1] = __builtin_shufflevector(y0, y1, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
-// TG 16: a head's rows are Q tiles of 16 tokens (QT = Q); TG 4: one tile, row = q * 4 + token (QT = 1).
-// NT: 16-column tiles of a head per wavefront; 8 / NT wavefronts share a head.  FI: feature loads of a
-// wavefront per slice.  NS: slices of features in LDS.
-template <int TG, int QT, int NT, int FI, int NS>
+// The same for two tokens.
+__device__ __forceinline__ void tr_fragments(uint32_t at0, uint32_t at1, uint32_t at2, uint32_t at3, bf16x8 (&a)[2][2]) {
+  bf16x4 x[8];
+  asm volatile(
+      "ds_read_b64_tr_b16 %0, %8\n\t"
+      "ds_read_b64_tr_b16 %1, %9\n\t"
+      "ds_read_b64_tr_b16 %2, %8 offset:8\n\t"
+      "ds_read_b64_tr_b16 %3, %9 offset:8\n\t"
+      "ds_read_b64_tr_b16 %4, %10\n\t"
+      "ds_read_b64_tr_b16 %5, %11\n\t"
+      "ds_read_b64_tr_b16 %6, %10 offset:8\n\t"
+      "ds_read_b64_tr_b16 %7, %11 offset:8\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3]), "=&v"(x[4]), "=&v"(x[5]), "=&v"(x[6]), "=&v"(x[7])
+      : "v"(at0), "v"(at1), "v"(at2), "v"(at3)
+      : "memory");
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) a[t][i] = __builtin_shufflevector(x[4 * t + 2 * i], x[4 * t + 2 * i + 1], 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
+// Softmax over the layers of row row0 + hq of token tok0 + t; to entry at of tab[2][n][4 pieces], values and remainders.
+__device__ __forceinline__ void softmax_layers(int at, int t, int hq, int n, int S, int L, int tok0, int row0, int rows_pad,
+                                               int parts, const float *__restrict__ part, u32x4 *tab) {
+  const int s = min(tok0 + t, S - 1);
+  const f32x4 *src = reinterpret_cast<const f32x4 *>(part + ((size_t)s * rows_pad + row0 + hq) * kMaxL);
+  const size_t stride = (size_t)S * rows_pad * (kMaxL / 4);
+  f32x4 sc[kMaxL / 4];
+#pragma unroll
+  for (int i = 0; i < kMaxL / 4; ++i) sc[i] = src[i];
+  for (int p = 1; p < parts; ++p)
+#pragma unroll
+    for (int i = 0; i < kMaxL / 4; ++i) sc[i] += src[p * stride + i];
+  float mx = -__builtin_huge_valf();
+#pragma unroll
+  for (int l = 0; l < kMaxL; ++l)
+    if (l < L) mx = fmaxf(mx, sc[l >> 2][l & 3]);
+  float sum = 0.f;
+#pragma unroll
+  for (int l = 0; l < kMaxL; ++l) {
+    const float e = l < L ? __expf(sc[l >> 2][l & 3] - mx) : 0.f;
+    sc[l >> 2][l & 3] = e;
+    sum += e;
+  }
+  const float inv = 1.f / sum;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    u32x4 hi, lo;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int l = 8 * i + 2 * e;
+      uint32_t a, b;
+      split_pair(sc[l >> 2][l & 3] * inv, sc[(l + 1) >> 2][(l + 1) & 3] * inv, a, b);
+      hi[e] = a;
+      lo[e] = b;
+    }
+    tab[at * 4 + i] = hi;
+    tab[(n + at) * 4 + i] = lo;
+  }
+}
+
+// 4 tokens: a head's rows are one tile, row = q * 4 + token.  NT: 16-column tiles of a head per wavefront; 8 / NT
+// wavefronts share a head.
+template <int NT>
 __global__ __launch_bounds__(kMpThreads) void meta_project_kernel(
     int S, int L, int D, int H, int Q, int hg, int rows_pad, int parts, const float *__restrict__ part,
     const u32x4 *__restrict__ feats, const u32x4 *__restrict__ packed, ResidualLayers res, bf16_t *__restrict__ pre,
     u32x4 *__restrict__ res_out) {
   constexpr int kWavesPerHead = 8 / NT;
-  constexpr int kTok = TG == 16 ? 2 : 1;   // tokens whose mixing a wavefront does
-  constexpr int kSub = TG == 16 ? 2 : 1;   // 32-feature halves of the slice it does for them
+  constexpr int TG = 4, NS = 2;            // tokens; slices of features in LDS
+  constexpr int FI = 2;                    // feature loads of a wavefront per slice
   extern __shared__ u32x4 meta_a_lds[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -425,7 +491,7 @@ __global__ __launch_bounds__(kMpThreads) void meta_project_kernel(
   u32x4 *lds_f = meta_a_lds;                // [NS][FI * 8 wavefronts * 8 rows][8]
   constexpr int kStagePieces = FI * kMpWaves * 64;
   u32x4 *lds_m = meta_a_lds + NS * kStagePieces;  // [2][mixed rows][8]: values, remainders
-  const int mixed = TG == 16 ? hg * Q * 16 : hg * 16;
+  const int mixed = hg * 16;
 
   // Features: 64 rows per round of the wavefronts, lane -> row lane / 8 of its wavefront's eight,
   // piece swizzled on the source side; rows past the workgroup's are out of the buffer's range and
@@ -447,60 +513,22 @@ __global__ __launch_bounds__(kMpThreads) void meta_project_kernel(
   issue_feats(0);
 
   // ---- softmax over the layers, one thread per (token, hq row); P goes through LDS ------------
-  bf16x8 p_hi[kTok][2], p_lo[kTok][2];
+  const int t = wave >> 1, g = wave & 1;    // the token whose mixing this wavefront does, and the half of the slice
+  bf16x8 p_hi[2], p_lo[2];
   {
     u32x4 *tab = lds_m;  // [2][TG * hq_rows][4 pieces]
     const int n = TG * hq_rows;
     if (tid < n) {
-      const int t = tid / hq_rows, hq = tid - t * hq_rows;
-      const int s = min(tok0 + t, S - 1);
-      const f32x4 *src = reinterpret_cast<const f32x4 *>(part + ((size_t)s * rows_pad + h0 * Q + hq) * kMaxL);
-      const size_t stride = (size_t)S * rows_pad * (kMaxL / 4);
-      f32x4 sc[kMaxL / 4];
-#pragma unroll
-      for (int i = 0; i < kMaxL / 4; ++i) sc[i] = src[i];
-      for (int p = 1; p < parts; ++p)
-#pragma unroll
-        for (int i = 0; i < kMaxL / 4; ++i) sc[i] += src[p * stride + i];
-      float mx = -__builtin_huge_valf();
-#pragma unroll
-      for (int l = 0; l < kMaxL; ++l)
-        if (l < L) mx = fmaxf(mx, sc[l >> 2][l & 3]);
-      float sum = 0.f;
-#pragma unroll
-      for (int l = 0; l < kMaxL; ++l) {
-        const float e = l < L ? __expf(sc[l >> 2][l & 3] - mx) : 0.f;
-        sc[l >> 2][l & 3] = e;
-        sum += e;
-      }
-      const float inv = 1.f / sum;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        u32x4 hi, lo;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int l = 8 * i + 2 * e;
-          uint32_t a, b;
-          split_pair(sc[l >> 2][l & 3] * inv, sc[(l + 1) >> 2][(l + 1) & 3] * inv, a, b);
-          hi[e] = a;
-          lo[e] = b;
-        }
-        tab[tid * 4 + i] = hi;
-        tab[(n + tid) * 4 + i] = lo;
-      }
+      softmax_layers(tid, tid / hq_rows, tid % hq_rows, n, S, L, tok0, h0 * Q, rows_pad, parts, part, tab);
     }
     __syncthreads();
 #pragma unroll
-    for (int tt = 0; tt < kTok; ++tt) {
-      const int t = TG == 16 ? 2 * wave + tt : wave >> 1;
-#pragma unroll
-      for (int ct = 0; ct < 2; ++ct) {
-        const int hq = 16 * ct + j16;
-        const int at = t * hq_rows + min(hq, hq_rows - 1);
-        const u32x4 zero = {0u, 0u, 0u, 0u};
-        p_hi[tt][ct] = __builtin_bit_cast(bf16x8, hq < hq_rows ? tab[at * 4 + kq] : zero);
-        p_lo[tt][ct] = __builtin_bit_cast(bf16x8, hq < hq_rows ? tab[(n + at) * 4 + kq] : zero);
-      }
+    for (int ct = 0; ct < 2; ++ct) {
+      const int hq = 16 * ct + j16;
+      const int at = t * hq_rows + min(hq, hq_rows - 1);
+      const u32x4 zero = {0u, 0u, 0u, 0u};
+      p_hi[ct] = __builtin_bit_cast(bf16x8, hq < hq_rows ? tab[at * 4 + kq] : zero);
+      p_lo[ct] = __builtin_bit_cast(bf16x8, hq < hq_rows ? tab[(n + at) * 4 + kq] : zero);
     }
   }
 
@@ -517,35 +545,30 @@ __global__ __launch_bounds__(kMpThreads) void meta_project_kernel(
   // transposing reads of the mixing: lane -> layer row and 8-byte half piece.  Layers past L repeat
   // the last one (their probabilities are zero).
   const uint32_t f_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) u32x4 *)lds_f;
-  uint32_t f_off[kTok][2];  // by half of the lane group's eight layers; ^ 64 for the slice's second 32 features
+  uint32_t f_off[2];  // by half of the lane group's eight layers; ^ 64 for the slice's second 32 features
 #pragma unroll
-  for (int tt = 0; tt < kTok; ++tt) {
-    const int t = TG == 16 ? 2 * wave + tt : wave >> 1;
-#pragma unroll
-    for (int hf = 0; hf < 2; ++hf) {
-      const int r = t * L + min(8 * kq + 4 * hf + (j16 >> 2), L - 1);
-      f_off[tt][hf] = f_lds + r * 128 + ((j16 & 3) ^ ((r >> 1) & 7)) * 16;
-    }
+  for (int hf = 0; hf < 2; ++hf) {
+    const int r = t * L + min(8 * kq + 4 * hf + (j16 >> 2), L - 1);
+    f_off[hf] = (f_lds + r * 128 + ((j16 & 3) ^ ((r >> 1) & 7)) * 16) ^ (64 * g);
   }
 
   const bool active = wave / kWavesPerHead < heads;        // a wavefront too many repeats the last head
   const int hl = min(wave / kWavesPerHead, heads - 1);     // this wavefront's head
   const int n0 = (wave % kWavesPerHead) * NT * 16;         // its first column in the head
-  const auto w_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(packed + (size_t)((h0 + hl) * 8 + n0 / 16) * steps * 128), 0,
-                                                        NT * steps * 2048, kBufferFlags);
-  f32x4 acc[QT][NT];
+  const int w_step = D / 16 * 1024;  // bytes of 32 columns
+  const auto w_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(packed + (size_t)((h0 + hl) * 8 + n0 / 16) * 64), 0,
+                                                        (2 * steps - 1) * w_step + NT * 1024, kBufferFlags);
+  f32x4 acc[NT];
 #pragma unroll
-  for (int q = 0; q < QT; ++q)
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) acc[q][nt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  for (int nt = 0; nt < NT; ++nt) acc[nt] = (f32x4){0.f, 0.f, 0.f, 0.f};
 
   bf16x8 w[2][NT];
   auto issue_weight = [&](int kt, int ks, int nt) {
     const int k = min(kt, steps - 1);
-    w[ks][nt] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, lane * 16, (nt * steps + k) * 2048 + ks * 1024, 0));
+    w[ks][nt] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, lane * 16, (2 * k + ks) * w_step + nt * 1024, 0));
   };
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the count below starts here
-  if (NS == 2) issue_feats(1);
+  issue_feats(1);
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) issue_weight(0, 0, nt);
@@ -556,46 +579,35 @@ __global__ __launch_bounds__(kMpThreads) void meta_project_kernel(
     // half of the slice's weights); everybody is done with the previous mixed features.
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NS - 1) * FI + NT) : "memory");
     const uint32_t stage = (uint32_t)(kt % NS) * (uint32_t)(kStagePieces * 16);
+    // the second half of the slice's weights
 #pragma unroll
-    for (int tt = 0; tt < kTok; ++tt) {
-      const int t = TG == 16 ? 2 * wave + tt : wave >> 1;
+    for (int nt = 0; nt < NT; ++nt) issue_weight(kt, 1, nt);
+    __builtin_amdgcn_sched_barrier(0);
+    bf16x8 a[2];
+    tr_fragments(stage + f_off[0], stage + f_off[1], a);
 #pragma unroll
-      for (int sub = 0; sub < kSub; ++sub) {
-        const int g = TG == 16 ? sub : wave & 1;
-        // the second half of the slice's weights, in the first half of the mixing
-        constexpr int kSpread = kTok * kSub > 1 ? kTok * kSub / 2 : 1;
-        if (tt * kSub + sub < kSpread) {
+    for (int ct = 0; ct < 2; ++ct) {
+      if (16 * ct >= hq_rows) break;
+      f32x4 c[2];
 #pragma unroll
-          for (int nt = 0; nt < NT / kSpread; ++nt) issue_weight(kt, 1, (tt * kSub + sub) * (NT / kSpread) + nt);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        bf16x8 a[2];
-        tr_fragments(stage + (f_off[tt][0] ^ (64 * g)), stage + (f_off[tt][1] ^ (64 * g)), a);
+      for (int i = 0; i < 2; ++i) {
+        c[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], p_hi[ct], (f32x4){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+        c[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], p_lo[ct], c[i], 0, 0, 0);
+      }
+      const int hq = 16 * ct + j16;
+      u32x4 hi, lo;
 #pragma unroll
-        for (int ct = 0; ct < 2; ++ct) {
-          if (16 * ct >= hq_rows) break;
-          f32x4 c[2];
-#pragma unroll
-          for (int i = 0; i < 2; ++i) {
-            c[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], p_hi[tt][ct], (f32x4){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-            c[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], p_lo[tt][ct], c[i], 0, 0, 0);
-          }
-          const int hq = 16 * ct + j16;
-          u32x4 hi, lo;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            uint32_t x, y;
-            split_pair(c[e >> 1][2 * (e & 1)], c[e >> 1][2 * (e & 1) + 1], x, y);
-            hi[e] = x;
-            lo[e] = y;
-          }
-          if (hq < hq_rows) {
-            const int row = TG == 16 ? hq * 16 + t : (hq / Q) * 16 + (hq % Q) * 4 + t;
-            const int at = row * 8 + ((4 * g + kq) ^ ((row + hq) & 7));
-            lds_m[at] = hi;
-            lds_m[mixed * 8 + at] = lo;
-          }
-        }
+      for (int e = 0; e < 4; ++e) {
+        uint32_t x, y;
+        split_pair(c[e >> 1][2 * (e & 1)], c[e >> 1][2 * (e & 1) + 1], x, y);
+        hi[e] = x;
+        lo[e] = y;
+      }
+      if (hq < hq_rows) {
+        const int row = (hq / Q) * 16 + (hq % Q) * 4 + t;
+        const int at = row * 8 + ((4 * g + kq) ^ ((row + hq) & 7));
+        lds_m[at] = hi;
+        lds_m[mixed * 8 + at] = lo;
       }
     }
     // the mixed features are complete; everybody is done with the slice's features
@@ -606,46 +618,266 @@ __global__ __launch_bounds__(kMpThreads) void meta_project_kernel(
     for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) asm volatile("" : "+v"(w[ks][nt]));
-    // The next slice's features and then the first half of its weights are requested among the matrix
-    // instructions: in front of them and behind them the address unit had every wavefront wait (1400 and 1300
-    // of 11000 clocks a slice at 16 tokens).
+    // The next slice's features and then the first half of its weights are requested among the matrix instructions: in
+    // front of them and behind them the address unit had every wavefront wait.
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks)
+    for (int ks = 0; ks < 2; ++ks) {
+      const int row = hl * 16 + j16, hq = hl * Q + (j16 >> 2);
+      const int at = row * 8 + ((4 * ks + kq) ^ ((row + hq) & 7));
+      const bf16x8 hi = __builtin_bit_cast(bf16x8, lds_m[at]);
+      const bf16x8 lo = __builtin_bit_cast(bf16x8, lds_m[mixed * 8 + at]);
 #pragma unroll
-      for (int q = 0; q < QT; ++q) {
-        const int row = (TG == 16 ? (hl * Q + q) * 16 : hl * 16) + j16;
-        const int hq = TG == 16 ? hl * Q + q : hl * Q + (j16 >> 2);
-        const int at = row * 8 + ((4 * ks + kq) ^ ((row + hq) & 7));
-        const bf16x8 hi = __builtin_bit_cast(bf16x8, lds_m[at]);
-        const bf16x8 lo = __builtin_bit_cast(bf16x8, lds_m[mixed * 8 + at]);
+      for (int nt = 0; nt < NT; ++nt) {
+        acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ks][nt], hi, acc[nt], 0, 0, 0);
+        acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ks][nt], lo, acc[nt], 0, 0, 0);
+        const int loads = ks ? NT : FI;
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-          acc[q][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ks][nt], hi, acc[q][nt], 0, 0, 0);
-          acc[q][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ks][nt], lo, acc[q][nt], 0, 0, 0);
-          constexpr int kPairs = QT * NT;
-          const int n = q * NT + nt, loads = ks ? NT : FI;
-#pragma unroll
-          for (int i = n * loads / kPairs; i < (n + 1) * loads / kPairs; ++i) {
-            if (ks) issue_weight(kt + 1, 0, i);
-            else issue_feat(kt + NS, i);
-          }
-          __builtin_amdgcn_sched_barrier(0);
+        for (int i = nt * loads / NT; i < (nt + 1) * loads / NT; ++i) {
+          if (ks) issue_weight(kt + 1, 0, i);
+          else issue_feat(kt + NS, i);
         }
+        __builtin_amdgcn_sched_barrier(0);
       }
+    }
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   // lane (j16, kq) holds columns 16 nt + 4 kq .. + 3 of row j16
   if (!active) return;
+  const int q = j16 >> 2, s = tok0 + (j16 & 3);
+  if (q >= Q || s >= S) return;
+  bf16_t *dst = pre + ((size_t)s * Q + q) * D + (h0 + hl) * kMpHeadDim + n0 + 4 * kq;
 #pragma unroll
-  for (int qt = 0; qt < QT; ++qt) {
-    const int t = TG == 16 ? j16 : j16 & 3, q = TG == 16 ? qt : j16 >> 2;
-    if (q >= Q || tok0 + t >= S) continue;
-    bf16_t *dst = pre + ((size_t)(tok0 + t) * Q + q) * D + (h0 + hl) * kMpHeadDim + n0 + 4 * kq;
+  for (int nt = 0; nt < NT; ++nt) {
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    *(u32x2 *)(dst + nt * 16) = (u32x2){(uint32_t)f32_to_bf16(acc[nt][0]) | ((uint32_t)f32_to_bf16(acc[nt][1]) << 16),
+                                        (uint32_t)f32_to_bf16(acc[nt][2]) | ((uint32_t)f32_to_bf16(acc[nt][3]) << 16)};
+  }
+}
+
+// The same for 16 tokens a workgroup: a head's rows are Q tiles of 16 tokens.  A step is 32 features.  The product of a step
+// and the mixing of the next one do not depend on each other, so a wavefront does both in one stream of instructions: it
+// reads the operands of both from LDS, and between the matrix instructions of the product the mixed values are split and
+// stored.  Features arrive in slices of 64 (whole lines: with 32 the kernel waited for memory, 480 us), two of them in LDS,
+// requested almost three steps ahead.
+constexpr int kMwTok = 16;
+constexpr int mw_loads(int L) { return L <= 24 ? 6 : L <= 28 ? 7 : 8; }  // feature loads of a wavefront per slice: 64 rows each
+constexpr int mw_stage(int fi) { return fi * kMpWaves * 64; }            // 16-byte pieces of a slice's features
+
+template <int QT, int NT, int FI>
+__global__ __launch_bounds__(kMpThreads) void meta_project_wide_kernel(
+    int S, int L, int D, int H, int Q, int hg, int rows_pad, int parts, const float *__restrict__ part,
+    const u32x4 *__restrict__ feats, const u32x4 *__restrict__ packed, ResidualLayers res, bf16_t *__restrict__ pre,
+    u32x4 *__restrict__ res_out) {
+  constexpr int kWavesPerHead = 8 / NT;
+  constexpr int CT = QT * 8 > 16 && NT == 8 ? 2 : 1;  // tiles of 16 hq rows (NT 4: at most 16 rows)
+  extern __shared__ u32x4 meta_a_lds[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int j16 = lane & 15, kq = lane >> 4;
+  const int dp = D / 8;
+  const int tok0 = blockIdx.x * kMwTok, h0 = blockIdx.y * hg;
+  const int heads = min(hg, H - h0);  // >= 1
+  const int hq_rows = heads * Q;
+  const int frows = min(kMwTok, S - tok0) * L;  // feature rows of the workgroup, consecutive in memory
+  constexpr int kStage = mw_stage(FI);
+  u32x4 *lds_f = meta_a_lds;               // [2][16 L rows][8]
+  u32x4 *lds_m = meta_a_lds + 2 * kStage;  // [values, remainders][token][hq][4]
+  const int mixed = kMwTok * hq_rows * 4;       // pieces
+
+  // Features: 64 rows per round of the wavefronts, lane -> row lane / 8 of its wavefront's eight, piece swizzled on the
+  // source side; rows past the workgroup's are out of the buffer's range and arrive as zeros.  Always FI loads (the
+  // waits below count them): a repeated slice changes nothing.
+  typedef __attribute__((address_space(3))) void *lptr_t;
+  const int steps = D / 32, slices = D / 64;
+  const auto f_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(feats + (size_t)tok0 * L * dp), 0, frows * dp * 16, kBufferFlags);
+  const int f_src = (wave * 8 + (lane >> 3)) * dp * 16 + ((lane & 7) ^ (((wave * 8 + (lane >> 3)) >> 1) & 7)) * 16;
+  auto issue_feats = [&](int slice) {
+    const int k = min(slice, slices - 1);
+#pragma unroll
+    for (int i = 0; i < FI; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(f_rsrc, (lptr_t)(lds_f + (slice & 1) * kStage + (wave + i * kMpWaves) * 64), 16,
+                                               f_src + i * kMpWaves * 8 * dp * 16, k * 128, 0, 0);
+  };
+  issue_feats(0);
+  issue_feats(1);
+
+  // ---- softmax over the layers, one thread per (token, hq row); P goes through LDS ------------
+  // Of tokens 2 wave and 2 wave + 1, hq rows in tiles of 16.  Lanes past the last row repeat one of the first tile and store
+  // the same values there again.
+  auto row_of = [&](int ct) { return 16 * ct + j16 < hq_rows ? 16 * ct + j16 : j16 % hq_rows; };
+  bf16x8 p_hi[2][CT], p_lo[2][CT];
+  {
+    u32x4 *tab = lds_m;  // [2][16 * hq_rows][4 pieces]
+    const int n = kMwTok * hq_rows;
+    if (tid < n) softmax_layers(tid, tid / hq_rows, tid % hq_rows, n, S, L, tok0, h0 * Q, rows_pad, parts, part, tab);
+    __syncthreads();
+#pragma unroll
+    for (int tt = 0; tt < 2; ++tt)
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) {
+        const int at = (2 * wave + tt) * hq_rows + row_of(ct);
+        p_hi[tt][ct] = __builtin_bit_cast(bf16x8, tab[at * 4 + kq]);
+        p_lo[tt][ct] = __builtin_bit_cast(bf16x8, tab[(n + at) * 4 + kq]);
+      }
+  }
+
+  // the residual rows of the workgroup's columns, kBatch loads in flight (one after the other they took 15 us)
+  if (res.on) {
+    constexpr int kBatch = 6;
+    const int cols = heads * (kMpHeadDim / 8), n = min(kMwTok, S - tok0) * Q * cols;
+    for (int i0 = tid; i0 < n; i0 += kBatch * kMpThreads) {
+      u32x4 x[kBatch];
+      size_t to[kBatch];
+#pragma unroll
+      for (int b = 0; b < kBatch; ++b) {
+        const int i = min(i0 + b * kMpThreads, n - 1);  // past the end: the last one again
+        const int row = i / cols, c = h0 * (kMpHeadDim / 8) + i - row * cols;
+        const int t = row / Q, q = row - t * Q;
+        x[b] = feats[((size_t)(tok0 + t) * L + res.layer[q]) * dp + c];
+        to[b] = ((size_t)(tok0 + t) * Q + q) * dp + c;
+      }
+#pragma unroll
+      for (int b = 0; b < kBatch; ++b) res_out[to[b]] = x[b];
+    }
+  }
+
+  // Transposing reads of the mixing: lane -> layer row and 8-byte half piece.  Layers past L repeat the last one (their
+  // probabilities are zero).
+  const uint32_t f_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) u32x4 *)lds_f;
+  uint32_t f_off[2][2];  // by token and half of the lane group's eight layers; ^ 64 for the slice's second 32 features
+#pragma unroll
+  for (int tt = 0; tt < 2; ++tt)
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf) {
+      const int r = (2 * wave + tt) * L + min(8 * kq + 4 * hf + (j16 >> 2), L - 1);
+      f_off[tt][hf] = f_lds + r * 128 + ((j16 & 3) ^ ((r >> 1) & 7)) * 16;
+    }
+
+  // Mixed features of (token t, row hq): 64 bytes.  The mixing writes 16 rows of one token at a time, the product reads
+  // one row of 16 tokens.  With rows of 64 bytes an odd number apart and piece p of every other four of them at p ^ 2, 16-byte
+  // reads run at 4 clocks and writes at 9.4 (8 in a row; without the exchange 6 and 17.5); an even number of rows is
+  // rotated by the token.
+  auto mixed_at = [&](int t, int hq, int p) {
+    const int r = hq_rows & 1 ? hq : (hq + (t & 3)) % hq_rows;
+    return (t * hq_rows + r) * 4 + (p ^ (((t >> 2) ^ (hq >> 2)) & 1) * 2);
+  };
+  const bool active = wave / kWavesPerHead < heads;     // a wavefront too many repeats the last head
+  const int hl = min(wave / kWavesPerHead, heads - 1);  // this wavefront's head
+  const int n0 = (wave % kWavesPerHead) * NT * 16;      // its first column in the head
+  int m_write[2][CT], m_read[QT];
+#pragma unroll
+  for (int tt = 0; tt < 2; ++tt)
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) m_write[tt][ct] = mixed_at(2 * wave + tt, row_of(ct), kq);
+#pragma unroll
+  for (int q = 0; q < QT; ++q) m_read[q] = mixed_at(j16, hl * Q + q, kq);
+
+  const int w_step = D / 16 * 1024;  // bytes of a slice
+  const auto w_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(packed + (size_t)((h0 + hl) * 8 + n0 / 16) * 64), 0,
+                                                        (steps - 1) * w_step + NT * 1024, kBufferFlags);
+  f32x4 acc[QT][NT];
+#pragma unroll
+  for (int q = 0; q < QT; ++q)
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) acc[q][nt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  bf16x8 w[NT];
+  auto issue_weight = [&](int kt, int nt) {
+    const int k = min(kt, steps - 1);
+    w[nt] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, lane * 16, k * w_step + nt * 1024, 0));
+  };
+
+  // the mixing of one tile of hq rows for both tokens: features x P
+  bf16x8 a[2][2];
+  f32x4 c[2][2];
+  auto mix_products = [&](int ct) {
+#pragma unroll
+    for (int tt = 0; tt < 2; ++tt)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        c[tt][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[tt][i], p_hi[tt][ct], (f32x4){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+    for (int tt = 0; tt < 2; ++tt)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) c[tt][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[tt][i], p_lo[tt][ct], c[tt][i], 0, 0, 0);
+  };
+  u32x4 mix_hi, mix_lo;
+  auto split_one = [&](int ct, int n) {  // n: token, pair; the fourth pair completes a piece
+    const int tt = n >> 2, e = n & 3;
+    uint32_t x, y;
+    split_pair(c[tt][e >> 1][2 * (e & 1)], c[tt][e >> 1][2 * (e & 1) + 1], x, y);
+    mix_hi[e] = x;
+    mix_lo[e] = y;
+    if (e == 3) {
+      lds_m[m_write[tt][ct]] = mix_hi;
+      lds_m[mixed + m_write[tt][ct]] = mix_lo;
+    }
+  };
+  auto read_features = [&](int slice, uint32_t half) {
+    const uint32_t at = (uint32_t)(slice & 1) * (uint32_t)(kStage * 16), x = half * 64;
+    tr_fragments(at + (f_off[0][0] ^ x), at + (f_off[0][1] ^ x), at + (f_off[1][0] ^ x), at + (f_off[1][1] ^ x), a);
+  };
+
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");  // P is read, the first slices are there
+  read_features(0, 0);
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct) {
+    mix_products(ct);
+#pragma unroll
+    for (int n = 0; n < 8; ++n) split_one(ct, n);
+  }
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) issue_weight(0, nt);
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  // the first weights are there, so that in the loop the compiler counts only what the loop requests
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) asm volatile("" : "+v"(w[nt]));
+  constexpr int kChunks = 2 * NT, kPairs = 8 * CT;
+  // step kt: product of its 32 features, mixing of the 32 after them (the first half of a slice in odd steps); the last step
+  // mixes what nobody reads
+  auto step = [&](int kt, auto odd) {
+    constexpr bool kOdd = decltype(odd)::value;
+    bf16x8 hi[QT], lo[QT];
+#pragma unroll
+    for (int q = 0; q < QT; ++q) {
+      hi[q] = __builtin_bit_cast(bf16x8, lds_m[m_read[q]]);
+      lo[q] = __builtin_bit_cast(bf16x8, lds_m[mixed + m_read[q]]);
+    }
+    read_features((kt + 1) >> 1, !kOdd);
+    asm volatile("s_barrier" ::: "memory");  // everybody has read: the mixed features may be replaced, and a slice's stage
+#pragma unroll
+    for (int n = 0; n < kChunks; ++n) {
+      const int nt = n >> 1;
+      if (n % (kChunks / CT) == 0) mix_products(n / (kChunks / CT));
+#pragma unroll
+      for (int q = 0; q < QT; ++q) acc[q][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[nt], n & 1 ? lo[q] : hi[q], acc[q][nt], 0, 0, 0);
+      // every weight fragment is requested for the next step right behind its last use, then the features
+      if (n & 1) issue_weight(kt + 1, nt);
+#pragma unroll
+      for (int i = n * kPairs / kChunks; i < (n + 1) * kPairs / kChunks; ++i) split_one(i / 8, i % 8);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (!kOdd) issue_feats((kt >> 1) + 2);
+    // The mixed features are complete.  Before an odd step the next slice's features must have landed: newer are the two
+    // steps' weights and the features just requested.
+    if (kOdd) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * NT + FI) : "memory");
+  };
+#pragma unroll 1
+  for (int kt = 0; kt < steps; kt += 2) {
+    step(kt, std::false_type());
+    step(kt + 1, std::true_type());
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  // lane (j16, kq) holds columns 16 nt + 4 kq .. + 3 of token j16
+  if (!active || tok0 + j16 >= S) return;
+#pragma unroll
+  for (int q = 0; q < QT; ++q) {
+    bf16_t *dst = pre + ((size_t)(tok0 + j16) * Q + q) * D + (h0 + hl) * kMpHeadDim + n0 + 4 * kq;
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
       typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-      *(u32x2 *)(dst + nt * 16) = (u32x2){(uint32_t)f32_to_bf16(acc[qt][nt][0]) | ((uint32_t)f32_to_bf16(acc[qt][nt][1]) << 16),
-                                          (uint32_t)f32_to_bf16(acc[qt][nt][2]) | ((uint32_t)f32_to_bf16(acc[qt][nt][3]) << 16)};
+      *(u32x2 *)(dst + nt * 16) = (u32x2){(uint32_t)f32_to_bf16(acc[q][nt][0]) | ((uint32_t)f32_to_bf16(acc[q][nt][1]) << 16),
+                                          (uint32_t)f32_to_bf16(acc[q][nt][2]) | ((uint32_t)f32_to_bf16(acc[q][nt][3]) << 16)};
     }
   }
 }
@@ -735,15 +967,32 @@ size_t meta_project_workspace_bytes(int32_t S, int32_t D, int32_t H, int32_t Q) 
 
 namespace {
 
-template <int TG, int QT, int NT, int FI, int NS>
+template <int NT>
 hipError_t launch_project(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q, int hg, int parts, const void *feats,
                           const void *packed, const ResidualLayers &res, void *pre, void *res_out, const float *part,
                           hipStream_t s) {
-  const size_t lds = ((size_t)NS * FI * kMpWaves * 64 + 2 * (size_t)(TG == 16 ? hg * Q : hg) * 16 * 8) * sizeof(u32x4);
-  auto kern = meta_project_kernel<TG, QT, NT, FI, NS>;
+  const size_t lds = ((size_t)2 * 2 * kMpWaves * 64 + 2 * (size_t)hg * 16 * 8) * sizeof(u32x4);  // two slices, mixed features
+  auto kern = meta_project_kernel<NT>;
   hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  kern<<<dim3((S + TG - 1) / TG, (H + hg - 1) / hg), kMpThreads, lds, s>>>(
+  kern<<<dim3((S + 3) / 4, (H + hg - 1) / hg), kMpThreads, lds, s>>>(
+      S, L, D, H, Q, hg, meta_rows_pad(H, Q), parts, part, (const u32x4 *)feats, (const u32x4 *)packed, res, (bf16_t *)pre,
+      (u32x4 *)res_out);
+  return hipGetLastError();
+}
+
+template <int QT, int NT, int FI>
+hipError_t launch_project_wide(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q, int hg, int parts, const void *feats,
+                               const void *packed, const ResidualLayers &res, void *pre, void *res_out, const float *part,
+                               hipStream_t s) {
+  if (FI > mw_loads(L)) {
+    if constexpr (FI > 6) return launch_project_wide<QT, NT, FI - 1>(S, L, D, H, Q, hg, parts, feats, packed, res, pre, res_out, part, s);
+  }
+  const size_t lds = ((size_t)2 * mw_stage(FI) + 2 * (size_t)hg * Q * kMwTok * 4) * sizeof(u32x4);
+  auto kern = meta_project_wide_kernel<QT, NT, FI>;
+  hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  kern<<<dim3((S + kMwTok - 1) / kMwTok, (H + hg - 1) / hg), kMpThreads, lds, s>>>(
       S, L, D, H, Q, hg, meta_rows_pad(H, Q), parts, part, (const u32x4 *)feats, (const u32x4 *)packed, res, (bf16_t *)pre,
       (u32x4 *)res_out);
   return hipGetLastError();
@@ -765,13 +1014,13 @@ static int split_heads(int H, int most) {  // heads per workgroup, evenly
   const int groups = (H + most - 1) / most;
   return (H + groups - 1) / groups;
 }
-static ProjectPlan project_plan(int32_t S, int32_t H, int32_t Q) {
+static ProjectPlan project_plan(int32_t S, int32_t L, int32_t H, int32_t Q) {
   const int64_t g4 = (S + 3) / 4, g16 = (S + 15) / 16;
   auto groups = [&](int hg) { return (int64_t)(H + hg - 1) / hg; };
   if (g4 * groups(2) <= 256) return {4, 2, split_heads(H, 2), 0.65};
   ProjectPlan best = {4, 4, split_heads(H, 4), (double)(g4 * H) * kMpHeadDim * 128 / 9.2e6};
   if (best.slice_us < 1.0) best.slice_us = 1.0;
-  const int wide = split_heads(H, Q <= 2 ? 8 : kMpHq / Q), narrow = split_heads(H, 4);
+  const int wide = split_heads(H, std::min(8, (L <= 28 ? kMpHq : 16) / Q)), narrow = split_heads(H, 4);
   const double narrow_us = 3.0 * (double)((g16 * groups(narrow) + 255) / 256);
   const double wide_us = 5.0 * (double)((g16 * groups(wide) + 255) / 256);
   if (narrow_us < best.slice_us) best = {16, 4, narrow, narrow_us};
@@ -787,7 +1036,7 @@ bool meta_project_pays(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q) {
   if (!meta_project_supports(D, H)) return false;
   const double product = 2.0 * S * L * D * (double)D / 0.85e9, mixing = 2.0 * S * L * (double)D / 2.6e6;
   const double first = (product < 20 ? 20 : product) + (mixing < 5 ? 5 : mixing);
-  return 5 + project_plan(S, H, Q).slice_us * (D / 64) < first;
+  return 5 + project_plan(S, L, H, Q).slice_us * (D / 64) < first;
 }
 
 hipError_t launch_meta_attn_project(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q, const void *feats,
@@ -798,23 +1047,23 @@ hipError_t launch_meta_attn_project(int32_t S, int32_t L, int32_t D, int32_t H, 
   hipError_t e = launch_scores(S, L, D, meta_rows_pad(H, Q), feats, a_fold, w_v, packed, part, &parts, s);
   if (e != hipSuccess) return e;
   const ResidualLayers res = residuals(Q, residual_layers, res_out);
-  const ProjectPlan plan = project_plan(S, H, Q);
-#define HB_MP(TG_, QT_, NT_, FI_, NS_) \
-  return launch_project<TG_, QT_, NT_, FI_, NS_>(S, L, D, H, Q, plan.hg, parts, feats, packed, res, pre, res_out, part, s)
-  if (plan.tg == 4 && plan.nt == 2) HB_MP(4, 1, 2, 2, 2);
-  if (plan.tg == 4) HB_MP(4, 1, 4, 2, 2);
+  const ProjectPlan plan = project_plan(S, L, H, Q);
+  if (plan.tg == 4)
+    return plan.nt == 2 ? launch_project<2>(S, L, D, H, Q, plan.hg, parts, feats, packed, res, pre, res_out, part, s)
+                        : launch_project<4>(S, L, D, H, Q, plan.hg, parts, feats, packed, res, pre, res_out, part, s);
+#define HB_MP(QT_, NT_) return launch_project_wide<QT_, NT_, 8>(S, L, D, H, Q, plan.hg, parts, feats, packed, res, pre, res_out, part, s)
   if (plan.nt == 4) {
     switch (Q) {
-      case 1: HB_MP(16, 1, 4, 8, 1);
-      case 2: HB_MP(16, 2, 4, 8, 1);
-      case 3: HB_MP(16, 3, 4, 8, 1);
-      default: HB_MP(16, 4, 4, 8, 1);
+      case 1: HB_MP(1, 4);
+      case 2: HB_MP(2, 4);
+      case 3: HB_MP(3, 4);
+      default: HB_MP(4, 4);
     }
   }
   switch (Q) {
-    case 1: HB_MP(16, 1, 8, 8, 1);
-    case 2: HB_MP(16, 2, 8, 8, 1);
-    default: HB_MP(16, 3, 8, 8, 1);
+    case 1: HB_MP(1, 8);
+    case 2: HB_MP(2, 8);
+    default: HB_MP(3, 8);
   }
 #undef HB_MP
 }

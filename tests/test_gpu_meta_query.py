@@ -105,6 +105,19 @@ def test_values_projected_after_the_mixing(S, n_tok, L, D, H, Q, layers):
     assert np.linalg.norm(got - ref) <= 4e-3 * np.linalg.norm(ref)
 
 
+@pytest.mark.parametrize("n_tok,L,D,H,Q,layers", [
+    (2060, 28, 1024, 8, 3, [0, 5, 27]),   # 16 tokens: 24 hq rows, all of LDS; 28 layers are the most of 7 loads a slice
+    (2040, 24, 1792, 14, 3, [1, 2, 23]),  # 21 rows; 6 loads
+    (2203, 25, 1280, 10, 3, None),        # 15 rows in two tiles of 16
+    (2061, 29, 1024, 8, 3, None),         # 12 rows of 4 heads; 8 loads
+    (2047, 32, 1024, 8, 2, [31, 0]),      # 16 rows
+    (700, 30, 1024, 8, 4, None),          # two wavefronts a head, four queries
+    (690, 7, 256, 2, 1, [6]),             # one row a head, eight steps
+])
+def test_sixteen_tokens_per_workgroup(S, n_tok, L, D, H, Q, layers):
+    test_values_projected_after_the_mixing(S, n_tok, L, D, H, Q, layers)
+
+
 @pytest.mark.parametrize("n_tok,L,D,H,Q", [(7, 28, 768, 6, 3), (1203, 5, 768, 6, 2), (1025, 5, 512, 4, 2)])
 @pytest.mark.parametrize("bad", [float("inf"), float("-inf"), float("nan")])
 def test_a_token_with_features_that_are_not_finite(S, n_tok, L, D, H, Q, bad):

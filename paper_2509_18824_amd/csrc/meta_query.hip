@@ -96,9 +96,9 @@ struct ResidualLayers {
 __device__ void pack_values(int wave, int waves, int D, const u32x4 *__restrict__ w_v, u32x4 *__restrict__ packed);
 
 constexpr int kScoreFeatRows = kTokPerGroup * kMaxL;                    // LDS rows of 64 features per stage
-constexpr int kScoreStage = (kScoreFeatRows + 2 * kMaxRows) * 8;        // pieces
-constexpr int kScoreLoads = (kScoreFeatRows + 2 * kMaxRows) / 8 / kScoreWaves;  // of a wavefront per step
-constexpr size_t kScoreLds = 2 * (size_t)kScoreStage * sizeof(u32x4);
+constexpr int kScoreFeatStage = kScoreFeatRows * 8, kScoreAStage = 2 * kMaxRows * 8;                       // pieces
+constexpr int kScoreFeatLoads = kScoreFeatRows / 8 / kScoreWaves, kScoreALoads = 2 * kMaxRows / 8 / kScoreWaves;  // of a wavefront per step
+constexpr size_t kScoreLds = (3 * (size_t)kScoreFeatStage + 2 * (size_t)kScoreAStage) * sizeof(u32x4);
 
 // part[p][s][row][l] (row stride 32): the scores of token s summed over the slices that
 // workgroup column p covers
@@ -108,7 +108,9 @@ __global__ __launch_bounds__(kScoreThreads) void meta_scores_kernel(int S, int L
                                                                     const u32x4 *__restrict__ feats,
                                                                     const u32x4 *__restrict__ a_fold,
                                                                     float *__restrict__ part) {
-  extern __shared__ u32x4 meta_a_lds[];  // [2][features of 8 x 32 rows, A (values, then remainders)][8 pieces]
+  // Features come from memory and have three stages, requested two steps ahead; A comes from the L2s, one step ahead.
+  extern __shared__ u32x4 meta_a_lds[];  // [3][features of 8 x 32 rows][8 pieces], [2][A: values, then remainders][8]
+  u32x4 *lds_a = meta_a_lds + 3 * kScoreFeatStage;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   if ((int)blockIdx.x < pack_wgs) {
@@ -135,18 +137,18 @@ __global__ __launch_bounds__(kScoreThreads) void meta_scores_kernel(int S, int L
   const auto a_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)a_fold, 0, 2 * rows_pad * row_bytes, kBufferFlags);
   const int r8 = lane >> 3;
   auto swz = [](int r, int c) { return r * 8 + (c ^ (r & 7)); };
-  auto issue = [&](int t) {
-    u32x4 *stage = meta_a_lds + (t & 1) * kScoreStage;
-    const int k = (k_begin + min(t, steps - 1)) * 128;
+  const int src = (wave * 8 + r8) * row_bytes + ((lane & 7) ^ r8) * 16;
+  auto issue_feats = [&](int t, int stage) {
 #pragma unroll
-    for (int i = 0; i < kScoreLoads; ++i) {
-      constexpr int kFeatLoads = kScoreFeatRows / 8 / kScoreWaves;  // the first of them: features, then A
-      const int row = (wave + (i < kFeatLoads ? i : i - kFeatLoads) * kScoreWaves) * 8 + r8;
-      const int src = row * row_bytes + ((lane & 7) ^ r8) * 16;
-      u32x4 *dst = stage + (wave + i * kScoreWaves) * 64;
-      if (i < kFeatLoads) __builtin_amdgcn_raw_ptr_buffer_load_lds(f_rsrc, (lptr_t)dst, 16, src, k, 0, 0);
-      else __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lptr_t)dst, 16, src, k, 0, 0);
-    }
+    for (int i = 0; i < kScoreFeatLoads; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(f_rsrc, (lptr_t)(meta_a_lds + stage * kScoreFeatStage + (wave + i * kScoreWaves) * 64), 16,
+                                               src + i * kScoreWaves * 8 * row_bytes, (k_begin + min(t, steps - 1)) * 128, 0, 0);
+  };
+  auto issue_a = [&](int t) {
+#pragma unroll
+    for (int i = 0; i < kScoreALoads; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lptr_t)(lds_a + (t & 1) * kScoreAStage + (wave + i * kScoreWaves) * 64), 16,
+                                               src + i * kScoreWaves * 8 * row_bytes, (k_begin + min(t, steps - 1)) * 128, 0, 0);
   };
   const int tw = (wave & 3) * kTokPerWave;   // first token
   const int mt0 = (wave >> 2) * (kMaxRowTiles / 2);
@@ -157,13 +159,18 @@ __global__ __launch_bounds__(kScoreThreads) void meta_scores_kernel(int S, int L
     for (int t = 0; t < kTokPerWave; ++t)
 #pragma unroll
       for (int ct = 0; ct < 2; ++ct) acc[mt][t][ct] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  issue(0);
-  issue(1);
+  issue_a(0);
+  issue_feats(0, 0);
+  issue_feats(1, 1);
+  issue_a(1);
+  issue_feats(2, 2);
+  int stage = 0;
 #pragma unroll 1
   for (int st = 0; st < steps; ++st) {
-    // this step's loads have landed, the next step's stay in flight
-    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kScoreLoads) : "memory");
-    const u32x4 *f = meta_a_lds + (st & 1) * kScoreStage, *ah = f + kScoreFeatRows * 8, *al = ah + rows_pad * 8;
+    // This step's loads have landed; in flight stay the features of the next two steps and the next A (the first
+    // step waits for more than it needs).
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * kScoreFeatLoads + kScoreALoads) : "memory");
+    const u32x4 *f = meta_a_lds + stage * kScoreFeatStage, *ah = lds_a + (st & 1) * kScoreAStage, *al = ah + rows_pad * 8;
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
       bf16x8 x[kTokPerWave][2];
@@ -177,18 +184,22 @@ __global__ __launch_bounds__(kScoreThreads) void meta_scores_kernel(int S, int L
           const int at = swz(16 * (mt0 + mt) + j16, 4 * ks + kq);
           const bf16x8 h8 = __builtin_bit_cast(bf16x8, ah[at]);
           const bf16x8 l8 = __builtin_bit_cast(bf16x8, al[at]);
+          // values for all, then remainders for all: neighbours do not wait for each other's sums
 #pragma unroll
           for (int t = 0; t < kTokPerWave; ++t)
 #pragma unroll
-            for (int ct = 0; ct < 2; ++ct) {
-              acc[mt][t][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h8, x[t][ct], acc[mt][t][ct], 0, 0, 0);
-              acc[mt][t][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(l8, x[t][ct], acc[mt][t][ct], 0, 0, 0);
-            }
+            for (int ct = 0; ct < 2; ++ct) acc[mt][t][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h8, x[t][ct], acc[mt][t][ct], 0, 0, 0);
+#pragma unroll
+          for (int t = 0; t < kTokPerWave; ++t)
+#pragma unroll
+            for (int ct = 0; ct < 2; ++ct) acc[mt][t][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(l8, x[t][ct], acc[mt][t][ct], 0, 0, 0);
         }
       }
     }
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // everybody has read the stage
-    issue(st + 2);
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // everybody has read the stages
+    issue_a(st + 2);
+    issue_feats(st + 3, stage);
+    stage = stage == 2 ? 0 : stage + 1;
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no load may land in LDS that belongs to somebody else
   // lane (j16, kq) holds rows 16 mt + 4 kq + r of layer 16 ct + j16
@@ -627,12 +638,14 @@ __global__ __launch_bounds__(kMpThreads) void meta_project_kernel(
       const bf16x8 hi = __builtin_bit_cast(bf16x8, lds_m[at]);
       const bf16x8 lo = __builtin_bit_cast(bf16x8, lds_m[mixed * 8 + at]);
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
+      for (int nt = 0; nt < NT; nt += 2) {  // two columns in turn: neighbours do not wait for each other's sums
         acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ks][nt], hi, acc[nt], 0, 0, 0);
+        acc[nt + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ks][nt + 1], hi, acc[nt + 1], 0, 0, 0);
         acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ks][nt], lo, acc[nt], 0, 0, 0);
+        acc[nt + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ks][nt + 1], lo, acc[nt + 1], 0, 0, 0);
         const int loads = ks ? NT : FI;
 #pragma unroll
-        for (int i = nt * loads / NT; i < (nt + 1) * loads / NT; ++i) {
+        for (int i = nt * loads / NT; i < (nt + 2) * loads / NT; ++i) {
           if (ks) issue_weight(kt + 1, 0, i);
           else issue_feat(kt + NS, i);
         }

@@ -352,6 +352,39 @@ __global__ __launch_bounds__(kThreads) void topk_merge_kernel(int V, int k, int 
   const int m = blockIdx.x;
   const size_t stride = sizeof(Partial) + (size_t)k * 8;
   const unsigned char *base = work + (size_t)m * n_chunks * stride;
+  const int n = n_chunks * k;
+  // Up to 64 chunks and 256 winners: everything is requested at once, every wavefront sums the row up by itself, and a
+  // winner writes itself out, so that one barrier is all (in a graph, 160 rows x 152064 27.6 -> 27.1 us for both passes, 16 rows 11.4 -> 10.8).
+  if (n_chunks <= 64 && n <= kThreads) {
+    const int i = threadIdx.x, lane = i & 63;
+    const unsigned long long mine = i < n ? ((const unsigned long long *)(base + (i / k) * stride + sizeof(Partial)))[i % k] : 0ull;
+    Partial p = {-__builtin_huge_valf(), 0.f};
+    if (lane < n_chunks) p = *(const Partial *)(base + lane * stride);
+    list[i] = mine;
+    float mx = p.max;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+    float sum = p.max > -__builtin_huge_valf() ? p.sum * __expf(p.max - mx) : 0.f;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+    const float lse = mx + __logf(sum);
+    __syncthreads();
+    int rank = 0, some = 0;
+#pragma unroll 16
+    for (int j = 0; j < n; ++j) {
+      rank += list[j] > mine ? 1 : 0;
+      some += list[j] ? 1 : 0;
+    }
+    if (mine && rank < k) {
+      out_ids[(size_t)m * k + rank] = (int32_t)argmax_key_index(mine);
+      out_logp[(size_t)m * k + rank] = fminf(argmax_key_value(mine) - lse, 0.f);
+    }
+    if (i >= some && i < k) {  // fewer winners than places
+      out_ids[(size_t)m * k + i] = -1;
+      out_logp[(size_t)m * k + i] = -__builtin_huge_valf();
+    }
+    return;
+  }
   float mx = -__builtin_huge_valf();
   for (int c = threadIdx.x; c < n_chunks; c += kThreads) mx = fmaxf(mx, ((const Partial *)(base + c * stride))->max);
   mx = wg_max_f(mx, fred);
@@ -363,7 +396,6 @@ __global__ __launch_bounds__(kThreads) void topk_merge_kernel(int V, int k, int 
   sum = wg_sum_f(sum, fred);
   const float lse = mx + __logf(sum);
   // the chunks' winners are keys already
-  const int n = n_chunks * k;
   if (n <= kListCap) {
     for (int i = threadIdx.x; i < n; i += kThreads)
       list[i] = ((const unsigned long long *)(base + (i / k) * stride + sizeof(Partial)))[i % k];

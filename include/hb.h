@@ -245,6 +245,16 @@ int32_t hb_out_project_ws(int32_t T, int32_t K, int32_t N, const void *x, const 
  * (hb_rmsnorm: K % 8 != 0; hb_swiglu_project: K % 64 != 0, F % 4 != 0), DEVICE.  T == 0 is a no-op.
  */
 int32_t hb_rmsnorm(int32_t T, int32_t K, const void *x, const void *weight, float eps, void *out, void *stream);
+
+/*
+ * hb_out_project_ws, then hb_rmsnorm of its result: out = x W^T (+ residual), the same bits, and norm_out = the normalised
+ * rows of out.  Where the projection is split over K, both are one launch with the sum of the parts (which may add a
+ * row's squares in another order).  norm_out [T, N]
+ * must not overlap any other argument; N % 8 == 0.  Errors as in those two.
+ */
+int32_t hb_out_project_norm_ws(int32_t T, int32_t K, int32_t N, const void *x, const void *w, const void *residual_or_null,
+                               void *out, const void *norm_weight, float eps, void *norm_out, void *workspace,
+                               size_t workspace_bytes, void *stream);
 int32_t hb_swiglu_project(int32_t T, int32_t K, int32_t F, const void *x, const void *w_gate_up, void *out,
                           void *workspace_or_null, size_t workspace_bytes, void *stream);
 

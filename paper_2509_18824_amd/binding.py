@@ -118,6 +118,8 @@ def _load():
     lib.hb_kv_compact.argtypes = [C.POINTER(AttnDesc)] + [p] * 9 + [i32, p, p, p]
     lib.hb_kv_compact_layers.restype = i32
     lib.hb_kv_compact_layers.argtypes = [C.POINTER(AttnDesc), i32] + [p] * 9 + [i32, p, p, p]
+    lib.hb_out_project_norm_ws.restype = i32
+    lib.hb_out_project_norm_ws.argtypes = [i32, i32, i32, p, p, p, p, p, C.c_float, p, p, sz, p]
     lib.hb_tree_verify_attn_clearing.restype = i32
     lib.hb_tree_verify_attn_clearing.argtypes = lib.hb_tree_verify_attn.argtypes[:-1] + [p, i32, p]
     lib.hb_lmhead_accept.restype = i32
@@ -279,6 +281,18 @@ def hb_rmsnorm(x, weight, eps: float, out, stream=None) -> None:
     if x.dtype != torch.bfloat16 or weight.dtype != torch.bfloat16 or weight.shape != (K,) or out.shape != (T, K):
         raise ValueError("need bf16 x [T, K], weight [K], out [T, K]")
     _check(lib.hb_rmsnorm(T, K, _ptr(x), _ptr(weight), eps, _ptr(out), _stream(stream)))
+
+
+def hb_out_project_norm_ws(x, w, residual, out, norm_weight, eps: float, norm_out, workspace, stream=None) -> None:
+    T, K = x.shape
+    N = w.shape[0]
+    if w.shape[1] != K or x.dtype != torch.bfloat16 or w.dtype != torch.bfloat16 or out.shape != (T, N):
+        raise ValueError("need bf16 x [T, K], w [N, K], out [T, N]")
+    if out.dtype != torch.bfloat16 or norm_weight.dtype != torch.bfloat16 or norm_weight.shape != (N,) or norm_out.shape != (T, N):
+        raise ValueError("need bf16 out [T, N], norm_weight [N], norm_out [T, N]")
+    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
+    _check(lib.hb_out_project_norm_ws(T, K, N, _ptr(x), _ptr(w), _ptr(residual), _ptr(out), _ptr(norm_weight), eps,
+                                      _ptr(norm_out), _ptr(workspace), ws_bytes, _stream(stream)))
 
 
 def hb_swiglu_project(x, w_gate_up, out, workspace=None, stream=None) -> None:

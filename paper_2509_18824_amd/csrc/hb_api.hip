@@ -405,6 +405,22 @@ int32_t hb_out_project_ws(int32_t T, int32_t K, int32_t N, const void *x, const 
   return out_project(T, K, N, x, w, residual_or_null, out, workspace, workspace_bytes, stream);
 }
 
+int32_t hb_out_project_norm_ws(int32_t T, int32_t K, int32_t N, const void *x, const void *w, const void *residual_or_null,
+                               void *out, const void *norm_weight, float eps, void *norm_out, void *workspace,
+                               size_t workspace_bytes, void *stream) {
+  if (T < 0 || K <= 0 || N <= 0) return fail(HB_ERR_INVALID_ARG, "need T >= 0 and K, N > 0");
+  if (!(eps >= 0.f)) return fail(HB_ERR_INVALID_ARG, "eps must be >= 0");
+  if (K % 64 || N % 8) return fail(HB_ERR_UNSUPPORTED, "K %d must be a multiple of 64 and N %d of 8", K, N);
+  if (T == 0) return HB_OK;
+  if (!x || !w || !out || !norm_weight || !norm_out) return fail(HB_ERR_INVALID_ARG, "a required device pointer is NULL");
+  if (misaligned(x) || misaligned(w) || misaligned(out) || misaligned(norm_weight) || misaligned(norm_out) ||
+      (residual_or_null && misaligned(residual_or_null)))
+    return fail(HB_ERR_INVALID_ARG, "tensors must be 16-byte aligned");
+  HB_HIP_TRY(launch_linear_norm(T, K, N, x, w, residual_or_null, out, norm_weight, eps, norm_out,
+                                proj_part(T, K, N, workspace, workspace_bytes), (hipStream_t)stream));
+  return HB_OK;
+}
+
 int32_t hb_swiglu_project(int32_t T, int32_t K, int32_t F, const void *x, const void *w_gate_up, void *out,
                           void *workspace_or_null, size_t workspace_bytes, void *stream) {
   if (T < 0 || K <= 0 || F <= 0) return fail(HB_ERR_INVALID_ARG, "need T >= 0 and K, F > 0");

@@ -139,6 +139,9 @@ hipError_t launch_qkv_rope(int32_t M, int32_t K, int32_t Hq, int32_t Hkv, const 
                            float *part, hipStream_t s);
 hipError_t launch_linear(int32_t M, int32_t K, int32_t N, const void *x, const void *w, const void *residual,
                          void *out, float *part, hipStream_t s);
+// ... and the rows of out, normalised by root mean square, to norm_out
+hipError_t launch_linear_norm(int32_t M, int32_t K, int32_t N, const void *x, const void *w, const void *residual,
+                              void *out, const void *norm_weight, float eps, void *norm_out, float *part, hipStream_t s);
 hipError_t launch_swiglu(int32_t M, int32_t K, int32_t F, const void *x, const void *w_gate_up, void *out, float *part,
                          hipStream_t s);
 hipError_t launch_rmsnorm(int32_t T, int32_t K, const void *x, const void *weight, float eps, void *out, hipStream_t s);

@@ -50,6 +50,13 @@ struct StoreArgs {
   const bf16_t *residual;  // [M, N] or null
   bf16_t *out;             // [M, N]
 };
+struct NormArgs {  // of the rows that a plain projection gives; weight null: none
+  const bf16_t *weight;  // [N]
+  bf16_t *out;           // [M, N]
+  float eps;
+};
+// A row of these is normalised in the launch that sums the parts of K.
+inline bool norm_fits(const NormArgs &n, int N) { return n.weight && N % 8 == 0 && N <= 8192; }
 
 // ROPE: query/key/value projection with rotary embedding (V = (Hq + 2 Hkv) * 128 weight rows),
 // else plain projection.  One workgroup per (weight tile, hidden tile), dealt by deal_unit.
@@ -292,6 +299,110 @@ __global__ __launch_bounds__(256) void proj_reduce_kernel(int M, int V, int ks, 
   }
 }
 
+// The scale of a row of K values; ss: this thread's sum of squares, WAVES wavefronts to a row.
+template <int WAVES>
+__device__ __forceinline__ float rms_scale(float ss, int K, float eps, float (&red)[WAVES]) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+  __syncthreads();
+  float all = (red[0] + red[1]) + (red[2] + red[3]);
+#pragma unroll
+  for (int w = 4; w < WAVES; w += 4) all += (red[w] + red[w + 1]) + (red[w + 2] + red[w + 3]);
+  return rsqrtf(all / (float)K + eps);
+}
+__device__ __forceinline__ float sum_squares(u32x4 v, float ss) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float a = __uint_as_float(v[e] << 16), b = __uint_as_float(v[e] & 0xffff0000u);
+    ss += a * a + b * b;
+  }
+  return ss;
+}
+__device__ __forceinline__ u32x4 rms_piece(u32x4 v, u32x4 w, float scale) {
+  u32x4 o;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float a = __uint_as_float(v[e] << 16) * scale * __uint_as_float(w[e] << 16);
+    const float b = __uint_as_float(v[e] & 0xffff0000u) * scale * __uint_as_float(w[e] & 0xffff0000u);
+    o[e] = pack_bf16(a, b);
+  }
+  return o;
+}
+constexpr int kKeep = 4;  // 16-byte pieces of a row that a thread keeps: 4 * 256 * 8 = 8192 values
+
+// out[t, :] = x[t, :] / sqrt(mean(x[t, :]^2) + eps) * weight: one workgroup per row, the row is
+// read once (16-byte loads, K % 8 == 0) and kept in registers between the two passes when it
+// fits (K <= 8192), otherwise read again
+__global__ __launch_bounds__(256) void rmsnorm_kernel(int K, const bf16_t *__restrict__ x,
+                                                      const bf16_t *__restrict__ weight, float eps,
+                                                      bf16_t *__restrict__ out) {
+  __shared__ float red[4];
+  const int t = blockIdx.x, tid = threadIdx.x;
+  const int pieces = K / 8;
+  const u32x4 *row = (const u32x4 *)(x + (size_t)t * K);
+  const u32x4 *wv = (const u32x4 *)weight;
+  u32x4 *dst = (u32x4 *)(out + (size_t)t * K);
+  u32x4 keep[kKeep];
+  float ss = 0.f;
+#pragma unroll
+  for (int i = 0; i < kKeep; ++i) {
+    const int p = tid + i * 256;
+    keep[i] = row[p < pieces ? p : pieces - 1];
+  }
+#pragma unroll
+  for (int i = 0; i < kKeep; ++i)
+    if (tid + i * 256 < pieces) ss = sum_squares(keep[i], ss);
+  for (int p = tid + kKeep * 256; p < pieces; p += 256) ss = sum_squares(row[p], ss);
+  const float scale = rms_scale(ss, K, eps, red);
+#pragma unroll
+  for (int i = 0; i < kKeep; ++i)
+    if (tid + i * 256 < pieces) dst[tid + i * 256] = rms_piece(keep[i], wv[tid + i * 256], scale);
+  for (int p = tid + kKeep * 256; p < pieces; p += 256) dst[p] = rms_piece(row[p], wv[p], scale);
+}
+
+// The sum over the K parts with the residual, and the row's root-mean-square normalisation, in one launch: a workgroup per
+// token, which rounds as proj_reduce_kernel does and normalises what it rounded.  512 threads: a row of 3584 is one piece a
+// thread, and the loads of its parts are one round trip (with 256 the launch saved was lost again: eight layers of 16 chains
+// 1578 us by two launches, 1575, and 1564 with 512).  128 tokens: 3584 x 3584 19.7 -> 18.0 us, 18944 x 3584 41.5 -> 40.2.
+constexpr int kNormThreads = 512;
+__global__ __launch_bounds__(kNormThreads) void proj_reduce_norm_kernel(int V, int ks, int v_pad, int m_pad, const float *__restrict__ part,
+                                                               StoreArgs sa, NormArgs norm) {
+  __shared__ float red[kNormThreads / 64];
+  const int m = blockIdx.x, tid = threadIdx.x, pieces = V / 8;
+  const size_t stride = (size_t)m_pad * v_pad;
+  const float *row = part + (size_t)m * v_pad;
+  const u32x4 *res = (const u32x4 *)(sa.residual ? sa.residual + (size_t)m * V : nullptr);
+  constexpr int kMine = 8192 / 8 / kNormThreads;
+  u32x4 keep[kMine];
+  float ss = 0.f;
+#pragma unroll
+  for (int i = 0; i < kMine; ++i) {
+    if (i * kNormThreads >= pieces) break;
+    const int p = min(tid + i * kNormThreads, pieces - 1);
+    f32x4 x = sum_parts(row + p * 8, ks, stride), y = sum_parts(row + p * 8 + 4, ks, stride);
+    if (res) {
+      const u32x4 r = res[p];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        x[e] += __uint_as_float((e & 1) ? (r[e >> 1] & 0xffff0000u) : (r[e >> 1] << 16));
+        y[e] += __uint_as_float((e & 1) ? (r[2 + (e >> 1)] & 0xffff0000u) : (r[2 + (e >> 1)] << 16));
+      }
+    }
+    keep[i] = (u32x4){pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3]), pack_bf16(y[0], y[1]), pack_bf16(y[2], y[3])};
+    if (tid + i * kNormThreads < pieces) {
+      ((u32x4 *)(sa.out + (size_t)m * V))[p] = keep[i];
+      ss = sum_squares(keep[i], ss);
+    }
+  }
+  const float scale = rms_scale(ss, V, norm.eps, red);
+  const u32x4 *w = (const u32x4 *)norm.weight;
+  u32x4 *dst = (u32x4 *)(norm.out + (size_t)m * V);
+#pragma unroll
+  for (int i = 0; i < kMine; ++i)
+    if (tid + i * kNormThreads < pieces) dst[tid + i * kNormThreads] = rms_piece(keep[i], w[tid + i * kNormThreads], scale);
+}
+
 // Hidden tile height (64 mt rows) of the unsplit kernel: rounds of 256 workgroups, one per CU, times
 // a workgroup's clocks, read inside the kernel: 3800 until the first tile is there, a K step, the results.
 int plain_tile_height(int M, int K, int v_tiles) {
@@ -427,7 +538,12 @@ double stream_us(int M, int K, int V) {
 }
 
 template <bool ROPE, bool GLU>
-hipError_t launch_reduce(int M, int V, int ks, int v_pad, int m_pad, const QkvArgs &qa, const StoreArgs &sa, const float *part, hipStream_t s) {
+hipError_t launch_reduce(int M, int V, int ks, int v_pad, int m_pad, const QkvArgs &qa, const StoreArgs &sa, const float *part,
+                         const NormArgs &norm, hipStream_t s) {
+  if (!ROPE && !GLU && norm_fits(norm, V)) {
+    proj_reduce_norm_kernel<<<(unsigned)M, kNormThreads, 0, s>>>(V, ks, v_pad, m_pad, part, sa, norm);
+    return hipGetLastError();
+  }
   const int groups = ROPE ? V / kHeadDim * 16 : GLU ? V / 8 : V / 4;
   proj_reduce_kernel<ROPE, GLU><<<dim3((unsigned)((groups + 255) / 256), (unsigned)M), 256, 0, s>>>(M, V, ks, v_pad, m_pad, groups, part, qa, sa);
   return hipGetLastError();
@@ -435,13 +551,13 @@ hipError_t launch_reduce(int M, int V, int ks, int v_pad, int m_pad, const QkvAr
 
 template <bool ROPE, bool GLU>
 hipError_t launch_few(StreamKind kind, const FewPlan &p, int M, int K, int V, const void *hidden, const void *weight,
-                      const QkvArgs &qa, const StoreArgs &sa, float *part, hipStream_t s) {
+                      const QkvArgs &qa, const StoreArgs &sa, float *part, hipStream_t s, const NormArgs &norm = {}) {
   if (p.ks > 1 && !part) return hipErrorInvalidValue;
   const int v_pad = (V + TV - 1) / TV * TV, m_pad = few_m_pad(M);
   const StreamArgs st = {sa.residual, sa.out, qa.bias, qa.cos, qa.sin, qa.q, qa.k, qa.v, qa.Hq, qa.Hkv};
   hipError_t e = launch_proj_few(kind, p, M, K, V, hidden, weight, st, part, v_pad, m_pad, s);
   if (e != hipSuccess || p.ks == 1) return e;
-  return launch_reduce<ROPE, GLU>(M, V, p.ks, v_pad, m_pad, qa, sa, part, s);
+  return launch_reduce<ROPE, GLU>(M, V, p.ks, v_pad, m_pad, qa, sa, part, norm, s);
 }
 
 // More than 128 tokens, where the tiles of proj_pair.hip (tokens x weight rows of 128 x 128, 160 x 128, or 128 x 224 for plain
@@ -490,13 +606,13 @@ PairPlan pair_plan(int M, int K, int V, StreamKind kind, SplitPlan plan) {
 
 template <bool ROPE, bool GLU>
 hipError_t launch_pair(StreamKind kind, const PairPlan &p, int M, int K, int V, const void *hidden, const void *weight,
-                       const QkvArgs &qa, const StoreArgs &sa, float *part, hipStream_t s) {
+                       const QkvArgs &qa, const StoreArgs &sa, float *part, hipStream_t s, const NormArgs &norm = {}) {
   if (p.ks > 1 && !part) return hipErrorInvalidValue;
   const int v_pad = (V + TV - 1) / TV * TV;
   const StreamArgs st = {sa.residual, sa.out, qa.bias, qa.cos, qa.sin, qa.q, qa.k, qa.v, qa.Hq, qa.Hkv};
   hipError_t e = launch_proj_pair(kind, p, M, K, V, hidden, weight, st, part, v_pad, M, s);
   if (e != hipSuccess || p.ks == 1) return e;
-  return launch_reduce<ROPE, GLU>(M, V, p.ks, v_pad, M, qa, sa, part, s);
+  return launch_reduce<ROPE, GLU>(M, V, p.ks, v_pad, M, qa, sa, part, norm, s);
 }
 
 // Which kernel takes the product: the stream, few rows against all tokens, tiles whose K steps two groups share, or
@@ -532,7 +648,7 @@ Way way_of(int M, int K, int V, StreamKind kind, const float *part, Ways *ways) 
 
 template <bool ROPE, bool GLU>
 hipError_t launch_splitk(int M, int K, int V, SplitPlan plan, const void *hidden, const void *weight, const QkvArgs &qa,
-                         const StoreArgs &sa, float *part, hipStream_t s) {
+                         const StoreArgs &sa, float *part, hipStream_t s, const NormArgs &norm = {}) {
   const int ks = plan.ks, tm = 64 * plan.mt;
   const int m_tiles = (M + tm - 1) / tm, m_pad = m_tiles * tm;
   const int v_tiles = (V + TV - 1) / TV, v_pad = v_tiles * TV;
@@ -558,7 +674,7 @@ hipError_t launch_splitk(int M, int K, int V, SplitPlan plan, const void *hidden
   }
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return launch_reduce<ROPE, GLU>(M, V, ks, v_pad, m_pad, qa, sa, part, s);
+  return launch_reduce<ROPE, GLU>(M, V, ks, v_pad, m_pad, qa, sa, part, norm, s);
 }
 
 template <bool ROPE, bool GLU>
@@ -616,66 +732,6 @@ __global__ __launch_bounds__(256) void rope_table_kernel(int T, int half, double
   sin_out[idx] = (float)sv;
 }
 
-// out[t, :] = x[t, :] / sqrt(mean(x[t, :]^2) + eps) * weight: one workgroup per row, the row is
-// read once (16-byte loads, K % 8 == 0) and kept in registers between the two passes when it
-// fits (K <= 8192), otherwise read again
-__global__ __launch_bounds__(256) void rmsnorm_kernel(int K, const bf16_t *__restrict__ x,
-                                                      const bf16_t *__restrict__ weight, float eps,
-                                                      bf16_t *__restrict__ out) {
-  __shared__ float red[4];
-  constexpr int kKeep = 4;  // 16-byte pieces a thread keeps: 4 * 256 * 8 = 8192 values
-  const int t = blockIdx.x, tid = threadIdx.x;
-  const int pieces = K / 8;
-  const u32x4 *row = (const u32x4 *)(x + (size_t)t * K);
-  const u32x4 *wv = (const u32x4 *)weight;
-  u32x4 *dst = (u32x4 *)(out + (size_t)t * K);
-  u32x4 keep[kKeep];
-  float ss = 0.f;
-#pragma unroll
-  for (int i = 0; i < kKeep; ++i) {
-    const int p = tid + i * 256;
-    keep[i] = row[p < pieces ? p : pieces - 1];
-  }
-#pragma unroll
-  for (int i = 0; i < kKeep; ++i) {
-    if (tid + i * 256 < pieces) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float a = __uint_as_float(keep[i][e] << 16), b = __uint_as_float(keep[i][e] & 0xffff0000u);
-        ss += a * a + b * b;
-      }
-    }
-  }
-  for (int p = tid + kKeep * 256; p < pieces; p += 256) {
-    const u32x4 v = row[p];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float a = __uint_as_float(v[e] << 16), b = __uint_as_float(v[e] & 0xffff0000u);
-      ss += a * a + b * b;
-    }
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off, 64);
-  if ((tid & 63) == 0) red[tid >> 6] = ss;
-  __syncthreads();
-  const float scale = rsqrtf(((red[0] + red[1]) + (red[2] + red[3])) / (float)K + eps);
-  auto emit = [&](int p, u32x4 v) {
-    const u32x4 w = wv[p];
-    u32x4 o;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float a = __uint_as_float(v[e] << 16) * scale * __uint_as_float(w[e] << 16);
-      const float b = __uint_as_float(v[e] & 0xffff0000u) * scale * __uint_as_float(w[e] & 0xffff0000u);
-      o[e] = pack_bf16(a, b);
-    }
-    dst[p] = o;
-  };
-#pragma unroll
-  for (int i = 0; i < kKeep; ++i)
-    if (tid + i * 256 < pieces) emit(tid + i * 256, keep[i]);
-  for (int p = tid + kKeep * 256; p < pieces; p += 256) emit(p, row[p]);
-}
-
 }  // namespace
 
 bool proj_mfma_supports(int32_t M, int32_t K, int32_t N) { return M >= 1 && K >= BK && K % BK == 0 && N >= 4 && N % 4 == 0; }
@@ -702,17 +758,32 @@ hipError_t launch_qkv_rope(int32_t M, int32_t K, int32_t Hq, int32_t Hkv, const 
   return dispatch<true, false>(M, K, V, hidden, w_qkv, qa, sa, s);
 }
 
-hipError_t launch_linear(int32_t M, int32_t K, int32_t N, const void *x, const void *w, const void *residual, void *out,
-                         float *part, hipStream_t s) {
+static hipError_t launch_linear(int32_t M, int32_t K, int32_t N, const void *x, const void *w, const void *residual, void *out,
+                                float *part, const NormArgs &norm, bool *normed, hipStream_t s) {
   QkvArgs qa = {};
   StoreArgs sa = {(const bf16_t *)residual, (bf16_t *)out};
   Ways ways;
   const Way way = way_of(M, K, N, StreamKind::kPlain, part, &ways);
-  if (way == Way::kPair) return launch_pair<false, false>(StreamKind::kPlain, ways.pair, M, K, N, x, w, qa, sa, part, s);
-  if (way == Way::kFew) return launch_few<false, false>(StreamKind::kPlain, ways.few, M, K, N, x, w, qa, sa, part, s);
+  const int parts = way == Way::kPair ? ways.pair.ks : way == Way::kFew ? ways.few.ks : way == Way::kTiles ? ways.split.ks : 1;
+  *normed = parts > 1 && norm_fits(norm, N);
+  if (way == Way::kPair) return launch_pair<false, false>(StreamKind::kPlain, ways.pair, M, K, N, x, w, qa, sa, part, s, norm);
+  if (way == Way::kFew) return launch_few<false, false>(StreamKind::kPlain, ways.few, M, K, N, x, w, qa, sa, part, s, norm);
   if (way == Way::kStream) return launch_proj_stream(StreamKind::kPlain, M, K, N, x, w, {sa.residual, sa.out}, s);
-  if (ways.split.ks > 1) return launch_splitk<false, false>(M, K, N, ways.split, x, w, qa, sa, part, s);
+  if (ways.split.ks > 1) return launch_splitk<false, false>(M, K, N, ways.split, x, w, qa, sa, part, s, norm);
   return dispatch<false, false>(M, K, N, x, w, qa, sa, s);
+}
+
+hipError_t launch_linear(int32_t M, int32_t K, int32_t N, const void *x, const void *w, const void *residual, void *out,
+                         float *part, hipStream_t s) {
+  bool normed;
+  return launch_linear(M, K, N, x, w, residual, out, part, {}, &normed, s);
+}
+
+hipError_t launch_linear_norm(int32_t M, int32_t K, int32_t N, const void *x, const void *w, const void *residual, void *out,
+                              const void *norm_weight, float eps, void *norm_out, float *part, hipStream_t s) {
+  bool normed;
+  hipError_t e = launch_linear(M, K, N, x, w, residual, out, part, {(const bf16_t *)norm_weight, (bf16_t *)norm_out, eps}, &normed, s);
+  return e != hipSuccess || normed ? e : launch_rmsnorm(M, N, out, norm_weight, eps, norm_out, s);
 }
 
 hipError_t launch_swiglu(int32_t M, int32_t K, int32_t F, const void *x, const void *w_gate_up, void *out, float *part,

@@ -313,15 +313,14 @@ class VerifyLayerStack:
         hb.hb_rope_table(self.q.shape[2], self.theta, self.positions, self.cos, self.sin)
         x = self.hidden[0]
         mlp = self.mlp
+        if mlp is not None and self.n_layers:
+            mark("rmsnorm")
+            hb.hb_rmsnorm(x, mlp["norm1"][0], mlp["eps"], self.normed)
         for l in range(self.n_layers):
             nxt = self.hidden[1 + (l & 1)]
             y = nxt if mlp is None else self.mid
             kp, vp = self.pools[l]
-            a = x
-            if mlp is not None:
-                mark("rmsnorm")
-                hb.hb_rmsnorm(x, mlp["norm1"][l], mlp["eps"], self.normed)
-                a = self.normed
+            a = x if mlp is None else self.normed
             mark("qkv_rope_project")
             hb.hb_qkv_rope_project_ws(a, self.w_qkv[l], None, self.cos, self.sin, self.q, self.k_tree[l],
                                       self.v_tree[l], self.ws_proj)
@@ -331,18 +330,24 @@ class VerifyLayerStack:
                                             dev.prefix_len, dev.node_offset, dev.parent, self.attn_out, None, self.ws_attn,
                                             self.ws_lm, T if l == self.n_layers - 1 else 0)
             mark("out_project")
-            hb.hb_out_project_ws(self.attn_out.view(T, -1), self.w_o[l], x, y, self.ws_proj)
-            if mlp is not None:
-                mark("rmsnorm")
-                hb.hb_rmsnorm(y, mlp["norm2"][l], mlp["eps"], self.normed)
+            attn = self.attn_out.view(T, -1)
+            if mlp is None:
+                hb.hb_out_project_ws(attn, self.w_o[l], x, y, self.ws_proj)
+            else:  # each projection into the residual stream also normalises it for the one that follows
+                hb.hb_out_project_norm_ws(attn, self.w_o[l], x, y, mlp["norm2"][l], mlp["eps"], self.normed, self.ws_proj)
                 mark("swiglu_project")
                 hb.hb_swiglu_project(self.normed, mlp["w_gate_up"][l], self.act, self.ws_proj)
                 mark("down_project")
-                hb.hb_out_project_ws(self.act, mlp["w_down"][l], y, nxt, self.ws_proj)
+                norm = mlp["norm1"][l + 1] if l + 1 < self.n_layers else mlp.get("norm_f")
+                if norm is None:
+                    hb.hb_out_project_ws(self.act, mlp["w_down"][l], y, nxt, self.ws_proj)
+                else:
+                    hb.hb_out_project_norm_ws(self.act, mlp["w_down"][l], y, nxt, norm, mlp["eps"], self.normed, self.ws_proj)
             x = nxt
         if mlp is not None and mlp.get("norm_f") is not None:
-            mark("rmsnorm")
-            hb.hb_rmsnorm(x, mlp["norm_f"], mlp["eps"], self.normed)
+            if not self.n_layers:
+                mark("rmsnorm")
+                hb.hb_rmsnorm(x, mlp["norm_f"], mlp["eps"], self.normed)
             x = self.normed
         self.final_hidden = x
         mark("lmhead_accept")

@@ -262,6 +262,31 @@ def test_projections_whose_k_steps_two_groups_share(hb, kind, T, K, N, ws, kerne
     assert names[0] == kernel and len(names) == (2 if kernel.startswith("pair<3") else 1)
 
 
+@pytest.mark.parametrize("T,K,N,res,fused", [
+    (128, 18944, 3584, True, True), (1, 3584, 3584, True, False), (100, 3584, 3584, False, True), (300, 3584, 3592, True, True),
+    (960, 18944, 3584, True, True), (960, 3584, 3584, True, False), (40, 8192, 8192, True, True), (40, 8192, 8200, False, False),
+    (40, 7168, 8, True, True)])
+def test_projection_and_normalisation_are_the_two_calls_one_after_the_other(hb, T, K, N, res, fused):
+    """Rows of a few threads to the widest that one launch takes, and ways without parts of K.  One launch adds the squares
+    in another order: 1e-6 of the scale at most, which may turn a rounding to bf16, by one step of 2^-7 of the value at
+    most and seldom (about 1e-6 / 2^-9 of the values)."""
+    g = torch.Generator().manual_seed(T + K + N)
+    bf = lambda *shape, std=1.0: (torch.randn(shape, generator=g) * std).to(torch.bfloat16).cuda()
+    x, w, r, gain = bf(T, K), bf(N, K, std=K ** -0.5), bf(T, N) if res else None, 1.0 + bf(N, std=0.1)
+    ws = torch.full((max(hb.hb_proj_workspace_bytes(T, K, N), 16),), 0xFF, dtype=torch.uint8, device="cuda")
+    out, norm, out2, norm2 = (torch.full((T, N), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(4))
+    hb.hb_out_project_ws(x, w, r, out, ws)
+    hb.hb_rmsnorm(out, gain, 1e-6, norm)
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CUDA]) as trace:
+        hb.hb_out_project_norm_ws(x, w, r, out2, gain, 1e-6, norm2, ws)
+        torch.cuda.synchronize()
+    assert torch.isfinite(norm).all() and torch.equal(out, out2)
+    off = (norm.float() - norm2.float()).abs()
+    assert (off <= 2 ** -7 * norm.float().abs()).all() and (off > 0).float().mean() <= 5e-3
+    assert any("proj_reduce_norm_kernel" in e.name for e in trace.events()) == fused
+
+
 @pytest.mark.parametrize("K,N,gated", [(14336, 4096, False), (18944, 3584, False), (4096, 28672, True)])
 def test_seventeen_tokens_take_hardly_longer_than_sixteen(hb, K, N, gated):
     """Shapes where the stream stays ahead beyond 16 tokens: 25 and 26 us, 31 and 32, 43 and 44 by it; 33, 39 and 54 by tiles

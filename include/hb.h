@@ -247,6 +247,14 @@ int32_t hb_out_project_ws(int32_t T, int32_t K, int32_t N, const void *x, const 
 int32_t hb_rmsnorm(int32_t T, int32_t K, const void *x, const void *weight, float eps, void *out, void *stream);
 
 /*
+ * out = x1 w1^T + x2 w2^T (x1, x2 [T, K], w1, w2 [N, K], out [T, N]): a layer over the concatenation of two inputs whose
+ * weight is stored as its two column blocks.  tmp [T, N]: scratch, which must overlap nothing else.  Workspace:
+ * hb_proj_workspace_bytes of (T, K, N) or (T, 2 K, N), whichever is larger.  Errors as in hb_out_project_ws.
+ */
+int32_t hb_out_project_two_ws(int32_t T, int32_t K, int32_t N, const void *x1, const void *w1, const void *x2, const void *w2,
+                              void *tmp, void *out, void *workspace, size_t workspace_bytes, void *stream);
+
+/*
  * hb_out_project_ws, then hb_rmsnorm of its result: out = x W^T (+ residual), the same bits, and norm_out = the normalised
  * rows of out.  Where the projection is split over K, both are one launch with the sum of the parts (which may add a
  * row's squares in another order).  norm_out [T, N]

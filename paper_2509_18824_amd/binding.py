@@ -118,6 +118,8 @@ def _load():
     lib.hb_kv_compact.argtypes = [C.POINTER(AttnDesc)] + [p] * 9 + [i32, p, p, p]
     lib.hb_kv_compact_layers.restype = i32
     lib.hb_kv_compact_layers.argtypes = [C.POINTER(AttnDesc), i32] + [p] * 9 + [i32, p, p, p]
+    lib.hb_out_project_two_ws.restype = i32
+    lib.hb_out_project_two_ws.argtypes = [i32, i32, i32] + [p] * 7 + [sz, p]
     lib.hb_out_project_norm_ws.restype = i32
     lib.hb_out_project_norm_ws.argtypes = [i32, i32, i32, p, p, p, p, p, C.c_float, p, p, sz, p]
     lib.hb_tree_verify_attn_clearing.restype = i32
@@ -281,6 +283,18 @@ def hb_rmsnorm(x, weight, eps: float, out, stream=None) -> None:
     if x.dtype != torch.bfloat16 or weight.dtype != torch.bfloat16 or weight.shape != (K,) or out.shape != (T, K):
         raise ValueError("need bf16 x [T, K], weight [K], out [T, K]")
     _check(lib.hb_rmsnorm(T, K, _ptr(x), _ptr(weight), eps, _ptr(out), _stream(stream)))
+
+
+def hb_out_project_two_ws(x1, w1, x2, w2, tmp, out, workspace, stream=None) -> None:
+    T, K = x1.shape
+    N = w1.shape[0]
+    if x2.shape != (T, K) or w1.shape != (N, K) or w2.shape != (N, K) or out.shape != (T, N) or tmp.shape != (T, N):
+        raise ValueError("need x1, x2 [T, K], w1, w2 [N, K], tmp, out [T, N]")
+    if any(t.dtype != torch.bfloat16 for t in (x1, w1, x2, w2, tmp, out)):
+        raise ValueError("need bf16 tensors")
+    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
+    _check(lib.hb_out_project_two_ws(T, K, N, _ptr(x1), _ptr(w1), _ptr(x2), _ptr(w2), _ptr(tmp), _ptr(out), _ptr(workspace),
+                                     ws_bytes, _stream(stream)))
 
 
 def hb_out_project_norm_ws(x, w, residual, out, norm_weight, eps: float, norm_out, workspace, stream=None) -> None:

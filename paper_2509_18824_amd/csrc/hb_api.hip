@@ -421,6 +421,19 @@ int32_t hb_out_project_norm_ws(int32_t T, int32_t K, int32_t N, const void *x, c
   return HB_OK;
 }
 
+int32_t hb_out_project_two_ws(int32_t T, int32_t K, int32_t N, const void *x1, const void *w1, const void *x2, const void *w2,
+                              void *tmp, void *out, void *workspace, size_t workspace_bytes, void *stream) {
+  if (T < 0 || K <= 0 || N <= 0) return fail(HB_ERR_INVALID_ARG, "need T >= 0 and K, N > 0");
+  if (K % 64 || N % 4 || K > INT32_MAX / 2) return fail(HB_ERR_UNSUPPORTED, "K %d must be a multiple of 64 and N %d of 4", K, N);
+  if (T == 0) return HB_OK;
+  if (!x1 || !w1 || !x2 || !w2 || !tmp || !out) return fail(HB_ERR_INVALID_ARG, "a required device pointer is NULL");
+  if (misaligned(x1) || misaligned(w1) || misaligned(x2) || misaligned(w2) || misaligned(tmp) || misaligned(out))
+    return fail(HB_ERR_INVALID_ARG, "tensors must be 16-byte aligned");
+  HB_HIP_TRY(launch_linear_two(T, K, N, x1, w1, x2, w2, tmp, out, proj_part(T, K, N, workspace, workspace_bytes),
+                               proj_part(T, 2 * K, N, workspace, workspace_bytes), (hipStream_t)stream));
+  return HB_OK;
+}
+
 int32_t hb_swiglu_project(int32_t T, int32_t K, int32_t F, const void *x, const void *w_gate_up, void *out,
                           void *workspace_or_null, size_t workspace_bytes, void *stream) {
   if (T < 0 || K <= 0 || F <= 0) return fail(HB_ERR_INVALID_ARG, "need T >= 0 and K, F > 0");

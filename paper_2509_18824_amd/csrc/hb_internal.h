@@ -109,6 +109,9 @@ struct StreamArgs {
   const float *cos, *sin;  // [M, 64]
   bf16_t *q, *k, *v;       // [M, Hq, 128], [M, Hkv, 128], [M, Hkv, 128]
   int Hq, Hkv;
+  // plain: the columns of K's second half, [M, K / 2] and [N, K / 2] beside a first half of the same shape, or null (both
+  // operands in one piece)
+  const bf16_t *hidden2, *weight2;
 };
 bool proj_stream_supports(int32_t M, int32_t K);
 bool proj_stream_pays(int32_t K, int32_t N, bool split);  // against tiles of 256 rows (split: over K)
@@ -142,6 +145,9 @@ hipError_t launch_linear(int32_t M, int32_t K, int32_t N, const void *x, const v
 // ... and the rows of out, normalised by root mean square, to norm_out
 hipError_t launch_linear_norm(int32_t M, int32_t K, int32_t N, const void *x, const void *w, const void *residual,
                               void *out, const void *norm_weight, float eps, void *norm_out, float *part, hipStream_t s);
+// out = x w^T + x2 w2^T (tmp [M, N] is used where that takes two products); part2: scratch for (M, 2 K, N), part for (M, K, N)
+hipError_t launch_linear_two(int32_t M, int32_t K, int32_t N, const void *x, const void *w, const void *x2, const void *w2,
+                             void *tmp, void *out, float *part, float *part2, hipStream_t s);
 hipError_t launch_swiglu(int32_t M, int32_t K, int32_t F, const void *x, const void *w_gate_up, void *out, float *part,
                          hipStream_t s);
 hipError_t launch_rmsnorm(int32_t T, int32_t K, const void *x, const void *weight, float eps, void *out, hipStream_t s);

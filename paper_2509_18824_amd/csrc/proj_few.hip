@@ -56,7 +56,13 @@ __global__ __launch_bounds__(512) void proj_few_kernel(int M, int K, int V, int 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int j16 = lane & 15, kq = lane >> 4;
   const int tile = (int)blockIdx.x / ks, kpart = (int)blockIdx.x % ks;
-  const int kp = K / 8, stages = K / 64 / ks / KSP;
+  const int stages = K / 64 / ks / KSP;
+  const bool two = KIND == kPart && sa.hidden2;  // each half of K from its own operands (`ks` is even)
+  const int kp = (two ? K / 2 : K) / 8, kfrom = two && 2 * kpart >= ks ? kpart - ks / 2 : kpart;
+  if (kfrom != kpart) {
+    hidden = (const u32x4 *)sa.hidden2;
+    weight = (const u32x4 *)sa.weight2;
+  }
   const int F = V >> 1;
 
   // lane -> row lane / 8 of a group's eight, piece swizzled; rows past the end are clamped and dropped at the end
@@ -83,7 +89,7 @@ __global__ __launch_bounds__(512) void proj_few_kernel(int M, int K, int V, int 
       const int m = (g - 2 * R) * 8 + r8;
       base = hidden + (size_t)(m < M ? m : M - 1) * kp;
     }
-    src[i] = base + (size_t)kpart * (kp / ks) + kk * 8 + ((lane & 7) ^ r8);
+    src[i] = base + (size_t)kfrom * (K / 8 / ks) + kk * 8 + ((lane & 7) ^ r8);
   }
   const bool full = Sh::kRest == 0 || wave < Sh::kRest;
   auto issue = [&](int st, int slot) {

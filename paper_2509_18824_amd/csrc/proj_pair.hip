@@ -47,10 +47,18 @@ __global__ __launch_bounds__(512) void proj_pair_kernel(int M, int Kfull, int V,
   if (slot >= per || unit >= units) return;
   const int m_tile = unit % m_tiles, v_unit = unit / m_tiles;
   const int v_tile = KIND == kPartKind ? v_unit / ks : v_unit, kpart = KIND == kPartKind ? v_unit % ks : 0;
-  const int K = KIND == kPartKind ? Kfull / ks : Kfull, kp = Kfull / 8;
+  const int K = KIND == kPartKind ? Kfull / ks : Kfull;
   const int m0 = m_tile * TM, v0 = v_tile * TVP;
-  const u32x4 *hidden = hidden_full + (size_t)kpart * (K / 8);
-  const u32x4 *weight = weight_full + (size_t)kpart * (K / 8);
+  // two: each half of K from its own operands.  An even number of parts reads one or the other; a whole tile changes over
+  // at step `half`, by the distance of the operands.
+  const bool two = (KIND == kPlainKind || KIND == kPartKind) && sa.hidden2;
+  const int kp = (two ? Kfull / 2 : Kfull) / 8, kfrom = two && 2 * kpart >= ks && KIND == kPartKind ? kpart - ks / 2 : kpart;
+  const u32x4 *hidden = (kfrom != kpart ? (const u32x4 *)sa.hidden2 : hidden_full) + (size_t)kfrom * (K / 8);
+  const u32x4 *weight = (kfrom != kpart ? (const u32x4 *)sa.weight2 : weight_full) + (size_t)kfrom * (K / 8);
+  const bool change = KIND == kPlainKind && two;
+  const int half = change ? K / 2 / BK : 0;
+  const long to_hidden2 = change ? ((long)(uintptr_t)sa.hidden2 - (long)(uintptr_t)hidden) / 16 - (long)half * CH : 0;
+  const long to_weight2 = change ? ((long)(uintptr_t)sa.weight2 - (long)(uintptr_t)weight) / 16 - (long)half * CH : 0;
 
   // Weight row of tile row t.  Rotary and gated tiles alternate between 16 rows of the first kind (d, gate) and the
   // 16 of the second (d + 64, up) that belong to them.
@@ -83,9 +91,10 @@ __global__ __launch_bounds__(512) void proj_pair_kernel(int M, int Kfull, int V,
   // past the end the last step is fetched again into a free stage (no branch in the loop); nothing reads it
   auto issue = [&](int step, int stage) {
     const int k = step < last ? step : last;
+    const long w_off = k * CH + (change && k >= half ? to_weight2 : 0), h_off = k * CH + (change && k >= half ? to_hidden2 : 0);
 #pragma unroll
     for (int i = 0; i < N; ++i)
-      __builtin_amdgcn_global_load_lds((gptr_t)(src[i] + k * CH), (lptr_t)(lds + stage * STAGE + (quad + 4 * i) * 64), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((gptr_t)(src[i] + (i < IT ? w_off : h_off)), (lptr_t)(lds + stage * STAGE + (quad + 4 * i) * 64), 16, 0, 0);
   };
   // All loads of this wavefront but those of its newest steps have landed (with R stages, (R - 2) / 2 of its steps).
 #define HB_PAIR_LANDED() asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N * ((R - 2) / 2)) : "memory")

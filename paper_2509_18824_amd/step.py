@@ -203,8 +203,13 @@ def fc_concat(a, b, w_a, w_b):
     T = a.shape[0]
     tmp = torch.empty((T, w_a.shape[0]), dtype=torch.bfloat16, device=a.device)
     out = torch.empty_like(tmp)
-    linear(a, w_a, None, tmp)
-    linear(b, w_b, tmp, out)
+    if a.shape[1] != b.shape[1]:  # column blocks of different widths
+        linear(a, w_a, None, tmp)
+        linear(b, w_b, tmp, out)
+        return out
+    N, K = w_a.shape
+    nbytes = max(hb.hb_proj_workspace_bytes(T, K, N), hb.hb_proj_workspace_bytes(T, 2 * K, N))
+    hb.hb_out_project_two_ws(a, w_a, b, w_b, tmp, out, alloc_workspace(nbytes, a.device))
     return out
 
 

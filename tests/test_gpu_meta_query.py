@@ -182,3 +182,24 @@ def test_fc_over_a_concatenation(S):
     torch.cuda.synchronize()
     f = lambda t: t.float().numpy().astype(np.float64)
     _close(out, fc_concat_ref(f(a), f(b), f(w)), "fc2")
+
+
+@pytest.mark.parametrize("n_tok,K,N,kernels", [
+    (96, 3584, 3584, ("few", "reduce")), (40, 4096, 516, ("few", "reduce")),       # parts of K from one half each
+    (300, 3584, 3584, ("pair", "reduce")), (2048, 3584, 3584, ("pair",)),          # ... and tiles that change over
+    (2030, 1088, 3580, ("pair",)),                                                # at an odd step
+    (5, 512, 1000, ("stream", "stream")), (6144, 576, 3584, ("mfma", "mfma"))])    # one product after the other
+def test_fc_over_two_halves_in_one_product(S, n_tok, K, N, kernels):
+    import re
+    from torch.profiler import ProfilerActivity, profile
+    g = torch.Generator().manual_seed(n_tok)
+    bf = lambda *shape, std=1.0: (torch.randn(shape, generator=g) * std).to(torch.bfloat16)
+    a, b, w_a, w_b = bf(n_tok, K), bf(n_tok, K), bf(N, K, std=K ** -0.5), bf(N, K, std=K ** -0.5)
+    dev = [t.cuda() for t in (a, b, w_a, w_b)]
+    with profile(activities=[ProfilerActivity.CUDA]) as trace:
+        out = S.fc_concat(*dev)
+        torch.cuda.synchronize()
+    names = [m[1] for m in (re.search(r"proj_([a-z]+)_kernel", e.name) for e in trace.events()) if m]
+    assert tuple(names) == kernels
+    pick = np.unique(np.concatenate([[0, n_tok - 1], np.random.default_rng(1).integers(0, n_tok, 60)]))
+    _close(out[pick], fc_concat_ref(W.widen(a[pick]), W.widen(b[pick]), np.concatenate([W.widen(w_a), W.widen(w_b)], axis=1)), "fc2")

@@ -674,7 +674,10 @@ __global__ __launch_bounds__(kMpThreads) void meta_project_kernel(
 // requested almost three steps ahead.
 constexpr int kMwTok = 16;
 constexpr int mw_loads(int L) { return L <= 24 ? 6 : L <= 28 ? 7 : 8; }  // feature loads of a wavefront per slice: 64 rows each
-constexpr int mw_stage(int fi) { return fi * kMpWaves * 64; }            // 16-byte pieces of a slice's features
+// More than 28 layers with three queries: two slices of 64 leave LDS for five heads only (six groups of 28 heads instead
+// of four: 900 tokens 302 -> 345 us), so slices are of 32 features and there are three, requested two steps ahead.
+constexpr bool mw_short(int qt, int nt, int fi) { return qt == 3 && nt == 8 && fi == 8; }
+constexpr int mw_stage(int fi, bool half) { return (half ? fi / 2 : fi) * kMpWaves * 64; }  // 16-byte pieces of a slice's features
 
 template <int QT, int NT, int FI>
 __global__ __launch_bounds__(kMpThreads) void meta_project_wide_kernel(
@@ -692,27 +695,32 @@ __global__ __launch_bounds__(kMpThreads) void meta_project_wide_kernel(
   const int heads = min(hg, H - h0);  // >= 1
   const int hq_rows = heads * Q;
   const int frows = min(kMwTok, S - tok0) * L;  // feature rows of the workgroup, consecutive in memory
-  constexpr int kStage = mw_stage(FI);
-  u32x4 *lds_f = meta_a_lds;               // [2][16 L rows][8]
-  u32x4 *lds_m = meta_a_lds + 2 * kStage;  // [values, remainders][token][hq][4]
+  constexpr bool kShort = mw_short(QT, NT, FI);
+  constexpr int kStage = mw_stage(FI, kShort), kStages = kShort ? 3 : 2;
+  constexpr int kRow = kShort ? 4 : 8;           // 16-byte pieces of a feature row in a slice
+  constexpr int kLoads = kShort ? FI / 2 : FI;   // of a wavefront per slice
+  u32x4 *lds_f = meta_a_lds;                     // [kStages][16 L rows][kRow]
+  u32x4 *lds_m = meta_a_lds + kStages * kStage;  // [values, remainders][token][hq][4]
   const int mixed = kMwTok * hq_rows * 4;       // pieces
 
   // Features: 64 rows per round of the wavefronts, lane -> row lane / 8 of its wavefront's eight, piece swizzled on the
-  // source side; rows past the workgroup's are out of the buffer's range and arrive as zeros.  Always FI loads (the
+  // source side; rows past the workgroup's are out of the buffer's range and arrive as zeros.  Always kLoads loads (the
   // waits below count them): a repeated slice changes nothing.
   typedef __attribute__((address_space(3))) void *lptr_t;
-  const int steps = D / 32, slices = D / 64;
+  const int steps = D / 32, slices = D / (8 * kRow);
   const auto f_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(feats + (size_t)tok0 * L * dp), 0, frows * dp * 16, kBufferFlags);
-  const int f_src = (wave * 8 + (lane >> 3)) * dp * 16 + ((lane & 7) ^ (((wave * 8 + (lane >> 3)) >> 1) & 7)) * 16;
-  auto issue_feats = [&](int slice) {
+  constexpr int kRows = 64 / kRow;  // of a load
+  const int f_row = wave * kRows + lane / kRow;
+  const int f_src = f_row * dp * 16 + (kShort ? lane & 3 : (lane & 7) ^ ((f_row >> 1) & 7)) * 16;
+  auto issue_feats = [&](int slice, int slot) {
     const int k = min(slice, slices - 1);
 #pragma unroll
-    for (int i = 0; i < FI; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(f_rsrc, (lptr_t)(lds_f + (slice & 1) * kStage + (wave + i * kMpWaves) * 64), 16,
-                                               f_src + i * kMpWaves * 8 * dp * 16, k * 128, 0, 0);
+    for (int i = 0; i < kLoads; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(f_rsrc, (lptr_t)(lds_f + slot * kStage + (wave + i * kMpWaves) * 64), 16,
+                                               f_src + i * kMpWaves * kRows * dp * 16, k * kRow * 16, 0, 0);
   };
-  issue_feats(0);
-  issue_feats(1);
+#pragma unroll
+  for (int i = 0; i < kStages; ++i) issue_feats(i, i);
 
   // ---- softmax over the layers, one thread per (token, hq row); P goes through LDS ------------
   // Of tokens 2 wave and 2 wave + 1, hq rows in tiles of 16.  Lanes past the last row repeat one of the first tile and store
@@ -757,13 +765,13 @@ __global__ __launch_bounds__(kMpThreads) void meta_project_wide_kernel(
   // Transposing reads of the mixing: lane -> layer row and 8-byte half piece.  Layers past L repeat the last one (their
   // probabilities are zero).
   const uint32_t f_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) u32x4 *)lds_f;
-  uint32_t f_off[2][2];  // by token and half of the lane group's eight layers; ^ 64 for the slice's second 32 features
+  uint32_t f_off[2][2];  // by token and half of the lane group's eight layers; ^ 64 for the second 32 features of 64
 #pragma unroll
   for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
     for (int hf = 0; hf < 2; ++hf) {
       const int r = (2 * wave + tt) * L + min(8 * kq + 4 * hf + (j16 >> 2), L - 1);
-      f_off[tt][hf] = f_lds + r * 128 + ((j16 & 3) ^ ((r >> 1) & 7)) * 16;
+      f_off[tt][hf] = f_lds + r * kRow * 16 + ((j16 & 3) ^ (kShort ? 0 : (r >> 1) & 7)) * 16;
     }
 
   // Mixed features of (token t, row hq): 64 bytes.  The mixing writes 16 rows of one token at a time, the product reads
@@ -825,8 +833,8 @@ __global__ __launch_bounds__(kMpThreads) void meta_project_wide_kernel(
       lds_m[mixed + m_write[tt][ct]] = mix_lo;
     }
   };
-  auto read_features = [&](int slice, uint32_t half) {
-    const uint32_t at = (uint32_t)(slice & 1) * (uint32_t)(kStage * 16), x = half * 64;
+  auto read_features = [&](int slot, uint32_t half) {
+    const uint32_t at = (uint32_t)slot * (uint32_t)(kStage * 16), x = half * 64;
     tr_fragments(at + (f_off[0][0] ^ x), at + (f_off[0][1] ^ x), at + (f_off[1][0] ^ x), at + (f_off[1][1] ^ x), a);
   };
 
@@ -847,6 +855,7 @@ __global__ __launch_bounds__(kMpThreads) void meta_project_wide_kernel(
   constexpr int kChunks = 2 * NT, kPairs = 8 * CT;
   // step kt: product of its 32 features, mixing of the 32 after them (the first half of a slice in odd steps); the last step
   // mixes what nobody reads
+  int slot = 1;  // of three: the one of step kt + 1
   auto step = [&](int kt, auto odd) {
     constexpr bool kOdd = decltype(odd)::value;
     bf16x8 hi[QT], lo[QT];
@@ -855,7 +864,8 @@ __global__ __launch_bounds__(kMpThreads) void meta_project_wide_kernel(
       hi[q] = __builtin_bit_cast(bf16x8, lds_m[m_read[q]]);
       lo[q] = __builtin_bit_cast(bf16x8, lds_m[mixed + m_read[q]]);
     }
-    read_features((kt + 1) >> 1, !kOdd);
+    if (kShort) read_features(slot, 0);
+    else read_features(((kt + 1) >> 1) & 1, !kOdd);
     asm volatile("s_barrier" ::: "memory");  // everybody has read: the mixed features may be replaced, and a slice's stage
 #pragma unroll
     for (int n = 0; n < kChunks; ++n) {
@@ -869,16 +879,23 @@ __global__ __launch_bounds__(kMpThreads) void meta_project_wide_kernel(
       for (int i = n * kPairs / kChunks; i < (n + 1) * kPairs / kChunks; ++i) split_one(i / 8, i % 8);
       __builtin_amdgcn_sched_barrier(0);
     }
-    if (!kOdd) issue_feats((kt >> 1) + 2);
-    // The mixed features are complete.  Before an odd step the next slice's features must have landed: newer are the two
-    // steps' weights and the features just requested.
-    if (kOdd) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * NT + FI) : "memory");
+    // The mixed features are complete, and the next slice's features have landed, where the next step begins it: newer are,
+    // with slices of 64, two steps' weights and the features just requested, with slices of 32 one step's weights and these.
+    if (kShort) {
+      issue_feats(kt + 3, slot ? slot - 1 : 2);  // where this step's were
+      slot = slot == 2 ? 0 : slot + 1;
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(NT + kLoads) : "memory");
+    } else if (kOdd) {
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    } else {
+      issue_feats((kt >> 1) + 2, (kt >> 1) & 1);
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * NT + kLoads) : "memory");
+    }
   };
 #pragma unroll 1
-  for (int kt = 0; kt < steps; kt += 2) {
+  for (int kt = 0; kt < steps; kt += kShort ? 1 : 2) {
     step(kt, std::false_type());
-    step(kt + 1, std::true_type());
+    if (!kShort) step(kt + 1, std::true_type());
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   // lane (j16, kq) holds columns 16 nt + 4 kq .. + 3 of token j16
@@ -1001,7 +1018,8 @@ hipError_t launch_project_wide(int32_t S, int32_t L, int32_t D, int32_t H, int32
   if (FI > mw_loads(L)) {
     if constexpr (FI > 6) return launch_project_wide<QT, NT, FI - 1>(S, L, D, H, Q, hg, parts, feats, packed, res, pre, res_out, part, s);
   }
-  const size_t lds = ((size_t)2 * mw_stage(FI) + 2 * (size_t)hg * Q * kMwTok * 4) * sizeof(u32x4);
+  constexpr bool kShort = mw_short(QT, NT, FI);
+  const size_t lds = ((size_t)(kShort ? 3 : 2) * mw_stage(FI, kShort) + 2 * (size_t)hg * Q * kMwTok * 4) * sizeof(u32x4);
   auto kern = meta_project_wide_kernel<QT, NT, FI>;
   hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
@@ -1033,7 +1051,7 @@ static ProjectPlan project_plan(int32_t S, int32_t L, int32_t H, int32_t Q) {
   if (g4 * groups(2) <= 256) return {4, 2, split_heads(H, 2), 0.65};
   ProjectPlan best = {4, 4, split_heads(H, 4), (double)(g4 * H) * kMpHeadDim * 128 / 9.2e6};
   if (best.slice_us < 1.0) best.slice_us = 1.0;
-  const int wide = split_heads(H, std::min(8, (L <= 28 ? kMpHq : 16) / Q)), narrow = split_heads(H, 4);
+  const int wide = split_heads(H, std::min(8, kMpHq / Q)), narrow = split_heads(H, 4);
   const double narrow_us = 3.0 * (double)((g16 * groups(narrow) + 255) / 256);
   const double wide_us = 5.0 * (double)((g16 * groups(wide) + 255) / 256);
   if (narrow_us < best.slice_us) best = {16, 4, narrow, narrow_us};

@@ -109,7 +109,8 @@ def test_values_projected_after_the_mixing(S, n_tok, L, D, H, Q, layers):
     (2060, 28, 1024, 8, 3, [0, 5, 27]),   # 16 tokens: 24 hq rows, all of LDS; 28 layers are the most of 7 loads a slice
     (2040, 24, 1792, 14, 3, [1, 2, 23]),  # 21 rows; 6 loads
     (2203, 25, 1280, 10, 3, None),        # 15 rows in two tiles of 16
-    (2061, 29, 1024, 8, 3, None),         # 12 rows of 4 heads; 8 loads
+    (2061, 29, 1024, 8, 3, None),         # three slices of 32 features, 24 rows
+    (2040, 32, 1792, 14, 3, [31, 0, 7]),  # ... 21 rows, all layers
     (2047, 32, 1024, 8, 2, [31, 0]),      # 16 rows
     (700, 30, 1024, 8, 4, None),          # two wavefronts a head, four queries
     (690, 7, 256, 2, 1, [6]),             # one row a head, eight steps

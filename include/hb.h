@@ -203,9 +203,11 @@ int32_t hb_out_project(int32_t T, int32_t K, int32_t N, const void *x, const voi
  *   up to 16 (K >= 512)   the weights are streamed in one kernel, K whole;
  *   17 to 128             tiles of few weight rows against all tokens at once, or (up to 32 tokens) the
  *                         stream, whichever is expected to be faster;
- *   more, and what has no such tiles: tiles of 256 weight rows.
- * Given a workspace, the last two may cut K into parts where that is expected to be faster (tiles of few
- * rows of the gated projection never): the parts' fp32 partial results go to the workspace, and a second
+ *   more than 128         tiles of 128 or 224 weight rows whose K steps two groups of wavefronts share, where they
+ *                         fill at most one round of CUs and are expected to be faster;
+ *   else, and what has no such tiles: tiles of 256 weight rows.
+ * Given a workspace, the last three may cut K into parts where that is expected to be faster (of the gated
+ * projection only the tiles of 256 rows): the parts' fp32 partial results go to the workspace, and a second
  * kernel finishes (sum in fixed order, bias, rotary embedding, residual).  Results are deterministic; they
  * differ from the calls above in fp32 summation order only.
  *   workspace   device, hb_proj_workspace_bytes(T, K, N) bytes (N = (Hq + 2 Hkv) * 128 for the

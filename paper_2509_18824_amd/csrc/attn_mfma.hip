@@ -310,7 +310,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mfma_kernel(
     const int32_t *__restrict__ block_table, const int32_t *__restrict__ prefix_len,
     const int32_t *__restrict__ node_offset, const int32_t *__restrict__ parent, bf16_t *__restrict__ out,
     float *__restrict__ lse, float *__restrict__ part_o, float *__restrict__ part_ml, ClearArgs clear) {
-  clear_words(clear, (int)(blockIdx.x * 64 * NW + threadIdx.x), (int)(gridDim.x * 64 * NW));
+  clear_words(clear, blockIdx.x, gridDim.x, threadIdx.x, 64 * NW);
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   // [NS stages][K tile 16 KiB | V tile 16 KiB] [64 ancestor masks]
   constexpr int kStageBytes = K_PIECES * 16 + V_BYTES;

@@ -145,7 +145,7 @@ __global__ __launch_bounds__(kThreads, E == 4 || (E == 1 && sizeof(T) == 2) ? 4 
     const int32_t *__restrict__ block_table, const int32_t *__restrict__ prefix_len,
     const int32_t *__restrict__ node_offset, const int32_t *__restrict__ parent, T *__restrict__ out,
     float *__restrict__ lse, float *__restrict__ part_o, float *__restrict__ part_ml, ClearArgs clear) {
-  if (blockIdx.y == 0) clear_words(clear, (int)(blockIdx.x * kThreads + threadIdx.x), (int)(gridDim.x * kThreads));
+  if (blockIdx.y == 0) clear_words(clear, blockIdx.x, gridDim.x, threadIdx.x, kThreads);
   __shared__ float q_lds[64 * E];
   __shared__ float acc_lds[kWaves][64 * E];
   __shared__ float ml_lds[kWaves][2];

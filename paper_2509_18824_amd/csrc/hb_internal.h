@@ -63,13 +63,14 @@ struct AttnPlan {
 };
 int32_t make_attn_plan(const hb_attn_desc *d, AttnPlan *plan);  // validates shape fields
 
-// 64-bit words that a kernel sets to zero on the way (0 words: none), for the launch after it
+// 64-bit words that a kernel sets to zero on the way (0 words: none), for the launch after it.  Every thread calls it,
+// with its place in the grid; a grid may have up to 2^32 - 1 threads in a dimension, so they are counted in 64 bits.
 struct ClearArgs {
   unsigned long long *at;
   int32_t words;
 };
-__device__ inline void clear_words(const ClearArgs &c, int first, int threads) {
-  for (int i = first; i < c.words; i += threads) c.at[i] = 0ull;
+__host__ __device__ inline void clear_words(const ClearArgs &c, uint32_t group, uint32_t groups, uint32_t thread, uint32_t threads) {
+  for (int64_t i = (int64_t)group * threads + thread; i < c.words; i += (int64_t)groups * threads) c.at[i] = 0ull;
 }
 
 // ---- kernel launchers (each enqueues on `s`, returns a hipError_t from the launch) -------

@@ -378,7 +378,7 @@ int32_t hb_kv_compact_layers(const hb_attn_desc *desc, int32_t n_layers, const v
 
 /*
  * hb_tree_verify_attn that also sets the clear_words 64-bit words at `clear` (device, 8-byte aligned) to zero, in the
- * same launch: the keys of the hb_lmhead_accept that follows it on the stream.  clear must not overlap any other
+ * same launch: the keys of the hb_lmhead_accept_cleared that follows it on the stream.  clear must not overlap any other
  * argument.  Errors as there.
  */
 int32_t hb_tree_verify_attn_clearing(const hb_attn_desc *desc, const void *q, const void *k_tree,
@@ -391,10 +391,12 @@ int32_t hb_tree_verify_attn_clearing(const hb_attn_desc *desc, const void *q, co
 /*
  * A verification step from the target's hidden states on: hb_lmhead_argmax (without out_max), hb_tree_accept (without
  * prev_target) and the append of the accepted nodes to n_layers layers (hb_kv_compact with tables == 0 and one layer,
- * hb_kv_compact_layers with tables != 0; 0 layers: no append), with their results, in two launches.
- *   keys   device, 8 M bytes, 8-byte aligned: ZERO when the call's kernels begin (hb_tree_verify_attn_clearing sees to
- *          it), overwritten
+ * hb_kv_compact_layers with tables != 0; 0 layers: no append), with their results, in three launches.
+ *   keys   device, 8 M bytes, 8-byte aligned: scratch, overwritten
  * desc: as in hb_kv_compact, and dtype and max_nodes_per_tree for the other two; hidden [M, K] holds the nodes' rows.
+ * hb_lmhead_accept_cleared: the same in two launches, for keys that are ZERO when the call's kernels begin
+ * (hb_tree_verify_attn_clearing in front of it sees to that).  Keys that are not, those of a call before for instance,
+ * give wrong ids: the call cannot tell.
  * Errors: INVALID_ARG, UNSUPPORTED, WORKSPACE, DEVICE.
  */
 int32_t hb_lmhead_accept(const hb_attn_desc *desc, int32_t M, int32_t K, int32_t V, const void *hidden, const void *weight,
@@ -403,6 +405,12 @@ int32_t hb_lmhead_accept(const hb_attn_desc *desc, int32_t M, int32_t K, int32_t
                          int32_t *bonus_id, void *keys, size_t keys_bytes, int32_t n_layers, int32_t tables,
                          const void *k_tree, const void *v_tree, void *k_pool, void *v_pool, const int32_t *block_table,
                          const int32_t *prefix_len, int32_t *out_slots, int32_t *new_len, void *stream);
+int32_t hb_lmhead_accept_cleared(const hb_attn_desc *desc, int32_t M, int32_t K, int32_t V, const void *hidden, const void *weight,
+                                 const int32_t *draft_ids, const int32_t *node_offset, const int32_t *parent, int32_t max_path,
+                                 int32_t *target_ids, int32_t *accept_len, int32_t *accept_path, int32_t *out_tokens,
+                                 int32_t *bonus_id, void *keys, size_t keys_bytes, int32_t n_layers, int32_t tables,
+                                 const void *k_tree, const void *v_tree, void *k_pool, void *v_pool, const int32_t *block_table,
+                                 const int32_t *prefix_len, int32_t *out_slots, int32_t *new_len, void *stream);
 
 /*
  * Construction of the draft tree from the draft model's outputs: the step before the

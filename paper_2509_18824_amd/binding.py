@@ -5,6 +5,7 @@ There is no fallback: if libhb.so is missing or a call fails, an exception is ra
 from __future__ import annotations
 
 import ctypes as C
+import functools
 import os
 from typing import Optional
 
@@ -124,8 +125,9 @@ def _load():
     lib.hb_out_project_norm_ws.argtypes = [i32, i32, i32, p, p, p, p, p, C.c_float, p, p, sz, p]
     lib.hb_tree_verify_attn_clearing.restype = i32
     lib.hb_tree_verify_attn_clearing.argtypes = lib.hb_tree_verify_attn.argtypes[:-1] + [p, i32, p]
-    lib.hb_lmhead_accept.restype = i32
-    lib.hb_lmhead_accept.argtypes = [C.POINTER(AttnDesc)] + [i32] * 3 + [p] * 5 + [i32] + [p] * 6 + [sz, i32, i32] + [p] * 9
+    for call in (lib.hb_lmhead_accept, lib.hb_lmhead_accept_cleared):
+        call.restype = i32
+        call.argtypes = [C.POINTER(AttnDesc)] + [i32] * 3 + [p] * 5 + [i32] + [p] * 6 + [sz, i32, i32] + [p] * 9
     return lib
 
 
@@ -470,7 +472,8 @@ def hb_tree_verify_attn_clearing(desc: AttnDesc, q, k_tree, v_tree, k_pool, v_po
 
 def hb_lmhead_accept(desc: AttnDesc, hidden, weight, draft_ids, node_offset, parent, max_path: int, target_ids,
                      accept_len, accept_path, out_tokens, bonus_id, keys, n_layers: int = 0, kv=(None,) * 4,
-                     block_table=None, prefix_len=None, out_slots=None, new_len=None, stream=None) -> None:
+                     block_table=None, prefix_len=None, out_slots=None, new_len=None, stream=None, *,
+                     _call=lib.hb_lmhead_accept) -> None:
     """``kv``: k_tree, v_tree, k_pool and v_pool of one layer, or int64 tables of every layer's data pointers."""
     M, K = hidden.shape
     V = weight.shape[0]
@@ -479,8 +482,11 @@ def hb_lmhead_accept(desc: AttnDesc, hidden, weight, draft_ids, node_offset, par
     tables = n_layers > 0 and kv[0].dtype == torch.int64
     if tables and any(t.dtype != torch.int64 or t.numel() < n_layers for t in kv):
         raise ValueError("pointer tables must be int64 tensors with one entry per layer")
-    _check(lib.hb_lmhead_accept(C.byref(desc), M, K, V, _ptr(hidden), _ptr(weight), _ptr(draft_ids), _ptr(node_offset),
-                                _ptr(parent), max_path, _ptr(target_ids), _ptr(accept_len), _ptr(accept_path),
-                                _ptr(out_tokens), _ptr(bonus_id), _ptr(keys), keys.numel() * keys.element_size(),
-                                n_layers, int(tables), *map(_ptr, kv), _ptr(block_table), _ptr(prefix_len),
-                                _ptr(out_slots), _ptr(new_len), _stream(stream)))
+    _check(_call(C.byref(desc), M, K, V, _ptr(hidden), _ptr(weight), _ptr(draft_ids), _ptr(node_offset), _ptr(parent),
+                 max_path, _ptr(target_ids), _ptr(accept_len), _ptr(accept_path), _ptr(out_tokens), _ptr(bonus_id),
+                 _ptr(keys), keys.numel() * keys.element_size(), n_layers, int(tables), *map(_ptr, kv), _ptr(block_table),
+                 _ptr(prefix_len), _ptr(out_slots), _ptr(new_len), _stream(stream)))
+
+
+# for keys that hb_tree_verify_attn_clearing has set to zero
+hb_lmhead_accept_cleared = functools.partial(hb_lmhead_accept, _call=lib.hb_lmhead_accept_cleared)

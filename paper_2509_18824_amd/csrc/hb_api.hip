@@ -719,12 +719,12 @@ int32_t hb_kv_compact_layers(const hb_attn_desc *desc, int32_t n_layers, const v
   return HB_OK;
 }
 
-int32_t hb_lmhead_accept(const hb_attn_desc *desc, int32_t M, int32_t K, int32_t V, const void *hidden, const void *weight,
-                         const int32_t *draft_ids, const int32_t *node_offset, const int32_t *parent, int32_t max_path,
-                         int32_t *target_ids, int32_t *accept_len, int32_t *accept_path, int32_t *out_tokens,
-                         int32_t *bonus_id, void *keys, size_t keys_bytes, int32_t n_layers, int32_t tables,
-                         const void *k_tree, const void *v_tree, void *k_pool, void *v_pool, const int32_t *block_table,
-                         const int32_t *prefix_len, int32_t *out_slots, int32_t *new_len, void *stream) {
+static int32_t lmhead_accept(bool clear, const hb_attn_desc *desc, int32_t M, int32_t K, int32_t V, const void *hidden, const void *weight,
+                             const int32_t *draft_ids, const int32_t *node_offset, const int32_t *parent, int32_t max_path,
+                             int32_t *target_ids, int32_t *accept_len, int32_t *accept_path, int32_t *out_tokens,
+                             int32_t *bonus_id, void *keys, size_t keys_bytes, int32_t n_layers, int32_t tables,
+                             const void *k_tree, const void *v_tree, void *k_pool, void *v_pool, const int32_t *block_table,
+                             const int32_t *prefix_len, int32_t *out_slots, int32_t *new_len, void *stream) {
   int32_t rc = check_shape(desc);
   if (rc) return rc;
   if (max_path <= 0 || n_layers < 0) return fail(HB_ERR_INVALID_ARG, "need max_path > 0 and n_layers >= 0");
@@ -745,12 +745,35 @@ int32_t hb_lmhead_accept(const hb_attn_desc *desc, int32_t M, int32_t K, int32_t
   }
   if (desc->batch == 0 && M == 0) return HB_OK;
   hipStream_t s = (hipStream_t)stream;
+  if (M > 0 && clear) HB_HIP_TRY(launch_lmhead_init((unsigned long long *)keys, M, s));
   if (M > 0) HB_HIP_TRY(launch_lmhead(desc->dtype, M, K, V, hidden, weight, (unsigned long long *)keys, s));
   const TailArgs t = {(const unsigned long long *)keys, M, V, max_path, desc->batch ? n_layers : 0, 0, tables != 0,
                       node_offset, parent, draft_ids, block_table, prefix_len, k_tree, v_tree, k_pool, v_pool,
                       target_ids, accept_len, accept_path, out_tokens, bonus_id, out_slots, new_len};
   HB_HIP_TRY(launch_verify_tail(*desc, t, s));
   return HB_OK;
+}
+
+int32_t hb_lmhead_accept(const hb_attn_desc *desc, int32_t M, int32_t K, int32_t V, const void *hidden, const void *weight,
+                         const int32_t *draft_ids, const int32_t *node_offset, const int32_t *parent, int32_t max_path,
+                         int32_t *target_ids, int32_t *accept_len, int32_t *accept_path, int32_t *out_tokens,
+                         int32_t *bonus_id, void *keys, size_t keys_bytes, int32_t n_layers, int32_t tables,
+                         const void *k_tree, const void *v_tree, void *k_pool, void *v_pool, const int32_t *block_table,
+                         const int32_t *prefix_len, int32_t *out_slots, int32_t *new_len, void *stream) {
+  return lmhead_accept(true, desc, M, K, V, hidden, weight, draft_ids, node_offset, parent, max_path, target_ids, accept_len, accept_path, out_tokens,
+                       bonus_id, keys, keys_bytes, n_layers, tables, k_tree, v_tree, k_pool, v_pool, block_table, prefix_len, out_slots,
+                       new_len, stream);
+}
+
+int32_t hb_lmhead_accept_cleared(const hb_attn_desc *desc, int32_t M, int32_t K, int32_t V, const void *hidden, const void *weight,
+                                 const int32_t *draft_ids, const int32_t *node_offset, const int32_t *parent, int32_t max_path,
+                                 int32_t *target_ids, int32_t *accept_len, int32_t *accept_path, int32_t *out_tokens,
+                                 int32_t *bonus_id, void *keys, size_t keys_bytes, int32_t n_layers, int32_t tables,
+                                 const void *k_tree, const void *v_tree, void *k_pool, void *v_pool, const int32_t *block_table,
+                                 const int32_t *prefix_len, int32_t *out_slots, int32_t *new_len, void *stream) {
+  return lmhead_accept(false, desc, M, K, V, hidden, weight, draft_ids, node_offset, parent, max_path, target_ids, accept_len, accept_path, out_tokens,
+                       bonus_id, keys, keys_bytes, n_layers, tables, k_tree, v_tree, k_pool, v_pool, block_table, prefix_len, out_slots,
+                       new_len, stream);
 }
 
 }  // extern "C"

@@ -249,10 +249,10 @@ class VerifyStep:
         hb.hb_tree_verify_attn_clearing(desc, dev.q, dev.k_tree, dev.v_tree, dev.k_pool, dev.v_pool, dev.block_table,
                                         dev.prefix_len, dev.node_offset, dev.parent, self.out, None, self.ws_attn,
                                         self.ws_lm, hidden.shape[0])
-        hb.hb_lmhead_accept(desc, hidden, self.weight, self.draft_ids, dev.node_offset, dev.parent, self.max_path,
-                            self.target_ids, self.accept_len, self.accept_path, self.out_tokens, self.bonus, self.ws_lm,
-                            int(compact), (dev.k_tree, dev.v_tree, dev.k_pool, dev.v_pool), dev.block_table,
-                            dev.prefix_len, self.out_slots, self.new_len)
+        hb.hb_lmhead_accept_cleared(desc, hidden, self.weight, self.draft_ids, dev.node_offset, dev.parent, self.max_path,
+                                    self.target_ids, self.accept_len, self.accept_path, self.out_tokens, self.bonus, self.ws_lm,
+                                    int(compact), (dev.k_tree, dev.v_tree, dev.k_pool, dev.v_pool), dev.block_table,
+                                    dev.prefix_len, self.out_slots, self.new_len)
 
 
 class VerifyLayerStack:
@@ -356,10 +356,8 @@ class VerifyLayerStack:
             x = self.normed
         self.final_hidden = x
         mark("lmhead_accept")
-        if not self.n_layers:
-            self.ws_lm.zero_()
-        hb.hb_lmhead_accept(desc, x, self.lm_weight, self.draft_ids, dev.node_offset, dev.parent, self.max_path,
-                            self.target_ids, self.accept_len, self.accept_path, self.out_tokens, self.bonus, self.ws_lm,
-                            self.n_layers if compact else 0, self.ptr_tables, dev.block_table, dev.prefix_len,
-                            self.out_slots, self.new_len)
+        accept = hb.hb_lmhead_accept_cleared if self.n_layers else hb.hb_lmhead_accept  # no layer, no attention to clear the keys
+        accept(desc, x, self.lm_weight, self.draft_ids, dev.node_offset, dev.parent, self.max_path, self.target_ids,
+               self.accept_len, self.accept_path, self.out_tokens, self.bonus, self.ws_lm, self.n_layers if compact else 0,
+               self.ptr_tables, dev.block_table, dev.prefix_len, self.out_slots, self.new_len)
         mark("end")

@@ -67,3 +67,30 @@ def test_lm_head_acceptance_and_append(kind, dtype, layers, short):
             assert np.array_equal(bits(d.k_pool), ref_k) and np.array_equal(bits(d.v_pool), ref_v)
     else:
         assert (slots == -7).all() and (new_len == -7).all()
+
+
+@pytest.mark.parametrize("dtype,nodes", [("f32", 4), ("bf16", 8), ("bf16", 40)])
+def test_a_second_call_on_the_same_keys(dtype, nodes):
+    """hb_lmhead_accept needs nothing of its keys: the second call's rows name other tokens than the first's, with smaller
+    logits, and so do both calls on keys that were never set.  Each way of the LM head by the number of rows."""
+    import paper_2509_18824_amd as hb
+    import paper_2509_18824_amd.step as S
+    B, K, V = 2, 256, 1000
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    desc = S.make_desc(dtype, B, 2, 1, 128, 16, 4, 8, B * nodes, nodes, 1.0)
+    off = torch.tensor([0, nodes, 2 * nodes], dtype=torch.int32, device="cuda")
+    parent = torch.from_numpy(np.concatenate([W.chain_tree(nodes)] * B).astype(np.int32)).cuda()
+    weight = torch.eye(V, K, dtype=td, device="cuda")
+    i32 = lambda *shape: torch.full(shape, -7, dtype=torch.int32, device="cuda")
+    keys = torch.full((8 * B * nodes,), 255, dtype=torch.uint8, device="cuda")
+    rng = np.random.default_rng(nodes)
+    for size in (4.0, 1.0):
+        target = rng.integers(0, K, size=B * nodes)
+        draft = np.roll(target, 1)  # every node names what the target chooses after its parent
+        hidden = (size * weight[torch.from_numpy(target).cuda()]).contiguous()
+        ids, alen, path, toks, bonus = i32(B * nodes), i32(B), i32(B, nodes), i32(B, nodes), i32(B)
+        hb.hb_lmhead_accept(desc, hidden, weight, torch.from_numpy(draft.astype(np.int32)).cuda(), off, parent, nodes, ids, alen,
+                            path, toks, bonus, keys)
+        torch.cuda.synchronize()
+        assert np.array_equal(ids.cpu().numpy(), target)
+        assert (alen == nodes).all() and np.array_equal(toks.cpu().numpy().reshape(-1), target)

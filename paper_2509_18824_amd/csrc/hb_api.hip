@@ -728,8 +728,7 @@ static int32_t lmhead_accept(bool clear, const hb_attn_desc *desc, int32_t M, in
   int32_t rc = check_shape(desc);
   if (rc) return rc;
   if (max_path <= 0 || n_layers < 0) return fail(HB_ERR_INVALID_ARG, "need max_path > 0 and n_layers >= 0");
-  if (n_layers > 65535 || (int64_t)desc->batch * max_path > INT32_MAX)
-    return fail(HB_ERR_UNSUPPORTED, "at most 65535 layers and 2^31 - 1 path slots per call");
+  if (n_layers > 65535) return fail(HB_ERR_UNSUPPORTED, "n_layers %d: at most 65535 layers per call", n_layers);
   if (!tables && n_layers > 1) return fail(HB_ERR_INVALID_ARG, "several layers need tables of their tensors");
   if ((rc = check_lmhead_args(desc->dtype, M, K, V, hidden, weight, target_ids))) return rc;
   if (M > 0 && (!keys || keys_bytes < (size_t)M * 8))
@@ -747,7 +746,7 @@ static int32_t lmhead_accept(bool clear, const hb_attn_desc *desc, int32_t M, in
   hipStream_t s = (hipStream_t)stream;
   if (M > 0 && clear) HB_HIP_TRY(launch_lmhead_init((unsigned long long *)keys, M, s));
   if (M > 0) HB_HIP_TRY(launch_lmhead(desc->dtype, M, K, V, hidden, weight, (unsigned long long *)keys, s));
-  const TailArgs t = {(const unsigned long long *)keys, M, V, max_path, desc->batch ? n_layers : 0, 0, tables != 0,
+  const TailArgs t = {(const unsigned long long *)keys, M, V, max_path, desc->batch ? n_layers : 0, 0, 0, tables != 0,
                       node_offset, parent, draft_ids, block_table, prefix_len, k_tree, v_tree, k_pool, v_pool,
                       target_ids, accept_len, accept_path, out_tokens, bonus_id, out_slots, new_len};
   HB_HIP_TRY(launch_verify_tail(*desc, t, s));

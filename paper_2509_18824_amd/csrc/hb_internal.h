@@ -207,7 +207,7 @@ hipError_t launch_kv_compact_layers(const hb_attn_desc &d, int32_t n_layers, con
 // given themselves, or tables of their device addresses, one per layer
 struct TailArgs {
   const unsigned long long *keys;
-  int32_t M, V, max_path, layers, row_bytes;
+  int32_t M, V, max_path, layers, row_bytes, path_slots;  // the last two are the launcher's
   bool tables;
   const int32_t *node_offset, *parent, *draft_ids, *block_table, *prefix_len;
   const void *k_tree, *v_tree;

@@ -94,3 +94,56 @@ def test_a_second_call_on_the_same_keys(dtype, nodes):
         torch.cuda.synchronize()
         assert np.array_equal(ids.cpu().numpy(), target)
         assert (alen == nodes).all() and np.array_equal(toks.cpu().numpy().reshape(-1), target)
+
+
+@pytest.mark.parametrize("B,max_path,layers", [
+    (3, 1 << 23, 1),         # more than 2^24 path slots, most of which no tree of 64 nodes reaches
+    (3, 1 << 23, 0),
+    (70000, 64, 1),          # more workgroups than the grid has: each takes several
+    (70000, 200, 0)])
+def test_more_path_slots_than_a_grid_has_threads(B, max_path, layers):
+    """Chains of two nodes that share pages: the root is always accepted, its child by every second sequence."""
+    import paper_2509_18824_amd as hb
+    import paper_2509_18824_amd.step as S
+    K, V, page, T = 8, 16, 16, 2 * B
+    rng = np.random.default_rng(B)
+    target = rng.integers(0, K, size=T)
+    draft = np.where(np.arange(T) % 4 == 1, np.roll(target, 1), (np.roll(target, 1) + 1) % V)
+    t32 = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)).cuda()
+    # sequence b: positions 3 (b % 5) .. + 1 of page b / 5, nobody else's
+    pages = B // 5 + 1
+    desc = S.make_desc("f32", B, 1, 1, 8, page, 1, pages, T, 2, 1.0)
+    off, parent = t32(2 * np.arange(B + 1)), t32(np.tile([-1, 0], B))
+    block_table, prefix = t32(np.arange(B)[:, None] // 5), t32(3 * (np.arange(B) % 5))
+    weight = torch.eye(V, K, device="cuda")
+    hidden = weight[torch.from_numpy(target).cuda()].contiguous()
+    i32 = lambda *shape: torch.full(shape, -7, dtype=torch.int32, device="cuda")
+    ids, alen, path, toks, bonus, slots, new_len = (i32(T), i32(B), i32(B, max_path), i32(B, max_path), i32(B),
+                                                    i32(B, max_path), i32(B))
+    k_tree, v_tree = torch.randn(T, 1, 8, device="cuda"), torch.randn(T, 1, 8, device="cuda")
+    k_pool, v_pool = torch.zeros(pages, 1, page, 8, device="cuda"), torch.zeros(pages, 1, page, 8, device="cuda")
+    keys = torch.empty(8 * T, dtype=torch.uint8, device="cuda")
+    hb.hb_lmhead_accept(desc, hidden, weight, t32(draft), off, parent, max_path, ids, alen, path, toks, bonus, keys, layers,
+                        (k_tree, v_tree, k_pool, v_pool), block_table, prefix, slots, new_len)
+    torch.cuda.synchronize()
+    assert np.array_equal(ids.cpu().numpy(), target)
+    want = 1 + (np.arange(B) % 2 == 0)
+    assert np.array_equal(alen.cpu().numpy(), want)
+    took = torch.arange(max_path, device="cuda") < alen[:, None]
+    assert torch.equal(path, torch.where(took, torch.arange(max_path, dtype=torch.int32, device="cuda"), -1))
+    assert torch.equal(toks[:, :2].cpu(), torch.from_numpy(np.where(want[:, None] == 2, target.reshape(B, 2),
+                                                                    np.stack([target[::2], -np.ones(B)], 1))).int())
+    assert (toks[:, 2:] == -1).all()
+    assert np.array_equal(bonus.cpu().numpy(), np.where(want == 2, target[1::2], target[::2]))
+    if not layers:
+        assert (slots == -7).all() and (new_len == -7).all()
+        return
+    assert torch.equal(new_len, prefix + alen)
+    at = block_table * page + prefix[:, None] + torch.arange(max_path, dtype=torch.int32, device="cuda")
+    assert torch.equal(slots, torch.where(took, at, -1))
+    two = alen == 2
+    for tree, pool in ((k_tree, k_pool), (v_tree, v_pool)):
+        ref = torch.zeros_like(pool).view(-1, 8)
+        ref[at[:, 0].long()] = tree[::2, 0]
+        ref[at[two, 1].long()] = tree[1::2, 0][two]
+        assert torch.equal(pool.view(-1, 8), ref)

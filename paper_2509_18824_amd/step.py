@@ -251,7 +251,7 @@ class VerifyStep:
                                         self.ws_lm, hidden.shape[0])
         hb.hb_lmhead_accept_cleared(desc, hidden, self.weight, self.draft_ids, dev.node_offset, dev.parent, self.max_path,
                                     self.target_ids, self.accept_len, self.accept_path, self.out_tokens, self.bonus, self.ws_lm,
-                                    int(compact), (dev.k_tree, dev.v_tree, dev.k_pool, dev.v_pool), dev.block_table,
+                                    int(bool(compact)), (dev.k_tree, dev.v_tree, dev.k_pool, dev.v_pool), dev.block_table,
                                     dev.prefix_len, self.out_slots, self.new_len)
 
 

@@ -308,10 +308,23 @@ class VerifyLayerStack:
                            table([p[1] for p in pools]))
 
     def run(self, compact=True, on_call=None):
-        """``on_call(name)`` (optional) is invoked before every library call, e.g. to record events."""
+        """``on_call(name)`` (optional) is invoked before every library call, e.g. to record events.  What a plain run does
+        in one call (a projection and the normalisation of its result; LM head, acceptance and append) is then made by
+        the calls it consists of, so that each has its name; the sum of a normalisation may round differently."""
         dev, desc = self.dev, self.desc
         T = self.q.shape[0]
         mark = on_call or (lambda name: None)
+
+        def project(x, w, residual, out, norm):
+            """Into the residual stream; norm: the weight that normalises it for the call that follows, or None."""
+            if norm is None or on_call:
+                hb.hb_out_project_ws(x, w, residual, out, self.ws_proj)
+                if norm is not None:
+                    mark("rmsnorm")
+                    hb.hb_rmsnorm(out, norm, self.mlp["eps"], self.normed)
+            else:
+                hb.hb_out_project_norm_ws(x, w, residual, out, norm, self.mlp["eps"], self.normed, self.ws_proj)
+
         mark("positions")
         hb.hb_tree_positions(desc.batch, desc.max_nodes_per_tree, dev.node_offset, dev.parent, dev.prefix_len,
                              self.positions)
@@ -335,19 +348,12 @@ class VerifyLayerStack:
                                             dev.prefix_len, dev.node_offset, dev.parent, self.attn_out, None, self.ws_attn,
                                             self.ws_lm, T if l == self.n_layers - 1 else 0)
             mark("out_project")
-            attn = self.attn_out.view(T, -1)
-            if mlp is None:
-                hb.hb_out_project_ws(attn, self.w_o[l], x, y, self.ws_proj)
-            else:  # each projection into the residual stream also normalises it for the one that follows
-                hb.hb_out_project_norm_ws(attn, self.w_o[l], x, y, mlp["norm2"][l], mlp["eps"], self.normed, self.ws_proj)
+            project(self.attn_out.view(T, -1), self.w_o[l], x, y, None if mlp is None else mlp["norm2"][l])
+            if mlp is not None:
                 mark("swiglu_project")
                 hb.hb_swiglu_project(self.normed, mlp["w_gate_up"][l], self.act, self.ws_proj)
                 mark("down_project")
-                norm = mlp["norm1"][l + 1] if l + 1 < self.n_layers else mlp.get("norm_f")
-                if norm is None:
-                    hb.hb_out_project_ws(self.act, mlp["w_down"][l], y, nxt, self.ws_proj)
-                else:
-                    hb.hb_out_project_norm_ws(self.act, mlp["w_down"][l], y, nxt, norm, mlp["eps"], self.normed, self.ws_proj)
+                project(self.act, mlp["w_down"][l], y, nxt, mlp["norm1"][l + 1] if l + 1 < self.n_layers else mlp.get("norm_f"))
             x = nxt
         if mlp is not None and mlp.get("norm_f") is not None:
             if not self.n_layers:
@@ -355,9 +361,21 @@ class VerifyLayerStack:
                 hb.hb_rmsnorm(x, mlp["norm_f"], mlp["eps"], self.normed)
             x = self.normed
         self.final_hidden = x
-        mark("lmhead_accept")
+        if on_call:
+            mark("lmhead_argmax")
+            hb.hb_lmhead_argmax(x, self.lm_weight, self.target_ids, None, self.ws_lm)
+            mark("tree_accept")
+            hb.hb_tree_accept(desc.batch, desc.max_nodes_per_tree, dev.node_offset, dev.parent, self.draft_ids,
+                              self.target_ids, self.max_path, self.accept_len, self.accept_path, self.out_tokens,
+                              self.bonus)
+            if compact:
+                mark("kv_compact")
+                hb.hb_kv_compact_layers(desc, self.n_layers, *self.ptr_tables, dev.block_table, dev.prefix_len,
+                                        dev.node_offset, self.accept_len, self.accept_path, self.max_path,
+                                        self.out_slots, self.new_len)
+            mark("end")
+            return
         accept = hb.hb_lmhead_accept_cleared if self.n_layers else hb.hb_lmhead_accept  # no layer, no attention to clear the keys
         accept(desc, x, self.lm_weight, self.draft_ids, dev.node_offset, dev.parent, self.max_path, self.target_ids,
                self.accept_len, self.accept_path, self.out_tokens, self.bonus, self.ws_lm, self.n_layers if compact else 0,
                self.ptr_tables, dev.block_table, dev.prefix_len, self.out_slots, self.new_len)
-        mark("end")

@@ -567,8 +567,8 @@ hipError_t launch_few(StreamKind kind, const FewPlan &p, int M, int K, int V, co
 // tokens, 2048 to 18944 x 2048 to 37888, weights too many to stay in the last-level cache; 6.6 % rms); a K step costs
 // by the share of the CUs at work, which meet at the L2s.  What is chosen is within 0.6 % of the faster one in the mean, 135
 // of the calls are taken and 17 % faster for it, 110 drawn ones 21 % (256-row tiles -> this, us: 960 x 3584 x 3584 44.6 -> 35.9, rotary 960 x 3584 x
-// 4608 53 -> 42, 1280 x 8192 x 4096 108 -> 81, gated 640 x 3584 x 8192 53 -> 43, 2048 x 10752 x 3584 145 -> 135); six are up
-// to 5 % slower, parts of K of 1 KB or 2 KB among 136 tokens (and 224 rows below K = 1024, hence not taken there).  More than a round never pays: then the taller tiles move fewer
+// 4608 53 -> 42, 1280 x 8192 x 4096 108 -> 81, gated 640 x 3584 x 8192 53 -> 43, 2048 x 10752 x 3584 145 -> 135); 224
+// rows below K = 1024 are slower, hence not taken there.  More than a round never pays: then the taller tiles move fewer
 // bytes from L2 to LDS.  Not kept: 96 x 192 (never the fastest by more than 1 %), 128 x 192, 128 x 256.
 double tiles_us(SplitPlan plan, int M, int K, int V) {
   static const double kB[5] = {0, -1.92, 3.25, 6.14, 8.91}, kS[5] = {0, 0.5815, 0.7597, 0.6764, 0.7521}, kF[5] = {0, 0.148, 0.103, 0.455, 0.652};
@@ -581,13 +581,33 @@ double tiles_us(SplitPlan plan, int M, int K, int V) {
   const long units = (long)v_tiles * ((M + 64 * mt - 1) / (64 * mt)), rounds = (units + 255) / 256;
   return 3.84 + (double)rounds * (kB[mt] + steps * kS[mt]) + steps * kF[mt] * (double)units / 256;
 }
+// Where the times above are wrong, and below their range (K from 512, rows from 200; us by the 256-row tiles -> by these).
+// K whole on a part of the CUs, where the others have it in parts, takes up to 1.4 times as long as they say: 347 x 2176 x
+// 4268 23.5 -> 27.6, rotary 384 x 1728 x 3584 20.2 -> 22.3, gated 242 x 2688 x 6016 25.8 -> 29.7; not so among up to 160
+// tokens or with few rows: gated 520 x 1152 x 640 15.9 -> 12.2, plain 1014 x 1152 x 292 15.6 -> 13.8.  Many tokens by few
+// rows and short K: 3840 x 1408 x 928 19.1 -> 22.3, 4491 x 2560 x 644 27.6 -> 30.6, at 224 rows a tile 3068 x 1152 x 1696
+// 24.8 -> 26.4, but 2250 x 1920 x 2824 37.6 -> 36.6.  With these lines 23 of 2356 drawn calls, most of them on purpose near
+// the lines, are more than 2 % slower than by the 256-row tiles (977 x 8960 x 1024 in parts by 8 %); all are 1.115 times as fast.
+// The share of the 256-row tiles' time that a plan must be expected to stay below; 0: it is not taken.
+double pair_margin(int M, int K, int V, StreamKind kind, SplitPlan plan, int it, int ks, long tiles) {
+  const bool plain = kind == StreamKind::kPlain;
+  if (ks > 1) return 0.98;
+  if (plan.ks > 1 && tiles < 171) {
+    if (plain) return M > 512 && V <= 1200 ? 0.98 : 0.0;
+    return M > 160 && (int64_t)K * V > (kind == StreamKind::kGlu ? 4000000 : 3000000) ? 0.87 : 0.98;
+  }
+  if (it == 7 && K < 2048 && (M > 2560 || (K < 1344 && tiles < 250))) return 0.0;
+  if (it == 4 && plain && M > 1024 && V < 1024 && K < (M > 4096 ? 3072 : 2048)) return 0.0;
+  return 0.98;
+}
 PairPlan pair_plan(int M, int K, int V, StreamKind kind, SplitPlan plan) {
   static const struct { int it, jt; double b, s, f; } kTiles[] = {
       {4, 4, 5.17, 0.416, 0.116}, {4, 5, 5.97, 0.513, 0.088}, {7, 4, 6.63, 0.679, 0.076}};
   PairPlan best = {0, 0, 1};
   if (M <= kFewMost) return best;
   const int steps = K / BK, v_pad = (V + TV - 1) / TV * TV;
-  double best_us = 0.98 * tiles_us(plan, M, K, V);
+  const double other_us = tiles_us(plan, M, K, V);
+  double best_us = other_us;
   for (const auto &t : kTiles) {
     if (t.it % 2 && (kind != StreamKind::kPlain || K < 1024)) continue;
     const long tiles = (long)((V + 32 * t.it - 1) / (32 * t.it)) * ((M + 32 * t.jt - 1) / (32 * t.jt));
@@ -596,7 +616,7 @@ PairPlan pair_plan(int M, int K, int V, StreamKind kind, SplitPlan plan) {
       if (steps % ks || (ks > 1 && (steps / ks < 8 || (size_t)ks * v_pad * M * sizeof(float) > split_bytes(plan, M, V)))) continue;
       const double sums = ks > 1 ? 3.5 + 0.728 * 8.0 * ks * v_pad * M / 4e6 : 0.0;
       const double us = t.b + steps / ks * (t.s + t.f * (double)(tiles * ks) / 256) + sums;
-      if (us < best_us) {
+      if (us < best_us && us < pair_margin(M, K, V, kind, plan, t.it, ks, tiles) * other_us) {
         best_us = us;
         best = {t.it, t.jt, ks};
       }

@@ -262,6 +262,24 @@ def test_projections_whose_k_steps_two_groups_share(hb, kind, T, K, N, ws, kerne
     assert names[0] == kernel and len(names) == (2 if kernel.startswith("pair<3") else 1)
 
 
+# Both sides of the lines between these tiles and the ones of 256 rows, which are ahead of them where they stand here
+@pytest.mark.parametrize("kind,T,K,N,ws,kernel", [
+    ("plain", 256, 2048, 5656, True, "pair<3, 4, 4>"), ("plain", 336, 1408, 1784, True, "splitk"), ("plain", 1014, 1152, 292, True, "pair<0, 4, 4>"),
+    ("plain", 700, 2048, 3588, True, "pair<0, 4, 4>"),
+    ("plain", 3840, 1408, 928, False, "mfma"), ("plain", 4491, 2560, 644, True, "mfma"), ("plain", 1100, 2112, 900, False, "pair<0, 4, 4>"),
+    ("plain", 3068, 1152, 1696, False, "mfma"), ("plain", 1446, 1280, 3328, False, "mfma"), ("plain", 2250, 1920, 2824, False, "pair<0, 7, 4>"),
+    ("rope", 384, 1728, 28, True, "splitk"), ("rope", 150, 1664, 40, True, "pair<1, 4, 4>"),
+    ("gated", 242, 2688, 3008, True, "splitk"), ("gated", 520, 1152, 320, True, "pair<2, 4, 4>")])
+def test_the_lines_between_the_tiles_of_more_than_128_tokens(hb, kind, T, K, N, ws, kernel):
+    if kind == "plain":
+        names = _kernels(lambda: _out_case(hb, T, K, N, T % 2 == 0, ws))
+    elif kind == "rope":
+        names = _kernels(lambda: _qkv_case(hb, T, K, N - 2 * (N // 9), N // 9, T % 2 == 0, ws))
+    else:
+        names = _kernels(lambda: test_gated_silu_projection(hb, T, K, N, ws))
+    assert names[0].startswith(kernel) and len(names) == (2 if kernel in ("splitk", "pair<3, 4, 4>") else 1)
+
+
 @pytest.mark.parametrize("T,K,N,res,fused", [
     (128, 18944, 3584, True, True), (1, 3584, 3584, True, False), (100, 3584, 3584, False, True), (300, 3584, 3592, True, True),
     (960, 18944, 3584, True, True), (960, 3584, 3584, True, False), (40, 8192, 8192, True, True), (40, 8192, 8200, False, False),

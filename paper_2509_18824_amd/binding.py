@@ -5,7 +5,6 @@ There is no fallback: if libhb.so is missing or a call fails, an exception is ra
 from __future__ import annotations
 
 import ctypes as C
-import functools
 import os
 from typing import Optional
 
@@ -470,23 +469,26 @@ def hb_tree_verify_attn_clearing(desc: AttnDesc, q, k_tree, v_tree, k_pool, v_po
                                             rows, _stream(stream)))
 
 
-def hb_lmhead_accept(desc: AttnDesc, hidden, weight, draft_ids, node_offset, parent, max_path: int, target_ids,
-                     accept_len, accept_path, out_tokens, bonus_id, keys, n_layers: int = 0, kv=(None,) * 4,
-                     block_table=None, prefix_len=None, out_slots=None, new_len=None, stream=None, *,
-                     _call=lib.hb_lmhead_accept) -> None:
-    """``kv``: k_tree, v_tree, k_pool and v_pool of one layer, or int64 tables of every layer's data pointers."""
-    M, K = hidden.shape
-    V = weight.shape[0]
-    if weight.shape[1] != K or weight.dtype != hidden.dtype or _dtype_code(hidden) != desc.dtype:
-        raise ValueError("hidden [M, K] and weight [V, K] must agree in K and dtype, and with the descriptor")
-    tables = n_layers > 0 and kv[0].dtype == torch.int64
-    if tables and any(t.dtype != torch.int64 or t.numel() < n_layers for t in kv):
-        raise ValueError("pointer tables must be int64 tensors with one entry per layer")
-    _check(_call(C.byref(desc), M, K, V, _ptr(hidden), _ptr(weight), _ptr(draft_ids), _ptr(node_offset), _ptr(parent),
-                 max_path, _ptr(target_ids), _ptr(accept_len), _ptr(accept_path), _ptr(out_tokens), _ptr(bonus_id),
-                 _ptr(keys), keys.numel() * keys.element_size(), n_layers, int(tables), *map(_ptr, kv), _ptr(block_table),
-                 _ptr(prefix_len), _ptr(out_slots), _ptr(new_len), _stream(stream)))
+def _lmhead_accept(call):
+    def hb_lmhead_accept(desc: AttnDesc, hidden, weight, draft_ids, node_offset, parent, max_path: int, target_ids,
+                         accept_len, accept_path, out_tokens, bonus_id, keys, n_layers: int = 0, kv=(None,) * 4,
+                         block_table=None, prefix_len=None, out_slots=None, new_len=None, stream=None) -> None:
+        """``kv``: k_tree, v_tree, k_pool and v_pool of one layer, or int64 tables of every layer's data pointers."""
+        M, K = hidden.shape
+        V = weight.shape[0]
+        if weight.shape[1] != K or weight.dtype != hidden.dtype or _dtype_code(hidden) != desc.dtype:
+            raise ValueError("hidden [M, K] and weight [V, K] must agree in K and dtype, and with the descriptor")
+        tables = n_layers > 0 and kv[0].dtype == torch.int64
+        if tables and any(t.dtype != torch.int64 or t.numel() < n_layers for t in kv):
+            raise ValueError("pointer tables must be int64 tensors with one entry per layer")
+        _check(call(C.byref(desc), M, K, V, _ptr(hidden), _ptr(weight), _ptr(draft_ids), _ptr(node_offset), _ptr(parent),
+                    max_path, _ptr(target_ids), _ptr(accept_len), _ptr(accept_path), _ptr(out_tokens), _ptr(bonus_id),
+                    _ptr(keys), keys.numel() * keys.element_size(), n_layers, int(tables), *map(_ptr, kv), _ptr(block_table),
+                    _ptr(prefix_len), _ptr(out_slots), _ptr(new_len), _stream(stream)))
+
+    return hb_lmhead_accept
 
 
+hb_lmhead_accept = _lmhead_accept(lib.hb_lmhead_accept)
 # for keys that hb_tree_verify_attn_clearing has set to zero
-hb_lmhead_accept_cleared = functools.partial(hb_lmhead_accept, _call=lib.hb_lmhead_accept_cleared)
+hb_lmhead_accept_cleared = _lmhead_accept(lib.hb_lmhead_accept_cleared)

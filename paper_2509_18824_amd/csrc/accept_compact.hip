@@ -152,9 +152,11 @@ __global__ __launch_bounds__(256) void kv_compact_layers_kernel(
 // more to clear the keys, which the attention kernel now does) they took 1.5 us each of the GPU's time in a full
 // stream and the host's of two calls: step of one 60-node tree 214.9 -> 210.3 us, 16 chains of 8 nodes 239.8 -> 234.8,
 // four nodes of a unit-sized float32 model 31.1 -> 20.3.  A workgroup per (path slot that a tree's nodes can fill,
-// sequence, layer), in a loop where a grid does not hold them all; its first wavefront works the sequence's acceptance out
+// sequence, layer); its first wavefront works the sequence's acceptance out
 // by itself (a key, a parent and a drafted token per lane), which is cheaper than to wait for anybody.  The first workgroup
 // of a sequence writes the results; the ids are dealt to all workgroups.
+// MANY: more of them than the grid has workgroups (a kernel of its own: the loop costs the other one 0.4 to 0.8 us).
+template <bool MANY>
 __global__ __launch_bounds__(256) void verify_tail_kernel(hb_attn_desc d, TailArgs t) {
   __shared__ int s_len, s_node;
   const int tid = threadIdx.x, l = blockIdx.y;
@@ -163,9 +165,10 @@ __global__ __launch_bounds__(256) void verify_tail_kernel(hb_attn_desc d, TailAr
     const int id = argmax_key_id(t.keys[i], t.V);
     t.target_ids[i] = id;
   }
-  const long items = (long)d.batch * t.path_slots;
-  for (long item = blockIdx.x; item < items; item += gridDim.x) {
-    const int b = (int)(item / t.path_slots), j = (int)(item % t.path_slots);
+  unsigned item = blockIdx.x;
+  do {
+    const int b = (int)item / t.path_slots, j = (int)item % t.path_slots;
+    if (b >= d.batch) return;  // an empty batch, or done
     if (tid < 64) {
       const int n0 = t.node_offset[b];
       int n = t.node_offset[b + 1] - n0;
@@ -182,18 +185,20 @@ __global__ __launch_bounds__(256) void verify_tail_kernel(hb_attn_desc d, TailAr
       if (tid == 0) s_len = a.len;
       if (((a.path >> tid) & 1ull) && __popcll(a.path & ((1ull << tid) - 1ull)) == j) s_node = tid;
     }
-    if (!t.layers) continue;
-    __syncthreads();
-    const bool tables = t.tables;
-    compact_one(d, t.row_bytes, j, b, s_len, j < s_len ? s_node : 0, (const uint4 *)(tables ? ((const void *const *)t.k_tree)[l] : t.k_tree),
-                (const uint4 *)(tables ? ((const void *const *)t.v_tree)[l] : t.v_tree),
-                (uint4 *)(tables ? ((void *const *)t.k_pool)[l] : t.k_pool), (uint4 *)(tables ? ((void *const *)t.v_pool)[l] : t.v_pool),
-                t.block_table, t.prefix_len, t.node_offset, t.max_path, l == 0 ? t.out_slots : nullptr, l == 0 ? t.new_len : nullptr);
-    // slots that no path of a tree reaches
-    if (j == 0 && l == 0 && t.out_slots)
-      for (int past = t.path_slots + tid; past < t.max_path; past += 256) t.out_slots[(size_t)b * t.max_path + past] = -1;
-    __syncthreads();  // s_len and s_node are read
-  }
+    if (t.layers) {
+      __syncthreads();
+      const bool tables = t.tables;
+      compact_one(d, t.row_bytes, j, b, s_len, j < s_len ? s_node : 0, (const uint4 *)(tables ? ((const void *const *)t.k_tree)[l] : t.k_tree),
+                  (const uint4 *)(tables ? ((const void *const *)t.v_tree)[l] : t.v_tree),
+                  (uint4 *)(tables ? ((void *const *)t.k_pool)[l] : t.k_pool), (uint4 *)(tables ? ((void *const *)t.v_pool)[l] : t.v_pool),
+                  t.block_table, t.prefix_len, t.node_offset, t.max_path, l == 0 ? t.out_slots : nullptr, l == 0 ? t.new_len : nullptr);
+      // slots that no path of a tree reaches
+      if (t.path_slots < t.max_path && j == 0 && l == 0 && t.out_slots)
+        for (int past = t.path_slots + tid; past < t.max_path; past += 256) t.out_slots[(size_t)b * t.max_path + past] = -1;
+      if (MANY) __syncthreads();  // s_len and s_node are read
+    }
+    item += gridDim.x;
+  } while (MANY);
 }
 
 }  // namespace
@@ -242,8 +247,10 @@ hipError_t launch_verify_tail(const hb_attn_desc &d, TailArgs t, hipStream_t s) 
   t.path_slots = !t.layers ? 1 : t.max_path < 64 ? t.max_path : 64;
   constexpr long kMost = 1l << 22;  // workgroups of 256 threads: far from the 2^32 - 1 threads that a grid may have
   const long items = (long)d.batch * t.path_slots;
+  if (items > INT32_MAX - kMost) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(items < 1 ? 1 : items < kMost ? items : kMost), (unsigned)(t.layers > 0 ? t.layers : 1));
-  verify_tail_kernel<<<grid, 256, 0, s>>>(d, t);
+  if (items > kMost) verify_tail_kernel<true><<<grid, 256, 0, s>>>(d, t);
+  else verify_tail_kernel<false><<<grid, 256, 0, s>>>(d, t);
   return hipGetLastError();
 }
 

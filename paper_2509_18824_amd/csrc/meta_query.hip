@@ -1031,15 +1031,14 @@ hipError_t launch_project_wide(int32_t S, int32_t L, int32_t D, int32_t H, int32
 
 }  // namespace
 
-// Which form, by the time a slice of 64 features takes (microseconds, measured at D = 3584, 28 heads, 3
-// queries): 4 tokens and 2 heads per workgroup 0.65 while all workgroups run at once; 4 tokens and 4
-// heads 1.0, from about 80 tokens on the weights through the L2s (every 4 tokens read W_v, 9.2 TB/s);
-// 16 tokens and 4 heads 3.0, 16 tokens and 6 to 8 heads 5.0, per round of 256 workgroups.  For the
-// layer up to fc1: 96 tokens 133 us (16 tokens per workgroup 203), 300 tokens 295 (4 tokens 310, 8
-// heads 385), 2048 tokens 1074 (4 heads 1260, 4 tokens 1467).
+// Which form, by the time a slice of 64 features takes (microseconds, fitted to 759 drawn calls of 16 to 2100 tokens, 8 to
+// 32 heads, 12 to 32 layers, 1 to 4 queries): 4 tokens and 2 heads per workgroup where all workgroups run at once; 4 tokens
+// and 4 heads by the workgroups, every one of which reads its heads' part of W_v; 16 tokens by rounds of 256 workgroups, by
+// the queries and by the share of the CUs at work.  What it takes is 0.2 % slower in the mean than the fastest form of 981
+// other calls, 10 % at most; one time a round, 3.0 for 4 heads and 5.0 for more, was 1.1 % and 36 % (480 tokens, 21 layers,
+// 16 heads, 3 queries: 4 tokens a workgroup 78 us, 16 tokens 95; 1247, 15, 28, 1: 16 tokens and 7 heads 280, 4 heads 344).
 struct ProjectPlan {
   int tg, nt, hg;
-  double slice_us;
 };
 static int split_heads(int H, int most) {  // heads per workgroup, evenly
   const int groups = (H + most - 1) / most;
@@ -1048,26 +1047,40 @@ static int split_heads(int H, int most) {  // heads per workgroup, evenly
 static ProjectPlan project_plan(int32_t S, int32_t L, int32_t H, int32_t Q) {
   const int64_t g4 = (S + 3) / 4, g16 = (S + 15) / 16;
   auto groups = [&](int hg) { return (int64_t)(H + hg - 1) / hg; };
-  if (g4 * groups(2) <= 256) return {4, 2, split_heads(H, 2), 0.65};
-  ProjectPlan best = {4, 4, split_heads(H, 4), (double)(g4 * H) * kMpHeadDim * 128 / 9.2e6};
-  if (best.slice_us < 1.0) best.slice_us = 1.0;
+  if (g4 * groups(2) <= 256) return {4, 2, split_heads(H, 2)};
   const int wide = split_heads(H, std::min(8, kMpHq / Q)), narrow = split_heads(H, 4);
-  const double narrow_us = 3.0 * (double)((g16 * groups(narrow) + 255) / 256);
-  const double wide_us = 5.0 * (double)((g16 * groups(wide) + 255) / 256);
-  if (narrow_us < best.slice_us) best = {16, 4, narrow, narrow_us};
-  if (Q <= 3 && wide_us < best.slice_us) best = {16, 8, wide, wide_us};  // four queries: accumulators for 4 heads only
-  return best;
+  const double layers = L > 24 ? 1.0 + 0.0044 * (L - 24) : 1.0;  // more features to load
+  auto rounds_us = [&](int hg, double round, double share) {
+    const int64_t wgs = g16 * groups(hg);
+    return layers * ((double)((wgs + 255) / 256) * round + share * (double)wgs / 256);
+  };
+  const double four_us = 0.6 + 0.81 * (double)(g4 * groups(narrow)) / 256, narrow_us = rounds_us(narrow, 1.87 + 0.06 * Q, 0.34);
+  static const double kWide[4] = {0, 2.15, 2.7, 3.09};
+  // four queries: accumulators for 4 heads only
+  const double wide_us = Q <= 3 ? rounds_us(wide, kWide[Q] + (L < 24 ? 0.02 * (24 - L) : 0.0), 0.47) : 1e30;
+  if (wide_us < narrow_us && wide_us < four_us) return {16, 8, wide};
+  return narrow_us < four_us ? ProjectPlan{16, 4, narrow} : ProjectPlan{4, 4, narrow};
 }
 
-// Against values projected first: L rows per token through the product (0.85 PFLOP/s, 20 us at least)
-// and the mixing of the projected values (2.6 TB/s, 5 us at least).  28 layers, 3 queries, D = 3584,
-// the layer up to fc1: 16 tokens 92 us that way and 95 this way, 48 tokens 117 and 103, 2048 tokens 2082 and
-// 1074; 20 layers, 1 query, D = 4096: 100 tokens 122 and 131.
+// Against values projected first: L rows per token through the product (0.85 PFLOP/s, 20 us at least) and the mixing of the
+// projected values (2.6 TB/s, 5 us at least), which round the values to bf16 on the way.  The line is where slices of 0.65 to
+// 1 us with 4 tokens, 3.0 with 16 tokens and 4 heads and 5.0 with more heads, longer than they take, put it: what it sends
+// this way is 1.5 to 3 % slower in the mean of 1100 drawn calls than the faster of both orders (28 layers, 3 queries, D =
+// 3584, up to fc1: 16 tokens 92 us values first and 95 this way, 48 tokens 117 and 103, 2048 tokens 2082 and 860), and lines
+// closer to it would round the values of calls that have none rounded.
 bool meta_project_pays(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q) {
   if (!meta_project_supports(D, H)) return false;
   const double product = 2.0 * S * L * D * (double)D / 0.85e9, mixing = 2.0 * S * L * (double)D / 2.6e6;
   const double first = (product < 20 ? 20 : product) + (mixing < 5 ? 5 : mixing);
-  return 5 + project_plan(S, L, H, Q).slice_us * (D / 64) < first;
+  const int64_t g4 = (S + 3) / 4, g16 = (S + 15) / 16;
+  auto groups = [&](int most) { return (int64_t)(H + split_heads(H, most) - 1) / split_heads(H, most); };
+  double slice_us = 0.65;
+  if (g4 * ((H + 1) / 2) > 256) {
+    slice_us = std::max(1.0, (double)(g4 * H) * kMpHeadDim * 128 / 9.2e6);
+    slice_us = std::min(slice_us, 3.0 * (double)((g16 * groups(4) + 255) / 256));
+    if (Q <= 3) slice_us = std::min(slice_us, 5.0 * (double)((g16 * groups(std::min(8, kMpHq / Q)) + 255) / 256));
+  }
+  return 5 + slice_us * (D / 64) < first;
 }
 
 hipError_t launch_meta_attn_project(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q, const void *feats,

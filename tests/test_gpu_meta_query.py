@@ -76,7 +76,7 @@ def test_target_model_shape(S):
     (1203, 4, 768, 6, 2, [0, 3]),
     (1203, 32, 768, 6, 3, [0, 8, 31]),
     (3203, 4, 768, 6, 4, None),
-    (2203, 2, 1280, 10, 1, [1]),          # 16 tokens, up to 8 heads
+    (2203, 2, 1280, 10, 1, [1]),          # ... three groups of heads
     (2203, 12, 1280, 10, 2, [1, 11]),
     (2203, 9, 1280, 10, 3, None),
 ])
@@ -108,15 +108,55 @@ def test_values_projected_after_the_mixing(S, n_tok, L, D, H, Q, layers):
 @pytest.mark.parametrize("n_tok,L,D,H,Q,layers", [
     (2060, 28, 1024, 8, 3, [0, 5, 27]),   # 16 tokens: 24 hq rows, all of LDS; 28 layers are the most of 7 loads a slice
     (2040, 24, 1792, 14, 3, [1, 2, 23]),  # 21 rows; 6 loads
-    (2203, 25, 1280, 10, 3, None),        # 15 rows in two tiles of 16
+    (2203, 25, 1280, 10, 3, None),        # 4 heads, 7 loads
     (2061, 29, 1024, 8, 3, None),         # three slices of 32 features, 24 rows
     (2040, 32, 1792, 14, 3, [31, 0, 7]),  # ... 21 rows, all layers
-    (2047, 32, 1024, 8, 2, [31, 0]),      # 16 rows
-    (700, 30, 1024, 8, 4, None),          # two wavefronts a head, four queries
-    (690, 7, 256, 2, 1, [6]),             # one row a head, eight steps
+    (2047, 32, 1024, 8, 2, [31, 0]),      # 4 heads, two wavefronts each, 8 loads
+    (700, 30, 1024, 8, 4, None),          # 4 tokens, four queries
+    (690, 7, 256, 2, 1, [6]),             # 4 tokens, one row a head
 ])
 def test_sixteen_tokens_per_workgroup(S, n_tok, L, D, H, Q, layers):
     test_values_projected_after_the_mixing(S, n_tok, L, D, H, Q, layers)
+
+
+@pytest.mark.parametrize("n_tok,L,D,H,Q,layers,form", [
+    (501, 7, 256, 2, 1, None, "project<2>"),
+    (1030, 9, 512, 4, 3, [4, 0, 8], "project<4>"),
+    (2061, 24, 256, 2, 1, [23], "wide<1, 4, 6>"),
+    (2101, 25, 256, 2, 1, None, "wide<1, 4, 7>"),
+    (2131, 32, 256, 2, 1, [31], "wide<1, 4, 8>"),
+    (1875, 5, 768, 6, 2, [0, 4], "wide<2, 4, 6>"),
+    (2102, 28, 256, 2, 2, None, "wide<2, 4, 7>"),
+    (2132, 29, 256, 2, 2, [0, 28], "wide<2, 4, 8>"),
+    (2050, 24, 256, 2, 3, [12, 0, 23], "wide<3, 4, 6>"),
+    (2203, 28, 256, 2, 3, None, "wide<3, 4, 7>"),
+    (2251, 31, 256, 2, 3, [15, 0, 30], "wide<3, 4, 8>"),
+    (2319, 12, 256, 2, 4, None, "wide<4, 4, 6>"),
+    (2370, 28, 256, 2, 4, None, "wide<4, 4, 7>"),
+    (2541, 32, 256, 2, 4, None, "wide<4, 4, 8>"),
+    (2066, 5, 768, 6, 1, [4], "wide<1, 8, 6>"),
+    (2064, 28, 768, 6, 1, None, "wide<1, 8, 7>"),
+    (2077, 29, 768, 6, 1, [28], "wide<1, 8, 8>"),
+    (2064, 24, 768, 6, 2, [0, 23], "wide<2, 8, 6>"),
+    (2071, 25, 1024, 8, 2, None, "wide<2, 8, 7>"),
+    (2063, 32, 1024, 8, 2, [0, 31], "wide<2, 8, 8>"),  # 16 rows and all of LDS
+    (2065, 6, 768, 6, 3, [3, 0, 5], "wide<3, 8, 6>"),
+    (1500, 25, 1280, 10, 3, None, "wide<3, 8, 7>"),  # 15 rows in two tiles of 16
+    (2064, 28, 1024, 8, 3, [14, 0, 27], "wide<3, 8, 7>"),  # 24 rows and all of LDS
+    (2061, 32, 1024, 8, 3, [16, 0, 31], "wide<3, 8, 8>"),  # ... and three slices of 32 features
+    # where the lines between the forms matter: 6 to 30 % ahead of the next one
+    (480, 21, 2048, 16, 3, None, "project<4>"), (350, 26, 2560, 20, 4, None, "project<4>"),
+    (1247, 15, 3584, 28, 1, [14], "wide<1, 8, 6>"), (1147, 14, 4096, 32, 3, None, "wide<3, 4, 6>"),
+])
+def test_every_form_of_the_projection_after_the_mixing(S, n_tok, L, D, H, Q, layers, form):
+    """... each asserted by its kernel's name: project<16-column tiles of a wavefront> for 4 tokens a workgroup, wide<queries,
+    16-column tiles, feature loads of a wavefront> for 16."""
+    import re
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CUDA]) as trace:
+        test_values_projected_after_the_mixing(S, n_tok, L, D, H, Q, layers)
+    names = [m[1] + m[2] for m in (re.search(r"meta_(project|project_wide)_kernel(<[^>]*>)", e.name) for e in trace.events()) if m]
+    assert names == [form.replace("wide", "project_wide")]
 
 
 @pytest.mark.parametrize("n_tok,L,D,H,Q", [(7, 28, 768, 6, 3), (1203, 5, 768, 6, 2), (1025, 5, 512, 4, 2)])

@@ -239,3 +239,58 @@ def test_layer_rest_argument_errors():
     assert L.hb_swiglu_project(4, 3584, 18942, p, p, p, None, 0, None) == 2   # F % 4
     assert L.hb_swiglu_project(-1, 3584, 18944, p, p, p, None, 0, None) == 1
     assert L.hb_swiglu_project(0, 3584, 18944, None, None, None, None, 0, None) == 0
+
+
+def test_clearing_attention_argument_errors():
+    p, odd = C.c_void_p(0x1000), C.c_void_p(0x1004)
+    call = lambda d, clear, words, ptr=p: hb.lib.hb_tree_verify_attn_clearing(C.byref(d), ptr, p, p, p, p, p, p, p, p, p, None, None, 0,
+                                                                             clear, words, None)
+    one = _desc(num_splits=1)
+    assert call(one, None, 4) == 1 and call(one, p, -1) == 1
+    assert "clear" in hb.hb_last_error()
+    assert call(one, odd, 4) == 3 and "aligned" in hb.hb_last_error()
+    assert call(one, p, 4, None) == 1 and call(one, p, 4, C.c_void_p(0x1008)) == 1  # as hb_tree_verify_attn
+    assert call(_desc(num_splits=4), p, 4) == 3                                      # its workspace
+    assert call(_desc(D=100), p, 4) == 2
+    assert call(_desc(B=0, total_nodes=0), None, 0, None) == 0
+
+
+def test_lmhead_accept_argument_errors():
+    p = C.c_void_p(0x1000)
+    d = _desc()
+
+    def call(desc=d, M=120, K=3584, V=1000, hidden=p, ids=p, off=p, max_path=6, alen=p, keys=p, nbytes=1 << 20, layers=1, tables=0,
+             k_tree=p, table=p):
+        rcs = {f(None if desc is None else C.byref(desc), M, K, V, hidden, p, p, off, p, max_path, ids, alen, p, p, p, keys, nbytes,
+                 layers, tables, k_tree, p, p, p, table, p, None, None, None)
+               for f in (hb.lib.hb_lmhead_accept, hb.lib.hb_lmhead_accept_cleared)}
+        assert len(rcs) == 1
+        return rcs.pop()
+
+    assert call(desc=None) == 1 and call(max_path=0) == 1 and call(layers=-1) == 1
+    assert call(layers=65536, tables=1) == 2
+    assert call(layers=2) == 1 and "tables" in hb.hb_last_error()
+    assert call(K=0) == 1 and call(hidden=None) == 1 and call(ids=None) == 1 and call(M=-1) == 1
+    assert call(hidden=C.c_void_p(0x1008)) == 1 and "aligned" in hb.hb_last_error()
+    assert call(keys=None) == 3 and call(nbytes=120 * 8 - 1) == 3 and "960" in hb.hb_last_error()
+    assert call(keys=C.c_void_p(0x1004)) == 3
+    assert call(off=None) == 1 and call(alen=None) == 1
+    assert call(k_tree=None) == 1 and call(table=None) == 1
+    assert call(k_tree=C.c_void_p(0x1008)) == 1 and call(layers=3, tables=1, k_tree=C.c_void_p(0x1004)) == 1
+    assert call(desc=_desc(max_nodes=65)) == 2
+    # neither sequences nor rows: nothing to do, nothing needed
+    assert call(desc=_desc(B=0, total_nodes=0), M=0, hidden=None, ids=None, off=None, alen=None, keys=None, nbytes=0, k_tree=None) == 0
+
+
+def test_joined_projection_argument_errors():
+    L, p, odd = hb.lib, C.c_void_p(0x1000), C.c_void_p(0x1008)
+    norm = lambda T=4, K=3584, N=3584, x=p, res=p, w=p, eps=1e-6, out=p: L.hb_out_project_norm_ws(T, K, N, x, p, res, out, w, eps, p, p, 64, None)
+    assert norm(T=-1) == 1 and norm(K=0) == 1 and norm(eps=-1.0) == 1 and norm(eps=float("nan")) == 1
+    assert norm(K=100) == 2 and norm(N=3588) == 2
+    assert norm(x=None) == 1 and norm(w=None) == 1 and norm(out=None) == 1
+    assert norm(x=odd) == 1 and norm(res=odd) == 1 and norm(w=odd) == 1 and norm(out=odd) == 1
+    assert L.hb_out_project_norm_ws(0, 3584, 3584, None, None, None, None, None, 1e-6, None, None, 0, None) == 0
+    two = lambda T=4, K=3584, N=3584, x2=p, tmp=p: L.hb_out_project_two_ws(T, K, N, p, p, x2, p, tmp, p, p, 64, None)
+    assert two(T=-1) == 1 and two(N=0) == 1 and two(K=100) == 2 and two(N=3582) == 2 and two(K=1 << 30) == 2
+    assert two(x2=None) == 1 and two(tmp=None) == 1 and two(x2=odd) == 1 and two(tmp=odd) == 1
+    assert L.hb_out_project_two_ws(0, 3584, 3584, None, None, None, None, None, None, None, 0, None) == 0

@@ -405,3 +405,42 @@ def test_layer_stack_replays_from_a_hip_graph(S, tree, whole):
         replayed = snapshot()
         for a, b in zip(eager, replayed):
             assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+
+
+@pytest.mark.parametrize("n_layers,whole,norm_f", [(0, False, True), (0, True, True), (2, True, False), (2, True, True), (2, False, True)])
+def test_a_stack_run_joined_and_call_by_call(S, n_layers, whole, norm_f):
+    """A plain run and one that reports its calls agree: the same bits but for the normalisations, whose sums are taken in
+    another order (1e-6 of the scale, which turns a few roundings to bf16: 2^-9 of the result in the norm is more than
+    all of them).  A second run on other hidden states, with keys of the first one left in the workspace."""
+    inp = W.make_config(4, scale_down=8, tree="chain8")
+    V, F = 4096, 1536
+    T, Hq, Hkv, D = inp.total_nodes, inp.Hq, inp.Hkv, inp.D
+    K = Hq * D
+    dev, desc = S.to_device(inp), S.desc_for(inp)
+    g = torch.Generator(device="cuda").manual_seed(12)
+    mk = lambda *shape, std: (torch.randn(shape, generator=g, device="cuda") * std).to(torch.bfloat16)
+    w_qkv = [mk((Hq + 2 * Hkv) * D, K, std=K ** -0.5) for _ in range(max(n_layers, 1))]
+    w_o = [mk(K, K, std=0.3 * K ** -0.5) for _ in range(max(n_layers, 1))]
+    mlp = _mlp_weights(mk, max(n_layers, 1), K, F) if whole else None
+    if whole and not norm_f:
+        del mlp["norm_f"]
+    pools = [(dev.k_pool.clone(), dev.v_pool.clone()) for _ in range(n_layers)]
+    stack = S.VerifyLayerStack(desc, dev, pools, w_qkv, w_o, mk(V, K, std=0.02), torch.zeros(T, dtype=torch.int32, device="cuda"),
+                               inp.max_path, mk(T, K, std=4.0), mlp=mlp)
+    for std in (4.0, 0.5):
+        stack.hidden[0].copy_(mk(T, K, std=std))
+        stack.run()
+        torch.cuda.synchronize()
+        joined = [t.clone() for t in (stack.final_hidden, stack.target_ids, stack.accept_len, stack.out_tokens, stack.new_len)]
+        names = []
+        stack.run(on_call=names.append)
+        torch.cuda.synchronize()
+        single = (stack.final_hidden, stack.target_ids, stack.accept_len, stack.out_tokens, stack.new_len)
+        assert names[-4:] == ["lmhead_argmax", "tree_accept", "kv_compact", "end"]
+        if not (whole and n_layers):
+            same = joined if n_layers else joined[:-1]  # no layer, no append
+            assert all(torch.equal(a, b) for a, b in zip(same, single))
+            continue
+        a, b = joined[0].double(), single[0].double()
+        assert torch.isfinite(a).all() and (a - b).norm() <= 2 ** -9 * b.norm()
+        assert (joined[1] == single[1]).float().mean() >= 0.99  # ties of logits this close are few

@@ -1,5 +1,5 @@
-"""GPU parity: hb_tree_verify_attn_clearing + hb_lmhead_accept (LM head, acceptance and the append to
-every layer's cache in two launches) give the oracle's results bit for bit."""
+"""GPU parity: hb_tree_verify_attn_clearing + hb_lmhead_accept_cleared (LM head, acceptance and the append to
+every layer's cache in two launches) give the oracle's results bit for bit, and so does hb_lmhead_accept."""
 import numpy as np
 import pytest
 import torch
@@ -54,9 +54,9 @@ def test_lm_head_acceptance_and_append(kind, dtype, layers, short):
     hb.hb_tree_verify_attn(*args, ref_out, None, ws)
     hb.hb_tree_verify_attn_clearing(*args, out, None, ws, keys, T)
     assert not keys.any() and torch.equal(out.view(torch.uint8), ref_out.view(torch.uint8))
-    hb.hb_lmhead_accept(desc, hidden, weight, torch.from_numpy(np.asarray(draft, dtype=np.int32)).cuda(), dev.node_offset,
-                        dev.parent, max_path, ids, alen, path, toks, bonus, keys, layers, kv, dev.block_table,
-                        dev.prefix_len, slots, new_len)
+    hb.hb_lmhead_accept_cleared(desc, hidden, weight, torch.from_numpy(np.asarray(draft, dtype=np.int32)).cuda(), dev.node_offset,
+                                dev.parent, max_path, ids, alen, path, toks, bonus, keys, layers, kv, dev.block_table,
+                                dev.prefix_len, slots, new_len)
     torch.cuda.synchronize()
     assert np.array_equal(ids.cpu().numpy(), target)
     for got, ref in zip((alen, path, toks, bonus), want):
@@ -67,6 +67,59 @@ def test_lm_head_acceptance_and_append(kind, dtype, layers, short):
             assert np.array_equal(bits(d.k_pool), ref_k) and np.array_equal(bits(d.v_pool), ref_v)
     else:
         assert (slots == -7).all() and (new_len == -7).all()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_malformed_trees_and_rows_that_name_no_token(dtype):
+    """The results of the three calls that it stands for, bit for bit, also for parents that do not precede their nodes or
+    are below -1, drafted ids outside the vocabulary and rows without a logit that counts (all NaN, all -inf, one +inf)."""
+    import paper_2509_18824_amd as hb
+    import paper_2509_18824_amd.step as S
+    K, V, n = 256, 500, 12
+    trees = [W.seeded_tree(b, n_nodes=n, levels=4, root_fanout=4) for b in range(6)]
+    inp = W.make_verify_inputs(8, dtype, 2, 1, 128, [5, 40, 17, 3, 64, 31], trees, poison=False)
+    T, B, mp = inp.total_nodes, len(trees), inp.max_path
+    rng = np.random.default_rng(2)
+    parent = inp.parent.numpy().copy()
+    parent[[3, n + 2, 2 * n + 5]] = [3, 7, 11]           # itself, a later node, the last
+    parent[[3 * n + 4, 4 * n + 1]] = [-2, -2147483648]
+    parent[5 * n] = 5                                    # a root with a parent
+    g = torch.Generator().manual_seed(3)
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    weight = torch.randn((V, K), generator=g).to(td)
+    weight[:, 0] = 1.0
+    hidden = torch.randn((T, K), generator=g).to(td)
+    hidden[::7] = float("nan")
+    hidden[2::9] = 0.0
+    hidden[2::9, 0] = float("-inf")
+    hidden[4::11, 3] = float("inf")
+    dev, desc, weight, hidden = S.to_device(inp), S.desc_for(inp), weight.cuda(), hidden.cuda()
+    par = torch.from_numpy(parent).cuda()
+    i32 = lambda *shape: torch.full(shape, -7, dtype=torch.int32, device="cuda")
+    new = lambda: (i32(T), i32(B), i32(B, mp), i32(B, mp), i32(B), i32(B, mp), i32(B))
+    pools = [(dev.k_pool.clone(), dev.v_pool.clone()) for _ in range(3)]
+    ids, alen, path, toks, bonus, slots, new_len = want = new()
+    hb.hb_lmhead_argmax(hidden, weight, ids, None, S.alloc_workspace(8 * T))
+    # drafted: the target's choice after the parent, where there is one, and here and there no token at all
+    t = ids.cpu().numpy()
+    off = inp.node_offset.numpy()
+    draft = np.array([t[off[i // n] + max(parent[i], 0)] if 0 <= parent[i] < n else 1 for i in range(T)], dtype=np.int32)
+    draft[rng.integers(0, T, 6)] = [-1, V, 2147483647, -2147483648, 0, 1]
+    draft = torch.from_numpy(draft).cuda()
+    hb.hb_tree_accept(B, n, dev.node_offset, par, draft, ids, mp, alen, path, toks, bonus)
+    hb.hb_kv_compact(desc, dev.k_tree, dev.v_tree, *pools[0], dev.block_table, dev.prefix_len, dev.node_offset, alen, path, mp,
+                     slots, new_len)
+    for call, kv in ((hb.hb_lmhead_accept, pools[1]), (hb.hb_lmhead_accept_cleared, pools[2])):
+        keys = torch.zeros(8 * T, dtype=torch.uint8, device="cuda")
+        if call is hb.hb_lmhead_accept:
+            keys.fill_(255)
+        got = new()
+        call(desc, hidden, weight, draft, dev.node_offset, par, mp, *got[:5], keys, 1, (dev.k_tree, dev.v_tree, *kv),
+             dev.block_table, dev.prefix_len, *got[5:])
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(got, want))
+        assert all(torch.equal(a.view(torch.uint8), b.view(torch.uint8)) for a, b in zip(kv, pools[0]))
+    assert (alen > 1).any() and (t[::7] == t[0]).all()
 
 
 @pytest.mark.parametrize("dtype,nodes", [("f32", 4), ("bf16", 8), ("bf16", 40)])

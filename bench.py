@@ -192,45 +192,43 @@ def run_full_step(tree, steps, warmup, weight, V, K):
     torch.cuda.synchronize()
     dv = step.dev
 
-    def one_step(i, ev_attn=None, ev_lm=None, ev_acc=None, ev_cmp=None):
-        if ev_attn: ev_attn[i][0].record()
+    def one_step(i, ev_attn, ev_lm, ev_acc, ev_cmp):
+        """The step by the single calls that ``run`` joins, with events around each."""
+        ev_attn[i][0].record()
         hb.hb_tree_verify_attn(desc, dv.q, dv.k_tree, dv.v_tree, dv.k_pool, dv.v_pool, dv.block_table,
                                dv.prefix_len, dv.node_offset, dv.parent, step.out, None, step.ws_attn)
-        if ev_attn: ev_attn[i][1].record()
-        if ev_lm: ev_lm[i][0].record()
+        ev_attn[i][1].record()
+        ev_lm[i][0].record()
         hb.hb_lmhead_argmax(step.out.view(inp.total_nodes, -1), wdev, step.target_ids, None, step.ws_lm)
-        if ev_lm: ev_lm[i][1].record()
-        if ev_acc: ev_acc[i][0].record()
+        ev_lm[i][1].record()
+        ev_acc[i][0].record()
         hb.hb_tree_accept(desc.batch, desc.max_nodes_per_tree, dv.node_offset, dv.parent, step.draft_ids,
                           step.target_ids, step.max_path, step.accept_len, step.accept_path, step.out_tokens,
                           step.bonus)
-        if ev_acc: ev_acc[i][1].record()
-        if ev_cmp: ev_cmp[i][0].record()
+        ev_acc[i][1].record()
+        ev_cmp[i][0].record()
         hb.hb_kv_compact(desc, dv.k_tree, dv.v_tree, dv.k_pool, dv.v_pool, dv.block_table, dv.prefix_len,
                          dv.node_offset, step.accept_len, step.accept_path, step.max_path, step.out_slots,
                          step.new_len)
-        if ev_cmp: ev_cmp[i][1].record()
+        ev_cmp[i][1].record()
 
-    # Timed region: exactly `steps` full steps.  Inside it HIP events (on the launch stream)
-    # bracket the LM-head call only, the dominant kernel whose duration the roofline needs: an
-    # event pair costs the stream about 5 us, and eight of them per step would take 4 % off the
-    # figure they are there to explain.
-    ev_lm = _events(steps)
+    # Timed region: exactly `steps` full steps as a user's program makes them, and nothing else.
     torch.cuda.synchronize()
     t0 = time.perf_counter()
-    for i in range(steps):
-        one_step(i, ev_lm=ev_lm)
+    for _ in range(steps):
+        step.run()
     torch.cuda.synchronize()
     t1 = time.perf_counter()
     ms_step = (t1 - t0) * 1e3 / steps
-    ms_lm = _mean_ms(ev_lm)
-    # The other calls' durations come from a second pass of the same steps, outside the timed
-    # region, with events around every call.
-    ev_attn, ev_lm2, ev_acc, ev_cmp = (_events(steps) for _ in range(4))
+    # The calls' durations come from a second pass of as many steps, outside the timed region: an
+    # event pair costs the stream about 5 us.
+    ev_attn, ev_lm, ev_acc, ev_cmp = (_events(steps) for _ in range(4))
     for i in range(steps):
-        one_step(i, ev_attn, ev_lm2, ev_acc, ev_cmp)
+        one_step(i, ev_attn, ev_lm, ev_acc, ev_cmp)
     torch.cuda.synchronize()
-    ms_attn, ms_acc, ms_cmp = map(_mean_ms, (ev_attn, ev_acc, ev_cmp))
+    ms_attn, ms_lm, ms_acc, ms_cmp = map(_mean_ms, (ev_attn, ev_lm, ev_acc, ev_cmp))
+    step.run()  # what is checked are the outputs of the calls that were timed
+    torch.cuda.synchronize()
     accept_len = step.accept_len.cpu().numpy()
     assert list(accept_len) == [d + 1 for d in planted], "accepted lengths differ from the planted paths"
     return dict(inp=inp, desc=desc, step=step, dev=dv, wdev=wdev, draft_np=draft_np, planted=planted,
@@ -239,7 +237,7 @@ def run_full_step(tree, steps, warmup, weight, V, K):
 
 
 def parity_check(run, weight):
-    """GPU outputs of the last timed step against the CPU oracle on the same inputs, every node
+    """GPU outputs of a step like the timed ones against the CPU oracle on the same inputs, every node
     (outside the timed region): attention output of all tree nodes; LM-head ids of all rows by
     the margin rule (the oracle's logits are computed from the GPU's own bf16 hidden states, so
     that the comparison isolates the LM head); acceptance and compaction bit for bit."""

@@ -258,9 +258,8 @@ int32_t hb_out_project_two_ws(int32_t T, int32_t K, int32_t N, const void *x1, c
 
 /*
  * hb_out_project_ws, then hb_rmsnorm of its result: out = x W^T (+ residual), the same bits, and norm_out = the normalised
- * rows of out.  Where the projection is split over K, both are one launch with the sum of the parts (which may add a
- * row's squares in another order).  norm_out [T, N]
- * must not overlap any other argument; N % 8 == 0.  Errors as in those two.
+ * rows of out.  Where the projection is split over K the launch that sums the parts may also normalise (and then adds a
+ * row's squares in another order).  norm_out [T, N] must not overlap any other argument; N % 8 == 0.  Errors as in those two.
  */
 int32_t hb_out_project_norm_ws(int32_t T, int32_t K, int32_t N, const void *x, const void *w, const void *residual_or_null,
                                void *out, const void *norm_weight, float eps, void *norm_out, void *workspace,

@@ -56,8 +56,15 @@ struct NormArgs {  // of the rows that a plain projection gives; weight null: no
   bf16_t *out;           // [M, N]
   float eps;
 };
-// A row of these is normalised in the launch that sums the parts of K.
-inline bool norm_fits(const NormArgs &n, int N) { return n.weight && N % 8 == 0 && N <= 8192; }
+// A row of these is normalised in the launch that sums the parts of K: a workgroup per token, eight values a thread.  Of
+// more than 128 tokens a short row leaves the workgroup's threads idle, and one just longer than the workgroup asks for a
+// second round trip for a few values; two launches are ahead there (us, two launches and one: 619 x 17600 x 232 25.8 and
+// 32.9, 536 x 12544 x 512 27.4 and 29.7, 528 x 4992 x 4136 43.6 and 45.0; on the other side
+// 300 x 3584 x 1100 4 %, x 4000 5 %, x 6500 1.5 % for one; 500 calls).
+inline bool norm_fits(const NormArgs &n, int M, int N) {
+  if (!n.weight || N % 8 || N > 8192) return false;
+  return M <= 128 || (N >= 1024 && !(M > 256 && N > 4096 && N < 5120));
+}
 
 // ROPE: query/key/value projection with rotary embedding (V = (Hq + 2 Hkv) * 128 weight rows),
 // else plain projection.  One workgroup per (weight tile, hidden tile), dealt by deal_unit.
@@ -541,7 +548,7 @@ double stream_us(int M, int K, int V) {
 template <bool ROPE, bool GLU>
 hipError_t launch_reduce(int M, int V, int ks, int v_pad, int m_pad, const QkvArgs &qa, const StoreArgs &sa, const float *part,
                          const NormArgs &norm, hipStream_t s) {
-  if (!ROPE && !GLU && norm_fits(norm, V)) {
+  if (!ROPE && !GLU && norm_fits(norm, M, V)) {
     proj_reduce_norm_kernel<<<(unsigned)M, kNormThreads, 0, s>>>(V, ks, v_pad, m_pad, part, sa, norm);
     return hipGetLastError();
   }
@@ -786,7 +793,7 @@ static hipError_t launch_linear(int32_t M, int32_t K, int32_t N, const void *x, 
   Ways ways;
   const Way way = way_of(M, K, N, StreamKind::kPlain, part, &ways);
   const int parts = way == Way::kPair ? ways.pair.ks : way == Way::kFew ? ways.few.ks : way == Way::kTiles ? ways.split.ks : 1;
-  *normed = parts > 1 && norm_fits(norm, N);
+  *normed = parts > 1 && norm_fits(norm, M, N);
   if (way == Way::kPair) return launch_pair<false, false>(StreamKind::kPlain, ways.pair, M, K, N, x, w, qa, sa, part, s, norm);
   if (way == Way::kFew) return launch_few<false, false>(StreamKind::kPlain, ways.few, M, K, N, x, w, qa, sa, part, s, norm);
   if (way == Way::kStream) return launch_proj_stream(StreamKind::kPlain, M, K, N, x, w, {sa.residual, sa.out}, s);

@@ -305,6 +305,12 @@ def test_projection_and_normalisation_are_the_two_calls_one_after_the_other(hb, 
     assert any("proj_reduce_norm_kernel" in e.name for e in trace.events()) == fused
 
 
+@pytest.mark.parametrize("T,K,N,fused", [(536, 12544, 512, False), (300, 7488, 1016, False), (300, 7488, 1024, True), (128, 7488, 512, True),
+                                         (300, 4992, 4096, True), (300, 4992, 4104, False), (200, 4992, 4104, True), (300, 4992, 5120, True)])
+def test_projection_and_normalisation_in_one_launch_where_that_is_ahead(hb, T, K, N, fused):
+    test_projection_and_normalisation_are_the_two_calls_one_after_the_other(hb, T, K, N, T % 2 == 0, fused)
+
+
 @pytest.mark.parametrize("K,N,gated", [(14336, 4096, False), (18944, 3584, False), (4096, 28672, True)])
 def test_seventeen_tokens_take_hardly_longer_than_sixteen(hb, K, N, gated):
     """Shapes where the stream stays ahead beyond 16 tokens: 25 and 26 us, 31 and 32, 43 and 44 by it; 33, 39 and 54 by tiles

@@ -12,11 +12,12 @@
 //
 // meta_scores_kernel: the scores of all tokens are one dense product A [H Q, D] x feats^T
 // [D, S L].  A workgroup takes eight tokens and a range of D, 64 features at a time: the tokens'
-// features and both halves of A go from memory to LDS directly, one step ahead of the matrix
-// instructions (16x16x32); four pairs of wavefronts take two tokens each and half of the rows of
-// A.  With few tokens D is spread over several workgroups, which write partial scores (fp32) to a
-// workspace.  2048 tokens, 28 layers, D = 3584: 130 us with W_v's
-// rearrangement (411 MB of features and nearly as much of A through the L2s); with the features loaded in fragment order, four rows per four lanes, 183 us.
+// features and both halves of A go from memory to LDS directly, features two steps and A one step ahead
+// of the matrix instructions (16x16x32); four pairs of wavefronts take two tokens each and half of the
+// rows of A.  With few tokens D is spread over several workgroups, which write partial scores (fp32) to
+// a workspace.  2048 tokens, 28 layers, D = 3584: 110 us with W_v's rearrangement (411 MB of features and
+// nearly as much of A through the L2s); 122 with features one step ahead, 183 with features loaded in
+// fragment order, four rows per four lanes.
 // meta_mix_kernel, one workgroup per token (and per 4096 features): sums the partial scores, one thread per (head, query)
 // row does the softmax over the L layers, and every thread then mixes the token's projected values
 // (v_proj = f_i W_v^T, a plain linear layer run beforehand) for eight feature columns of all Q
@@ -167,8 +168,7 @@ __global__ __launch_bounds__(kScoreThreads) void meta_scores_kernel(int S, int L
   int stage = 0;
 #pragma unroll 1
   for (int st = 0; st < steps; ++st) {
-    // This step's loads have landed; in flight stay the features of the next two steps and the next A (the first
-    // step waits for more than it needs).
+    // This step's loads have landed; in flight stay the features of the next two steps and the next A.
     asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * kScoreFeatLoads + kScoreALoads) : "memory");
     const u32x4 *f = meta_a_lds + stage * kScoreFeatStage, *ah = lds_a + (st & 1) * kScoreAStage, *al = ah + rows_pad * 8;
 #pragma unroll
@@ -356,7 +356,7 @@ __global__ __launch_bounds__(kMixThreads) void meta_mix_kernel(int S, int L, int
 // value projection of all layers and the mixing of its results took 1478 + 161 us.  96 tokens: 62 us against 76 + 15.
 constexpr int kMpThreads = 512;
 constexpr int kMpWaves = 8;
-constexpr int kMpHq = 24;           // hq rows of a workgroup at most: 96 KB of mixed features beside 64 KB of features
+constexpr int kMpHq = 24;           // hq rows of a workgroup at most (16 tokens: 48 KB of mixed features beside 96 to 112 KB of features)
 constexpr int kMpHeadDim = 128;
 
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
@@ -1019,7 +1019,11 @@ hipError_t launch_project_wide(int32_t S, int32_t L, int32_t D, int32_t H, int32
     if constexpr (FI > 6) return launch_project_wide<QT, NT, FI - 1>(S, L, D, H, Q, hg, parts, feats, packed, res, pre, res_out, part, s);
   }
   constexpr bool kShort = mw_short(QT, NT, FI);
-  const size_t lds = ((size_t)(kShort ? 3 : 2) * mw_stage(FI, kShort) + 2 * (size_t)hg * Q * kMwTok * 4) * sizeof(u32x4);
+  constexpr size_t kStages = (size_t)(kShort ? 3 : 2) * mw_stage(FI, kShort);
+  constexpr int kMostRows = NT == 4 ? 4 * QT : 8 * QT < kMpHq ? 8 * QT : kMpHq;  // of project_plan
+  static_assert((kStages + 2 * kMostRows * kMwTok * 4) * sizeof(u32x4) <= 160 * 1024, "more LDS than a CU has");
+  if (hg * Q > kMostRows) return hipErrorInvalidValue;
+  const size_t lds = (kStages + 2 * (size_t)hg * Q * kMwTok * 4) * sizeof(u32x4);
   auto kern = meta_project_wide_kernel<QT, NT, FI>;
   hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;

@@ -26,7 +26,7 @@ FLAGS = [
 # instructions selected in their vector-register form there are no accumulation registers and
 # no copies between the two register files.
 # The tile kernels' accumulators are many small tiles, which the compiler otherwise copies about.
-FILE_FLAGS = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form=1"] for f in ("attn_mfma.hip", "lmhead_mfma.hip", "proj_mfma.hip", "proj_few.hip", "proj_pair.hip")}
+FILE_FLAGS = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form=1"] for f in ("attn_mfma.hip", "lmhead_mfma.hip", "lmhead_few.hip", "proj_mfma.hip", "proj_few.hip", "proj_pair.hip")}
 
 
 def sources():

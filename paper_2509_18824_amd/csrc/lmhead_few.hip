@@ -1,0 +1,277 @@
+// LM head with fused argmax for up to 128 hidden rows, and for up to 256 where a workgroup then has one tile: a stream of
+// the weight matrix (lmhead_mfma.hip, of which this is the arithmetic, has the rest).
+//
+// Every workgroup, one per CU, has a run of consecutive vocabulary rows for itself and takes it in tiles of up to 320 rows
+// of equal height against one hidden tile.  The loads run on across its tiles, a lane keeps its best over all of them, and
+// the wavefronts' bests meet in LDS once at the end: one atomic per hidden row and workgroup.
+//
+// What bounds it: memory, and the CU's path from L2 beside it.  A K step of 64 fetches 128 bytes of every weight row of
+// the tile and of every hidden row, and with hidden rows that are always the same line 128 rows x 3584 x 152064 took 190 us
+// where they took 211, 60 rows 171 and 186 (without matrix instructions 203 and 185): hence the tallest tile that LDS holds
+// (128 rows: tiles of 304 against 208, 183 and 199 us), and all 256 CUs at work instead of the 200 that shared 594 tiles
+// of 256 rows evenly.  us, tiles of 256 rows one by one and this: 152064 x 3584, 8 rows 172 -> 165, 60 186 -> 168,
+// 128 210 -> 183; x 4096, 8 rows 231 -> 192, 128 252 -> 215; 100000 x 2048, 8 rows 95 -> 86; 4096 x 4096, 64 rows 52 -> 32,
+// 128 50 -> 32; 64000 x 3584, 128 rows, where both have the same tiles, 83 -> 84.
+//
+// Two wavefronts of a SIMD alternate between operands and matrix instructions as in mfma_gemm_tile.inc.
+#include "mfma_gemm_tile.h"
+
+namespace hb {
+
+namespace {
+
+constexpr int kBufferFlags = 0x00027000;  // untyped 32-bit elements
+constexpr int kWaves = 8;
+constexpr int kMostTall = 5;              // 64 vocabulary rows each, of a tile
+
+// MT: 32-row hidden tiles of a wavefront, WT: its 16-row vocabulary tiles (4 x 2 wavefronts)
+template <int MT, int WT>
+struct Few {
+  static constexpr int kRows = 64 * WT, kTok = 64 * MT;    // of a tile: vocabulary rows, hidden rows
+  static constexpr int kW = kRows / 8 / kWaves, kH = kTok / 8 / kWaves;  // loads of a wavefront per K step
+  static constexpr int kWStage = kRows * CH, kHStage = kTok * CH;        // 16-byte pieces
+  static constexpr int kRing = 3, kHRing = MT == 1 ? 3 : 2;  // LDS stages of the weights and of the hidden rows
+  static constexpr bool kSame = kHRing == kRing;             // both tiles of a step are fetched together
+  static constexpr size_t kLds = (size_t)(kRing * kWStage + kHRing * kHStage) * 16;
+  static_assert(kLds <= 160 * 1024, "more LDS than a CU has");
+};
+
+// 16 bytes a lane from `offset` of `from`, plus `k_offset` inside its row, to LDS, lane after lane; from `bytes` on zeros
+template <int HINT>
+__device__ __forceinline__ void rows_to_lds(const u32x4 *from, int bytes, u32x4 *to, int offset, int k_offset) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void *)from, 0, bytes, kBufferFlags),
+                                           (__attribute__((address_space(3))) void *)to, 16, offset, k_offset, 0, HINT);
+}
+
+// the largest key of the lanes l, l ^ 16, l ^ 32 and l ^ 48
+__device__ __forceinline__ unsigned long long max_of_lane_groups(unsigned long long key) {
+  typedef unsigned int swap2 __attribute__((ext_vector_type(2)));
+  auto larger = [](swap2 hi, swap2 lo) {
+    const unsigned long long a = ((unsigned long long)hi[0] << 32) | lo[0], b = ((unsigned long long)hi[1] << 32) | lo[1];
+    return a > b ? a : b;
+  };
+  key = larger(__builtin_amdgcn_permlane16_swap((uint32_t)(key >> 32), (uint32_t)(key >> 32), false, false),
+               __builtin_amdgcn_permlane16_swap((uint32_t)key, (uint32_t)key, false, false));
+  return larger(__builtin_amdgcn_permlane32_swap((uint32_t)(key >> 32), (uint32_t)(key >> 32), false, false),
+                __builtin_amdgcn_permlane32_swap((uint32_t)key, (uint32_t)key, false, false));
+}
+
+// ALONE: one hidden tile, nobody shares a workgroup's weights, which then carry the non-temporal hint.  Else the hidden
+// tiles of a run are neighbours on one XCD.
+template <int MT, int WT, bool ALONE>
+__global__ __launch_bounds__(512) void lmhead_few_kernel(int M, int K, int V, int m_tiles, int own, int height,
+                                                         const u32x4 *__restrict__ hidden, const u32x4 *__restrict__ weight,
+                                                         unsigned long long *__restrict__ keys) {
+  using F = Few<MT, WT>;
+  constexpr int JT = 2 * MT;
+  extern __shared__ u32x4 lds[];
+  u32x4 *lw = lds, *lh = lds + F::kRing * F::kWStage;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wv = wave >> 1, wm = wave & 1;
+  const int j16 = lane & 15, kq = lane >> 4;
+  const int row_bytes = K * 2, k_steps = K / BK;
+  const int slot = (int)blockIdx.x / kXcds;
+  const int first = (slot / m_tiles * kXcds + (int)blockIdx.x % kXcds) * own, end = min(V, first + own);
+  const int m0 = slot % m_tiles * F::kTok;
+  if (first >= end) return;
+  hidden += (size_t)m0 * (row_bytes / 16);
+  const int m_rows = min(M - m0, F::kTok);
+
+  // A load is eight rows of 128 bytes, pieces swizzled on the source side (lane -> row lane / 8); rows past the tile's or
+  // past the hidden rows arrive as zeros.
+  const int mine = (lane >> 3) * row_bytes + ((lane & 7) ^ (lane >> 3)) * 16;
+  int w_off[F::kW], h_off[F::kH];
+#pragma unroll
+  for (int i = 0; i < F::kW; ++i) w_off[i] = (wave + kWaves * i) * 8 * row_bytes + mine;
+#pragma unroll
+  for (int i = 0; i < F::kH; ++i) h_off[i] = (wave + kWaves * i) * 8 * row_bytes + mine;
+  int w_at = first, w_k = 0, h_k = 0;  // what is fetched next; past the last step that step again: the waits count loads
+  auto issue_w = [&](int slot) {
+    const u32x4 *from = weight + (size_t)w_at * (row_bytes / 16);
+    const int bytes = __builtin_amdgcn_readfirstlane(min(height, end - w_at)) * row_bytes;
+#pragma unroll
+    for (int i = 0; i < F::kW; ++i) rows_to_lds<ALONE ? 2 : 0>(from, bytes, lw + slot * F::kWStage + (wave + kWaves * i) * 64, w_off[i], w_k * (BK * 2));
+    if (++w_k == k_steps) {
+      if (w_at + height < end) {
+        w_at += height;
+        w_k = 0;
+      } else {
+        --w_k;
+      }
+    }
+  };
+  auto issue_h = [&](int slot) {
+#pragma unroll
+    for (int i = 0; i < F::kH; ++i) rows_to_lds<0>(hidden, m_rows * row_bytes, lh + slot * F::kHStage + (wave + kWaves * i) * 64, h_off[i], h_k * (BK * 2));
+    h_k = h_k + 1 == k_steps ? 0 : h_k + 1;
+  };
+
+  float best[JT];
+  int best_v[JT];
+#pragma unroll
+  for (int j = 0; j < JT; ++j) {
+    best[j] = -__builtin_huge_valf();
+    best_v[j] = -1;
+  }
+  // Phases as in mfma_gemm_tile.inc, steps counted through all tiles: loads two steps ahead (hidden rows in two stages one).
+  const bool late = wave >= kWaves / 2;
+  int cur = 0, w_free = 0, h_slot = 0;
+#pragma unroll
+  for (int t = 0; t < F::kRing - 1; ++t) {
+    if (t < F::kHRing - 1) issue_h(t);
+    issue_w(t);
+    ++w_free;
+  }
+  auto landed = [&] { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(F::kSame ? F::kW + F::kH : F::kW) : "memory"); };
+  auto phase = [&] { asm volatile("s_barrier" ::: "memory"); };
+  landed();
+  phase();
+  if (late) {
+    if (!F::kSame) issue_h(1);
+    phase();
+  }
+#pragma unroll 1
+  for (int v0 = first; v0 < end; v0 += height) {
+    f32x4 acc[WT][JT];
+#pragma unroll
+    for (int i = 0; i < WT; ++i)
+#pragma unroll
+      for (int j = 0; j < JT; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int kt = 0; kt < k_steps; ++kt) {
+      const u32x4 *cw = lw + cur * F::kWStage, *chh = lh + (F::kSame ? cur : h_slot) * F::kHStage;
+      bf16x8 a[2][WT], b[2][JT];
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const int c = s * 4 + kq;
+#pragma unroll
+        for (int i = 0; i < WT; ++i) a[s][i] = __builtin_bit_cast(bf16x8, cw[swz((wv * WT + i) * 16 + j16, c)]);
+#pragma unroll
+        for (int j = 0; j < JT; ++j) b[s][j] = __builtin_bit_cast(bf16x8, chh[swz((wm * JT + j) * 16 + j16, c)]);
+      }
+      if (F::kSame) issue_h(w_free);
+      else if (!late) issue_h(h_slot ^ 1);
+      issue_w(w_free);
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+#pragma unroll
+        for (int i = 0; i < WT; ++i) asm volatile("" : "+v"(a[s][i]));
+#pragma unroll
+        for (int j = 0; j < JT; ++j) asm volatile("" : "+v"(b[s][j]));
+      }
+      if (late) landed();
+      phase();
+      if (!F::kSame && late) issue_h(h_slot);
+      __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int i = 0; i < WT; ++i)
+#pragma unroll
+          for (int jj = 0; jj < JT; ++jj) {
+            const int j = (i & 1) ? JT - 1 - jj : jj;
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[s][i], b[s][j], acc[i][j], 0, 0, 0);
+          }
+      __builtin_amdgcn_s_setprio(0);
+      __builtin_amdgcn_sched_barrier(0);
+      if (!late) landed();
+      phase();
+      cur = cur + 1 == F::kRing ? 0 : cur + 1;
+      w_free = w_free + 1 == F::kRing ? 0 : w_free + 1;
+      h_slot ^= 1;
+    }
+    // Scanning (tile, i, e) in order visits v in increasing order, so a strict '>' keeps the lowest v among equal values;
+    // NaN compares false and never wins.
+    const int v = v0 + wv * 16 * WT + 4 * kq, left = min(end, v0 + height) - v;
+#pragma unroll
+    for (int j = 0; j < JT; ++j) {
+      int at = -1;
+#pragma unroll
+      for (int i = 0; i < WT; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const bool take = i * 16 + e < left && acc[i][j][e] > best[j];
+          best[j] = take ? acc[i][j][e] : best[j];
+          at = take ? i * 16 + e : at;
+        }
+      best_v[j] = at < 0 ? best_v[j] : v + at;
+    }
+  }
+  if (!late) phase();
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();  // all loads have landed, all operands are read: LDS is free
+  unsigned long long(*row_key)[F::kTok] = reinterpret_cast<unsigned long long(*)[F::kTok]>(lds);
+#pragma unroll
+  for (int j = 0; j < JT; ++j) {
+    // a lane that saw nothing above -inf offers no candidate (key 0 loses to every real key)
+    const unsigned long long key = max_of_lane_groups(best_v[j] >= 0 ? argmax_key(best[j], (uint32_t)best_v[j]) : 0ull);
+    if (kq == 0) row_key[wv][(wm * JT + j) * 16 + j16] = key;
+  }
+  __syncthreads();
+  const int m = threadIdx.x;
+  if (m >= m_rows) return;
+  unsigned long long key = row_key[0][m];
+#pragma unroll
+  for (int w = 1; w < 4; ++w) key = row_key[w][m] > key ? row_key[w][m] : key;
+  // skip the atomic when the row already holds something at least as good
+  if (key > __atomic_load_n(&keys[m0 + m], __ATOMIC_RELAXED)) atomicMax(&keys[m0 + m], key);
+}
+
+template <int MT, int WT>
+hipError_t launch(int M, int K, int V, int m_tiles, int own, int height, const void *hidden, const void *weight, unsigned long long *keys, hipStream_t s) {
+  using F = Few<MT, WT>;
+  auto kern = m_tiles == 1 ? lmhead_few_kernel<MT, WT, true> : lmhead_few_kernel<MT, WT, false>;
+  hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)F::kLds);
+  if (e != hipSuccess) return e;
+  const int groups = (V + own - 1) / own;
+  kern<<<(groups + kXcds - 1) / kXcds * kXcds * m_tiles, 512, F::kLds, s>>>(M, K, V, m_tiles, own, height, (const u32x4 *)hidden, (const u32x4 *)weight, keys);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+// How M hidden rows are tiled: 64 or 128 rows a tile; none where the tiles of lmhead_mfma.hip are ahead.  One tile of up to
+// 64.  From there to 128 one of 128 where a run is long; with short ones a workgroup reads mostly hidden rows, and two tiles of
+// 64 are ahead (us, one tile and two: 24576 x 2048 37.5 and 33.2, x 4096 61.5 and 57.9; 32000 x 3584 58.2 and 61.3).  Up to
+// 256 rows tiles of 64 with short runs (256 rows, this way and 256-row tiles: 8192 x 2048 24.6 and 29.5, 16384 x 2048 33.1 and
+// 32.2), two tiles of 128 where a run is one tile and no shorter than 161 (24576 x 4096 68 and 85, 32000 x 3584 72 and 81; 16384
+// x 2048 35 and 32, 50000 x 3584 118 and 94).
+static int few_height(int M, int V) {
+  auto run = [&](int rows) {
+    const int groups = 32 / ((M + rows - 1) / rows) * kXcds;
+    return (V + groups - 1) / groups;
+  };
+  if (M <= 64) return 64;
+  if (M <= 128) return run(64) <= 208 ? 64 : 128;
+  if (M > 256) return 0;
+  if (run(64) <= 192) return 64;
+  return run(128) > 160 && run(128) <= 320 ? 128 : 0;
+}
+bool lmhead_few_takes(int32_t M, int32_t V) { return few_height(M, V) != 0; }
+
+hipError_t launch_lmhead_few(int32_t M, int32_t K, int32_t V, const void *hidden, const void *weight,
+                             unsigned long long *keys, hipStream_t s) {
+  const int rows = few_height(M, V);
+  if (!rows) return hipErrorInvalidValue;
+  const int m_tiles = (M + rows - 1) / rows, groups = 32 / m_tiles * kXcds;
+  const int own = ((V + groups - 1) / groups + 15) / 16 * 16;
+  const int n = (own + 64 * kMostTall - 1) / (64 * kMostTall), height = ((own + n - 1) / n + 15) / 16 * 16;
+#define HB_FEW(MT_, WT_) \
+  case WT_: return launch<MT_, WT_>(M, K, V, m_tiles, own, height, hidden, weight, keys, s)
+#define HB_FEW_ALL(MT_)       \
+  switch ((height + 63) / 64) { \
+    HB_FEW(MT_, 1);           \
+    HB_FEW(MT_, 2);           \
+    HB_FEW(MT_, 3);           \
+    HB_FEW(MT_, 4);           \
+    HB_FEW(MT_, 5);           \
+    default: return hipErrorInvalidValue; \
+  }
+  if (rows == 64) HB_FEW_ALL(1);
+  HB_FEW_ALL(2);
+#undef HB_FEW_ALL
+#undef HB_FEW
+}
+
+}  // namespace hb

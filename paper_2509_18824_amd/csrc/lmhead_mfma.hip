@@ -19,6 +19,8 @@
 // 826 us, 1024 rows 940 -> 839, 768 rows 752 -> 667 against 32x32x16 with one barrier per K step.
 // Workgroups go in lockstep so that shared tiles are fetched from HBM once.
 //
+// Up to 128 rows, and some calls of up to 256, go to lmhead_few.hip.
+//
 // Grid: persistent workgroups, one per CU, in groups that walk the vocabulary tiles in lockstep
 // (one hidden tile per member) on one XCD.
 #include "mfma_gemm_tile.h"
@@ -182,6 +184,7 @@ bool lmhead_mfma_supports(int32_t dtype, int32_t M, int32_t K, int32_t V) {
 
 hipError_t launch_lmhead_mfma(int32_t M, int32_t K, int32_t V, const void *hidden, const void *weight,
                               unsigned long long *keys, hipStream_t s) {
+  if (lmhead_few_takes(M, V)) return launch_lmhead_few(M, K, V, hidden, weight, keys, s);
   // hidden tile height: the multiple of 64 (up to 256) that wastes the fewest padded rows,
   // preferring the taller tile on ties (fewer re-reads of the weight tile)
   int best_mt = 4;
@@ -192,16 +195,13 @@ hipError_t launch_lmhead_mfma(int32_t M, int32_t K, int32_t V, const void *hidde
     if (best_rows < 0 || rows < best_rows) { best_rows = rows; best_mt = mt; }
   }
   // One taller tile on a few CUs waits for its own K steps (950 ns each with 128 rows, 550 with 64), not for memory:
-  // 64-row tiles as long as one round of CUs holds them all (32 per XCD).  Taller -> 64-row tiles, us: 128 rows x 4096 x
-  // 4096 62 -> 50, x 24576 71 -> 63, x 32768 79 -> 73; 192 rows x 4096 x 8192 72 -> 51; 256 rows x 4096 x 16384 84 -> 57.
-  // With another round they lose (128 rows x 4096 x 36000 78 and 112).
+  // 64-row tiles as long as one round of CUs holds them all (32 per XCD).  Taller -> 64-row tiles, us: 192 rows x 4096 x 8192
+  // 72 -> 51; 256 rows x 4096 x 16384 84 -> 57.  With another round they lose (128 rows x 4096 x 36000 78 and 112).
   const int v_tiles = (V + TV - 1) / TV;
   if (M <= 64 * best_mt && (v_tiles + kXcds - 1) / kXcds * ((M + 63) / 64) <= 32) best_mt = 1;
   switch (best_mt) {
-    case 1: return M <= 64 * 1 ? launch<1, true>(M, K, V, hidden, weight, keys, s)
-                            : launch<1, false>(M, K, V, hidden, weight, keys, s);
-    case 2: return M <= 64 * 2 ? launch<2, true>(M, K, V, hidden, weight, keys, s)
-                            : launch<2, false>(M, K, V, hidden, weight, keys, s);
+    case 1: return launch<1, false>(M, K, V, hidden, weight, keys, s);  // one tile of up to 128 rows is lmhead_few.hip's
+    case 2: return launch<2, false>(M, K, V, hidden, weight, keys, s);
     case 3: return M <= 64 * 3 ? launch<3, true>(M, K, V, hidden, weight, keys, s)
                             : launch<3, false>(M, K, V, hidden, weight, keys, s);
     default: return M <= 64 * 4 ? launch<4, true>(M, K, V, hidden, weight, keys, s)

@@ -10,8 +10,8 @@
 // where they took 211, 60 rows 171 and 186 (without matrix instructions 203 and 185): hence the tallest tile that LDS holds
 // (128 rows: tiles of 304 against 208, 183 and 199 us), and all 256 CUs at work instead of the 200 that shared 594 tiles
 // of 256 rows evenly.  us, tiles of 256 rows one by one and this: 152064 x 3584, 8 rows 172 -> 165, 60 186 -> 168,
-// 128 210 -> 183; x 4096, 8 rows 231 -> 192, 128 252 -> 215; 100000 x 2048, 8 rows 95 -> 86; 4096 x 4096, 64 rows 52 -> 32,
-// 128 50 -> 32; 64000 x 3584, 128 rows, where both have the same tiles, 83 -> 84.
+// 128 210 -> 183; x 4096, 8 rows 231 -> 192, 128 252 -> 215; 100000 x 2048, 8 rows 95 -> 86; 4096 x 4096, 64 rows 52 -> 30,
+// 128 50 -> 29; 64000 x 3584, 128 rows, where both have the same tiles, 83 -> 84.
 //
 // Two wavefronts of a SIMD alternate between operands and matrix instructions as in mfma_gemm_tile.inc.
 #include "mfma_gemm_tile.h"
@@ -30,7 +30,11 @@ struct Few {
   static constexpr int kRows = 64 * WT, kTok = 64 * MT;    // of a tile: vocabulary rows, hidden rows
   static constexpr int kW = kRows / 8 / kWaves, kH = kTok / 8 / kWaves;  // loads of a wavefront per K step
   static constexpr int kWStage = kRows * CH, kHStage = kTok * CH;        // 16-byte pieces
-  static constexpr int kRing = 3, kHRing = MT == 1 ? 3 : 2;  // LDS stages of the weights and of the hidden rows
+  // LDS stages of the weights and of the hidden rows: four where they fit (hidden rows one step ahead, in two stages, made
+  // every step of a short tile wait: 128 rows x 4096 x 8192 36.6 us, with four 30.5; x 3584 x 32000 58.0 and 52.4; five or six
+  // the same or 4 % slower).  The tallest tile with 128 hidden rows has three and two.
+  static constexpr int kFit = 160 / (8 * (WT + MT));
+  static constexpr int kRing = kFit < 3 ? 3 : kFit < 4 ? kFit : 4, kHRing = kFit < 3 ? 2 : kRing;
   static constexpr bool kSame = kHRing == kRing;             // both tiles of a step are fetched together
   static constexpr size_t kLds = (size_t)(kRing * kWStage + kHRing * kHStage) * 16;
   static_assert(kLds <= 160 * 1024, "more LDS than a CU has");
@@ -114,7 +118,7 @@ __global__ __launch_bounds__(512) void lmhead_few_kernel(int M, int K, int V, in
     best[j] = -__builtin_huge_valf();
     best_v[j] = -1;
   }
-  // Phases as in mfma_gemm_tile.inc, steps counted through all tiles: loads two steps ahead (hidden rows in two stages one).
+  // Phases as in mfma_gemm_tile.inc, steps counted through all tiles: loads as far ahead as there are stages, less one.
   const bool late = wave >= kWaves / 2;
   int cur = 0, w_free = 0, h_slot = 0;
 #pragma unroll
@@ -123,7 +127,7 @@ __global__ __launch_bounds__(512) void lmhead_few_kernel(int M, int K, int V, in
     issue_w(t);
     ++w_free;
   }
-  auto landed = [&] { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(F::kSame ? F::kW + F::kH : F::kW) : "memory"); };
+  auto landed = [&] { asm volatile("s_waitcnt vmcnt(%0)" ::"n"((F::kRing - 2) * (F::kSame ? F::kW + F::kH : F::kW)) : "memory"); };
   auto phase = [&] { asm volatile("s_barrier" ::: "memory"); };
   landed();
   phase();
@@ -233,8 +237,9 @@ hipError_t launch(int M, int K, int V, int m_tiles, int own, int height, const v
 
 // How M hidden rows are tiled: 64 or 128 rows a tile; none where the tiles of lmhead_mfma.hip are ahead.  One tile of up to
 // 64.  From there to 128 one of 128 where a run is long; with short ones a workgroup reads mostly hidden rows, and two tiles of
-// 64 are ahead (us, one tile and two: 24576 x 2048 37.5 and 33.2, x 4096 61.5 and 57.9; 32000 x 3584 58.2 and 61.3).  Up to
-// 256 rows tiles of 64 with short runs (256 rows, this way and 256-row tiles: 8192 x 2048 24.6 and 29.5, 16384 x 2048 33.1 and
+// 64 are ahead (us, one tile and two: 24576 x 2048 37.5 and 33.2, x 4096 61.5 and 57.9; 32000 x 3584 58.2 and 61.3, with three stages of the weights and two or three
+// of the hidden rows).  Up to
+// 256 rows tiles of 64 with short runs (256 rows, this way and 256-row tiles: 8192 x 2048 22.8 and 29.5, 16384 x 2048 33.1 and
 // 32.2), two tiles of 128 where a run is one tile and no shorter than 161 (24576 x 4096 68 and 85, 32000 x 3584 72 and 81; 16384
 // x 2048 35 and 32, 50000 x 3584 118 and 94).
 static int few_height(int M, int V) {

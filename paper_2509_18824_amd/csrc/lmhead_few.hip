@@ -10,8 +10,8 @@
 // where they took 211, 60 rows 171 and 186 (without matrix instructions 203 and 185): hence the tallest tile that LDS holds
 // (128 rows: tiles of 304 against 208, 183 and 199 us), and all 256 CUs at work instead of the 200 that shared 594 tiles
 // of 256 rows evenly.  us, tiles of 256 rows one by one and this: 152064 x 3584, 8 rows 172 -> 165, 60 186 -> 168,
-// 128 210 -> 183; x 4096, 8 rows 231 -> 192, 128 252 -> 215; 100000 x 2048, 8 rows 95 -> 86; 4096 x 4096, 64 rows 52 -> 30,
-// 128 50 -> 29; 64000 x 3584, 128 rows, where both have the same tiles, 83 -> 84.
+// 128 210 -> 183; x 4096, 8 rows 231 -> 190, 128 252 -> 201; 100000 x 2048, 8 rows 95 -> 68; 32000 x 3584, 64 rows 58 -> 45; 64000 x 3584, 128
+// rows, where both have the same tiles, 83 -> 84.
 //
 // Two wavefronts of a SIMD alternate between operands and matrix instructions as in mfma_gemm_tile.inc.
 #include "mfma_gemm_tile.h"
@@ -31,8 +31,7 @@ struct Few {
   static constexpr int kW = kRows / 8 / kWaves, kH = kTok / 8 / kWaves;  // loads of a wavefront per K step
   static constexpr int kWStage = kRows * CH, kHStage = kTok * CH;        // 16-byte pieces
   // LDS stages of the weights and of the hidden rows: four where they fit (hidden rows one step ahead, in two stages, made
-  // every step of a short tile wait: 128 rows x 4096 x 8192 36.6 us, with four 30.5; x 3584 x 32000 58.0 and 52.4; five or six
-  // the same or 4 % slower).  The tallest tile with 128 hidden rows has three and two.
+  // every step of a short tile wait: 128 rows x 3584 x 32000 58.0 us, with four 52.4; five or six the same or slower).  The tallest tile with 128 hidden rows has three and two.
   static constexpr int kFit = 160 / (8 * (WT + MT));
   static constexpr int kRing = kFit < 3 ? 3 : kFit < 4 ? kFit : 4, kHRing = kFit < 3 ? 2 : kRing;
   static constexpr bool kSame = kHRing == kRing;             // both tiles of a step are fetched together
@@ -90,12 +89,17 @@ __global__ __launch_bounds__(512) void lmhead_few_kernel(int M, int K, int V, in
   for (int i = 0; i < F::kW; ++i) w_off[i] = (wave + kWaves * i) * 8 * row_bytes + mine;
 #pragma unroll
   for (int i = 0; i < F::kH; ++i) h_off[i] = (wave + kWaves * i) * 8 * row_bytes + mine;
+  // Rows a multiple of 4 KB apart meet on few memory channels where everybody reads the same columns: the XCD's runs begin
+  // at K steps of their own (us: 2048 x 100000, 8 rows 86 -> 68, 128 rows 95 -> 81; 4096 x 152064 201 -> 190 and 221 -> 201;
+  // with rows of 7 KB no difference).
+  const int k0 = row_bytes % 4096 == 0 ? (int)((unsigned)(slot / m_tiles * 7) % (unsigned)k_steps) : 0;
+  auto column = [&](int k) { return (k + k0 < k_steps ? k + k0 : k + k0 - k_steps) * (BK * 2); };
   int w_at = first, w_k = 0, h_k = 0;  // what is fetched next; past the last step that step again: the waits count loads
   auto issue_w = [&](int slot) {
     const u32x4 *from = weight + (size_t)w_at * (row_bytes / 16);
     const int bytes = __builtin_amdgcn_readfirstlane(min(height, end - w_at)) * row_bytes;
 #pragma unroll
-    for (int i = 0; i < F::kW; ++i) rows_to_lds<ALONE ? 2 : 0>(from, bytes, lw + slot * F::kWStage + (wave + kWaves * i) * 64, w_off[i], w_k * (BK * 2));
+    for (int i = 0; i < F::kW; ++i) rows_to_lds<ALONE ? 2 : 0>(from, bytes, lw + slot * F::kWStage + (wave + kWaves * i) * 64, w_off[i], column(w_k));
     if (++w_k == k_steps) {
       if (w_at + height < end) {
         w_at += height;
@@ -107,7 +111,7 @@ __global__ __launch_bounds__(512) void lmhead_few_kernel(int M, int K, int V, in
   };
   auto issue_h = [&](int slot) {
 #pragma unroll
-    for (int i = 0; i < F::kH; ++i) rows_to_lds<0>(hidden, m_rows * row_bytes, lh + slot * F::kHStage + (wave + kWaves * i) * 64, h_off[i], h_k * (BK * 2));
+    for (int i = 0; i < F::kH; ++i) rows_to_lds<0>(hidden, m_rows * row_bytes, lh + slot * F::kHStage + (wave + kWaves * i) * 64, h_off[i], column(h_k));
     h_k = h_k + 1 == k_steps ? 0 : h_k + 1;
   };
 
@@ -235,23 +239,15 @@ hipError_t launch(int M, int K, int V, int m_tiles, int own, int height, const v
 
 }  // namespace
 
-// How M hidden rows are tiled: 64 or 128 rows a tile; none where the tiles of lmhead_mfma.hip are ahead.  One tile of up to
-// 64.  From there to 128 one of 128 where a run is long; with short ones a workgroup reads mostly hidden rows, and two tiles of
-// 64 are ahead (us, one tile and two: 24576 x 2048 37.5 and 33.2, x 4096 61.5 and 57.9; 32000 x 3584 58.2 and 61.3, with three stages of the weights and two or three
-// of the hidden rows).  Up to
-// 256 rows tiles of 64 with short runs (256 rows, this way and 256-row tiles: 8192 x 2048 22.8 and 29.5, 16384 x 2048 33.1 and
-// 32.2), two tiles of 128 where a run is one tile and no shorter than 161 (24576 x 4096 68 and 85, 32000 x 3584 72 and 81; 16384
-// x 2048 35 and 32, 50000 x 3584 118 and 94).
+// How M hidden rows are tiled: 64 or 128 rows a tile; none where the tiles of lmhead_mfma.hip stay.  With up to 16384
+// vocabulary rows a workgroup would read mostly hidden rows, and 128 of them take up to 1.2 times as long as 64 (x 4096, 16384
+// rows: 42 and 36 us), which those tiles avoid (60 and 58).  Two hidden tiles of 128 where a run is one tile (256 rows, us,
+// this way and 256-row tiles: 24576 x 4096 66 and 85, 32000 x 3584 72 and 81; several tiles, 50000 x 3584, 118 and 94).
 static int few_height(int M, int V) {
-  auto run = [&](int rows) {
-    const int groups = 32 / ((M + rows - 1) / rows) * kXcds;
-    return (V + groups - 1) / groups;
-  };
+  if (V <= 16384 || M > 256) return 0;
   if (M <= 64) return 64;
-  if (M <= 128) return run(64) <= 208 ? 64 : 128;
-  if (M > 256) return 0;
-  if (run(64) <= 192) return 64;
-  return run(128) > 160 && run(128) <= 320 ? 128 : 0;
+  const int groups = 32 / ((M + 127) / 128) * kXcds, run = (V + groups - 1) / groups;
+  return M <= 128 || (run > 160 && run <= 64 * kMostTall) ? 128 : 0;
 }
 bool lmhead_few_takes(int32_t M, int32_t V) { return few_height(M, V) != 0; }
 
@@ -260,8 +256,11 @@ hipError_t launch_lmhead_few(int32_t M, int32_t K, int32_t V, const void *hidden
   const int rows = few_height(M, V);
   if (!rows) return hipErrorInvalidValue;
   const int m_tiles = (M + rows - 1) / rows, groups = 32 / m_tiles * kXcds;
-  const int own = ((V + groups - 1) / groups + 15) / 16 * 16;
-  const int n = (own + 64 * kMostTall - 1) / (64 * kMostTall), height = ((own + n - 1) / n + 15) / 16 * 16;
+  // Runs of several tiles in whole 16 rows (128 rows x 3584 x 152064, 608 a run 183 us, 594 185), of one tile as they come
+  // (64000: 250 a run 77.0, 256 77.5).
+  int own = (V + groups - 1) / groups;
+  if (own > 64 * kMostTall) own = (own + 15) / 16 * 16;
+  const int n = (own + 64 * kMostTall - 1) / (64 * kMostTall), height = ((own + n - 1) / n + 7) / 8 * 8;  // whole loads
 #define HB_FEW(MT_, WT_) \
   case WT_: return launch<MT_, WT_>(M, K, V, m_tiles, own, height, hidden, weight, keys, s)
 #define HB_FEW_ALL(MT_)       \

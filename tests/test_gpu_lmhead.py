@@ -66,13 +66,13 @@ def test_small_shapes(step, dtype, M, K, V):
     _check(hidden, weight, ids, mx)
 
 
-@pytest.mark.parametrize("M,K,V", [(1, 64, 17), (64, 128, 4096), (64, 64, 4097), (60, 192, 81920), (8, 64, 81921), (61, 64, 152064),
-                                   (128, 64, 152065), (100, 128, 164000), (128, 64, 26624), (65, 64, 26625), (70, 192, 900),
-                                   (192, 64, 15360), (129, 64, 15361), (256, 128, 12288), (193, 64, 12289), (256, 64, 20481),
+@pytest.mark.parametrize("M,K,V", [(1, 64, 16385), (64, 128, 16384), (64, 64, 20480), (60, 192, 81920), (8, 64, 81921),
+                                   (61, 64, 152064), (128, 64, 152065), (100, 128, 164000), (65, 64, 36864), (70, 192, 17000),
+                                   (33, 4096, 16400), (128, 2048, 24600), (192, 64, 20480), (129, 64, 20481), (256, 128, 24600),
                                    (255, 64, 40960), (256, 64, 40961)])
 def test_runs_of_vocabulary_rows(step, M, K, V):
     """Up to 128 rows, and some calls of up to 256, a workgroup has a run of vocabulary rows for itself: runs that are missing,
-    ragged, one tile, one row more, several tiles; both sides of the lines between one, two and four hidden tiles.  The
+    ragged, one tile, one row more, several tiles; both sides of the lines; columns in another order (K a multiple of 2048).  The
     first and the last row of the vocabulary and the rows at a run's ends hold equal largest logits for some hidden rows."""
     hidden, weight = W.make_lmhead_inputs(M + V, M, K, V, dtype="bf16", w_std=0.05)
     rng = np.random.default_rng(M + V)

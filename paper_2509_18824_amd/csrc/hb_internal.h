@@ -127,6 +127,13 @@ hipError_t launch_proj_stream(StreamKind kind, int32_t M, int32_t K, int32_t N, 
 struct FewPlan {
   int32_t rows, ks;
 };
+// Rows and parts of K a multiple of 4 KB apart meet on few memory channels while everybody reads the same columns: there
+// the workgroups begin at K steps of their own.  Few weights lose 1 to 2 % by it, since the tokens' columns are shared less
+// (24 tokens, 6144 x 1216 9.52 and 9.68 us), from some 30 MB on they gain (2048 x 8576 12.9 -> 12.3); low tiles of rows an odd
+// multiple of 4 KB apart do not (128 tokens, rotary 14336 x 3072 in seven parts 26.5 and 28.5).
+inline bool few_turns(int32_t K, int32_t N, const FewPlan &p) {
+  return K / p.ks % 2048 == 0 && (p.ks == 1 || K % 4096 == 0 || p.rows >= 8) && (int64_t)K * N >= 15000000;
+}
 hipError_t launch_proj_few(StreamKind kind, const FewPlan &p, int32_t M, int32_t K, int32_t N, const void *hidden,
                            const void *weight, const StreamArgs &sa, float *part, int32_t v_pad, int32_t m_pad, hipStream_t s);
 

@@ -13,7 +13,9 @@
 // of the same features), so that both members are one lane's own accumulators.
 //
 // What bounds it: memory where the weights are many, else the CU's path from L2 (64 bytes a clock for 16 R +
-// 128 rows a K step) and the time until the first tile is there.
+// 128 rows a K step) and the time until the first tile is there.  Rows a multiple of 4 KB apart also met on few memory
+// channels until the workgroups walked K from steps of their own (few_turns; us before and now: gated 64 tokens 4096 x 32768
+// 62 and 44, 128 tokens 64 and 55, 24 tokens 4096 x 16384 37 and 25; 64 tokens 16384 x 2048 22 and 19.6).
 #include "hb_internal.h"
 
 namespace hb {
@@ -45,10 +47,10 @@ struct Shape {
   static constexpr size_t kLdsBytes = (size_t)kStages * kLoads * 1024;
 };
 
-template <Kind KIND, int R, int TOK, int KSP>
-__global__ __launch_bounds__(512) void proj_few_kernel(int M, int K, int V, int ks, bool uncached, int v_pad, int m_pad,
-                                                       const u32x4 *__restrict__ hidden, const u32x4 *__restrict__ weight,
-                                                       StreamArgs sa, float *__restrict__ part) {
+// TURN: workgroups begin at stages of their own
+template <Kind KIND, int R, int TOK, int KSP, bool TURN>
+__device__ __forceinline__ void few_tile(int M, int K, int V, int ks, bool uncached, int v_pad, int m_pad, const u32x4 *__restrict__ hidden,
+                                         const u32x4 *__restrict__ weight, const StreamArgs &sa, float *__restrict__ part) {
   using Sh = Shape<R, TOK, KSP>;
   constexpr int SUB = TOK == 128 ? 2 : 1;  // 32-k sub-steps of a K step that a wavefront takes
   extern __shared__ u32x4 lds[];
@@ -92,8 +94,10 @@ __global__ __launch_bounds__(512) void proj_few_kernel(int M, int K, int V, int 
     src[i] = base + (size_t)kfrom * (K / 8 / ks) + kk * 8 + ((lane & 7) ^ r8);
   }
   const bool full = Sh::kRest == 0 || wave < Sh::kRest;
+  const int turn = TURN ? (int)((blockIdx.x >> 3) % (unsigned)stages) : 0;
   auto issue = [&](int st, int slot) {
     st = st < stages ? st : stages - 1;  // past the end the last stage again: the waits count loads
+    if (TURN) st = st + turn < stages ? st + turn : st + turn - stages;
 #pragma unroll
     for (int i = 0; i < Sh::kMost; ++i) {
       if (i == Sh::kMost - 1 && !full) break;
@@ -230,15 +234,35 @@ __global__ __launch_bounds__(512) void proj_few_kernel(int M, int K, int V, int 
 }
 
 template <Kind KIND, int R, int TOK, int KSP>
+__global__ __launch_bounds__(512) void proj_few_kernel(int M, int K, int V, int ks, bool uncached, int v_pad, int m_pad,
+                                                       const u32x4 *__restrict__ hidden, const u32x4 *__restrict__ weight,
+                                                       StreamArgs sa, float *__restrict__ part) {
+  few_tile<KIND, R, TOK, KSP, false>(M, K, V, ks, uncached, v_pad, m_pad, hidden, weight, sa, part);
+}
+// A kernel of its own for those that turn: asked for in the one, it cost short calls 1 to 2 %.
+struct Turned {};
+template <Kind KIND, int R, int TOK, int KSP>
+__global__ __launch_bounds__(512) void proj_few_kernel(int M, int K, int V, int ks, bool uncached, int v_pad, int m_pad,
+                                                       const u32x4 *__restrict__ hidden, const u32x4 *__restrict__ weight,
+                                                       StreamArgs sa, float *__restrict__ part, Turned) {
+  few_tile<KIND, R, TOK, KSP, true>(M, K, V, ks, uncached, v_pad, m_pad, hidden, weight, sa, part);
+}
+
+template <Kind KIND, int R, int TOK, int KSP>
 hipError_t launch(int M, int K, int V, int ks, int v_pad, int m_pad, const void *hidden, const void *weight, const StreamArgs &sa,
                   float *part, hipStream_t s) {
   using Sh = Shape<R, TOK, KSP>;
   const int tiles = KIND == kGlu ? (V / 2 + 8 * R - 1) / (8 * R) : (V + 16 * R - 1) / (16 * R);
-  auto kern = proj_few_kernel<KIND, R, TOK, KSP>;
-  hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)Sh::kLdsBytes);
-  if (e != hipSuccess) return e;
-  kern<<<tiles * ks, 512, Sh::kLdsBytes, s>>>(M, K, V, ks, (int64_t)K * V >= kUncached, v_pad, m_pad, (const u32x4 *)hidden, (const u32x4 *)weight, sa, part);
-  return hipGetLastError();
+  const bool uncached = (int64_t)K * V >= kUncached;
+  auto run = [&](auto kern, auto... turned) {
+    const hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)Sh::kLdsBytes);
+    if (e != hipSuccess) return e;
+    kern<<<tiles * ks, 512, Sh::kLdsBytes, s>>>(M, K, V, ks, uncached, v_pad, m_pad, (const u32x4 *)hidden, (const u32x4 *)weight, sa, part, turned...);
+    return hipGetLastError();
+  };
+  using Whole = void (*)(int, int, int, int, bool, int, int, const u32x4 *, const u32x4 *, StreamArgs, float *);
+  using Turning = void (*)(int, int, int, int, bool, int, int, const u32x4 *, const u32x4 *, StreamArgs, float *, Turned);
+  return few_turns(K, V, {R, ks}) ? run((Turning)proj_few_kernel<KIND, R, TOK, KSP>, Turned{}) : run((Whole)proj_few_kernel<KIND, R, TOK, KSP>);
 }
 
 template <Kind KIND, int TOK>

@@ -649,8 +649,11 @@ hipError_t launch_pair(StreamKind kind, const PairPlan &p, int M, int K, int V, 
 // 3584 x 3584 10.8 / 11.8 and 10.6 / 11.0; 14336 x 4096 26 / 32 and 34 / 35, in parts 28; 8192 x 8192 29 / 33 and 37; 3584 x
 // 16384 28 / 30 and 24; gated 3584 x 37888 50 / 54 and 45, 4096 x 28672 44 / 47 and 53 / 54): the one expected to be faster,
 // within 0.3 % of the faster one in the mean of the 2400 calls, and more than 3 % slower in 60 of them.
-// Parts of K of 4 KB in tiles of 96 or 128 rows lose to the split into 256-row tiles (32 / 128 tokens, 8192 x 8192 41 / 45 and
-// 33 / 41, 8192 x 7168 35 / 40 and 30 / 37, 14336 x 4608 38 / 43 and 33 / 41); other parts do not.
+// Gated rows a multiple of 4 KB apart, more than 150 MB of them, are few rows' (24 tokens, by the stream and by few rows: 4096 x 28672
+// 46 and 43 us, x 32768 53 and 43, 8192 x 28672 95 and 82).
+// Parts of K of 4 KB in tiles of 96 or 128 rows lose to the split into 256-row tiles (32 / 64 tokens, 8192 x 8192 36.6 / 36.1 and
+// 33.3 / 34.4, 8192 x 7168 33.9 / 31.8 and 30.2 / 31.0; 128 tokens 14336 x 4608 46 and 41), except eight of them (64 / 128
+// tokens, 16384 x 4096 30 / 36 and 34 / 42); other parts do not.
 enum class Way { kStream, kFew, kPair, kTiles };
 struct Ways {
   FewPlan few;
@@ -666,8 +669,9 @@ Way way_of(int M, int K, int V, StreamKind kind, const float *part, Ways *ways) 
   if (part) *plan = split_plan(M, K, V);
   *few = few_plan(M, K, V, kind, split_bytes(*plan, M, V));
   if (few->rows) {
-    if (stream && stream_us(M, K, V) < few_us(*few, M, K, V, kind)) return Way::kStream;
-    return few->ks > 1 && K / few->ks == 2048 && (few->rows == 6 || few->rows == 8) ? Way::kTiles : Way::kFew;
+    const bool turned = kind == StreamKind::kGlu && K > 2048 && few_turns(K, V, *few) && (int64_t)K * V >= 75000000;
+    if (stream && !turned && stream_us(M, K, V) < few_us(*few, M, K, V, kind)) return Way::kStream;
+    return few->ks > 1 && few->ks < 8 && K / few->ks == 2048 && (few->rows == 6 || few->rows == 8) ? Way::kTiles : Way::kFew;
   }
   if (stream && proj_stream_pays(K, V, plan->ks > 1)) return Way::kStream;
   ways->pair = pair_plan(M, K, V, kind, *plan);

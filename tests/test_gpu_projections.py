@@ -185,6 +185,19 @@ def test_gated_silu_projection_of_all_tokens_at_once(hb, T, K, F):
         test_gated_silu_projection(hb, T, K, F, ws)
 
 
+# Rows or parts of K a multiple of 4 KB apart, 15 million weights and more: the workgroups begin at K steps of their own.  One
+# and several K steps of a stage, whole and in parts, one token over; the sizes below the line stand in the tests above.
+@pytest.mark.parametrize("T,K,N,ws", [(24, 2048, 7328, False), (100, 4096, 4100, False), (33, 6144, 2564, False), (128, 8192, 4096, True),
+                                      (64, 16384, 1028, True), (17, 12288, 6272, True)])
+def test_output_projection_of_rows_that_meet_on_few_channels(hb, T, K, N, ws):
+    _out_case(hb, T, K, N, T % 2 == 1, ws)
+
+
+@pytest.mark.parametrize("T,K,F", [(17, 2048, 4100), (40, 6144, 2052), (128, 4096, 4100), (64, 8192, 1028)])
+def test_gated_projection_of_rows_that_meet_on_few_channels(hb, T, K, F):
+    test_gated_silu_projection(hb, T, K, F, False)
+
+
 def _kernels(call):
     """Names of the projection kernels that a call runs, each as it is in the source with its template arguments."""
     import re

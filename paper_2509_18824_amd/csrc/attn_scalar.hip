@@ -7,7 +7,8 @@
 // What bounds it at the sizes it is used for is latency: memory round trips in a row and chains of
 // dependent instructions, not bytes.  The four wavefronts of a workgroup deal out blocks of 64 keys;
 // a block is a handful of round trips (page ids, K, the V rows 16 at a time) and one softmax update
-// whatever the number of keys in it.  4 nodes x 4 heads of 64 over 256 float32 positions: 12 us;
+// whatever the number of keys in it.  4 nodes x 4 heads of 64 over 256 float32 positions: 12 us (7.7 by the kernel of few
+// workgroups below);
 // one wavefront that took the keys one by one, each with a sum across lanes and two exponentials,
 // 138 us.
 #include "hb_internal.h"
@@ -250,6 +251,176 @@ __global__ __launch_bounds__(kThreads, E == 4 || (E == 1 && sizeof(T) == 2) ? 4 
   }
 }
 
+// ---- float32 rows of up to 64 values in one round of CUs: as few memory round trips in a row as there can be --------
+// Four nodes or forty leave most of the chip idle, and what a workgroup does is wait: for the sequence's bounds, the page
+// ids, K, four times for 16 rows of V, and in its last wavefront for the parents and the tree's keys after all that.  Here
+// the bounds of all sequences come in one load, K and V of a block of 64 keys are in flight together (a load of V is four
+// rows, four values a lane), the prefix has seven wavefronts and the tree one of its own.  That takes 200 registers a lane
+// and a CU per workgroup, so only what fits the CUs once is taken (kEagerMost): 4 nodes x 4 heads of 64 over 256 positions
+// 12.0 -> 7.7 us, 8 nodes over 1024 15.5 -> 11.0.
+constexpr int kEagerWaves = 7, kEagerThreads = 64 * (kEagerWaves + 1);
+constexpr int kEagerMost = 320;  // workgroups; 288 17.7 -> 13.3 us, 480 14.7 and 15.0
+
+struct EagerSoftmax {
+  float m, l;  // reference exponent; this lane's share of the sum
+  f32x4 acc;   // of values 4 (lane % 16) ..., over the keys whose place in their block is lane / 16 more than a multiple of 4
+};
+
+// Up to 64 keys, one per lane, as absorb_keys takes them.
+__device__ __forceinline__ void absorb_eagerly(EagerSoftmax &st, const float *q_lds, const float *k, const float *v, size_t off,
+                                               unsigned long long live, int D, int lane, float scale) {
+  if (live == 0) return;
+  const bool mine = (live >> lane) & 1;
+  const int d4 = min(4 * (lane & 15), D - 4), g = lane >> 4;
+  const unsigned long long live_g = live >> g;
+  f32x4 kx[16], vx[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i)
+    if (4 * i < D) kx[i] = *reinterpret_cast<const f32x4 *>(k + off + 4 * i);
+  const uint32_t off_lo = (uint32_t)off, off_hi = (uint32_t)(off >> 32);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    // a lane without a key has the address of one, and what it loads is not used
+    const size_t o = (size_t)(uint32_t)__shfl((int)off_lo, 4 * i + g, 64) | ((size_t)(uint32_t)__shfl((int)off_hi, 4 * i + g, 64) << 32);
+    vx[i] = *reinterpret_cast<const f32x4 *>(v + o + d4);
+  }
+  f32x4 part = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < 16; ++i)
+    if (4 * i < D) {
+      const f32x4 qv = *reinterpret_cast<const f32x4 *>(q_lds + 4 * i);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) part[e] = fmaf(qv[e], kx[i][e], part[e]);
+    }
+  const float s = mine ? ((part[0] + part[1]) + (part[2] + part[3])) * scale : -__builtin_huge_valf();
+  const float m_new = fmaxf(st.m, wave_max(s));
+  // scores of -inf weigh nothing, also where there is nothing else yet to weigh them against
+  const float m_ref = fmaxf(m_new, -__FLT_MAX__);
+  const float corr = expf(st.m - m_ref);  // exp(-inf) = 0 on the first keys
+  const float p = mine ? expf(s - m_ref) : 0.f;
+  st.l = st.l * corr + p;
+  st.m = m_new;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) st.acc[e] *= corr;
+#pragma unroll
+  for (int i = 0; i < 16; ++i)
+  {
+    const float w = __shfl(p, 4 * i + g, 64);
+    const bool has = (live_g >> (4 * i)) & 1;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) st.acc[e] = fmaf(w, has ? vx[i][e] : 0.f, st.acc[e]);
+  }
+}
+
+__global__ __launch_bounds__(kEagerThreads) void attn_scalar_eager_kernel(
+    hb_attn_desc d, int splits, int chunk_tokens, const float *__restrict__ q, const float *__restrict__ k_tree,
+    const float *__restrict__ v_tree, const float *__restrict__ k_pool, const float *__restrict__ v_pool,
+    const int32_t *__restrict__ block_table, const int32_t *__restrict__ prefix_len,
+    const int32_t *__restrict__ node_offset, const int32_t *__restrict__ parent, float *__restrict__ out,
+    float *__restrict__ lse, float *__restrict__ part_o, float *__restrict__ part_ml, ClearArgs clear) {
+  if (blockIdx.y == 0) clear_words(clear, blockIdx.x, gridDim.x, threadIdx.x, kEagerThreads);
+  __shared__ __align__(16) float q_lds[64];
+  __shared__ __align__(16) float acc_lds[kEagerWaves + 1][64];
+  __shared__ float ml_lds[kEagerWaves + 1][2];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int row = blockIdx.x;  // node * Hq + head
+  const int c = blockIdx.y;
+  const int node = row / d.num_q_heads;
+  const int h = row - node * d.num_q_heads;
+  const int g = h / (d.num_q_heads / d.num_kv_heads);
+  const int D = d.head_dim;
+
+  // the sequence of this node: the largest b with node_offset[b] <= node; at most 63 of them, one per lane
+  const int offset_mine = node_offset[min(lane, d.batch)], len_mine = prefix_len[min(lane, max(d.batch - 1, 0))];
+  if (threadIdx.x < D) q_lds[threadIdx.x] = q[(size_t)row * D + threadIdx.x];
+  const unsigned long long begun = __ballot(lane < d.batch && offset_mine <= node);
+  const int b = begun ? 63 - __builtin_clzll(begun) : 0;
+  const int n0 = __builtin_amdgcn_readlane(offset_mine, b);
+  int n_nodes = __builtin_amdgcn_readlane(offset_mine, b + 1) - n0;
+  if (n_nodes > d.max_nodes_per_tree) n_nodes = d.max_nodes_per_tree;
+  int L = __builtin_amdgcn_readlane(len_mine, b);
+  const int cap = d.max_blocks_per_seq * d.page_size;
+  L = L < 0 ? 0 : (L > cap ? cap : L);
+
+  EagerSoftmax st = {-__builtin_huge_valf(), 0.f, {0.f, 0.f, 0.f, 0.f}};
+  const int begin = c * chunk_tokens;
+  const int end = (c == splits - 1) ? L : min(L, begin + chunk_tokens);
+  const size_t page_stride = (size_t)d.num_kv_heads * d.page_size * D;
+  const int32_t *pages = block_table + (size_t)b * d.max_blocks_per_seq;
+  const int at = max(0, min(n0 + lane, d.total_nodes - 1));
+  const bool tree = wave == kEagerWaves;
+  int p0 = begin + 64 * wave, blk = 0;
+  auto place = [&] { return p0 + min(lane, end - p0 - 1); };
+  if (!tree && p0 < end) blk = pages[place() / d.page_size];
+  const int par = tree && c == 0 ? parent[at] : -1;
+  __syncthreads();
+  if (!tree) {
+    for (; p0 < end; p0 += 64 * kEagerWaves) {
+      const int n = min(64, end - p0), p = place();
+      const int page = blk < 0 ? 0 : (blk >= d.num_blocks ? d.num_blocks - 1 : blk);
+      const size_t off = (size_t)page * page_stride + ((size_t)g * d.page_size + p % d.page_size) * D;
+      const int next = p0 + 64 * kEagerWaves;
+      if (next < end) blk = pages[(next + min(lane, end - next - 1)) / d.page_size];
+      absorb_eagerly(st, q_lds, k_pool, v_pool, off, n < 64 ? (1ull << n) - 1 : ~0ull, D, lane, d.softmax_scale);
+    }
+  } else if (c == 0) {
+    // as above: up from the node to the root through the parents held by the lanes
+    unsigned long long live = 0;
+    int x = __builtin_amdgcn_readfirstlane(node - n0);
+    if (x >= n_nodes) x = -1;
+    for (int guard = 0; x >= 0 && guard < 64; ++guard) {
+      live |= 1ull << x;
+      const int px = __builtin_amdgcn_readlane(par, x);
+      x = (px < x) ? px : -1;  // a malformed parent ends the walk
+    }
+    absorb_eagerly(st, q_lds, k_tree, v_tree, ((size_t)at * d.num_kv_heads + g) * D, live, D, lane, d.softmax_scale);
+  }
+
+  // the wavefronts' results are combined through LDS; one without keys has l = 0 and no weight
+  const float l_wave = wave_sum(st.l);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    st.acc[e] += __shfl_xor(st.acc[e], 16, 64);
+    st.acc[e] += __shfl_xor(st.acc[e], 32, 64);
+  }
+  if (lane < 16) *reinterpret_cast<f32x4 *>(&acc_lds[wave][4 * lane]) = st.acc;
+  if (lane == 0) {
+    ml_lds[wave][0] = st.m;
+    ml_lds[wave][1] = l_wave;
+  }
+  __syncthreads();
+  if (wave) return;
+  float m = ml_lds[0][0], l = 0.f, o = 0.f;
+#pragma unroll
+  for (int i = 1; i <= kEagerWaves; ++i) m = fmaxf(m, ml_lds[i][0]);
+#pragma unroll
+  for (int i = 0; i <= kEagerWaves; ++i) {
+    const float li = ml_lds[i][1];
+    const float w = li == 0.f ? 0.f : expf(ml_lds[i][0] - m);
+    l += w * li;
+    o += w * acc_lds[i][lane];
+  }
+  // keys, but every score is -inf: NaN, or a chunk that is there and has no weight beside others
+  if (l == 0.f && (end > begin || (c == 0 && node - n0 < n_nodes))) l = splits == 1 ? __builtin_nanf("") : 1.f;
+  const float inv = l == 0.f ? 0.f : 1.f / l;
+  const size_t slot = (size_t)row * splits + c;
+  if (lane < D) {
+    if (splits == 1)
+      out[(size_t)row * D + lane] = o * inv;
+    else
+      part_o[slot * D + lane] = o;
+  }
+  if (lane == 0) {
+    if (splits == 1) {
+      if (lse) lse[row] = m + logf(l);
+    } else {
+      part_ml[slot * 2 + 0] = m;
+      part_ml[slot * 2 + 1] = l;
+    }
+  }
+}
+
 // out[row] = sum_c O_c e^{m_c - m} / sum_c l_c e^{m_c - m}; chunks with l_c == 0 are empty and
 // their O_c was never written.  One thread per four consecutive d of a row (D / 4 threads per
 // row, 16-byte loads and stores); every thread reads its row's (m_c, l_c) pairs itself (they are
@@ -341,6 +512,13 @@ hipError_t launch_attn_scalar(const hb_attn_desc &d, const AttnPlan &plan, const
   attn_scalar_kernel<T_, E_><<<grid, kThreads, 0, s>>>(d, plan.splits, plan.chunk_tokens, (const T_ *)q,        \
       (const T_ *)k_tree, (const T_ *)v_tree, (const T_ *)k_pool, (const T_ *)v_pool, block_table, prefix_len,  \
       node_offset, parent, (T_ *)out, lse, part_o, part_ml, clear)
+  if (d.dtype == HB_F32 && d.head_dim <= 64 && d.batch < 64 && (int64_t)grid.x * grid.y <= kEagerMost) {
+    attn_scalar_eager_kernel<<<grid, kEagerThreads, 0, s>>>(d, plan.splits, plan.chunk_tokens, (const float *)q, (const float *)k_tree,
+                                                            (const float *)v_tree, (const float *)k_pool, (const float *)v_pool,
+                                                            block_table, prefix_len, node_offset, parent, (float *)out, lse, part_o,
+                                                            part_ml, clear);
+    return hipGetLastError();
+  }
   const int e = d.head_dim <= 64 ? 1 : d.head_dim <= 128 ? 2 : 4;  // head dimensions per lane
   if (d.dtype == HB_F32) {
     if (e == 1) HB_ATTN_SCALAR(float, 1);

@@ -137,6 +137,46 @@ def test_scalar_kernel_keys_with_scores_of_minus_infinity(hb, step, dtype, D):
         assert np.abs(got[:last] - ref[:last]).max() <= tol and np.abs(got_lse[:last] - ref_lse[:last]).max() <= 1e-4, splits
 
 
+@pytest.mark.parametrize("D,page", [(8, 16), (40, 4), (64, 16), (64, 48)])
+@pytest.mark.parametrize("lens", [[0], [1, 63, 64, 65], [447, 448, 449, 0, 20], [900], [2, 0, 260]])
+def test_float32_rows_in_one_round_of_workgroups(hb, step, D, page, lens):
+    """The float32 kernel of few workgroups, in which a wavefront has K and V of 64 keys in flight and the tree one of its own:
+    prefixes around a block of 64 keys and a round of its seven wavefronts (448 keys), trees of one to 64 nodes, poisoned
+    slots and off-path nodes; and 70 sequences or 400 workgroups, which it leaves to the other kernel."""
+    trees = [W.chain_tree(2), W.seeded_tree(2, n_nodes=13, levels=4, root_fanout=4), W.chain_tree(1), W.chain_tree(5), W.chain_tree(3)][:len(lens)]
+    for Hq, Hkv in ((2, 1), (3, 3)):
+        inp = W.make_verify_inputs(91 + D, "f32", Hq, Hkv, D, lens, trees, page=page, kv_std=1.0, q_std=1.0)
+        ref = oracle_attn(inp)
+        for splits in (1, 2, 0):
+            out, lse, _ = _run(step, inp, num_splits=splits)
+            check_attn(inp, out, lse, ref=ref, label=f"f32 D={D} page={page} {lens} splits={splits}")
+    for trees in ([W.chain_tree(1)] * 70, [W.seeded_tree(3, n_nodes=64)] * 4, [W.seeded_tree(3, n_nodes=64), W.chain_tree(7)]):
+        inp = W.make_verify_inputs(92, "f32", 2, 1, D, (lens * 70)[:len(trees)], trees, page=page, kv_std=1.0, q_std=1.0)
+        out, lse, _ = _run(step, inp)
+        check_attn(inp, out, lse, ref=oracle_attn(inp), label=f"f32 D={D} {len(trees)} trees")
+
+
+def test_float32_rows_in_one_round_with_scores_of_minus_infinity(hb, step):
+    """As above for whole blocks, wavefronts and rows of keys without weight."""
+    trees = [W.chain_tree(2), W.chain_tree(3), W.chain_tree(4), W.chain_tree(2)]
+    inp = W.make_verify_inputs(93, "f32", 4, 2, 64, [600, 64, 900, 100], trees, kv_std=1.0, q_std=1.0)
+    inp.q[..., 0] = inp.q[..., 0].abs() + 0.25
+    masked = [list(range(0, 128)) + list(range(256, 520)), range(0, 64), list(range(0, 200)) + list(range(250, 900)), range(0, 100)]
+    for b, positions in enumerate(masked):
+        for p in positions:
+            inp.k_pool[int(inp.block_table[b, p // inp.page]), :, p % inp.page, 0] = float("-inf")
+    last = int(inp.node_offset[3])
+    inp.k_tree[last:, :, 0] = float("-inf")
+    with np.errstate(invalid="ignore"):
+        ref, ref_lse = oracle_attn(inp)
+    assert np.isfinite(ref[:last]).all() and np.isnan(ref[last:]).all()
+    for splits in (1, 2, 3, 0):
+        out, lse, _ = _run(step, inp, num_splits=splits)
+        got, got_lse = W.widen(out), W.widen(lse)
+        assert np.isnan(got[last:]).all(), splits
+        assert np.abs(got[:last] - ref[:last]).max() <= 1e-5 and np.abs(got_lse[:last] - ref_lse[:last]).max() <= 1e-4, splits
+
+
 @pytest.mark.parametrize("nodes", [8, 60])
 @pytest.mark.parametrize("lens", [[1], [191], [193], [2048], [640, 64, 1500], [300] * 8, [100, 900, 0, 500, 70, 1400, 33, 256, 812]])
 def test_short_pieces_of_a_few_sequences(hb, step, nodes, lens):

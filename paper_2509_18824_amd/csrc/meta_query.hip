@@ -667,6 +667,78 @@ __global__ __launch_bounds__(kMpThreads) void meta_project_kernel(
   }
 }
 
+// Where several workgroups share D (see there), their probabilities are made once, from all rows of a token: eight lanes a
+// row.  probs[2][S][rows][4 pieces of eight layers], values, then remainders.
+constexpr int kSoftmaxThreads = 256;
+__global__ __launch_bounds__(kSoftmaxThreads) void meta_softmax_kernel(int S, int L, int rows, int rows_pad, int parts,
+                                                                       const f32x4 *__restrict__ part, uint32_t *__restrict__ probs) {
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  const int s = blockIdx.x, c4 = threadIdx.x & 7;
+  const size_t stride = (size_t)S * rows_pad * (kMaxL / 4);
+  for (int row = threadIdx.x >> 3; row < rows; row += kSoftmaxThreads / 8) {  // the eight lanes of a row go together
+    const f32x4 *src = part + ((size_t)s * rows_pad + row) * (kMaxL / 4) + c4;
+    f32x4 v[kMaxParts];
+#pragma unroll
+    for (int p = 0; p < kMaxParts; ++p)
+      if (p < parts) v[p] = src[p * stride];
+    f32x4 sc = v[0];
+#pragma unroll
+    for (int p = 1; p < kMaxParts; ++p)
+      if (p < parts) sc += v[p];
+    float mx = -__builtin_huge_valf();
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (4 * c4 + e < L) mx = fmaxf(mx, sc[e]);
+#pragma unroll
+    for (int off = 4; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+    float sum = 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      sc[e] = 4 * c4 + e < L ? __expf(sc[e] - mx) : 0.f;
+      sum += sc[e];
+    }
+#pragma unroll
+    for (int off = 4; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+    const float inv = 1.f / sum;
+    u32x2 hi, lo;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      uint32_t a, b;
+      split_pair(sc[2 * e] * inv, sc[2 * e + 1] * inv, a, b);
+      hi[e] = a;
+      lo[e] = b;
+    }
+    const size_t at = (((size_t)s * rows + row) * 8 + c4) * 2;
+    *(u32x2 *)(probs + at) = hi;
+    *(u32x2 *)(probs + (size_t)S * rows * 16 + at) = lo;
+  }
+}
+
+// The sum over D's parts, in order, of four values, and the residual rows.
+__global__ __launch_bounds__(256) void meta_sum_kernel(int S, int L, int D, int Q, int parts, const f32x4 *__restrict__ sums,
+                                                       const uint2 *__restrict__ feats, ResidualLayers res, uint2 *__restrict__ pre,
+                                                       uint2 *__restrict__ res_out) {
+  const size_t n4 = (size_t)S * Q * (D / 4), i = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n4) return;
+  uint2 r;
+  if (res.on) {
+    const int d4 = D / 4, col = (int)(i % d4), row = (int)(i / d4), t = row / Q;
+    r = feats[((size_t)t * L + res.layer[row - t * Q]) * d4 + col];
+  }
+  f32x4 x = {0.f, 0.f, 0.f, 0.f};
+  for (int p0 = 0; p0 < parts; p0 += 8) {
+    f32x4 v[8];
+#pragma unroll
+    for (int p = 0; p < 8; ++p) v[p] = sums[(size_t)min(p0 + p, parts - 1) * n4 + i];
+#pragma unroll
+    for (int p = 0; p < 8; ++p)
+      if (p0 + p < parts) x += v[p];
+  }
+  pre[i] = make_uint2((uint32_t)f32_to_bf16(x[0]) | ((uint32_t)f32_to_bf16(x[1]) << 16),
+                      (uint32_t)f32_to_bf16(x[2]) | ((uint32_t)f32_to_bf16(x[3]) << 16));
+  if (res.on) res_out[i] = r;
+}
+
 // The same for 16 tokens a workgroup: a head's rows are Q tiles of 16 tokens.  A step is 32 features.  The product of a step
 // and the mixing of the next one do not depend on each other, so a wavefront does both in one stream of instructions: it
 // reads the operands of both from LDS, and between the matrix instructions of the product the mixed values are split and
@@ -683,7 +755,7 @@ template <int QT, int NT, int FI>
 __global__ __launch_bounds__(kMpThreads) void meta_project_wide_kernel(
     int S, int L, int D, int H, int Q, int hg, int rows_pad, int parts, const float *__restrict__ part,
     const u32x4 *__restrict__ feats, const u32x4 *__restrict__ packed, ResidualLayers res, bf16_t *__restrict__ pre,
-    u32x4 *__restrict__ res_out) {
+    u32x4 *__restrict__ res_out, int share, const u32x4 *__restrict__ probs, float *__restrict__ sums) {
   constexpr int kWavesPerHead = 8 / NT;
   constexpr int CT = QT * 8 > 16 && NT == 8 ? 2 : 1;  // tiles of 16 hq rows (NT 4: at most 16 rows)
   extern __shared__ u32x4 meta_a_lds[];
@@ -707,7 +779,8 @@ __global__ __launch_bounds__(kMpThreads) void meta_project_wide_kernel(
   // source side; rows past the workgroup's are out of the buffer's range and arrive as zeros.  Always kLoads loads (the
   // waits below count them): a repeated slice changes nothing.
   typedef __attribute__((address_space(3))) void *lptr_t;
-  const int steps = D / 32, slices = D / (8 * kRow);
+  const int first = (int)blockIdx.z * share, mine = min(share, D / 64 - first);  // of D, in slices of 64
+  const int steps = 2 * mine, slices = kShort ? 2 * mine : mine;
   const auto f_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(feats + (size_t)tok0 * L * dp), 0, frows * dp * 16, kBufferFlags);
   constexpr int kRows = 64 / kRow;  // of a load
   const int f_row = wave * kRows + lane / kRow;
@@ -717,7 +790,7 @@ __global__ __launch_bounds__(kMpThreads) void meta_project_wide_kernel(
 #pragma unroll
     for (int i = 0; i < kLoads; ++i)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(f_rsrc, (lptr_t)(lds_f + slot * kStage + (wave + i * kMpWaves) * 64), 16,
-                                               f_src + i * kMpWaves * kRows * dp * 16, k * kRow * 16, 0, 0);
+                                               f_src + i * kMpWaves * kRows * dp * 16, first * 128 + k * kRow * 16, 0, 0);
   };
 #pragma unroll
   for (int i = 0; i < kStages; ++i) issue_feats(i, i);
@@ -727,7 +800,16 @@ __global__ __launch_bounds__(kMpThreads) void meta_project_wide_kernel(
   // the same values there again.
   auto row_of = [&](int ct) { return 16 * ct + j16 < hq_rows ? 16 * ct + j16 : j16 % hq_rows; };
   bf16x8 p_hi[2][CT], p_lo[2][CT];
-  {
+  if (probs) {
+#pragma unroll
+    for (int tt = 0; tt < 2; ++tt)
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) {
+        const u32x4 *at = probs + ((size_t)min(tok0 + 2 * wave + tt, S - 1) * (H * Q) + h0 * Q + row_of(ct)) * 4 + kq;
+        p_hi[tt][ct] = __builtin_bit_cast(bf16x8, at[0]);
+        p_lo[tt][ct] = __builtin_bit_cast(bf16x8, at[(size_t)S * H * Q * 4]);
+      }
+  } else {
     u32x4 *tab = lds_m;  // [2][16 * hq_rows][4 pieces]
     const int n = kMwTok * hq_rows;
     if (tid < n) softmax_layers(tid, tid / hq_rows, tid % hq_rows, n, S, L, tok0, h0 * Q, rows_pad, parts, part, tab);
@@ -743,7 +825,7 @@ __global__ __launch_bounds__(kMpThreads) void meta_project_wide_kernel(
   }
 
   // the residual rows of the workgroup's columns, kBatch loads in flight (one after the other they took 15 us)
-  if (res.on) {
+  if (res.on && !sums) {
     constexpr int kBatch = 6;
     const int cols = heads * (kMpHeadDim / 8), n = min(kMwTok, S - tok0) * Q * cols;
     for (int i0 = tid; i0 < n; i0 += kBatch * kMpThreads) {
@@ -795,7 +877,7 @@ __global__ __launch_bounds__(kMpThreads) void meta_project_wide_kernel(
 
   const int w_step = D / 16 * 1024;  // bytes of a slice
   const auto w_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(packed + (size_t)((h0 + hl) * 8 + n0 / 16) * 64), 0,
-                                                        (steps - 1) * w_step + NT * 1024, kBufferFlags);
+                                                        (D / 32 - 1) * w_step + NT * 1024, kBufferFlags);
   f32x4 acc[QT][NT];
 #pragma unroll
   for (int q = 0; q < QT; ++q)
@@ -803,7 +885,7 @@ __global__ __launch_bounds__(kMpThreads) void meta_project_wide_kernel(
     for (int nt = 0; nt < NT; ++nt) acc[q][nt] = (f32x4){0.f, 0.f, 0.f, 0.f};
   bf16x8 w[NT];
   auto issue_weight = [&](int kt, int nt) {
-    const int k = min(kt, steps - 1);
+    const int k = 2 * first + min(kt, steps - 1);
     w[nt] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, lane * 16, k * w_step + nt * 1024, 0));
   };
 
@@ -900,6 +982,15 @@ __global__ __launch_bounds__(kMpThreads) void meta_project_wide_kernel(
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   // lane (j16, kq) holds columns 16 nt + 4 kq .. + 3 of token j16
   if (!active || tok0 + j16 >= S) return;
+  if (sums) {
+#pragma unroll
+    for (int q = 0; q < QT; ++q) {
+      float *dst = sums + (((size_t)blockIdx.z * S + tok0 + j16) * Q + q) * D + (h0 + hl) * kMpHeadDim + n0 + 4 * kq;
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) *(f32x4 *)(dst + nt * 16) = acc[q][nt];
+    }
+    return;
+  }
 #pragma unroll
   for (int q = 0; q < QT; ++q) {
     bf16_t *dst = pre + ((size_t)(tok0 + j16) * Q + q) * D + (h0 + hl) * kMpHeadDim + n0 + 4 * kq;
@@ -931,11 +1022,14 @@ hipError_t launch_meta_fold(int32_t Q, int32_t D, int32_t H, const void *f_q, co
 }
 
 // Workgroup columns of the score kernel: one workgroup per CU, as many as that leaves room for (with
-// 512 wanted, 2048 tokens took 8 us more, 300 tokens 19 us more for the layer)
-static void score_split(int32_t S, int32_t D, int *slices_per_wg, int *parts) {
+// 512 wanted, 2048 tokens took 8 us more, 300 tokens 19 us more for the layer).  Beside the rearrangement of W_v up to 320
+// tokens leave half of the CUs to that: with columns on all of them half of the scores came behind it (28 layers x 3584, the
+// whole call, 96 tokens 79.2 -> 74.6 us, 128 83.4 -> 77.9, 192 97 -> 93; 400 tokens 173 -> 182).
+constexpr int kPackWorkgroups = 128;
+static void score_split(int32_t S, int32_t D, int *slices_per_wg, int *parts, bool packs = false) {
   const int slices = D / kSlice;
   const int groups = (S + kTokPerGroup - 1) / kTokPerGroup;
-  int p = 256 / groups;
+  int p = (packs && S <= 320 ? 256 - kPackWorkgroups : 256) / groups;
   if (p > slices) p = slices;
   if (p > kMaxParts) p = kMaxParts;
   if (p < 1) p = 1;
@@ -953,11 +1047,12 @@ size_t meta_attn_workspace_bytes(int32_t S, int32_t D, int32_t H, int32_t Q) {
 static hipError_t launch_scores(int32_t S, int32_t L, int32_t D, int32_t rows_pad, const void *feats, const void *a_fold,
                                 const void *w_v, void *packed, float *part, int *parts, hipStream_t s) {
   int spw;
-  score_split(S, D, &spw, parts);
+  score_split(S, D, &spw, parts, packed != nullptr);
   hipError_t e = hipFuncSetAttribute((const void *)meta_scores_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kScoreLds);
   if (e != hipSuccess) return e;
-  const int groups = (S + kTokPerGroup - 1) / kTokPerGroup, pack_wgs = packed ? 128 : 0;
-  meta_scores_kernel<<<pack_wgs + groups * *parts, kScoreThreads, kScoreLds, s>>>(
+  const int groups = (S + kTokPerGroup - 1) / kTokPerGroup, work = groups * *parts;
+  const int pack_wgs = !packed ? 0 : std::max(kPackWorkgroups, 256 - work);
+  meta_scores_kernel<<<pack_wgs + work, kScoreThreads, kScoreLds, s>>>(
       S, L, D, rows_pad / 16, spw, groups, pack_wgs, (const u32x4 *)w_v, (u32x4 *)packed, (const u32x4 *)feats,
       (const u32x4 *)a_fold, part);
   return hipGetLastError();
@@ -991,8 +1086,13 @@ bool meta_project_supports(int32_t D, int32_t H) { return D == H * kMpHeadDim; }
 static size_t meta_packed_offset(int32_t S, int32_t D, int32_t H, int32_t Q) {
   return (meta_attn_workspace_bytes(S, D, H, Q) + 255) / 256 * 256;
 }
+// behind them, where workgroups share D: the probabilities, and the sums of D's parts (as many as there may be)
+static size_t meta_probs_bytes(int32_t S, int32_t H, int32_t Q) { return (size_t)S * H * Q * 128; }
+static int project_most_shares(int32_t S, int32_t D, int32_t H, int32_t Q);
 size_t meta_project_workspace_bytes(int32_t S, int32_t D, int32_t H, int32_t Q) {
-  return meta_packed_offset(S, D, H, Q) + (size_t)D * D * sizeof(bf16_t);
+  const int most = project_most_shares(S, D, H, Q);
+  const size_t shared = most > 1 ? meta_probs_bytes(S, H, Q) + (size_t)most * S * Q * D * sizeof(float) : 0;
+  return meta_packed_offset(S, D, H, Q) + (size_t)D * D * sizeof(bf16_t) + shared;
 }
 
 namespace {
@@ -1014,9 +1114,10 @@ hipError_t launch_project(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q,
 template <int QT, int NT, int FI>
 hipError_t launch_project_wide(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q, int hg, int parts, const void *feats,
                                const void *packed, const ResidualLayers &res, void *pre, void *res_out, const float *part,
-                               hipStream_t s) {
+                               int share, const void *probs, float *sums, hipStream_t s) {
   if (FI > mw_loads(L)) {
-    if constexpr (FI > 6) return launch_project_wide<QT, NT, FI - 1>(S, L, D, H, Q, hg, parts, feats, packed, res, pre, res_out, part, s);
+    if constexpr (FI > 6)
+      return launch_project_wide<QT, NT, FI - 1>(S, L, D, H, Q, hg, parts, feats, packed, res, pre, res_out, part, share, probs, sums, s);
   }
   constexpr bool kShort = mw_short(QT, NT, FI);
   constexpr size_t kStages = (size_t)(kShort ? 3 : 2) * mw_stage(FI, kShort);
@@ -1027,9 +1128,9 @@ hipError_t launch_project_wide(int32_t S, int32_t L, int32_t D, int32_t H, int32
   auto kern = meta_project_wide_kernel<QT, NT, FI>;
   hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  kern<<<dim3((S + kMwTok - 1) / kMwTok, (H + hg - 1) / hg), kMpThreads, lds, s>>>(
+  kern<<<dim3((S + kMwTok - 1) / kMwTok, (H + hg - 1) / hg, (D / 64 + share - 1) / share), kMpThreads, lds, s>>>(
       S, L, D, H, Q, hg, meta_rows_pad(H, Q), parts, part, (const u32x4 *)feats, (const u32x4 *)packed, res, (bf16_t *)pre,
-      (u32x4 *)res_out);
+      (u32x4 *)res_out, share, (const u32x4 *)probs, sums);
   return hipGetLastError();
 }
 
@@ -1043,12 +1144,45 @@ hipError_t launch_project_wide(int32_t S, int32_t L, int32_t D, int32_t H, int32
 // 16 heads, 3 queries: 4 tokens a workgroup 78 us, 16 tokens 95; 1247, 15, 28, 1: 16 tokens and 7 heads 280, 4 heads 344).
 struct ProjectPlan {
   int tg, nt, hg;
+  int ds = 1;  // workgroups that share D
 };
 static int split_heads(int H, int most) {  // heads per workgroup, evenly
   const int groups = (H + most - 1) / most;
   return (H + groups - 1) / groups;
 }
-static ProjectPlan project_plan(int32_t S, int32_t L, int32_t H, int32_t Q) {
+// Workgroups that share D: where 16 tokens a workgroup occupy a part of the CUs only, each takes a share of D, the
+// probabilities are made once in front of them and the float32 sums of the shares are added up behind them.
+// us before and now (scores included): 28 layers x 3584, 28 heads, 3 queries 16 tokens 61 -> 44, 64 67 -> 59, 96 85 -> 75, 192 126 ->
+// 93; 24 x 4096, 32 heads, 2 queries 64 tokens 74 -> 60, 256 158 -> 97; 16 x 2048, 16 heads, 1 query 400 tokens 67 -> 48.  Which
+// form and how many shares: rounds of 256 workgroups, by times fitted to 480 measurements (30 shapes of 8 to 600 tokens, 2 to
+// 14 shares; 3 % rms).  The forms below keep three queries of more than 320 tokens (400 tokens 175 and 178, 600 240 and 229)
+// and short D, where a share is hardly longer than its start (1024, 2 queries 416 tokens 30 and 36, 3 queries 210 24 and 31;
+// 2048, 3 queries 96 38 and 42; but 1 query 20 tokens x 1024 22.3 and 20.6).  Of 70 drawn calls of 9 to 640 tokens those it takes
+// are 1.35 times as fast.
+constexpr int kMostShares = 16;
+static ProjectPlan shared_plan(int32_t S, int32_t D, int32_t H, int32_t Q) {
+  ProjectPlan best = {0, 0, 0, 1};
+  const int short_d = Q == 3 ? (S <= 48 ? 2048 : 3072) : Q == 2 ? 2048 : S <= 128 ? 1024 : 2048;
+  if (Q > 3 || D < short_d || S > (Q <= 2 ? 640 : 320)) return best;
+  double best_us = 1e30;
+  for (int nt : {4, 8}) {
+    const int hg = split_heads(H, nt == 4 ? 4 : std::min(8, kMpHq / Q));
+    const int64_t per = (int64_t)((S + 15) / 16) * ((H + hg - 1) / hg);
+    for (int ds = 2; ds <= kMostShares && ds * 2 <= D / 64; ++ds) {
+      const int share = (D / 64 + ds - 1) / ds, parts = (D / 64 + share - 1) / share;
+      const double us = (double)((per * parts + 255) / 256) * (share * (nt == 4 ? 1.3 + 0.2 * Q : 1.6 + 0.5 * Q) + 6) + 2e-6 * parts * S * Q * D;
+      if (us < best_us) {
+        best_us = us;
+        best = {16, nt, hg, parts};
+      }
+    }
+  }
+  return best;
+}
+static int project_most_shares(int32_t S, int32_t D, int32_t H, int32_t Q) { return shared_plan(S, D, H, Q).ds; }
+static ProjectPlan project_plan(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q) {
+  const ProjectPlan shared = shared_plan(S, D, H, Q);
+  if (shared.ds > 1) return shared;
   const int64_t g4 = (S + 3) / 4, g16 = (S + 15) / 16;
   auto groups = [&](int hg) { return (int64_t)(H + hg - 1) / hg; };
   if (g4 * groups(2) <= 256) return {4, 2, split_heads(H, 2)};
@@ -1071,9 +1205,12 @@ static ProjectPlan project_plan(int32_t S, int32_t L, int32_t H, int32_t Q) {
 // 1 us with 4 tokens, 3.0 with 16 tokens and 4 heads and 5.0 with more heads, longer than they take, put it: what it sends
 // this way is 1.5 to 3 % slower in the mean of 1100 drawn calls than the faster of both orders (28 layers, 3 queries, D =
 // 3584, up to fc1: 16 tokens 92 us values first and 95 this way, 48 tokens 117 and 103, 2048 tokens 2082 and 860), and lines
-// closer to it would round the values of calls that have none rounded.
+// closer to it would round the values of calls that have none rounded.  Workgroups that share D are ahead from some ten
+// tokens on (up to fc2, us, values first and this way: 28 layers x 3584, 3 queries 8 tokens 93 to 99 and 82, 16 103 and 95, 32 115 and 103;
+// 16 x 2048, 1 query 8 tokens 50 and 51, 12 59 and 52, 64 55 and 49; 4 tokens 48 and 51).
 bool meta_project_pays(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q) {
   if (!meta_project_supports(D, H)) return false;
+  if (S >= 10 && shared_plan(S, D, H, Q).ds > 1) return true;
   const double product = 2.0 * S * L * D * (double)D / 0.85e9, mixing = 2.0 * S * L * (double)D / 2.6e6;
   const double first = (product < 20 ? 20 : product) + (mixing < 5 ? 5 : mixing);
   const int64_t g4 = (S + 3) / 4, g16 = (S + 15) / 16;
@@ -1095,11 +1232,20 @@ hipError_t launch_meta_attn_project(int32_t S, int32_t L, int32_t D, int32_t H, 
   hipError_t e = launch_scores(S, L, D, meta_rows_pad(H, Q), feats, a_fold, w_v, packed, part, &parts, s);
   if (e != hipSuccess) return e;
   const ResidualLayers res = residuals(Q, residual_layers, res_out);
-  const ProjectPlan plan = project_plan(S, L, H, Q);
+  const ProjectPlan plan = project_plan(S, L, D, H, Q);
   if (plan.tg == 4)
     return plan.nt == 2 ? launch_project<2>(S, L, D, H, Q, plan.hg, parts, feats, packed, res, pre, res_out, part, s)
                         : launch_project<4>(S, L, D, H, Q, plan.hg, parts, feats, packed, res, pre, res_out, part, s);
-#define HB_MP(QT_, NT_) return launch_project_wide<QT_, NT_, 8>(S, L, D, H, Q, plan.hg, parts, feats, packed, res, pre, res_out, part, s)
+  const int share = plan.ds > 1 ? (D / 64 + plan.ds - 1) / plan.ds : D / 64, shares = (D / 64 + share - 1) / share;
+  char *more = (char *)packed + (size_t)D * D * sizeof(bf16_t);
+  void *probs = plan.ds > 1 ? more : nullptr;
+  float *sums = plan.ds > 1 ? (float *)(more + meta_probs_bytes(S, H, Q)) : nullptr;
+  if (probs) {
+    meta_softmax_kernel<<<S, kSoftmaxThreads, 0, s>>>(S, L, H * Q, meta_rows_pad(H, Q), parts, (const f32x4 *)part, (uint32_t *)probs);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  auto project = [&] {
+#define HB_MP(QT_, NT_) return launch_project_wide<QT_, NT_, 8>(S, L, D, H, Q, plan.hg, parts, feats, packed, res, pre, res_out, part, share, probs, sums, s)
   if (plan.nt == 4) {
     switch (Q) {
       case 1: HB_MP(1, 4);
@@ -1114,6 +1260,12 @@ hipError_t launch_meta_attn_project(int32_t S, int32_t L, int32_t D, int32_t H, 
     default: HB_MP(3, 8);
   }
 #undef HB_MP
+  };
+  if ((e = project()) != hipSuccess || !sums) return e;
+  const size_t n4 = (size_t)S * Q * D / 4;
+  meta_sum_kernel<<<(unsigned)((n4 + 255) / 256), 256, 0, s>>>(S, L, D, Q, shares, (const f32x4 *)sums, (const uint2 *)feats, res,
+                                                               (uint2 *)pre, (uint2 *)res_out);
+  return hipGetLastError();
 }
 
 }  // namespace hb

@@ -159,6 +159,23 @@ def test_every_form_of_the_projection_after_the_mixing(S, n_tok, L, D, H, Q, lay
     assert names == [form.replace("wide", "project_wide")]
 
 
+@pytest.mark.parametrize("n_tok,L,D,H,Q,layers,form,shared", [
+    (1, 28, 2048, 16, 3, [27, 0, 5], "wide<3, 4, 7>", True), (17, 32, 1280, 10, 1, None, "wide<1, 4, 8>", True),
+    (40, 5, 2304, 18, 2, [4, 0], "wide<2, 4, 6>", True), (300, 30, 3584, 28, 3, None, "wide<3, 8, 8>", True),  # slices of 32 features
+    (320, 24, 3072, 24, 3, [0, 23, 7], "wide<3, 4, 6>", True), (640, 25, 2048, 16, 1, [3], "wide<1, 8, 7>", True),
+    (321, 24, 1024, 8, 3, None, "project<4>", False), (17, 9, 768, 6, 2, [8, 1], "project<2>", False), (49, 9, 2048, 16, 3, None, "project<2>", False)])
+def test_workgroups_that_share_d(S, n_tok, L, D, H, Q, layers, form, shared):
+    """Probabilities made in front and float32 sums of the shares added up behind: shares of unequal and of the
+    shortest length, ragged tokens, both forms; and both sides of the lines."""
+    import re
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CUDA]) as trace:
+        test_values_projected_after_the_mixing(S, n_tok, L, D, H, Q, layers)
+    names = [m[1] + (m[2] or "") for m in (re.search(r"meta_(project|project_wide|softmax|sum)_kernel(<[^>]*>)?", e.name) for e in trace.events()) if m]
+    form = form.replace("wide", "project_wide")
+    assert names == (["softmax", form, "sum"] if shared else [form])
+
+
 @pytest.mark.parametrize("n_tok,L,D,H,Q", [(7, 28, 768, 6, 3), (1203, 5, 768, 6, 2), (1025, 5, 512, 4, 2)])
 @pytest.mark.parametrize("bad", [float("inf"), float("-inf"), float("nan")])
 def test_a_token_with_features_that_are_not_finite(S, n_tok, L, D, H, Q, bad):

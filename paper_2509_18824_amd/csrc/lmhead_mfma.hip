@@ -132,47 +132,47 @@ __global__ __launch_bounds__(512) void lmhead_mfma_kernel(int M, int K, int V, i
   }  // vocabulary tiles of this workgroup
 }
 
-template <int MT, bool WNT>
-hipError_t launch(int M, int K, int V, const void *hidden, const void *weight, unsigned long long *keys,
-                  hipStream_t s) {
-  constexpr int TM = 64 * MT;
-  int m_tiles = (M + TM - 1) / TM;
-  int v_tiles = (V + TV - 1) / TV;
+// How the workgroups of an XCD share v_tiles / 8 vocabulary tiles against m_tiles hidden tiles.
+struct Shares {
+  int groups, spare, spare_tiles, rounds;
+};
+Shares share_tiles(int m_tiles, int v_tiles) {
   // groups per XCD: at most as many as its 32 CUs hold with one workgroup per CU; then the
   // fewest that still need the same number of rounds, so that every group gets the same number
   // of vocabulary tiles (594 tiles of one hidden tile: 25 groups x 3 rounds per XCD instead of 32
   // groups of which a third work a round longer)
   int max_groups = 32 / m_tiles;
   if (max_groups < 1) max_groups = 1;
-  int need = (v_tiles + kXcds - 1) / kXcds;
-  int rounds = (need + max_groups - 1) / max_groups;
-  int groups = (need + rounds - 1) / rounds;
+  const int need = (v_tiles + kXcds - 1) / kXcds, rounds = (need + max_groups - 1) / max_groups;
+  Shares sh = {(need + rounds - 1) / rounds, 0, 0, rounds};
   // CUs of an XCD that no group occupies: if handing them a few vocabulary tiles (every XCD has
   // at least v_tiles / 8) saves the groups a round, do so (960 rows = 5 hidden tiles: 6 groups
   // on 30 CUs would need 13 rounds for 75 tiles; with 3 tiles on the 2 other CUs, 15 units in 8
   // rounds, they need 12).  The fewest tiles that reach the best round count are handed over.
-  int spare = 0, spare_tiles = 0;
   if (m_tiles <= 32) {
     const int left = 32 - max_groups * m_tiles;
-    int best = rounds;
     for (int y = 1; left > 0 && y <= v_tiles / kXcds; ++y) {
       const int full = (need - y + max_groups - 1) / max_groups;
       const int mine = (y * m_tiles + left - 1) / left;
       const int cost = full > mine ? full : mine;
-      if (cost < best) {
-        best = cost;
-        spare = left;
-        spare_tiles = y;
-      }
+      if (cost < sh.rounds) sh = {max_groups, left, y, cost};
     }
-    if (spare) groups = max_groups;
   }
+  return sh;
+}
+
+template <int MT, bool WNT>
+hipError_t launch(int M, int K, int V, const void *hidden, const void *weight, unsigned long long *keys,
+                  hipStream_t s) {
+  constexpr int TM = 64 * MT;
+  const int m_tiles = (M + TM - 1) / TM, v_tiles = (V + TV - 1) / TV;
+  const Shares sh = share_tiles(m_tiles, v_tiles);
   size_t lds_bytes = tile_lds_bytes(MT);
   auto kern = lmhead_mfma_kernel<MT, WNT>;
   hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
   if (e != hipSuccess) return e;
-  dim3 grid((unsigned)((groups * m_tiles + spare) * kXcds));
-  kern<<<grid, 512, lds_bytes, s>>>(M, K, V, m_tiles, v_tiles, groups, spare, spare_tiles, (const u32x4 *)hidden, (const u32x4 *)weight, keys);
+  dim3 grid((unsigned)((sh.groups * m_tiles + sh.spare) * kXcds));
+  kern<<<grid, 512, lds_bytes, s>>>(M, K, V, m_tiles, v_tiles, sh.groups, sh.spare, sh.spare_tiles, (const u32x4 *)hidden, (const u32x4 *)weight, keys);
   return hipGetLastError();
 }
 
@@ -185,20 +185,24 @@ bool lmhead_mfma_supports(int32_t dtype, int32_t M, int32_t K, int32_t V) {
 hipError_t launch_lmhead_mfma(int32_t M, int32_t K, int32_t V, const void *hidden, const void *weight,
                               unsigned long long *keys, hipStream_t s) {
   if (lmhead_few_takes(M, V)) return launch_lmhead_few(M, K, V, hidden, weight, keys, s);
-  // hidden tile height: the multiple of 64 (up to 256) that wastes the fewest padded rows,
-  // preferring the taller tile on ties (fewer re-reads of the weight tile)
-  int best_mt = 4;
-  long best_rows = -1;
-  for (int mt = 4; mt >= 1; --mt) {
-    int tm = 64 * mt;
-    long rows = (long)((M + tm - 1) / tm) * tm;
-    if (best_rows < 0 || rows < best_rows) { best_rows = rows; best_mt = mt; }
-  }
-  // One taller tile on a few CUs waits for its own K steps (950 ns each with 128 rows, 550 with 64), not for memory:
-  // 64-row tiles as long as one round of CUs holds them all (32 per XCD).  Taller -> 64-row tiles, us: 192 rows x 4096 x 8192
-  // 72 -> 51; 256 rows x 4096 x 16384 84 -> 57.  With another round they lose (128 rows x 4096 x 36000 78 and 112).
+  // Hidden tile height: rounds of a vocabulary tile by what one takes (us a round of 56 K steps, 500 to 1000 rows x 3584 x
+  // 152064: 40, 53, 68 and 83 for 64 to 256 hidden rows; on few CUs a tile waits for its own K steps, and a lower one is
+  // ahead there too).  The fewest padded rows, which chose before, gave 257 to 320, 385 to 448, 641 to 704 and 769 to 832 rows
+  // tiles of 64, many to a vocabulary tile (us, so and by rounds: 320 x 3584 x 152064 519 and 371, 400 683 and 446, 700 1050 and
+  // 662, 800 1218 and 813, 880 893 and 813; 700 x 4096 x 32000 262 and 164).  Equal rounds: the fewest padded rows.
+  static const int kRound[5] = {0, 40, 53, 68, 83};
   const int v_tiles = (V + TV - 1) / TV;
-  if (M <= 64 * best_mt && (v_tiles + kXcds - 1) / kXcds * ((M + 63) / 64) <= 32) best_mt = 1;
+  int best_mt = 4;
+  long best = -1;
+  for (int mt = 4; mt >= 1; --mt) {
+    const int m_tiles = (M + 64 * mt - 1) / (64 * mt);
+    const long us = (long)share_tiles(m_tiles, v_tiles).rounds * ((m_tiles + 31) / 32) * kRound[mt];
+    const long cost = us * 1000000 + (long)m_tiles * 64 * mt;
+    if (best < 0 || cost < best) {
+      best = cost;
+      best_mt = mt;
+    }
+  }
   switch (best_mt) {
     case 1: return launch<1, false>(M, K, V, hidden, weight, keys, s);  // one tile of up to 128 rows is lmhead_few.hip's
     case 2: return launch<2, false>(M, K, V, hidden, weight, keys, s);

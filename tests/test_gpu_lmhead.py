@@ -84,6 +84,17 @@ def test_runs_of_vocabulary_rows(step, M, K, V):
     _check(hidden, weight, ids, mx)
 
 
+@pytest.mark.parametrize("M,K,V", [(257, 64, 41000), (320, 128, 16500), (385, 64, 50001), (448, 64, 9000), (577, 128, 6000), (700, 64, 32001),
+                                   (769, 64, 20000), (900, 128, 2100), (2100, 64, 1000), (200, 2048, 45000), (130, 4096, 42000)])
+def test_tile_heights_by_rounds(step, M, K, V):
+    """Rows a little beyond a tile's height, where many low tiles would hold fewer padded rows; several heights and numbers of
+    hidden tiles; and one hidden tile whose columns come in another order (K a multiple of 2048)."""
+    hidden, weight = W.make_lmhead_inputs(M + V, M, K, V, dtype="bf16", w_std=0.05)
+    ids, mx = step.lmhead_argmax(hidden.cuda(), weight.cuda())
+    torch.cuda.synchronize()
+    _check(hidden, weight, ids, mx, rows=np.unique(np.concatenate([np.arange(0, M, max(1, M // 150)), [M - 1]])))
+
+
 @pytest.mark.parametrize("M,K,V", [(65, 64, 32768), (128, 128, 32769), (128, 192, 32700), (129, 64, 20480), (192, 128, 20481),
                                    (193, 64, 16384), (256, 128, 16385), (256, 192, 300)])
 def test_tile_height_of_few_vocabulary_tiles(step, M, K, V):

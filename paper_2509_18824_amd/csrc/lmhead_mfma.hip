@@ -88,8 +88,14 @@ __global__ __launch_bounds__(512) void lmhead_mfma_kernel(int M, int K, int V, i
   const int m0 = m_tile * TM;
   const int v0 = v_tile * TV;
 
+  // Rows a multiple of 4 KB apart meet on few memory channels where everybody reads the same columns.  One hidden tile: every
+  // vocabulary tile begins with a K step of its own (160 rows, us: 4096 x 152064 267 -> 248, 2048 x 100000 102 -> 91); several
+  // lose what they share in the L2s (960 rows x 4096 910 -> 972).
+  const int turn = WNT && K % 2048 == 0 ? (int)((unsigned)(nth * 5) % (unsigned)(K / BK)) : 0;
 #define HB_GEMM_W_ROW(t_) (v0 + (t_))
+#define HB_GEMM_TURN turn
 #include "mfma_gemm_tile.inc"
+#undef HB_GEMM_TURN
 #undef HB_GEMM_W_ROW
 
   // Epilogue.  Accumulator e of lane l in tile (i, j) is C^T[v, m] with

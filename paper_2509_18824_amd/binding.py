@@ -146,16 +146,6 @@ def _ptr(t: Optional[torch.Tensor]):
     return t.data_ptr()  # the declared argument types convert it
 
 
-def _not_contiguous():
-    raise ValueError("tensors handed to libhb must be contiguous")
-
-
-def _ptrs(*tensors):
-    """``_ptr`` of each, for the calls of a step: a function call less per tensor (15 tensors 4.4 -> 3.0 us; a step of a
-    unit-sized model is bound by its two calls)."""
-    return [None if t is None else t.data_ptr() if t.is_contiguous() else _not_contiguous() for t in tensors]
-
-
 # the raw handle of a device's current stream; a private function of torch that a build of it may lack
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
@@ -473,8 +463,10 @@ def hb_tree_verify_attn_clearing(desc: AttnDesc, q, k_tree, v_tree, k_pool, v_po
     ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
     if rows * 8 > keys.numel() * keys.element_size():
         raise ValueError("keys needs 8 bytes a row")
-    ptrs = _ptrs(q, k_tree, v_tree, k_pool, v_pool, block_table, prefix_len, node_offset, parent, out, lse, workspace)
-    _check(lib.hb_tree_verify_attn_clearing(C.byref(desc), *ptrs, ws_bytes, _ptr(keys), rows, _stream(stream)))
+    _check(lib.hb_tree_verify_attn_clearing(C.byref(desc), _ptr(q), _ptr(k_tree), _ptr(v_tree), _ptr(k_pool),
+                                            _ptr(v_pool), _ptr(block_table), _ptr(prefix_len), _ptr(node_offset),
+                                            _ptr(parent), _ptr(out), _ptr(lse), _ptr(workspace), ws_bytes, _ptr(keys),
+                                            rows, _stream(stream)))
 
 
 def _lmhead_accept(call):
@@ -489,10 +481,10 @@ def _lmhead_accept(call):
         tables = n_layers > 0 and kv[0].dtype == torch.int64
         if tables and any(t.dtype != torch.int64 or t.numel() < n_layers for t in kv):
             raise ValueError("pointer tables must be int64 tensors with one entry per layer")
-        of_nodes = _ptrs(hidden, weight, draft_ids, node_offset, parent)
-        rest = _ptrs(*kv, block_table, prefix_len, out_slots, new_len)
-        _check(call(C.byref(desc), M, K, V, *of_nodes, max_path, *_ptrs(target_ids, accept_len, accept_path, out_tokens, bonus_id, keys),
-                    keys.numel() * keys.element_size(), n_layers, int(tables), *rest, _stream(stream)))
+        _check(call(C.byref(desc), M, K, V, _ptr(hidden), _ptr(weight), _ptr(draft_ids), _ptr(node_offset), _ptr(parent),
+                    max_path, _ptr(target_ids), _ptr(accept_len), _ptr(accept_path), _ptr(out_tokens), _ptr(bonus_id),
+                    _ptr(keys), keys.numel() * keys.element_size(), n_layers, int(tables), *map(_ptr, kv), _ptr(block_table),
+                    _ptr(prefix_len), _ptr(out_slots), _ptr(new_len), _stream(stream)))
 
     return hb_lmhead_accept
 

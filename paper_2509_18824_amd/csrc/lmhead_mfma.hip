@@ -196,12 +196,16 @@ hipError_t launch_lmhead_mfma(int32_t M, int32_t K, int32_t V, const void *hidde
   // ahead there too).  The fewest padded rows, which chose before, gave 257 to 320, 385 to 448, 641 to 704 and 769 to 832 rows
   // tiles of 64, many to a vocabulary tile (us, so and by rounds: 320 x 3584 x 152064 519 and 371, 400 683 and 446, 700 1050 and
   // 662, 800 1218 and 813, 880 893 and 813; 700 x 4096 x 32000 262 and 164).  Equal rounds: the fewest padded rows.
+  // Rows that fit one tile stay in it once two would go round more than once: rounds beyond the first wait for the weights,
+  // and one tile reads them once a CU (227 x 4096 x 69031: two of 128 193, one 166; 237 x 3584 x 96490 193 and 176; within the
+  // round two are ahead, 203 x 2048 x 20148 38 and 47).
   static const int kRound[5] = {0, 40, 53, 68, 83};
   const int v_tiles = (V + TV - 1) / TV;
   int best_mt = 4;
   long best = -1;
   for (int mt = 4; mt >= 1; --mt) {
     const int m_tiles = (M + 64 * mt - 1) / (64 * mt);
+    if (M <= 256 && m_tiles > 1 && v_tiles > 32 / 2 * kXcds) continue;
     const long us = (long)share_tiles(m_tiles, v_tiles).rounds * ((m_tiles + 31) / 32) * kRound[mt];
     const long cost = us * 1000000 + (long)m_tiles * 64 * mt;
     if (best < 0 || cost < best) {

@@ -85,10 +85,12 @@ def test_runs_of_vocabulary_rows(step, M, K, V):
 
 
 @pytest.mark.parametrize("M,K,V", [(257, 64, 41000), (320, 128, 16500), (385, 64, 50001), (448, 64, 9000), (577, 128, 6000), (700, 64, 32001),
-                                   (769, 64, 20000), (900, 128, 2100), (2100, 64, 1000), (200, 2048, 45000), (130, 4096, 42000)])
+                                   (769, 64, 20000), (900, 128, 2100), (2100, 64, 1000), (200, 2048, 45000), (130, 4096, 42000),
+                                   (193, 64, 32768), (193, 64, 32769), (250, 128, 90001)])
 def test_tile_heights_by_rounds(step, M, K, V):
     """Rows a little beyond a tile's height, where many low tiles would hold fewer padded rows; several heights and numbers of
-    hidden tiles; and one hidden tile whose columns come in another order (K a multiple of 2048)."""
+    hidden tiles; one hidden tile whose columns come in another order (K a multiple of 2048); up to 256 rows on both sides of the
+    128 vocabulary tiles that two hidden tiles meet in one round."""
     hidden, weight = W.make_lmhead_inputs(M + V, M, K, V, dtype="bf16", w_std=0.05)
     ids, mx = step.lmhead_argmax(hidden.cuda(), weight.cuda())
     torch.cuda.synchronize()

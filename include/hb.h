@@ -536,8 +536,9 @@ int32_t hb_meta_query_attn(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q
  * workspace, 16-byte aligned, also takes a copy of w_v that every call makes anew.
  * A token with a feature that is not finite has NaN in its own rows both ways; weights are taken to be
  * finite (an infinite W_v may give NaN here where the other way gives an infinity).
- * hb_meta_query_attn_project_pays: 1 where this is the faster way (from about 25 tokens on for 28
- * layers and 3 queries), else 0.
+ * Up to some hundred tokens the queried size has room for partial sums of workgroups that share D.  A workspace without it
+ * (hb_meta_query_attn_workspace_bytes rounded up to 256, and D * D * 2) is taken too, by a slower way.
+ * hb_meta_query_attn_project_pays: 1 where this is the faster way (from about 10 tokens on), else 0.
  */
 int32_t hb_meta_query_attn_project_pays(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q);
 

@@ -637,7 +637,7 @@ static int32_t meta_attn(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q, 
   if (misaligned(feats) || misaligned(v_proj_or_w_v) || misaligned(a_fold) || misaligned(pre) ||
       (residual_out_or_null && misaligned(residual_out_or_null)))
     return fail(HB_ERR_INVALID_ARG, "tensors must be 16-byte aligned");
-  const size_t need = project ? meta_project_workspace_bytes(S, D, H, Q) : meta_attn_workspace_bytes(S, D, H, Q);
+  const size_t need = project ? meta_project_least_bytes(S, D, H, Q) : meta_attn_workspace_bytes(S, D, H, Q);
   if (!workspace || workspace_bytes < need)
     return fail(HB_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need,
                 workspace ? workspace_bytes : (size_t)0);
@@ -647,7 +647,7 @@ static int32_t meta_attn(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q, 
   hipStream_t s = (hipStream_t)stream;
   if (project)
     HB_HIP_TRY(launch_meta_attn_project(S, L, D, H, Q, feats, a_fold, v_proj_or_w_v, residual_layers_or_null, pre, res,
-                                        (float *)workspace, s));
+                                        (float *)workspace, workspace_bytes, s));
   else
     HB_HIP_TRY(launch_meta_attn(S, L, D, H, Q, feats, v_proj_or_w_v, a_fold, residual_layers_or_null, pre, res,
                                 (float *)workspace, s));

@@ -196,9 +196,10 @@ hipError_t launch_meta_attn(int32_t S, int32_t L, int32_t D, int32_t H, int32_t 
 bool meta_project_supports(int32_t D, int32_t H);
 bool meta_project_pays(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q);
 size_t meta_project_workspace_bytes(int32_t S, int32_t D, int32_t H, int32_t Q);
+size_t meta_project_least_bytes(int32_t S, int32_t D, int32_t H, int32_t Q);  // less is refused
 hipError_t launch_meta_attn_project(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q, const void *feats,
                                     const void *a_fold, const void *w_v, const int32_t *residual_layers, void *pre,
-                                    void *res_out, float *part, hipStream_t s);
+                                    void *res_out, float *part, size_t part_bytes, hipStream_t s);
 size_t meta_attn_workspace_bytes(int32_t S, int32_t D, int32_t H, int32_t Q);
 hipError_t launch_kv_compact(const hb_attn_desc &d, const void *k_tree, const void *v_tree,
                              void *k_pool, void *v_pool, const int32_t *block_table,

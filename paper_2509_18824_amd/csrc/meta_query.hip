@@ -22,6 +22,8 @@
 // row does the softmax over the L layers, and every thread then mixes the token's projected values
 // (v_proj = f_i W_v^T, a plain linear layer run beforehand) for eight feature columns of all Q
 // queries:  pre[q, c] = sum_l P[head(c) Q + q, l] v_proj[l, c].
+// meta_project_kernel, meta_project_wide_kernel: the features are mixed first and W_v is applied to the mixture.  Where tokens in
+// sixteens leave CUs idle, workgroups share D: meta_softmax_kernel makes the probabilities once, meta_sum_kernel adds the shares.
 // The output projection and the skip connection (Section 3.1.2) are a linear layer with residual
 // run afterwards on pre; the mixing kernel also copies the residual rows f_i[residual_layers[q]].
 #include "hb_internal.h"
@@ -1089,10 +1091,13 @@ static size_t meta_packed_offset(int32_t S, int32_t D, int32_t H, int32_t Q) {
 // behind them, where workgroups share D: the probabilities, and the sums of D's parts (as many as there may be)
 static size_t meta_probs_bytes(int32_t S, int32_t H, int32_t Q) { return (size_t)S * H * Q * 128; }
 static int project_most_shares(int32_t S, int32_t D, int32_t H, int32_t Q);
+size_t meta_project_least_bytes(int32_t S, int32_t D, int32_t H, int32_t Q) {
+  return meta_packed_offset(S, D, H, Q) + (size_t)D * D * sizeof(bf16_t);
+}
 size_t meta_project_workspace_bytes(int32_t S, int32_t D, int32_t H, int32_t Q) {
   const int most = project_most_shares(S, D, H, Q);
   const size_t shared = most > 1 ? meta_probs_bytes(S, H, Q) + (size_t)most * S * Q * D * sizeof(float) : 0;
-  return meta_packed_offset(S, D, H, Q) + (size_t)D * D * sizeof(bf16_t) + shared;
+  return meta_project_least_bytes(S, D, H, Q) + shared;
 }
 
 namespace {
@@ -1158,12 +1163,12 @@ static int split_heads(int H, int most) {  // heads per workgroup, evenly
 // 14 shares; 3 % rms).  The forms below keep three queries of more than 320 tokens (400 tokens 175 and 178, 600 240 and 229)
 // and short D, where a share is hardly longer than its start (1024, 2 queries 416 tokens 30 and 36, 3 queries 210 24 and 31;
 // 2048, 3 queries 96 38 and 42; but 1 query 20 tokens x 1024 22.3 and 20.6).  Of 70 drawn calls of 9 to 640 tokens those it takes
-// are 1.35 times as fast.
+// are 1.35 times as fast.  Fewer than 10 tokens are left to values projected first (meta_project_pays).
 constexpr int kMostShares = 16;
 static ProjectPlan shared_plan(int32_t S, int32_t D, int32_t H, int32_t Q) {
   ProjectPlan best = {0, 0, 0, 1};
   const int short_d = Q == 3 ? (S <= 48 ? 2048 : 3072) : Q == 2 ? 2048 : S <= 128 ? 1024 : 2048;
-  if (Q > 3 || D < short_d || S > (Q <= 2 ? 640 : 320)) return best;
+  if (S < 10 || Q > 3 || D < short_d || S > (Q <= 2 ? 640 : 320)) return best;
   double best_us = 1e30;
   for (int nt : {4, 8}) {
     const int hg = split_heads(H, nt == 4 ? 4 : std::min(8, kMpHq / Q));
@@ -1180,8 +1185,8 @@ static ProjectPlan shared_plan(int32_t S, int32_t D, int32_t H, int32_t Q) {
   return best;
 }
 static int project_most_shares(int32_t S, int32_t D, int32_t H, int32_t Q) { return shared_plan(S, D, H, Q).ds; }
-static ProjectPlan project_plan(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q) {
-  const ProjectPlan shared = shared_plan(S, D, H, Q);
+static ProjectPlan project_plan(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q, bool may_share) {
+  const ProjectPlan shared = may_share ? shared_plan(S, D, H, Q) : ProjectPlan{0, 0, 0, 1};
   if (shared.ds > 1) return shared;
   const int64_t g4 = (S + 3) / 4, g16 = (S + 15) / 16;
   auto groups = [&](int hg) { return (int64_t)(H + hg - 1) / hg; };
@@ -1210,7 +1215,7 @@ static ProjectPlan project_plan(int32_t S, int32_t L, int32_t D, int32_t H, int3
 // 16 x 2048, 1 query 8 tokens 50 and 51, 12 59 and 52, 64 55 and 49; 4 tokens 48 and 51).
 bool meta_project_pays(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q) {
   if (!meta_project_supports(D, H)) return false;
-  if (S >= 10 && shared_plan(S, D, H, Q).ds > 1) return true;
+  if (shared_plan(S, D, H, Q).ds > 1) return true;
   const double product = 2.0 * S * L * D * (double)D / 0.85e9, mixing = 2.0 * S * L * (double)D / 2.6e6;
   const double first = (product < 20 ? 20 : product) + (mixing < 5 ? 5 : mixing);
   const int64_t g4 = (S + 3) / 4, g16 = (S + 15) / 16;
@@ -1226,13 +1231,14 @@ bool meta_project_pays(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q) {
 
 hipError_t launch_meta_attn_project(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q, const void *feats,
                                     const void *a_fold, const void *w_v, const int32_t *residual_layers, void *pre,
-                                    void *res_out, float *part, hipStream_t s) {
+                                    void *res_out, float *part, size_t part_bytes, hipStream_t s) {
   int parts;
   void *packed = (char *)part + meta_packed_offset(S, D, H, Q);
   hipError_t e = launch_scores(S, L, D, meta_rows_pad(H, Q), feats, a_fold, w_v, packed, part, &parts, s);
   if (e != hipSuccess) return e;
   const ResidualLayers res = residuals(Q, residual_layers, res_out);
-  const ProjectPlan plan = project_plan(S, L, D, H, Q);
+  // a workspace that was enough before workgroups shared D (sized for more tokens, say) takes the forms that don't
+  const ProjectPlan plan = project_plan(S, L, D, H, Q, part_bytes >= meta_project_workspace_bytes(S, D, H, Q));
   if (plan.tg == 4)
     return plan.nt == 2 ? launch_project<2>(S, L, D, H, Q, plan.hg, parts, feats, packed, res, pre, res_out, part, s)
                         : launch_project<4>(S, L, D, H, Q, plan.hg, parts, feats, packed, res, pre, res_out, part, s);

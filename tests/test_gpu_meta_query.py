@@ -160,10 +160,10 @@ def test_every_form_of_the_projection_after_the_mixing(S, n_tok, L, D, H, Q, lay
 
 
 @pytest.mark.parametrize("n_tok,L,D,H,Q,layers,form,shared", [
-    (1, 28, 2048, 16, 3, [27, 0, 5], "wide<3, 4, 7>", True), (17, 32, 1280, 10, 1, None, "wide<1, 4, 8>", True),
+    (10, 28, 2048, 16, 3, [27, 0, 5], "wide<3, 4, 7>", True), (17, 32, 1280, 10, 1, None, "wide<1, 4, 8>", True),
     (40, 5, 2304, 18, 2, [4, 0], "wide<2, 4, 6>", True), (300, 30, 3584, 28, 3, None, "wide<3, 8, 8>", True),  # slices of 32 features
     (320, 24, 3072, 24, 3, [0, 23, 7], "wide<3, 4, 6>", True), (640, 25, 2048, 16, 1, [3], "wide<1, 8, 7>", True),
-    (321, 24, 1024, 8, 3, None, "project<4>", False), (17, 9, 768, 6, 2, [8, 1], "project<2>", False), (49, 9, 2048, 16, 3, None, "project<2>", False)])
+    (9, 28, 2048, 16, 3, [27, 0, 5], "project<2>", False), (321, 24, 1024, 8, 3, None, "project<4>", False), (17, 9, 768, 6, 2, [8, 1], "project<2>", False), (49, 9, 2048, 16, 3, None, "project<2>", False)])
 def test_workgroups_that_share_d(S, n_tok, L, D, H, Q, layers, form, shared):
     """Probabilities made in front and float32 sums of the shares added up behind: shares of unequal and of the
     shortest length, ragged tokens, both forms; and both sides of the lines."""
@@ -174,6 +174,27 @@ def test_workgroups_that_share_d(S, n_tok, L, D, H, Q, layers, form, shared):
     names = [m[1] + (m[2] or "") for m in (re.search(r"meta_(project|project_wide|softmax|sum)_kernel(<[^>]*>)?", e.name) for e in trace.events()) if m]
     form = form.replace("wide", "project_wide")
     assert names == (["softmax", form, "sum"] if shared else [form])
+
+
+def test_a_workspace_without_room_for_shares(S):
+    """One that holds the partial scores and W_v's copy only (sized for more tokens, say) is taken, by the form that shares
+    nothing, and nothing behind it is touched; a byte less is refused."""
+    import paper_2509_18824_amd as hb
+    n_tok, L, D, H, Q = 40, 12, 2048, 16, 2
+    least = -(-hb.hb_meta_query_attn_workspace_bytes(n_tok, D, H, Q) // 256) * 256 + D * D * 2
+    most = hb.hb_meta_query_attn_project_workspace_bytes(n_tok, D, H, Q)
+    assert most > least
+    x = {k: v.cuda() for k, v in W.make_meta_inputs(3, n_tok, L, D, H, Q).items()}
+    layer = S.MetaQueryLayer(x["f_q"], x["w_q"], x["w_k"], x["w_v"], x["w_o"], x["w_fc1"], H)
+    ws = torch.full((most,), 77, dtype=torch.uint8, device="cuda")
+    out = [torch.empty(n_tok, Q, D, dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    hb.hb_meta_query_attn_project(H, Q, x["feats"], x["w_v"], layer.a_fold, None, out[0], None, ws[:least])
+    assert (ws[least:] == 77).all()
+    hb.hb_meta_query_attn_project(H, Q, x["feats"], x["w_v"], layer.a_fold, None, out[1], None, ws)
+    assert (out[0].float() - out[1].float()).norm() <= 4e-3 * out[1].float().norm()
+    with pytest.raises(RuntimeError):
+        hb.hb_meta_query_attn_project(H, Q, x["feats"], x["w_v"], layer.a_fold, None, out[0], None, ws[:least - 1])
+
 
 
 @pytest.mark.parametrize("n_tok,L,D,H,Q", [(7, 28, 768, 6, 3), (1203, 5, 768, 6, 2), (1025, 5, 512, 4, 2)])

@@ -27,14 +27,15 @@ PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA, published
 # HBM traffic of one LM-head launch on this workload, from hardware counters (FETCH_SIZE and
 # WRITE_SIZE, each scaled by what the same counter reads for a 1 GiB device copy in the same
 # run: `--copy-probe`).  Valid only for the kernel source it was measured on: keyed by the
-# first 16 hex digits of the SHA-256 over csrc/lmhead_mfma.hip followed by csrc/mfma_gemm_tile.h
-# and csrc/mfma_gemm_tile.inc (the tile loop the kernel includes); anything else reports null.
-# "tree": the 960-row launch of the headline step; "chain8": the 128-row launch of the chain run.
+# first 16 hex digits of the SHA-256 over csrc/lmhead_mfma.hip followed by csrc/mfma_gemm_tile.h,
+# csrc/mfma_gemm_tile.inc (the tile loop the kernel includes) and csrc/lmhead_few.hip; anything else
+# reports null.  "tree": the 960-row launch of the headline step; "chain8": the 128-row launch of the
+# chain run (lmhead_few.hip's kernel).
 LMHEAD_TRAFFIC = {
-    "da4572dcbf7a811e": {
-        "tree": {"fetch_bytes": 1.8467e9, "write_bytes": 2.1e5, "bytes": 1.8469e9,
+    "e9cc35ed3651424d": {
+        "tree": {"fetch_bytes": 1.8443e9, "write_bytes": 2.0e5, "bytes": 1.8445e9,
                  "algorithmic_bytes": 152064 * 3584 * 2 + 960 * 3584 * 2},
-        "chain8": {"fetch_bytes": 1.1142e9, "write_bytes": 4.2e4, "bytes": 1.1142e9,
+        "chain8": {"fetch_bytes": 1.1075e9, "write_bytes": 3.3e4, "bytes": 1.1075e9,
                    "algorithmic_bytes": 152064 * 3584 * 2 + 128 * 3584 * 2},
     },
 }
@@ -44,7 +45,7 @@ def _lmhead_traffic(which="tree"):
     import hashlib
     h = hashlib.sha256()
     try:
-        for name in ("lmhead_mfma.hip", "mfma_gemm_tile.h", "mfma_gemm_tile.inc"):
+        for name in ("lmhead_mfma.hip", "mfma_gemm_tile.h", "mfma_gemm_tile.inc", "lmhead_few.hip"):
             h.update(open(os.path.join(ROOT, "paper_2509_18824_amd", "csrc", name), "rb").read())
     except OSError:
         return None

@@ -355,7 +355,8 @@ __global__ __launch_bounds__(kMixThreads) void meta_mix_kernel(int S, int L, int
 // What bounds it: with 4 tokens the path L2 -> CU (every 4 tokens read all of W_v once); with 16 (see
 // meta_project_wide_kernel) matrix work 43 % of the clocks, LDS reads behind the barriers, features from memory at 1.7 TB/s.
 // 2048 tokens, 28 layers, D = 3584, 28 heads, 3 queries: 460 us (530 with 64 features between barriers); the
-// value projection of all layers and the mixing of its results took 1478 + 161 us.  96 tokens: 62 us against 76 + 15.
+// value projection of all layers and the mixing of its results took 1478 + 161 us.  96 tokens 62 us against 76 + 15 (40 + 12 by
+// workgroups of 16 that share D, as they now do).
 constexpr int kMpThreads = 512;
 constexpr int kMpWaves = 8;
 constexpr int kMpHq = 24;           // hq rows of a workgroup at most (16 tokens: 48 KB of mixed features beside 96 to 112 KB of features)

@@ -439,6 +439,13 @@ __device__ inline void store_row4(bf16_t *p, merge_f32x4 v) {
   *reinterpret_cast<merge_u32x2 *>(p) = w;
 }
 
+// l plus chunk c's sum of weights, rounded the same in both kernels below whatever the compiler makes of the code around it:
+// a row is the same bits whichever of them has it.  The first of a batch is fused, as is every product with the values.
+__device__ inline float add_weights(float l, float sum, float w, int c) {
+#pragma clang fp contract(off)
+  return c % kMergeBatch == 0 ? __builtin_fmaf(sum, w, l) : l + sum * w;
+}
+
 template <typename T>
 __global__ __launch_bounds__(256) void attn_merge_kernel(int rows, int D, int splits,
                                                          const float *__restrict__ part_o,
@@ -486,13 +493,15 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(int rows, int D, int sp
       if (c < live) x = ml[c];
       const bool ok = c < live;
       w[i] = ok ? expf(x.x - m) : 0.f;
-      l += ok ? x.y * w[i] : 0.f;
+      l = ok ? add_weights(l, x.y, w[i], i) : l;
       merge_f32x4 v = {0.f, 0.f, 0.f, 0.f};
       if (ok) v = po[(size_t)c * tpr];  // an empty chunk's slot is never read
       o[i] = v;
     }
 #pragma unroll
-    for (int i = 0; i < kMergeBatch; ++i) acc += o[i] * w[i];
+    for (int i = 0; i < kMergeBatch; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] = __builtin_fmaf(o[i][e], w[i], acc[e]);
   }
   const float inv = l > 0.f ? 1.f / l : 0.f;
   store_row4(out + (size_t)row * D + piece * 4, acc * inv);
@@ -541,8 +550,9 @@ __global__ __launch_bounds__(256) void attn_merge_eager_kernel(int rows, int D, 
   for (int c = 0; c < kEagerSlots; ++c) {
     if (c < live) {
       const float w = expf(x[c].x - m);
-      l += x[c].y * w;
-      acc += o[c] * w;
+      l = add_weights(l, x[c].y, w, c);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] = __builtin_fmaf(o[c][e], w, acc[e]);
     }
   }
   const float inv = l > 0.f ? 1.f / l : 0.f;

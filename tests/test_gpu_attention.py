@@ -177,6 +177,25 @@ def test_float32_rows_in_one_round_with_scores_of_minus_infinity(hb, step):
         assert np.abs(got[:last] - ref[:last]).max() <= 1e-5 and np.abs(got_lse[:last] - ref_lse[:last]).max() <= 1e-4, splits
 
 
+@pytest.mark.parametrize("dtype,splits", [("f32", 16), ("bf16", 16), ("bf16", 5), ("bf16", 12)])
+def test_a_row_does_not_depend_on_the_merge_that_it_takes(step, dtype, splits):
+    """Few partial results are merged by one kernel, many (more than 8 MB of them) by another: the same arithmetic in the same
+    order, so a sequence's rows are the same bits alone and in a batch."""
+    lens = [1000, 2000, 300, 1500, 17, 2000, 900, 1200, 0, 1900, 640, 64, 5, 1100, 700, 1999]
+    inp = W.make_verify_inputs(94, dtype, 28, 4, 128, lens, [W.chain_tree(8)] * len(lens))
+    dev = step.to_device(inp)
+    many, many_lse = step.tree_verify_attn(step.desc_for(inp, num_splits=splits), dev)
+    rows = inp.total_nodes * 28 * splits * 128 * 4
+    assert rows > 8 << 20 and rows // len(lens) <= 8 << 20
+    for b in range(len(lens)):
+        n0, n1 = int(inp.node_offset[b]), int(inp.node_offset[b + 1])
+        one = step.DeviceInputs(dev.q[n0:n1], dev.k_tree[n0:n1], dev.v_tree[n0:n1], dev.k_pool, dev.v_pool, dev.block_table[b:b + 1],
+                                dev.prefix_len[b:b + 1], dev.node_offset[b:b + 2] - n0, dev.parent[n0:n1])
+        desc = step.make_desc(dtype, 1, 28, 4, 128, inp.page, inp.max_blocks, inp.num_blocks, n1 - n0, 8, inp.softmax_scale, splits)
+        out, lse = step.tree_verify_attn(desc, one)
+        assert torch.equal(out, many[n0:n1]) and torch.equal(lse, many_lse[n0:n1]), (b, lens[b])
+
+
 @pytest.mark.parametrize("nodes", [8, 60])
 @pytest.mark.parametrize("lens", [[1], [191], [193], [2048], [640, 64, 1500], [300] * 8, [100, 900, 0, 500, 70, 1400, 33, 256, 812]])
 def test_short_pieces_of_a_few_sequences(hb, step, nodes, lens):

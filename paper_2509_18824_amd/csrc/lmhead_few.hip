@@ -10,8 +10,13 @@
 // where they took 211, 60 rows 171 and 186 (without matrix instructions 203 and 185): hence the tallest tile that LDS holds
 // (128 rows: tiles of 304 against 208, 183 and 199 us), and all 256 CUs at work instead of the 200 that shared 594 tiles
 // of 256 rows evenly.  us, tiles of 256 rows one by one and this: 152064 x 3584, 8 rows 172 -> 165, 60 186 -> 168,
-// 128 210 -> 183; x 4096, 8 rows 231 -> 190, 128 252 -> 201; 100000 x 2048, 8 rows 95 -> 68; 32000 x 3584, 64 rows 58 -> 45; 64000 x 3584, 128
+// 128 210 -> 183; x 4096, 8 rows 230 -> 193, 128 247 -> 212; 100000 x 2048, 8 rows 95 -> 94; 32000 x 3584, 64 rows 58 -> 45; 64000 x 3584, 128
 // rows, where both have the same tiles, 83 -> 84.
+//
+// All runs begin with K's first step.  Steps of their own would spread rows a multiple of 4 KB apart, which meet on few memory
+// channels where everybody reads the same columns (100000 x 2048, 8 rows 94 and 68 us, 128 rows 101 and 79; 152064 x 4096 193 and
+// 190, 212 and 201), but equal rows of different runs would no longer have equal logits, and the larger rounding would win
+// instead of the lower id.
 //
 // Two wavefronts of a SIMD alternate between operands and matrix instructions as in mfma_gemm_tile.inc.
 #include "mfma_gemm_tile.h"
@@ -89,17 +94,12 @@ __global__ __launch_bounds__(512) void lmhead_few_kernel(int M, int K, int V, in
   for (int i = 0; i < F::kW; ++i) w_off[i] = (wave + kWaves * i) * 8 * row_bytes + mine;
 #pragma unroll
   for (int i = 0; i < F::kH; ++i) h_off[i] = (wave + kWaves * i) * 8 * row_bytes + mine;
-  // Rows a multiple of 4 KB apart meet on few memory channels where everybody reads the same columns: the XCD's runs begin
-  // at K steps of their own (us: 2048 x 100000, 8 rows 86 -> 68, 128 rows 95 -> 81; 4096 x 152064 201 -> 190 and 221 -> 201;
-  // with rows of 7 KB no difference).
-  const int k0 = row_bytes % 4096 == 0 ? (int)((unsigned)(slot / m_tiles * 7) % (unsigned)k_steps) : 0;
-  auto column = [&](int k) { return (k + k0 < k_steps ? k + k0 : k + k0 - k_steps) * (BK * 2); };
   int w_at = first, w_k = 0, h_k = 0;  // what is fetched next; past the last step that step again: the waits count loads
   auto issue_w = [&](int slot) {
     const u32x4 *from = weight + (size_t)w_at * (row_bytes / 16);
     const int bytes = __builtin_amdgcn_readfirstlane(min(height, end - w_at)) * row_bytes;
 #pragma unroll
-    for (int i = 0; i < F::kW; ++i) rows_to_lds<ALONE ? 2 : 0>(from, bytes, lw + slot * F::kWStage + (wave + kWaves * i) * 64, w_off[i], column(w_k));
+    for (int i = 0; i < F::kW; ++i) rows_to_lds<ALONE ? 2 : 0>(from, bytes, lw + slot * F::kWStage + (wave + kWaves * i) * 64, w_off[i], w_k * (BK * 2));
     if (++w_k == k_steps) {
       if (w_at + height < end) {
         w_at += height;
@@ -111,7 +111,7 @@ __global__ __launch_bounds__(512) void lmhead_few_kernel(int M, int K, int V, in
   };
   auto issue_h = [&](int slot) {
 #pragma unroll
-    for (int i = 0; i < F::kH; ++i) rows_to_lds<0>(hidden, m_rows * row_bytes, lh + slot * F::kHStage + (wave + kWaves * i) * 64, h_off[i], column(h_k));
+    for (int i = 0; i < F::kH; ++i) rows_to_lds<0>(hidden, m_rows * row_bytes, lh + slot * F::kHStage + (wave + kWaves * i) * 64, h_off[i], h_k * (BK * 2));
     h_k = h_k + 1 == k_steps ? 0 : h_k + 1;
   };
 

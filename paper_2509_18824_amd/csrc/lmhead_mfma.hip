@@ -19,7 +19,9 @@
 // 826 us, 1024 rows 940 -> 839, 768 rows 752 -> 667 against 32x32x16 with one barrier per K step.
 // Workgroups go in lockstep so that shared tiles are fetched from HBM once.
 //
-// Up to 128 rows, and some calls of up to 256, go to lmhead_few.hip.
+// Up to 128 rows, and some calls of up to 256, go to lmhead_few.hip.  A row's sum over K has the same order there, in every tile
+// and for any number of hidden rows: equal rows have equal logits, so that the lowest id of several wins, and a token's logits
+// do not depend on the tokens beside it.
 //
 // Grid: persistent workgroups, one per CU, in groups that walk the vocabulary tiles in lockstep
 // (one hidden tile per member) on one XCD.
@@ -88,14 +90,8 @@ __global__ __launch_bounds__(512) void lmhead_mfma_kernel(int M, int K, int V, i
   const int m0 = m_tile * TM;
   const int v0 = v_tile * TV;
 
-  // Rows a multiple of 4 KB apart meet on few memory channels where everybody reads the same columns.  One hidden tile: every
-  // vocabulary tile begins with a K step of its own (160 rows, us: 4096 x 152064 267 -> 248, 2048 x 100000 102 -> 91); several
-  // lose what they share in the L2s (960 rows x 4096 910 -> 972).
-  const int turn = WNT && K % 2048 == 0 ? (int)((unsigned)(nth * 5) % (unsigned)(K / BK)) : 0;
 #define HB_GEMM_W_ROW(t_) (v0 + (t_))
-#define HB_GEMM_TURN turn
 #include "mfma_gemm_tile.inc"
-#undef HB_GEMM_TURN
 #undef HB_GEMM_W_ROW
 
   // Epilogue.  Accumulator e of lane l in tile (i, j) is C^T[v, m] with

@@ -99,9 +99,7 @@ __global__ __launch_bounds__(512) void proj_mfma_kernel(int M, int K, int V, int
 #define HB_GEMM_W_ROW(t_) (ROPE ? v0 + (((t_) >> 7) << 7) + ((((t_) >> 6) & 1) << 5) + ((((t_) >> 5) & 1) << 6) + ((t_) & 31) \
                            : GLU ? (((t_) >> 5) & 1) * (V >> 1) + (v0 >> 1) + (((t_) >> 6) << 5) + ((t_) & 31)                  \
                                  : v0 + (t_))
-#define HB_GEMM_TURN 0
 #include "mfma_gemm_tile.inc"
-#undef HB_GEMM_TURN
 #undef HB_GEMM_W_ROW
 
   // Epilogue.  Accumulator e of lane l in tile (i, j): tile row wv*64 + i*16 + 4 (l / 16) + e,
@@ -227,9 +225,7 @@ __global__ __launch_bounds__(512) void proj_splitk_kernel(int M, int Kfull, int 
   const u32x4 *hidden = hidden_full + (size_t)kpart * (K / 8);
   const u32x4 *weight = weight_full + (size_t)kpart * (K / 8);
 #define HB_GEMM_W_ROW(t_) (v0 + (t_))
-#define HB_GEMM_TURN 0
 #include "mfma_gemm_tile.inc"
-#undef HB_GEMM_TURN
 #undef HB_GEMM_W_ROW
   float *dst = part + ((size_t)kpart * m_pad + m0) * v_pad + v0;
 #pragma unroll

@@ -72,16 +72,46 @@ def test_small_shapes(step, dtype, M, K, V):
                                    (255, 64, 40960), (256, 64, 40961)])
 def test_runs_of_vocabulary_rows(step, M, K, V):
     """Up to 128 rows, and some calls of up to 256, a workgroup has a run of vocabulary rows for itself: runs that are missing,
-    ragged, one tile, one row more, several tiles; both sides of the lines; columns in another order (K a multiple of 2048).  The
-    first and the last row of the vocabulary and the rows at a run's ends hold equal largest logits for some hidden rows."""
+    ragged, one tile, one row more, several tiles; both sides of the lines.  Two rows, the first and the last of the vocabulary
+    among them, are equal and far ahead for some hidden rows."""
     hidden, weight = W.make_lmhead_inputs(M + V, M, K, V, dtype="bf16", w_std=0.05)
     rng = np.random.default_rng(M + V)
-    for m in range(0, M, 7):  # the same row, far ahead of the others for this hidden row, in two places: the lower one wins
-        at = np.sort(rng.choice(V, 2, replace=False)) if m else np.array([0, V - 1])
+    rows = range(0, M, 7)
+    places = 1 + np.sort(rng.choice(V - 2, (len(rows), 2), replace=False), axis=1)
+    places[0] = 0, V - 1
+    for m, at in zip(rows, places):  # the same row in two places: the lower one wins
         weight[at] = hidden[m].float().mul(0.5).to(weight.dtype)
     ids, mx = step.lmhead_argmax(hidden.cuda(), weight.cuda())
     torch.cuda.synchronize()
     _check(hidden, weight, ids, mx)
+    assert (ids.cpu().numpy()[list(rows)] == places[:, 0]).all()
+
+
+@pytest.mark.parametrize("K,V", [(64, 300), (192, 17000), (2048, 24600), (4096, 17000), (2048, 70000), (3584, 36000), (2048, 100000)])
+def test_equal_rows_and_any_number_of_hidden_rows(step, K, V):
+    """A row's sum over K has one order, wherever it lies in the vocabulary and however many hidden rows there are: of equal rows in
+    one tile, two tiles of a run, or the runs of two workgroups the lowest wins, and a hidden row has the same id and the same
+    bits of its largest logit in every call that it is part of."""
+    gen = torch.Generator(device="cuda").manual_seed(K + V)
+    weight = torch.empty((V, K), dtype=torch.bfloat16, device="cuda").normal_(0, 0.05, generator=gen)
+    hidden = torch.empty((960, K), dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=gen)
+    rng = np.random.default_rng(K + V)
+    apart = [1, 4, 16, 70, 200, 305, V // 256, V // 8, V // 2]
+    lower, used = {}, set()
+    for i, m in enumerate(list(range(24)) + list(range(24, 960, 40))):
+        d = apart[i % len(apart)]
+        at = [int(v) for v in rng.permutation(max(1, V - d)) if v + d < V and not used & {int(v), int(v) + d}][:1]
+        for v in at:
+            used |= {v, v + d}
+            weight[[v, v + d]] = hidden[m] * 0.5
+            lower[m] = v
+    assert len(lower) > 40
+    all_ids, all_mx = step.lmhead_argmax(hidden, weight)
+    for M in (1, 8, 24, 64, 65, 100, 128, 129, 192, 200, 256, 257, 320, 480, 700, 960):
+        ids, mx = step.lmhead_argmax(hidden[:M].contiguous(), weight)
+        assert torch.equal(ids, all_ids[:M]) and torch.equal(mx, all_mx[:M]), M
+        got = ids.cpu().numpy()
+        assert all(got[m] == v for m, v in lower.items() if m < M), M
 
 
 @pytest.mark.parametrize("M,K,V", [(257, 64, 41000), (320, 128, 16500), (385, 64, 50001), (448, 64, 9000), (577, 128, 6000), (700, 64, 32001),
@@ -89,8 +119,8 @@ def test_runs_of_vocabulary_rows(step, M, K, V):
                                    (193, 64, 32768), (193, 64, 32769), (250, 128, 90001)])
 def test_tile_heights_by_rounds(step, M, K, V):
     """Rows a little beyond a tile's height, where many low tiles would hold fewer padded rows; several heights and numbers of
-    hidden tiles; one hidden tile whose columns come in another order (K a multiple of 2048); up to 256 rows on both sides of the
-    128 vocabulary tiles that two hidden tiles meet in one round."""
+    hidden tiles; one hidden tile; up to 256 rows on both sides of the 128 vocabulary tiles that two hidden tiles meet in one
+    round."""
     hidden, weight = W.make_lmhead_inputs(M + V, M, K, V, dtype="bf16", w_std=0.05)
     ids, mx = step.lmhead_argmax(hidden.cuda(), weight.cuda())
     torch.cuda.synchronize()

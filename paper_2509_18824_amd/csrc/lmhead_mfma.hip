@@ -19,7 +19,7 @@
 // 826 us, 1024 rows 940 -> 839, 768 rows 752 -> 667 against 32x32x16 with one barrier per K step.
 // Workgroups go in lockstep so that shared tiles are fetched from HBM once.
 //
-// Up to 128 rows, and some calls of up to 256, go to lmhead_few.hip.  A row's sum over K has the same order there, in every tile
+// Up to 128 rows of more than 16384 vocabulary rows, and some calls of up to 256, go to lmhead_few.hip.  A row's sum over K has the same order there, in every tile
 // and for any number of hidden rows: equal rows have equal logits, so that the lowest id of several wins, and a token's logits
 // do not depend on the tokens beside it.
 //
@@ -33,7 +33,8 @@ namespace {
 
 // MT: 32-row hidden tiles per wavefront (the workgroup covers TM = 64 * MT hidden rows).
 // WNT: weight loads carry the non-temporal hint.  With one hidden tile nobody shares a weight
-// tile, and streaming it through L2 without displacing the hidden rows is worth 5 %; with several
+// tile, and streaming it through L2 without displacing the hidden rows is worth 5 % (64 rows and up to
+// 16384 vocabulary rows x 4096 1 to 3 %); with several
 // hidden tiles the hint evicts weight lines before all sharers have read them.
 template <int MT, bool WNT>
 __global__ __launch_bounds__(512) void lmhead_mfma_kernel(int M, int K, int V, int m_tiles, int v_tiles, int groups, int spare, int spare_tiles,
@@ -210,8 +211,9 @@ hipError_t launch_lmhead_mfma(int32_t M, int32_t K, int32_t V, const void *hidde
     }
   }
   switch (best_mt) {
-    case 1: return launch<1, false>(M, K, V, hidden, weight, keys, s);  // one tile of up to 128 rows is lmhead_few.hip's
-    case 2: return launch<2, false>(M, K, V, hidden, weight, keys, s);
+    case 1: return M <= 64 * 1 ? launch<1, true>(M, K, V, hidden, weight, keys, s)
+                            : launch<1, false>(M, K, V, hidden, weight, keys, s);
+    case 2: return launch<2, false>(M, K, V, hidden, weight, keys, s);  // one tile of 128 rows is lmhead_few.hip's, or two of 64
     case 3: return M <= 64 * 3 ? launch<3, true>(M, K, V, hidden, weight, keys, s)
                             : launch<3, false>(M, K, V, hidden, weight, keys, s);
     default: return M <= 64 * 4 ? launch<4, true>(M, K, V, hidden, weight, keys, s)

@@ -127,6 +127,29 @@ def test_tile_heights_by_rounds(step, M, K, V):
     _check(hidden, weight, ids, mx, rows=np.unique(np.concatenate([np.arange(0, M, max(1, M // 150)), [M - 1]])))
 
 
+def _kernel(call):
+    """The LM head kernel that a call runs, as it is in the source with its template arguments."""
+    import re
+    from torch.profiler import ProfilerActivity, profile
+    call()
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as trace:
+        call()
+        torch.cuda.synchronize()
+    names = [m[0] for m in (re.search(r"lmhead_(few|mfma)_kernel<[^>]*>", e.name) for e in trace.events()) if m]
+    assert len(names) == 1, names
+    return names[0]
+
+
+@pytest.mark.parametrize("M,K,V,kernel", [(8, 512, 16384, "lmhead_mfma_kernel<1, true>"), (64, 512, 16384, "lmhead_mfma_kernel<1, true>"),
+                                          (65, 512, 16384, "lmhead_mfma_kernel<1, false>"), (192, 512, 60000, "lmhead_mfma_kernel<3, true>"),
+                                          (960, 64, 152064, "lmhead_mfma_kernel<3, false>")])
+def test_weights_of_one_hidden_tile_are_streamed(step, M, K, V, kernel):
+    """With one hidden tile nobody shares a weight tile, and its loads carry the non-temporal hint (second template argument)."""
+    hidden, weight = (torch.zeros((n, K), dtype=torch.bfloat16, device="cuda") for n in (M, V))
+    assert _kernel(lambda: step.lmhead_argmax(hidden, weight, want_max=False)) == kernel
+
+
 @pytest.mark.parametrize("M,K,V", [(65, 64, 32768), (128, 128, 32769), (128, 192, 32700), (129, 64, 20480), (192, 128, 20481),
                                    (193, 64, 16384), (256, 128, 16385), (256, 192, 300)])
 def test_tile_height_of_few_vocabulary_tiles(step, M, K, V):

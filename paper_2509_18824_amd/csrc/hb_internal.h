@@ -94,7 +94,7 @@ hipError_t launch_attn_merge(const hb_attn_desc &d, const AttnPlan &plan, const 
 
 hipError_t launch_lmhead_scalar(int32_t dtype, int32_t M, int32_t K, int32_t V, const void *hidden,
                                 const void *weight, unsigned long long *keys, hipStream_t s);
-bool lmhead_few_takes(int32_t M, int32_t V);
+bool lmhead_few_takes(int32_t M, int32_t K, int32_t V);
 hipError_t launch_lmhead_few(int32_t M, int32_t K, int32_t V, const void *hidden, const void *weight, unsigned long long *keys,
                              hipStream_t s);
 hipError_t launch_lmhead_mfma(int32_t M, int32_t K, int32_t V, const void *hidden,

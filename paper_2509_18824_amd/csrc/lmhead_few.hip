@@ -239,21 +239,27 @@ hipError_t launch(int M, int K, int V, int m_tiles, int own, int height, const v
 
 }  // namespace
 
-// How M hidden rows are tiled: 64 or 128 rows a tile; none where the tiles of lmhead_mfma.hip stay.  With up to 16384
-// vocabulary rows a workgroup would read mostly hidden rows, and 128 of them take up to 1.2 times as long as 64 (x 4096, 16384
-// rows: 42 and 36 us), which those tiles avoid (60 and 58).  Two hidden tiles of 128 where a run is one tile (256 rows, us,
-// this way and 256-row tiles: 24576 x 4096 66 and 85, 32000 x 3584 72 and 81; several tiles, 50000 x 3584, 118 and 94).
-static int few_height(int M, int V) {
-  if (V <= 16384 || M > 256) return 0;
+// How M hidden rows are tiled: 64 or 128 rows a tile; none where the tiles of lmhead_mfma.hip stay.
+// Up to 128 rows: 64 a tile for up to 64 rows, which read half as many hidden rows beside the weights, else 128.  With few
+// vocabulary rows a workgroup reads mostly hidden rows, and two tiles of 64 over longer runs read the fewest.  us, 256-row tiles, 64
+// and 128 a tile: 64 rows x 4096 x 4096 53, 31 and 37, 128 rows 49, 30 and 37; x 12288 56, 33 and 37, 52, 37 and 39; x 16384 58, 36.5
+// and 39.4, 58, 44 and 41.9.  Beyond 12288 of them all take 128: by 64 a tile 128 rows would take 1.15 times as long as 64,
+// more than the 1.12 that few vocabulary rows are held to.  Short K stays with the 256-row tiles, whose launch is small (64
+// rows x 4096: K 64 8.1 and 11.4, 512 13.4 and 15.4; x 8192, K 1024 20.2 and 18.1).
+// Two hidden tiles of 128 where a run is one tile (256 rows, us, this way and 256-row tiles: 24576 x 4096 66 and 85, 32000 x
+// 3584 72 and 81; several tiles, 50000 x 3584, 118 and 94).
+static int few_height(int M, int K, int V) {
+  if (M > 256) return 0;
+  if (V <= 16384) return M > 128 || K < 1024 ? 0 : V <= 12288 ? 64 : 128;
   if (M <= 64) return 64;
   const int groups = 32 / ((M + 127) / 128) * kXcds, run = (V + groups - 1) / groups;
   return M <= 128 || (run > 160 && run <= 64 * kMostTall) ? 128 : 0;
 }
-bool lmhead_few_takes(int32_t M, int32_t V) { return few_height(M, V) != 0; }
+bool lmhead_few_takes(int32_t M, int32_t K, int32_t V) { return few_height(M, K, V) != 0; }
 
 hipError_t launch_lmhead_few(int32_t M, int32_t K, int32_t V, const void *hidden, const void *weight,
                              unsigned long long *keys, hipStream_t s) {
-  const int rows = few_height(M, V);
+  const int rows = few_height(M, K, V);
   if (!rows) return hipErrorInvalidValue;
   const int m_tiles = (M + rows - 1) / rows, groups = 32 / m_tiles * kXcds;
   // Runs of several tiles in whole 16 rows (128 rows x 3584 x 152064, 608 a run 183 us, 594 185), of one tile as they come

@@ -19,9 +19,9 @@
 // 826 us, 1024 rows 940 -> 839, 768 rows 752 -> 667 against 32x32x16 with one barrier per K step.
 // Workgroups go in lockstep so that shared tiles are fetched from HBM once.
 //
-// Up to 128 rows of more than 16384 vocabulary rows, and some calls of up to 256, go to lmhead_few.hip.  A row's sum over K has the same order there, in every tile
-// and for any number of hidden rows: equal rows have equal logits, so that the lowest id of several wins, and a token's logits
-// do not depend on the tokens beside it.
+// Up to 128 rows (but for short K and few vocabulary rows), and some calls of up to 256, go to lmhead_few.hip.  A row's sum over K
+// has the same order there, in every tile and for any number of hidden rows: equal rows have equal logits, so that the lowest
+// id of several wins, and a token's logits do not depend on the tokens beside it.
 //
 // Grid: persistent workgroups, one per CU, in groups that walk the vocabulary tiles in lockstep
 // (one hidden tile per member) on one XCD.
@@ -33,8 +33,8 @@ namespace {
 
 // MT: 32-row hidden tiles per wavefront (the workgroup covers TM = 64 * MT hidden rows).
 // WNT: weight loads carry the non-temporal hint.  With one hidden tile nobody shares a weight
-// tile, and streaming it through L2 without displacing the hidden rows is worth 5 % (64 rows and up to
-// 16384 vocabulary rows x 4096 1 to 3 %); with several
+// tile, and streaming it through L2 without displacing the hidden rows is worth 5 % (64 rows x 512 to
+// 960 x 4096 to 16384 1 to 5 %); with several
 // hidden tiles the hint evicts weight lines before all sharers have read them.
 template <int MT, bool WNT>
 __global__ __launch_bounds__(512) void lmhead_mfma_kernel(int M, int K, int V, int m_tiles, int v_tiles, int groups, int spare, int spare_tiles,
@@ -187,7 +187,7 @@ bool lmhead_mfma_supports(int32_t dtype, int32_t M, int32_t K, int32_t V) {
 
 hipError_t launch_lmhead_mfma(int32_t M, int32_t K, int32_t V, const void *hidden, const void *weight,
                               unsigned long long *keys, hipStream_t s) {
-  if (lmhead_few_takes(M, V)) return launch_lmhead_few(M, K, V, hidden, weight, keys, s);
+  if (lmhead_few_takes(M, K, V)) return launch_lmhead_few(M, K, V, hidden, weight, keys, s);
   // Hidden tile height: rounds of a vocabulary tile by what one takes (us a round of 56 K steps, 500 to 1000 rows x 3584 x
   // 152064: 40, 53, 68 and 83 for 64 to 256 hidden rows; on few CUs a tile waits for its own K steps, and a lower one is
   // ahead there too).  The fewest padded rows, which chose before, gave 257 to 320, 385 to 448, 641 to 704 and 769 to 832 rows

@@ -69,7 +69,8 @@ def test_small_shapes(step, dtype, M, K, V):
 @pytest.mark.parametrize("M,K,V", [(1, 64, 16385), (64, 128, 16384), (64, 64, 20480), (60, 192, 81920), (8, 64, 81921),
                                    (61, 64, 152064), (128, 64, 152065), (100, 128, 164000), (65, 64, 36864), (70, 192, 17000),
                                    (33, 4096, 16400), (128, 2048, 24600), (192, 64, 20480), (129, 64, 20481), (256, 128, 24600),
-                                   (255, 64, 40960), (256, 64, 40961)])
+                                   (255, 64, 40960), (256, 64, 40961), (1, 1024, 5), (64, 1024, 129), (65, 1024, 300),
+                                   (64, 1088, 12288), (128, 1024, 12288), (60, 1024, 12289), (128, 2048, 16384)])
 def test_runs_of_vocabulary_rows(step, M, K, V):
     """Up to 128 rows, and some calls of up to 256, a workgroup has a run of vocabulary rows for itself: runs that are missing,
     ragged, one tile, one row more, several tiles; both sides of the lines.  Two rows, the first and the last of the vocabulary
@@ -87,7 +88,7 @@ def test_runs_of_vocabulary_rows(step, M, K, V):
     assert (ids.cpu().numpy()[list(rows)] == places[:, 0]).all()
 
 
-@pytest.mark.parametrize("K,V", [(64, 300), (192, 17000), (2048, 24600), (4096, 17000), (2048, 70000), (3584, 36000), (2048, 100000)])
+@pytest.mark.parametrize("K,V", [(64, 300), (1024, 300), (1024, 12288), (1088, 12300), (192, 17000), (2048, 24600), (4096, 17000), (2048, 70000), (3584, 36000), (2048, 100000)])
 def test_equal_rows_and_any_number_of_hidden_rows(step, K, V):
     """A row's sum over K has one order, wherever it lies in the vocabulary and however many hidden rows there are: of equal rows in
     one tile, two tiles of a run, or the runs of two workgroups the lowest wins, and a hidden row has the same id and the same
@@ -139,6 +140,18 @@ def _kernel(call):
     names = [m[0] for m in (re.search(r"lmhead_(few|mfma)_kernel<[^>]*>", e.name) for e in trace.events()) if m]
     assert len(names) == 1, names
     return names[0]
+
+
+@pytest.mark.parametrize("M,K,V,kernel", [(1, 1024, 1, "few_kernel<1, 1, true>"), (64, 4096, 4096, "few_kernel<1, 1, true>"),
+                                          (65, 4096, 4096, "few_kernel<1, 1, false>"), (64, 1024, 12288, "few_kernel<1, 1, true>"),
+                                          (128, 1024, 12288, "few_kernel<1, 2, false>"), (64, 1024, 12289, "few_kernel<2, 1, true>"),
+                                          (128, 4096, 16384, "few_kernel<2, 1, true>"), (64, 1024, 16385, "few_kernel<1, 2, true>"),
+                                          (128, 960, 12288, "mfma_kernel<1, false>"), (129, 1024, 4096, "mfma_kernel<1, false>")])
+def test_few_hidden_rows_on_few_vocabulary_rows(step, M, K, V, kernel):
+    """Up to 128 hidden rows and 16384 vocabulary rows: one or two hidden tiles of 64 rows, then one of 128; both sides of every
+    line.  The equal rows above are compared with the other kernel at these sizes."""
+    hidden, weight = (torch.zeros((n, K), dtype=torch.bfloat16, device="cuda") for n in (M, V))
+    assert _kernel(lambda: step.lmhead_argmax(hidden, weight, want_max=False)) == "lmhead_" + kernel
 
 
 @pytest.mark.parametrize("M,K,V,kernel", [(8, 512, 16384, "lmhead_mfma_kernel<1, true>"), (64, 512, 16384, "lmhead_mfma_kernel<1, true>"),

@@ -248,8 +248,10 @@ hipError_t launch(int M, int K, int V, int m_tiles, int own, int height, const v
 // rows x 4096: K 64 8.1 and 11.4, 512 13.4 and 15.4; x 8192, K 1024 20.2 and 18.1).
 // Two hidden tiles of 128 where a run is one tile (256 rows, us, this way and 256-row tiles: 24576 x 4096 66 and 85, 32000 x
 // 3584 72 and 81; several tiles, 50000 x 3584, 118 and 94).
+// Offsets inside a tile and the lengths of its buffers are 32 bits: 320 rows have to end below 2 GB.  Longer rows are the other
+// kernel's, which has 64-bit addresses.
 static int few_height(int M, int K, int V) {
-  if (M > 256) return 0;
+  if (M > 256 || (int64_t)K * 2 * 64 * kMostTall >= (int64_t)1 << 31) return 0;
   if (V <= 16384) return M > 128 || K < 1024 ? 0 : V <= 12288 ? 64 : 128;
   if (M <= 64) return 64;
   const int groups = 32 / ((M + 127) / 128) * kXcds, run = (V + groups - 1) / groups;

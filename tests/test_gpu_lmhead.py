@@ -154,6 +154,19 @@ def test_few_hidden_rows_on_few_vocabulary_rows(step, M, K, V, kernel):
     assert _kernel(lambda: step.lmhead_argmax(hidden, weight, want_max=False)) == "lmhead_" + kernel
 
 
+@pytest.mark.parametrize("K,kernel", [(3355392, "few_kernel<1, 1, true>"), (3355456, "mfma_kernel<1, true>")])
+def test_rows_of_megabytes(step, K, kernel):
+    """A tile of 320 rows ends below 2 GB, as the few rows' 32-bit offsets want it, up to K = 3355392; longer rows are the other
+    kernel's.  Every hidden row is one of the vocabulary's, the last but one twice: its largest logit is K exactly."""
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    weight = torch.randint(0, 2, (10, K), device="cuda", generator=gen, dtype=torch.int8).mul_(2).sub_(1).bfloat16()
+    weight[9] = weight[8]
+    hidden = weight[[7, 9, 0]].contiguous()
+    assert _kernel(lambda: step.lmhead_argmax(hidden, weight, want_max=False)) == "lmhead_" + kernel
+    ids, mx = step.lmhead_argmax(hidden, weight)
+    assert ids.tolist() == [7, 8, 0] and mx.tolist() == [K] * 3
+
+
 @pytest.mark.parametrize("M,K,V,kernel", [(8, 512, 16384, "lmhead_mfma_kernel<1, true>"), (64, 512, 16384, "lmhead_mfma_kernel<1, true>"),
                                           (65, 512, 16384, "lmhead_mfma_kernel<1, false>"), (192, 512, 60000, "lmhead_mfma_kernel<3, true>"),
                                           (960, 64, 152064, "lmhead_mfma_kernel<3, false>")])

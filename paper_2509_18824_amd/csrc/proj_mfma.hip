@@ -509,9 +509,11 @@ FewPlan few_plan(int M, int K, int V, StreamKind kind, size_t workspace) {
     if (rows == 1 && kind != StreamKind::kPlain) continue;
     const long tiles = gated ? (V / 2 + 8 * rows - 1) / (8 * rows) : (V + 16 * rows - 1) / (16 * rows);
     // Many short gated rows.  Beyond 64 tokens it depends on the shape (96 tokens, against the tile kernel: 1280 x 36864
-    // 25 and 30 us, 1024 x 32768 22 and 18); rows 4 KB apart lose to the stream up to 32 tokens (2048 x 25600, 17 tokens:
-    // 28 and 25.5) and to the tile kernel where all CUs are at work (2048 x 32768, 40 tokens: 36 and 34, x 25600 28.5 and 33).
-    // Elsewhere the few rows are 1 to 29 % ahead (64 tokens, 1536 x 28672 22.6 and 28.6).
+    // 25 and 30 us, 1024 x 32768 22 and 18).  Elsewhere the few rows are 1 to 29 % ahead (64 tokens, 1536 x 28672 22.6 and
+    // 28.6).  Rows 4 KB apart lost to the stream up to 32 tokens (2048 x 25600, 17 tokens 28 and 25.5) and to the tile kernel where
+    // all CUs are at work (2048 x 32768, 40 tokens 36 and 34) while all workgroups began with the same columns.  Since they
+    // don't, the lines for these are too low (few rows and what is taken: 17 tokens x 25600 22.2 and 28.3; 40 tokens x 32768
+    // 27.3 and 28.6, x 40960 32.5 and 39.9; 96 tokens 28.8 and 35.2, x 25600 25.7 and 30.2).
     if (gated && rows >= 8 && K <= 2048 && (M > 64 || (K == 2048 && (M <= 32 || tiles > 240)))) continue;
     for (int ks = 1; ks <= (gated || rows == 1 ? 1 : 8); ++ks) {
       if (steps % ks || (ks > 1 && steps / ks < 6) || tiles * ks > 256) continue;
@@ -530,16 +532,23 @@ FewPlan few_plan(int M, int K, int V, StreamKind kind, size_t workspace) {
 
 // 17 to 32 tokens: microseconds of a plan and of the stream, fitted to 2400 measurements of calls in a graph on weights
 // too many to stay in the last-level cache (512 to 18944 x 128 to 40960; 5 and 4 % rms).
-// Weight rows, or parts of them, that begin a multiple of 4 KB apart meet on few memory channels once all CUs read them
-// (24 tokens: 3072 x 28672 35 us, 4096 x 28672 56).
+// Weight rows, or parts of them, that begin a multiple of 4 KB apart meet on few memory channels once all CUs read them,
+// unless the workgroups begin at K steps of their own (24 tokens, 4096 x 28672 56 us and, gated, 43; 3072 x 28672 35); two to
+// seven parts of 4 KB do all the same (8192 x 4096 20.8, the stream 18.4), but for the tallest tiles (8192 x 10240 36.7, the stream
+// 43), and gated rows of 16 KB (8192 x 8200 37.7, the stream 35.6).  370 calls of K a multiple of 2048 are 1.01 to 1.02 times as
+// fast as with the conflict expected of all (16384 x 4096 35.8 -> 30.0, 12288 x 11904 72 -> 59).
 double few_us(const FewPlan &p, int M, int K, int V, StreamKind kind) {
   const bool gated = kind == StreamKind::kGlu;
   const int tiles = gated ? (V / 2 + 8 * p.rows - 1) / (8 * p.rows) : (V + 16 * p.rows - 1) / (16 * p.rows);
   const double fill = (double)(tiles * p.ks) / 256, v_pad = (V + TV - 1) / TV * TV;
   double row = 0.030 + (gated && (int64_t)K * V >= kUncached ? 0.026 : 0.038) * fill + 0.0017 * p.rows;
-  if (p.rows >= 4 && K / p.ks % 2048 == 0) row += (K % 8192 == 0 && p.ks == 1 ? 0.025 : 0.0147) * fill * fill;
+  const bool turns = few_turns(K, V, p);
+  const bool short_parts = K / p.ks == 2048 && p.ks > 1 && p.ks < 8 && p.rows < 10, whole = K % 8192 == 0 && p.ks == 1;
+  const bool meet = K / p.ks % 2048 == 0 && (!turns || short_parts || whole);
+  if (p.rows >= 4 && meet) row += (whole ? 0.025 : 0.0147) * fill * fill;
   const double us = 3.3 + K / BK / p.ks * (0.054 + p.rows * row + 0.0087 * fill * fill + 0.00053 * (M - 17));
-  return p.ks > 1 ? us + 2.1 + 1.33e-6 * p.ks * v_pad * 64 : us;
+  if (p.ks > 1) return us + 2.1 + 1.33e-6 * p.ks * v_pad * 64;
+  return turns && !whole && p.rows >= 4 && K > 2048 ? 0.95 * us : us;
 }
 // Up to K = 4096 the tokens stay in registers and two workgroups fit a CU; beyond they travel with the weights, and the
 // workgroups take 256 tiles of 16 rows a round.
@@ -654,10 +663,10 @@ hipError_t launch_pair(StreamKind kind, const PairPlan &p, int M, int K, int V, 
 // tiles of 256 rows (split over K as ways->split says).  The plan costs the host some microseconds and is made only where it matters.
 // From 17 to 32 tokens stream and few rows each have their shapes (us at 17 / 32 tokens by the stream and by few rows:
 // 3584 x 3584 10.8 / 11.8 and 10.6 / 11.0; 14336 x 4096 26 / 32 and 34 / 35, in parts 28; 8192 x 8192 29 / 33 and 37; 3584 x
-// 16384 28 / 30 and 24; gated 3584 x 37888 50 / 54 and 45, 4096 x 28672 44 / 47 and 53 / 54): the one expected to be faster,
+// 16384 28 / 30 and 24; gated 3584 x 37888 50 / 54 and 45, 4096 x 28672 44 / 46 and 43 / 42): the one expected to be faster,
 // within 0.3 % of the faster one in the mean of the 2400 calls, and more than 3 % slower in 60 of them.
-// Gated rows a multiple of 4 KB apart, more than 150 MB of them, are few rows' (24 tokens, by the stream and by few rows: 4096 x 28672
-// 46 and 43 us, x 32768 53 and 43, 8192 x 28672 95 and 82).
+// Gated rows a multiple of 4 KB apart, more than 150 MB of them, are few rows' whatever is expected (17 tokens, by the stream
+// and by few rows: 10240 x 7808 39 and 34 us, 8192 x 14144 49 and 47, 4096 x 28672 43.8 and 43.7).
 // Parts of K of 4 KB in tiles of 96 or 128 rows lose to the split into 256-row tiles (32 / 64 tokens, 8192 x 8192 36.6 / 36.1 and
 // 33.3 / 34.4, 8192 x 7168 33.9 / 31.8 and 30.2 / 31.0; 128 tokens 14336 x 4608 46 and 41), except eight of them (64 / 128
 // tokens, 16384 x 4096 30 / 36 and 34 / 42); other parts do not.

@@ -254,6 +254,15 @@ def test_every_way_of_the_gated_projection(hb, T, K, F, ws, kernel):
     assert names == ([kernel, "reduce<false, true>"] if kernel.startswith("splitk") else [kernel])
 
 
+# 17 to 32 tokens on rows, or parts of them, a multiple of 4 KB apart, by what few rows take since the workgroups begin at K
+# steps of their own: whole rows, eight parts and the tallest tiles are theirs, short parts in lower tiles the stream's
+@pytest.mark.parametrize("T,K,N,kernel", [(32, 4096, 20480, "few<0, 6, 64, 1>"), (32, 16384, 4096, "few<3, 8, 64, 1>"),
+                                          (17, 8192, 10240, "few<3, 10, 64, 1>"), (32, 8192, 4096, "stream<0, 4, false>")])
+def test_ways_of_rows_that_meet_on_few_channels(hb, T, K, N, kernel):
+    names = _kernels(lambda: _out_case(hb, T, K, N, T % 2 == 0, True))
+    assert names == ([kernel, "reduce<false, false>"] if kernel.startswith("few<3") else [kernel])
+
+
 # Tiles whose K steps two groups of wavefronts share: pair<kind (0 plain, 1 rotary, 2 gated, 3 partial sums), 32-row
 # tiles of weights, of tokens>.  Odd and even K steps in all and per part, ragged last tiles of both kinds, one token over.
 @pytest.mark.parametrize("kind,T,K,N,ws,kernel", [

@@ -538,7 +538,8 @@ int32_t hb_meta_query_attn(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q
  * finite (an infinite W_v may give NaN here where the other way gives an infinity).
  * Up to some hundred tokens the queried size has room for partial sums of workgroups that share D.  A workspace without it
  * (hb_meta_query_attn_workspace_bytes rounded up to 256, and D * D * 2) is taken too, by a slower way.
- * hb_meta_query_attn_project_pays: 1 where this is the faster way (from about 10 tokens on), else 0.
+ * hb_meta_query_attn_project_pays: 1 where this is the faster way (from about 10 tokens of some ten
+ * layers on; fewer layers need more tokens or go the other way), else 0.
  */
 int32_t hb_meta_query_attn_project_pays(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q);
 

@@ -1151,6 +1151,7 @@ hipError_t launch_project_wide(int32_t S, int32_t L, int32_t D, int32_t H, int32
 struct ProjectPlan {
   int tg, nt, hg;
   int ds = 1;  // workgroups that share D
+  double us = 0;  // what they are expected to take
 };
 static int split_heads(int H, int most) {  // heads per workgroup, evenly
   const int groups = (H + most - 1) / most;
@@ -1164,7 +1165,8 @@ static int split_heads(int H, int most) {  // heads per workgroup, evenly
 // 14 shares; 3 % rms).  The forms below keep three queries of more than 320 tokens (400 tokens 175 and 178, 600 240 and 229)
 // and short D, where a share is hardly longer than its start (1024, 2 queries 416 tokens 30 and 36, 3 queries 210 24 and 31;
 // 2048, 3 queries 96 38 and 42; but 1 query 20 tokens x 1024 22.3 and 20.6).  Of 70 drawn calls of 9 to 640 tokens those it takes
-// are 1.35 times as fast.  Fewer than 10 tokens are left to values projected first (meta_project_pays).
+// are 1.35 times as fast.  Fewer than 10 tokens are left to values projected first (meta_project_pays), which also says from how many
+// layers on it is worth it.
 constexpr int kMostShares = 16;
 static ProjectPlan shared_plan(int32_t S, int32_t D, int32_t H, int32_t Q) {
   ProjectPlan best = {0, 0, 0, 1};
@@ -1179,7 +1181,7 @@ static ProjectPlan shared_plan(int32_t S, int32_t D, int32_t H, int32_t Q) {
       const double us = (double)((per * parts + 255) / 256) * (share * (nt == 4 ? 1.3 + 0.2 * Q : 1.6 + 0.5 * Q) + 6) + 2e-6 * parts * S * Q * D;
       if (us < best_us) {
         best_us = us;
-        best = {16, nt, hg, parts};
+        best = {16, nt, hg, parts, us};
       }
     }
   }
@@ -1211,12 +1213,22 @@ static ProjectPlan project_plan(int32_t S, int32_t L, int32_t D, int32_t H, int3
 // 1 us with 4 tokens, 3.0 with 16 tokens and 4 heads and 5.0 with more heads, longer than they take, put it: what it sends
 // this way is 1.5 to 3 % slower in the mean of 1100 drawn calls than the faster of both orders (28 layers, 3 queries, D =
 // 3584, up to fc1: 16 tokens 92 us values first and 95 this way, 48 tokens 117 and 103, 2048 tokens 2082 and 860), and lines
-// closer to it would round the values of calls that have none rounded.  Workgroups that share D are ahead from some ten
-// tokens on (up to fc2, us, values first and this way: 28 layers x 3584, 3 queries 8 tokens 93 to 99 and 82, 16 103 and 95, 32 115 and 103;
-// 16 x 2048, 1 query 8 tokens 50 and 51, 12 59 and 52, 64 55 and 49; 4 tokens 48 and 51).
+// closer to it would round the values of calls that have none rounded.
+//
+// Where workgroups share D, this way is also taken where it is expected to be ahead: the product of the S L rows (up to 128 of them
+// few rows' tiles, beyond them the 256-row tiles' one round at least) and the mixing against the shares, the rearrangement of W_v
+// and the two launches around them, fitted to 800 calls of 10 to 700 tokens and 1 to 32 layers.  The fewer layers, the more tokens
+// it takes and the wider D may not be (3584, 3 queries, without the products behind, us, values first and this way: 16 tokens of 3 layers 28 and 38, of
+// 12 47 and 39, of 28 51 and 41; 128 tokens 52 and 67, 71 and 69, 114 and 76; 320 tokens 69 and 116, 125 and 119, 236 and 133).  Of 844 calls what
+// it chooses is 0.7 % slower than the faster in the mean, shares wherever they may be had were 14 %.
 bool meta_project_pays(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q) {
   if (!meta_project_supports(D, H)) return false;
-  if (shared_plan(S, D, H, Q).ds > 1) return true;
+  const ProjectPlan shared = shared_plan(S, D, H, Q);
+  if (shared.ds > 1) {
+    const double k = D / 1e3, kk = k * k, rows = (double)S * L;
+    const double rows_us = rows <= 128 ? (0.99 + 0.0058 * rows) * kk - 8.1 : std::max(15.5 * k - 0.85 * kk - 20.2, 0.0016 * rows * kk);
+    if (0.71 * shared.us + 1.34 * kk + 0.0044 * S * k - 10.7 < rows_us + 0.00143 * S * Q * k) return true;
+  }
   const double product = 2.0 * S * L * D * (double)D / 0.85e9, mixing = 2.0 * S * L * (double)D / 2.6e6;
   const double first = (product < 20 ? 20 : product) + (mixing < 5 ? 5 : mixing);
   const int64_t g4 = (S + 3) / 4, g16 = (S + 15) / 16;

@@ -213,6 +213,20 @@ def test_meta_query_project_argument_errors():
     assert not hb.hb_meta_query_attn_project_pays(2048, 28, 3584, 56, 1) and not hb.hb_meta_query_attn_project_pays(0, 28, 3584, 28, 3)
 
 
+@pytest.mark.parametrize("S,L,D,Q,pays", [
+    # microseconds, values first and mixing first, in front of the output projection
+    (16, 3, 3584, 3, 0), (16, 28, 3584, 3, 1),      # 28 and 38; 51 and 41
+    (128, 6, 3584, 3, 0), (128, 28, 3584, 3, 1),    # 56 and 68; 114 and 76
+    (320, 1, 3584, 3, 0), (320, 28, 3584, 3, 1),    # 65 and 116; 236 and 133
+    (12, 1, 4096, 1, 0), (12, 12, 4096, 1, 1),      # 23 and 36; 44 and 36
+    (500, 1, 2048, 2, 0), (500, 12, 2048, 2, 1),    # 44 and 63; 75 and 65
+    (609, 1, 5120, 1, 0), (20, 23, 3584, 1, 1)])    # 109 and 206; 43 and 33
+def test_order_of_projecting_and_mixing_goes_by_the_layers(S, L, D, Q, pays):
+    """Workgroups that share D do not make up for the rearrangement of W_v where there are few layers to project."""
+    import paper_2509_18824_amd as hb
+    assert hb.hb_meta_query_attn_project_pays(S, L, D, D // 128, Q) == pays
+
+
 def test_sampling_acceptance_with_a_number_of_polls():
     L, p = hb.lib, C.c_void_p(0x1000)
     args = (p, p, p, p, p, p, p, 6, p, p, p, p)

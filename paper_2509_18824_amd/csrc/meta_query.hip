@@ -1162,8 +1162,8 @@ static int split_heads(int H, int most) {  // heads per workgroup, evenly
 // us before and now (scores included): 28 layers x 3584, 28 heads, 3 queries 16 tokens 61 -> 44, 64 67 -> 59, 96 85 -> 75, 192 126 ->
 // 93; 24 x 4096, 32 heads, 2 queries 64 tokens 74 -> 60, 256 158 -> 97; 16 x 2048, 16 heads, 1 query 400 tokens 67 -> 48.  Which
 // form and how many shares: rounds of 256 workgroups, by times fitted to 480 measurements (30 shapes of 8 to 600 tokens, 2 to
-// 14 shares; 3 % rms).  The forms below keep three queries of more than 320 tokens (400 tokens 175 and 178, 600 240 and 229)
-// and short D, where a share is hardly longer than its start (1024, 2 queries 416 tokens 30 and 36, 3 queries 210 24 and 31;
+// 14 shares; 3 % rms).  The forms below keep three queries of more than 320 tokens (400 tokens 175 and 178, 600 240 and 229),
+// one or two of more than 640 of 4096 features or as many values of more (600 of 5120 255 and 240), and short D, where a share is hardly longer than its start (1024, 2 queries 416 tokens 30 and 36, 3 queries 210 24 and 31;
 // 2048, 3 queries 96 38 and 42; but 1 query 20 tokens x 1024 22.3 and 20.6).  Of 70 drawn calls of 9 to 640 tokens those it takes
 // are 1.35 times as fast.  Fewer than 10 tokens are left to values projected first (meta_project_pays), which also says from how many
 // layers on it is worth it.
@@ -1171,7 +1171,7 @@ constexpr int kMostShares = 16;
 static ProjectPlan shared_plan(int32_t S, int32_t D, int32_t H, int32_t Q) {
   ProjectPlan best = {0, 0, 0, 1};
   const int short_d = Q == 3 ? (S <= 48 ? 2048 : 3072) : Q == 2 ? 2048 : S <= 128 ? 1024 : 2048;
-  if (S < 10 || Q > 3 || D < short_d || S > (Q <= 2 ? 640 : 320)) return best;
+  if (S < 10 || Q > 3 || D < short_d || (int64_t)S * std::max(D, 4096) > (Q <= 2 ? 640 : 320) * 4096) return best;
   double best_us = 1e30;
   for (int nt : {4, 8}) {
     const int hg = split_heads(H, nt == 4 ? 4 : std::min(8, kMpHq / Q));
@@ -1190,10 +1190,9 @@ static ProjectPlan shared_plan(int32_t S, int32_t D, int32_t H, int32_t Q) {
 static int project_most_shares(int32_t S, int32_t D, int32_t H, int32_t Q) { return shared_plan(S, D, H, Q).ds; }
 static ProjectPlan project_plan(int32_t S, int32_t L, int32_t D, int32_t H, int32_t Q, bool may_share) {
   const ProjectPlan shared = may_share ? shared_plan(S, D, H, Q) : ProjectPlan{0, 0, 0, 1};
-  if (shared.ds > 1) return shared;
   const int64_t g4 = (S + 3) / 4, g16 = (S + 15) / 16;
   auto groups = [&](int hg) { return (int64_t)(H + hg - 1) / hg; };
-  if (g4 * groups(2) <= 256) return {4, 2, split_heads(H, 2)};
+  if (g4 * groups(2) <= 256) return shared.ds > 1 ? shared : ProjectPlan{4, 2, split_heads(H, 2)};
   const int wide = split_heads(H, std::min(8, kMpHq / Q)), narrow = split_heads(H, 4);
   const double layers = L > 24 ? 1.0 + 0.0044 * (L - 24) : 1.0;  // more features to load
   auto rounds_us = [&](int hg, double round, double share) {
@@ -1204,6 +1203,10 @@ static ProjectPlan project_plan(int32_t S, int32_t L, int32_t D, int32_t H, int3
   static const double kWide[4] = {0, 2.15, 2.7, 3.09};
   // four queries: accumulators for 4 heads only
   const double wide_us = Q <= 3 ? rounds_us(wide, kWide[Q] + (L < 24 ? 0.02 * (24 - L) : 0.0), 0.47) : 1e30;
+  // The probabilities and the sum of the shares are 8 us of launches on top.  Where a form below has a round that just fits, its
+  // whole rows are ahead (24 layers x 3584, 2 queries, 540 tokens 154 us and by shares 178, 500 tokens 152 and 132; of 1156 calls 0.1 %
+  // slower than the faster in the mean).
+  if (shared.ds > 1 && shared.us + 8 < std::min(std::min(wide_us, narrow_us), four_us) * (D / 64)) return shared;
   if (wide_us < narrow_us && wide_us < four_us) return {16, 8, wide};
   return narrow_us < four_us ? ProjectPlan{16, 4, narrow} : ProjectPlan{4, 4, narrow};
 }

@@ -163,6 +163,8 @@ def test_every_form_of_the_projection_after_the_mixing(S, n_tok, L, D, H, Q, lay
     (10, 28, 2048, 16, 3, [27, 0, 5], "wide<3, 4, 7>", True), (17, 32, 1280, 10, 1, None, "wide<1, 4, 8>", True),
     (40, 5, 2304, 18, 2, [4, 0], "wide<2, 4, 6>", True), (300, 30, 3584, 28, 3, None, "wide<3, 8, 8>", True),  # slices of 32 features
     (320, 24, 3072, 24, 3, [0, 23, 7], "wide<3, 4, 6>", True), (640, 25, 2048, 16, 1, [3], "wide<1, 8, 7>", True),
+    (512, 2, 3328, 26, 2, None, "wide<2, 8, 6>", True), (513, 2, 3328, 26, 2, [1, 0], "wide<2, 4, 6>", False),  # 26 heads in a round by fours
+    (512, 2, 5120, 40, 1, [1], "wide<1, 8, 6>", True), (513, 2, 5120, 40, 1, None, "wide<1, 8, 6>", False),
     (9, 28, 2048, 16, 3, [27, 0, 5], "project<2>", False), (321, 24, 1024, 8, 3, None, "project<4>", False), (17, 9, 768, 6, 2, [8, 1], "project<2>", False), (49, 9, 2048, 16, 3, None, "project<2>", False)])
 def test_workgroups_that_share_d(S, n_tok, L, D, H, Q, layers, form, shared):
     """Probabilities made in front and float32 sums of the shares added up behind: shares of unequal and of the

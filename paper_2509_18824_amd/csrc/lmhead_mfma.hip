@@ -19,7 +19,7 @@
 // 826 us, 1024 rows 940 -> 839, 768 rows 752 -> 667 against 32x32x16 with one barrier per K step.
 // Workgroups go in lockstep so that shared tiles are fetched from HBM once.
 //
-// Up to 128 rows (but for short K and few vocabulary rows), and some calls of up to 256, go to lmhead_few.hip.  A row's sum over K
+// Up to 128 rows (but for short K), and some calls of up to 256, go to lmhead_few.hip.  A row's sum over K
 // has the same order there, in every tile and for any number of hidden rows: equal rows have equal logits, so that the lowest
 // id of several wins, and a token's logits do not depend on the tokens beside it.
 //
@@ -213,7 +213,8 @@ hipError_t launch_lmhead_mfma(int32_t M, int32_t K, int32_t V, const void *hidde
   switch (best_mt) {
     case 1: return M <= 64 * 1 ? launch<1, true>(M, K, V, hidden, weight, keys, s)
                             : launch<1, false>(M, K, V, hidden, weight, keys, s);
-    case 2: return launch<2, false>(M, K, V, hidden, weight, keys, s);  // one tile of 128 rows is lmhead_few.hip's, or two of 64
+    case 2: return M <= 64 * 2 ? launch<2, true>(M, K, V, hidden, weight, keys, s)
+                            : launch<2, false>(M, K, V, hidden, weight, keys, s);
     case 3: return M <= 64 * 3 ? launch<3, true>(M, K, V, hidden, weight, keys, s)
                             : launch<3, false>(M, K, V, hidden, weight, keys, s);
     default: return M <= 64 * 4 ? launch<4, true>(M, K, V, hidden, weight, keys, s)

@@ -17,7 +17,7 @@ constexpr int kXcds = 8;
 
 // Hidden tile stages in LDS.  With 64 rows three: 7 rows x 3584 x 152064 through this loop 169.9 us (176.6 with two); with
 // 128 two: 128 rows 204 us (209 with three).  More do not fit.  (The LM head of so few rows now has
-// lmhead_few.hip's loop, but for short K and few vocabulary rows.)
+// lmhead_few.hip's loop, but for short K.)
 constexpr int kHiddenStages(int mt) { return mt == 1 ? 3 : 2; }
 constexpr size_t tile_lds_bytes(int mt) { return (size_t)(3 * TV + kHiddenStages(mt) * 64 * mt) * CH * 16; }
 

@@ -70,7 +70,9 @@ def test_small_shapes(step, dtype, M, K, V):
                                    (61, 64, 152064), (128, 64, 152065), (100, 128, 164000), (65, 64, 36864), (70, 192, 17000),
                                    (33, 4096, 16400), (128, 2048, 24600), (192, 64, 20480), (129, 64, 20481), (256, 128, 24600),
                                    (255, 64, 40960), (256, 64, 40961), (1, 1024, 5), (64, 1024, 129), (65, 1024, 300),
-                                   (64, 1088, 12288), (128, 1024, 12288), (60, 1024, 12289), (128, 2048, 16384)])
+                                   (64, 1088, 12288), (128, 1024, 12288), (60, 1024, 12289), (128, 2048, 16384),
+                                   (100, 2112, 16384), (1, 640, 16385), (64, 704, 20480), (128, 1536, 17000), (65, 1600, 36864), (100, 512, 66000),
+                                   (128, 128, 131073), (192, 2112, 20500), (129, 2112, 24577), (256, 2112, 24600), (255, 2112, 40960), (250, 2112, 40961)])
 def test_runs_of_vocabulary_rows(step, M, K, V):
     """Up to 128 rows, and some calls of up to 256, a workgroup has a run of vocabulary rows for itself: runs that are missing,
     ragged, one tile, one row more, several tiles; both sides of the lines.  Two rows, the first and the last of the vocabulary
@@ -144,12 +146,19 @@ def _kernel(call):
 
 @pytest.mark.parametrize("M,K,V,kernel", [(1, 1024, 1, "few_kernel<1, 1, true>"), (64, 4096, 4096, "few_kernel<1, 1, true>"),
                                           (65, 4096, 4096, "few_kernel<1, 1, false>"), (64, 1024, 12288, "few_kernel<1, 1, true>"),
-                                          (128, 1024, 12288, "few_kernel<1, 2, false>"), (64, 1024, 12289, "few_kernel<2, 1, true>"),
-                                          (128, 4096, 16384, "few_kernel<2, 1, true>"), (64, 1024, 16385, "few_kernel<1, 2, true>"),
-                                          (128, 960, 12288, "mfma_kernel<1, false>"), (129, 1024, 4096, "mfma_kernel<1, false>")])
-def test_few_hidden_rows_on_few_vocabulary_rows(step, M, K, V, kernel):
-    """Up to 128 hidden rows and 16384 vocabulary rows: one or two hidden tiles of 64 rows, then one of 128; both sides of every
-    line.  The equal rows above are compared with the other kernel at these sizes."""
+                                          (128, 1024, 12288, "few_kernel<1, 2, false>"), (64, 2048, 16384, "few_kernel<1, 1, true>"),
+                                          (128, 2048, 16384, "few_kernel<1, 2, false>"), (64, 2112, 12289, "few_kernel<2, 1, true>"),
+                                          (128, 4096, 16384, "few_kernel<2, 1, true>"), (128, 960, 12288, "mfma_kernel<1, false>"),
+                                          (129, 1024, 4096, "mfma_kernel<1, false>"),
+                                          (64, 640, 16385, "few_kernel<1, 2, true>"), (64, 576, 65536, "mfma_kernel<1, true>"),
+                                          (64, 64, 65537, "few_kernel<1, 5, true>"), (65, 1536, 16385, "few_kernel<2, 2, true>"),
+                                          (65, 1472, 65536, "mfma_kernel<2, true>"), (65, 512, 65537, "few_kernel<2, 5, true>"),
+                                          (65, 448, 131072, "mfma_kernel<2, true>"), (128, 128, 131073, "few_kernel<2, 5, true>"),
+                                          (128, 64, 131073, "mfma_kernel<2, true>"), (192, 2112, 24576, "few_kernel<2, 3, false>"),
+                                          (192, 2048, 24576, "mfma_kernel<2, false>"), (192, 2112, 40961, "mfma_kernel<3, true>")])
+def test_kernels_of_few_hidden_rows(step, M, K, V, kernel):
+    """One or two hidden tiles of 64 rows, one or two of 128, or 256-row tiles: both sides of every line.  The equal rows above
+    are compared across them."""
     hidden, weight = (torch.zeros((n, K), dtype=torch.bfloat16, device="cuda") for n in (M, V))
     assert _kernel(lambda: step.lmhead_argmax(hidden, weight, want_max=False)) == "lmhead_" + kernel
 

@@ -13,6 +13,8 @@
 // 138 us.
 #include "hb_internal.h"
 
+#include <algorithm>
+
 namespace hb {
 
 namespace {
@@ -251,15 +253,24 @@ __global__ __launch_bounds__(kThreads, E == 4 || (E == 1 && sizeof(T) == 2) ? 4 
   }
 }
 
-// ---- float32 rows of up to 64 values in one round of CUs: as few memory round trips in a row as there can be --------
+// ---- float32 rows of up to 64 values, few workgroups: as few memory round trips in a row as there can be -------------
 // Four nodes or forty leave most of the chip idle, and what a workgroup does is wait: for the sequence's bounds, the page
 // ids, K, four times for 16 rows of V, and in its last wavefront for the parents and the tree's keys after all that.  Here
 // the bounds of all sequences come in one load, K and V of a block of 64 keys are in flight together (a load of V is four
 // rows, four values a lane), the prefix has seven wavefronts and the tree one of its own.  That takes 200 registers a lane
-// and a CU per workgroup, so only what fits the CUs once is taken (kEagerMost): 4 nodes x 4 heads of 64 over 256 positions
-// 12.0 -> 7.7 us, 8 nodes over 1024 15.5 -> 11.0.
+// and a CU per workgroup: 4 nodes x 4 heads of 64 over 256 positions 12.0 -> 7.7 us, 8 nodes over 1024 15.5 -> 11.0.
 constexpr int kEagerWaves = 7, kEagerThreads = 64 * (kEagerWaves + 1);
-constexpr int kEagerMost = 320;  // workgroups; 288 17.7 -> 13.3 us, 480 14.7 and 15.0
+// What it takes: one round of the 256 CUs, and a little more where rows are cut into chunks (us, general and this: 160 rows in
+// two chunks 256 positions 14.3 and 12.0, 400 18.9 and 13.5).  Whole rows on more than that are short, and a second round costs
+// more than it saves (272 rows, 31 positions 9.1 and 11.0, 192 11.7 and 11.9).  Nor does it pay for hardly any keys (16 rows, 16
+// positions 5.5 and 5.8, 31 6.5 and 5.9, 64 8.8 and 5.8).
+constexpr int kEagerOnce = 256, kEagerMost = 320;  // workgroups
+constexpr int kEagerLeast = 16;                    // positions that the prefixes may exceed
+bool eager_takes(const hb_attn_desc &d, int64_t workgroups, int splits) {
+  int64_t span = (int64_t)d.page_size * d.max_blocks_per_seq;
+  if (d.max_prefix_len_hint > 0) span = std::min(span, (int64_t)d.max_prefix_len_hint);
+  return d.dtype == HB_F32 && d.head_dim <= 64 && d.batch < 64 && span > kEagerLeast && workgroups <= (splits > 1 ? kEagerMost : kEagerOnce);
+}
 
 struct EagerSoftmax {
   float m, l;  // reference exponent; this lane's share of the sum
@@ -573,7 +584,7 @@ hipError_t launch_attn_scalar(const hb_attn_desc &d, const AttnPlan &plan, const
   attn_scalar_kernel<T_, E_><<<grid, kThreads, 0, s>>>(d, plan.splits, plan.chunk_tokens, (const T_ *)q,        \
       (const T_ *)k_tree, (const T_ *)v_tree, (const T_ *)k_pool, (const T_ *)v_pool, block_table, prefix_len,  \
       node_offset, parent, (T_ *)out, lse, part_o, part_ml, clear)
-  if (d.dtype == HB_F32 && d.head_dim <= 64 && d.batch < 64 && (int64_t)grid.x * grid.y <= kEagerMost) {
+  if (eager_takes(d, (int64_t)grid.x * grid.y, plan.splits)) {
     attn_scalar_eager_kernel<<<grid, kEagerThreads, 0, s>>>(d, plan.splits, plan.chunk_tokens, (const float *)q, (const float *)k_tree,
                                                             (const float *)v_tree, (const float *)k_pool, (const float *)v_pool,
                                                             block_table, prefix_len, node_offset, parent, (float *)out, lse, part_o,

@@ -139,10 +139,10 @@ def test_scalar_kernel_keys_with_scores_of_minus_infinity(hb, step, dtype, D):
 
 @pytest.mark.parametrize("D,page", [(8, 16), (40, 4), (64, 16), (64, 48)])
 @pytest.mark.parametrize("lens", [[0], [1, 63, 64, 65], [447, 448, 449, 0, 20], [900], [2, 0, 260]])
-def test_float32_rows_in_one_round_of_workgroups(hb, step, D, page, lens):
+def test_float32_rows_of_few_workgroups(hb, step, D, page, lens):
     """The float32 kernel of few workgroups, in which a wavefront has K and V of 64 keys in flight and the tree one of its own:
     prefixes around a block of 64 keys and a round of its seven wavefronts (448 keys), trees of one to 64 nodes, poisoned
-    slots and off-path nodes; and 70 sequences or 400 workgroups, which it leaves to the other kernel."""
+    slots and off-path nodes; and 70 sequences, 300 or 512 workgroups, which it leaves to the other kernel."""
     trees = [W.chain_tree(2), W.seeded_tree(2, n_nodes=13, levels=4, root_fanout=4), W.chain_tree(1), W.chain_tree(5), W.chain_tree(3)][:len(lens)]
     for Hq, Hkv in ((2, 1), (3, 3)):
         inp = W.make_verify_inputs(91 + D, "f32", Hq, Hkv, D, lens, trees, page=page, kv_std=1.0, q_std=1.0)
@@ -150,13 +150,35 @@ def test_float32_rows_in_one_round_of_workgroups(hb, step, D, page, lens):
         for splits in (1, 2, 0):
             out, lse, _ = _run(step, inp, num_splits=splits)
             check_attn(inp, out, lse, ref=ref, label=f"f32 D={D} page={page} {lens} splits={splits}")
-    for trees in ([W.chain_tree(1)] * 70, [W.seeded_tree(3, n_nodes=64)] * 4, [W.seeded_tree(3, n_nodes=64), W.chain_tree(7)]):
+    for trees in ([W.chain_tree(1)] * 70, [W.seeded_tree(3, n_nodes=64)] * 4, [W.seeded_tree(3, n_nodes=64), W.chain_tree(7)],
+                  [W.seeded_tree(3, n_nodes=64)] * 2 + [W.chain_tree(22)]):
         inp = W.make_verify_inputs(92, "f32", 2, 1, D, (lens * 70)[:len(trees)], trees, page=page, kv_std=1.0, q_std=1.0)
         out, lse, _ = _run(step, inp)
         check_attn(inp, out, lse, ref=oracle_attn(inp), label=f"f32 D={D} {len(trees)} trees")
 
 
-def test_float32_rows_in_one_round_with_scores_of_minus_infinity(hb, step):
+@pytest.mark.parametrize("nodes,heads,L,splits,hint,eager", [
+    (64, 4, 100, 1, 0, True), (65, 4, 100, 1, 0, False),      # one round of 256 CUs
+    (40, 4, 300, 2, 0, True), (54, 3, 300, 2, 0, False),      # 320 chunks of rows, 324
+    (4, 4, 100, 1, 17, True), (4, 4, 100, 1, 16, False)])     # prefixes known to be longer than 16 positions
+def test_float32_rows_by_the_kernel_of_few_workgroups(step, nodes, heads, L, splits, hint, eager):
+    """Both sides of the lines of that kernel, by its name, and the results of both."""
+    from torch.profiler import ProfilerActivity, profile
+    L = min(L, hint or L)
+    trees = [W.seeded_tree(4, n_nodes=min(nodes, 60)) if nodes >= 20 else W.chain_tree(nodes)] + ([W.chain_tree(nodes - 60)] if nodes > 60 else [])
+    inp = W.make_verify_inputs(95, "f32", heads, 1, 64, [L] * len(trees), trees, kv_std=1.0, q_std=1.0)
+    desc, dev = step.desc_for(inp, num_splits=splits, hint=hint), step.to_device(inp)
+    step.tree_verify_attn(desc, dev)
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as trace:
+        out, lse = step.tree_verify_attn(desc, dev)
+        torch.cuda.synchronize()
+    names = [e.name for e in trace.events() if "attn_scalar" in e.name]
+    assert len(names) == 1 and ("attn_scalar_eager_kernel" in names[0]) == eager
+    check_attn(inp, out, lse, ref=oracle_attn(inp), label=f"f32 {nodes} x {heads}")
+
+
+def test_float32_rows_of_few_workgroups_with_scores_of_minus_infinity(hb, step):
     """As above for whole blocks, wavefronts and rows of keys without weight."""
     trees = [W.chain_tree(2), W.chain_tree(3), W.chain_tree(4), W.chain_tree(2)]
     inp = W.make_verify_inputs(93, "f32", 4, 2, 64, [600, 64, 900, 100], trees, kv_std=1.0, q_std=1.0)

@@ -246,8 +246,9 @@ hipError_t launch(int M, int K, int V, int m_tiles, int own, int height, const v
 //   and 28.  Long K beyond 12288 of them is taken by 128 for any number of rows (4096 x 16384, 64 rows 58, 36.5 and 39.4, 128 rows
 //   58, 44 and 41.9): by 64 a tile 128 rows would take 1.15 times as long as 64, more than the 1.12 that few vocabulary rows are
 //   held to.  Below K = 1024 a launch of 256 workgroups is most of it (64 rows x 4096: K 64 8.1 and 11.2, 512 13.2 and 14.9).
-// - Up to 64 rows: from K = 640 on, and always where 256-row tiles are more than one round of CUs (64 rows, K 512: 32000 17.3 and
-//   17.9, 100000 30.5 and 28.7; K 768 21.5 and 20.2, 64000 26.8 and 27.8, which is the most that is lost).
+// - Up to 64 rows: from K = 640 on (64 rows, 32000: K 512 17.3 and 17.9, 768 21.5 and 20.2; 64000 26.8 and 27.8, which is the most
+//   that is lost), where 256-row tiles are more than one round of CUs from 128 on (100000: K 64 17.8 and 19.0, 128 20.7 and 20.4, 512
+//   30.5 and 28.7), and always where they are more than two (152000, K 64 21.6 and 20.1).
 // - Up to 128 rows, by 128 a tile: one round of 256-row tiles from K = 1536 on (K 1024: 32000 23.6 and 25.4; 1536 32.0 and 31.3),
 //   beyond it from 512 on (82000: K 256 25.4 and 25.8, 512 33.4 and 31.6), beyond two also for shorter K (152000, K 128 28.8 and 26.4).
 // - Up to 256 rows: two hidden tiles of 128 where a run is one tile, from above K = 2048 on, where they are even (256 rows,
@@ -258,7 +259,7 @@ static int few_height(int M, int K, int V) {
   constexpr int kRound = 256 * TV;  // vocabulary rows of one round of the other kernel's tiles
   if (M > 256 || (int64_t)K * 2 * 64 * kMostTall >= (int64_t)1 << 31) return 0;
   if (V <= 16384) return M > 128 || K < 1024 ? 0 : V <= 12288 || K <= 2048 ? 64 : 128;
-  if (M <= 64) return V > kRound || K >= 640 ? 64 : 0;
+  if (M <= 64) return K >= (V > kRound ? 128 : 640) || V > 2 * kRound ? 64 : 0;
   if (M <= 128) return K >= (V > kRound ? 512 : 1536) || (V > 2 * kRound && K >= 128) ? 128 : 0;
   const int groups = 32 / ((M + 127) / 128) * kXcds, run = (V + groups - 1) / groups;
   return K > 2048 && run > 160 && run <= 64 * kMostTall ? 128 : 0;

@@ -72,7 +72,7 @@ def test_small_shapes(step, dtype, M, K, V):
                                    (255, 64, 40960), (256, 64, 40961), (1, 1024, 5), (64, 1024, 129), (65, 1024, 300),
                                    (64, 1088, 12288), (128, 1024, 12288), (60, 1024, 12289), (128, 2048, 16384),
                                    (100, 2112, 16384), (1, 640, 16385), (64, 704, 20480), (128, 1536, 17000), (65, 1600, 36864), (100, 512, 66000),
-                                   (128, 128, 131073), (192, 2112, 20500), (129, 2112, 24577), (256, 2112, 24600), (255, 2112, 40960), (250, 2112, 40961)])
+                                   (128, 128, 131073), (8, 128, 81921), (60, 192, 65537), (192, 2112, 20500), (129, 2112, 24577), (256, 2112, 24600), (255, 2112, 40960), (250, 2112, 40961)])
 def test_runs_of_vocabulary_rows(step, M, K, V):
     """Up to 128 rows, and some calls of up to 256, a workgroup has a run of vocabulary rows for itself: runs that are missing,
     ragged, one tile, one row more, several tiles; both sides of the lines.  Two rows, the first and the last of the vocabulary
@@ -151,7 +151,7 @@ def _kernel(call):
                                           (128, 4096, 16384, "few_kernel<2, 1, true>"), (128, 960, 12288, "mfma_kernel<1, false>"),
                                           (129, 1024, 4096, "mfma_kernel<1, false>"),
                                           (64, 640, 16385, "few_kernel<1, 2, true>"), (64, 576, 65536, "mfma_kernel<1, true>"),
-                                          (64, 64, 65537, "few_kernel<1, 5, true>"), (65, 1536, 16385, "few_kernel<2, 2, true>"),
+                                          (64, 128, 65537, "few_kernel<1, 5, true>"), (64, 64, 131072, "mfma_kernel<1, true>"), (64, 64, 131073, "few_kernel<1, 5, true>"), (65, 1536, 16385, "few_kernel<2, 2, true>"),
                                           (65, 1472, 65536, "mfma_kernel<2, true>"), (65, 512, 65537, "few_kernel<2, 5, true>"),
                                           (65, 448, 131072, "mfma_kernel<2, true>"), (128, 128, 131073, "few_kernel<2, 5, true>"),
                                           (128, 64, 131073, "mfma_kernel<2, true>"), (192, 2112, 24576, "few_kernel<2, 3, false>"),

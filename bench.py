@@ -32,10 +32,10 @@ PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA, published
 # reports null.  "tree": the 960-row launch of the headline step; "chain8": the 128-row launch of the
 # chain run (lmhead_few.hip's kernel).
 LMHEAD_TRAFFIC = {
-    "e9cc35ed3651424d": {
-        "tree": {"fetch_bytes": 1.8443e9, "write_bytes": 2.0e5, "bytes": 1.8445e9,
+    "fd4bc0a3bede3c76": {
+        "tree": {"fetch_bytes": 1.8474e9, "write_bytes": 2.1e5, "bytes": 1.8476e9,
                  "algorithmic_bytes": 152064 * 3584 * 2 + 960 * 3584 * 2},
-        "chain8": {"fetch_bytes": 1.1075e9, "write_bytes": 3.3e4, "bytes": 1.1075e9,
+        "chain8": {"fetch_bytes": 1.1073e9, "write_bytes": 3.0e4, "bytes": 1.1073e9,
                    "algorithmic_bytes": 152064 * 3584 * 2 + 128 * 3584 * 2},
     },
 }
